@@ -1,71 +1,13 @@
 // Merge of the per-chunk partial results, and the page-criticality finalisation.
 #pragma once
+#include <type_traits>
+
 #include "vegas_common.hpp"
 
 namespace vegas {
 
-// One workgroup of D threads (= head dims; 128 or 64) per (query row, KV head, sequence): merges the
-// chunk partials of that row with the usual max/sum bookkeeping (all in log2 units), writes the
-// bf16 output row (Eq. 1).  The per-chunk (max, sum) pairs are
-// fetched by one thread each, so the whole merge costs two dependent memory round trips.
-__global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p) {
-  __shared__ float sw[128];
-  __shared__ float sred[4];
-  const int r = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x;
-  const int wave = tid >> 6;
-  const int T = p.D;                                              // threads of this workgroup = head dims
-  int n = p.lens[b];
-  n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
-  const ColumnSlots cs = column_slots(p.plan, p.slots_total, b, p.Hkv, p.nsplit, p.chunk_tokens);
-  const int ns = (n + cs.chunk - 1) / cs.chunk;
-  const int64_t pbase = cs.off + static_cast<int64_t>(h) * cs.stride_h;
-  const float2* ml = p.part_ml + pbase * p.R + r;                 // stride R between chunks
-  const float* po = p.part_o + (pbase * p.R + r) * T + tid;       // stride R*D between chunks
-  const int64_t ostride = static_cast<int64_t>(p.R) * T;
-
-  const int s_lo = first_live_chunk(n, p.G, p.window, cs.chunk);   // earlier chunks were skipped (local masking)
-  // pass 1: global max over chunks
-  float m = -INFINITY;
-  for (int s = s_lo + tid; s < ns; s += T) m = fmaxf(m, ml[static_cast<int64_t>(s) * p.R].x);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-  if ((tid & 63) == 0) sred[wave] = m;
-  __syncthreads();
-  m = T > 64 ? fmaxf(sred[0], sred[1]) : sred[0];
-  const float m_use = (m == -INFINITY) ? 0.f : m;
-
-  // pass 2: weights of up to D chunks at a time, then the weighted sum of the partial rows
-  float accv = 0.f, L = 0.f;
-  for (int s0 = s_lo; s0 < ns; s0 += T) {
-    const int cnt = min(T, ns - s0);
-    float wl = 0.f;
-    if (tid < cnt) {
-      const float2 v = ml[static_cast<int64_t>(s0 + tid) * p.R];
-      const float w = fast_exp2(v.x - m_use);
-      sw[tid] = w;
-      wl = w * v.y;
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) wl += __shfl_xor(wl, off, 64);
-    if ((tid & 63) == 0) sred[2 + wave] = wl;
-    __syncthreads();
-    L += T > 64 ? sred[2] + sred[3] : sred[2];
-    int s = 0;
-    for (; s + 4 <= cnt; s += 4) {
-      const float x0 = po[(s0 + s) * ostride], x1 = po[(s0 + s + 1) * ostride];
-      const float x2 = po[(s0 + s + 2) * ostride], x3 = po[(s0 + s + 3) * ostride];
-      accv += sw[s] * x0 + sw[s + 1] * x1 + sw[s + 2] * x2 + sw[s + 3] * x3;
-    }
-    for (; s < cnt; ++s) accv += sw[s] * po[(s0 + s) * ostride];
-    __syncthreads();
-  }
-  const float o = (L > 0.f) ? accv / L : 0.f;
-  const int t = r / p.g, j = r % p.g;
-  p.out[((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * T + tid] = float_to_bf16_bits(o);
-}
-
-// The same merge for at most MAXS (<= 64) chunks, in ONE memory round trip: the sequence length, the
+// Merge of the chunk partials of one output row with the usual max/sum bookkeeping (all in log2 units), for at
+// most MAXS (<= 64) chunks, in ONE memory round trip: the sequence length, the
 // chunks' (max, sum) pairs (lane s of every wave fetches chunk s) and the thread's element of every
 // chunk's partial row are all requested before any of them is used.  Chunks at or past the end of the
 // sequence were never written; their slots are loaded all the same (the workspace holds nsplit of them)
@@ -113,6 +55,84 @@ struct RowMerge {
   }
 };
 
+// One workgroup of D threads (= head dims; 128 or 64) per (query row, KV head, sequence): merges the
+// chunk partials of that row and writes the bf16 output row (Eq. 1), for any number of chunks and for balanced
+// chunking, where a sequence has few of its head's slots and how many is known once the plan has been read: they, and
+// no others, are then requested together.  Many chunks take two passes: the (max, sum) pairs, fetched by one thread
+// each, then the partial rows.
+__global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p) {
+  __shared__ float sw[128];
+  __shared__ float sred[4];
+  const int r = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  const int tid = threadIdx.x;
+  const int wave = tid >> 6;
+  const int T = p.D;                                              // threads of this workgroup = head dims
+  int n = p.lens[b];
+  n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
+  const ColumnSlots cs = column_slots(p.plan, p.slots_total, b, p.Hkv, p.nsplit, p.chunk_tokens);
+  const int ns = (n + cs.chunk - 1) / cs.chunk;
+  const int64_t pbase = cs.off + static_cast<int64_t>(h) * cs.stride_h;
+  const float2* ml = p.part_ml + pbase * p.R + r;                 // stride R between chunks
+  const float* po = p.part_o + (pbase * p.R + r) * T + tid;       // stride R*D between chunks
+  const int64_t ostride = static_cast<int64_t>(p.R) * T;
+
+  const int s_lo = first_live_chunk(n, p.G, p.window, cs.chunk);   // earlier chunks were skipped (local masking)
+  const int t = r / p.g, j = r % p.g;
+  uint16_t* const out = p.out + ((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * T + tid;
+  if (ns <= 32) {
+    const int last = min(cs.last, max(ns - 1, 0));
+    auto merge = [&](auto maxs) {
+      RowMerge<decltype(maxs)::value> rm;
+      rm.issue(ml, po - tid, tid, p.R, last, T);
+      return rm.finish(ns, s_lo);
+    };
+    float o;
+    if (ns <= 4) o = merge(std::integral_constant<int, 4>{});
+    else if (ns <= 8) o = merge(std::integral_constant<int, 8>{});
+    else if (ns <= 16) o = merge(std::integral_constant<int, 16>{});
+    else o = merge(std::integral_constant<int, 32>{});
+    *out = float_to_bf16_bits(o);
+    return;
+  }
+  // pass 1: global max over chunks
+  float m = -INFINITY;
+  for (int s = s_lo + tid; s < ns; s += T) m = fmaxf(m, ml[static_cast<int64_t>(s) * p.R].x);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  if ((tid & 63) == 0) sred[wave] = m;
+  __syncthreads();
+  m = T > 64 ? fmaxf(sred[0], sred[1]) : sred[0];
+  const float m_use = (m == -INFINITY) ? 0.f : m;
+
+  // pass 2: weights of up to D chunks at a time, then the weighted sum of the partial rows
+  float accv = 0.f, L = 0.f;
+  for (int s0 = s_lo; s0 < ns; s0 += T) {
+    const int cnt = min(T, ns - s0);
+    float wl = 0.f;
+    if (tid < cnt) {
+      const float2 v = ml[static_cast<int64_t>(s0 + tid) * p.R];
+      const float w = fast_exp2(v.x - m_use);
+      sw[tid] = w;
+      wl = w * v.y;
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) wl += __shfl_xor(wl, off, 64);
+    if ((tid & 63) == 0) sred[2 + wave] = wl;
+    __syncthreads();
+    L += T > 64 ? sred[2] + sred[3] : sred[2];
+    int s = 0;
+    for (; s + 4 <= cnt; s += 4) {
+      const float x0 = po[(s0 + s) * ostride], x1 = po[(s0 + s + 1) * ostride];
+      const float x2 = po[(s0 + s + 2) * ostride], x3 = po[(s0 + s + 3) * ostride];
+      accv += sw[s] * x0 + sw[s + 1] * x1 + sw[s + 2] * x2 + sw[s + 3] * x3;
+    }
+    for (; s < cnt; ++s) accv += sw[s] * po[(s0 + s) * ostride];
+    __syncthreads();
+  }
+  const float o = (L > 0.f) ? accv / L : 0.f;
+  *out = float_to_bf16_bits(o);
+}
+
 template <int MAXS>
 __global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_HOT_PARAMS, const CombineParams pfull) {   // launched with D threads
   CombineParams p = pfull;                   // what the requests depend on arrives preloaded in scalar registers
@@ -138,10 +158,11 @@ __global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_H
 // last paragraph of Sec. 3.3): score[b][j] = inv_norm * sum_h sum_{rows in R} 2^(page_lse - row_lse).
 // A score workgroup derives the global row log-sum-exps itself from the chunks' (max, sum) pairs,
 // so it does not depend on the merge workgroups.  Pages at or beyond the sequence's page count get 0.
-// MAXS > 0: at most MAXS chunks, the merge workgroups take the one-round-trip path; 0: any number.
+// MAXS > 0: at most MAXS chunks, the merge workgroups take the one-round-trip path; 0: any number; kFinPlanned:
+// balanced chunking (any number, usually few).
 // Loads are ordered so that a workgroup's dependent memory round trips are as few as possible: the
 // kernel runs for a handful of microseconds and every trip is a sizeable part of that.
-constexpr int kFinUnits = 6;     // (row, eighth of the chunks) units a score thread loads per batch
+constexpr int kFinPlanned = -1;
 constexpr int kFinPre = 8;       // page log-sum-exps a score thread keeps in registers: 4 * kFinPre rows
 
 // METRIC 1 (the paper's logit metric, token granularity) replaces the page-score role by workgroups
@@ -176,18 +197,22 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
       int n = p.lens[b];
       n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
       const int ns = (n + cs.chunk - 1) / cs.chunk;
-      // The host's bound on the chunks of one sequence may be far above what this sequence has (balanced chunking
-      // bounds it by all the slots of a head): with few chunks the one-round-trip merge is taken after all.
-      if (ns <= 32) {
-        if (ns <= 16) {
-          RowMerge<16> rm;
-          rm.issue(ml, p.part_o + (pbase * p.R + r) * T, t128, p.R, cs.last, T);
-          o = rm.finish(ns);
-        } else {
-          RowMerge<32> rm;
-          rm.issue(ml, p.part_o + (pbase * p.R + r) * T, t128, p.R, cs.last, T);
-          o = rm.finish(ns);
-        }
+      // Balanced chunking (the plan has to be read before anything can be addressed, so the length is known by now):
+      // a sequence has few of its head's slots, and only those are read.  (Reading as many as the host's bound allows,
+      // most of them other sequences', took the whole kernel 30 us on 24 sequences of 1K..20K tokens with 32 rows; this
+      // and the smaller score role below take 13.7.  16 of 8K..64K tokens, 40 rows: 33 -> 24 us.)
+      if (MAXS == kFinPlanned && ns <= 32) {
+        const float* const po = p.part_o + (pbase * p.R + r) * T;
+        const int last = min(cs.last, max(ns - 1, 0));
+        auto merge = [&](auto maxs) {
+          RowMerge<decltype(maxs)::value> rm;
+          rm.issue(ml, po, t128, p.R, last, T);
+          return rm.finish(ns);
+        };
+        if (ns <= 4) o = merge(std::integral_constant<int, 4>{});
+        else if (ns <= 8) o = merge(std::integral_constant<int, 8>{});
+        else if (ns <= 16) o = merge(std::integral_constant<int, 16>{});
+        else o = merge(std::integral_constant<int, 32>{});
         if (valid) {
           const int t = r / p.g, j = r % p.g;
           p.out[((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * T + t128] = float_to_bf16_bits(o);
@@ -273,32 +298,42 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
   float* out_row = p.block_scores + static_cast<int64_t>(b) * p.max_blocks;
   float* sm_row = smf;                        // [HR] global row lse; -inf for rows that do not count
   float* sm_sum = smf + HR;                   // [8][32]
-  float2* sm_pair = reinterpret_cast<float2*>(smf + HR + 256);   // [HR][8] (max, sum) of a row over 1/8 of the chunks
+  float2* sm_pair = reinterpret_cast<float2*>(smf + HR + 256);   // [HR][parts] (max, sum) of a row over one part of the chunks
 
-  // Each (row, eighth of the chunks) pair is one unit of work: a thread requests the (max, sum) pairs of
-  // kFinUnits units (four chunks each) at once and merges them afterwards, so the table costs about one
+  // Each (row, part of the chunks) pair is one unit of work: a thread requests the (max, sum) pairs of
+  // kUnits units (four chunks each) at once and merges them afterwards, so the table costs about one
   // memory round trip per batch instead of one per chunk.  Slots of chunks past the sequence's end are
-  // loaded too (the workspace holds nsplit of them) and dropped at the merge.
+  // loaded too (the workspace holds nsplit of them) and dropped at the merge.  Eight parts, or as few as cover a
+  // smaller number of chunks four at a time (units without chunks would only add rounds).
   // ns_live: chunk slots worth loading.  With balanced chunking the slots of a head are shared by all sequences and
   // one sequence owns few of them, so its count is worked out first (one more round trip, in a kernel that is
   // bound by bytes at such batch sizes); otherwise every slot up to the host's bound is requested at once.
+  // (Six units per batch hold the whole table of one sequence of 32 chunks and 160 rows in flight; a planned
+  // sequence has few chunks, and there it pays to have more workgroups on a CU than its registers would leave room for.)
+  constexpr int kUnits = MAXS == kFinPlanned ? 2 : 6;
   int ns_live = p.nsplit;
-  if (p.plan) {
+  if constexpr (MAXS == kFinPlanned) {
     int n0 = p.lens[b];
     n0 = n0 < 0 ? 0 : (n0 > p.max_tokens ? p.max_tokens : n0);
     ns_live = (n0 + cs.chunk - 1) / cs.chunk;
+    if (jbase * kPage >= n0) {                                     // whole workgroup past the sequence
+      if (tid < 32 && jbase + tid < p.max_blocks) out_row[jbase + tid] = 0.f;
+      return;
+    }
   }
-  float2 v[kFinUnits][4];
+  const int lg = MAXS != kFinPlanned ? 3 : (ns_live <= 4 ? 0 : (ns_live <= 8 ? 1 : (ns_live <= 16 ? 2 : 3)));   // log2 of the parts
+  const int parts = 1 << lg, units = HR << lg;
+  float2 v[kUnits][4];
   auto load_units = [&](int s0, int u0) {
 #pragma unroll
-    for (int a = 0; a < kFinUnits; ++a) {
+    for (int a = 0; a < kUnits; ++a) {
       const int u = u0 + 256 * a;
-      const int i = u < HR * 8 ? (u >> 3) : 0, sg = u & 7;
+      const int i = u < units ? (u >> lg) : 0, sg = u & (parts - 1);
       const int h = i / p.R, r = i % p.R;
       const float2* ml = p.part_ml + (cs.off + static_cast<int64_t>(h) * cs.stride_h) * p.R + r;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int sidx = s0 + sg + 8 * q;
+        const int sidx = s0 + sg + (q << lg);
         v[a][q] = sidx < ns_live ? ml[static_cast<int64_t>(min(sidx, cs.last)) * p.R] : make_float2(-INFINITY, 0.f);
       }
     }
@@ -326,20 +361,20 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
     return;
   }
   bool loaded = true;
-  for (int s0 = 0; s0 < ns; s0 += 32) {
-    for (int u0 = tid; u0 < HR * 8; u0 += kFinUnits * 256) {
+  for (int s0 = 0; s0 < ns; s0 += 4 << lg) {
+    for (int u0 = tid; u0 < units; u0 += kUnits * 256) {
       if (!loaded) load_units(s0, u0);
       loaded = false;
 #pragma unroll
-      for (int a = 0; a < kFinUnits; ++a) {
+      for (int a = 0; a < kUnits; ++a) {
         const int u = u0 + 256 * a;
-        if (u < HR * 8) {
-          const int sg = u & 7;
+        if (u < units) {
+          const int sg = u & (parts - 1);
           float2 cur = (s0 == 0) ? make_float2(-INFINITY, 0.f) : sm_pair[u];
           float m = cur.x;
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            if (s0 + sg + 8 * q >= ns) v[a][q] = make_float2(-INFINITY, 0.f);
+            if (s0 + sg + (q << lg) >= ns) v[a][q] = make_float2(-INFINITY, 0.f);
             m = fmaxf(m, v[a][q].x);
           }
           const float mu = (m == -INFINITY) ? 0.f : m;
@@ -356,12 +391,12 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
     const int src = (i / Rc) * p.R + collected_row(i % Rc, p.collect_rows, p.G, p.g);
     float m = -INFINITY;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) m = fmaxf(m, sm_pair[src * 8 + q].x);
+    for (int q = 0; q < parts; ++q) m = fmaxf(m, sm_pair[(src << lg) + q].x);
     const float m_use = (m == -INFINITY) ? 0.f : m;
     float L = 0.f;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const float2 pr = sm_pair[src * 8 + q];
+    for (int q = 0; q < parts; ++q) {
+      const float2 pr = sm_pair[(src << lg) + q];
       L += fast_exp2(pr.x - m_use) * pr.y;
     }
     sm_row[i] = (L > 0.f) ? m_use + fast_log2(L) : -INFINITY;

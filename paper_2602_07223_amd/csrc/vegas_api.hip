@@ -409,7 +409,9 @@ int launch_combine(const vegas_desc* d, const SplitPlan& pl, const SplitParams& 
   cp.plan = sp.plan;
   cp.slots_total = sp.slots_total;
   const dim3 grid(pl.R, sp.Hkv, d->batch);
-  if (pl.nsplit <= 8)
+  if (pl.balanced)
+    hipLaunchKernelGGL(attn_combine_kernel, grid, dim3(cp.D), 0, st, cp);
+  else if (pl.nsplit <= 8)
     hipLaunchKernelGGL(attn_combine_small_kernel<8>, grid, dim3(cp.D), 0, st, VEGAS_COMBINE_HOT_ARGS(cp), cp);
   else if (pl.nsplit <= 12)
     hipLaunchKernelGGL(attn_combine_small_kernel<12>, grid, dim3(cp.D), 0, st, VEGAS_COMBINE_HOT_ARGS(cp), cp);
@@ -498,6 +500,7 @@ int for_each_lds_kernel(F f) {
   one(verify_finalize_kernel<64, 0>); one(verify_finalize_kernel<0, 0>);
   one(verify_finalize_kernel<16, 1>); one(verify_finalize_kernel<32, 1>);
   one(verify_finalize_kernel<64, 1>); one(verify_finalize_kernel<0, 1>);
+  one(verify_finalize_kernel<kFinPlanned, 0>); one(verify_finalize_kernel<kFinPlanned, 1>);
   one(select_blocks_kernel);
   return rc;
 }
@@ -612,12 +615,14 @@ static int verify_impl(const vegas_desc* desc, const void* q, const void* k_cach
     return VEGAS_OK;
   };
   if (logits) {
-    if (pl.nsplit <= 16) rc = launch_finalize(verify_finalize_kernel<16, 1>);
+    if (pl.balanced) rc = launch_finalize(verify_finalize_kernel<kFinPlanned, 1>);
+    else if (pl.nsplit <= 16) rc = launch_finalize(verify_finalize_kernel<16, 1>);
     else if (pl.nsplit <= 32) rc = launch_finalize(verify_finalize_kernel<32, 1>);
     else if (pl.nsplit <= 64) rc = launch_finalize(verify_finalize_kernel<64, 1>);
     else rc = launch_finalize(verify_finalize_kernel<0, 1>);
   } else {
-    if (pl.nsplit <= 16) rc = launch_finalize(verify_finalize_kernel<16>);
+    if (pl.balanced) rc = launch_finalize(verify_finalize_kernel<kFinPlanned>);
+    else if (pl.nsplit <= 16) rc = launch_finalize(verify_finalize_kernel<16>);
     else if (pl.nsplit <= 32) rc = launch_finalize(verify_finalize_kernel<32>);
     else if (pl.nsplit <= 64) rc = launch_finalize(verify_finalize_kernel<64>);
     else rc = launch_finalize(verify_finalize_kernel<0>);

@@ -1,0 +1,34 @@
+"""Balanced chunking's merge and page scores over every number of chunks the merge distinguishes: a batch in which one
+sequence gets 1, 4, 5, 8, 9, 16, 17, 31 or 57 chunks (the shortest chunk is 128 tokens) and the others one each, with
+and without collection, against the oracle."""
+import pytest
+import torch
+
+from oracle import vegas_oracle as O
+from paper_2602_07223_amd import binding as vb
+from paper_2602_07223_amd import harness, synth
+from tests import parity_util as U
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("Hq", [32, 64], ids=["20_rows", "40_rows"])
+@pytest.mark.parametrize("chunks", [1, 4, 5, 8, 9, 16, 17, 31, 57])
+def test_planned_sequences_with_every_chunk_count(chunks, Hq):
+    lens = [128 * chunks - 3, 16] if chunks < 32 else [128 * chunks - 3] + [16] * 7
+    L = synth.make_random_case(seed=41000 + chunks + Hq, batch=len(lens), num_q_heads=Hq, num_kv_heads=8, num_queries=5,
+                               seq_lens=lens, logit_std=2.0, value_std=1.0, outliers=2, outlier_logit=25.0)
+    print(f"[case] planned merge, {chunks} chunks, Hq={Hq}", flush=True)
+    dl = harness.DeviceLayer.upload(L)
+    ref_out, ref_scores = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens,
+                                             L.softmax_scale, vb.COLLECT_ALL_ROWS)
+    for collect in (vb.COLLECT_ALL_ROWS, vb.COLLECT_NONE):
+        path = harness.VegasPath.for_layer(L, budget_tokens=256, collect_rows=collect)
+        path.workspace.fill_(0xFF)                # NaN partials where nothing was written
+        path.out_verify.fill_(float("nan"))
+        path.block_scores.fill_(float("nan"))
+        path.verify(dl)
+        torch.cuda.synchronize()
+        U.check_out(f"planned.{chunks}.{collect}", path.out_verify, ref_out, U.vmax_visible(L))
+        if collect:
+            U.check_scores(f"planned.{chunks}", path.block_scores, ref_scores)
