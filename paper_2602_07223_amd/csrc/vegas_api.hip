@@ -49,9 +49,30 @@ int device_cu_count() {
   known[dev] = n;
   return n;
 }
-// longest selection a draft call streams with one workgroup per (sequence, KV head): 256 tokens at head dimension 128,
-// 384 at 64 (tiles of half the bytes), each plus the two pages of slack a selection table carries
+// Longest selection a draft call of more than kDraftRows rows per KV head streams with one workgroup per (sequence,
+// KV head): 256 tokens at head dimension 128, 384 at 64 (tiles of half the bytes), each plus the two pages of slack a
+// selection table carries.  (Smaller groups: one_chunk_draft.)
 constexpr int kFinishTokens128 = 288, kFinishTokens64 = 416;
+
+// Draft calls of up to kDraftRows rows per KV head (attn_draft16_kernel): does one workgroup per (sequence, KV head)
+// stream the whole selection and write the output rows itself, or is it cut into chunks that a second launch merges?
+// A single workgroup streams about 60 GB/s (0.27 us per 16-KB tile behind 3.4 us), the merge costs a launch and a
+// round trip through memory.  Draft calls back to back, us, one workgroup per column against chunks + merge, by
+// columns (sequences x KV heads) and selected tokens (head dimension 128 unless noted):
+//   8..64 columns:  544 tokens 7.7 / 10.1 (in a GPU-bound iteration 0.4 less per call), 1056 12.0 / 10.2;
+//                   head dimension 64: 1056 tokens 8.2 / 10.8, 2080 13.3 / 10.2   -> up to 272 KB of K/V per column
+//   96:  1056 12.8 / 13.1, 2080 22.0 / 22.7, 4128 45.5 / 39.2;  128:  544 8.2 / 10.5, 1056 13.2 / 15.6,
+//        2080 23.0 / 24.8, 4128 53.0 / 44.7 (too few workgroups to cover the latency of HBM, and a selection that no
+//        longer sits in the last-level cache); head dimension 64: 2080 14.0 / 18.0, 4128 24.5 / 29.4
+//                                                                                 -> up to 1.06 MB
+//   192:  1056 17.5 / 21.2, 2080 32.5 / 36.4, 4128 75.3 / 83.8;  256:  21.8 / 25.7, 41.1 / 46.8, 94.6 / 117.8;
+//   384:  2080 78.4 / 98.6, 4128 156.7 / 163.2                                    -> any length
+bool one_chunk_draft(int64_t columns, int num_cu, int max_len, int head_dim) {
+  const int64_t bytes = static_cast<int64_t>(max_len) * head_dim * 4;            // K and V of one column's selection
+  if (4 * columns >= 3 * num_cu) return true;
+  if (8 * columns >= 3 * num_cu) return bytes <= 1088 * 1024;
+  return bytes <= 272 * 1024;
+}
 
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -111,19 +132,21 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   // number of tiles; otherwise (and for 3 or 4 blocks) sibling workgroups, one per block, share an XCD's L2.
   pl->pair = may_pair && !sum_block && pl->NB == 2;
   if (pl->pair && d->kv_chunk_tokens != 0 && d->kv_chunk_tokens % (kTile * kPairs) != 0) pl->pair = false;
-  // A draft call over a short selection (may_finish): one workgroup per (sequence, KV head) streams all of it and
-  // writes the output rows itself, so no merge kernel is launched.  Measured at 4K context, five draft calls per
-  // iteration: 256 selected tokens (eight tiles, two per wave) 54.7 us against 59.3 us with three chunks and a merge;
-  // 384 tokens 61.8 against 59.4; 512 tokens 67.2 against 59.8 -- a workgroup takes about 0.35 us per further tile,
-  // with four waves or with eight, so the merge launch is the cheaper price from nine or ten tiles on.  At head
-  // dimension 64 (32K context, 64 query heads): 256 tokens 66.5 against 73.0 us, 384 tokens 71.4 against 73.0,
-  // 512 tokens 75.1 against 73.3.
-  const bool finish = may_finish && d->kv_chunk_tokens == 0 &&
-                      max_len <= (d->head_dim == 64 ? kFinishTokens64 : kFinishTokens128) &&
-                      static_cast<int64_t>(d->batch) * d->num_kv_heads * pl->NB <= num_cu;
+  // A draft call (may_finish) over a selection that one workgroup per (sequence, KV head) streams fast enough: it
+  // writes the output rows itself, so no merge kernel is launched.  Groups of more than kDraftRows heads run the 32-row
+  // kernel, whose workgroups take about 0.35 us per tile; at 4K context, five draft calls per iteration: 256 selected
+  // tokens (eight tiles, two per wave) 54.7 us against 59.3 us with three chunks and a merge; 384 tokens 61.8 against
+  // 59.4; 512 tokens 67.2 against 59.8.  At head dimension 64 (32K context, 64 query heads): 256 tokens 66.5 against
+  // 73.0 us, 384 tokens 71.4 against 73.0, 512 tokens 75.1 against 73.3.
+  const bool own_chunks = may_finish && d->kv_chunk_tokens == 0;
+  const bool short_call = own_chunks && max_len <= (d->head_dim == 64 ? kFinishTokens64 : kFinishTokens128) &&
+                          heads * pl->NB <= num_cu;
+  const bool finish = short_call || (own_chunks && rows_per_head <= kDraftRows &&
+                                     one_chunk_draft(heads, num_cu, max_len, d->head_dim));
   const int unit = kTile * pl->NW;
   int chunk = d->kv_chunk_tokens;
-  if (finish) chunk = (max_len + unit - 1) / unit * unit;
+  const int whole = (max_len + unit - 1) / unit * unit;
+  if (short_call) chunk = whole;
   if (chunk == 0) {
     // Verification: one workgroup per CU when the batch is small (at 32K context 256 equal workgroups
     // beat 512); draft calls are latency-bound and like two small workgroups per CU.  With many
@@ -165,9 +188,12 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   const int64_t per_head = static_cast<int64_t>(d->num_kv_heads) * (pl->pair ? 1 : pl->NB);   // workgroups per slot
   pl->balanced = may_pair && d->kv_chunk_tokens == 0 && d->batch >= 2 && d->batch <= 64 && max_len < (1 << 24) &&
                  per_head <= num_cu;
+  // (A call that one workgroup per column finishes uses no partials; its workspace is sized for the chunked plan all
+  //  the same, so that one_chunk_draft moves neither the sizes callers allocate nor what the built-in scratch takes.)
+  size_t slots = static_cast<size_t>(heads) * ((max_len + chunk - 1) / chunk);   // chunk partials the workspace holds
+  if (finish) chunk = whole;
   pl->chunk = chunk;
   pl->nsplit = (max_len + chunk - 1) / chunk;
-  size_t slots = static_cast<size_t>(heads) * pl->nsplit;       // chunk partials the workspace holds
   if (pl->balanced) {
     int64_t most_chunks;                                        // of one sequence
     if (pl->pair) {

@@ -68,3 +68,19 @@ def test_single_chunk_and_merged_chunks_agree():
     ref = O.draft_attention(L.q_draft[0], L.k_cache, L.v_cache, sel, ssl, L.softmax_scale)
     U.check_out("draft.single_chunk", a, ref, U.vmax_visible(L))
     U.check_out("draft.merged_chunks", b, ref, U.vmax_visible(L))
+
+
+@pytest.mark.parametrize("Hkv,n,D", [(8, 544, 128), (8, 545, 128), (8, 1088, 64), (8, 1089, 64),        # few columns
+                                     (96, 2176, 128), (96, 2177, 128),                                  # 3/8 of the CUs
+                                     (192, 2300, 64), (257, 301, 128)])                                 # 3/4, more than one each
+def test_one_workgroup_per_column_on_both_sides_of_its_rule(Hkv, n, D):
+    """The planner's choice (chunk 0) at the edges of the rule that gives a column to one workgroup, for 256 compute
+    units: against the oracle and against chunks with a merge."""
+    L = synth.make_random_case(seed=5100 + n + Hkv, batch=1, num_q_heads=2 * Hkv, num_kv_heads=Hkv, num_queries=1,
+                               seq_lens=[n], head_dim=D, logit_std=1.5, value_std=1.0)
+    sel, ssl = random_selection(L, PAGE, np.random.default_rng(3), keep_fraction=1.0)
+    print(f"[case] one workgroup per column Hkv={Hkv} n={n} D={D}", flush=True)
+    ref = O.draft_attention(L.q_draft[0], L.k_cache, L.v_cache, sel, ssl, L.softmax_scale)
+    for chunk in (0, 256):
+        U.check_out(f"draft.column.Hkv{Hkv}.n{n}.chunk{chunk}", draft_small_pages(L, PAGE, sel, ssl, chunk=chunk), ref,
+                    U.vmax_visible(L))
