@@ -1,27 +1,36 @@
-// KV-streaming verification kernel for 33..64 query rows per KV head (two 32-row blocks), gfx950.
+// KV-streaming verification kernel for more than 32 query rows per KV head, gfx950: two 32-row blocks per wave.
 //
 // Same arithmetic and the same partial-result layout as attn_split_kernel (Eq. 1 split over the context, page
-// log-sum-exps for Eq. 2 / Eq. 3, or the token sums of the logit metric), but the two row blocks are served from
-// ONE read of K and V.  Sibling workgroups that each load the whole stream (the other way to serve two row blocks)
-// hold the same bytes twice in their registers, so only half of what a CU has in flight is new to the memory
-// system and the stream turns latency-bound.  Here instead:
-//   * a workgroup of 4 waves is two PAIRS; pair p takes the 32-token tiles p, p+2, ... of the chunk;
-//   * within a pair, wave `role` (0 or 1) owns row block `role` AND loads page `role` of every tile (16 tokens:
-//     4 KB of K, 4 KB of V), two tiles ahead, into registers -- so a wave still keeps 16 KB in flight, all of it
-//     bytes nobody else requests, and the non-temporal hint applies (one reader per line);
-//   * both waves drop their page into the pair's K and V tiles in LDS, the workgroup meets at a barrier, and both
-//     read the whole tile from there: K as the A operand of S^T = K Q^T, V as the A operand of O^T += V^T P^T
-//     (8-byte reads in the same token/lane pattern the register path uses), then a second barrier frees the tile.
-// What a step collects (the page log-sum-exps of its four pages for the collected rows, or the token sums of its 64 tokens) meets in a few
-// hundred bytes of LDS and leaves right after the step's closing barrier in ONE store per thread, so a chunk may be
-// arbitrarily long.  That store is unconditional and issued after the step's loads: invalid elements go to a
-// scratch word instead of being branched around, because a store under a run-time branch would make the
-// compiler's load-counter waits assume the worst and stall every step on the loads it has just issued (the
-// counter covers loads and stores in issue order).  A bulk flush of a longer LDS ring every 2048 tokens was
-// measured 15 % slower: the whole GPU drained its loads behind a synchronised burst of stores.
-// Every pair runs the same number of steps (a pair whose last tile lies past the chunk works on a fully masked
-// tile; that only happens in a sequence's last chunk because a full chunk holds an even number of tiles), and
-// every load is unconditional with clamped page ids, so the barriers are uniform and the load counter waits exact.
+// log-sum-exps for Eq. 2 / Eq. 3, or the token sums of the logit metric), but a wave serves 64 query rows from ONE read
+// of K and V.  Two row blocks leave no registers for tiles in flight (128 accumulators), so K and V never pass through
+// registers on their way in: they are loaded straight into LDS.
+//   * A workgroup = 4 waves on one (sequence, KV head, chunk); every wave takes a contiguous quarter of the chunk's
+//     32-token tiles and owns a ring of kPairRing bytes of LDS (2 tiles at head dimension 128, 4 at 64) that only it
+//     fills and reads, so the streaming loop has no barrier and no wave waits for another one.
+//   * K goes into a ring slot as soon as the first contraction has read the slot's old K, V as soon as the second one
+//     has read the old V: 64 to 128 KB per compute unit are in flight all the time.  The load counter returns in
+//     order: "all but the n newest" is an exact wait for a tile's K or V (stores in between only make it stricter).
+//   * A load instruction lands 64 x 16 bytes side by side in LDS, whatever their addresses; the lanes therefore choose
+//     WHICH 16 bytes they fetch so that the reads below are free of bank conflicts: a K row's 16-byte pieces are
+//     exchanged by the token's number (piece c of token t sits at c ^ (t mod 16); at head dimension 64, where two rows
+//     share a bank line, at c ^ (t / 2 mod 8)); V rows stay whole, at head dimension 64 in the order in which the two
+//     halves of a wave read them.
+//   * S^T = K Q^T and O^T += V^T P^T as in attn_split_kernel; each operand read from LDS feeds the MFMAs of both row
+//     blocks.  Page ids come through the scalar path one tile ahead (their wait must not count loads).
+//   * A row's reference maximum is raised only when a tile exceeds it by more than 2^8: the accumulators are rescaled
+//     once or twice per chunk instead of at most tiles (64 rows almost always include one with a new maximum).
+//     Weights are at most 2^8 then; their relative rounding, like that of the fp32 sums, does not depend on the scale.
+//   * What is collected (2 % of the bytes read) must not trickle into the read stream: 47 MB written in 320-byte pieces
+//     beside 2.4 GB read took 421 us instead of 347 in a stand-alone kernel, the same with a writing wave of its own, in
+//     bursts of 5 KB per wave (417), and in bursts at common times too (416: dirty L2 lines are evicted later, into the
+//     reads); bursts at common times that are written THROUGH the L2 took 362.  So a wave parks its tiles' values in
+//     LDS and writes them through when the wall clock enters a new interval, or its part of the LDS is full.  (When a
+//     value leaves depends on the clock; the value does not.)
+// Streaming kernel, 40 rows: 16 x 36864 tokens 488 us with a store per tile, 430 now, 395 without collection (6.1 TB/s);
+// 16 of 8192..65536 tokens 483 -> 445; one sequence of 32768 25.8 -> 20.1 us at head dimension 64, 48 rows at 128 40.2 ->
+// 28.6: against the kernel this one replaced, which passed K and V through the registers of two waves and their LDS
+// tiles between two barriers per 64 tokens.  What bounds it: HBM from 64K tokens on, its head and merge below.
+// Rows beyond 64 go to sibling workgroups of 64 rows each.
 #pragma once
 #include <type_traits>
 
@@ -30,242 +39,391 @@
 
 namespace vegas {
 
-constexpr int kPairWaves = 4;    // two pairs
-constexpr int kPairs = 2;
+constexpr int kPairWaves = 4;
+constexpr int kPairRows = 64;               // query rows (of one KV head) of a workgroup
+constexpr int kPairRing = 32 * 1024;        // bytes of K and V tiles per wave
+constexpr float kPairSlack = 8.0f;          // log2 of how far a logit may exceed its row's reference maximum
 
-template <int COLLECT, int D>
+// 64 lanes x 16 bytes from (base + lane offset) to LDS [lds, lds + 1 KB), for N lane offsets and consecutive kilobytes.
+// Nothing is returned in registers; the load counter counts one per kilobyte.  (Assembly, because the compiler makes every
+// LDS read that follows the builtin wait for all such loads.  M0 has no other use on gfx950 than these instructions.)
+// STREAMING: with the non-temporal hint (16 x 36864 tokens without collection 399 us against 446).
+template <int N, bool STREAMING>
+__device__ __forceinline__ void load_to_lds(uint32_t lds, const unsigned char* base, const uint32_t (&off)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    if constexpr (STREAMING)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                   :: "s"(lds + 1024u * i), "v"(off[i]), "s"(base) : "memory");
+    else
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                   :: "s"(lds + 1024u * i), "v"(off[i]), "s"(base) : "memory");
+  }
+}
+// Waits until at most N of this wave's loads and stores are under way.
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "the counter has six bits");
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
+}
+// Write-through store of 16 bytes (4-byte aligned) to base + off.
+__device__ __forceinline__ void store_through(unsigned char* base, uint32_t off, f32x4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, %2 sc0 sc1\n\ts_nop 1" :: "v"(off), "v"(v), "s"(base) : "memory");
+}
+__device__ __forceinline__ void store_through(unsigned char* base, uint32_t off, float v) {
+  asm volatile("global_store_dword %0, %1, %2 sc0 sc1\n\ts_nop 1" :: "v"(off), "v"(v), "s"(base) : "memory");
+}
+// This wave's LDS reads are done: what follows may land on their source.
+__device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
+// ONE: all rows fit one workgroup, which is then the only reader of its K/V lines (non-temporal loads); otherwise sibling
+// workgroups read them too and want to find them in the L2.
+template <int COLLECT, int D, bool ONE>
 __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPLIT_HOT_PARAMS, const SplitParams pfull) {
   VEGAS_TL_DECL;                             // (profiling builds: per-wave phase stamps, see vegas_common.hpp)
   VEGAS_TL(kTlEntry);
   SplitParams p = pfull;                     // (see attn_split_kernel: the preloaded arguments)
   VEGAS_SPLIT_HOT_ASSIGN(p);
   static_assert(D == 128 || D == 64, "head dimension");
-  // Dynamic LDS: [pair][K tile | V tile][page lse or token sums | merge buffer (aliases everything before)]
-  //              [queries, 64 rows][row maxima][row sums]
+  // Dynamic LDS (pair_lds): [ring of every wave][queries][collected values of every wave][row maxima][row sums]; the
+  // merge buffer aliases everything before the row maxima.
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int NW = kPairWaves, NP = kPairs;
-  constexpr int CH = D / 8;                  // 16-byte chunks of a K/Q row
-  constexpr int TPI = 64 / CH;               // token rows one K load instruction covers
-  constexpr int NKH = kPage / TPI;           // K load instructions per page
+  constexpr int NW = kPairWaves;
+  constexpr int NB = 2;                      // 32-row blocks of a wave
+  constexpr int CH = D / 8;                  // 16-byte pieces of a K/V row
+  constexpr int TPI = 64 / CH;               // token rows of one load instruction
+  constexpr int NP = kPage / TPI;            // load instructions per page (of K, of V)
+  constexpr int NL = 2 * NP;                 // ... per tile
   constexpr int NBLK = D / 32;               // 32-wide blocks of the output's head dimension
+  constexpr int kRow = 2 * D;                // bytes of a K/V row
+  constexpr int kHalfSlot = 32 * kRow;       // bytes of a tile's K (then as many of V)
+  constexpr int NS = kPairRing / (2 * kHalfSlot);   // tiles the ring holds
   constexpr int kRowPitch = row_pitch(D);
   constexpr int kRedPitch = red_pitch(D);
-  constexpr int kTileBytes = 32 * kRowPitch;
   using VReg = typename std::conditional<D == 128, u32x2, uint32_t>::type;   // NBLK head dims of one token
-  unsigned char* qlds = smem + p.lds_q_off;
-  float* sm_m = reinterpret_cast<float*>(qlds + 64 * kRowPitch);
-  float* sm_l = sm_m + NP * 64;
-  float* lse_lds = reinterpret_cast<float*>(smem + NP * 2 * kTileBytes);   // COLLECT 1: [4 pages of the step][R]
-  float* tok_lds = lse_lds;                                                // COLLECT 2: [2][64 tokens of the step]
-
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int pr = wave >> 1, role = wave & 1;
   const int half = lane >> 5;
   const int l32 = lane & 31;
-  // Grid (chunk, KV head, sequence): workgroup ids go round-robin to the XCDs, so with chunks fastest every XCD works
-  // on all KV heads (measured 3.5 % faster for this kernel than one XCD per head; the other streaming kernels, which
-  // are shorter, keep heads fastest).
-  const int h = blockIdx.y;
-  int split = blockIdx.x;
+  unsigned char* const ring = smem + wave * kPairRing;
+  unsigned char* const qlds = smem + NW * kPairRing;
+  float* const sm_m = reinterpret_cast<float*>(smem + p.lds_q_off);             // [wave][64]
+  float* const sm_l = sm_m + NW * kPairRows;
+
+  // Grid: (chunk, KV head, sequence).  Workgroup ids go round-robin to the XCDs, so with chunks fastest every XCD works
+  // on all KV heads.  With several row blocks (KV head, row block + row_blocks * chunk, sequence): siblings share an XCD.
+  const int h = ONE ? blockIdx.y : blockIdx.x;
+  const int rb = ONE ? 0 : static_cast<int>(blockIdx.y) % p.row_blocks;
+  const int slot_j = ONE ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.y) / p.row_blocks;
+  int split = slot_j;
   int b = blockIdx.z;
   int chunk_tokens = p.chunk_tokens;
   int64_t pbase = (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + split;   // this workgroup's partial slot
   if (p.plan) {                              // balanced chunking: slot j of this head -> (sequence, chunk)
-    const int j = split;
     const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2,
-                                          p.chunk_cap_units, p.chunk_unit, j,
+                                          p.chunk_cap_units, p.chunk_unit, slot_j,
                                           ((blockIdx.x | blockIdx.y) == 0 && wave == 0) ? p.plan : nullptr);
     if (bs.b < 0) return;
-    b = bs.b;
-    split = bs.split;
-    chunk_tokens = bs.chunk;
-    pbase = static_cast<int64_t>(h) * p.slots_total + j;
+    b = __builtin_amdgcn_readfirstlane(bs.b);
+    split = __builtin_amdgcn_readfirstlane(bs.split);
+    chunk_tokens = __builtin_amdgcn_readfirstlane(bs.chunk);
+    pbase = static_cast<int64_t>(h) * p.slots_total + slot_j;
   }
-  const int row0 = 32 * role;                // first query row (of this KV head) of this wave's block
-  const int Rl = min(32, p.R - row0);        // valid rows in it (R > 32)
+  const int row0 = kPairRows * rb;           // first query row (of this KV head) of this workgroup
+  const int Rl = max(min(kPairRows, p.R - row0), 0);   // valid rows (none in a block that only carries the sum rows)
 
-  // Page ids of this wave's page of the pair's next 64 tiles, one per lane, read back with readlane.  Requested
-  // before the sequence length is known; indices are clamped to the table row and ids to the pool.
-  const int32_t* table = p.table + static_cast<int64_t>(b) * p.table_stride;
+  // Page ids through the scalar path: entry clamped to the table row, id to the pool.
+  typedef const __attribute__((address_space(4))) int32_t* sptr;
+  const sptr table = (sptr)(p.table + static_cast<int64_t>(b) * p.table_stride);
   const int c0 = split * chunk_tokens;
-  const int tile0 = c0 / kTile;
-  int pagevec = 0;
-  auto load_pagevec = [&](int kbase) {
-    int page = 2 * (tile0 + pr + (kbase + lane) * NP) + role;
-    page = page < p.table_stride ? page : p.table_stride - 1;
-    int64_t ph = table[page];
-    ph = ph < 0 ? 0 : (ph >= p.num_pages ? p.num_pages - 1 : ph);
-    pagevec = static_cast<int>(ph);
+  auto into_pool = [&](int raw) -> int {
+    return static_cast<int>(raw < 0 ? 0 : (static_cast<int64_t>(raw) >= p.num_pages ? p.num_pages - 1 : raw));
   };
-  load_pagevec(0);
 
+  constexpr int QI = kPairRows * CH / (NW * 64);
+  u32x4 qraw[QI];
+  const int qrows = ONE ? p.R + (COLLECT == 2 ? 2 : 0) : kPairRows;      // rows the query tile holds
+  if constexpr (COLLECT != 2) issue_query_loads<D, QI>(qraw, p, b, h, qrows, row0, Rl, tid, NW * 64);
   int n = p.lens[b];
   n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
   if (c0 >= n) return;                       // whole workgroup: nothing to do, no partial is read
   VEGAS_TL(kTlLength);
   const int c1 = min(c0 + chunk_tokens, n);
   const int nblk = (n + kPage - 1) / kPage;
-  const int tile_end = (c1 + kTile - 1) / kTile;
-  // Steps of every pair, rounded up to an even number: the streaming loop below works on two register sets in turn,
-  // and one loop shape (pairs of steps, the last pair without loads) keeps the kernel inside its register budget.  A
-  // chunk that is a multiple of four tiles has an even count by itself; otherwise (the ragged end of a sequence, a
-  // caller's chunk length) the extra step sees a tile past the chunk's end, which is masked out like any other token
-  // the rows may not see.
-  const int T = ((tile_end - tile0 + NP - 1) / NP + 1) & ~1;
+  // A wave's tiles are a contiguous quarter of the chunk's: what it collects is contiguous too.
+  const int chunk_tiles = (c1 - c0 + kTile - 1) / kTile;
+  const int tile_first = c0 / kTile + chunk_tiles * wave / NW;
+  const int ntiles = c0 / kTile + chunk_tiles * (wave + 1) / NW - tile_first;
+  auto page_id = [&](int k, int pg) -> int {           // page pg of this wave's tile k
+    const int page = min(2 * (tile_first + k) + pg, p.table_stride - 1);
+    return table[page];
+  };
 
-  // ---- per-lane constants
+  // ---- query rows -> LDS [rows][CH pieces of 16 B], padded rows (lanes of later rows work on a copy of the last one).
+  // COLLECT == 2: the last row block's rows Rl (high part) and Rl + 1 (low part) carry the sum of the collected rows.
+  // (Before the first tile is requested: the wait for the queries would count its loads.)
+  const bool has_extra = COLLECT == 2 && (ONE || rb == p.row_blocks - 1);
+  if constexpr (COLLECT == 2) load_queries_to_lds<D>(qlds, p, b, h, qrows, row0, Rl, has_extra, tid, NW * 64);
+  else store_queries_to_lds<D, QI>(qlds, qraw, qrows, tid, NW * 64);
+
+  // ---- which 16 bytes of a page this lane fetches with each load instruction
   const int64_t head_off = static_cast<int64_t>(h) * p.head_stride;
-  const int k_tok = lane / CH;               // K load i: token TPI*i + lane/CH of the page ...
-  const int k_chunk = lane % CH;             // ... 16-byte chunk lane%CH
-  unsigned char* kt = smem + pr * (2 * kTileBytes);
-  unsigned char* vt = kt + kTileBytes;
   const uint32_t ts_bytes = static_cast<uint32_t>(p.token_stride) * 2u;
-  const uint32_t k_lane_off = static_cast<uint32_t>(k_tok) * ts_bytes + static_cast<uint32_t>(k_chunk) * 16u;
-  const uint32_t v_lane_off = static_cast<uint32_t>(4 * half) * ts_bytes + static_cast<uint32_t>(l32) * (2u * NBLK);
+  uint32_t koff[NP], voff[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const int row = TPI * i + lane / CH, piece = lane % CH;       // where the 16 bytes land
+    if constexpr (D == 128) {
+      koff[i] = static_cast<uint32_t>(row) * ts_bytes + static_cast<uint32_t>(piece ^ row) * 16u;
+      voff[i] = static_cast<uint32_t>(row) * ts_bytes + static_cast<uint32_t>(piece) * 16u;
+    } else {
+      koff[i] = static_cast<uint32_t>(row) * ts_bytes + static_cast<uint32_t>(piece ^ (row >> 1)) * 16u;
+      const int tok = (row & 8) | ((row >> 1) & 3) | ((row & 1) << 2);   // V row r holds this token of the page
+      voff[i] = static_cast<uint32_t>(tok) * ts_bytes + static_cast<uint32_t>(piece) * 16u;
+    }
+  }
+  typedef const __attribute__((address_space(3))) unsigned char* lptr;
+  const uint32_t ring_lds = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lptr)ring)));
   auto page_base = [&](const uint16_t* cache, int ph) -> const unsigned char* {
     return uniform_ptr(reinterpret_cast<const unsigned char*>(cache + static_cast<int64_t>(ph) * p.page_stride + head_off));
   };
-  // Loads of this wave's page of the pair's tile k: K rows TPI*i + lane/CH; V load jj: token
-  // 8(jj/4) + 4*half + jj%4 of the page, head dims NBLK*l32 .. NBLK*l32 + NBLK-1.
-  auto issue = [&](int k, u32x4 (&kr)[NKH], VReg (&vr)[8]) {
-    if ((k & 63) == 0 && k > 0) load_pagevec(k);
-    const int ph = __builtin_amdgcn_readlane(pagevec, k & 63);
-    const unsigned char* kb = page_base(p.k, ph);
-    const unsigned char* vb = page_base(p.v, ph);
-#pragma unroll
-    for (int i = 0; i < NKH; ++i) kr[i] = gload<u32x4, true>(kb + static_cast<uint32_t>(TPI * i) * ts_bytes, k_lane_off);
-#pragma unroll
-    for (int jj = 0; jj < 8; ++jj)
-      vr[jj] = gload<VReg, true>(vb + static_cast<uint32_t>(8 * (jj >> 2) + (jj & 3)) * ts_bytes, v_lane_off);
+  auto load_k = [&](int slot, int id0, int id1) {
+    load_to_lds<NP, ONE>(ring_lds + static_cast<uint32_t>(slot * 2 * kHalfSlot), page_base(p.k, id0), koff);
+    load_to_lds<NP, ONE>(ring_lds + static_cast<uint32_t>(slot * 2 * kHalfSlot + kHalfSlot / 2), page_base(p.k, id1), koff);
+  };
+  auto load_v = [&](int slot, int id0, int id1) {
+    load_to_lds<NP, ONE>(ring_lds + static_cast<uint32_t>(slot * 2 * kHalfSlot + kHalfSlot), page_base(p.v, id0), voff);
+    load_to_lds<NP, ONE>(ring_lds + static_cast<uint32_t>(slot * 2 * kHalfSlot + kHalfSlot + kHalfSlot / 2), page_base(p.v, id1), voff);
   };
 
-  // ---- the first two tiles' loads go out before anything else (tile 1 may be a masked one: still a valid address)
-  u32x4 kr0[NKH], kr1[NKH];
-  VReg vr0[8], vr1[8];
-  issue(0, kr0, vr0);
-  issue(1, kr1, vr1);
+  // ---- the ring's first tiles
+#pragma unroll
+  for (int k = 0; k < NS; ++k) {
+    if (k < ntiles) {
+      const int id0 = into_pool(page_id(k, 0)), id1 = into_pool(page_id(k, 1));
+      load_k(k, id0, id1);
+      load_v(k, id0, id1);
+    }
+  }
+  int next0 = page_id(NS, 0), next1 = page_id(NS, 1);             // ids of the tile that enters the ring next
   VEGAS_TL(kTlLoadsIssued);
 
-  // ---- query rows -> LDS [64 rows][CH chunks of 16 B], padded rows; rows past R are zero.
-  // COLLECT == 2: rows R (high part) and R + 1 (low part) carry the sum of the collected query rows.
-  load_queries_to_lds<D>(qlds, p, b, h, 64, 0, p.R, COLLECT == 2, tid, NW * 64);
-  VEGAS_TL(kTlQueries);                      // (queries written; the first step's barrier publishes them)
-  const int xr = p.R - row0;                 // COLLECT 2: column of the high-part sum row inside block 1
-  const bool has_extra = COLLECT == 2 && role == 1;
-  // last visible token of this lane's row: the causal bound, and nothing past this workgroup's chunk
-  const int limit = min(n - p.G + ((l32 < Rl) ? (row0 + l32) / p.g : 0), c1 - 1);
-  // (the first barrier of the first step also publishes the queries)
-
-  // ---- collection: the element of a step's collected values this thread stores (elements repeat when there are
-  //      fewer than threads: the same value goes to the same address twice), and where step 0's copy goes
-  // (Threads beyond the step's element count have nothing to store: their store goes to the workgroup's scratch word
-  //  too.  Repeating elements instead -- the same value to the same address from a second thread -- costs real write
-  //  requests: a step's values then leave in 256 stores instead of 160, or of 64.)
-  int col_elem = 0, col_page = 0;
-  float* const trash = p.trash + ((blockIdx.x + 8 * blockIdx.y) & 63);        // one of 64 words: workgroups do not all share one
-  float* col_dst = trash;
-  bool col_active = false;
+  // last visible token of this lane's row of each block: the causal bound, and nothing past this workgroup's chunk
+  int limit[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int r = 32 * nb + l32;
+    limit[nb] = min(n - p.G + ((r < Rl) ? (row0 + r) / p.g : 0), c1 - 1);
+  }
+  // ---- collection: index of this lane's rows among the collected ones (COLLECT 1), columns of the sum rows (COLLECT 2)
+  int ci[NB];
   if constexpr (COLLECT == 1) {
-    col_active = tid < 4 * p.Rc;
-    const int e = tid % (4 * p.Rc);            // [page of the step][collected row]
-    col_page = e / p.Rc;
-    col_elem = col_page * p.R + collected_row(e % p.Rc, p.collect_rows, p.G, p.g);   // where it sits in LDS
-    col_dst = p.page_lse + ((static_cast<int64_t>(b) * p.Hkv + h) * p.lse_pages + c0 / kPage) * p.Rc + e;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int r = row0 + 32 * nb + l32;
+      const bool all = p.collect_rows == 1 || p.G <= 2;
+      const int c = (all || r < p.g) ? r : (r >= (p.G - 1) * p.g ? r - (p.G - 2) * p.g : -1);
+      ci[nb] = (32 * nb + l32 < Rl) ? c : -1;
+    }
+  }
+  // Collected rows of this row block: ci runs over [ci_lo, ci_hi) (one contiguous range of a page's Rc values).
+  int ci_lo = 0, nci = 0;
+  int tile_vals = 0;                         // values a tile parks
+  float* park = nullptr;                     // this wave's parked values, park_tiles tiles of them
+  unsigned char* col_dst = nullptr;          // where the first of them belongs (wave-uniform)
+  if constexpr (COLLECT == 1) {
+    auto before = [&](int r) {                                    // collected rows below row r
+      return (p.collect_rows == 1 || p.G <= 2) ? r : min(r, p.g) + max(r - (p.G - 1) * p.g, 0);
+    };
+    ci_lo = before(row0);
+    nci = before(row0 + Rl) - ci_lo;
+    tile_vals = 2 * nci;
+    col_dst = reinterpret_cast<unsigned char*>(
+        p.page_lse + ((static_cast<int64_t>(b) * p.Hkv + h) * p.lse_pages + 2 * tile_first) * p.Rc);
   }
   if constexpr (COLLECT == 2) {
-    col_active = tid < kTile * NP;
-    col_elem = tid % (kTile * NP);             // token of the step
-    col_dst = p.page_lse + (static_cast<int64_t>(b) * p.Hkv + h) * p.lse_pages + c0 + col_elem;
+    tile_vals = 2 * kTile;                   // high and low parts
+    col_dst = reinterpret_cast<unsigned char*>(
+        p.page_lse + (static_cast<int64_t>(b) * p.Hkv + h) * p.lse_pages + kTile * tile_first);
   }
+  if constexpr (COLLECT != 0)
+    park = reinterpret_cast<float*>(qlds + qrows * kRowPitch) + wave * p.park_tiles * (COLLECT == 2 ? 2 * kTile : 2 * min(p.Rc, kPairRows));
+  int parked = 0, flushed = 0;               // tiles parked now; tiles that left before them
+  uint32_t epoch = 0;
+  auto clock_epoch = [&]() -> uint32_t {     // number of the wall-clock interval (100 MHz ticks, the same on every unit)
+    return __umulhi(static_cast<uint32_t>(__builtin_amdgcn_s_memrealtime()), p.epoch_mul);
+  };
+  if constexpr (COLLECT != 0) epoch = clock_epoch();
+  // The parked values leave.
+  auto flush = [&]() {
+    wave_lds_fence();
+    if constexpr (COLLECT == 1) {
+      const int pages = min(2 * parked, min(nblk, (c1 + kPage - 1) / kPage) - 2 * (tile_first + flushed));
+      unsigned char* dst = uniform_ptr_mut(col_dst + static_cast<int64_t>(flushed) * (8 * p.Rc));
+      if (nci == p.Rc) {                     // one contiguous run
+        const int vals = pages * nci;
+        for (int e = 4 * lane; e < vals; e += 256) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(park + e);
+          if (e + 4 <= vals) {
+            store_through(dst, 4u * e, v);
+          } else {
+            for (int i = 0; e + i < vals; ++i) store_through(dst, 4u * (e + i), v[i]);
+          }
+        }
+      } else {                               // a row block among several: a run per page
+        for (int pg = 0; pg < pages; ++pg)
+          if (lane < nci) store_through(dst, 4u * (pg * p.Rc + ci_lo + lane), park[pg * nci + lane]);
+      }
+    }
+    if constexpr (COLLECT == 2) {
+      if (has_extra) {
+        unsigned char* dst = uniform_ptr_mut(col_dst + static_cast<int64_t>(flushed) * (4 * kTile));
+        const int vals = min(kTile * parked, c1 - kTile * (tile_first + flushed));
+        for (int e = lane; e < vals; e += 64) {
+          const float* src = park + (e / kTile) * (2 * kTile) + e % kTile;
+          store_through(dst, 4u * e, src[0] + src[kTile]);
+        }
+      }
+    }
+    wave_lds_fence();
+    flushed += parked;
+    parked = 0;
+  };
+  __syncthreads();                           // queries in LDS
+  VEGAS_TL(kTlQueries);
 
-  // ---- running state: lane (row, half) keeps the row max m (same in both halves), its half's partial sum l,
-  //      and O^T accumulators acc[blk][i] = O[row][NBLK*(8(i/4) + 4half + i%4) + blk]
-  float m_run = -INFINITY, l_run = 0.f;
-  f32x16 acc[NBLK];
+  // ---- running state: lane (row, half) keeps the reference maximum m (same in both halves), its half's partial sum l,
+  //      and O^T accumulators acc[nb][blk][i] = O[row][NBLK*(8(i/4) + 4half + i%4) + blk]
+  float m_run[NB], l_run[NB];
+  f32x16 acc[NB][NBLK];
 #pragma unroll
-  for (int blk = 0; blk < NBLK; ++blk)
+  for (int nb = 0; nb < NB; ++nb) {
+    m_run[nb] = -INFINITY;
+    l_run[nb] = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[blk][i] = 0.f;
+    for (int blk = 0; blk < NBLK; ++blk)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[nb][blk][i] = 0.f;
+  }
+  // K reads of a slot: piece 2 kk + half of token l32, exchanged as above
+  const uint32_t k_first = static_cast<uint32_t>(l32 * kRow + ((half ^ (D == 128 ? (l32 & 15) : ((l32 >> 1) & 7))) * 16));
+  uint32_t q_row[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) q_row[nb] = static_cast<uint32_t>(min(32 * nb + l32, qrows - 1) * kRowPitch + half * 16);
 
-  // One step of the pair: krs/vrs hold this wave's page of tile k and are refilled with tile k + 2.
-  auto step = [&](int k, u32x4 (&krs)[NKH], VReg (&vrs)[8], auto load_tag) {
+  // One tile.  load_next: the tile NS further enters the ring as this one leaves it.
+  auto step = [&](int k, int slot, auto load_tag) {
     constexpr bool load_next = decltype(load_tag)::value;
-    const int cur = tile0 + pr + k * NP;
-    const int tok0 = cur * kTile;
-    // this wave's page -> the pair's K and V tiles
+    const int tok0 = (tile_first + k) * kTile;
+    const uint32_t now = COLLECT != 0 ? clock_epoch() : 0u;
+    const unsigned char* kt = ring + slot * (2 * kHalfSlot);
+    const unsigned char* vt = kt + kHalfSlot;
+    const int after = ntiles - 1 - k;        // (tail) tiles requested after this one
+    const int id0 = into_pool(next0), id1 = into_pool(next1);
+    if constexpr (load_next) {
+      wait_vm<(2 * NS - 1) * NL>();
+      next0 = page_id(k + NS + 1, 0);
+      next1 = page_id(k + NS + 1, 1);
+    } else {
+      if (after == 0) wait_vm<NL>();
+      else if (after == 1) wait_vm<3 * NL>();
+      else if (after == 2) wait_vm<(NS > 2 ? 5 : 0) * NL>();
+      else wait_vm<(NS > 3 ? 7 : 0) * NL>();
+    }
+    f32x16 st[NB];
 #pragma unroll
-    for (int i = 0; i < NKH; ++i)
-      *reinterpret_cast<u32x4*>(kt + (kPage * role + TPI * i + k_tok) * kRowPitch + k_chunk * 16) = krs[i];
+    for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-    for (int jj = 0; jj < 8; ++jj)
-      *reinterpret_cast<VReg*>(vt + (kPage * role + 8 * (jj >> 2) + 4 * half + (jj & 3)) * kRowPitch + l32 * (2 * NBLK)) = vrs[jj];
-    if (load_next) issue(k + 2, krs, vrs);
-    __syncthreads();                         // both pages of the tile are in LDS
-
-    f32x16 st;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) st[i] = 0.f;
+      for (int i = 0; i < 16; ++i) st[nb][i] = 0.f;
+    uint32_t k_at = k_first;
+    asm volatile("" : "+v"(k_at));           // (the eight addresses are not worth eight registers of the whole loop)
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
-      const int off = l32 * kRowPitch + half * 16 + kk * 32;
-      const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(kt + off));
-      const bf16x8 qb = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qlds + row0 * kRowPitch + off));
-      st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qb, st, 0, 0, 0);
+      const bf16x8 a = __builtin_bit_cast(
+          bf16x8, *reinterpret_cast<const u32x4*>(kt + (k_at ^ static_cast<uint32_t>(32 * kk))));
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const bf16x8 qb = __builtin_bit_cast(
+            bf16x8, *reinterpret_cast<const u32x4*>(qlds + q_row[nb] + kk * 32));
+        st[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qb, st[nb], 0, 0, 0);
+      }
+    }
+    if constexpr (load_next) {
+      wait_lds();
+      load_k(slot, id0, id1);
     }
 
     if constexpr (COLLECT == 2) {
-      // Columns xr and xr + 1 of block 1's S^T hold k_i . (high part) and k_i . (low part) for the tile's tokens.
-      if (has_extra && (l32 == xr || l32 == xr + 1)) {
-        float* dst = tok_lds + (l32 - xr) * (kTile * NP) + pr * kTile + 4 * half;
+      // Columns Rl and Rl + 1 of S^T hold k_i . (high part) and k_i . (low part) for the tile's tokens.
+      if (has_extra) {
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4)
-          *reinterpret_cast<f32x4*>(dst + 8 * i4) = f32x4{st[4 * i4], st[4 * i4 + 1], st[4 * i4 + 2], st[4 * i4 + 3]};
+        for (int nb = 0; nb < NB; ++nb) {
+          const int r = 32 * nb + l32;
+          if (r == Rl || r == Rl + 1) {
+            float* dst = park + parked * tile_vals + (r - Rl) * kTile + 4 * half;
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4)
+              *reinterpret_cast<f32x4*>(dst + 8 * i4) = f32x4{st[nb][4 * i4], st[nb][4 * i4 + 1], st[nb][4 * i4 + 2], st[nb][4 * i4 + 3]};
+          }
+        }
       }
     }
 
     const bool tail = (tok0 + kTile > c1) || (tok0 + kTile - 1 > n - p.G);
-    if (tail) {
+    bf16x8 pb[NB][2];
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int tok = tok0 + 8 * (i >> 2) + 4 * half + (i & 3);
-        if (tok > limit) st[i] = -INFINITY;
+    for (int nb = 0; nb < NB; ++nb) {
+      if (tail) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int tok = tok0 + 8 * (i >> 2) + 4 * half + (i & 3);
+          if (tok > limit[nb]) st[nb][i] = -INFINITY;
+        }
       }
+      float tmax = st[nb][0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, st[nb][i]);
+      tmax = half_max(tmax) * p.scale_log2e;               // scale > 0: max commutes with scaling
+      const float m_before = m_run[nb];
+      const float m_new = (tmax > m_before + kPairSlack) ? tmax : m_before;
+      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+      m_run[nb] = m_new;
+      float pw[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) pw[i] = fast_exp2(__builtin_fmaf(st[nb][i], p.scale_log2e, -m_use));
+      float ps0 = 0.f, ps1 = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) { ps0 += pw[i]; ps1 += pw[8 + i]; }
+      // (nothing to rescale where the row had seen no key yet: its sums are still zero)
+      if (__builtin_amdgcn_ballot_w64(m_new != m_before && m_before != -INFINITY) != 0) {
+        const float alpha = fast_exp2(m_before - m_use);
+        l_run[nb] *= alpha;
+#pragma unroll
+        for (int blk = 0; blk < NBLK; ++blk)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) acc[nb][blk][i] *= alpha;
+      }
+      l_run[nb] += ps0 + ps1;
+      if constexpr (COLLECT == 1) {
+        const float f0 = half_sum(ps0);
+        const float f1 = half_sum(ps1);                    // page `half` of the tile
+        if (ci[nb] >= 0) park[parked * tile_vals + half * nci + ci[nb] - ci_lo] = m_use + fast_log2(half ? f1 : f0);
+      }
+#pragma unroll
+      for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) pb[nb][s2][jj] = static_cast<__bf16>(pw[s2 * 8 + jj]);
     }
-    float tmax = st[0];
-#pragma unroll
-    for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, st[i]);
-    tmax = half_max(tmax) * p.scale_log2e;               // scale > 0: max commutes with scaling
-    const float m_new = fmaxf(m_run, tmax);
-    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-    const float alpha = fast_exp2(m_run - m_use);
-    float pw[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) pw[i] = fast_exp2(__builtin_fmaf(st[i], p.scale_log2e, -m_use));
-    float ps0 = 0.f, ps1 = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { ps0 += pw[i]; ps1 += pw[8 + i]; }
-    l_run = l_run * alpha + (ps0 + ps1);
-    const float m_before = m_run;
-    m_run = m_new;
-    if (COLLECT == 1) {
-      const float f0 = half_sum(ps0);
-      const float f1 = half_sum(ps1);                    // page 2 pr + half of the step
-      if (l32 < Rl) lse_lds[(2 * pr + half) * p.R + row0 + l32] = m_use + fast_log2(half ? f1 : f0);
-    }
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f && m_before != -INFINITY) != 0) {   // (no key seen yet: sums still zero)
-#pragma unroll
-      for (int blk = 0; blk < NBLK; ++blk)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[blk][i] *= alpha;
-    }
-    bf16x8 pb[2];
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-      for (int jj = 0; jj < 8; ++jj) pb[s2][jj] = static_cast<__bf16>(pw[s2 * 8 + jj]);
 
+    if constexpr (load_next) {
+      wait_vm<(2 * NS - 1) * NL>();
+    } else {
+      if (after == 0) wait_vm<0>();
+      else if (after == 1) wait_vm<2 * NL>();
+      else if (after == 2) wait_vm<(NS > 2 ? 4 : 0) * NL>();
+      else wait_vm<(NS > 3 ? 6 : 0) * NL>();
+    }
     const bool past_end = tok0 + kTile > n;              // slots past the end may hold anything: feed zeros
 #pragma unroll
     for (int s2 = 0; s2 < 2; ++s2) {
@@ -273,7 +431,8 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
 #pragma unroll
       for (int jj = 0; jj < 8; ++jj) {
         const int tl = 16 * s2 + 8 * (jj >> 2) + 4 * half + (jj & 3);
-        vcur[jj] = *reinterpret_cast<const VReg*>(vt + tl * kRowPitch + l32 * (2 * NBLK));
+        const int row = D == 128 ? tl : (16 * s2 + 8 * (jj >> 2) + 2 * (jj & 3) + half);   // where that token's V sits
+        vcur[jj] = *reinterpret_cast<const VReg*>(vt + row * kRow + l32 * (2 * NBLK));
         if (past_end && tok0 + tl >= n) vcur[jj] = VReg{};
       }
 #pragma unroll
@@ -291,97 +450,125 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
           }
           raw[pp] = __builtin_amdgcn_perm(hi, lo, (blk & 1) ? 0x07060302u : 0x05040100u);
         }
-        acc[blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, raw), pb[s2], acc[blk], 0, 0, 0);
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          acc[nb][blk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, raw), pb[nb][s2], acc[nb][blk], 0, 0, 0);
       }
     }
-    __syncthreads();                         // everybody is done with the tile: the next step may overwrite it
-    // What the step collected leaves now (nobody writes the LDS values again before the next step's first barrier,
-    // which no wave passes before every wave has read its element here).
-    if constexpr (COLLECT == 1) {
-      const bool ok = col_active && c0 / kPage + 4 * k + col_page < min(nblk, (c1 + kPage - 1) / kPage);
-      float* dst = ok ? col_dst + static_cast<int64_t>(k) * (4 * p.Rc) : trash;
-      *dst = lse_lds[col_elem];
+    if constexpr (load_next) {
+      wait_lds();
+      load_v(slot, id0, id1);
     }
-    if constexpr (COLLECT == 2) {
-      const bool ok = col_active && c0 + (kTile * NP) * k + col_elem < c1;
-      float* dst = ok ? col_dst + k * (kTile * NP) : trash;
-      *dst = tok_lds[col_elem] + tok_lds[kTile * NP + col_elem];
+    if constexpr (COLLECT != 0) {
+      ++parked;
+      if (parked == p.park_tiles || now != epoch) {
+        flush();
+        epoch = now;
+      }
     }
 #ifdef VEGAS_TIMELINE
     if (tl_stamps[kTlFirstTile] == 0) VEGAS_TL(kTlFirstTile);
 #endif
   };
 
-  // ---- stream the chunk: T steps (even), the two register sets in turn; the last two steps issue no loads
+  // ---- stream the chunk's tiles
   {
     using yes = std::integral_constant<bool, true>;
     using no = std::integral_constant<bool, false>;
-    int k = 0;
-    for (; k + 2 < T; k += 2) {
-      step(k, kr0, vr0, yes{});
-      step(k + 1, kr1, vr1, yes{});
+    int k = 0, slot = 0;
+    for (; k + NS < ntiles; ++k) {
+      step(k, slot, yes{});
+      slot = slot + 1 == NS ? 0 : slot + 1;
     }
-    step(k, kr0, vr0, no{});
-    step(k + 1, kr1, vr1, no{});
+    for (; k < ntiles; ++k) {
+      step(k, slot, no{});
+      slot = slot + 1 == NS ? 0 : slot + 1;
+    }
   }
 
-  // ---- merge the two pairs, one row block after the other (the merge buffer aliases the tiles and the parked
-  //      values): row maxima meet in LDS, every wave rescales, the waves of the block park their rows as
-  //      [pair][row][d], all threads add the pairs and write the block's rows of the workgroup's partial.
+  if constexpr (COLLECT != 0) {
+    if (parked > 0) flush();
+  }
+
+  // ---- merge the waves: row maxima meet in LDS, every wave rescales and parks its valid rows as [wave][row][d], all
+  //      threads add the waves' copies and write the workgroup's partial with consecutive threads on consecutive addresses
   VEGAS_TL(kTlStreamed);
-  if (half == 0) sm_m[pr * 64 + row0 + l32] = m_run;
-  __syncthreads();                           // also: the collected values have been read out of LDS
+  if (half == 0) {
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) sm_m[wave * kPairRows + 32 * nb + l32] = m_run[nb];
+  }
+  __syncthreads();                           // also: every wave is done with its ring and the queries
   VEGAS_TL(kTlMerged);
-  const float mw = fmaxf(sm_m[row0 + l32], sm_m[64 + row0 + l32]);
-  const float m_fin = (mw == -INFINITY) ? 0.f : mw;
-  const float sc = fast_exp2(m_run - m_fin);
-  const float lsum = half_sum(l_run * sc);
-  if (half == 0) sm_l[pr * 64 + row0 + l32] = lsum;
   float* red = reinterpret_cast<float*>(smem);
-#pragma unroll 1
-  for (int blk_rows = 0; blk_rows < 2; ++blk_rows) {
-    const int rows = min(32, p.R - 32 * blk_rows);       // valid rows of this block
-    if (role == blk_rows && l32 < rows) {
-      float* dst = red + (pr * rows + l32) * kRedPitch;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const int row = 32 * nb + l32;
+    float mw = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) mw = fmaxf(mw, sm_m[w * kPairRows + row]);
+    const float m_fin = (mw == -INFINITY) ? 0.f : mw;
+    const float sc = fast_exp2(m_run[nb] - m_fin);
+    const float lsum = half_sum(l_run[nb] * sc);
+    if (half == 0) sm_l[wave * kPairRows + row] = lsum;
+    if (row < Rl) {
+      float* dst = red + (wave * Rl + row) * kRedPitch;
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int d0 = NBLK * (8 * (i >> 2) + 4 * half + (i & 3));
         if constexpr (D == 128) {
-          *reinterpret_cast<f32x4*>(dst + d0) = f32x4{acc[0][i] * sc, acc[1][i] * sc, acc[2][i] * sc, acc[3][i] * sc};
+          *reinterpret_cast<f32x4*>(dst + d0) =
+              f32x4{acc[nb][0][i] * sc, acc[nb][1][i] * sc, acc[nb][2][i] * sc, acc[nb][3][i] * sc};
         } else {
-          *reinterpret_cast<f32x2*>(dst + d0) = f32x2{acc[0][i] * sc, acc[1][i] * sc};
+          *reinterpret_cast<f32x2*>(dst + d0) = f32x2{acc[nb][0][i] * sc, acc[nb][1][i] * sc};
         }
       }
     }
-    __syncthreads();
-    float* po = p.part_o + (pbase * p.R + 32 * blk_rows) * D;
-    for (int e = tid; e < rows * D; e += NW * 64) {
-      const int row = e / D, d = e % D;
-      po[e] = red[row * kRedPitch + d] + red[(rows + row) * kRedPitch + d];
-    }
-    __syncthreads();
   }
-  if (tid < p.R) {
-    const float m2 = fmaxf(sm_m[tid], sm_m[64 + tid]);
-    p.part_ml[pbase * p.R + tid] = make_float2(m2, sm_l[tid] + sm_l[64 + tid]);
+  __syncthreads();
+  constexpr int V4 = D / 4;
+  float* po = p.part_o + (pbase * p.R + row0) * D;
+#pragma unroll 2
+  for (int e = tid; e < Rl * V4; e += NW * 64) {
+    const float* src = red + (e / V4) * kRedPitch + 4 * (e % V4);
+    f32x4 acc4 = *reinterpret_cast<const f32x4*>(src);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) acc4 += *reinterpret_cast<const f32x4*>(src + w * Rl * kRedPitch);
+    *reinterpret_cast<f32x4*>(po + 4 * e) = acc4;
+  }
+  if (tid < Rl) {
+    float mw = -INFINITY, lw = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      mw = fmaxf(mw, sm_m[w * kPairRows + tid]);
+      lw += sm_l[w * kPairRows + tid];
+    }
+    p.part_ml[pbase * p.R + row0 + tid] = make_float2(mw, lw);
   }
   VEGAS_TL(kTlExit);
   VEGAS_TL_FLUSH(p.timeline, NW);
 }
 
-// Dynamic LDS bytes of attn_pair_kernel for R rows per KV head.
-inline size_t pair_lds_tail_bytes(int D) {
-  return static_cast<size_t>(64) * row_pitch(D) + 2 * static_cast<size_t>(kPairs) * 64 * sizeof(float);   // queries, row maxima and sums
-}
-inline size_t pair_lds_bytes(int R, int collect, int D) {
-  size_t park = 0;                                                         // what one step collects
-  if (collect == 1) park = static_cast<size_t>(4) * R * sizeof(float);
-  if (collect == 2) park = 2 * static_cast<size_t>(kTile * kPairs) * sizeof(float);
-  size_t stage = static_cast<size_t>(kPairs) * 2 * 32 * row_pitch(D) + park;
-  const size_t red = static_cast<size_t>(kPairs) * 32 * red_pitch(D) * sizeof(float);
-  if (red > stage) stage = red;
-  stage = (stage + 15) / 16 * 16;
-  return stage + pair_lds_tail_bytes(D);
+// Dynamic LDS of attn_pair_kernel: bytes, where the row maxima start, and how many tiles of collected values a wave parks.
+struct PairLds {
+  size_t bytes, off_max;
+  int park_tiles;
+};
+inline PairLds pair_lds(int R, int Rc, int row_blocks, int collect, int D) {
+  const size_t q = static_cast<size_t>(row_blocks == 1 ? R + (collect == 2 ? 2 : 0) : kPairRows) * row_pitch(D);
+  const size_t rows_ml = 2 * static_cast<size_t>(kPairWaves) * kPairRows * sizeof(float);
+  size_t before = kPairWaves * kPairRing + q;
+  PairLds l = {0, 0, 0};
+  if (collect != 0) {
+    const size_t tile = 2 * sizeof(float) * (collect == 2 ? kTile : (Rc < kPairRows ? Rc : kPairRows));
+    l.park_tiles = static_cast<int>((160 * 1024 - rows_ml - before) / (kPairWaves * tile));
+    if (l.park_tiles > 64) l.park_tiles = 64;
+    before += kPairWaves * tile * l.park_tiles;
+  }
+  const size_t red = static_cast<size_t>(kPairWaves) * (R < kPairRows ? R : kPairRows) * red_pitch(D) * sizeof(float);
+  if (red > before) before = red;
+  l.off_max = (before + 15) / 16 * 16;
+  l.bytes = l.off_max + rows_ml;
+  return l;
 }
 
 }  // namespace vegas

@@ -25,8 +25,9 @@
 //     and two byte-permutes per register pair build the operand.
 //   * All query rows of the GQA group (x G verification rows) are stacked in the N dimension, so
 //     every K/V byte is loaded once per workgroup and never re-read.  The queries sit in LDS
-//     (padded like K) and are shared by the workgroup's waves.  More than 32 rows per KV head are
-//     split into 32-row blocks handled by sibling workgroups whose ids differ by the number of KV
+//     (padded like K) and are shared by the workgroup's waves.  More than 32 rows per KV head take
+//     attn_pair_kernel in verification; where a local mask applies, and in draft calls, they are split into 32-row
+//     blocks handled by sibling workgroups whose ids differ by the number of KV
 //     heads: ids are dealt round-robin to the 8 XCDs, so siblings share an L2 and the second
 //     reader of a K/V line is served from it -- HBM still sees each byte once.
 //   * Loads run one tile ahead: as soon as K(current) has been handed to LDS, K(next) goes into
@@ -161,9 +162,7 @@ __device__ __forceinline__ void store_queries_to_lds(unsigned char* qlds, const 
 // A sum of logits is linear in the query, sum_r q_r . k = (sum_r q_r) . k, so the sum of the collected
 // query rows of this KV head rides along as two spare rows of the query tile (a bf16 high part and a
 // bf16 low part, together good to 2^-17) and the first MFMA delivers the token sums for free.  The host puts
-// them in the last row block of the KV head; when that block is full (or one row short of full) the last
-// row block is one that holds nothing but those two rows (Rl = 0: it streams K like its siblings, parks the
-// token sums, and writes no partial output).
+// them behind the real rows (at most 30 of them: with more the call takes attn_pair_kernel).
 // PS: log2 of the tokens per page of the table the kernel walks.  4 (16-token pages) is the path
 // described above; 0..3 (1, 2, 4, 8-token pages: Sec. 4 drafts with one-token pages, App. D sweeps
 // 1..16) is for draft calls only: a tile then spans 32 >> PS pages, every lane looks up the page of

@@ -79,11 +79,10 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 struct SplitPlan {
   int R = 0, Rc = 0, NB = 0, NW = 0, chunk = 0, nsplit = 0, lse_pages = 0;   // Rc: collected rows per KV head
-  bool pair = false;                 // 33..64 rows per KV head: one workgroup serves both row blocks (attn_pair_kernel)
+  bool pair = false;                 // verification of more than 32 rows per KV head: 64-row workgroups (attn_pair_kernel)
   bool balanced = false;             // chunk lengths per sequence, computed on the GPU from the lengths (ragged batches)
   int J = 0, J2 = 0, JS = 0;         // balanced: workgroups per KV head of a one-wave and a two-wave plan; slots held
   int cap_units = 0;                 // balanced: longest chunk, in units of kTile * NW tokens
-  size_t off_trash = 0;              // a word for stores that must go nowhere
   size_t off_plan = 0;               // balanced: [B] (first slot, chunk tokens)
   size_t off_part_o = 0, off_part_ml = 0, off_page_lse = 0, total = 0;
 };
@@ -119,19 +118,18 @@ int check_paged16(const vegas_desc* d) {
 // Rows stacked on one KV head decide the kernel variant; the chunk size decides the grid.
 // max_len bounds the lengths the call may see; small problems get small workgroups.
 // collect: 0 nothing, 1 page log-sum-exps [pages x rows], 2 token sums [padded tokens] per (sequence, KV head)
-// sum_block: the logit metric's two query-sum rows get a row block of their own (no spare rows in the last real one)
 int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect, int wg_per_cu, SplitPlan* pl,
-               bool may_pair = false, bool may_finish = false, bool sum_block = false) {
+               bool may_pair = false, bool may_finish = false) {
   pl->R = rows_per_head;
   const int num_cu = device_cu_count();
   const int64_t heads = static_cast<int64_t>(d->batch) * d->num_kv_heads;
   if (rows_per_head > 128) return VEGAS_ERR_UNSUPPORTED;
-  pl->NB = (rows_per_head + 31) / 32 + (sum_block ? 1 : 0);   // 32-row blocks
   pl->NW = 4;                                        // measured: 4-wave groups match or beat 8-wave groups everywhere
-  // Two row blocks: one workgroup per chunk reads K/V once for both (attn_pair_kernel) when the chunk holds an even
-  // number of tiles; otherwise (and for 3 or 4 blocks) sibling workgroups, one per block, share an XCD's L2.
-  pl->pair = may_pair && !sum_block && pl->NB == 2;
-  if (pl->pair && d->kv_chunk_tokens != 0 && d->kv_chunk_tokens % (kTile * kPairs) != 0) pl->pair = false;
+  // Row blocks: 32 rows each, sibling workgroups that share an XCD's L2; verification of more than 32 rows (with the two
+  // sum rows of the logit metric, which take a block's spare rows) has blocks of 64 served from one read of K/V.
+  const int tile_rows = rows_per_head + (collect == 2 ? 2 : 0);
+  pl->pair = may_pair && tile_rows > 32;
+  pl->NB = pl->pair ? (tile_rows + kPairRows - 1) / kPairRows : (rows_per_head + 31) / 32;
   // A draft call (may_finish) over a selection that one workgroup per (sequence, KV head) streams fast enough: it
   // writes the output rows itself, so no merge kernel is launched.  Groups of more than kDraftRows heads run the 32-row
   // kernel, whose workgroups take about 0.35 us per tile; at 4K context, five draft calls per iteration: 256 selected
@@ -151,7 +149,7 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
     // Verification: one workgroup per CU when the batch is small (at 32K context 256 equal workgroups
     // beat 512); draft calls are latency-bound and like two small workgroups per CU.  With many
     // (sequence, head) columns, shorter chunks balance ragged lengths better.
-    const int64_t columns = heads * (pl->pair ? 1 : pl->NB);
+    const int64_t columns = heads * pl->NB;
     int64_t splits = static_cast<int64_t>(num_cu) * wg_per_cu / columns;
     if (splits < 1) splits = 1;
     int64_t c = (max_len + splits - 1) / splits;
@@ -161,13 +159,6 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
       const int64_t up = (c + unit - 1) / unit * unit, down = c / unit * unit;
       c = up;
       if (down >= unit && ((max_len + down - 1) / down) * columns * 4 <= static_cast<int64_t>(num_cu) * wg_per_cu * 5) c = down;
-    }
-    if (pl->pair) {
-      // the pair kernel likes two workgroups per CU once their chunks are long enough (one sequence of 128K tokens,
-      // 40 rows: 512 chunks of 2048 tokens 115 us, 256 of 4096 132 us; at 32K tokens the finalising kernel's
-      // larger table of chunks eats the gain)
-      const int64_t c2 = ((max_len + 2 * splits - 1) / (2 * splits) + unit - 1) / unit * unit;
-      if (wg_per_cu == 1 && c2 >= 2048) { c = c2; splits *= 2; }
     }
     // What a workgroup collects is parked in LDS until its chunk ends, so a chunk cannot be arbitrarily long.  A
     // chunk that gives every CU exactly one workgroup is taken as it is while its LDS fits (batch 4 x 64K tokens:
@@ -185,7 +176,7 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   // number of workgroups stream about the same number of tokens each.  (A host-side chunk length cuts a ragged
   // batch into unequal numbers of equal chunks: 45 % of the HBM peak on 16 sequences of 8K..64K tokens, 40 rows,
   // against 68 % with the plan; and it sizes chunks for lengths that may never occur.)
-  const int64_t per_head = static_cast<int64_t>(d->num_kv_heads) * (pl->pair ? 1 : pl->NB);   // workgroups per slot
+  const int64_t per_head = static_cast<int64_t>(d->num_kv_heads) * pl->NB;   // workgroups per slot
   pl->balanced = may_pair && d->kv_chunk_tokens == 0 && d->batch >= 2 && d->batch <= 64 && max_len < (1 << 24) &&
                  per_head <= num_cu;
   // (A call that one workgroup per column finishes uses no partials; its workspace is sized for the chunked plan all
@@ -195,33 +186,24 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   pl->chunk = chunk;
   pl->nsplit = (max_len + chunk - 1) / chunk;
   if (pl->balanced) {
-    int64_t most_chunks;                                        // of one sequence
-    if (pl->pair) {
-      // one launch wave (two workgroups per CU) without collection; with it, shorter chunks in two waves were
-      // measured faster (16 sequences of 8K..64K tokens, 40 rows: 505 us against 515 us).  Nothing is parked.
-      pl->J = pl->J2 = static_cast<int>((collect ? 4 : 2) * num_cu / per_head);
-      pl->cap_units = 1 << 20;
-      pl->chunk = unit;                                         // (unused: every sequence has its own)
-      most_chunks = pl->J;
-    } else {
-      // one workgroup per CU with chunks as long as its LDS can park (16 x 36864 tokens, 20 rows: 256 chunks of
-      // 18432 tokens reach 80 % of the peak, 512 of 9216 75 %, 4096-token chunks 69 %); two waves when the
-      // lengths are too ragged for one
-      pl->J = static_cast<int>(num_cu / per_head);
-      // (slots no plan uses still cost a workgroup that works that out, at one workgroup per CU in a wave of their
-      // own behind the others: a small batch, whose kernel is short, gets the one-wave plan only)
-      pl->J2 = d->batch >= 8 ? 2 * pl->J : pl->J;
+    // one workgroup per CU with chunks as long as its LDS can park (16 x 36864 tokens, 20 rows: 256 chunks of
+    // 18432 tokens reach 80 % of the peak, 512 of 9216 75 %, 4096-token chunks 69 %); two waves when the
+    // lengths are too ragged for one.  The same for 64-row workgroups, which park no whole chunk (4 x 65536 tokens, 40
+    // rows: 256 chunks 196 us, 512 198, 1024 208; 2 x 8192: 18.5, 26.9, 36.1; 16 of 8192..65536: 488, 450, 447).
+    pl->J = static_cast<int>(num_cu / per_head);
+    // (slots no plan uses still cost a workgroup that works that out, at one workgroup per CU in a wave of their
+    // own behind the others: a small batch, whose kernel is short, gets the one-wave plan only)
+    pl->J2 = d->batch >= 8 ? 2 * pl->J : pl->J;
+    int cap = 1 << 24;
+    if (collect != 0 && !pl->pair) {
       const int prows = rows_per_head < 32 ? rows_per_head : 32;
-      int cap = 1 << 24;
-      if (collect != 0) {
-        cap = unit;
-        while (split_lds_bytes(pl->NW, prows, collect, cap + unit, d->head_dim) <= 150 * 1024 && cap < (1 << 24)) cap += unit;
-      }
-      pl->cap_units = cap / unit;
-      pl->chunk = collect != 0 ? cap : unit;                    // sizes the LDS that parks a chunk's collected values
-      most_chunks = (static_cast<int64_t>(max_len) + cap - 1) / cap;
-      if (most_chunks < pl->J2) most_chunks = pl->J2;
+      cap = unit;
+      while (split_lds_bytes(pl->NW, prows, collect, cap + unit, d->head_dim) <= 150 * 1024 && cap < (1 << 24)) cap += unit;
     }
+    pl->cap_units = cap / unit;
+    pl->chunk = collect != 0 && !pl->pair ? cap : unit;         // sizes the LDS that parks a chunk's collected values
+    int64_t most_chunks = (static_cast<int64_t>(max_len) + cap - 1) / cap;   // of one sequence
+    if (most_chunks < pl->J2) most_chunks = pl->J2;
     if (pl->J < 1) pl->J = 1;
     if (pl->J2 < pl->J) pl->J2 = pl->J;
     // slots: a plan for J2 workgroups never takes more than max(J2, B) of them; a capped one B * most_chunks
@@ -244,8 +226,7 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   off += align_up(hs * static_cast<size_t>(pl->lse_pages) * (collect == 2 ? 1 : pl->Rc) * sizeof(float));
   pl->off_plan = off;
   if (pl->balanced) off += align_up(static_cast<size_t>(d->batch) * sizeof(int2));
-  pl->off_trash = off;
-  off += kAlign;
+  off += kAlign;                                    // (a spare line: no stage uses it)
   pl->total = off;
   return VEGAS_OK;
 }
@@ -258,11 +239,7 @@ int plan_verify(const vegas_desc* d, SplitPlan* pl) {
     return VEGAS_ERR_SHAPE;
   const int R = d->num_queries * g;
   const int collect = d->collect_rows == 0 ? 0 : (d->score_metric == VEGAS_METRIC_TOKEN_LOGITS ? 2 : 1);
-  // The logit metric's two query-sum rows ride in spare rows of the last 32-row block of a KV head; where that block
-  // has fewer than two (R = 31, 32, 63, 64, ... rows) they get a sibling row block of their own, which streams K
-  // alongside the others (same XCD, served by its L2) and writes no output rows.
-  const bool sum_block = collect == 2 && (R % 32 == 0 || R % 32 == 31);
-  return plan_split(d, R, d->max_seq_len, collect, 1, pl, d->window == 0, false, sum_block);
+  return plan_split(d, R, d->max_seq_len, collect, 1, pl, d->window == 0, false);
 }
 
 int plan_draft(const vegas_desc* d, SplitPlan* pl) {
@@ -309,13 +286,22 @@ int launch_one(Kern kern, dim3 grid, dim3 block, size_t lds, hipStream_t st, Spl
 template <bool CAUSAL, int COLLECT, int D>
 int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t st, int page_size) {
   if constexpr (CAUSAL) {
-    if (pl.pair) {                                  // both row blocks from one read of K/V
-      const dim3 pgrid = pl.balanced ? dim3(pl.JS, sp.Hkv, 1) : dim3(pl.nsplit, sp.Hkv, batch);   // chunks fastest
-      const size_t plds = pair_lds_bytes(pl.R, COLLECT, D);
-      sp.lds_q_off = static_cast<int32_t>(plds - pair_lds_tail_bytes(D));
-      sp.row_blocks = 1;
-      if (plds > 160 * 1024) return VEGAS_ERR_UNSUPPORTED;
-      return launch_one(attn_pair_kernel<COLLECT, D>, pgrid, dim3(kPairWaves * 64), plds, st, sp);
+    if (pl.pair) {
+      const unsigned slots = pl.balanced ? pl.JS : pl.nsplit, seqs = pl.balanced ? 1 : batch;
+      const PairLds lds = pair_lds(pl.R, pl.Rc, pl.NB, COLLECT, D);
+      sp.row_blocks = pl.NB;
+      sp.lds_q_off = static_cast<int32_t>(lds.off_max);
+      sp.park_tiles = lds.park_tiles;
+      if (lds.bytes > 160 * 1024 || (COLLECT != 0 && lds.park_tiles < 1)) return VEGAS_ERR_UNSUPPORTED;
+      // A wave parks a tile every 2.7 us (1.35 at head dimension 64) where HBM bounds the stream; the interval ends when
+      // its LDS is three quarters full, so that the faster compute units seldom have to write before it does (16 x 36864
+      // tokens, 40 rows, 15 tiles: 60 % 434 us, 75 % 430, 95 % 440, 140 % 446; without collection 395).
+      const double ticks = 0.75 * lds.park_tiles * (D == 128 ? 270 : 135);
+      sp.epoch_mul = static_cast<uint32_t>(4294967296.0 / (ticks < 256 ? 256 : ticks));
+      if (pl.NB == 1)
+        return launch_one(attn_pair_kernel<COLLECT, D, true>, dim3(slots, sp.Hkv, seqs), dim3(kPairWaves * 64), lds.bytes, st, sp);
+      if (static_cast<unsigned>(pl.NB) * slots > 65535u) return VEGAS_ERR_UNSUPPORTED;
+      return launch_one(attn_pair_kernel<COLLECT, D, false>, dim3(sp.Hkv, pl.NB * slots, seqs), dim3(kPairWaves * 64), lds.bytes, st, sp);
     }
   }
   // (KV head, row block + NB * chunk, sequence): the kernels read their indices off the grid without a division
@@ -354,10 +340,8 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
       return launch_one(attn_split_kernel<4, 2, true, 0, false, 4, true, D>, grid, dim3(256), lds, st, sp);
     }
   }
-  constexpr bool kVerify = CAUSAL;                  // the verification pass is the only causal caller
-  if (kVerify && pl.NB == 1)                        // one reader per K/V line, read once: stream it
-    return launch_one(attn_split_kernel<4, 2, CAUSAL, COLLECT, kVerify, 4, false, D>, grid, dim3(256), lds, st, sp);
-  return launch_one(attn_split_kernel<4, 2, CAUSAL, COLLECT, false, 4, false, D>, grid, dim3(256), lds, st, sp);
+  // verification of up to 32 rows: one reader per K/V line, read once: stream it
+  return launch_one(attn_split_kernel<4, 2, CAUSAL, COLLECT, CAUSAL, 4, false, D>, grid, dim3(256), lds, st, sp);
 }
 
 template <bool CAUSAL, int COLLECT>
@@ -390,7 +374,8 @@ void fill_split_params(const vegas_desc* d, const SplitPlan& pl, int G, const vo
   sp->Rc = pl.Rc;
   sp->window = 0;
   sp->out_direct = nullptr;
-  sp->trash = reinterpret_cast<float*>(ws + pl.off_trash);
+  sp->park_tiles = 0;
+  sp->epoch_mul = 0;
   sp->plan = pl.balanced ? reinterpret_cast<int2*>(ws + pl.off_plan) : nullptr;
   sp->batch = d->batch;
   sp->slots_target = pl.J;
@@ -505,20 +490,17 @@ int for_each_lds_kernel(F f) {
     one(attn_split_kernel<4, 2, false, 0, false, 4, false, D>);
     one(attn_split_kernel<4, 2, true, 0, true, 4, true, D>);         // verification of a banded layer
     one(attn_split_kernel<4, 2, true, 0, false, 4, true, D>);
-    one(attn_split_kernel<4, 2, true, 0, true, 4, false, D>);        // verification: no collection / page weights / logits,
-    one(attn_split_kernel<4, 2, true, 0, false, 4, false, D>);       // one reader per line or sibling row blocks
+    one(attn_split_kernel<4, 2, true, 0, true, 4, false, D>);        // verification: no collection / page weights / logits
     one(attn_split_kernel<4, 2, true, 1, true, 4, false, D>);
-    one(attn_split_kernel<4, 2, true, 1, false, 4, false, D>);
     one(attn_split_kernel<4, 2, true, 2, true, 4, false, D>);
-    one(attn_split_kernel<4, 2, true, 2, false, 4, false, D>);
     one(attn_draft16_kernel<D, 0>);
     one(attn_draft16_kernel<D, 1>);
     one(attn_draft16_kernel<D, 2>);
     one(attn_draft16_kernel<D, 3>);
     one(attn_draft16_kernel<D, 4>);
-    one(attn_pair_kernel<0, D>);
-    one(attn_pair_kernel<1, D>);
-    one(attn_pair_kernel<2, D>);
+    one(attn_pair_kernel<0, D, true>); one(attn_pair_kernel<0, D, false>);
+    one(attn_pair_kernel<1, D, true>); one(attn_pair_kernel<1, D, false>);
+    one(attn_pair_kernel<2, D, true>); one(attn_pair_kernel<2, D, false>);
   };
   per_dim(std::integral_constant<int, 128>{});
   per_dim(std::integral_constant<int, 64>{});

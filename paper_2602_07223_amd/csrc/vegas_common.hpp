@@ -50,6 +50,10 @@ __device__ __forceinline__ const unsigned char* uniform_ptr(const unsigned char*
   return reinterpret_cast<const unsigned char*>((static_cast<uint64_t>(hi) << 32) | lo);
 }
 
+__device__ __forceinline__ unsigned char* uniform_ptr_mut(unsigned char* ptr) {
+  return const_cast<unsigned char*>(uniform_ptr(ptr));
+}
+
 // Global-memory load at (wave-uniform base) + (32-bit lane offset).  STREAMING marks data that is
 // read once (the verification pass over the whole cache): the non-temporal hint keeps it from
 // displacing useful lines and was worth 7-12 % of the kernel time.
@@ -83,7 +87,8 @@ struct SplitParams {
   int32_t window;           // > 0: local masking, a row at position pos sees keys pos - window + 1 .. pos (causal calls)
   uint16_t* out_direct;     // draft calls with one chunk per (sequence, KV head): the bf16 output [B, G, Hq, D], which
                             // the streaming kernel then normalises and writes itself (nullptr: partials for a merge kernel)
-  float* trash;             // attn_pair_kernel: a word of the workspace that takes the stores of invalid elements
+  int32_t park_tiles;       // attn_pair_kernel: tiles of collected values a wave holds back in LDS
+  uint32_t epoch_mul;       // attn_pair_kernel: 2^32 / ticks of the wall-clock interval at whose end they leave
   int2* plan;               // balanced chunking (or nullptr): [B] (first partial slot, chunk tokens) per sequence,
                             // computed by every workgroup from the lengths and written here by workgroup 0
   int32_t batch;            // B (balanced chunking)

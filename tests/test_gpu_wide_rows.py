@@ -1,0 +1,37 @@
+"""Verification of more than 32 rows per KV head where its kernel can go wrong: chunks of less than a tile to more than a
+wave parks or its ring holds, row counts at the edges of the two row blocks and of a second workgroup, both collection
+modes and none, against the float64 oracle."""
+import pytest
+import torch
+
+from oracle import vegas_oracle as O
+from paper_2602_07223_amd import binding as vb
+from paper_2602_07223_amd import harness, synth
+from tests import parity_util as U
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("Hq,Hkv,G", [(33, 1, 1), (16, 2, 5), (64, 4, 4), (26, 2, 5), (64, 2, 4)],
+                         ids=["33_rows", "40_rows", "64_rows", "65_rows", "128_rows"])
+@pytest.mark.parametrize("n,chunk", [(1, 0), (31, 32), (97, 0), (129, 128), (1025, 416), (4133, 4160), (9000, 9024)])
+def test_chunks_of_every_length(n, chunk, Hq, Hkv, G, D):
+    lens = [n] if chunk else [n, max(n - 17, 0), 2 * n]          # (no chunk length: also the balanced plan)
+    L = synth.make_random_case(seed=6100 + n + Hq + D, batch=len(lens), num_q_heads=Hq, num_kv_heads=Hkv, num_queries=G,
+                               seq_lens=lens, head_dim=D, logit_std=2.0, value_std=1.0, outliers=min(2, n // 2),
+                               outlier_logit=25.0)
+    print(f"[case] wide rows n={n} chunk={chunk} Hq={Hq} Hkv={Hkv} G={G} D={D}", flush=True)
+    dl = harness.DeviceLayer.upload(L)
+    for collect in (vb.COLLECT_ALL_ROWS, vb.COLLECT_FIRST_LAST, vb.COLLECT_NONE):
+        path = harness.VegasPath.for_layer(L, budget_tokens=256, collect_rows=collect, verify_chunk=chunk)
+        path.workspace.fill_(0xFF)                # NaN partials where nothing was written
+        path.out_verify.fill_(float("nan"))
+        path.block_scores.fill_(float("nan"))
+        path.verify(dl)
+        torch.cuda.synchronize()
+        ref_out, ref_scores = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens,
+                                                 L.softmax_scale, collect or vb.COLLECT_ALL_ROWS)
+        U.check_out(f"wide.{n}.{Hq}.{collect}", path.out_verify, ref_out, U.vmax_visible(L))
+        if collect:
+            U.check_scores(f"wide.{n}.{Hq}.{collect}", path.block_scores, ref_scores)
