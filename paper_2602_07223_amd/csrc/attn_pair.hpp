@@ -26,9 +26,9 @@
 //     reads); bursts at common times that are written THROUGH the L2 took 362.  So a wave parks its tiles' values in
 //     LDS and writes them through when the wall clock enters a new interval, or its part of the LDS is full.  (When a
 //     value leaves depends on the clock; the value does not.)
-// Streaming kernel, 40 rows: 16 x 36864 tokens 488 us with a store per tile, 430 now, 395 without collection (6.1 TB/s);
-// 16 of 8192..65536 tokens 483 -> 445; one sequence of 32768 25.8 -> 20.1 us at head dimension 64, 48 rows at 128 40.2 ->
-// 28.6: against the kernel this one replaced, which passed K and V through the registers of two waves and their LDS
+// Streaming kernel, 40 rows: 16 x 36864 tokens 412 us, 380 without collection (6.4 TB/s; a store per tile cost 90 us);
+// 16 of 8192..65536 tokens 483 -> 441; one sequence of 32768 25.8 -> 19.8 us at head dimension 64, 48 rows at 128 40.2 ->
+// 27.9: against the kernel this one replaced, which passed K and V through the registers of two waves and their LDS
 // tiles between two barriers per 64 tokens.  What bounds it: HBM from 64K tokens on, its head and merge below.
 // Rows beyond 64 go to sibling workgroups of 64 rows each.
 #pragma once
@@ -65,13 +65,6 @@ template <int N>
 __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "the counter has six bits");
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
-}
-// Write-through store of 16 bytes (4-byte aligned) to base + off.
-__device__ __forceinline__ void store_through(unsigned char* base, uint32_t off, f32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, %2 sc0 sc1\n\ts_nop 1" :: "v"(off), "v"(v), "s"(base) : "memory");
-}
-__device__ __forceinline__ void store_through(unsigned char* base, uint32_t off, float v) {
-  asm volatile("global_store_dword %0, %1, %2 sc0 sc1\n\ts_nop 1" :: "v"(off), "v"(v), "s"(base) : "memory");
 }
 // This wave's LDS reads are done: what follows may land on their source.
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
@@ -111,11 +104,12 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
   float* const sm_m = reinterpret_cast<float*>(smem + p.lds_q_off);             // [wave][64]
   float* const sm_l = sm_m + NW * kPairRows;
 
-  // Grid: (chunk, KV head, sequence).  Workgroup ids go round-robin to the XCDs, so with chunks fastest every XCD works
-  // on all KV heads.  With several row blocks (KV head, row block + row_blocks * chunk, sequence): siblings share an XCD.
-  const int h = ONE ? blockIdx.y : blockIdx.x;
+  // Grid (KV head, row block + row_blocks * chunk, sequence): the 8 KV heads of a chunk, whose rows interleave in memory,
+  // run side by side on the 8 XCDs, and sibling row blocks share one (chunks fastest: 396 us instead of 380 for 16 x 36864
+  // tokens without collection).
+  const int h = blockIdx.x;
   const int rb = ONE ? 0 : static_cast<int>(blockIdx.y) % p.row_blocks;
-  const int slot_j = ONE ? static_cast<int>(blockIdx.x) : static_cast<int>(blockIdx.y) / p.row_blocks;
+  const int slot_j = ONE ? static_cast<int>(blockIdx.y) : static_cast<int>(blockIdx.y) / p.row_blocks;
   int split = slot_j;
   int b = blockIdx.z;
   int chunk_tokens = p.chunk_tokens;

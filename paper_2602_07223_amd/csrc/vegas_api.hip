@@ -298,10 +298,10 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
       // tokens, 40 rows, 15 tiles: 60 % 434 us, 75 % 430, 95 % 440, 140 % 446; without collection 395).
       const double ticks = 0.75 * lds.park_tiles * (D == 128 ? 270 : 135);
       sp.epoch_mul = static_cast<uint32_t>(4294967296.0 / (ticks < 256 ? 256 : ticks));
-      if (pl.NB == 1)
-        return launch_one(attn_pair_kernel<COLLECT, D, true>, dim3(slots, sp.Hkv, seqs), dim3(kPairWaves * 64), lds.bytes, st, sp);
-      if (static_cast<unsigned>(pl.NB) * slots > 65535u) return VEGAS_ERR_UNSUPPORTED;
-      return launch_one(attn_pair_kernel<COLLECT, D, false>, dim3(sp.Hkv, pl.NB * slots, seqs), dim3(kPairWaves * 64), lds.bytes, st, sp);
+      const dim3 pgrid(sp.Hkv, pl.NB * slots, seqs);
+      if (pgrid.y > 65535u) return VEGAS_ERR_UNSUPPORTED;       // more chunks per sequence than a grid dimension holds
+      if (pl.NB == 1) return launch_one(attn_pair_kernel<COLLECT, D, true>, pgrid, dim3(kPairWaves * 64), lds.bytes, st, sp);
+      return launch_one(attn_pair_kernel<COLLECT, D, false>, pgrid, dim3(kPairWaves * 64), lds.bytes, st, sp);
     }
   }
   // (KV head, row block + NB * chunk, sequence): the kernels read their indices off the grid without a division

@@ -65,6 +65,14 @@ __device__ __forceinline__ T gload(const unsigned char* sbase, uint32_t voff) {
   else return *ptr;
 }
 
+// Write-through store of 16 bytes (4-byte aligned) to base + off.
+__device__ __forceinline__ void store_through(unsigned char* base, uint32_t off, f32x4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, %2 sc0 sc1\n\ts_nop 1" :: "v"(off), "v"(v), "s"(base) : "memory");
+}
+__device__ __forceinline__ void store_through(unsigned char* base, uint32_t off, float v) {
+  asm volatile("global_store_dword %0, %1, %2 sc0 sc1\n\ts_nop 1" :: "v"(off), "v"(v), "s"(base) : "memory");
+}
+
 // Arguments of the KV-streaming attention kernel (verification and draft share it).
 struct SplitParams {
   const uint16_t* q;        // verify [B, G, Hq, D]; draft [B, Hq, D] (G = 1)
