@@ -382,9 +382,16 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
     ids_pending = load_ids(1);
     wave_lds_fence();
   }
-  if (tile_first < tile_end) {
-    issue_k(0, kr);
-    issue_v(0, va);
+  const int ntiles = tile_first < tile_end ? (tile_end - tile_first + NW - 1) / NW : 0;   // this wave's tiles
+  int k_first = 0;                           // the first of them that is streamed
+  if constexpr (LOCAL) {                     // ... reaches lo_min
+    const int first_tile = lo_min / kTile;
+    if (first_tile > tile_first) k_first = (first_tile - tile_first + NW - 1) / NW;
+    if (k_first >= 32 && k_first < ntiles) load_pagevec(k_first & ~31);
+  }
+  if (k_first < ntiles) {
+    issue_k(k_first, kr);
+    issue_v(k_first, va);
   }
   VEGAS_TL(kTlLoadsIssued);
 
@@ -565,20 +572,10 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
   };
 
   // ---- stream the chunk's tiles
-  if (tile_first < tile_end) {
-    const int ntiles = (tile_end - tile_first + NW - 1) / NW;      // this wave's tiles
+  if (ntiles > 0) {
     using yes = std::integral_constant<bool, true>;
     using no = std::integral_constant<bool, false>;
-    int k = 0;
-    if constexpr (LOCAL) {                   // this wave's first tile that reaches lo_min
-      const int first_tile = lo_min / kTile;
-      if (first_tile > tile_first) k = (first_tile - tile_first + NW - 1) / NW;
-      if (k > 0 && k < ntiles) {             // the preloaded tile 0 is not the first one: fetch the right one
-        if (k >= 32) load_pagevec(k & ~31);
-        issue_k(k, kr);
-        issue_v(k, va);
-      }
-    }
+    int k = k_first;
     if constexpr (LOCAL) {
       // (Local masking may leave this wave without a tile.)  This variant always steps two tiles at a time, the last
       // one possibly past the chunk's end, where every token is masked out: one loop shape less keeps it inside its

@@ -35,3 +35,23 @@ def test_chunks_of_every_length(n, chunk, Hq, Hkv, G, D):
         U.check_out(f"wide.{n}.{Hq}.{collect}", path.out_verify, ref_out, U.vmax_visible(L))
         if collect:
             U.check_scores(f"wide.{n}.{Hq}.{collect}", path.block_scores, ref_scores)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(16, 2, 64), (8, 2, 128), (96, 96, 128)], ids=["40_rows", "20_rows", "96_columns"])
+@pytest.mark.parametrize("window", [1, 128, 539, 540, 1083, 1084, 2171, 2172])
+def test_local_mask_on_both_sides_of_the_one_workgroup_rule(window, Hq, Hkv, D):
+    """The bands of 544, 1088 and 2176 tokens are where the rule changes (256 compute units); 9000 tokens make a
+    workgroup begin behind its first batch of page ids."""
+    lens = [9000, 0, 1, 4100] if Hkv == 2 else [4500]
+    L = synth.make_random_case(seed=6300 + window + Hq, batch=len(lens), num_q_heads=Hq, num_kv_heads=Hkv, num_queries=5,
+                               seq_lens=lens, head_dim=D, logit_std=1.5, value_std=1.0)
+    print(f"[case] local mask W={window} Hq={Hq} Hkv={Hkv} D={D}", flush=True)
+    dl = harness.DeviceLayer.upload(L)
+    path = harness.VegasPath.for_layer(L, budget_tokens=64, collect_rows=vb.COLLECT_NONE, window=window)
+    path.workspace.fill_(0xFF)
+    path.out_verify.fill_(float("nan"))
+    path.verify(dl)
+    torch.cuda.synchronize()
+    ref_out, _ = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens, L.softmax_scale, 0,
+                                    window=window)
+    U.check_out(f"local.{window}.{Hq}", path.out_verify, ref_out, U.vmax_visible(L))
