@@ -322,14 +322,16 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
     }
   }
   const int lg = MAXS != kFinPlanned ? 3 : (ns_live <= 4 ? 0 : (ns_live <= 8 ? 1 : (ns_live <= 16 ? 2 : 3)));   // log2 of the parts
-  const int parts = 1 << lg, units = HR << lg;
+  // (Only the collected rows' pairs: two-row collection of 48 rows and 32K tokens, verification 38.0 -> 34.0 us.)
+  const int Rc = p.Rc;                        // collected rows per KV head: the only ones whose page values were written
+  const int parts = 1 << lg, units = (p.Hkv * Rc) << lg;
   float2 v[kUnits][4];
   auto load_units = [&](int s0, int u0) {
 #pragma unroll
     for (int a = 0; a < kUnits; ++a) {
       const int u = u0 + 256 * a;
       const int i = u < units ? (u >> lg) : 0, sg = u & (parts - 1);
-      const int h = i / p.R, r = i % p.R;
+      const int h = i / Rc, r = collected_row(i % Rc, p.collect_rows, p.G, p.g);
       const float2* ml = p.part_ml + (cs.off + static_cast<int64_t>(h) * cs.stride_h) * p.R + r;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -340,7 +342,6 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
   };
   // The first batch, and (with few rows) this thread's page log-sum-exps, are
   // requested before the sequence length is needed.
-  const int Rc = p.Rc;                        // collected rows per KV head: the only ones that were written
   const bool pre_ok = (Rc & 3) == 0 && Rc <= 4 * kFinPre && p.Hkv <= 8;
   f32x4 pre[kFinPre];
   const int jpre = min(jbase + pg, p.lse_pages - 1);
@@ -388,15 +389,14 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
   }
   __syncthreads();
   for (int i = tid; i < p.Hkv * Rc; i += 256) {           // sm_row: [Hkv][Rc], the collected rows only
-    const int src = (i / Rc) * p.R + collected_row(i % Rc, p.collect_rows, p.G, p.g);
     float m = -INFINITY;
 #pragma unroll
-    for (int q = 0; q < parts; ++q) m = fmaxf(m, sm_pair[(src << lg) + q].x);
+    for (int q = 0; q < parts; ++q) m = fmaxf(m, sm_pair[(i << lg) + q].x);
     const float m_use = (m == -INFINITY) ? 0.f : m;
     float L = 0.f;
 #pragma unroll
     for (int q = 0; q < parts; ++q) {
-      const float2 pr = sm_pair[(src << lg) + q];
+      const float2 pr = sm_pair[(i << lg) + q];
       L += fast_exp2(pr.x - m_use) * pr.y;
     }
     sm_row[i] = (L > 0.f) ? m_use + fast_log2(L) : -INFINITY;
