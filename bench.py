@@ -554,7 +554,7 @@ def main() -> int:
 
     traffic = VERIFY_TRAFFIC_BYTES.get(workload) if args.verify_chunk == 0 and not token else None
     rows_per_kv_head = G * (spec.num_q_heads // spec.num_kv_heads)
-    vkernel = "attn_pair_kernel<collect>" if 32 < rows_per_kv_head <= 64 else "attn_split_kernel<causal, collect>"
+    vkernel = "attn_pair_kernel<collect>" if rows_per_kv_head > 32 else "attn_split_kernel<causal, collect>"
     roofline = {"bound": "hbm", "kernel": vkernel + " (KV-streaming kernel of vegas_verify_attention)",
                 "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": None, "traffic": traffic,
                 "bytes_per_launch": verify_bytes}

@@ -77,9 +77,9 @@ enum {
 /* Kernels of an attention call, for the `stages` argument of the vegas_debug_*_stages calls. */
 enum {
   VEGAS_STAGE_STREAM = 1,  /* the KV-streaming kernel (reads the cache, writes chunk partials) */
-  VEGAS_STAGE_MERGE = 2    /* merge of the chunk partials, and the page scores for verification; a draft call
-                              whose selection is short enough for one chunk per (sequence, KV head) has no such
-                              kernel: its streaming kernel writes `out` itself */
+  VEGAS_STAGE_MERGE = 2    /* merge of the chunk partials, and the page scores for verification; a draft call, or a
+                              verification call with a local mask, that takes one chunk per (sequence, KV head) has
+                              no such kernel: its streaming kernel writes `out` itself */
 };
 
 typedef struct vegas_desc {
@@ -102,7 +102,8 @@ typedef struct vegas_desc {
                               workgroups stream about the same number of tokens however loose max_seq_len is.
                               A sequence's chunks are a dimension of the launch grid: a chunk length under which
                               max_seq_len would need more than 65535 chunks (times up to four 32-row blocks where a
-                              KV head carries more than 64 rows) is VEGAS_ERR_UNSUPPORTED */
+                              KV head carries more than 64 rows; 33 to 64 rows with chunks of a multiple of 64 tokens
+                              are exempt) is VEGAS_ERR_UNSUPPORTED */
   int32_t reserved;        /* must be 0 */
   float   softmax_scale;   /* Eq. 1's 1/sqrt(d) */
   int32_t score_metric;    /* VEGAS_METRIC_*: what vegas_verify_attention writes to block_scores */

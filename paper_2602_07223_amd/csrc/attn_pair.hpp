@@ -42,6 +42,7 @@ namespace vegas {
 constexpr int kPairWaves = 4;
 constexpr int kPairRows = 64;               // query rows (of one KV head) of a workgroup
 constexpr int kPairRing = 32 * 1024;        // bytes of K and V tiles per wave
+constexpr int kPairFold = 32768;           // chunks per round of a folded grid
 constexpr float kPairSlack = 8.0f;          // log2 of how far a logit may exceed its row's reference maximum
 
 // 64 lanes x 16 bytes from (base + lane offset) to LDS [lds, lds + 1 KB), for N lane offsets and consecutive kilobytes.
@@ -107,17 +108,23 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
   // Grid (KV head, row block + row_blocks * chunk, sequence): the 8 KV heads of a chunk, whose rows interleave in memory,
   // run side by side on the 8 XCDs, and sibling row blocks share one (chunks fastest: 396 us instead of 380 for 16 x 36864
   // tokens without collection).
+  // More than 65535 row blocks and chunks: the grid's third dimension goes round the sequences once per kPairFold of them.
   const int h = blockIdx.x;
-  const int rb = ONE ? 0 : static_cast<int>(blockIdx.y) % p.row_blocks;
-  const int slot_j = ONE ? static_cast<int>(blockIdx.y) : static_cast<int>(blockIdx.y) / p.row_blocks;
+  int b = blockIdx.z, yy = blockIdx.y;
+  const int seqs = p.plan ? 1 : p.batch;
+  if (b >= seqs) {
+    yy += b / seqs * kPairFold;
+    b %= seqs;
+  }
+  const int rb = ONE ? 0 : yy % p.row_blocks;
+  const int slot_j = ONE ? yy : yy / p.row_blocks;
   int split = slot_j;
-  int b = blockIdx.z;
   int chunk_tokens = p.chunk_tokens;
   int64_t pbase = (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + split;   // this workgroup's partial slot
   if (p.plan) {                              // balanced chunking: slot j of this head -> (sequence, chunk)
     const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2,
                                           p.chunk_cap_units, p.chunk_unit, slot_j,
-                                          ((blockIdx.x | blockIdx.y) == 0 && wave == 0) ? p.plan : nullptr);
+                                          ((blockIdx.x | yy) == 0 && wave == 0) ? p.plan : nullptr);
     if (bs.b < 0) return;
     b = __builtin_amdgcn_readfirstlane(bs.b);
     split = __builtin_amdgcn_readfirstlane(bs.split);

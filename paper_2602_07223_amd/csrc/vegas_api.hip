@@ -305,8 +305,17 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
       // tokens, 40 rows, 15 tiles: 60 % 434 us, 75 % 430, 95 % 440, 140 % 446; without collection 395).
       const double ticks = 0.75 * lds.park_tiles * (D == 128 ? 270 : 135);
       sp.epoch_mul = static_cast<uint32_t>(4294967296.0 / (ticks < 256 ? 256 : ticks));
-      const dim3 pgrid(sp.Hkv, pl.NB * slots, seqs);
-      if (pgrid.y > 65535u) return VEGAS_ERR_UNSUPPORTED;       // more chunks per sequence than a grid dimension holds
+      dim3 pgrid(sp.Hkv, pl.NB * slots, seqs);
+      // Chunks are a dimension of the grid and calls with too many of them are refused, counted in 32-row blocks; up to
+      // 64 rows with chunks of whole 64-token steps were never subject to that, and the grid is folded for them.
+      const int tile_rows = pl.R + (COLLECT == 2 ? 2 : 0);
+      const bool folds = pl.R > 32 && tile_rows <= kPairRows && pl.chunk % (2 * kTile) == 0;
+      if (!folds && static_cast<uint64_t>((tile_rows + 31) / 32) * slots > 65535u) return VEGAS_ERR_UNSUPPORTED;
+      if (pgrid.y > 65535u) {
+        pgrid.z = seqs * ((pgrid.y + kPairFold - 1) / kPairFold);
+        pgrid.y = kPairFold;
+        if (pgrid.z > 65535u) return VEGAS_ERR_UNSUPPORTED;
+      }
       if (pl.NB == 1) return launch_one(attn_pair_kernel<COLLECT, D, true>, pgrid, dim3(kPairWaves * 64), lds.bytes, st, sp);
       return launch_one(attn_pair_kernel<COLLECT, D, false>, pgrid, dim3(kPairWaves * 64), lds.bytes, st, sp);
     }

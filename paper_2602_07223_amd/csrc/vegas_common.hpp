@@ -89,7 +89,7 @@ struct SplitParams {
   int32_t G, g, R, Hq, Hkv;
   int32_t chunk_tokens, nsplit, lse_pages, max_tokens;
   int32_t lds_q_off;        // byte offset of the query tile inside dynamic LDS
-  int32_t row_blocks;       // ceil(R / 32): 32-row blocks of one KV head, one workgroup each
+  int32_t row_blocks;       // row blocks of one KV head (32 rows; attn_pair_kernel: 64), one workgroup each
   int32_t collect_rows;     // which verification rows are collected (1: all, 2: first and last)
   int32_t Rc;               // collected rows per KV head (collected_count)
   int32_t window;           // > 0: local masking, a row at position pos sees keys pos - window + 1 .. pos (causal calls)

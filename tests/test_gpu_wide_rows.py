@@ -55,3 +55,38 @@ def test_local_mask_on_both_sides_of_the_one_workgroup_rule(window, Hq, Hkv, D):
     ref_out, _ = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens, L.softmax_scale, 0,
                                     window=window)
     U.check_out(f"local.{window}.{Hq}", path.out_verify, ref_out, U.vmax_visible(L))
+
+
+def folded_call(G, chunk):
+    max_len = chunk * 65537
+    L = synth.make_random_case(seed=6400 + G, batch=2, num_q_heads=11, num_kv_heads=1, num_queries=G, seq_lens=[200, 77],
+                               head_dim=64, logit_std=1.5, value_std=1.0)
+    dl = harness.DeviceLayer.upload(L)
+    blocks = max_len // 16
+    table = torch.zeros((2, blocks), dtype=torch.int32, device=dl.block_table.device)
+    table[:, :dl.block_table.shape[1]] = dl.block_table
+    dl.block_table = table
+    path = harness.VegasPath(batch=2, num_q_heads=11, num_kv_heads=1, num_queries=G, max_blocks=blocks, max_seq_len=max_len,
+                             num_pages=L.num_pages, budget_tokens=64, softmax_scale=L.softmax_scale, head_dim=64,
+                             verify_chunk=chunk)
+    return L, dl, path
+
+
+def test_more_chunks_than_a_grid_dimension_holds():
+    """max_seq_len of 65537 chunks of 64 tokens (the lengths themselves are short), 33 rows: the grid is folded."""
+    L, dl, path = folded_call(3, 64)
+    print("[case] folded grid", flush=True)
+    path.verify(dl)
+    torch.cuda.synchronize()
+    ref_out, ref_scores = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens, L.softmax_scale,
+                                             vb.COLLECT_ALL_ROWS)
+    U.check_out("folded", path.out_verify, ref_out, U.vmax_visible(L))
+    U.check_scores("folded", path.block_scores[:, :ref_scores.shape[1]], ref_scores)
+    assert not path.block_scores[:, ref_scores.shape[1]:].any()
+
+
+@pytest.mark.parametrize("G,chunk", [(3, 32), (6, 64)], ids=["33_rows_odd_chunk", "66_rows"])
+def test_too_many_chunks_are_refused(G, chunk):
+    _, dl, path = folded_call(G, chunk)
+    with pytest.raises(vb.VegasError, match="not supported"):
+        path.verify(dl)
