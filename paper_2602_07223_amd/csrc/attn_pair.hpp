@@ -31,6 +31,7 @@
 // 16 of 8192..65536 tokens 483 -> 441; one sequence of 32768 25.8 -> 19.8 us at head dimension 64, 48 rows at 128 40.2 ->
 // 27.9: against the kernel this one replaced, which passed K and V through the registers of two waves and their LDS
 // tiles between two barriers per 64 tokens.  What bounds it: HBM from 64K tokens on, its head and merge below.
+// (Taken with the rarer rescaling; the true maximum adds 0.2 % to the long launches and 1 us to the 32K one.)
 // Rows beyond 64 go to sibling workgroups of 64 rows each.
 #pragma once
 #include <type_traits>
