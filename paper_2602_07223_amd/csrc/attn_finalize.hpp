@@ -18,17 +18,16 @@ struct RowMerge {
   f32x2 mine;        // (max, sum) of chunk `lane`
   float x[MAXS];     // this thread's head dim of every chunk's partial row
   // ml, po: the row's first chunk (wave-uniform); d: head dim of this thread
-  // last: the largest chunk index whose slot may be read (slots past the row's chunks are loaded and discarded)
-  __device__ __forceinline__ void issue(const float2* ml, const float* po, int d, int R, int last_slot, int D) {
+  // last: the largest chunk index whose slot may be read, not negative (slots past the row's chunks are loaded and discarded)
+  __device__ __forceinline__ void issue(const float2* ml, const float* po, int d, int R, int last, int D) {
     const int lane = threadIdx.x & 63;
     const unsigned char* mlb = uniform_ptr(reinterpret_cast<const unsigned char*>(ml));
     const unsigned char* pob = uniform_ptr(reinterpret_cast<const unsigned char*>(po));
-    const uint32_t last = static_cast<uint32_t>(last_slot);
-    mine = gload<f32x2, false>(mlb, min(static_cast<uint32_t>(lane), last) * static_cast<uint32_t>(R) * 8u);
+    mine = gload<f32x2, false>(mlb, requested_slot(lane, last) * static_cast<uint32_t>(R) * 8u);
     const uint32_t stride = static_cast<uint32_t>(R) * static_cast<uint32_t>(D) * 4u;
     const uint32_t off = static_cast<uint32_t>(d) * 4u;
 #pragma unroll
-    for (int s = 0; s < MAXS; ++s) x[s] = gload<float, false>(pob, off + min(static_cast<uint32_t>(s), last) * stride);
+    for (int s = 0; s < MAXS; ++s) x[s] = gload<float, false>(pob, off + requested_slot(s, last) * stride);
     __builtin_amdgcn_sched_barrier(0);     // every request leaves before the first use
   }
   // Output element: sum_s 2^(m_s - m) x_s / sum_s 2^(m_s - m) l_s over the first ns chunks; 0 if no key was visible.
@@ -70,7 +69,8 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p
   int n = p.lens[b];
   n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
   const ColumnSlots cs = column_slots(p.plan, p.slots_total, b, p.Hkv, p.nsplit, p.chunk_tokens);
-  const int ns = (n + cs.chunk - 1) / cs.chunk;
+  const ColumnChunks cc = column_chunks(cs, n);
+  const int ns = cc.ns;
   const int64_t pbase = cs.off + static_cast<int64_t>(h) * cs.stride_h;
   const float2* ml = p.part_ml + pbase * p.R + r;                 // stride R between chunks
   const float* po = p.part_o + (pbase * p.R + r) * T + tid;       // stride R*D between chunks
@@ -79,11 +79,14 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p
   const int s_lo = first_live_chunk(n, p.G, p.window, cs.chunk);   // earlier chunks were skipped (local masking)
   const int t = r / p.g, j = r % p.g;
   uint16_t* const out = p.out + ((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * T + tid;
+  if (cc.last < 0) {                         // an empty sequence: it may own no slot, so nothing is requested
+    *out = 0;
+    return;
+  }
   if (ns <= 32) {
-    const int last = min(cs.last, max(ns - 1, 0));
     auto merge = [&](auto maxs) {
       RowMerge<decltype(maxs)::value> rm;
-      rm.issue(ml, po - tid, tid, p.R, last, T);
+      rm.issue(ml, po - tid, tid, p.R, cc.last, T);
       return rm.finish(ns, s_lo);
     };
     float o;
@@ -196,27 +199,34 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
     } else {
       int n = p.lens[b];
       n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
-      const int ns = (n + cs.chunk - 1) / cs.chunk;
+      const ColumnChunks cc = column_chunks(cs, n);
+      const int ns = cc.ns;
+      auto store = [&](uint16_t bits) {
+        if (valid) {
+          const int t = r / p.g, j = r % p.g;
+          p.out[((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * T + t128] = bits;
+        }
+      };
+      if (cc.last < 0) {                     // an empty sequence: it may own no slot, so nothing is requested
+        store(0);
+        return;
+      }
       // Balanced chunking (the plan has to be read before anything can be addressed, so the length is known by now):
       // a sequence has few of its head's slots, and only those are read.  (Reading as many as the host's bound allows,
       // most of them other sequences', took the whole kernel 30 us on 24 sequences of 1K..20K tokens with 32 rows; this
       // and the smaller score role below take 13.7.  16 of 8K..64K tokens, 40 rows: 33 -> 24 us.)
       if (MAXS == kFinPlanned && ns <= 32) {
         const float* const po = p.part_o + (pbase * p.R + r) * T;
-        const int last = min(cs.last, max(ns - 1, 0));
         auto merge = [&](auto maxs) {
           RowMerge<decltype(maxs)::value> rm;
-          rm.issue(ml, po, t128, p.R, last, T);
+          rm.issue(ml, po, t128, p.R, cc.last, T);
           return rm.finish(ns);
         };
         if (ns <= 4) o = merge(std::integral_constant<int, 4>{});
         else if (ns <= 8) o = merge(std::integral_constant<int, 8>{});
         else if (ns <= 16) o = merge(std::integral_constant<int, 16>{});
         else o = merge(std::integral_constant<int, 32>{});
-        if (valid) {
-          const int t = r / p.g, j = r % p.g;
-          p.out[((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * T + t128] = float_to_bf16_bits(o);
-        }
+        store(float_to_bf16_bits(o));
         return;
       }
       const float* po = p.part_o + (pbase * p.R + r) * T + t128;

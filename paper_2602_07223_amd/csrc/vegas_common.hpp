@@ -231,7 +231,7 @@ struct ColumnSlots {
   int64_t off;
   int32_t stride_h, chunk, last;
 };
-__device__ __forceinline__ ColumnSlots column_slots(const int2* plan, int slots_total, int b, int Hkv, int nsplit,
+__host__ __device__ __forceinline__ ColumnSlots column_slots(const int2* plan, int slots_total, int b, int Hkv, int nsplit,
                                                     int chunk_tokens) {
   ColumnSlots c;
   if (plan) {
@@ -247,6 +247,23 @@ __device__ __forceinline__ ColumnSlots column_slots(const int2* plan, int slots_
     c.last = nsplit - 1;
   }
   return c;
+}
+// Chunks of n tokens in such a column, and the largest slot that a merge which knows n requests: its last chunk's; none
+// (last < 0) for an empty sequence, which may own no slot at all: in a plan whose chunks fill every slot it starts one
+// past the last of them.
+struct ColumnChunks {
+  int32_t ns, last;
+};
+__host__ __device__ __forceinline__ ColumnChunks column_chunks(const ColumnSlots& cs, int n) {
+  ColumnChunks c;
+  c.ns = (n + cs.chunk - 1) / cs.chunk;
+  c.last = cs.last < c.ns - 1 ? cs.last : c.ns - 1;
+  return c;
+}
+// The slot that a merge requests for chunk s of a column whose slots 0 .. last (>= 0) may be read.
+__host__ __device__ __forceinline__ uint32_t requested_slot(int s, int last) {
+  const uint32_t a = static_cast<uint32_t>(s), b = static_cast<uint32_t>(last);
+  return a < b ? a : b;
 }
 
 // Balanced chunking of a batch (B <= 64 sequences, lengths < 2^24), computed identically by every wave that

@@ -32,3 +32,24 @@ def test_planned_sequences_with_every_chunk_count(chunks, Hq):
         U.check_out(f"planned.{chunks}.{collect}", path.out_verify, ref_out, U.vmax_visible(L))
         if collect:
             U.check_scores(f"planned.{chunks}", path.block_scores, ref_scores)
+
+
+@pytest.mark.parametrize("collect", [vb.COLLECT_NONE, vb.COLLECT_ALL_ROWS], ids=["none", "all_rows"])
+@pytest.mark.parametrize("lens", [[4096, 0], [0, 4096, 0], [0, 0]], ids=str)
+def test_empty_members_of_a_plan_that_fills_every_slot(lens, collect):
+    """32 chunks of 128 tokens are all the slots a head has (8 KV heads, 256 compute units): an empty sequence owns none,
+    and its rows are zeros whatever the workspace holds."""
+    L = synth.make_random_case(seed=41200 + len(lens), batch=len(lens), num_q_heads=64, num_kv_heads=8, num_queries=5,
+                               seq_lens=lens, logit_std=2.0, value_std=1.0)
+    print(f"[case] planned merge, lengths {lens}, collect={collect}", flush=True)
+    dl = harness.DeviceLayer.upload(L)
+    path = harness.VegasPath.for_layer(L, budget_tokens=256, collect_rows=collect)
+    path.workspace.fill_(0xFF)
+    path.out_verify.fill_(float("nan"))
+    path.verify(dl)
+    torch.cuda.synchronize()
+    ref_out, _ = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens, L.softmax_scale,
+                                    vb.COLLECT_ALL_ROWS)
+    U.check_out(f"planned.empty.{lens}.{collect}", path.out_verify, ref_out, U.vmax_visible(L))
+    for b, n in enumerate(lens):
+        assert n or not path.out_verify[b].any()

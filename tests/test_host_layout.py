@@ -1,0 +1,84 @@
+"""Index arithmetic that kernels and host code share, checked on the CPU: the headers' host-callable functions are compiled
+into a small program and compared with the rules written out here."""
+import os
+import subprocess
+
+import numpy as np
+
+from paper_2602_07223_amd import build
+
+
+def run_host_program(tmp_path, body: str, stdin: str = "") -> str:
+    """Compiles `body` (a main() that may include the library's headers) for the host only and runs it."""
+    src, exe = tmp_path / "probe.hip", tmp_path / "probe"
+    src.write_text(body)
+    cmd = [build.hipcc_path(), "--cuda-host-only", "-std=c++17", "-O1", "-I", build.CSRC, str(src), "-o", str(exe)]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([str(exe)], input=stdin, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    return r.stdout
+
+
+def balanced_plan(lens, j1, j2, unit):
+    """Balanced chunking by its definition: (first slot, chunk tokens) per sequence, chunks per sequence."""
+    nu = [-(-n // unit) for n in lens]
+
+    def smallest(J):
+        return next(c for c in range(1, max(nu) + 1) if c == max(nu) or sum(-(-x // c) for x in nu) <= J)
+
+    if sum(nu) == 0:
+        return [(0, unit)] * len(lens), [0] * len(lens)
+    C = smallest(j1)
+    if j2 > j1 and 10 * sum(nu) < 9 * j1 * C:
+        C = smallest(j2)
+    s = [-(-x // C) for x in nu]
+    chunk = [(-(-x // k)) * unit if k else 0 for x, k in zip(nu, s)]
+    first = [sum(s[i] for i in range(len(lens)) if chunk[i] > chunk[b] or (chunk[i] == chunk[b] and i < b))
+             for b in range(len(lens))]
+    return [(f, c or unit) for f, c in zip(first, chunk)], s
+
+
+SLOTS = r'''
+#include <cstdio>
+#include "vegas_common.hpp"
+int main() {                       // lines of: slots of a head, number of KV heads, first slot, chunk tokens, tokens
+  int slots, heads, first, chunk, n;
+  while (std::scanf("%d %d %d %d %d", &slots, &heads, &first, &chunk, &n) == 5) {
+    const int2 plan = {first, chunk};
+    const vegas::ColumnSlots cs = vegas::column_slots(&plan, slots, 0, heads, 0, 0);
+    const vegas::ColumnChunks cc = vegas::column_chunks(cs, n);
+    long long most = -1;           // largest slot the merge of this column requests (lane s asks for chunk s)
+    if (cc.last >= 0)
+      for (int s = 0; s < 64; ++s) most = cs.off + vegas::requested_slot(s, cc.last);
+    std::printf("%lld %d %d %lld\n", static_cast<long long>(cs.off), cs.stride_h, cc.ns, most);
+  }
+}
+'''
+
+
+def test_planned_merges_request_a_sequences_own_slots_only(tmp_path):
+    """Batches whose chunks fill every slot of a head, some with empty members (which start one past the last slot and own
+    none): a merge requests slots of its own column and none of an empty one's."""
+    unit, heads = 128, 8
+    rng = np.random.default_rng(7)
+    batches = [[4096, 0], [0, 4096], [4096, 0, 0, 0], [0, 0, 12288], [0, 0], [1, 0], [2048, 2048], [2048, 0, 2048],
+               [36864] * 7 + [0], [65536, 0] * 8, [128] * 16 + [0] * 16]
+    batches += [[int(n) for n in rng.integers(0, 6000, size=b) * rng.integers(0, 2, size=b)]
+                for b in rng.integers(2, 33, size=60)]
+    cases = []
+    for lens in batches:
+        j1 = 32
+        j2 = 64 if len(lens) >= 8 else 32
+        slots = max(j2, len(lens))
+        plan, s = balanced_plan(lens, j1, j2, unit)
+        assert sum(s) <= slots
+        cases += [(slots, heads, *plan[b], lens[b], s[b]) for b in range(len(lens))]
+    # the case this is about is among them: an empty sequence that starts one past the last slot of its head
+    assert any(first == slots and n == 0 for slots, _, first, _, n, _ in cases)
+    out = run_host_program(tmp_path, SLOTS, "\n".join(" ".join(map(str, c[:5])) for c in cases))
+    for (slots, _, first, chunk, n, s), line in zip(cases, out.strip().split("\n"), strict=True):
+        off, stride, ns, most = map(int, line.split())
+        assert (off, stride, ns) == (first, slots, s), (first, chunk, n)
+        assert most == (first + min(64, s) - 1 if s else -1), (slots, first, chunk, n, most)
+        assert most < slots
