@@ -46,6 +46,12 @@ constexpr int kPairRows = 64;               // query rows (of one KV head) of a 
 constexpr int kPairRing = 32 * 1024;        // bytes of K and V tiles per wave
 constexpr int kPairFold = 32768;           // chunks per round of a folded grid
 
+// Floats of one wave's parked values: park_tiles tiles of two pages x the collected rows a workgroup can have, or of the
+// high and low token sums.  (A multiple of four: a wave reads them in 16-byte pieces; see pair_lds.)
+__host__ __device__ __forceinline__ int pair_park_floats(int park_tiles, int Rc, int collect) {
+  return park_tiles * 2 * (collect == 2 ? kTile : (Rc < kPairRows ? Rc : kPairRows));
+}
+
 // 64 lanes x 16 bytes from (base + lane offset) to LDS [lds, lds + 1 KB), for N lane offsets and consecutive kilobytes.
 // Nothing is returned in registers; the load counter counts one per kilobyte.  (Assembly, because the compiler makes every
 // LDS read that follows the builtin wait for all such loads.  M0 has no other use on gfx950 than these instructions.)
@@ -250,7 +256,7 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
         p.page_lse + (static_cast<int64_t>(b) * p.Hkv + h) * p.lse_pages + kTile * tile_first);
   }
   if constexpr (COLLECT != 0)
-    park = reinterpret_cast<float*>(qlds + qrows * kRowPitch) + wave * p.park_tiles * (COLLECT == 2 ? 2 * kTile : 2 * min(p.Rc, kPairRows));
+    park = reinterpret_cast<float*>(qlds + qrows * kRowPitch) + wave * pair_park_floats(p.park_tiles, p.Rc, COLLECT);
   int parked = 0, flushed = 0;               // tiles parked now; tiles that left before them
   uint32_t epoch = 0;
   auto clock_epoch = [&]() -> uint32_t {     // number of the wall-clock interval (100 MHz ticks, the same on every unit)
@@ -561,9 +567,10 @@ inline PairLds pair_lds(int R, int Rc, int row_blocks, int collect, int D) {
   size_t before = kPairWaves * kPairRing + q;
   PairLds l = {0, 0, 0};
   if (collect != 0) {
-    const size_t tile = 2 * sizeof(float) * (collect == 2 ? kTile : (Rc < kPairRows ? Rc : kPairRows));
+    const size_t tile = sizeof(float) * pair_park_floats(1, Rc, collect);
     l.park_tiles = static_cast<int>((160 * 1024 - rows_ml - before) / (kPairWaves * tile));
     if (l.park_tiles > 64) l.park_tiles = 64;
+    if (tile % 16) l.park_tiles &= ~1;       // (an odd number of collected rows: tiles of 8 bytes more than a multiple of 16)
     before += kPairWaves * tile * l.park_tiles;
   }
   const size_t red = static_cast<size_t>(kPairWaves) * (R < kPairRows ? R : kPairRows) * red_pitch(D) * sizeof(float);

@@ -37,6 +37,27 @@ def test_chunks_of_every_length(n, chunk, Hq, Hkv, G, D):
             U.check_scores(f"wide.{n}.{Hq}.{collect}", path.block_scores, ref_scores)
 
 
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("Hq,Hkv,G", [(28, 4, 7), (37, 1, 1), (61, 1, 1)], ids=["49_rows", "37_rows", "61_rows"])
+def test_odd_numbers_of_collected_rows(Hq, Hkv, G, D):
+    """Row counts with which an odd number of parked tiles would leave waves 1 and 3 between two 16-byte pieces of the LDS:
+    one chunk long enough that every wave writes out what it has parked more than once."""
+    L = synth.make_random_case(seed=6200 + Hq + D, batch=1, num_q_heads=Hq, num_kv_heads=Hkv, num_queries=G,
+                               seq_lens=[4133], head_dim=D, logit_std=2.0, value_std=1.0, outliers=2, outlier_logit=25.0)
+    print(f"[case] odd collected rows Hq={Hq} Hkv={Hkv} G={G} D={D}", flush=True)
+    dl = harness.DeviceLayer.upload(L)
+    path = harness.VegasPath.for_layer(L, budget_tokens=256, verify_chunk=4160)
+    path.workspace.fill_(0xFF)
+    path.out_verify.fill_(float("nan"))
+    path.block_scores.fill_(float("nan"))
+    path.verify(dl)
+    torch.cuda.synchronize()
+    ref_out, ref_scores = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens, L.softmax_scale,
+                                             vb.COLLECT_ALL_ROWS)
+    U.check_out(f"odd.{Hq}.{D}", path.out_verify, ref_out, U.vmax_visible(L))
+    U.check_scores(f"odd.{Hq}.{D}", path.block_scores, ref_scores)
+
+
 @pytest.mark.parametrize("Hq,Hkv,D", [(16, 2, 64), (8, 2, 128), (96, 96, 128)], ids=["40_rows", "20_rows", "96_columns"])
 @pytest.mark.parametrize("window", [1, 128, 539, 540, 1083, 1084, 2171, 2172])
 def test_local_mask_on_both_sides_of_the_one_workgroup_rule(window, Hq, Hkv, D):

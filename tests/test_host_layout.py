@@ -82,3 +82,34 @@ def test_planned_merges_request_a_sequences_own_slots_only(tmp_path):
         assert (off, stride, ns) == (first, slots, s), (first, chunk, n)
         assert most == (first + min(64, s) - 1 if s else -1), (slots, first, chunk, n, most)
         assert most < slots
+
+
+PARKS = r'''
+#include <cstdio>
+#include "attn_pair.hpp"
+int main() {                       // lines of: query rows, collected rows, collection mode, head dimension
+  int R, Rc, collect, D;
+  while (std::scanf("%d %d %d %d", &R, &Rc, &collect, &D) == 4) {
+    const int tile_rows = R + (collect == 2 ? 2 : 0), blocks = (tile_rows + vegas::kPairRows - 1) / vegas::kPairRows;
+    const vegas::PairLds lds = vegas::pair_lds(R, Rc, blocks, collect, D);
+    const int queries = (blocks == 1 ? tile_rows : vegas::kPairRows) * vegas::row_pitch(D);
+    std::printf("%d %d %zu %zu %zu\n", lds.park_tiles, vegas::pair_park_floats(lds.park_tiles, Rc, collect),
+                static_cast<size_t>(vegas::kPairWaves * vegas::kPairRing + queries), lds.off_max, lds.bytes);
+  }
+}
+'''
+
+
+def test_parked_values_of_every_wave_are_aligned(tmp_path):
+    """64-row workgroups: a wave reads what it has parked in 16-byte pieces, so its part of the LDS starts on a multiple of
+    16 bytes and ends before the row maxima, for every row count, collection mode and head dimension."""
+    cases = [(R, Rc, collect, D) for D in (128, 64) for R in range(31, 129)
+             for collect, rcs in ((1, {R} | {2 * g for g in range(1, 43) if R % g == 0 and R // g > 2}), (2, {R}))
+             for Rc in sorted(rcs) if R + (2 if collect == 2 else 0) > 32]
+    out = run_host_program(tmp_path, PARKS, "\n".join(" ".join(map(str, c)) for c in cases))
+    for case, line in zip(cases, out.strip().split("\n"), strict=True):
+        tiles, floats, parks, off_max, total = map(int, line.split())
+        R, Rc, collect, _ = case
+        assert tiles >= 2 and floats >= tiles * 2 * (32 if collect == 2 else min(Rc, 64)), case
+        assert parks % 16 == 0 and floats % 4 == 0, case
+        assert parks + 4 * floats * 4 <= off_max and total <= 160 * 1024, case
