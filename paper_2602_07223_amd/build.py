@@ -50,14 +50,14 @@ def build_library(verbose: bool = True, extra_flags=(), timeline: bool = False) 
     return out
 
 
-def kernel_resource_usage() -> dict:
-    """Compiles the device code once more (nothing is written) with the compiler's resource report switched on and
+def kernel_resource_usage(asm_path: str = os.devnull) -> dict:
+    """Compiles the device code once more (to assembly, written to asm_path) with the compiler's resource report switched on and
     returns {demangled kernel name: {"vgprs", "agprs", "sgprs", "scratch_bytes_per_lane", "lds_bytes", "occupancy"}}.
     Used by the CPU tests to hold the streaming kernels to zero scratch (no register spills)."""
     import re
     build_flags = [f for f in FLAGS if f not in ("-shared", "-fPIC")]
-    cmd = [hipcc_path(), *build_flags, "-c", "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage",
-           "-o", os.devnull] + [os.path.join(CSRC, s) for s in SOURCES]
+    cmd = [hipcc_path(), *build_flags, "-S", "--cuda-device-only", "-Rpass-analysis=kernel-resource-usage",
+           "-o", asm_path] + [os.path.join(CSRC, s) for s in SOURCES]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + res.stderr)

@@ -54,7 +54,8 @@ __host__ __device__ __forceinline__ int pair_park_floats(int park_tiles, int Rc,
 
 // 64 lanes x 16 bytes from (base + lane offset) to LDS [lds, lds + 1 KB), for N lane offsets and consecutive kilobytes.
 // Nothing is returned in registers; the load counter counts one per kilobyte.  (Assembly, because the compiler makes every
-// LDS read that follows the builtin wait for all such loads.  M0 has no other use on gfx950 than these instructions.)
+// LDS read that follows the builtin wait for all such loads.  M0 cannot be declared as overwritten, it is a reserved
+// register; the build report's test holds these kernels to no other use of it.)
 // STREAMING: with the non-temporal hint (16 x 36864 tokens without collection 399 us against 446).
 template <int N, bool STREAMING>
 __device__ __forceinline__ void load_to_lds(uint32_t lds, const unsigned char* base, const uint32_t (&off)[N]) {

@@ -1,16 +1,24 @@
 """The compiler's own resource report for the device code (CPU only: hipcc cross-compiles without a GPU): no kernel
 of the library may use scratch memory -- a register spill in a KV-streaming kernel costs it the very loads it is
 built to keep in flight -- and the streaming kernels must fit two waves per SIMD (256 registers per lane)."""
+import re
+
 import pytest
 
 from paper_2602_07223_amd import build
 
 
 @pytest.fixture(scope="module")
-def usage():
-    u = build.kernel_resource_usage()
+def report(tmp_path_factory):
+    path = tmp_path_factory.mktemp("asm") / "device.s"
+    u = build.kernel_resource_usage(str(path))
     assert u, "the compiler printed no resource report"
-    return u
+    return u, path.read_text()
+
+
+@pytest.fixture(scope="module")
+def usage(report):
+    return report[0]
 
 
 def test_no_kernel_spills_registers(usage):
@@ -24,3 +32,24 @@ def test_streaming_kernels_fit_two_waves_per_simd(usage):
     for name, v in streaming.items():
         assert v["vgprs"] + v.get("agprs", 0) <= 256, (name, v)
         assert v["occupancy"] >= 2, (name, v)
+
+
+def foreign_m0_lines(asm: str):
+    """Lines of each attn_pair_kernel in the assembly that mention M0, other than the three-instruction loads into LDS of
+    its inline assembly; and the number of those loads."""
+    loads, foreign = 0, []
+    for body in re.findall(r"^_ZN5vegas16attn_pair_kernel\w*:(.*?)^\.Lfunc_end", asm, flags=re.M | re.S):
+        body = re.sub(r"[ \t]*;.*", "", body)
+        own = re.compile(r"s_mov_b32 m0, s\d+\s+s_nop 0\s+global_load_lds_dwordx4 v\d+, s\[\d+:\d+\]")
+        loads += len(own.findall(body))
+        foreign += [line.strip() for line in own.sub("", body).splitlines() if re.search(r"\bm0\b|global_load_lds", line)]
+    return loads, foreign
+
+
+def test_m0_belongs_to_the_loads_into_lds(report):
+    """attn_pair_kernel writes M0 in inline assembly and cannot say so (a reserved register): the compiler must not use it
+    in these kernels."""
+    loads, foreign = foreign_m0_lines(report[1])
+    assert loads >= 12 * 16 and not foreign, (loads, foreign[:4])
+    planted = report[1].replace("s_nop 0\n\tglobal_load_lds", "v_readlane_b32 s0, v1, m0\n\ts_nop 0\n\tglobal_load_lds", 1)
+    assert foreign_m0_lines(planted)[1]
