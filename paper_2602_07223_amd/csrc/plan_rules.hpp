@@ -1,0 +1,46 @@
+// Rules by which the host decides how a call is cut into chunks (pure host code).
+#pragma once
+#include <cstdint>
+
+namespace vegas {
+
+// Draft calls of up to kDraftRows rows per KV head (attn_draft16_kernel): the longest selection that one workgroup per
+// column (sequence x KV head) streams by itself, writing the output rows; a longer one is cut into chunks that a second
+// launch merges.  A single workgroup takes 0.3 us per 32 tokens at head dimension 128 (0.18 at 64) behind 3.4 us and no
+// other helps it, the merge costs 2.5-4 us; with many columns the chip is full either way, with few it idles beside a
+// long selection.  The rule sees the batch's bound only, so it has to hold for selections of unequal length as well.
+// Microseconds of a draft call within a GPU-bound iteration (captured; 6 draft calls), one workgroup minus chunks; equal
+// selections / between a tenth and all of the bound / one at the bound beside others of 256 tokens:
+//   columns   head dimension 128                                  head dimension 64
+//     8..48   416 tokens -0.1, 448 +0.2, 512 +0.7, 544 +1.0       544 -0.4, 608 0.0, 672 +0.2, 1056 +2.1   (all equal)
+//    64..80   512 +0.3..-1.7, 544 -0.8, 800 +1.6                  736 -0.4..-0.6, 800 0.0, 1056 +0.5       (all equal)
+//       96    800 -1.0/-0.8/-0.7, 1056 0.0/+1.5/+1.6              928 -0.7/-0.7/-0.7, 1056 -0.1/-0.2/-0.1 (one-token pages: +1.1)
+//      128    1056 -2.4/+0.3/+1.1, 1312 -2.2/+0.8/+2.6            1056 -1.5/-0.5/-0.2, 1312 -1.1/-0.3/+0.6
+//      144    1312 -5.0/-3.7/+0.7                                 1312 -3.9/-2.3/-0.3
+//      160    1312 -4.4/-3.7/+0.2, 2080 -3.8/-1.6/+6.4            1312 -3.9/-2.8/-0.4, 2080 -4.3/-1.9/+3.1
+//      192    2080 -4.0/-4.5/+2.8, 3104 -6.3/-5.3/+7.7            2080 -4.4/-3.3/+1.0, 4128 -6.4/-6.0/+5.9
+//      256    2080 -6.0/-5.0/+3.0, 4128 -23/-4.5/+13              2080 -3.4/-4.2/+0.5, 4128 -5.3/-5.5/+5.4
+//      512    2080 -37/-26/-3.4, 4128 -23/+7.6/+15                2080 -30/-9.4/-5.5, 4128 -15/-2.9/+5.1
+// The lines lie where equal lengths gain and spread ones lose less than half a microsecond; a lone long selection costs up
+// to 3 us more there (192 columns, 2080 tokens: 19 -> 22 us), beyond them up to tens of microseconds.
+inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
+  struct Line { int sixteenths, tokens128, tokens64; };   // from that share of the compute units on
+  constexpr Line lines[] = {{12, 2176, 2176}, {9, 1312, 1312}, {8, 1056, 1056}, {6, 800, 928}, {4, 544, 736}, {0, 416, 608}};
+  for (const Line& l : lines)
+    if (16 * columns >= static_cast<int64_t>(l.sixteenths) * num_cu) return head_dim == 64 ? l.tokens64 : l.tokens128;
+  return 0;
+}
+
+// Verification with a local mask: does one workgroup per column (sequence x KV head x row block) stream the whole band
+// (`seen` = window + queries tokens, no row sees more) and write the output rows, or is the context cut into chunks
+// (`chunk` tokens, of which the band touches a few) and merged?  Cutting only helps where the chunks are shorter than the
+// band: us, chunks + merge / one workgroup, head dimension 128, 20 rows, by chunk length and band:
+//   128: 261 10.8 / 10.2, 389 10.8 / 10.0, 517 10.9 / 12.3, 1029 11.0 / 16.3;   256 (40 rows): 389 10.6 / 10.3, 517 10.6 / 12.6
+//   1024: 517 15.3 / 12.4, 1029 16.9 / 16.7;   1792: 1029 19.8 / 17.6, 2053 26.4 / 29.1, 4101 28.8 / 52.9
+//   3840: 1029 28.3 / 19.4, 2053 51.9 / 31.6;   7936: 1029 25.4 / 21.1, 4101 67.1 / 62.3
+// head dimension 64:  128: 389 9.1 / 7.5, 517 9.1 / 9.5;  1024: 1029 13.2 / 12.6;  1792: 1029 15.1 / 12.7, 2053 17.7 / 18.6.
+// (Where in its chunk a band of less than a chunk falls decides whether it is one part or two, which is worth up to half
+// of the streaming time: the figures are for one place at batch 1, for a batch of many beyond.)
+inline bool lone_workgroup_band(int64_t seen, int chunk) { return seen <= 416 || seen <= chunk; }
+
+}  // namespace vegas

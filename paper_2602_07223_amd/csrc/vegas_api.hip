@@ -16,6 +16,7 @@
 #include "attn_split.hpp"
 #include "debug_kernels.hpp"
 #include "kv_append.hpp"
+#include "plan_rules.hpp"
 #include "select_blocks.hpp"
 #include "select_tokens.hpp"
 #include "vegas_common.hpp"
@@ -51,28 +52,8 @@ int device_cu_count() {
 }
 // Longest selection a draft call of more than kDraftRows rows per KV head streams with one workgroup per (sequence,
 // KV head): 256 tokens at head dimension 128, 384 at 64 (tiles of half the bytes), each plus the two pages of slack a
-// selection table carries.  (Smaller groups: one_workgroup_per_column.)
+// selection table carries.  (Smaller groups: lone_workgroup_tokens.)
 constexpr int kFinishTokens128 = 288, kFinishTokens64 = 416;
-
-// Draft calls of up to kDraftRows rows per KV head (attn_draft16_kernel): does one workgroup per (sequence, KV head)
-// stream the whole selection (or, with a local mask, the band) and write the output rows itself, or is it cut into chunks that a second launch merges?
-// A single workgroup streams about 60 GB/s (0.27 us per 16-KB tile behind 3.4 us), the merge costs a launch and a
-// round trip through memory.  Draft calls back to back, us, one workgroup per column against chunks + merge, by
-// columns (sequences x KV heads) and selected tokens (head dimension 128 unless noted):
-//   8..64 columns:  544 tokens 7.7 / 10.1 (in a GPU-bound iteration 0.4 less per call), 1056 12.0 / 10.2;
-//                   head dimension 64: 1056 tokens 8.2 / 10.8, 2080 13.3 / 10.2   -> up to 272 KB of K/V per column
-//   96:  1056 12.8 / 13.1, 2080 22.0 / 22.7, 4128 45.5 / 39.2;  128:  544 8.2 / 10.5, 1056 13.2 / 15.6,
-//        2080 23.0 / 24.8, 4128 53.0 / 44.7 (too few workgroups to cover the latency of HBM, and a selection that no
-//        longer sits in the last-level cache); head dimension 64: 2080 14.0 / 18.0, 4128 24.5 / 29.4
-//                                                                                 -> up to 1.06 MB
-//   192:  1056 17.5 / 21.2, 2080 32.5 / 36.4, 4128 75.3 / 83.8;  256:  21.8 / 25.7, 41.1 / 46.8, 94.6 / 117.8;
-//   384:  2080 78.4 / 98.6, 4128 156.7 / 163.2                                    -> any length
-bool one_workgroup_per_column(int64_t columns, int num_cu, int max_len, int head_dim) {
-  const int64_t bytes = static_cast<int64_t>(max_len) * head_dim * 4;            // K and V of one column's selection
-  if (4 * columns >= 3 * num_cu) return true;
-  if (8 * columns >= 3 * num_cu) return bytes <= 1088 * 1024;
-  return bytes <= 272 * 1024;
-}
 
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -136,18 +117,9 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   // tokens (eight tiles, two per wave) 54.7 us against 59.3 us with three chunks and a merge; 384 tokens 61.8 against
   // 59.4; 512 tokens 67.2 against 59.8.  At head dimension 64 (32K context, 64 query heads): 256 tokens 66.5 against
   // 73.0 us, 384 tokens 71.4 against 73.0, 512 tokens 75.1 against 73.3.
-  // A verification call with a local mask: no row sees more than window + G - 1 tokens, and a workgroup begins where the
-  // first of them is, so the same rule holds for that many tokens (16 sequences of 8192..65536 tokens, 40 rows, head
-  // dimension 64, window 128: 11.7 us with a merge, 8.1 without; window 1024: 18.1, 13.5; one sequence, 20 rows, head
-  // dimension 128, window 512: 13.9, 12.5).
   const bool own_chunks = may_finish && d->kv_chunk_tokens == 0;
   const bool short_call = own_chunks && max_len <= (d->head_dim == 64 ? kFinishTokens64 : kFinishTokens128) &&
                           heads * pl->NB <= num_cu;
-  const int64_t seen = static_cast<int64_t>(d->window) + d->num_queries;
-  const bool banded = !may_finish && !may_pair && d->kv_chunk_tokens == 0 &&
-                      one_workgroup_per_column(heads * pl->NB, num_cu, static_cast<int>(seen < max_len ? seen : max_len), d->head_dim);
-  const bool finish = short_call || banded || (own_chunks && rows_per_head <= kDraftRows &&
-                                               one_workgroup_per_column(heads, num_cu, max_len, d->head_dim));
   const int unit = kTile * pl->NW;
   int chunk = d->kv_chunk_tokens;
   const int whole = (max_len + unit - 1) / unit * unit;
@@ -186,8 +158,14 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   const int64_t per_head = static_cast<int64_t>(d->num_kv_heads) * pl->NB;   // workgroups per slot
   pl->balanced = may_pair && d->kv_chunk_tokens == 0 && d->batch >= 2 && d->batch <= 64 && max_len < (1 << 24) &&
                  per_head <= num_cu;
+  // Smaller groups have a rule of their own, and so has verification with a local mask: no row sees more than
+  // window + G - 1 tokens, and a workgroup begins where the first of them is (16 sequences of 8192..65536 tokens, 40 rows,
+  // head dimension 64, window 128: 11.7 us with a merge, 8.1 without).
+  const bool banded = !may_finish && d->window > 0 && d->kv_chunk_tokens == 0 &&
+                      lone_workgroup_band(static_cast<int64_t>(d->window) + d->num_queries, chunk);
+  const bool finish = banded || (own_chunks && rows_per_head <= kDraftRows && max_len <= lone_workgroup_tokens(heads, num_cu, d->head_dim));
   // (A call that one workgroup per column finishes uses no partials; its workspace is sized for the chunked plan all
-  //  the same, so that one_workgroup_per_column moves neither the sizes callers allocate nor what the built-in scratch takes.)
+  //  the same, so that these rules move neither the sizes callers allocate nor what the built-in scratch takes.)
   size_t slots = static_cast<size_t>(heads) * ((max_len + chunk - 1) / chunk);   // chunk partials the workspace holds
   if (finish) chunk = whole;
   pl->chunk = chunk;

@@ -70,9 +70,12 @@ def test_single_chunk_and_merged_chunks_agree():
     U.check_out("draft.merged_chunks", b, ref, U.vmax_visible(L))
 
 
-@pytest.mark.parametrize("Hkv,n,D", [(8, 544, 128), (8, 545, 128), (8, 1088, 64), (8, 1089, 64),        # few columns
-                                     (96, 2176, 128), (96, 2177, 128),                                  # 3/8 of the CUs
-                                     (192, 2300, 64), (257, 301, 128)])                                 # 3/4, more than one each
+@pytest.mark.parametrize("Hkv,n,D", [(8, 416, 128), (8, 417, 128), (8, 608, 64), (8, 609, 64),          # few columns
+                                     (64, 544, 128), (64, 545, 128), (96, 928, 64), (96, 929, 64),    # 1/4, 3/8 of the CUs
+                                     (144, 1312, 128), (144, 1313, 128), (192, 2176, 64), (192, 2177, 64),   # 9/16, 3/4
+                                     (8, 544, 128), (8, 545, 128), (8, 1088, 64), (8, 1089, 64),
+                                     (96, 2176, 128), (96, 2177, 128),
+                                     (192, 2300, 64), (257, 301, 128)])                                 # ... more than one each
 def test_one_workgroup_per_column_on_both_sides_of_its_rule(Hkv, n, D):
     """The planner's choice (chunk 0) at the edges of the rule that gives a column to one workgroup, for 256 compute
     units: against the oracle and against chunks with a merge."""
