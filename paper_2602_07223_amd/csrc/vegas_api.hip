@@ -134,10 +134,12 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
     int64_t c = (max_len + splits - 1) / splits;
     {
       // Round to whole units: up, unless a bound a little above a multiple (a selection table with two pages of
-      // slack) would then double every wave's tiles -- a quarter more workgroups than planned is the better price.
+      // slack) would then double every wave's tiles -- a quarter more workgroups than planned is the better price where
+      // two of them fit a compute unit.  (64-row workgroups fill its LDS: 288 of them, 80 rows, 32749 tokens, took two
+      // rounds of the chip.)
       const int64_t up = (c + unit - 1) / unit * unit, down = c / unit * unit;
       c = up;
-      if (down >= unit && ((max_len + down - 1) / down) * columns * 4 <= static_cast<int64_t>(num_cu) * wg_per_cu * 5) c = down;
+      if (!pl->pair && down >= unit && ((max_len + down - 1) / down) * columns * 4 <= static_cast<int64_t>(num_cu) * wg_per_cu * 5) c = down;
     }
     // What a workgroup collects is parked in LDS until its chunk ends, so a chunk cannot be arbitrarily long.  A
     // chunk that gives every CU exactly one workgroup is taken as it is while its LDS fits (batch 4 x 64K tokens:

@@ -4,7 +4,9 @@ import os
 import subprocess
 
 import numpy as np
+import pytest
 
+from paper_2602_07223_amd import binding as vb
 from paper_2602_07223_amd import build
 
 
@@ -150,3 +152,20 @@ def test_rules_for_calls_without_a_merge(tmp_path):
         assert per == sorted(per) and per[-1] == 2176
     for (seen, chunk, alone), (_, got) in zip(bands, out[-len(bands):]):
         assert bool(got) == alone, (seen, chunk)
+
+
+def chunk_slots(batch, rows, kv_heads, max_len, head_dim=128, group=8):
+    """Chunk partials (sequence, KV head, chunk) a verification call without collection holds, from what its workspace takes."""
+    desc = vb.make_desc(batch=batch, num_q_heads=group * kv_heads, num_kv_heads=kv_heads, num_queries=rows // group,
+                        max_blocks=-(-max_len // 16), max_sel_blocks=1, max_seq_len=max_len, num_pages=1 << 20,
+                        softmax_scale=0.1, collect_rows=vb.COLLECT_NONE, head_dim=head_dim, page_size=16)
+    total, up = vb.vegas_workspace_bytes(desc), lambda x: -(-x // 256) * 256
+    return max(s for s in range(1, 1 << 14) if up(s * rows * head_dim * 4) + up(s * rows * 8) <= total)
+
+
+@pytest.mark.parametrize("rows", [40, 64, 72, 96, 128])
+@pytest.mark.parametrize("n", [4097, 12345, 32749, 65521])
+def test_one_long_sequence_takes_one_round_of_64_row_workgroups(n, rows):
+    """They fill a compute unit's LDS: more workgroups than the 256 compute units would take a second round."""
+    blocks = -(-rows // 64)
+    assert chunk_slots(1, rows, 8, n) * blocks <= 256
