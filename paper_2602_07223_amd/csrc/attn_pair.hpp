@@ -44,6 +44,7 @@ namespace vegas {
 constexpr int kPairWaves = 4;
 constexpr int kPairRows = 64;               // query rows (of one KV head) of a workgroup
 constexpr int kPairRing = 32 * 1024;        // bytes of K and V tiles per wave
+constexpr int kPairSecondCost = 11;         // what a second launch wave costs, in units of 128 tokens (see wants_second_wave)
 constexpr int kPairFold = 32768;           // chunks per round of a folded grid
 
 // Floats of one wave's parked values: park_tiles tiles of two pages x the collected rows a workgroup can have, or of the
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
   int chunk_tokens = p.chunk_tokens;
   int64_t pbase = (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + split;   // this workgroup's partial slot
   if (p.plan) {                              // balanced chunking: slot j of this head -> (sequence, chunk)
-    const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2,
+    const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2, kPairSecondCost,
                                           p.chunk_cap_units, p.chunk_unit, slot_j,
                                           ((blockIdx.x | yy) == 0 && wave == 0) ? p.plan : nullptr);
     if (bs.b < 0) return;

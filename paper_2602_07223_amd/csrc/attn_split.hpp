@@ -209,7 +209,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
   if constexpr (CAUSAL && PS == 4 && !LOCAL) {
     if (p.plan) {                            // balanced chunking: slot j of this head -> (sequence, chunk)
       const int j = split;
-      const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2,
+      const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2, 0,
                                             p.chunk_cap_units, p.chunk_unit, j,
                                             ((blockIdx.x | blockIdx.y) == 0 && wave == 0) ? p.plan : nullptr);
       if (bs.b < 0) return;

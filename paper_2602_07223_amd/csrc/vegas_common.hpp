@@ -272,7 +272,7 @@ __host__ __device__ __forceinline__ uint32_t requested_slot(int s, int last) {
 // sum_b ceil(n_b / C) <= J, sequence b is cut into s_b = ceil(n_b / C) equal chunks (multiples of `unit` tokens).
 // J is j1 (one launch wave of workgroups) unless the lengths are so ragged that the chunks of that plan would
 // leave more than a tenth of the wave idle; then it is j2 (two waves of half-size chunks, handed out longest
-// first, which evens the waves out).  No chunk is longer than cap_units * unit tokens (what a workgroup can park
+// first, which evens the waves out: wants_second_wave).  No chunk is longer than cap_units * unit tokens (what a workgroup can park
 // in LDS); a batch too long for J chunks of that size simply takes more slots.  Slot ranges [P_b, P_b + s_b)
 // are laid out by descending chunk length, so workgroups start in that order; slot j maps to chunk j - P_b of
 // the sequence whose range holds it.
@@ -310,8 +310,16 @@ __device__ __forceinline__ uint32_t balanced_chunk_units(uint32_t nu, uint32_t t
   }
   return lo;
 }
+// C: chunk length of the one-wave plan, total / j1 its lower bound (all in units).  second_cost: units of streaming that a
+// second wave costs where its workgroups cannot start beside the first's (64-row workgroups fill a compute unit's LDS).
+// Verification with collection there, us, one wave / two, by C / bound: 8 sequences of 500..2000 tokens, 40 rows, 3 / 2.6:
+// 25.6 / 35.6; 12 of 2000..20000, 49 rows, 19 / 16.7: 80.2 / 92.0; 32 of 300..1500, 40 rows, 12 / 7.6: 52.9 / 60.8; 16 of
+// 4000..16000, 54 / 40: 153.5 / 150.4; 24 of 1000..8000, 44 / 27: 126.0 / 117.9; 12 of 2000..20000, 80 rows, 103 / 67: 244 / 197.
+__host__ __device__ __forceinline__ bool wants_second_wave(uint32_t total, uint32_t j1, uint32_t C, uint32_t second_cost) {
+  return C > second_cost && 10u * total < 9u * j1 * (C - second_cost);
+}
 __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B, int max_tokens, int j1, int j2,
-                                                      int cap_units, int unit, int j, int2* plan_out) {
+                                                      int second_cost, int cap_units, int unit, int j, int2* plan_out) {
   const int lane = threadIdx.x & 63;
   uint32_t n = 0u;
   if (lane < B) {
@@ -330,7 +338,7 @@ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) longest = max(longest, static_cast<uint32_t>(__shfl_xor(longest, off, 64)));
   uint32_t C = balanced_chunk_units(nu, total, longest, static_cast<uint32_t>(j1));
-  if (j2 > j1 && 10u * total < 9u * static_cast<uint32_t>(j1) * C)   // less than 90 % of the wave would be busy
+  if (j2 > j1 && wants_second_wave(total, static_cast<uint32_t>(j1), C, static_cast<uint32_t>(second_cost)))
     C = balanced_chunk_units(nu, total, longest, static_cast<uint32_t>(j2));
   C = min(C, static_cast<uint32_t>(cap_units));
   const uint32_t s = (nu + C - 1u) / C;                         // chunks of this sequence (0 if empty)

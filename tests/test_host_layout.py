@@ -169,3 +169,27 @@ def test_one_long_sequence_takes_one_round_of_64_row_workgroups(n, rows):
     """They fill a compute unit's LDS: more workgroups than the 256 compute units would take a second round."""
     blocks = -(-rows // 64)
     assert chunk_slots(1, rows, 8, n) * blocks <= 256
+
+
+WAVES = r'''
+#include <cstdio>
+#include "attn_pair.hpp"
+int main() {                       // lines of: units of all sequences, workgroups of one wave, chunk units of its plan
+  unsigned total, j1, C;
+  while (std::scanf("%u %u %u", &total, &j1, &C) == 3)
+    std::printf("%d %d\n", vegas::wants_second_wave(total, j1, C, 0), vegas::wants_second_wave(total, j1, C, vegas::kPairSecondCost));
+}
+'''
+
+
+def test_second_wave_of_64_row_workgroups(tmp_path):
+    """Ragged batches, for which chunks half as long were measured faster (True) or slower although the first wave is not
+    full: (units of 128 tokens, workgroups of one wave, longest chunk of its plan)."""
+    measured = [((84, 32, 3), False), ((1067, 64, 19), False), ((244, 32, 12), False), ((100, 32, 4), False),
+                ((320, 32, 17), False), ((640, 32, 23), False), ((1066, 32, 41), False), ((1293, 64, 32), False),
+                ((877, 32, 44), True), ((1066, 16, 103), True), ((1263, 16, 120), True), ((4608, 32, 190), True)]
+    out = run_host_program(tmp_path, WAVES, "\n".join(" ".join(map(str, m)) for m, _ in measured)).strip().split("\n")
+    for (m, two), line in zip(measured, out, strict=True):
+        anywhere, here = map(int, line.split())
+        assert anywhere == 1, m                   # less than nine tenths of the wave is busy in all of them
+        assert here == two, m
