@@ -5,7 +5,7 @@
 // of K and V.  Two row blocks leave no registers for tiles in flight (128 accumulators), so K and V never pass through
 // registers on their way in: they are loaded straight into LDS.
 //   * A workgroup = 4 waves on one (sequence, KV head, chunk); every wave takes a contiguous quarter of the chunk's
-//     32-token tiles and owns a ring of kPairRing bytes of LDS (2 tiles at head dimension 128, 4 at 64) that only it
+//     32-token tiles and owns a ring of LDS (2 tiles at head dimension 128, 4 at 64; pair_ring) that only it
 //     fills and reads, so the streaming loop has no barrier and no wave waits for another one.
 //   * K goes into a ring slot as soon as the first contraction has read the slot's old K, V as soon as the second one
 //     has read the old V: 64 to 128 KB per compute unit are in flight all the time.  The load counter returns in
@@ -43,8 +43,12 @@ namespace vegas {
 
 constexpr int kPairWaves = 4;
 constexpr int kPairRows = 64;               // query rows (of one KV head) of a workgroup
-constexpr int kPairRing = 32 * 1024;        // bytes of K and V tiles per wave
-constexpr int kPairSecondCost = 11;         // what a second launch wave costs, in units of 128 tokens (see wants_second_wave)
+// Bytes of K and V tiles per wave.  At head dimension 64 without collection, where nothing is parked, two tiles instead of
+// four let two workgroups share a compute unit: 48 sequences of 300..3000 tokens, 49 rows, 4 KV heads 52.1 -> 35.1 us, 32 of
+// 300..1500, 80 rows, 8 KV heads 49.3 -> 36.6, one of 32768, 40 rows 21.9 -> 20.0.
+constexpr int pair_ring(int D, int collect) { return D == 64 && collect == 0 ? 16 * 1024 : 32 * 1024; }
+// What a second launch wave costs, in units of 128 tokens (see wants_second_wave): nothing where two workgroups fit.
+constexpr int pair_second_cost(int D, int collect) { return D == 64 && collect == 0 ? 0 : 11; }
 constexpr int kPairFold = 32768;           // chunks per round of a folded grid
 
 // Floats of one wave's parked values: park_tiles tiles of two pages x the collected rows a workgroup can have, or of the
@@ -95,12 +99,13 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
   constexpr int NB = 2;                      // 32-row blocks of a wave
   constexpr int CH = D / 8;                  // 16-byte pieces of a K/V row
   constexpr int TPI = 64 / CH;               // token rows of one load instruction
+  constexpr int kRing = pair_ring(D, COLLECT);
   constexpr int NP = kPage / TPI;            // load instructions per page (of K, of V)
   constexpr int NL = 2 * NP;                 // ... per tile
   constexpr int NBLK = D / 32;               // 32-wide blocks of the output's head dimension
   constexpr int kRow = 2 * D;                // bytes of a K/V row
   constexpr int kHalfSlot = 32 * kRow;       // bytes of a tile's K (then as many of V)
-  constexpr int NS = kPairRing / (2 * kHalfSlot);   // tiles the ring holds
+  constexpr int NS = kRing / (2 * kHalfSlot);   // tiles the ring holds
   constexpr int kRowPitch = row_pitch(D);
   constexpr int kRedPitch = red_pitch(D);
   using VReg = typename std::conditional<D == 128, u32x2, uint32_t>::type;   // NBLK head dims of one token
@@ -109,8 +114,8 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5;
   const int l32 = lane & 31;
-  unsigned char* const ring = smem + wave * kPairRing;
-  unsigned char* const qlds = smem + NW * kPairRing;
+  unsigned char* const ring = smem + wave * kRing;
+  unsigned char* const qlds = smem + NW * kRing;
   float* const sm_m = reinterpret_cast<float*>(smem + p.lds_q_off);             // [wave][64]
   float* const sm_l = sm_m + NW * kPairRows;
 
@@ -131,7 +136,7 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
   int chunk_tokens = p.chunk_tokens;
   int64_t pbase = (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + split;   // this workgroup's partial slot
   if (p.plan) {                              // balanced chunking: slot j of this head -> (sequence, chunk)
-    const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2, kPairSecondCost,
+    const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2, pair_second_cost(D, COLLECT),
                                           p.chunk_cap_units, p.chunk_unit, slot_j,
                                           ((blockIdx.x | yy) == 0 && wave == 0) ? p.plan : nullptr);
     if (bs.b < 0) return;
@@ -566,7 +571,7 @@ struct PairLds {
 inline PairLds pair_lds(int R, int Rc, int row_blocks, int collect, int D) {
   const size_t q = static_cast<size_t>(row_blocks == 1 ? R + (collect == 2 ? 2 : 0) : kPairRows) * row_pitch(D);
   const size_t rows_ml = 2 * static_cast<size_t>(kPairWaves) * kPairRows * sizeof(float);
-  size_t before = kPairWaves * kPairRing + q;
+  size_t before = kPairWaves * pair_ring(D, collect) + q;
   PairLds l = {0, 0, 0};
   if (collect != 0) {
     const size_t tile = sizeof(float) * pair_park_floats(1, Rc, collect);

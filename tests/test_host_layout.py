@@ -96,7 +96,7 @@ int main() {                       // lines of: query rows, collected rows, coll
     const vegas::PairLds lds = vegas::pair_lds(R, Rc, blocks, collect, D);
     const int queries = (blocks == 1 ? tile_rows : vegas::kPairRows) * vegas::row_pitch(D);
     std::printf("%d %d %zu %zu %zu\n", lds.park_tiles, vegas::pair_park_floats(lds.park_tiles, Rc, collect),
-                static_cast<size_t>(vegas::kPairWaves * vegas::kPairRing + queries), lds.off_max, lds.bytes);
+                static_cast<size_t>(vegas::kPairWaves * vegas::pair_ring(D, collect) + queries), lds.off_max, lds.bytes);
   }
 }
 '''
@@ -105,13 +105,18 @@ int main() {                       // lines of: query rows, collected rows, coll
 def test_parked_values_of_every_wave_are_aligned(tmp_path):
     """64-row workgroups: a wave reads what it has parked in 16-byte pieces, so its part of the LDS starts on a multiple of
     16 bytes and ends before the row maxima, for every row count, collection mode and head dimension."""
-    cases = [(R, Rc, collect, D) for D in (128, 64) for R in range(31, 129)
+    cases = [(R, R, 0, D) for D in (128, 64) for R in range(33, 129)]
+    cases += [(R, Rc, collect, D) for D in (128, 64) for R in range(31, 129)
              for collect, rcs in ((1, {R} | {2 * g for g in range(1, 43) if R % g == 0 and R // g > 2}), (2, {R}))
              for Rc in sorted(rcs) if R + (2 if collect == 2 else 0) > 32]
     out = run_host_program(tmp_path, PARKS, "\n".join(" ".join(map(str, c)) for c in cases))
     for case, line in zip(cases, out.strip().split("\n"), strict=True):
         tiles, floats, parks, off_max, total = map(int, line.split())
-        R, Rc, collect, _ = case
+        R, Rc, collect, D = case
+        if collect == 0:
+            # nothing is parked; at head dimension 64 two workgroups fit a compute unit
+            assert tiles == 0 and total <= (80 if D == 64 else 160) * 1024, (case, total)
+            continue
         assert tiles >= 2 and floats >= tiles * 2 * (32 if collect == 2 else min(Rc, 64)), case
         assert parks % 16 == 0 and floats % 4 == 0, case
         assert parks + 4 * floats * 4 <= off_max and total <= 160 * 1024, case
@@ -177,7 +182,7 @@ WAVES = r'''
 int main() {                       // lines of: units of all sequences, workgroups of one wave, chunk units of its plan
   unsigned total, j1, C;
   while (std::scanf("%u %u %u", &total, &j1, &C) == 3)
-    std::printf("%d %d\n", vegas::wants_second_wave(total, j1, C, 0), vegas::wants_second_wave(total, j1, C, vegas::kPairSecondCost));
+    std::printf("%d %d\n", vegas::wants_second_wave(total, j1, C, 0), vegas::wants_second_wave(total, j1, C, vegas::pair_second_cost(128, 1)));
 }
 '''
 
