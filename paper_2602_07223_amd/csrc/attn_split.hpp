@@ -26,8 +26,8 @@
 //   * All query rows of the GQA group (x G verification rows) are stacked in the N dimension, so
 //     every K/V byte is loaded once per workgroup and never re-read.  The queries sit in LDS
 //     (padded like K) and are shared by the workgroup's waves.  More than 32 rows per KV head take
-//     attn_pair_kernel in verification; where a local mask applies, and in draft calls, they are split into 32-row
-//     blocks handled by sibling workgroups whose ids differ by the number of KV
+//     attn_pair_kernel in verification; where a local mask applies, in small calls of more than 64 rows, and in draft
+//     calls, they are split into 32-row blocks handled by sibling workgroups whose ids differ by the number of KV
 //     heads: ids are dealt round-robin to the 8 XCDs, so siblings share an L2 and the second
 //     reader of a K/V line is served from it -- HBM still sees each byte once.
 //   * Loads run one tile ahead: as soon as K(current) has been handed to LDS, K(next) goes into

@@ -43,4 +43,23 @@ inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
 // of the streaming time: the figures are for one place at batch 1, for a batch of many beyond.)
 inline bool lone_workgroup_band(int64_t seen, int chunk) { return seen <= 416 || seen <= chunk; }
 
+// Verification of more than 64 rows per KV head: sibling workgroups of 32 rows (attn_split_kernel, two per compute unit, each
+// reading K and V through the L2) instead of 64 rows each (attn_pair_kernel)?  The latter read half as often but take longer
+// to begin and to end, so small calls keep the siblings; bound: sequences x KV heads x longest length, in tokens.  us, 32-row
+// siblings / 64 rows, captured:
+//   no collection: 1 sequence x 8 heads x 4096, 128 rows 15.3 / 17.7; 8 x 8 x 500..2000, 80 rows 27.2 / 30.1; 16 x 8 x
+//     300..1200, 80 rows 30.9 / 36.1; head dimension 64, 80 rows: 1 x 4 x 32768 19.8 / 20.8; 1 x 8 x 32768 30.3 / 29.4;
+//     4 x 8 x 16384 67.0 / 51.1
+//   all rows: 1 x 4 x 4096, 80 rows 19.4 / 22.0; 1 x 8 x 12345, 80 rows 37.4 / 38.1, 128 rows 49.5 / 45.9; 2 x 8 x 8192,
+//     80 rows 39.2 / 38.2; 8 x 8 x 500..2000, 80 rows 47.5 / 40.7
+//   first and last token's rows: 2 x 8 x 8192, 80 rows 29.6 / 32.5; head dimension 64, 1 x 4 x 32768, 80 rows 23.6 / 28.1;
+//     1 x 8 x 32768, 128 rows 51.3 / 50.1
+inline bool wide_rows_as_siblings(int batch, int kv_heads, int max_len, int rows, int collect_rows, int head_dim) {
+  const int64_t bound = static_cast<int64_t>(batch) * kv_heads * max_len;
+  if (collect_rows == 0) return bound <= 160000;
+  if (batch >= 8) return false;
+  if (collect_rows == 1) return bound <= (rows <= 96 ? 100000 : 50000);
+  return rows <= 96 && bound * head_dim <= (1 << 24);
+}
+
 }  // namespace vegas

@@ -38,6 +38,29 @@ def test_chunks_of_every_length(n, chunk, Hq, Hkv, G, D):
 
 
 @pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("Hq,Hkv,G", [(26, 2, 5), (32, 4, 10), (64, 4, 8)], ids=["65_rows", "80_rows", "128_rows"])
+@pytest.mark.parametrize("lens", [[1025], [4133], [30011], [517, 0, 2049], [97, 0, 16, 1300, 640, 33, 1, 900]], ids=str)
+def test_more_than_64_rows_on_both_sides_of_the_sibling_rule(lens, Hq, Hkv, G, D):
+    """Small calls run as 32-row siblings, larger ones and batches of eight that collect as 64-row workgroups."""
+    L = synth.make_random_case(seed=6500 + sum(lens) + Hq + D, batch=len(lens), num_q_heads=Hq, num_kv_heads=Hkv, num_queries=G,
+                               seq_lens=lens, head_dim=D, logit_std=2.0, value_std=1.0, outliers=2, outlier_logit=25.0)
+    print(f"[case] siblings lens={lens} Hq={Hq} Hkv={Hkv} G={G} D={D}", flush=True)
+    dl = harness.DeviceLayer.upload(L)
+    for collect in (vb.COLLECT_ALL_ROWS, vb.COLLECT_FIRST_LAST, vb.COLLECT_NONE):
+        path = harness.VegasPath.for_layer(L, budget_tokens=256, collect_rows=collect)
+        path.workspace.fill_(0xFF)
+        path.out_verify.fill_(float("nan"))
+        path.block_scores.fill_(float("nan"))
+        path.verify(dl)
+        torch.cuda.synchronize()
+        ref_out, ref_scores = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens,
+                                                 L.softmax_scale, collect or vb.COLLECT_ALL_ROWS)
+        U.check_out(f"sib.{sum(lens)}.{Hq}.{collect}", path.out_verify, ref_out, U.vmax_visible(L))
+        if collect:
+            U.check_scores(f"sib.{sum(lens)}.{Hq}.{collect}", path.block_scores, ref_scores)
+
+
+@pytest.mark.parametrize("D", [128, 64])
 @pytest.mark.parametrize("Hq,Hkv,G", [(28, 4, 7), (37, 1, 1), (61, 1, 1)], ids=["49_rows", "37_rows", "61_rows"])
 def test_odd_numbers_of_collected_rows(Hq, Hkv, G, D):
     """Row counts with which an odd number of parked tiles would leave waves 1 and 3 between two 16-byte pieces of the LDS:

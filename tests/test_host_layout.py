@@ -168,8 +168,7 @@ def chunk_slots(batch, rows, kv_heads, max_len, head_dim=128, group=8):
     return max(s for s in range(1, 1 << 14) if up(s * rows * head_dim * 4) + up(s * rows * 8) <= total)
 
 
-@pytest.mark.parametrize("rows", [40, 64, 72, 96, 128])
-@pytest.mark.parametrize("n", [4097, 12345, 32749, 65521])
+@pytest.mark.parametrize("rows,n", [(40, 4097), (64, 12345), (40, 32749), (64, 65521), (72, 32749), (96, 65521), (128, 32749)])
 def test_one_long_sequence_takes_one_round_of_64_row_workgroups(n, rows):
     """They fill a compute unit's LDS: more workgroups than the 256 compute units would take a second round."""
     blocks = -(-rows // 64)
@@ -198,3 +197,26 @@ def test_second_wave_of_64_row_workgroups(tmp_path):
         anywhere, here = map(int, line.split())
         assert anywhere == 1, m                   # less than nine tenths of the wave is busy in all of them
         assert here == two, m
+
+
+SIBLINGS = r'''
+#include <cstdio>
+#include "plan_rules.hpp"
+int main() {                       // lines of: sequences, KV heads, longest, rows, collection, head dimension
+  int B, H, n, R, c, D;
+  while (std::scanf("%d %d %d %d %d %d", &B, &H, &n, &R, &c, &D) == 6)
+    std::printf("%d\n", vegas::wide_rows_as_siblings(B, H, n, R, c, D) ? 1 : 0);
+}
+'''
+
+
+def test_more_than_64_rows_as_siblings_where_that_is_faster(tmp_path):
+    """(sequences, KV heads, longest, rows, collection, head dimension): siblings measured faster, or not."""
+    measured = [((1, 8, 4096, 128, 0, 128), 1), ((8, 8, 2000, 80, 0, 128), 1), ((16, 8, 1200, 80, 0, 128), 1),
+                ((1, 4, 32768, 80, 0, 64), 1), ((1, 8, 32768, 128, 0, 64), 0), ((4, 8, 16384, 80, 0, 64), 0),
+                ((1, 4, 4096, 80, 1, 128), 1), ((1, 8, 12345, 80, 1, 128), 1), ((1, 8, 12345, 128, 1, 128), 0),
+                ((2, 8, 8192, 80, 1, 128), 0), ((8, 8, 2000, 80, 1, 128), 0), ((2, 8, 8192, 80, 2, 128), 1),
+                ((1, 4, 32768, 80, 2, 64), 1), ((1, 8, 32768, 128, 2, 128), 0), ((16, 8, 1200, 80, 2, 64), 0),
+                ((4, 8, 16384, 80, 2, 128), 0)]
+    out = run_host_program(tmp_path, SIBLINGS, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
+    assert [int(x) for x in out] == [s for _, s in measured]
