@@ -43,12 +43,16 @@ namespace vegas {
 
 constexpr int kPairWaves = 4;
 constexpr int kPairRows = 64;               // query rows (of one KV head) of a workgroup
-// Bytes of K and V tiles per wave.  At head dimension 64 without collection, where nothing is parked, two tiles instead of
-// four let two workgroups share a compute unit: 48 sequences of 300..3000 tokens, 49 rows, 4 KV heads 52.1 -> 35.1 us, 32 of
-// 300..1500, 80 rows, 8 KV heads 49.3 -> 36.6, one of 32768, 40 rows 21.9 -> 20.0.
-constexpr int pair_ring(int D, int collect) { return D == 64 && collect == 0 ? 16 * 1024 : 32 * 1024; }
+// At head dimension 64, unless page values are parked (they are many), the LDS is laid out for two workgroups per compute
+// unit, in rings of two tiles instead of four.  No collection: 48 sequences of 300..3000 tokens, 49 rows, 4 KV heads 52.1 ->
+// 35.1 us, 32 of 300..1500, 80 rows, 8 KV heads 49.3 -> 36.6, one of 32768, 40 rows 21.9 -> 20.0.  Token sums: 24 of
+// 1000..8000, 80 rows, 8 KV heads 132.2 -> 110.6, 16 of 4000..16000, 64 rows, 4 KV heads 101.1 -> 77.8.  (Of page values
+// only two tiles could be parked beside 64 rows, and short bursts are what slows the reads.)
+constexpr bool pair_two_per_cu(int D, int collect) { return D == 64 && collect != 1; }
+// Bytes of K and V tiles per wave.
+constexpr int pair_ring(int D, int collect) { return pair_two_per_cu(D, collect) ? 16 * 1024 : 32 * 1024; }
 // What a second launch wave costs, in units of 128 tokens (see wants_second_wave): nothing where two workgroups fit.
-constexpr int pair_second_cost(int D, int collect) { return D == 64 && collect == 0 ? 0 : 11; }
+constexpr int pair_second_cost(int D, int collect) { return pair_two_per_cu(D, collect) ? 0 : 11; }
 constexpr int kPairFold = 32768;           // chunks per round of a folded grid
 
 // Floats of one wave's parked values: park_tiles tiles of two pages x the collected rows a workgroup can have, or of the
@@ -575,7 +579,8 @@ inline PairLds pair_lds(int R, int Rc, int row_blocks, int collect, int D) {
   PairLds l = {0, 0, 0};
   if (collect != 0) {
     const size_t tile = sizeof(float) * pair_park_floats(1, Rc, collect);
-    l.park_tiles = static_cast<int>((160 * 1024 - rows_ml - before) / (kPairWaves * tile));
+    const size_t room = (pair_two_per_cu(D, collect) ? 80 : 160) * 1024;
+    l.park_tiles = static_cast<int>((room - rows_ml - before) / (kPairWaves * tile));
     if (l.park_tiles > 64) l.park_tiles = 64;
     if (tile % 16) l.park_tiles &= ~1;       // (an odd number of collected rows: tiles of 8 bytes more than a multiple of 16)
     before += kPairWaves * tile * l.park_tiles;
