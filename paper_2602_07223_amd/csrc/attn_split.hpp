@@ -162,7 +162,8 @@ __device__ __forceinline__ void store_queries_to_lds(unsigned char* qlds, const 
 // A sum of logits is linear in the query, sum_r q_r . k = (sum_r q_r) . k, so the sum of the collected
 // query rows of this KV head rides along as two spare rows of the query tile (a bf16 high part and a
 // bf16 low part, together good to 2^-17) and the first MFMA delivers the token sums for free.  The host puts
-// them behind the real rows (at most 30 of them: with more the call takes attn_pair_kernel).
+// them behind the real rows; where the last row block has fewer than two to spare they get a block of their own (Rl = 0: it
+// streams K like its siblings, parks the token sums, and writes no partial output).
 // PS: log2 of the tokens per page of the table the kernel walks.  4 (16-token pages) is the path
 // described above; 0..3 (1, 2, 4, 8-token pages: Sec. 4 drafts with one-token pages, App. D sweeps
 // 1..16) is for draft calls only: a tile then spans 32 >> PS pages, every lane looks up the page of

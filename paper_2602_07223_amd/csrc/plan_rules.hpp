@@ -43,10 +43,10 @@ inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
 // of the streaming time: the figures are for one place at batch 1, for a batch of many beyond.)
 inline bool lone_workgroup_band(int64_t seen, int chunk) { return seen <= 416 || seen <= chunk; }
 
-// Verification of more than 64 rows per KV head: sibling workgroups of 32 rows (attn_split_kernel, two per compute unit, each
-// reading K and V through the L2) instead of 64 rows each (attn_pair_kernel)?  The latter read half as often but take longer
-// to begin and to end, so small calls keep the siblings; bound: sequences x KV heads x longest length, in tokens.  us, 32-row
-// siblings / 64 rows, captured:
+// Verification of more than 64 rows per KV head (with the two sum rows of the logit metric, and there of just above 32 as
+// well): sibling workgroups of 32 rows (attn_split_kernel, two per compute unit, each reading K and V through the L2)
+// instead of 64 rows each (attn_pair_kernel)?  The latter read half as often but take longer to begin and to end, so small
+// calls keep the siblings; bound: sequences x KV heads x longest length, in tokens.  us, 32-row siblings / 64 rows, captured:
 //   no collection: 1 sequence x 8 heads x 4096, 128 rows 15.3 / 17.7; 8 x 8 x 500..2000, 80 rows 27.2 / 30.1; 16 x 8 x
 //     300..1200, 80 rows 30.9 / 36.1; head dimension 64, 80 rows: 1 x 4 x 32768 19.8 / 20.8; 1 x 8 x 32768 30.3 / 29.4;
 //     4 x 8 x 16384 67.0 / 51.1
@@ -54,12 +54,18 @@ inline bool lone_workgroup_band(int64_t seen, int chunk) { return seen <= 416 ||
 //     80 rows 39.2 / 38.2; 8 x 8 x 500..2000, 80 rows 47.5 / 40.7
 //   first and last token's rows: 2 x 8 x 8192, 80 rows 29.6 / 32.5; head dimension 64, 1 x 4 x 32768, 80 rows 23.6 / 28.1;
 //     1 x 8 x 32768, 128 rows 51.3 / 50.1
-inline bool wide_rows_as_siblings(int batch, int kv_heads, int max_len, int rows, int collect_rows, int head_dim) {
+//   token sums, 1 sequence x 8 heads: head dimension 64, all rows: 12345, 32 rows 17.9 / 19.7; 32749, 32 rows 34.5 / 26.1,
+//     80 rows 41.3 / 42.7; 128: 4096, 96 rows, first and last 17.2 / 18.7; 32749, 64 rows, first and last 39.7 / 41.8, all
+//     51.9 / 52.6; 4 x 8 x 16384, head dimension 64, 80 rows 76.5 / 67.2; 16 x 8 x 300..1200, 64 rows 47.5 / 43.9
+inline bool rows_as_siblings(int batch, int kv_heads, int max_len, int rows, int collect_rows, bool token_sums, int head_dim) {
+  const int tile_rows = rows + (token_sums && collect_rows != 0 ? 2 : 0), blocks = (tile_rows + 31) / 32;
+  if (tile_rows <= 64 && (rows > 32 || tile_rows <= 32)) return false;   // (33..62 rows: 64-row workgroups at any size)
   const int64_t bound = static_cast<int64_t>(batch) * kv_heads * max_len;
   if (collect_rows == 0) return bound <= 160000;
   if (batch >= 8) return false;
-  if (collect_rows == 1) return bound <= (rows <= 96 ? 100000 : 50000);
-  return rows <= 96 && bound * head_dim <= (1 << 24);
+  if (token_sums) return bound <= (blocks != 3 ? 100000 : collect_rows == 2 ? 1 << 18 : (1 << 24) / head_dim);
+  if (collect_rows == 1) return bound <= (blocks <= 3 ? 100000 : 50000);
+  return blocks <= 3 && bound * head_dim <= (1 << 24);
 }
 
 }  // namespace vegas

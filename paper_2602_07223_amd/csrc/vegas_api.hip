@@ -108,12 +108,13 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   pl->NW = 4;                                        // measured: 4-wave groups match or beat 8-wave groups everywhere
   // Row blocks: 32 rows each, sibling workgroups that share an XCD's L2; verification of more than 32 rows (with the two
   // sum rows of the logit metric, which take a block's spare rows) has blocks of 64 served from one read of K/V, small
-  // calls of more than 64 excepted (unless they bring a chunk length, whose collected values siblings might not park).
+  // calls excepted (unless they bring a chunk length, whose collected values siblings might not park).  The sum rows may
+  // have the last block to themselves.
   const int tile_rows = rows_per_head + (collect == 2 ? 2 : 0);
-  const bool siblings = rows_per_head > 64 && collect != 2 && d->kv_chunk_tokens == 0 &&
-                        wide_rows_as_siblings(d->batch, d->num_kv_heads, max_len, rows_per_head, d->collect_rows, d->head_dim);
+  const bool siblings = d->kv_chunk_tokens == 0 && rows_as_siblings(d->batch, d->num_kv_heads, max_len, rows_per_head,
+                                                                    d->collect_rows, collect == 2, d->head_dim);
   pl->pair = may_pair && tile_rows > 32 && !siblings;
-  pl->NB = pl->pair ? (tile_rows + kPairRows - 1) / kPairRows : (rows_per_head + 31) / 32;
+  pl->NB = (tile_rows + (pl->pair ? kPairRows : 32) - 1) / (pl->pair ? kPairRows : 32);
   // A draft call (may_finish) over a selection that one workgroup per (sequence, KV head) streams fast enough: it
   // writes the output rows itself, so no merge kernel is launched.  Groups of more than kDraftRows heads run the 32-row
   // kernel, whose workgroups take about 0.35 us per tile; at 4K context, five draft calls per iteration: 256 selected
@@ -339,7 +340,7 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
       return launch_one(attn_split_kernel<4, 2, true, 0, false, 4, true, D>, grid, dim3(256), lds, st, sp);
     }
   }
-  if constexpr (CAUSAL && COLLECT != 2) {           // sibling workgroups: the second reader of a line finds it in the L2
+  if constexpr (CAUSAL) {                           // sibling workgroups: the second reader of a line finds it in the L2
     if (pl.NB > 1) return launch_one(attn_split_kernel<4, 2, true, COLLECT, false, 4, false, D>, grid, dim3(256), lds, st, sp);
   }
   // verification of up to 32 rows: one reader per K/V line, read once: stream it
@@ -496,6 +497,7 @@ int for_each_lds_kernel(F f) {
     one(attn_split_kernel<4, 2, true, 1, true, 4, false, D>);
     one(attn_split_kernel<4, 2, true, 0, false, 4, false, D>);       // ... as sibling row blocks
     one(attn_split_kernel<4, 2, true, 1, false, 4, false, D>);
+    one(attn_split_kernel<4, 2, true, 2, false, 4, false, D>);
     one(attn_split_kernel<4, 2, true, 2, true, 4, false, D>);
     one(attn_draft16_kernel<D, 0>);
     one(attn_draft16_kernel<D, 1>);

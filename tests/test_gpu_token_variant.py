@@ -360,3 +360,30 @@ def test_token_variant_clamps_corrupt_lengths_and_page_ids():
     U.check_out("token.corrupt.clean.draft0", path.out_draft[0][:1], ref_d, U.vmax_visible(L))
     assert int(ssl[1]) == 0 and bool((sel[1] == -1).all())
     assert 0 <= int(ssl[2]) <= path.max_sel_blocks
+
+
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("rows", [30, 31, 32, 63, 64, 95, 96, 127, 128])
+def test_token_logit_scores_where_the_sum_rows_need_a_block(rows, D):
+    """Row counts at which the two sum rows fill the last row block or have one to themselves: as 32-row siblings (small
+    calls) and as 64-row workgroups (a chunk length, or a bound of more than 262144 tokens)."""
+    for lens, chunk, bound in (([1300, 0, 77], 0, 0), ([1300, 0, 77], 256, 0), ([3000], 0, 300000)):
+        L = synth.make_random_case(seed=6600 + rows + D + chunk, batch=len(lens), num_q_heads=rows, num_kv_heads=1, num_queries=1,
+                                   seq_lens=lens, head_dim=D, logit_std=1.5, value_std=1.0, outliers=2, outlier_logit=20.0,
+                                   max_blocks=-(-bound // 16))
+        print(f"[case] sum rows={rows} D={D} lens={lens} chunk={chunk} bound={bound}", flush=True)
+        dl = harness.DeviceLayer.upload(L)
+        path = harness.VegasPath(batch=len(lens), num_q_heads=rows, num_kv_heads=1, num_queries=1, max_blocks=L.max_blocks,
+                                 max_seq_len=bound or max(lens), num_pages=L.num_pages, budget_tokens=100,
+                                 softmax_scale=L.softmax_scale, head_dim=D, verify_chunk=chunk,
+                                 score_metric=vb.METRIC_TOKEN_LOGITS)
+        path.workspace.fill_(0xFF)
+        path.out_verify.fill_(float("nan"))
+        path.block_scores.fill_(float("nan"))
+        path.verify(dl)
+        torch.cuda.synchronize()
+        name = f"sum_rows.{rows}.{D}.{chunk}.{bound}"
+        check_token_scores(name, L, path, vb.COLLECT_ALL_ROWS)
+        ref_out, _ = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens, L.softmax_scale,
+                                        vb.COLLECT_ALL_ROWS)
+        U.check_out(name, path.out_verify, ref_out, U.vmax_visible(L))

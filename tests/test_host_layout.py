@@ -203,21 +203,25 @@ def test_second_wave_of_64_row_workgroups(tmp_path):
 SIBLINGS = r'''
 #include <cstdio>
 #include "plan_rules.hpp"
-int main() {                       // lines of: sequences, KV heads, longest, rows, collection, head dimension
-  int B, H, n, R, c, D;
-  while (std::scanf("%d %d %d %d %d %d", &B, &H, &n, &R, &c, &D) == 6)
-    std::printf("%d\n", vegas::wide_rows_as_siblings(B, H, n, R, c, D) ? 1 : 0);
+int main() {                       // lines of: sequences, KV heads, longest, rows, collected rows, token sums, head dimension
+  int B, H, n, R, c, tokens, D;
+  while (std::scanf("%d %d %d %d %d %d %d", &B, &H, &n, &R, &c, &tokens, &D) == 7)
+    std::printf("%d\n", vegas::rows_as_siblings(B, H, n, R, c, tokens, D) ? 1 : 0);
 }
 '''
 
 
-def test_more_than_64_rows_as_siblings_where_that_is_faster(tmp_path):
-    """(sequences, KV heads, longest, rows, collection, head dimension): siblings measured faster, or not."""
-    measured = [((1, 8, 4096, 128, 0, 128), 1), ((8, 8, 2000, 80, 0, 128), 1), ((16, 8, 1200, 80, 0, 128), 1),
-                ((1, 4, 32768, 80, 0, 64), 1), ((1, 8, 32768, 128, 0, 64), 0), ((4, 8, 16384, 80, 0, 64), 0),
-                ((1, 4, 4096, 80, 1, 128), 1), ((1, 8, 12345, 80, 1, 128), 1), ((1, 8, 12345, 128, 1, 128), 0),
-                ((2, 8, 8192, 80, 1, 128), 0), ((8, 8, 2000, 80, 1, 128), 0), ((2, 8, 8192, 80, 2, 128), 1),
-                ((1, 4, 32768, 80, 2, 64), 1), ((1, 8, 32768, 128, 2, 128), 0), ((16, 8, 1200, 80, 2, 64), 0),
-                ((4, 8, 16384, 80, 2, 128), 0)]
+def test_wide_rows_as_siblings_where_that_is_faster(tmp_path):
+    """(sequences, KV heads, longest, rows, collected rows, token sums, head dimension): siblings measured faster, or not."""
+    measured = [((1, 8, 4096, 128, 0, 0, 128), 1), ((8, 8, 2000, 80, 0, 0, 128), 1), ((16, 8, 1200, 80, 0, 0, 128), 1),
+                ((1, 4, 32768, 80, 0, 0, 64), 1), ((1, 8, 32768, 128, 0, 0, 64), 0), ((4, 8, 16384, 80, 0, 0, 64), 0),
+                ((1, 4, 4096, 80, 1, 0, 128), 1), ((1, 8, 12345, 80, 1, 0, 128), 1), ((1, 8, 12345, 128, 1, 0, 128), 0),
+                ((2, 8, 8192, 80, 1, 0, 128), 0), ((8, 8, 2000, 80, 1, 0, 128), 0), ((2, 8, 8192, 80, 2, 0, 128), 1),
+                ((1, 4, 32768, 80, 2, 0, 64), 1), ((1, 8, 32768, 128, 2, 0, 128), 0), ((16, 8, 1200, 80, 2, 0, 64), 0),
+                ((4, 8, 16384, 80, 2, 0, 128), 0), ((1, 8, 4096, 40, 1, 0, 128), 0), ((1, 8, 4096, 64, 0, 0, 128), 0),
+                ((1, 8, 12345, 32, 1, 1, 64), 1), ((1, 8, 32749, 32, 1, 1, 64), 0), ((1, 8, 12345, 40, 1, 1, 64), 0),
+                ((1, 8, 4096, 96, 2, 1, 128), 1), ((1, 8, 32749, 96, 1, 1, 128), 0), ((1, 8, 32749, 80, 1, 1, 64), 1),
+                ((1, 8, 32749, 64, 2, 1, 128), 1), ((1, 8, 32749, 64, 1, 1, 128), 0), ((4, 8, 16384, 80, 1, 1, 64), 0),
+                ((16, 8, 1200, 64, 1, 1, 128), 0), ((1, 8, 4096, 31, 1, 1, 128), 1), ((1, 8, 4096, 30, 1, 1, 128), 0)]
     out = run_host_program(tmp_path, SIBLINGS, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
     assert [int(x) for x in out] == [s for _, s in measured]
