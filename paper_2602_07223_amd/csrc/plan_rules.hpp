@@ -54,6 +54,9 @@ inline bool lone_workgroup_band(int64_t seen, int chunk) { return seen <= 416 ||
 //     80 rows 39.2 / 38.2; 8 x 8 x 500..2000, 80 rows 47.5 / 40.7
 //   first and last token's rows: 2 x 8 x 8192, 80 rows 29.6 / 32.5; head dimension 64, 1 x 4 x 32768, 80 rows 23.6 / 28.1;
 //     1 x 8 x 32768, 128 rows 51.3 / 50.1
+//   more than 64 sequences (no plan, every chunk length one for all; 64-row workgroups take a whole sequence each, for an
+//     empty one of them waits for a compute unit's LDS), 65 x 8 heads, 80 rows, all rows: 2048..16384 872 / 894, at head
+//     dimension 64 540 / 659; 64 of 512 and one of 65536 496 / 1145
 //   token sums, 1 sequence x 8 heads: head dimension 64, all rows: 12345, 32 rows 17.9 / 19.7; 32749, 32 rows 34.5 / 26.1,
 //     80 rows 41.3 / 42.7; 128: 4096, 96 rows, first and last 17.2 / 18.7; 32749, 64 rows, first and last 39.7 / 41.8, all
 //     51.9 / 52.6; 4 x 8 x 16384, head dimension 64, 80 rows 76.5 / 67.2; 16 x 8 x 300..1200, 64 rows 47.5 / 43.9
@@ -62,10 +65,21 @@ inline bool rows_as_siblings(int batch, int kv_heads, int max_len, int rows, int
   if (tile_rows <= 64 && (rows > 32 || tile_rows <= 32)) return false;   // (33..62 rows: 64-row workgroups at any size)
   const int64_t bound = static_cast<int64_t>(batch) * kv_heads * max_len;
   if (collect_rows == 0) return bound <= 160000;
-  if (batch >= 8) return false;
+  if (batch >= 8) return batch > 64;
   if (token_sums) return bound <= (blocks != 3 ? 100000 : collect_rows == 2 ? 1 << 18 : (1 << 24) / head_dim);
   if (collect_rows == 1) return bound <= (blocks <= 3 ? 100000 : 50000);
   return blocks <= 3 && bound * head_dim <= (1 << 24);
+}
+
+// Chunk length of 64-row workgroups where the columns alone are as many as the compute units and no plan evens out the
+// lengths (more than 64 sequences): whole sequences up to 8192 tokens and halves beyond, with more than 64 rows at most 4096
+// tokens.  A chunk past its sequence's end still waits for a compute unit, so shorter ones cost a batch of similar lengths
+// more than they save; a single long sequence runs on by itself.  us, whole / as chosen, 65 x 8 heads, 40 rows: 16384 each
+// 1015 / 949; 2048..16384 620 / 624 (100 sequences 887 / 945); 64 of 512 and one of 65536 1000 / 554; 80 rows without
+// collection: 2048..16384 692 / 743, 64 of 512 and one of 65536 807 / 275
+inline int unplanned_pair_chunk(int rows, int max_len) {
+  if (rows > 64) return max_len < 4096 ? max_len : 4096;
+  return max_len > 8192 ? (max_len + 1) / 2 : max_len;
 }
 
 }  // namespace vegas

@@ -148,12 +148,13 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
     // What a workgroup collects is parked in LDS until its chunk ends, so a chunk cannot be arbitrarily long.  A
     // chunk that gives every CU exactly one workgroup is taken as it is while its LDS fits (batch 4 x 64K tokens:
     // 256 chunks of 8192 tokens reach 78 % of the HBM peak, 512 chunks of 4096 tokens 75 %); otherwise chunks are
-    // capped so that two workgroups fit a CU.  (The pair kernel parks nothing per chunk: any chunk length.)
+    // capped so that two workgroups fit a CU.  (64-row workgroups park no whole chunk: unplanned_pair_chunk.)
     const int64_t cap = (columns >= num_cu) ? 2048 : 4096;
     const int prows = rows_per_head < 32 ? rows_per_head : 32;
     const bool fits_alone = columns * splits >= num_cu / 2 &&
                             split_lds_bytes(pl->NW, prows, collect, static_cast<int>(c), d->head_dim) <= 150 * 1024;
     if (!pl->pair && c > cap && !(wg_per_cu == 1 && fits_alone)) c = cap;
+    if (pl->pair && splits == 1) c = (unplanned_pair_chunk(rows_per_head, max_len) + unit - 1) / unit * unit;
     chunk = static_cast<int>(c);
   }
   // A batch of several sequences whose lengths the host does not know (only max_seq_len, which may be loose): every

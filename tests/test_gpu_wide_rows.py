@@ -1,6 +1,7 @@
 """Verification of more than 32 rows per KV head where its kernel can go wrong: chunks of less than a tile to more than a
 wave parks or its ring holds, row counts at the edges of the two row blocks and of a second workgroup, both collection
 modes and none, against the float64 oracle."""
+import numpy as np
 import pytest
 import torch
 
@@ -99,6 +100,30 @@ def test_local_mask_on_both_sides_of_the_one_workgroup_rule(window, Hq, Hkv, D):
     ref_out, _ = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens, L.softmax_scale, 0,
                                     window=window)
     U.check_out(f"local.{window}.{Hq}", path.out_verify, ref_out, U.vmax_visible(L))
+
+
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("Hq,G", [(32, 5), (32, 10)], ids=["40_rows", "80_rows"])
+def test_one_long_sequence_among_more_than_64(Hq, G, D):
+    """No plan (more than 64 sequences): the long one is cut into chunks that the short ones have nothing in."""
+    lens = [int(n) for n in np.random.default_rng(65 + G).integers(0, 40, size=65)]
+    lens[21] = 8209
+    L = synth.make_random_case(seed=6700 + G + D, batch=65, num_q_heads=Hq, num_kv_heads=4, num_queries=G, seq_lens=lens,
+                               head_dim=D, logit_std=2.0, value_std=1.0, outliers=1, outlier_logit=25.0)
+    print(f"[case] one long among 65 Hq={Hq} G={G} D={D}", flush=True)
+    dl = harness.DeviceLayer.upload(L)
+    for collect in (vb.COLLECT_ALL_ROWS, vb.COLLECT_NONE):
+        path = harness.VegasPath.for_layer(L, budget_tokens=256, collect_rows=collect)
+        path.workspace.fill_(0xFF)
+        path.out_verify.fill_(float("nan"))
+        path.block_scores.fill_(float("nan"))
+        path.verify(dl)
+        torch.cuda.synchronize()
+        ref_out, ref_scores = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens,
+                                                 L.softmax_scale, vb.COLLECT_ALL_ROWS)
+        U.check_out(f"one_long.{Hq}.{G}.{collect}", path.out_verify, ref_out, U.vmax_visible(L))
+        if collect:
+            U.check_scores(f"one_long.{Hq}.{G}.{collect}", path.block_scores, ref_scores)
 
 
 def folded_call(G, chunk):
