@@ -211,11 +211,14 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
         store(0);
         return;
       }
-      // Balanced chunking (the plan has to be read before anything can be addressed, so the length is known by now):
-      // a sequence has few of its head's slots, and only those are read.  (Reading as many as the host's bound allows,
-      // most of them other sequences', took the whole kernel 30 us on 24 sequences of 1K..20K tokens with 32 rows; this
-      // and the smaller score role below take 13.7.  16 of 8K..64K tokens, 40 rows: 33 -> 24 us.)
-      if (MAXS == kFinPlanned && ns <= 32) {
+      // A sequence may have few chunks although the host's bound on them is high (balanced chunking bounds them by all
+      // the slots of a head; a loose max_seq_len or a caller's chunk length may too): only its own slots are read, in one
+      // round trip.  (Balanced chunking: the plan has to be read before anything can be addressed, so the length is known
+      // by now.  Reading as many as the host's bound allows, most of them other sequences', took the whole kernel 30 us on
+      // 24 sequences of 1K..20K tokens with 32 rows; this and the smaller score role below take 13.7.  16 of 8K..64K
+      // tokens, 40 rows: 33 -> 24 us.  One sequence of 4000 tokens in chunks of 128 under a bound of 131072, 20 rows, first
+      // and last collected: the whole call 22.0 -> 20.8.)
+      if (ns <= 32) {
         const float* const po = p.part_o + (pbase * p.R + r) * T;
         auto merge = [&](auto maxs) {
           RowMerge<decltype(maxs)::value> rm;
