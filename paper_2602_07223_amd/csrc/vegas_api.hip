@@ -218,7 +218,6 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   off += align_up(hs * static_cast<size_t>(pl->lse_pages) * (collect == 2 ? 1 : pl->Rc) * sizeof(float));
   pl->off_plan = off;
   if (pl->balanced) off += align_up(static_cast<size_t>(d->batch) * sizeof(int2));
-  off += kAlign;                                    // (a spare line: no stage uses it)
   pl->total = off;
   return VEGAS_OK;
 }
@@ -291,8 +290,8 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
       const double ticks = 0.75 * lds.park_tiles * (D == 128 ? 270 : 135);
       sp.epoch_mul = static_cast<uint32_t>(4294967296.0 / (ticks < 256 ? 256 : ticks));
       dim3 pgrid(sp.Hkv, pl.NB * slots, seqs);
-      // Chunks are a dimension of the grid and calls with too many of them are refused, counted in 32-row blocks; up to
-      // 64 rows with chunks of whole 64-token steps were never subject to that, and the grid is folded for them.
+      // Chunks are a dimension of the grid, and the interface's limit on them (vegas.h, kv_chunk_tokens) counts 32-row
+      // blocks.  33 to 64 rows with chunks of a multiple of 64 tokens are exempt from it: the grid is folded for them.
       const int tile_rows = pl.R + (COLLECT == 2 ? 2 : 0);
       const bool folds = pl.R > 32 && tile_rows <= kPairRows && pl.chunk % (2 * kTile) == 0;
       if (!folds && static_cast<uint64_t>((tile_rows + 31) / 32) * slots > 65535u) return VEGAS_ERR_UNSUPPORTED;

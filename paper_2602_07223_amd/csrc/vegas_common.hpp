@@ -93,8 +93,9 @@ struct SplitParams {
   int32_t collect_rows;     // which verification rows are collected (1: all, 2: first and last)
   int32_t Rc;               // collected rows per KV head (collected_count)
   int32_t window;           // > 0: local masking, a row at position pos sees keys pos - window + 1 .. pos (causal calls)
-  uint16_t* out_direct;     // draft calls with one chunk per (sequence, KV head): the bf16 output [B, G, Hq, D], which
-                            // the streaming kernel then normalises and writes itself (nullptr: partials for a merge kernel)
+  uint16_t* out_direct;     // draft calls, and verification with a local mask, with one chunk per (sequence, KV head): the
+                            // bf16 output [B, G, Hq, D], which the streaming kernel then normalises and writes itself
+                            // (nullptr: partials for a merge kernel)
   int32_t park_tiles;       // attn_pair_kernel: tiles of collected values a wave holds back in LDS
   uint32_t epoch_mul;       // attn_pair_kernel: 2^32 / ticks of the wall-clock interval at whose end they leave
   int2* plan;               // balanced chunking (or nullptr): [B] (first partial slot, chunk tokens) per sequence,
