@@ -18,14 +18,14 @@ namespace vegas {
 //      128    1056 -2.4/+0.3/+1.1, 1312 -2.2/+0.8/+2.6            1056 -1.5/-0.5/-0.2, 1312 -1.1/-0.3/+0.6
 //      144    1312 -5.0/-3.7/+0.7                                 1312 -3.9/-2.3/-0.3
 //      160    1312 -4.4/-3.7/+0.2, 2080 -3.8/-1.6/+6.4            1312 -3.9/-2.8/-0.4, 2080 -4.3/-1.9/+3.1
-//      192    2080 -4.0/-4.5/+2.8, 3104 -6.3/-5.3/+7.7            2080 -4.4/-3.3/+1.0, 4128 -6.4/-6.0/+5.9
-//      256    2080 -6.0/-5.0/+3.0, 4128 -23/-4.5/+13              2080 -3.4/-4.2/+0.5, 4128 -5.3/-5.5/+5.4
-//      512    2080 -37/-26/-3.4, 4128 -23/+7.6/+15                2080 -30/-9.4/-5.5, 4128 -15/-2.9/+5.1
-// The lines lie where equal lengths gain and spread ones lose less than half a microsecond; a lone long selection costs up
-// to 3 us more there (192 columns, 2080 tokens: 19 -> 22 us), beyond them up to tens of microseconds.
+//      192    2080 -4.0/-4.5/+2.8, 3104 -6.3/-5.3/+7.7            3104 -4.9/-4.4/+3.6, 4128 -6.4/-6.0/+5.9
+//      256    2080 -6.0/-5.0/+3.0, 4128 -23/-4.5/+13              3104 -5.2/-4.4/+3.1, 4128 -5.3/-5.5/+5.4
+//      512    2080 -37/-26/-3.4, 4128 -23/+7.6/+15                3104 -17/-11/-0.1, 4128 -15/-2.9/+5.1
+// The lines lie where equal and spread lengths gain (at most half a microsecond is lost) and a lone long selection costs up
+// to 3.6 us more (192 columns, 2080 tokens, head dimension 128: 19 -> 22 us); beyond them that is up to tens of microseconds.
 inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
   struct Line { int sixteenths, tokens128, tokens64; };   // from that share of the compute units on
-  constexpr Line lines[] = {{12, 2176, 2176}, {9, 1312, 1312}, {8, 1056, 1056}, {6, 800, 928}, {4, 544, 736}, {0, 416, 608}};
+  constexpr Line lines[] = {{12, 2176, 3200}, {10, 1312, 2176}, {9, 1312, 1312}, {8, 1056, 1056}, {6, 800, 928}, {4, 544, 736}, {0, 416, 608}};
   for (const Line& l : lines)
     if (16 * columns >= static_cast<int64_t>(l.sixteenths) * num_cu) return head_dim == 64 ? l.tokens64 : l.tokens128;
   return 0;

@@ -72,7 +72,7 @@ def test_single_chunk_and_merged_chunks_agree():
 
 @pytest.mark.parametrize("Hkv,n,D", [(8, 416, 128), (8, 417, 128), (8, 608, 64), (8, 609, 64),          # few columns
                                      (64, 544, 128), (64, 545, 128), (96, 928, 64), (96, 929, 64),    # 1/4, 3/8 of the CUs
-                                     (144, 1312, 128), (144, 1313, 128), (192, 2176, 64), (192, 2177, 64),   # 9/16, 3/4
+                                     (144, 1312, 128), (144, 1313, 128), (192, 2176, 128), (192, 2177, 128), (192, 3200, 64), (192, 3201, 64),   # 9/16, 3/4
                                      (8, 544, 128), (8, 545, 128), (8, 1088, 64), (8, 1089, 64),
                                      (96, 2176, 128), (96, 2177, 128),
                                      (192, 2300, 64), (257, 301, 128)])                                 # ... more than one each
