@@ -12,22 +12,25 @@ namespace vegas {
 // Microseconds of a draft call within a GPU-bound iteration (captured; 6 draft calls), one workgroup minus chunks; equal
 // selections / between a tenth and all of the bound / one at the bound beside others of 256 tokens:
 //   columns   head dimension 128                                  head dimension 64
-//     8..48   416 tokens -0.1, 448 +0.2, 512 +0.7, 544 +1.0       544 -0.4, 608 0.0, 672 +0.2, 1056 +2.1   (all equal)
-//    64..80   512 +0.3..-1.7, 544 -0.8, 800 +1.6                  736 -0.4..-0.6, 800 0.0, 1056 +0.5       (all equal)
-//       96    800 -1.0/-0.8/-0.7, 1056 0.0/+1.5/+1.6              928 -0.7/-0.7/-0.7, 1056 -0.1/-0.2/-0.1 (one-token pages: +1.1)
-//      128    1056 -2.4/+0.3/+1.1, 1312 -2.2/+0.8/+2.6            1056 -1.5/-0.5/-0.2, 1312 -1.1/-0.3/+0.6
-//      144    1312 -5.0/-3.7/+0.7                                 1312 -3.9/-2.3/-0.3
-//      160    1312 -4.4/-3.7/+0.2, 2080 -3.8/-1.6/+6.4            1312 -3.9/-2.8/-0.4, 2080 -4.3/-1.9/+3.1
-//      192    2080 -4.0/-4.5/+2.8, 3104 -6.3/-5.3/+7.7            3104 -4.9/-4.4/+3.6, 4128 -6.4/-6.0/+5.9
-//      256    2080 -6.0/-5.0/+3.0, 4128 -23/-4.5/+13              3104 -5.2/-4.4/+3.1, 4128 -5.3/-5.5/+5.4
-//      512    2080 -37/-26/-3.4, 4128 -23/+7.6/+15                3104 -17/-11/-0.1, 4128 -15/-2.9/+5.1
-// The lines lie where equal and spread lengths gain (at most half a microsecond is lost) and a lone long selection costs up
-// to 3.6 us more (192 columns, 2080 tokens, head dimension 128: 19 -> 22 us); beyond them that is up to tens of microseconds.
+//     8..48   416 tokens -0.1, 448 +0.2..-0.3, 544 +1.0             608 0.0, 672 +0.2, 800 +0.9, 1056 +2.1     (all equal)
+//       64    544 -0.1/+0.1/+0.7, 800 +1.6                          800 0.0, 928 +0.6/+0.6/+0.7
+//       80    544 -1.0/-0.4/+0.5                                    928 -0.1/-0.2/-0.4
+//       96    800 -1.0/-0.8/-0.7, 1056 0.0/+1.5/+1.6                928 -0.7/-0.7/-0.7, 2080 -0.4/+2.5/+4.6
+//      128    1312 -2.3/+0.7/+2.7, 2080 -1.5/+2.7/+7.7              2080 -3.4/+0.8/+3.8, 3104 -3.4/+4.1/+7.8
+//      136    1312 -5.4/-2.4/+0.7, 2080 -6.6/+2.5/+6.5              3104 -6.7/-0.9/+6.5
+//      144    2080 -5.9/-1.2/+6.7                                   3104 -6.7/-3.6/+6.5
+//      176    2080 -5.1/-5.2/+2.6                                   3104 -5.9/-4.5/+3.8
+//      192    3200 -8.0/-4.9/+8.5, 6176 -7.9/-6.1/+23               3200 -5.6/-4.1/+4.2, 6176 -7.4/-5.7/+12
+//      256    3200 -6.2/-3.3/+8.6, 6176 -18/-24/+30                 3200 -6.3/-3.7/+3.4, 6176 -17/-14/+14
+//      320    3200 +0.4/-10/+5.4, 4128 +7.2/+21/+14                 3200 -2.6/-3.2/+0.9, 4128 +11/-1.6/+5.4
+// The lines lie where a call gains with equal and with spread lengths (0.8 us lost at most) and a lone long selection takes no
+// more than half as long again (192 columns, 3200 tokens, head dimension 128: 24 -> 32 us, in an iteration of 319).
 inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
-  struct Line { int sixteenths, tokens128, tokens64; };   // from that share of the compute units on
-  constexpr Line lines[] = {{12, 2176, 3200}, {10, 1312, 2176}, {9, 1312, 1312}, {8, 1056, 1056}, {6, 800, 928}, {4, 544, 736}, {0, 416, 608}};
+  struct Line { int per32, tokens128, tokens64; };        // from that many 32nds of the compute units on
+  constexpr Line lines[] = {{24, 3200, 3200}, {18, 2176, 3200}, {17, 1312, 3200}, {16, 1312, 2176},
+                            {12, 800, 928}, {9, 544, 928}, {0, 448, 672}};
   for (const Line& l : lines)
-    if (16 * columns >= static_cast<int64_t>(l.sixteenths) * num_cu) return head_dim == 64 ? l.tokens64 : l.tokens128;
+    if (32 * columns >= static_cast<int64_t>(l.per32) * num_cu) return head_dim == 64 ? l.tokens64 : l.tokens128;
   return 0;
 }
 

@@ -70,9 +70,11 @@ def test_single_chunk_and_merged_chunks_agree():
     U.check_out("draft.merged_chunks", b, ref, U.vmax_visible(L))
 
 
-@pytest.mark.parametrize("Hkv,n,D", [(8, 416, 128), (8, 417, 128), (8, 608, 64), (8, 609, 64),          # few columns
-                                     (64, 544, 128), (64, 545, 128), (96, 928, 64), (96, 929, 64),    # 1/4, 3/8 of the CUs
-                                     (144, 1312, 128), (144, 1313, 128), (192, 2176, 128), (192, 2177, 128), (192, 3200, 64), (192, 3201, 64),   # 9/16, 3/4
+@pytest.mark.parametrize("Hkv,n,D", [(8, 448, 128), (8, 449, 128), (8, 672, 64), (8, 673, 64),          # few columns
+                                     (72, 544, 128), (72, 545, 128), (96, 928, 64), (96, 929, 64),      # 9/32, 3/8 of the CUs
+                                     (128, 1312, 128), (128, 1313, 128), (128, 2176, 64), (128, 2177, 64),   # half
+                                     (144, 2176, 128), (144, 2177, 128),                                # 9/16
+                                     (192, 3200, 128), (192, 3201, 128), (192, 3200, 64), (192, 3201, 64),   # 3/4
                                      (8, 544, 128), (8, 545, 128), (8, 1088, 64), (8, 1089, 64),
                                      (96, 2176, 128), (96, 2177, 128),
                                      (192, 2300, 64), (257, 301, 128)])                                 # ... more than one each

@@ -135,16 +135,15 @@ int main() {                       // lines of: columns, head dimension, band, c
 
 
 def test_rules_for_calls_without_a_merge(tmp_path):
-    """A column is left to one workgroup where that was measured no slower, for selections of unequal length too: never the
-    longer the fewer columns there are, and not beyond 2176 (head dimension 64: 3200) tokens however many."""
-    measured = [(8, 128, 416, True), (8, 128, 544, False), (64, 128, 544, True), (64, 128, 800, False),
-                (8, 64, 544, True), (32, 64, 608, True), (16, 64, 800, False), (64, 64, 1056, False), (16, 64, 1056, False),
-                (96, 128, 800, True), (96, 128, 1056, False), (96, 64, 928, True), (128, 128, 2080, False),
-                (128, 64, 2080, False), (160, 128, 1312, True), (160, 128, 2080, False), (160, 64, 2080, True), (160, 64, 4128, False),
-                (192, 128, 2080, True), (192, 64, 3104, True),
-                (192, 128, 6176, False), (192, 64, 4128, False), (256, 128, 4128, False), (512, 64, 2080, True),
-                (512, 128, 6176, False)]
-    every = [(c, D) for D in (128, 64) for c in (1, 8, 24, 63, 64, 65, 95, 96, 127, 128, 143, 144, 159, 160, 191, 192, 256, 1000)]
+    """A column is left to one workgroup where that was measured faster, for selections of unequal length too (or within a
+    microsecond): never the longer the fewer columns there are, and not beyond 3200 tokens however many."""
+    measured = [(8, 128, 416, True), (8, 128, 544, False), (80, 128, 544, True), (64, 128, 800, False),
+                (8, 64, 608, True), (32, 64, 608, True), (16, 64, 800, False), (64, 64, 1056, False), (16, 64, 1056, False),
+                (96, 128, 800, True), (96, 128, 1056, False), (80, 64, 928, True), (96, 64, 928, True), (96, 64, 2080, False),
+                (128, 128, 1312, True), (128, 128, 2080, False), (128, 64, 2080, True), (128, 64, 3104, False),
+                (136, 64, 3104, True), (136, 128, 2080, False), (144, 128, 2080, True), (144, 64, 3104, True), (192, 128, 3200, True), (192, 128, 6176, False),
+                (256, 64, 3200, True), (256, 64, 6176, False), (320, 128, 4128, False), (512, 64, 2080, True)]
+    every = [(c, D) for D in (128, 64) for c in (1, 8, 24, 71, 72, 95, 96, 127, 128, 135, 136, 143, 144, 191, 192, 256, 1000)]
     bands = [(389, 128, True), (517, 128, False), (517, 256, False), (1029, 1024, False), (1029, 1792, True),
              (2053, 1792, False), (4101, 15744, True)]
     ask = [(c, D, 1, 1) for c, D, _, _ in measured] + [(c, D, 1, 1) for c, D in every] + [(8, 128, s, c) for s, c, _ in bands]
@@ -156,7 +155,7 @@ def test_rules_for_calls_without_a_merge(tmp_path):
     limits = dict(zip(every, (o[0] for o in out[len(measured):])))
     for D in (128, 64):
         per = [limits[(c, D)] for c, d in every if d == D]
-        assert per == sorted(per) and per[-1] == (2176 if D == 128 else 3200)
+        assert per == sorted(per) and per[-1] == 3200
     for (seen, chunk, alone), (_, got) in zip(bands, out[-len(bands):]):
         assert bool(got) == alone, (seen, chunk)
 
