@@ -5,7 +5,7 @@
 // of K and V.  Two row blocks leave no registers for tiles in flight (128 accumulators), so K and V never pass through
 // registers on their way in: they are loaded straight into LDS.
 //   * A workgroup = 4 waves on one (sequence, KV head, chunk); every wave takes a contiguous quarter of the chunk's
-//     32-token tiles and owns a ring of LDS (2 tiles at head dimension 128, 4 at 64; pair_ring) that only it
+//     32-token tiles and owns a ring of LDS (2 tiles, or 4 at head dimension 64; pair_ring) that only it
 //     fills and reads, so the streaming loop has no barrier and no wave waits for another one.
 //   * K goes into a ring slot as soon as the first contraction has read the slot's old K, V as soon as the second one
 //     has read the old V: 64 to 128 KB per compute unit are in flight all the time.  The load counter returns in
@@ -27,12 +27,13 @@
 //     reads); bursts at common times that are written THROUGH the L2 took 362.  So a wave parks its tiles' values in
 //     LDS and writes them through when the wall clock enters a new interval, or its part of the LDS is full.  (When a
 //     value leaves depends on the clock; the value does not.)
-// Streaming kernel, 40 rows: 16 x 36864 tokens 412 us, 380 without collection (6.4 TB/s; a store per tile cost 90 us);
-// 16 of 8192..65536 tokens 483 -> 441; one sequence of 32768 25.8 -> 19.8 us at head dimension 64, 48 rows at 128 40.2 ->
-// 27.9: against the kernel this one replaced, which passed K and V through the registers of two waves and their LDS
-// tiles between two barriers per 64 tokens.  What bounds it: HBM from 64K tokens on, its head and merge below.
-// (Taken with the rarer rescaling; the true maximum adds 0.2 % to the long launches and 1 us to the 32K one.)
-// Rows beyond 64 go to sibling workgroups of 64 rows each.
+// Streaming kernel, 40 rows, captured launches: 16 x 36864 tokens 403 us, 376 without collection (6.4 TB/s; a store per
+// tile cost 90 us); 16 of 8192..65536 tokens 443 and 399; one of 32768 20.6 at head dimension 64; 48 rows, two of twelve
+// tokens' collected, 28.5 at 128.  By the profiler within whole iterations 437, 22.8 and 29.9; the kernel this one replaced,
+// which passed K and V through the registers of two waves and their LDS tiles between two barriers per 64 tokens, 483,
+// 25.8 and 40.2.  What bounds it: HBM from 64K tokens on, its head and merge below.
+// Rows beyond 64 go to sibling workgroups of 64 rows each; small calls of that kind stay with attn_split_kernel
+// (rows_as_siblings).
 #pragma once
 #include <type_traits>
 
