@@ -68,7 +68,7 @@ inline bool rows_as_siblings(int batch, int kv_heads, int max_len, int rows, int
   if (tile_rows <= 64 && (rows > 32 || tile_rows <= 32)) return false;   // (33..62 rows: 64-row workgroups at any size)
   const int64_t bound = static_cast<int64_t>(batch) * kv_heads * max_len;
   if (collect_rows == 0) return bound <= 160000;
-  if (batch >= 8) return batch > 64;
+  if (batch >= 8) return batch > 64 && max_len < (1 << 24);        // (beyond, too many of a sibling's chunks for a launch grid)
   if (token_sums) return bound <= (blocks != 3 ? 100000 : collect_rows == 2 ? 1 << 18 : (1 << 24) / head_dim);
   if (collect_rows == 1) return bound <= (blocks <= 3 ? 100000 : 50000);
   return blocks <= 3 && bound * head_dim <= (1 << 24);
@@ -81,7 +81,10 @@ inline bool rows_as_siblings(int batch, int kv_heads, int max_len, int rows, int
 // 1015 / 949; 2048..16384 620 / 624 (100 sequences 887 / 945); 64 of 512 and one of 65536 1000 / 554; 80 rows without
 // collection: 2048..16384 692 / 743, 64 of 512 and one of 65536 807 / 275
 inline int unplanned_pair_chunk(int rows, int max_len) {
-  if (rows > 64) return max_len < 4096 ? max_len : 4096;
+  if (rows > 64) {
+    const int chunk = max_len < (1 << 24) ? 4096 : max_len / 4096;   // (chunks are a dimension of the launch grid)
+    return max_len < chunk ? max_len : chunk;
+  }
   return max_len > 8192 ? (max_len + 1) / 2 : max_len;
 }
 

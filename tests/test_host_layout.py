@@ -1,6 +1,6 @@
 """Index arithmetic that kernels and host code share, checked on the CPU: the headers' host-callable functions are compiled
 into a small program and compared with the rules written out here."""
-import os
+import bisect
 import subprocess
 
 import numpy as np
@@ -160,7 +160,8 @@ def test_rules_for_calls_without_a_merge(tmp_path):
         assert bool(got) == alone, (seen, chunk)
 
 
-@pytest.mark.parametrize("rows,n,chunks", [(40, 8192, 1), (40, 8193, 2), (64, 16384, 2), (80, 4096, 1), (80, 65536, 16), (128, 16384, 4)])
+@pytest.mark.parametrize("rows,n,chunks", [(40, 8192, 1), (40, 8193, 2), (64, 16384, 2), (80, 4096, 1), (80, 65536, 16), (128, 16384, 4),
+                                           (128, (1 << 24) - 16, 4096), (128, 1 << 28, 4096)])
 def test_many_sequences_are_not_left_to_a_workgroup_each(rows, n, chunks):
     """More than 64 sequences have no plan: a long one is cut all the same."""
     assert chunk_slots(65, rows, 8, n) == 65 * 8 * chunks
@@ -172,7 +173,7 @@ def chunk_slots(batch, rows, kv_heads, max_len, head_dim=128, group=8):
                         max_blocks=-(-max_len // 16), max_sel_blocks=1, max_seq_len=max_len, num_pages=1 << 20,
                         softmax_scale=0.1, collect_rows=vb.COLLECT_NONE, head_dim=head_dim, page_size=16)
     total, up = vb.vegas_workspace_bytes(desc), lambda x: -(-x // 256) * 256
-    return max(s for s in range(1, 1 << 15) if up(s * rows * head_dim * 4) + up(s * rows * 8) <= total)
+    return bisect.bisect_right(range(1, 1 << 26), total, key=lambda s: up(s * rows * head_dim * 4) + up(s * rows * 8))
 
 
 @pytest.mark.parametrize("rows,n", [(40, 4097), (64, 12345), (40, 32749), (64, 65521), (72, 32749), (96, 65521), (128, 32749)])
@@ -230,6 +231,7 @@ def test_wide_rows_as_siblings_where_that_is_faster(tmp_path):
                 ((1, 8, 32749, 64, 2, 1, 128), 1), ((1, 8, 32749, 64, 1, 1, 128), 0), ((4, 8, 16384, 80, 1, 1, 64), 0),
                 ((16, 8, 1200, 64, 1, 1, 128), 0), ((65, 8, 16384, 80, 1, 0, 64), 1), ((65, 8, 65536, 80, 2, 0, 128), 1),
                 ((65, 8, 65536, 80, 0, 0, 128), 0), ((65, 8, 65536, 40, 1, 0, 128), 0), ((64, 8, 65536, 80, 1, 0, 128), 0),
+                ((65, 8, 1 << 24, 80, 1, 0, 128), 0), ((65, 1, 1 << 30, 128, 2, 0, 64), 0),
                 ((1, 8, 4096, 31, 1, 1, 128), 1), ((1, 8, 4096, 30, 1, 1, 128), 0)]
     out = run_host_program(tmp_path, SIBLINGS, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
     assert [int(x) for x in out] == [s for _, s in measured]
