@@ -161,7 +161,7 @@ def test_rules_for_calls_without_a_merge(tmp_path):
 
 
 @pytest.mark.parametrize("rows,n,chunks", [(40, 8192, 1), (40, 8193, 2), (64, 16384, 2), (80, 4096, 1), (80, 65536, 16), (128, 16384, 4),
-                                           (128, (1 << 24) - 16, 4096), (128, 1 << 28, 4096)])
+                                           (128, (1 << 24) - 16, 4096), (128, 1 << 26, 4096)])
 def test_many_sequences_are_not_left_to_a_workgroup_each(rows, n, chunks):
     """More than 64 sequences have no plan: a long one is cut all the same."""
     assert chunk_slots(65, rows, 8, n) == 65 * 8 * chunks
