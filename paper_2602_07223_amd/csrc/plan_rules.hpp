@@ -35,7 +35,7 @@ inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
 }
 
 // Verification with a local mask: does one workgroup per column (sequence x KV head x row block) stream the whole band
-// (`seen` = window + queries tokens, no row sees more) and write the output rows, or is the context cut into chunks
+// (no row sees more than window + queries tokens, nor than the longest sequence has) and write the output rows, or is the context cut into chunks
 // (`chunk` tokens, of which the band touches a few) and merged?  Cutting only helps where the chunks are shorter than the
 // band: us, chunks + merge / one workgroup, head dimension 128, 20 rows, by chunk length and band:
 //   128: 261 10.8 / 10.2, 389 10.8 / 10.0, 517 10.9 / 12.3, 1029 11.0 / 16.3;   256 (40 rows): 389 10.6 / 10.3, 517 10.6 / 12.6
@@ -44,7 +44,11 @@ inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
 // head dimension 64:  128: 389 9.1 / 7.5, 517 9.1 / 9.5;  1024: 1029 13.2 / 12.6;  1792: 1029 15.1 / 12.7, 2053 17.7 / 18.6.
 // (Where in its chunk a band of less than a chunk falls decides whether it is one part or two, which is worth up to half
 // of the streaming time: the figures are for one place at batch 1, for a batch of many beyond.)
-inline bool lone_workgroup_band(int64_t seen, int chunk) { return seen <= 416 || seen <= chunk; }
+inline bool lone_workgroup_band(int window, int queries, int max_len, int chunk) {
+  int64_t seen = static_cast<int64_t>(window) + queries;
+  if (seen > max_len) seen = max_len;
+  return seen <= 416 || seen <= chunk;
+}
 
 // Verification of more than 64 rows per KV head (with the two sum rows of the logit metric, and there of just above 32 as
 // well): sibling workgroups of 32 rows (attn_split_kernel, two per compute unit, each reading K and V through the L2)

@@ -169,7 +169,7 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   // window + G - 1 tokens, and a workgroup begins where the first of them is (16 sequences of 8192..65536 tokens, 40 rows,
   // head dimension 64, window 128: 11.7 us with a merge, 8.1 without).
   const bool banded = !may_finish && d->window > 0 && d->kv_chunk_tokens == 0 &&
-                      lone_workgroup_band(static_cast<int64_t>(d->window) + d->num_queries, chunk);
+                      lone_workgroup_band(d->window, d->num_queries, max_len, chunk);
   const bool finish = banded || (own_chunks && rows_per_head <= kDraftRows && max_len <= lone_workgroup_tokens(heads, num_cu, d->head_dim));
   // (A call that one workgroup per column finishes uses no partials; its workspace is sized for the chunked plan all
   //  the same, so that these rules move neither the sizes callers allocate nor what the built-in scratch takes.)

@@ -83,11 +83,14 @@ def test_odd_numbers_of_collected_rows(Hq, Hkv, G, D):
 
 
 @pytest.mark.parametrize("Hq,Hkv,D", [(16, 2, 64), (8, 2, 128), (96, 96, 128)], ids=["40_rows", "20_rows", "96_columns"])
-@pytest.mark.parametrize("window", [1, 128, 411, 412, 507, 508, 539, 540, 1083, 1084, 2171, 2172])
+@pytest.mark.parametrize("window", [1, 128, 411, 412, 507, 508, 539, 540, 1083, 1084, 2171, 2172, 9600])
 def test_local_mask_on_both_sides_of_the_one_workgroup_rule(window, Hq, Hkv, D):
     """The rule changes at a band of 416 tokens, or of a chunk where that is longer (256 compute units: 512 tokens with
-    40 rows, 2176 with 96 columns); 9000 tokens make a workgroup begin behind its first batch of page ids."""
+    40 rows, 2176 with 96 columns); 9000 tokens make a workgroup begin behind its first batch of page ids.
+    A window longer than the context is a band of the context: 400 tokens are left to one workgroup."""
     lens = [9000, 0, 1, 4100] if Hkv == 2 else [4500]
+    if window > 9000:
+        lens = [400, 0, 1, 137] if Hkv == 2 else [400]
     L = synth.make_random_case(seed=6300 + window + Hq, batch=len(lens), num_q_heads=Hq, num_kv_heads=Hkv, num_queries=5,
                                seq_lens=lens, head_dim=D, logit_std=1.5, value_std=1.0)
     print(f"[case] local mask W={window} Hq={Hq} Hkv={Hkv} D={D}", flush=True)
