@@ -36,14 +36,10 @@ struct RowMerge {
     const int lane = threadIdx.x & 63;
     const bool live = lane >= s_lo && lane < ns;
     const float ms = live ? mine[0] : -INFINITY;
-    float m = ms;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    const float m = wave_max(ms);
     const float m_use = (m == -INFINITY) ? 0.f : m;
     const float w = fast_exp2(ms - m_use);              // 0 for lanes at or past ns
-    float L = live ? w * mine[1] : 0.f;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) L += __shfl_xor(L, off, 64);
+    const float L = wave_sum(live ? w * mine[1] : 0.f);
     float acc = 0.f;
 #pragma unroll
     for (int s = 0; s < MAXS; ++s) {
@@ -100,8 +96,7 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p
   // pass 1: global max over chunks
   float m = -INFINITY;
   for (int s = s_lo + tid; s < ns; s += T) m = fmaxf(m, ml[static_cast<int64_t>(s) * p.R].x);
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  m = wave_max(m);
   if ((tid & 63) == 0) sred[wave] = m;
   __syncthreads();
   m = T > 64 ? fmaxf(sred[0], sred[1]) : sred[0];
@@ -118,8 +113,7 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p
       sw[tid] = w;
       wl = w * v.y;
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) wl += __shfl_xor(wl, off, 64);
+    wl = wave_sum(wl);
     if ((tid & 63) == 0) sred[2 + wave] = wl;
     __syncthreads();
     L += T > 64 ? sred[2] + sred[3] : sred[2];
@@ -238,8 +232,7 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
       const int64_t ostride = static_cast<int64_t>(p.R) * T;
       float m = -INFINITY;
       for (int s = t128; s < ns; s += T) m = fmaxf(m, ml[static_cast<int64_t>(s) * p.R].x);
-#pragma unroll
-      for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+      m = wave_max(m);
       if ((tid & 63) == 0) sred[wv] = m;
       __syncthreads();
       m = T > 64 ? fmaxf(sred[0], sred[1]) : sred[0];
@@ -254,8 +247,7 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
           sw[t128] = w;
           wl = w * v.y;
         }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) wl += __shfl_xor(wl, off, 64);
+        wl = wave_sum(wl);
         if ((tid & 63) == 0) sred[2 + wv] = wl;
         __syncthreads();
         L += T > 64 ? sred[2] + sred[3] : sred[2];
