@@ -320,7 +320,7 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
   if constexpr (MAXS == kFinPlanned) {
     int n0 = p.lens[b];
     n0 = n0 < 0 ? 0 : (n0 > p.max_tokens ? p.max_tokens : n0);
-    ns_live = (n0 + cs.chunk - 1) / cs.chunk;
+    ns_live = column_chunks(cs, n0).ns;
     if (jbase * kPage >= n0) {                                     // whole workgroup past the sequence
       if (tid < 32 && jbase + tid < p.max_blocks) out_row[jbase + tid] = 0.f;
       return;
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
 
   int n = p.lens[b];
   n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
-  const int ns = (n + cs.chunk - 1) / cs.chunk;
+  const int ns = column_chunks(cs, n).ns;
   const int nblk = (n + kPage - 1) / kPage;
   if (jbase >= nblk) {                                             // whole workgroup past the sequence
     if (tid < 32 && jbase + tid < p.max_blocks) out_row[jbase + tid] = 0.f;

@@ -136,19 +136,19 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
     b %= seqs;
   }
   const int rb = ONE ? 0 : yy % p.row_blocks;
-  const int slot_j = ONE ? yy : yy / p.row_blocks;
-  int split = slot_j;
+  const int split = ONE ? yy : yy / p.row_blocks;
   int chunk_tokens = p.chunk_tokens;
+  int c0 = split * chunk_tokens;
   int64_t pbase = (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + split;   // this workgroup's partial slot
-  if (p.plan) {                              // balanced chunking: slot j of this head -> (sequence, chunk)
-    const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2, pair_second_cost(D, COLLECT),
-                                          p.chunk_cap_units, p.chunk_unit, slot_j,
+  if (p.plan) {                              // balanced chunking: workgroup `split` of this head -> (sequence, tokens)
+    const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2, p.share_wgs,
+                                          p.share_group, 4, pair_second_cost(D, COLLECT), p.chunk_cap_units, p.chunk_unit, split,
                                           ((blockIdx.x | yy) == 0 && wave == 0) ? p.plan : nullptr);
     if (bs.b < 0) return;
     b = __builtin_amdgcn_readfirstlane(bs.b);
-    split = __builtin_amdgcn_readfirstlane(bs.split);
+    c0 = __builtin_amdgcn_readfirstlane(bs.c0);
     chunk_tokens = __builtin_amdgcn_readfirstlane(bs.chunk);
-    pbase = static_cast<int64_t>(h) * p.slots_total + slot_j;
+    pbase = static_cast<int64_t>(h) * p.slots_total + __builtin_amdgcn_readfirstlane(bs.slot);
   }
   const int row0 = kPairRows * rb;           // first query row (of this KV head) of this workgroup
   const int Rl = max(min(kPairRows, p.R - row0), 0);   // valid rows (none in a block that only carries the sum rows)
@@ -156,7 +156,6 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
   // Page ids through the scalar path: entry clamped to the table row, id to the pool.
   typedef const __attribute__((address_space(4))) int32_t* sptr;
   const sptr table = (sptr)(p.table + static_cast<int64_t>(b) * p.table_stride);
-  const int c0 = split * chunk_tokens;
   auto into_pool = [&](int raw) -> int {
     return static_cast<int>(raw < 0 ? 0 : (static_cast<int64_t>(raw) >= p.num_pages ? p.num_pages - 1 : raw));
   };

@@ -203,24 +203,23 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
   // head-fastest, so the 8 KV heads of a chunk still land on the 8 XCDs and sibling row blocks share one.
   const int h = blockIdx.x;
   const int rb = p.row_blocks == 1 ? 0 : static_cast<int>(blockIdx.y) % p.row_blocks;
-  int split = p.row_blocks == 1 ? static_cast<int>(blockIdx.y) : static_cast<int>(blockIdx.y) / p.row_blocks;
+  const int split = p.row_blocks == 1 ? static_cast<int>(blockIdx.y) : static_cast<int>(blockIdx.y) / p.row_blocks;
   int b = blockIdx.z;
   int chunk_tokens = p.chunk_tokens;
-  bool planned = false;                      // balanced chunking: the partial slot is the plan's
+  int c0 = split * chunk_tokens;
+  int64_t pbase = (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + split;   // this workgroup's partial slot
   if constexpr (CAUSAL && PS == 4 && !LOCAL) {
-    if (p.plan) {                            // balanced chunking: slot j of this head -> (sequence, chunk)
-      const int j = split;
-      const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2, 0,
-                                            p.chunk_cap_units, p.chunk_unit, j,
+    if (p.plan) {                            // balanced chunking: workgroup `split` of this head -> (sequence, tokens)
+      const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2, p.share_wgs,
+                                            p.share_group, 2, 2, p.chunk_cap_units, p.chunk_unit, split,
                                             ((blockIdx.x | blockIdx.y) == 0 && wave == 0) ? p.plan : nullptr);
       if (bs.b < 0) return;
       b = bs.b;
-      split = bs.split;
+      c0 = bs.c0;
       chunk_tokens = bs.chunk;
-      planned = true;
+      pbase = static_cast<int64_t>(h) * p.slots_total + bs.slot;
     }
   }
-  const int slot_j = p.row_blocks == 1 ? static_cast<int>(blockIdx.y) : static_cast<int>(blockIdx.y) / p.row_blocks;
   const int row0 = rb * 32;                  // first query row (of this KV head) handled here
   const int Rl = max(min(32, p.R - row0), 0);   // valid rows in this block (none in a block that only carries the sum rows)
 
@@ -230,7 +229,6 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
   // known (one memory round trip less at the head of the kernel): indices are clamped to the table
   // row, entries past the sequence's pages are read but never used.
   const int32_t* table = p.table + static_cast<int64_t>(b) * p.table_stride;
-  const int c0 = split * chunk_tokens;
   const int tile_first = c0 / kTile + wave;
   int pagevec = 0;
   auto table_entry = [&](int kbase) -> int {           // (raw: clamped into the pool by the caller)
@@ -281,9 +279,6 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
   float* lse_lds = reinterpret_cast<float*>(smem + NW * 32 * kRowPitch);
   float* tok_lds = lse_lds;                  // COLLECT == 2: [2][chunk tokens] high-part and low-part token sums
   int* ids_lds = reinterpret_cast<int*>(sm_l + NW * NB * 32) + wave * 64;   // [2 tiles][32 page ids] of this wave
-  // this workgroup's partial slot
-  const int64_t pbase = planned ? static_cast<int64_t>(h) * p.slots_total + slot_j
-                                : (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + split;
   int ids_pending = 0;
   if constexpr (PS == 4) pagevec = into_pool(first_entry);
   else ids_pending = into_pool(first_entry);

@@ -17,18 +17,6 @@ constexpr int kSelectThreads = 1024;
 constexpr int kSelectKeyCap = 16384;   // keys kept in LDS (64 KB); longer prefixes re-read the scores
 constexpr int kSelectRegRows = 8;      // prefixes of up to 8 x 1024 pages keep their keys in registers instead
 
-// Inclusive prefix sum over the 64 lanes of a wave with DPP row shifts and row broadcasts (no LDS).
-__device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
-  int v = static_cast<int>(x);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
-  return static_cast<uint32_t>(v);
-}
-
 // Order-preserving key of a score (larger float <=> larger unsigned); -0 is folded onto +0 and every NaN onto
 // key 0, below -infinity: a NaN score ranks last, NaNs among themselves by index like any other tie.
 __device__ __forceinline__ uint32_t score_key(float s) {

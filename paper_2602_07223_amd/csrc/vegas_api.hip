@@ -27,6 +27,7 @@ using namespace vegas;
 
 constexpr int kDefaultCU = 256;       // MI355X compute units: assumed where no device is visible
 constexpr size_t kAlign = 256;
+constexpr size_t kLoneLds = 81 * 1024;   // LDS of a workgroup that is to have a compute unit to itself
 
 // Compute units of the current device, asked once per device.  The launch plans aim at one or two workgroups per
 // compute unit, and the workspace is sized from the same plans, so sizing and launching must see the same number:
@@ -62,7 +63,7 @@ struct SplitPlan {
   int R = 0, Rc = 0, NB = 0, NW = 0, chunk = 0, nsplit = 0, lse_pages = 0;   // Rc: collected rows per KV head
   bool pair = false;                 // verification of more than 32 rows per KV head: 64-row workgroups (attn_pair_kernel)
   bool balanced = false;             // chunk lengths per sequence, computed on the GPU from the lengths (ragged batches)
-  int J = 0, J2 = 0, JS = 0;         // balanced: workgroups per KV head of a one-wave and a two-wave plan; slots held
+  int J = 0, J2 = 0, JS = 0, JR = 0; // balanced: workgroups per KV head of a one-wave and a two-wave plan; slots held; running at a time
   int cap_units = 0;                 // balanced: longest chunk, in units of kTile * NW tokens
   size_t off_plan = 0;               // balanced: [B] (first slot, chunk tokens)
   size_t off_part_o = 0, off_part_ml = 0, off_page_lse = 0, total = 0;
@@ -179,13 +180,17 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   pl->nsplit = (max_len + chunk - 1) / chunk;
   if (pl->balanced) {
     // one workgroup per CU with chunks as long as its LDS can park (16 x 36864 tokens, 20 rows: 256 chunks of
-    // 18432 tokens reach 80 % of the peak, 512 of 9216 75 %, 4096-token chunks 69 %); two waves when the
-    // lengths are too ragged for one.  The same for 64-row workgroups, which park no whole chunk (4 x 65536 tokens, 40
-    // rows: 256 chunks 196 us, 512 198, 1024 208; 2 x 8192: 18.5, 26.9, 36.1; 16 of 8192..65536: 488, 450, 447).
+    // 18432 tokens reach 80 % of the peak, 512 of 9216 75 %, 4096-token chunks 69 %), or shares of the batch when the
+    // lengths are too ragged for equal chunks.  The same for 64-row workgroups, which park no whole chunk (4 x 65536 tokens, 40
+    // rows: 256 chunks 196 us, 512 198, 1024 208; 2 x 8192: 18.5, 26.9, 36.1).
     pl->J = static_cast<int>(num_cu / per_head);
-    // (slots no plan uses still cost a workgroup that works that out, at one workgroup per CU in a wave of their
-    // own behind the others: a small batch, whose kernel is short, gets the one-wave plan only)
-    pl->J2 = d->batch >= 8 ? 2 * pl->J : pl->J;
+    // Slots no plan uses still cost a workgroup that works that out, so only those that can be used are launched: two waves
+    // of equal chunks are planned for where there are more sequences than workgroups, or where workgroups that park nothing
+    // run side by side.
+    const bool two_per_cu = pl->pair && pair_two_per_cu(d->head_dim, collect);
+    pl->JR = two_per_cu ? 2 * pl->J : pl->J;
+    const bool two_waves = d->batch > pl->J || (two_per_cu && d->batch >= 8) || (!pl->pair && collect == 0 && 2 * d->batch > pl->J);
+    pl->J2 = two_waves ? 2 * pl->J : pl->J;
     int cap = 1 << 24;
     if (collect != 0 && !pl->pair) {
       const int prows = rows_per_head < 32 ? rows_per_head : 32;
@@ -196,10 +201,11 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
     pl->chunk = collect != 0 && !pl->pair ? cap : unit;         // sizes the LDS that parks a chunk's collected values
     int64_t most_chunks = (static_cast<int64_t>(max_len) + cap - 1) / cap;   // of one sequence
     if (most_chunks < pl->J2) most_chunks = pl->J2;
-    if (pl->J < 1) pl->J = 1;
-    if (pl->J2 < pl->J) pl->J2 = pl->J;
-    // slots: a plan for J2 workgroups never takes more than max(J2, B) of them; a capped one B * most_chunks
+    // slots: a plan for J2 workgroups never takes more than max(J2, B) of them; a capped one B * most_chunks; JR shares one
+    // each and one more where a sequence ends inside a share (there are at most as many sequences as shares)
     int64_t js = pl->J2 > d->batch ? pl->J2 : d->batch;
+    const int64_t shared = pl->JR + (d->batch < pl->JR ? d->batch : pl->JR) - 1;
+    if (shared > js) js = shared;
     const int64_t capped = static_cast<int64_t>(d->batch) * ((static_cast<int64_t>(max_len) + static_cast<int64_t>(pl->cap_units) * unit - 1) /
                                                             (static_cast<int64_t>(pl->cap_units) * unit));
     if (capped > js) js = capped;
@@ -309,7 +315,13 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
                                 : dim3(sp.Hkv, static_cast<unsigned>(pl.NB) * pl.nsplit, batch);
   if (grid.y > 65535u) return VEGAS_ERR_UNSUPPORTED;        // more chunks per sequence than a grid dimension holds
   const int rows = pl.R < 32 ? pl.R : 32;
-  const size_t lds = split_lds_bytes(pl.NW, rows, COLLECT, pl.chunk, D);
+  size_t lds = split_lds_bytes(pl.NW, rows, COLLECT, pl.chunk, D);
+  // A long batch's workgroups have a compute unit to themselves, as their plan assumes: sharing one, the pieces of a plan by
+  // shares all start at once, on some units two (no collection, 24 sequences of 1001..20011 tokens 184 -> 200 us; 48 of 300..3000
+  // in equal chunks 70 -> 79).  Short ones gain from workgroups side by side (16 of 300..1200 18.4 us, alone 18.9).
+  if (pl.balanced && lds < kLoneLds &&
+      static_cast<int64_t>(batch) * sp.max_tokens >= static_cast<int64_t>(16) * pl.J * sp.chunk_unit)
+    lds = kLoneLds;
   sp.lds_q_off = static_cast<int32_t>(lds - split_lds_tail_bytes(pl.NW, D));
   sp.row_blocks = pl.NB;
   if (lds > 160 * 1024) return VEGAS_ERR_UNSUPPORTED;
@@ -383,6 +395,10 @@ void fill_split_params(const vegas_desc* d, const SplitPlan& pl, int G, const vo
   sp->batch = d->batch;
   sp->slots_target = pl.J;
   sp->slots_target2 = pl.J2;
+  sp->share_wgs = pl.JR;
+  // Workgroups go round the 8 XCDs, on each round its 4 shader engines: every 32nd starts on the same engine.
+  sp->share_group = 32;
+  for (int step = d->num_kv_heads * pl.NB; step % 2 == 0 && sp->share_group > 1; step /= 2) sp->share_group /= 2;
   sp->chunk_cap_units = pl.cap_units;
   sp->slots_total = pl.JS;
   sp->chunk_unit = kTile * pl.NW;

@@ -51,6 +51,18 @@ __device__ __forceinline__ float wave_sum(float x) { return wave_reduce(x, [](fl
 __device__ __forceinline__ uint32_t wave_max(uint32_t x) { return wave_reduce(x, [](uint32_t a, uint32_t b) { return a > b ? a : b; }); }
 __device__ __forceinline__ uint32_t wave_sum(uint32_t x) { return wave_reduce(x, [](uint32_t a, uint32_t b) { return a + b; }); }
 
+// Inclusive prefix sum over the 64 lanes of a wave with DPP row shifts and row broadcasts (no LDS).
+__device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
+  int v = static_cast<int>(x);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return static_cast<uint32_t>(v);
+}
+
 // Orders LDS traffic between the lanes of ONE wave (a wave's LDS instructions execute in order,
 // so only the compiler has to be kept from moving accesses across this point).
 __device__ __forceinline__ void wave_lds_fence() {
@@ -130,8 +142,10 @@ struct SplitParams {
   int2* plan;               // balanced chunking (or nullptr): [B] (first partial slot, chunk tokens) per sequence,
                             // computed by every workgroup from the lengths and written here by workgroup 0
   int32_t batch;            // B (balanced chunking)
-  int32_t slots_target;     // j1: workgroups per KV head (and row block) of one launch wave
+  int32_t slots_target;     // workgroups per KV head (and row block) of one launch wave
   int32_t slots_target2;    // j2: of two waves (= j1 where only one plan is wanted)
+  int32_t share_wgs;        // workgroups per KV head (and row block) that run at a time
+  int32_t share_group;      // so many consecutive workgroups of a head start on as many shader engines (a power of two)
   int32_t chunk_cap_units;  // longest chunk the plan may produce, in units
   int32_t slots_total;      // slots per KV head the workspace holds
   int32_t chunk_unit;       // chunk lengths are multiples of this many tokens
@@ -260,6 +274,7 @@ __device__ __forceinline__ int first_live_chunk(int n, int G, int window, int ch
 struct ColumnSlots {
   int64_t off;
   int32_t stride_h, chunk, last;
+  int32_t count;               // chunks the column has, where they are not equal (0: they follow from `chunk`)
 };
 __host__ __device__ __forceinline__ ColumnSlots column_slots(const int2* plan, int slots_total, int b, int Hkv, int nsplit,
                                                     int chunk_tokens) {
@@ -270,11 +285,13 @@ __host__ __device__ __forceinline__ ColumnSlots column_slots(const int2* plan, i
     c.stride_h = slots_total;
     c.chunk = e.y > 0 ? e.y : 1;
     c.last = slots_total - 1 - e.x;
+    c.count = e.y < 0 ? -e.y : 0;
   } else {
     c.off = static_cast<int64_t>(b) * Hkv * nsplit;
     c.stride_h = nsplit;
     c.chunk = chunk_tokens;
     c.last = nsplit - 1;
+    c.count = 0;
   }
   return c;
 }
@@ -286,7 +303,7 @@ struct ColumnChunks {
 };
 __host__ __device__ __forceinline__ ColumnChunks column_chunks(const ColumnSlots& cs, int n) {
   ColumnChunks c;
-  c.ns = (n + cs.chunk - 1) / cs.chunk;
+  c.ns = cs.count > 0 ? (n > 0 ? cs.count : 0) : (n + cs.chunk - 1) / cs.chunk;
   c.last = cs.last < c.ns - 1 ? cs.last : c.ns - 1;
   return c;
 }
@@ -297,18 +314,32 @@ __host__ __device__ __forceinline__ uint32_t requested_slot(int s, int last) {
 }
 
 // Balanced chunking of a batch (B <= 64 sequences, lengths < 2^24), computed identically by every wave that
-// calls it, from the lengths alone (the host does not know them).  J workgroups per KV head are given to the
-// sequences so that the longest chunk is as short as possible: with C the smallest chunk length for which
-// sum_b ceil(n_b / C) <= J, sequence b is cut into s_b = ceil(n_b / C) equal chunks (multiples of `unit` tokens).
-// J is j1 (one launch wave of workgroups) unless the lengths are so ragged that the chunks of that plan would
-// leave more than a tenth of the wave idle; then it is j2 (two waves of half-size chunks, handed out longest
-// first, which evens the waves out: wants_second_wave).  No chunk is longer than cap_units * unit tokens (what a workgroup can park
-// in LDS); a batch too long for J chunks of that size simply takes more slots.  Slot ranges [P_b, P_b + s_b)
-// are laid out by descending chunk length, so workgroups start in that order; slot j maps to chunk j - P_b of
-// the sequence whose range holds it.
+// calls it, from the lengths alone (the host does not know them).  Two plans:
+//   * Equal chunks.  J workgroups per KV head are given to the sequences so that the longest chunk is as short as possible:
+//     with C the smallest chunk length for which sum_b ceil(n_b / C) <= J, sequence b is cut into s_b = ceil(n_b / C) equal
+//     chunks (multiples of `unit` tokens).  J is j1 (one launch wave) or j2 (two waves of half-size chunks, handed out longest
+//     first; wants_second_wave).  Partial slot j = workgroup j, laid out by descending chunk length.
+//   * Shares.  Where the longest equal chunk is well above the mean (wants_shares), the sequences are laid end to end and cut
+//     every S units, S = 1/J of the whole, whatever sequence that falls into.  A share that holds an end of a sequence is as
+//     many pieces, each a workgroup of its own: whole shares start first, then the others by descending length, so that the
+//     pieces of one share meet on a compute unit again (the shortest first piece ends first and is followed by the longest
+//     second one).  A sequence's partial slots are consecutive: cuts before it + sequences before it, one per piece.
+//     The hardware deals workgroups to the shader engines in turn, and none starts before its predecessor has: while every unit
+//     is taken, workgroup J + i waits for a unit of the engine on which J - share_group + i started.  So the first J are
+//     reversed in groups of share_group: of the last such group the shortest piece sits where the next workgroup, the longest
+//     of the second pieces, will wait, and so on.  Verification with collection, 20 rows, us, two waves of equal chunks /
+//     shares without / with the reversal: 8 sequences of 16384..131072 tokens 439 / 465 / 413; 16 of 8192..65536 424 / 444 / 407;
+//     16 of 4000..16000 132 / 123 / 117; 24 of 1001..20011 205 / 197 / 194.  40 rows: 16 of 8192..65536 449 / 477 / 431.
+// No chunk is longer than cap_units * unit tokens (what a workgroup can park in LDS); a batch too long for J chunks of that
+// size simply takes more slots.
 struct BalancedSlot {
-  int32_t b, split, chunk;      // b < 0: slot j is not used
+  int32_t b;                    // sequence; < 0: workgroup j has nothing to do
+  int32_t c0, chunk;            // its first token here, and how many follow (as far as the sequence reaches)
+  int32_t slot;                 // partial slot of the KV head
 };
+// Units of streaming that beginning one more piece costs a compute unit: 0, 1, 2, 3 of them, verification with collection, us:
+// 16 sequences of 4000..16000 tokens, 20 rows 132 / 124 / 131 / 123; 8 of 1001..20011 75.4 / 81.5 / 70.6 / 70.3.
+constexpr uint32_t kShareCost = 3;
 // ceil(x / d) for 0 <= x < 2^23, 1 <= d < 2^23 (a float reciprocal and one correction step instead of an integer division)
 __device__ __forceinline__ uint32_t ceil_div_small(uint32_t x, uint32_t d) {
   uint32_t q = static_cast<uint32_t>(static_cast<float>(x) * __builtin_amdgcn_rcpf(static_cast<float>(d)));
@@ -335,16 +366,30 @@ __device__ __forceinline__ uint32_t balanced_chunk_units(uint32_t nu, uint32_t t
   }
   return lo;
 }
-// C: chunk length of the one-wave plan, total / j1 its lower bound (all in units).  second_cost: units of streaming that a
-// second wave costs where its workgroups cannot start beside the first's (64-row workgroups fill a compute unit's LDS).
-// Verification with collection there, us, one wave / two, by C / bound: 8 sequences of 500..2000 tokens, 40 rows, 3 / 2.6:
-// 25.6 / 35.6; 12 of 2000..20000, 49 rows, 19 / 16.7: 80.2 / 92.0; 32 of 300..1500, 40 rows, 12 / 7.6: 52.9 / 60.8; 16 of
-// 4000..16000, 54 / 40: 153.5 / 150.4; 24 of 1000..8000, 44 / 27: 126.0 / 117.9; 12 of 2000..20000, 80 rows, 103 / 67: 244 / 197.
+// Would chunks of C units, the longest of a plan for j1 workgroups, leave more than a tenth of them idle after giving up
+// second_cost units, what the alternative costs?  total / j1 is the lower bound of any plan.  second_cost is high where its workgroups cannot start beside the first's (64-row workgroups fill a
+// compute unit's LDS).  There, us, one wave / two, by C / bound: 8 sequences of 500..2000 tokens, 40 rows, 3 / 2.6: 25.6 / 35.6;
+// 12 of 2000..20000, 49 rows, 19 / 16.7: 80.2 / 92.0; 32 of 300..1500, 40 rows, 12 / 7.6: 52.9 / 60.8; 24 of 1000..8000,
+// 44 / 27: 126.0 / 117.9; 12 of 2000..20000, 80 rows, 103 / 67: 244 / 197.
 __host__ __device__ __forceinline__ bool wants_second_wave(uint32_t total, uint32_t j1, uint32_t C, uint32_t second_cost) {
   return C > second_cost && 10u * total < 9u * j1 * (C - second_cost);
 }
-__device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B, int max_tokens, int j1, int j2,
-                                                      int second_cost, int cap_units, int unit, int j, int2* plan_out) {
+// Is a batch cut into shares?  priced: units of all sequences plus kShareCost for every one but the first, lives: sequences, J
+// workgroups, C: longest equal chunk.  us, equal chunks / shares, verification with collection, by C / (priced / J): 20 rows:
+// 8 of 1001..20011 tokens, 25 / 22.4: 71.4 / 68.5; 16 of 4000..16000, 54 / 41: 131 / 117; 32 of 300..1500, 12 / 10.5: 38.5 /
+// 39.3; without collection 34.2 / 39.4; 4 of 4096..32768, 21 / 19.6: 63.5 / 71.5.  40 rows: 12 of 2000..20000, 41 / 34.3: 120.7 /
+// 114.6; 24 of 5000, 40 / 32.2: 107 / 110, at head dimension 64 78.6 / 74.2; 35 rows, 4 heads (J = 64): 48 of 300..3000,
+// 17 / 12.2: 64.8 / 59.8; 32 of 2000..8000, 27 / 21.5: 95.6 / 91.2.  margin: units that have to be won at least, 2 (2 of
+// 3000..30000, 40 rows, head dimension 64, 4 / 3.6, no collection: 21 / 24.8), 4 with 64-row workgroups, which take longer to
+// begin and to end (7 of 15501, 48 rows and token sums, 31 / 27.3: 215.9 / 218.9 for the iteration).
+__host__ __device__ __forceinline__ bool wants_shares(uint32_t priced, uint32_t lives, uint32_t J, uint32_t C, uint32_t margin) {
+  return lives <= J && 10u * J * C > 11u * priced + 8u * lives && C >= (priced + J - 1u) / J + margin;
+}
+// share_wgs: workgroups per KV head that run at a time (J of the shares); share_margin: for wants_shares; second_cost: for
+// wants_second_wave.
+__device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B, int max_tokens, int j1, int j2, int share_wgs,
+                                                      int share_group, int share_margin, int second_cost, int cap_units, int unit,
+                                                      int j, int2* plan_out) {
   const int lane = threadIdx.x & 63;
   uint32_t n = 0u;
   if (lane < B) {
@@ -353,14 +398,53 @@ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B
   }
   const uint32_t nu = (n + unit - 1u) / unit;                   // length in units
   const uint32_t total = wave_sum(nu);
-  BalancedSlot r;
-  r.b = -1; r.split = 0; r.chunk = unit;
+  BalancedSlot r = {-1, 0, unit, 0};
   if (total == 0u) {
     if (plan_out && lane < B) plan_out[lane] = make_int2(0, unit);
     return r;
   }
   const uint32_t longest = wave_max(nu);
-  uint32_t C = balanced_chunk_units(nu, total, longest, static_cast<uint32_t>(j1));
+  const uint64_t live = __builtin_amdgcn_ballot_w64(nu > 0u);
+  const uint32_t J = share_wgs, lives = __popcll(live);
+  uint32_t C = balanced_chunk_units(nu, total, longest, J);
+  const uint32_t priced = total + kShareCost * (lives - 1u), S = (priced + J - 1u) / J;
+  if (S <= static_cast<uint32_t>(cap_units) && wants_shares(priced, lives, J, C, static_cast<uint32_t>(share_margin))) {
+    const uint32_t rank = __popcll(live & ((1ull << lane) - 1ull));
+    const uint32_t base = wave_prefix_sum(nu) - nu + kShareCost * rank;       // where the sequence's first token lies
+    const uint32_t q = base / S, count = nu > 0u ? (base + nu - 1u) / S - q + 1u : 0u;
+    if (plan_out && lane < B) plan_out[lane] = nu > 0u ? make_int2(q + rank, -static_cast<int>(count)) : make_int2(0, unit);
+    const uint32_t head = min(nu, (q + 1u) * S - base);                       // first piece (0 if empty); last one, where there
+    const uint32_t tail = count > 1u ? nu - head - (count - 2u) * S : 0u;     // are several; whole shares between them
+    const uint32_t mid = count > 2u ? count - 2u : 0u;
+    const uint32_t before = wave_prefix_sum(mid) - mid;
+    const uint32_t mids = __builtin_amdgcn_readlane(before + mid, 63);
+    const uint32_t at = static_cast<uint32_t>(j) < (J & -static_cast<uint32_t>(share_group)) ? j ^ (share_group - 1) : j;
+    uint64_t hit;
+    uint32_t piece;
+    if (at < mids) {
+      hit = __builtin_amdgcn_ballot_w64(at >= before && at - before < mid);
+      piece = at - __builtin_amdgcn_readlane(before, __builtin_ctzll(hit)) + 1u;
+    } else {                                                    // the others, longest first
+      uint32_t at_head = mids, at_tail = mids;
+      for (int i = 0; i < B; ++i) {
+        const uint32_t hi = __builtin_amdgcn_readlane(head, i), ti = __builtin_amdgcn_readlane(tail, i);
+        at_head += (hi > head || (hi == head && i < lane) ? 1u : 0u) + (ti > head ? 1u : 0u);
+        at_tail += (hi >= tail ? 1u : 0u) + (ti > tail || (ti == tail && i < lane) ? 1u : 0u);
+      }
+      const uint64_t heads = __builtin_amdgcn_ballot_w64(head > 0u && at_head == at);
+      const uint64_t tails = __builtin_amdgcn_ballot_w64(tail > 0u && at_tail == at);
+      hit = heads | tails;
+      if (hit == 0ull) return r;
+      piece = heads ? 0u : __builtin_amdgcn_readlane(count, __builtin_ctzll(hit)) - 1u;
+    }
+    r.b = __builtin_ctzll(hit);
+    const uint32_t first = __builtin_amdgcn_readlane(head, r.b);
+    r.c0 = piece == 0u ? 0 : static_cast<int>((first + (piece - 1u) * S) * unit);
+    r.chunk = static_cast<int>((piece == 0u ? first : S) * unit);
+    r.slot = __builtin_amdgcn_readlane(q + rank, r.b) + piece;
+    return r;
+  }
+  if (static_cast<uint32_t>(j1) != J) C = balanced_chunk_units(nu, total, longest, static_cast<uint32_t>(j1));
   if (j2 > j1 && wants_second_wave(total, static_cast<uint32_t>(j1), C, static_cast<uint32_t>(second_cost)))
     C = balanced_chunk_units(nu, total, longest, static_cast<uint32_t>(j2));
   C = min(C, static_cast<uint32_t>(cap_units));
@@ -375,10 +459,10 @@ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B
   if (plan_out && lane < B) plan_out[lane] = make_int2(P, chunk > 0 ? chunk : unit);
   const uint64_t hit = __builtin_amdgcn_ballot_w64(lane < B && s > 0u && j >= P && j < P + static_cast<int>(s));
   if (hit == 0ull) return r;
-  const int b = __builtin_ctzll(hit);
-  r.b = b;
-  r.split = j - __builtin_amdgcn_readlane(P, b);
-  r.chunk = __builtin_amdgcn_readlane(chunk, b);
+  r.b = __builtin_ctzll(hit);
+  r.chunk = __builtin_amdgcn_readlane(chunk, r.b);
+  r.c0 = (j - __builtin_amdgcn_readlane(P, r.b)) * r.chunk;
+  r.slot = j;
   return r;
 }
 

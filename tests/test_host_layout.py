@@ -238,3 +238,25 @@ def test_wide_rows_as_siblings_where_that_is_faster(tmp_path):
                 ((1, 8, 4096, 31, 1, 1, 128), 1), ((1, 8, 4096, 30, 1, 1, 128), 0)]
     out = run_host_program(tmp_path, SIBLINGS, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
     assert [int(x) for x in out] == [s for _, s in measured]
+
+
+SHARES = r'''
+#include <cstdio>
+#include "vegas_common.hpp"
+int main() {                       // lines of: units of all sequences with what further pieces cost, sequences, workgroups, longest equal chunk, margin
+  unsigned priced, lives, J, C, margin;
+  while (std::scanf("%u %u %u %u %u", &priced, &lives, &J, &C, &margin) == 5)
+    std::printf("%d\n", vegas::wants_shares(priced, lives, J, C, margin) ? 1 : 0);
+}
+'''
+
+
+def test_batches_are_cut_into_shares_where_that_is_faster(tmp_path):
+    """(units of all sequences + 3 for every one but the first, sequences, workgroups, longest equal chunk, margin: 2, or 4 of
+    64-row workgroups): shares measured faster, or not; never with more sequences than workgroups."""
+    measured = [((718, 8, 32, 25, 2), 1), ((1312, 16, 32, 54, 2), 1), ((1099, 12, 32, 41, 4), 1), ((2110, 24, 32, 105, 4), 1),
+                ((781, 48, 64, 17, 4), 1), ((1375, 32, 64, 27, 4), 1), ((336, 32, 32, 12, 2), 0), ((627, 4, 32, 21, 2), 0),
+                ((145, 16, 32, 4, 2), 0), ((105, 8, 32, 3, 2), 0), ((230, 2, 64, 4, 4), 0), ((872, 7, 32, 31, 4), 0),
+                ((778, 48, 32, 23, 2), 0), ((778, 48, 32, 500, 2), 0)]
+    out = run_host_program(tmp_path, SHARES, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
+    assert [int(x) for x in out] == [s for _, s in measured]
