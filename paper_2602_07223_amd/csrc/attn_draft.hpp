@@ -51,7 +51,12 @@ inline size_t draft16_lds_bytes(int R, int D) {
 // Sec. 4 / App. D).  With small pages a tile spans 32 >> PS pages: their ids are loaded one tile ahead into one
 // register (lane e <-> page e of the tile), every lane fetches the id of each of its tokens with a lane permute and
 // forms a 64-bit address of its own; everything after the loads is the 16-token code.
-template <int D, int PS = 4>
+// STREAM: K and V are read with the non-temporal hint, K in whole 128-byte lines (half lines would fetch each of them twice
+// then).  For selections that the last-level cache cannot hold until the next draft step reads them again
+// (streamed_selection): 16 x 8192 tokens, one-token pages 106.7 -> 95.0 us (5.7 TB/s), 16-token pages 102.9 -> 92.4;
+// 32 x 3000, two-token pages 74.1 -> 68.1.  A plain read of the same addresses takes 96 us without the hint and 86 with it: what
+// bounds the kernel then is HBM.  Whole lines alone change nothing.
+template <int D, int PS = 4, bool STREAM = false>
 __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS_SPLIT_HOT_PARAMS, const SplitParams pfull) {
   VEGAS_TL_DECL;
   VEGAS_TL(kTlEntry);
@@ -142,7 +147,10 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
 
   const int64_t head_off = static_cast<int64_t>(h) * p.head_stride;
   const uint32_t ts_bytes = static_cast<uint32_t>(p.token_stride) * 2u;
-  const uint32_t k_lane_off = static_cast<uint32_t>(l16) * ts_bytes + static_cast<uint32_t>(kg) * 16u;
+  // K: token and byte of its row this lane fetches with load (pg, kk) before the lane exchange (see exchange_k)
+  const int k_tok = STREAM ? l16 & 7 : l16;
+  const uint32_t k_byte = static_cast<uint32_t>(kg) * 16u + (STREAM ? static_cast<uint32_t>(l16 >> 3) * 64u : 0u);
+  const uint32_t k_lane_off = static_cast<uint32_t>(k_tok) * ts_bytes + k_byte;
   const uint32_t v_lane_off = static_cast<uint32_t>(4 * kg) * ts_bytes + static_cast<uint32_t>(l16) * (2u * NBLK);
   auto page_base = [&](const uint16_t* cache, int ph) -> const unsigned char* {
     return uniform_ptr(reinterpret_cast<const unsigned char*>(cache + static_cast<int64_t>(ph) * p.page_stride + head_off));
@@ -158,12 +166,20 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   // K load (pg, kk): token l16 of page pg, head dims 32 kk + 8 kg .. + 7
   auto issue_k = [&](int k, u32x4 (&kr)[2][KK]) {
     if constexpr (PS != 4) {
-      typedef const __attribute__((address_space(1))) u32x4* gp;
 #pragma unroll
       for (int pg = 0; pg < 2; ++pg) {
-        const gbytes row = token_addr(p.k, 16 * pg + l16) + kg * 16;
+        if constexpr (STREAM) {
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) kr[pg][kk] = *(gp)(row + kk * 64);
+          for (int e = 0; e < 2; ++e) {
+            const gbytes row = token_addr(p.k, 16 * pg + 8 * e + k_tok) + k_byte;
+#pragma unroll
+            for (int kk = e; kk < KK; kk += 2) kr[pg][kk] = gload_at<u32x4, STREAM>(row + (kk >> 1) * 128);
+          }
+        } else {
+          const gbytes row = token_addr(p.k, 16 * pg + l16) + kg * 16;
+#pragma unroll
+          for (int kk = 0; kk < KK; ++kk) kr[pg][kk] = gload_at<u32x4, STREAM>(row + kk * 64);
+        }
       }
       return;
     }
@@ -173,21 +189,37 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
 #pragma unroll
     for (int pg = 0; pg < 2; ++pg)
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) kr[pg][kk] = gload<u32x4, false>((pg ? kb1 : kb0) + kk * 64, k_lane_off);
+      for (int kk = 0; kk < KK; ++kk)
+        kr[pg][kk] = gload<u32x4, STREAM>((pg ? kb1 : kb0) + (STREAM ? (kk >> 1) * 128u + (kk & 1) * 8u * ts_bytes : kk * 64u), k_lane_off);
   };
   // V load e: token 4 kg + e % 4 of page e / 4, head dims NBLK l16 .. + NBLK - 1
   auto issue_v = [&](int k, VReg (&vr)[8]) {
     if constexpr (PS != 4) {
-      typedef const __attribute__((address_space(1))) VReg* gp;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) vr[e] = *(gp)(token_addr(p.v, 16 * (e >> 2) + 4 * kg + (e & 3)) + l16 * (2 * NBLK));
+      for (int e = 0; e < 8; ++e) vr[e] = gload_at<VReg, STREAM>(token_addr(p.v, 16 * (e >> 2) + 4 * kg + (e & 3)) + l16 * (2 * NBLK));
       return;
     }
     const unsigned char* vb0 = page_base(p.v, __builtin_amdgcn_readlane(pagevec, k & 31));
     const unsigned char* vb1 = page_base(p.v, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31)));
 #pragma unroll
     for (int e = 0; e < 8; ++e)
-      vr[e] = gload<VReg, false>((e < 4 ? vb0 : vb1) + static_cast<uint32_t>(e & 3) * ts_bytes, v_lane_off);
+      vr[e] = gload<VReg, STREAM>((e < 4 ? vb0 : vb1) + static_cast<uint32_t>(e & 3) * ts_bytes, v_lane_off);
+  };
+
+  // Loads of whole 128-byte lines bring two tokens' pieces to the wrong lanes: of loads 2 q and 2 q + 1 the first holds, in
+  // lanes l16 < 8, the first half of line q of token l16 and, in the others, the second half of token l16 - 8's; the second
+  // load the same of tokens l16 + 8 and l16.  Lanes 8 apart exchange them.
+  auto exchange_k = [&](u32x4 (&kr)[2][KK]) {
+#pragma unroll
+    for (int pg = 0; pg < 2; ++pg)
+#pragma unroll
+      for (int q = 0; q < KK / 2; ++q)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const int a = static_cast<int>(kr[pg][2 * q][w]), b = static_cast<int>(kr[pg][2 * q + 1][w]);
+          kr[pg][2 * q][w] = static_cast<unsigned>(__builtin_amdgcn_update_dpp(a, b, 0x128, 0xf, 0xc, false));       // row_ror:8
+          kr[pg][2 * q + 1][w] = static_cast<unsigned>(__builtin_amdgcn_update_dpp(b, a, 0x128, 0xf, 0x3, false));
+        }
   };
 
   u32x4 kr[2][KK];
@@ -210,6 +242,7 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   auto step = [&](int k, VReg (&vcur)[8], VReg (&vnxt)[8], auto has_next_tag) {
     constexpr bool has_next = decltype(has_next_tag)::value;
     const int tok0 = (tile_first + k * NW) * kTile;
+    if constexpr (STREAM) exchange_k(kr);
     f32x4 st[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};     // st[pg][r]: token 4 kg + r of page pg, row l16
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk)

@@ -330,12 +330,18 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
     if (pl.R <= kDraftRows && sp.G == 1 && pl.NB == 1) {
       const dim3 dblock(kDraftWaves * 64);
       const size_t dlds = draft16_lds_bytes(pl.R, D);
+      const bool stream = streamed_selection(batch, sp.Hkv, sp.max_tokens, D);
+      auto launch = [&](auto ps) {
+        constexpr int PS = decltype(ps)::value;
+        if (stream) return launch_one(attn_draft16_kernel<D, PS, true>, grid, dblock, dlds, st, sp);
+        return launch_one(attn_draft16_kernel<D, PS, false>, grid, dblock, dlds, st, sp);
+      };
       switch (page_size) {                              // (draft calls may walk a table of smaller pages)
-        case 1: return launch_one(attn_draft16_kernel<D, 0>, grid, dblock, dlds, st, sp);
-        case 2: return launch_one(attn_draft16_kernel<D, 1>, grid, dblock, dlds, st, sp);
-        case 4: return launch_one(attn_draft16_kernel<D, 2>, grid, dblock, dlds, st, sp);
-        case 8: return launch_one(attn_draft16_kernel<D, 3>, grid, dblock, dlds, st, sp);
-        default: return launch_one(attn_draft16_kernel<D, 4>, grid, dblock, dlds, st, sp);
+        case 1: return launch(std::integral_constant<int, 0>{});
+        case 2: return launch(std::integral_constant<int, 1>{});
+        case 4: return launch(std::integral_constant<int, 2>{});
+        case 8: return launch(std::integral_constant<int, 3>{});
+        default: return launch(std::integral_constant<int, 4>{});
       }
     }
     switch (page_size) {                                // larger groups: the 32-row kernel, any page size
@@ -515,11 +521,11 @@ int for_each_lds_kernel(F f) {
     one(attn_split_kernel<4, 2, true, 1, false, 4, false, D>);
     one(attn_split_kernel<4, 2, true, 2, false, 4, false, D>);
     one(attn_split_kernel<4, 2, true, 2, true, 4, false, D>);
-    one(attn_draft16_kernel<D, 0>);
-    one(attn_draft16_kernel<D, 1>);
-    one(attn_draft16_kernel<D, 2>);
-    one(attn_draft16_kernel<D, 3>);
-    one(attn_draft16_kernel<D, 4>);
+    one(attn_draft16_kernel<D, 0, false>); one(attn_draft16_kernel<D, 0, true>);
+    one(attn_draft16_kernel<D, 1, false>); one(attn_draft16_kernel<D, 1, true>);
+    one(attn_draft16_kernel<D, 2, false>); one(attn_draft16_kernel<D, 2, true>);
+    one(attn_draft16_kernel<D, 3, false>); one(attn_draft16_kernel<D, 3, true>);
+    one(attn_draft16_kernel<D, 4, false>); one(attn_draft16_kernel<D, 4, true>);
     one(attn_pair_kernel<0, D, true>); one(attn_pair_kernel<0, D, false>);
     one(attn_pair_kernel<1, D, true>); one(attn_pair_kernel<1, D, false>);
     one(attn_pair_kernel<2, D, true>); one(attn_pair_kernel<2, D, false>);

@@ -106,6 +106,14 @@ __device__ __forceinline__ T gload(const unsigned char* sbase, uint32_t voff) {
   else return *ptr;
 }
 
+// The same from a per-lane address.
+template <typename T, bool STREAMING>
+__device__ __forceinline__ T gload_at(const __attribute__((address_space(1))) unsigned char* at) {
+  typedef const __attribute__((address_space(1))) T* gp;
+  if constexpr (STREAMING) return __builtin_nontemporal_load((gp)at);
+  else return *(gp)at;
+}
+
 // Write-through store of 16 bytes (4-byte aligned) to base + off.
 __device__ __forceinline__ void store_through(unsigned char* base, uint32_t off, f32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, %2 sc0 sc1\n\ts_nop 1" :: "v"(off), "v"(v), "s"(base) : "memory");
