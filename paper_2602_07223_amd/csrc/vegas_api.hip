@@ -139,12 +139,15 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
     int64_t c = (max_len + splits - 1) / splits;
     {
       // Round to whole units: up, unless a bound a little above a multiple (a selection table with two pages of
-      // slack) would then double every wave's tiles -- a quarter more workgroups than planned is the better price where
-      // two of them fit a compute unit.  (64-row workgroups fill its LDS: 288 of them, 80 rows, 32749 tokens, took two
-      // rounds of the chip.)
+      // slack) would then double every wave's tiles -- a few more workgroups than planned, of a tile per wave at most in
+      // all, are the better price where two of them fit a compute unit.  (More than that are a second round of the chip:
+      // one sequence, verification with collection, up to a quarter more workgroups / rounded up: 17000 tokens 26.1 / 20.8 us,
+      // 45000 51.3 / 38.2, 100000 92.8 / 73.5, with 4 KV heads 61.8 / 44.1; draft calls, 16 x 4352 tokens 61.2 / 51.0, 1 x 8704
+      // 17.5 / 12.4.  64-row workgroups fill a compute unit's LDS: 288 of them, 80 rows, 32749 tokens, took two rounds.)
       const int64_t up = (c + unit - 1) / unit * unit, down = c / unit * unit;
       c = up;
-      if (!pl->pair && down >= unit && ((max_len + down - 1) / down) * columns * 4 <= static_cast<int64_t>(num_cu) * wg_per_cu * 5) c = down;
+      if (!pl->pair && down >= unit && max_len - splits * down < unit &&
+          ((max_len + down - 1) / down) * columns * 4 <= static_cast<int64_t>(num_cu) * wg_per_cu * 5) c = down;
     }
     // What a workgroup collects is parked in LDS until its chunk ends, so a chunk cannot be arbitrarily long.  A
     // chunk that gives every CU exactly one workgroup is taken as it is while its LDS fits (batch 4 x 64K tokens:

@@ -186,6 +186,13 @@ def test_one_long_sequence_takes_one_round_of_64_row_workgroups(n, rows):
     assert chunk_slots(1, rows, 8, n) * blocks <= 256
 
 
+@pytest.mark.parametrize("n,chunks", [(9000, 24), (16384, 32), (16385, 33), (16511, 33), (16512, 26), (17000, 27), (45000, 32), (100000, 32)])
+def test_one_sequence_of_any_length_takes_one_round(n, chunks):
+    """24 rows, 8 KV heads: 32 chunks per head are one workgroup per compute unit; more only where all that lies beyond 32
+    of them is less than a unit of 128 tokens."""
+    assert chunk_slots(1, 24, 8, n) == 8 * chunks
+
+
 WAVES = r'''
 #include <cstdio>
 #include "attn_pair.hpp"
