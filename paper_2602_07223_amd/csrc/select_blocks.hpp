@@ -25,16 +25,131 @@ __device__ __forceinline__ uint32_t score_key(float s) {
   return (s != s) ? 0u : key;
 }
 
+// ---- selection among keys that the threads of a workgroup hold in registers ----
+struct RegisterSelectShared {
+  uint32_t hist[3][2048];                       // digit counts of the up to three passes
+  uint32_t low[kSelectThreads / 64], high[kSelectThreads / 64];
+  uint32_t bin, need, count;
+};
+// Taken are the keys above base + span and the first `need`, by position, of those in [base, base + span].
+struct LastKey {
+  uint32_t base, span, need;
+};
+
+// Radix select: where the `take` largest of the workgroup's keys end.  Keys below `full` of every thread hold positions, of
+// those from there to `live` valid(u) says which; a key without a position is 0 and its place lies behind all positions.  0 <
+// take < positions.  Followed by no barrier; the first thing it does is not ordered behind reads of `sh` either.
+// A digit is 11 bits of key - smallest key, from the highest bit in which the keys differ: what the scores have in common
+// (sign, most of the exponent) costs no pass, the counts spread over the bins so that one shared histogram and plain adds
+// do, and two passes as a rule, three at most, find the end.  (With four passes over 8 fixed bits, a histogram per wave and
+// one add for the lanes that share a digit, an iteration took, us: 2048 pages 70.2 instead of 69.7, 4096 pages of each of 16
+// sequences 590.6 instead of 587.6, 8192 pages 161.0 instead of 158.0.)  What bounds it is latency, a barrier and one wave's walk through the counts per pass, and
+// with 16 and more keys a thread the instructions issued per key.
+template <int N, typename Valid>
+__device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int full, int live, Valid valid, uint32_t take,
+                                                 RegisterSelectShared& sh) {
+  constexpr int kWaves = kSelectThreads / 64;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int i = tid; i < 3 * 2048 / 4; i += kSelectThreads) reinterpret_cast<u32x4*>(sh.hist)[i] = u32x4{0u, 0u, 0u, 0u};
+  uint32_t hi = 0u, inv_lo = 0u;                                    // (the smallest as the largest complement)
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    if (u >= live) continue;
+    hi = max(hi, key[u]);
+    if (u < full || valid(u)) inv_lo = max(inv_lo, ~key[u]);
+  }
+  hi = wave_max(hi);
+  inv_lo = wave_max(inv_lo);
+  if (lane == 0) {
+    sh.high[wave] = hi;
+    sh.low[wave] = inv_lo;
+  }
+  __syncthreads();
+  hi = __builtin_amdgcn_readfirstlane(wave_max(sh.high[lane & (kWaves - 1)]));
+  LastKey r;
+  r.base = ~__builtin_amdgcn_readfirstlane(wave_max(sh.low[lane & (kWaves - 1)]));
+  r.span = hi - r.base;
+  r.need = take;
+  // (Keys without a position lie outside every range unless it starts at 0, the key of NaNs, and are the last there: a bin is
+  //  then never taken whole, and of equal keys the first positions are.)
+  int shift = max(32 - __builtin_clz(r.span | 1u) - 11, 0);
+#pragma unroll
+  for (int pass = 0; pass < 3; ++pass) {
+    uint32_t* const h = sh.hist[pass];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      if (u >= live) continue;
+      const uint32_t d = key[u] - r.base;
+      if ((pass == 0 && u < full) || d <= r.span) atomicAdd(&h[d >> shift], 1u);
+    }
+    __syncthreads();
+    if (wave == 0) {
+      // lane l owns the 32 bins from 32 (63 - l) on, read in an order that spreads the lanes over the banks; then lanes
+      // 0..31 the bins of the lane that holds the wanted key, both from the top bin down
+      const u32x4* g4 = reinterpret_cast<const u32x4*>(h) + 8 * (63 - lane);
+      u32x4 s4 = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int i = 0; i < 8; ++i) s4 += g4[(i + lane) & 7];
+      const uint32_t mine = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+      const uint32_t above = wave_prefix_sum(mine) - mine;
+      const uint64_t who = __builtin_amdgcn_ballot_w64(above < r.need && r.need <= above + mine);   // one lane: 0 < need <= all
+      const int src = who ? __builtin_ctzll(who) : 0;
+      const int top = 32 * (63 - src) + 31;
+      const uint32_t left = r.need - __builtin_amdgcn_readlane(above, src);
+      const uint32_t c = lane < 32 ? h[top - lane] : 0u;
+      const uint32_t over = wave_prefix_sum(c) - c;
+      const uint64_t in = __builtin_amdgcn_ballot_w64(over < left && left <= over + c);
+      const int at = in ? __builtin_ctzll(in) : 0;
+      if (lane == at) {
+        sh.bin = static_cast<uint32_t>(top - at);
+        sh.need = left - over;
+        sh.count = c;
+      }
+    }
+    __syncthreads();
+    r.base += __builtin_amdgcn_readfirstlane(sh.bin) << shift;
+    r.need = __builtin_amdgcn_readfirstlane(sh.need);
+    r.span = (1u << shift) - 1u;
+    if (shift == 0 || __builtin_amdgcn_readfirstlane(sh.count) == r.need) break;   // equal keys, or the whole bin is taken
+    shift = max(shift - 11, 0);
+  }
+  return r;
+}
+
+// ROWS x 16 cells in LDS, row-major, one per (row, wave), each with two 16-bit counts: lane kCellLanes u + wave / kCellsPerLane of
+// the result holds the sum of the cells before cell (u, this wave).  `rows` of them are in use.
+template <int ROWS>
+struct CellWalk {
+  static constexpr int kWaves = kSelectThreads / 64;
+  static constexpr int kPerLane = ROWS * kWaves > 64 ? ROWS * kWaves / 64 : 1;
+  static_assert(kWaves % kPerLane == 0, "a wave's cells sit at one place of their lanes");
+  static __device__ __forceinline__ uint32_t before(const uint32_t* cells, int rows, int wave, int lane) {
+    uint32_t part = 0u, all = 0u;
+#pragma unroll
+    for (int c = 0; c < kPerLane; ++c) {
+      const int cell = kPerLane * lane + c;
+      const uint32_t v = cell < rows * kWaves ? cells[cell] : 0u;
+      if (c < (wave & (kPerLane - 1))) part += v;
+      all += v;
+    }
+    return wave_prefix_sum(all) - all + part;
+  }
+  static __device__ __forceinline__ int lane_of(int u, int wave) { return (kWaves * u + wave) / kPerLane; }
+};
+
 __global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const SelectParams p) {
   extern __shared__ uint32_t skeys[];                 // [min(prefix pages, key_cap)]
-  __shared__ uint32_t hist[kSelectThreads / 64][256];   // one digit histogram per wave: no cross-wave contention
+  __shared__ __align__(16) RegisterSelectShared reg_shared;
+  uint32_t (*hist)[256] = reinterpret_cast<uint32_t (*)[256]>(reg_shared.hist);   // general path: one digit histogram per wave
+  static_assert(sizeof(reg_shared.hist) >= (kSelectThreads / 64) * 256 * sizeof(uint32_t), "a histogram per wave");
   __shared__ uint32_t sh_prefix, sh_need, sh_count;
   __shared__ uint32_t wave_take[kSelectThreads / 64], wave_eq[kSelectThreads / 64];
-  __shared__ uint32_t cell_eq[kSelectRegRows * (kSelectThreads / 64)], cell_gt[kSelectRegRows * (kSelectThreads / 64)];
+  __shared__ uint32_t cells[kSelectRegRows * (kSelectThreads / 64)];
 
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int32_t* sel = p.sel_table + static_cast<int64_t>(b) * p.max_sel_blocks;
   const int32_t* table = p.block_table + static_cast<int64_t>(b) * p.max_blocks;
   const float* scores = p.block_scores + static_cast<int64_t>(b) * p.max_blocks;
@@ -74,149 +189,50 @@ __global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const Sel
     for (int j = tid; j < f0; j += kSelectThreads) sel[j] = table[j];
   }
 
-  // ---- up to 8192 prefix pages: a thread keeps the keys of pages tid, tid + 1024, ... in registers for the digit
-  //      passes and the compaction (no key ever goes through LDS; a wave is bound by the instructions it issues
-  //      here, and this is the shortest stream).  Cell (row u, wave w) covers pages 1024 u + 64 w + lane, so cells
-  //      in (u, w) order are the pages in ascending order.
+  // ---- up to 8192 prefix pages: a thread keeps the keys of pages tid, tid + 1024, ... and their table entries in registers
   auto register_path = [&]() {
     constexpr int kRows = kSelectRegRows;
-    constexpr int kWaves = kSelectThreads / 64;
-    constexpr int kCells = kRows * kWaves / 64;                           // cells per lane in the scan below
     const int rows = (f0 + kSelectThreads - 1) / kSelectThreads;          // 1 .. kRows, uniform
     uint32_t key[kRows];
     int32_t page[kRows];
-    {
-      // (rows past the prefix are skipped by uniform branches: loops stay fully unrolled, arrays in registers)
-      float v[kRows];
-#pragma unroll
-      for (int u = 0; u < kRows; ++u) {
-        v[u] = 0.f;
-        page[u] = 0;
-        if (u < rows) {
-          v[u] = (prefetched && u < kPre) ? pre[u < kPre ? u : 0] : scores[min(u * kSelectThreads + tid, f0 - 1)];
-          page[u] = table[min(u * kSelectThreads + tid, f0 - 1)];         // coalesced, used if the page is taken
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kRows; ++u) key[u] = score_key(v[u]);
-    }
-    // radix select (see the general path below for the early exit)
-    uint32_t prefix = 0u, mask = 0u, need = static_cast<uint32_t>(kc);
-    // Scores cluster: the top byte of nearly all keys is the same, background pages often agree to a percent (two
-    // bytes), tie-heavy scores in every byte -- and per-lane atomics would then collide on one LDS address.  A pass
-    // whose predecessor left at least three quarters of its keys in one bin counts the lanes that share the first
-    // active lane's digit with ONE atomic (the others add themselves); otherwise digits are spread and every lane
-    // adds itself, which is fewer instructions.
-    bool clustered = true;
-    uint32_t active = static_cast<uint32_t>(f0);
-#pragma unroll 1
-    for (int pass = 0; pass < 4; ++pass) {
-      const int shift = 24 - 8 * pass;
-      uint32_t* h = hist[wave];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) h[lane + 64 * i] = 0u;       // wave-private: ordered by the wave's own LDS stream
-#pragma unroll
-      for (int u = 0; u < kRows; ++u) {
-        if (u >= rows) continue;
-        const bool act = u * kSelectThreads + tid < f0 && (key[u] & mask) == prefix;
-        const uint32_t d = (key[u] >> shift) & 255u;
-        if (clustered) {
-          const uint64_t am = __builtin_amdgcn_ballot_w64(act);
-          const int leader = am ? __builtin_ctzll(am) : 0;
-          const uint32_t dl = __builtin_amdgcn_readlane(d, leader);
-          const uint64_t same = __builtin_amdgcn_ballot_w64(act && d == dl);
-          if (lane == leader && am != 0ull) atomicAdd(&h[dl], static_cast<uint32_t>(__popcll(same)));
-          if (act && d != dl) atomicAdd(&h[d], 1u);
-        } else if (act) {
-          atomicAdd(&h[d], 1u);
-        }
-      }
-      __syncthreads();
-      if (wave == 0) {
-        uint32_t c[4] = {0u, 0u, 0u, 0u};                     // lane l owns bins 4l .. 4l+3
-        for (int w = 0; w < kWaves; ++w) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) c[i] += hist[w][4 * lane + i];
-        }
-        const uint32_t mine = c[0] + c[1] + c[2] + c[3];
-        const uint32_t incl = wave_prefix_sum(mine);
-        uint32_t above = __builtin_amdgcn_readlane(incl, 63) - incl;      // keys in the bins above this lane's
-#pragma unroll
-        for (int i = 3; i >= 0; --i) {
-          if (above < need && need <= above + c[i]) {
-            sh_prefix = prefix | (static_cast<uint32_t>(4 * lane + i) << shift);
-            sh_need = need - above;
-            sh_count = c[i];
-          }
-          above += c[i];
-        }
-      }
-      __syncthreads();
-      prefix = sh_prefix;
-      need = sh_need;
-      mask |= 255u << shift;
-      const uint32_t count = sh_count;         // keys in the chosen bin: the next pass's active keys
-      if (count == need) break;                // the whole bin is taken: its lower digits do not matter
-      clustered = 4u * count >= 3u * active;
-      active = count;
-    }
-    const uint32_t T = prefix, need_eq = need, kmask = mask;
-    // compaction: per cell the keys above T and the ties; one wave turns the 128 counts into tie ranks and
-    // output positions; then every thread places its taken pages
-    const uint64_t lt = (1ull << lane) - 1ull;
-    uint64_t beq[kRows], bgt[kRows];
+    // (rows past the prefix are skipped by uniform branches: loops stay fully unrolled, arrays in registers)
+    float v[kRows];
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
-      beq[u] = bgt[u] = 0ull;
-      if (u >= rows) continue;
-      const bool valid = u * kSelectThreads + tid < f0;
-      const uint32_t km = key[u] & kmask;
-      beq[u] = __builtin_amdgcn_ballot_w64(valid && km == T);
-      bgt[u] = __builtin_amdgcn_ballot_w64(valid && km > T);
-      if (lane == 0) {
-        cell_eq[u * kWaves + wave] = static_cast<uint32_t>(__popcll(beq[u]));
-        cell_gt[u * kWaves + wave] = static_cast<uint32_t>(__popcll(bgt[u]));
+      v[u] = 0.f;
+      page[u] = 0;
+      if (u < rows) {
+        v[u] = (prefetched && u < kPre) ? pre[u < kPre ? u : 0] : scores[min(u * kSelectThreads + tid, f0 - 1)];
+        page[u] = table[min(u * kSelectThreads + tid, f0 - 1)];           // coalesced, used if the page is taken
       }
     }
-    __syncthreads();
-    if (wave == 0) {                                          // lane l owns cells kCells l .. kCells l + kCells - 1
-      const int live = rows * kWaves;                         // cells of rows past the prefix were never written
-      uint32_t e[kCells], g[kCells], esum = 0u;
 #pragma unroll
-      for (int c = 0; c < kCells; ++c) {
-        const int cell = kCells * lane + c;
-        e[c] = cell < live ? cell_eq[cell] : 0u;
-        g[c] = cell < live ? cell_gt[cell] : 0u;
-        esum += e[c];
-      }
-      uint32_t eb = wave_prefix_sum(esum) - esum, tsum = 0u;  // ties before the lane's first cell
-      uint32_t t[kCells];
-#pragma unroll
-      for (int c = 0; c < kCells; ++c) {
-        t[c] = g[c] + min(e[c], need_eq > eb ? need_eq - eb : 0u);      // pages the cell takes
-        if (kCells * lane + c < live) cell_eq[kCells * lane + c] = eb;  // ties before the cell
-        eb += e[c];
-        tsum += t[c];
-      }
-      uint32_t pb = wave_prefix_sum(tsum) - tsum;
-#pragma unroll
-      for (int c = 0; c < kCells; ++c) {
-        if (kCells * lane + c < live) cell_gt[kCells * lane + c] = pb;  // output position of the cell
-        pb += t[c];
-      }
-    }
-    __syncthreads();
+    for (int u = 0; u < kRows; ++u) key[u] = tid < f0 - u * kSelectThreads ? score_key(v[u]) : 0u;
+    const LastKey last = find_last_key(key, f0 / kSelectThreads, rows, [&](int u) { return tid < f0 - u * kSelectThreads; },
+                                       static_cast<uint32_t>(kc), reg_shared);
+    // Cell (row u, wave w) covers the 64 pages from 1024 u + 64 w on; it counts its keys above the last bin (low half) and in
+    // it.  A taken page's place: keys above before it + keys in the bin before it, of these at most as many as are taken.
+    const uint32_t top = last.base + last.span;
+    uint32_t packed = 0u;
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
       if (u >= rows) continue;
-      const uint32_t eb = cell_eq[u * kWaves + wave], pb = cell_gt[u * kWaves + wave];
-      const bool eq = (beq[u] >> lane) & 1ull, gt = (bgt[u] >> lane) & 1ull;
-      const bool take = gt || (eq && eb + __popcll(beq[u] & lt) < need_eq);
-      const uint64_t btk = __builtin_amdgcn_ballot_w64(take);
-      if (take) {
-        const uint32_t pos = pb + __popcll(btk & lt);
-        if (pos < static_cast<uint32_t>(p.max_sel_blocks)) sel[pos] = page[u];
-      }
+      const uint32_t gt = __popcll(__builtin_amdgcn_ballot_w64(key[u] > top));
+      const uint32_t eq = __popcll(__builtin_amdgcn_ballot_w64(key[u] - last.base <= last.span));
+      if (lane == u) packed = gt | (eq << 16);
+    }
+    if (lane < rows) cells[lane * (kSelectThreads / 64) + wave] = packed;
+    __syncthreads();
+    const uint32_t before = CellWalk<kRows>::before(cells, rows, wave, lane);
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) {
+      if (u >= rows) continue;
+      const bool gt = key[u] > top, eq = key[u] - last.base <= last.span;
+      const uint64_t bgt = __builtin_amdgcn_ballot_w64(gt), beq = __builtin_amdgcn_ballot_w64(eq);
+      const uint32_t w = __builtin_amdgcn_readlane(before, CellWalk<kRows>::lane_of(u, wave));
+      const uint32_t e = lanes_below(beq, w >> 16);
+      const uint32_t rank = lanes_below(bgt, w & 0xFFFFu) + min(e, last.need);
+      if ((gt || (eq && e < last.need)) && rank < static_cast<uint32_t>(p.max_sel_blocks)) sel[rank] = page[u];
     }
   };
 

@@ -63,6 +63,12 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
   return static_cast<uint32_t>(v);
 }
 
+// base + how many of the lanes below this one are set in mask.
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask, uint32_t base) {
+  return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                   __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), base));
+}
+
 // Orders LDS traffic between the lanes of ONE wave (a wave's LDS instructions execute in order,
 // so only the compiler has to be kept from moving accesses across this point).
 __device__ __forceinline__ void wave_lds_fence() {
