@@ -1,7 +1,7 @@
 // Top-k selection over single tokens (the paper's own granularity: Sec. 3.3 last paragraph, Sec. 4).
 //
 // A sequence has up to a few hundred thousand prefix tokens, too many for one workgroup, so the
-// radix select of the page version is spread over workgroups that own 4096-token slices and meet in
+// radix select of the page version is spread over workgroups (beyond 32768 tokens; up to there token_select_one_kernel) that own 4096-token slices and meet in
 // per-slice digit histograms between launches (plain stores, nothing to clear, no global atomics):
 //   token_select_hist x 4  pass q: every workgroup sums the slices' histograms of passes < q, derives
 //                          the key prefix they fix, counts digit q of its own slice's matching keys
@@ -274,6 +274,101 @@ __global__ __launch_bounds__(kTokThreads) void token_select_write(const TokenSel
     }
     pos_run += __popcll(btk);
   }
+}
+
+// One workgroup per sequence, for prefixes of at most 4096 ROWS tokens, in one launch instead of five: a thread holds the keys
+// of tokens 4096 g + 4 tid .. + 3 in registers, find_last_key finds where the selection ends, and the taken tokens' places come
+// from one prefix sum over a wave per four keys.  The sequence's page ids wait in LDS.
+// Bound by the instructions issued on one compute unit (with one key per lane and row, places by ballots, twice as many: 32768
+// tokens 22.5 us).  us, captured, five launches / one, normally distributed
+// scores: 1 sequence of 4096 tokens 19.2 / 5.1, 8192 19.9 / 6.6, 16384 20.5 / 9.9, 32768 21.0 / 16.7; 16 of 4096 19.9 / 5.4, of
+// 32768 22.4 / 18.5.
+template <int ROWS>
+__global__ __launch_bounds__(kTokThreads) void token_select_one_kernel(const TokenSelectParams p) {
+  static_assert(kTokThreads == kSelectThreads, "find_last_key");
+  constexpr int kWaves = kTokThreads / 64;
+  constexpr int kRowTokens = 4 * kTokThreads;
+  constexpr int kPageTrips = (ROWS * kRowTokens / kPage + kTokThreads - 1) / kTokThreads;
+  __shared__ __align__(16) RegisterSelectShared reg_shared;
+  __shared__ uint32_t cells[ROWS * kWaves];
+  __shared__ int32_t pages[kPageTrips * kTokThreads];
+  typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));     // (scores may start at any float)
+  const int b = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int32_t* table = p.block_table + static_cast<int64_t>(b) * p.max_blocks;
+  const float* scores = p.scores + static_cast<int64_t>(b) * p.max_blocks * kPage;
+  int32_t* sel = p.sel_table + static_cast<int64_t>(b) * p.max_sel;
+  // Scores and page ids are requested before the sequence length is known: clamped to the row, what lies past the prefix is
+  // dropped.
+  const int cap = p.max_blocks * kPage;
+  f32x4_any sc[ROWS];
+#pragma unroll
+  for (int g = 0; g < ROWS; ++g) sc[g] = *reinterpret_cast<const f32x4_any*>(scores + min(kRowTokens * g + 4 * tid, cap - 4));
+  int32_t page[kPageTrips];
+#pragma unroll
+  for (int i = 0; i < kPageTrips; ++i) page[i] = table[min(i * kTokThreads + tid, p.max_blocks - 1)];
+  const TokenPlan t = token_plan(p, b);
+#pragma unroll
+  for (int i = 0; i < kPageTrips; ++i) pages[i * kTokThreads + tid] = page[i];
+  __syncthreads();
+  auto slot_of = [&](int j) -> int32_t { return pages[j >> 4] * kPage + (j & 15); };
+  if (t.need_search) {
+    const int rows = (t.p_len + kRowTokens - 1) / kRowTokens;        // at most ROWS: the host's bound on the lengths says so
+    uint32_t key[4 * ROWS];
+    auto valid = [&](int u) { return kRowTokens * (u >> 2) + 4 * tid + (u & 3) < t.p_len; };
+#pragma unroll
+    for (int u = 0; u < 4 * ROWS; ++u) {
+      key[u] = score_key(sc[u >> 2][u & 3]);
+      if (kRowTokens * ((u >> 2) + 1) > t.p_len && !valid(u)) key[u] = 0u;
+    }
+    const LastKey last = find_last_key(key, t.p_len / kRowTokens * 4, 4 * rows, valid, static_cast<uint32_t>(t.kc), reg_shared);
+    // Counts of keys above the last bin (low half) and in it, of the lower lanes of this wave and of each (row, wave).
+    const uint32_t top = last.base + last.span;
+    uint32_t below[ROWS], total = 0u;
+#pragma unroll
+    for (int g = 0; g < ROWS; ++g) {
+      below[g] = 0u;
+      if (g >= rows) continue;
+      uint32_t gt = 0u, ge = 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        gt += key[4 * g + e] > top ? 1u : 0u;
+        ge += key[4 * g + e] >= last.base ? 1u : 0u;
+      }
+      const uint32_t mine = gt | ((ge - gt) << 16);
+      const uint32_t incl = wave_prefix_sum(mine);
+      below[g] = incl - mine;
+      const uint32_t of_wave = __builtin_amdgcn_readlane(incl, 63);
+      if (lane == g) total = of_wave;
+    }
+    if (lane < rows) cells[lane * kWaves + wave] = total;
+    __syncthreads();
+    const uint32_t before = CellWalk<ROWS>::before(cells, rows, wave, lane);
+#pragma unroll
+    for (int g = 0; g < ROWS; ++g) {
+      if (g >= rows) continue;
+      const uint32_t run = below[g] + __builtin_amdgcn_readlane(before, CellWalk<ROWS>::lane_of(g, wave));
+      uint32_t above = run & 0xFFFFu, in = run >> 16;
+      const int j0 = kRowTokens * g + 4 * tid;
+      const int32_t slot0 = slot_of(j0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool gt = key[4 * g + e] > top, ge = key[4 * g + e] >= last.base;
+        const uint32_t rank = above + min(in, last.need);
+        if (ge && (gt || in < last.need) && rank < static_cast<uint32_t>(p.max_sel)) sel[rank] = slot0 + e;
+        above += gt ? 1u : 0u;
+        in += ge && !gt ? 1u : 0u;
+      }
+    }
+  } else if (t.take_all) {
+    for (int j = tid; j < min(t.p_len, p.max_sel); j += kTokThreads) sel[j] = slot_of(j);
+  }
+  // ---- the kept tail, the padding and the length
+  for (int i = tid; i < t.tail; i += kTokThreads)
+    if (t.kc + i < p.max_sel) sel[t.kc + i] = table[(t.p_len + i) >> 4] * kPage + ((t.p_len + i) & 15);
+  for (int i = t.k + tid; i < p.max_sel; i += kTokThreads) sel[i] = -1;
+  if (tid == 0) p.sel_seq_lens[b] = t.k;
 }
 
 }  // namespace vegas

@@ -753,10 +753,26 @@ int vegas_select_tokens(const vegas_desc* desc, const float* token_scores, const
   tp.max_tokens = desc->max_seq_len;
   tp.slices = token_slices(desc);
   tp.budget_ratio = desc->budget_ratio;
-  const dim3 grid(tp.slices, desc->batch);
-  for (int pass = 0; pass < 4; ++pass)
-    hipLaunchKernelGGL(token_select_hist, grid, dim3(kTokThreads), 0, st, tp, pass);
-  hipLaunchKernelGGL(token_select_write, grid, dim3(kTokThreads), 0, st, tp);
+  // Up to 32768 tokens one workgroup per sequence (figures: token_select_one_kernel; beyond, it takes 0.42 us per 1024 tokens
+  // more and the five launches 0.03: even at about 43000, but 32 keys are what a thread holds), built for the fewest rows of
+  // 4096 that the bound on the lengths allows: a row that is not there costs its tests and requests.
+  auto launch_one_wg = [&](auto rows) {
+    hipLaunchKernelGGL(token_select_one_kernel<decltype(rows)::value>, dim3(desc->batch), dim3(kTokThreads), 0, st, tp);
+  };
+  if (desc->max_seq_len <= 4 * kTokThreads) {
+    launch_one_wg(std::integral_constant<int, 1>{});
+  } else if (desc->max_seq_len <= 8 * kTokThreads) {
+    launch_one_wg(std::integral_constant<int, 2>{});
+  } else if (desc->max_seq_len <= 16 * kTokThreads) {
+    launch_one_wg(std::integral_constant<int, 4>{});
+  } else if (desc->max_seq_len <= 32 * kTokThreads) {
+    launch_one_wg(std::integral_constant<int, 8>{});
+  } else {
+    const dim3 grid(tp.slices, desc->batch);
+    for (int pass = 0; pass < 4; ++pass)
+      hipLaunchKernelGGL(token_select_hist, grid, dim3(kTokThreads), 0, st, tp, pass);
+    hipLaunchKernelGGL(token_select_write, grid, dim3(kTokThreads), 0, st, tp);
+  }
   return hipGetLastError() == hipSuccess ? VEGAS_OK : VEGAS_ERR_LAUNCH;
 }
 
