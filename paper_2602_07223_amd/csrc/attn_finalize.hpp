@@ -149,31 +149,98 @@ __global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_H
 }
 
 // Verification epilogue in ONE launch (a kernel boundary costs ~3 us on this GPU): workgroups
-// [0, nA) merge the chunk partials of two query rows each (as the combine kernels do) and write
+// [0, nA) merge the chunk partials of a few query rows each (as the combine kernels do) and write
 // the bf16 output rows (Eq. 1); workgroups [nA, nA + nB) turn the per-(row, page) log-sum-exps of
 // 32 pages into page criticalities (Eq. 2 / Eq. 3 with weights, averaged over rows and heads as in the
 // last paragraph of Sec. 3.3): score[b][j] = inv_norm * sum_h sum_{rows in R} 2^(page_lse - row_lse).
 // A score workgroup derives the global row log-sum-exps itself from the chunks' (max, sum) pairs,
 // so it does not depend on the merge workgroups.  Pages at or beyond the sequence's page count get 0.
 // MAXS > 0: at most MAXS chunks, the merge workgroups take the one-round-trip path; 0: any number; kFinPlanned:
-// balanced chunking (any number, usually few).
+// balanced chunking (any number, usually few; merge_planned_rows).
 // Loads are ordered so that a workgroup's dependent memory round trips are as few as possible: the
 // kernel runs for a handful of microseconds and every trip is a sizeable part of that.
 constexpr int kFinPlanned = -1;
 constexpr int kFinPre = 8;       // page log-sum-exps a score thread keeps in registers: 4 * kFinPre rows
+
+// Merge under balanced chunking: 1024 / D consecutive rows of the Hkv R rows per workgroup, a thread has four head dims of
+// one, and asks for the slots of its sequence (few as a rule, and known by now: the plan had to be read first) four or eight at a
+// time, (max, sum) pairs and partial rows together.  A batch has thousands of rows, so it is not one row's round trip that
+// counts but how many workgroups have to follow one another.  (With the page values below, by the profiler: 16 sequences of 8K..64K
+// tokens, 40 rows 20.4 -> 17.3 us, 24 of 1K..20K, 32 rows 13.7 -> 10.0; 4 of 64K, 20 rows 7.9 -> 7.9.)
+__device__ __forceinline__ void merge_planned_rows(const FinalizeParams& p, const ColumnSlots& cs, int b, int HR) {
+  const int per_row = p.D >> 2;                                   // threads
+  const int rr = static_cast<int>(blockIdx.x) * (256 / per_row) + static_cast<int>(threadIdx.x) / per_row;
+  const int d = 4 * (static_cast<int>(threadIdx.x) & (per_row - 1));
+  if (rr >= HR) return;
+  const int h = static_cast<int>((static_cast<float>(rr) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(p.R)));   // rr / R < 2^15
+  const int r = rr - h * p.R;
+  const int64_t row = (cs.off + static_cast<int64_t>(h) * cs.stride_h) * p.R + r;   // of the first slot; R rows between slots
+  const float2* const ml = p.part_ml + row;
+  const float* const po = p.part_o + row * p.D + d;
+  int n = p.lens[b];
+  n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
+  const ColumnChunks cc = column_chunks(cs, n);
+  float m = -INFINITY, L = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  auto slots = [&](int s0, auto tag) {
+    constexpr int N = decltype(tag)::value;
+    float2 v[N];
+    f32x4 x[N];
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+      const int64_t at = static_cast<int64_t>(requested_slot(s0 + s, cc.last)) * p.R;
+      v[s] = ml[at];
+      x[s] = *reinterpret_cast<const f32x4*>(po + at * p.D);
+    }
+    __builtin_amdgcn_sched_barrier(0);       // every request leaves before the first use
+    float top = m;
+#pragma unroll
+    for (int s = 0; s < N; ++s)
+      if (s0 + s < cc.ns) top = fmaxf(top, v[s].x);
+    const float use = (top == -INFINITY) ? 0.f : top;
+    const float old = fast_exp2(m - use);
+    L *= old;
+    acc *= old;
+    m = top;
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+      if (s0 + s < cc.ns) {
+        const float w = fast_exp2(v[s].x - use);
+        L += w * v[s].y;
+        acc += w * x[s];
+      }
+    }
+  };
+  if (cc.last >= 0) {                        // (an empty sequence may own no slot, so nothing is requested)
+    if (cc.ns <= 4) slots(0, std::integral_constant<int, 4>{});
+    else for (int s0 = 0; s0 < cc.ns; s0 += 8) slots(s0, std::integral_constant<int, 8>{});
+  }
+  f32x4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = (L > 0.f) ? acc[e] / L : 0.f;
+  const int t = r / p.g, j = r % p.g;
+  u32x2 packed;
+  packed[0] = static_cast<uint32_t>(float_to_bf16_bits(o[0])) | (static_cast<uint32_t>(float_to_bf16_bits(o[1])) << 16);
+  packed[1] = static_cast<uint32_t>(float_to_bf16_bits(o[2])) | (static_cast<uint32_t>(float_to_bf16_bits(o[3])) << 16);
+  *reinterpret_cast<u32x2*>(p.out + ((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * p.D + d) = packed;
+}
 
 // METRIC 1 (the paper's logit metric, token granularity) replaces the page-score role by workgroups
 // [nA, nA + nC) that add the H_kv per-head token sums of 1024 tokens each: score[b][i] = tok_norm *
 // sum_h partial[b][h][i] for prefix tokens i < n_b - G (Sec. 3.3, last paragraph), 0 elsewhere.
 template <int MAXS, int METRIC = 0>
 __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizeParams p) {
-  extern __shared__ float smf[];              // role A (general path): [256 / D][D] weights + [256 / D][4]; role B: [Hkv*R] + [8][32] + [Hkv*R][8] pairs
+  extern __shared__ __attribute__((aligned(16))) float smf[];              // role A (general path): [256 / D][D] weights + [256 / D][4]; role B: [Hkv*R] + [8][32] + [Hkv*R][8] pairs
   const int b = blockIdx.y;
   const int tid = threadIdx.x;
   const int HR = p.Hkv * p.R;
   const ColumnSlots cs = column_slots(p.plan, p.slots_total, b, p.Hkv, p.nsplit, p.chunk_tokens);
 
   if (static_cast<int>(blockIdx.x) < p.nA) {
+    if constexpr (MAXS == kFinPlanned) {
+      merge_planned_rows(p, cs, b, HR);
+      return;
+    }
     // ---- role A: 256 / D consecutive rows of the Hkv*R rows, D threads (= head dims) each
     const int T = p.D;
     const int sub = tid / T, t128 = tid % T, wv = (tid >> 6) % (T >> 6);
@@ -201,17 +268,13 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
           p.out[((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * T + t128] = bits;
         }
       };
-      if (cc.last < 0) {                     // an empty sequence: it may own no slot, so nothing is requested
+      if (cc.last < 0) {                     // an empty sequence: nothing is requested
         store(0);
         return;
       }
-      // A sequence may have few chunks although the host's bound on them is high (balanced chunking bounds them by all
-      // the slots of a head; a loose max_seq_len or a caller's chunk length may too): only its own slots are read, in one
-      // round trip.  (Balanced chunking: the plan has to be read before anything can be addressed, so the length is known
-      // by now.  Reading as many as the host's bound allows, most of them other sequences', took the whole kernel 30 us on
-      // 24 sequences of 1K..20K tokens with 32 rows; this and the smaller score role below take 13.7.  16 of 8K..64K
-      // tokens, 40 rows: 33 -> 24 us.  One sequence of 4000 tokens in chunks of 128 under a bound of 131072, 20 rows, first
-      // and last collected: the whole call 22.0 -> 20.8.)
+      // A sequence may have few chunks although the host's bound on them is high (a loose max_seq_len or a caller's chunk
+      // length): only its own slots are read, in one round trip.  (One sequence of 4000 tokens in chunks of 128 under a bound
+      // of 131072, 20 rows, first and last collected: the whole call 22.0 -> 20.8 us.)
       if (ns <= 32) {
         const float* const po = p.part_o + (pbase * p.R + r) * T;
         auto merge = [&](auto maxs) {
@@ -347,7 +410,7 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
   };
   // The first batch, and (with few rows) this thread's page log-sum-exps, are
   // requested before the sequence length is needed.
-  const bool pre_ok = (Rc & 3) == 0 && Rc <= 4 * kFinPre && p.Hkv <= 8;
+  const bool pre_ok = MAXS != kFinPlanned && (Rc & 3) == 0 && Rc <= 4 * kFinPre && p.Hkv <= 8;
   f32x4 pre[kFinPre];
   const int jpre = min(jbase + pg, p.lse_pages - 1);
   if (pre_ok && slot < p.Hkv) {
@@ -356,7 +419,30 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
     for (int q = 0; q < kFinPre; ++q)
       if (4 * q < Rc) pre[q] = *reinterpret_cast<const f32x4*>(pl + 4 * q);
   }
+  // Balanced chunking: the page values of a head are one run of 32 pages x Rc floats.  The workgroup reads the runs as they lie,
+  // in 16-byte pieces (quads of rows), and requests what a batch of kQuads per thread holds now; a quad's sum goes through LDS
+  // to the thread that adds up its page.  (A thread that reads the rows of its page itself, 128 or 160 bytes apart from its
+  // neighbour's, touches every line of the run with every request; figures: merge_planned_rows.)
+  constexpr int kQuads = 10;
+  const bool by_quads = MAXS == kFinPlanned && (Rc & 3) == 0;
+  const int q4 = Rc >> 2, run = 32 * q4, quads = p.Hkv * run;     // quads of a page, a head's run, the workgroup
+  const int run_live = min(32, p.lse_pages - jbase) * q4;         // quads of a run that exist
+  const float rcp_run = __builtin_amdgcn_rcpf(static_cast<float>(run)), rcp_q4 = __builtin_amdgcn_rcpf(static_cast<float>(q4));
+  const float* const lse_base = p.page_lse + (static_cast<int64_t>(b) * p.Hkv * p.lse_pages + jbase) * Rc;
+  f32x4 quad[MAXS == kFinPlanned ? kQuads : 1];
+  auto head_of = [&](int i) { return static_cast<int>((static_cast<float>(i) + 0.5f) * rcp_run); };   // i < 2^20: exact
+  auto load_quads = [&](int i0) {
+#pragma unroll
+    for (int a = 0; a < kQuads; ++a) {
+      const int i = min(i0 + 256 * a, quads - 1);
+      const int hd = head_of(i);
+      quad[a] = *reinterpret_cast<const f32x4*>(lse_base + static_cast<int64_t>(hd) * p.lse_pages * Rc + 4 * min(i - hd * run, run_live - 1));
+    }
+  };
   load_units(0, tid);
+  if constexpr (MAXS == kFinPlanned) {
+    if (by_quads) load_quads(tid);
+  }
 
   int n = p.lens[b];
   n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
@@ -407,11 +493,40 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
     sm_row[i] = (L > 0.f) ? m_use + fast_log2(L) : -INFINITY;
   }
   __syncthreads();
+  if constexpr (MAXS == kFinPlanned) {
+    if (by_quads) {
+      float* const sm_quad = smf + HR + 256;                       // [Hkv * 32][pitch], where the pairs were
+      const int pitch = q4 | 1;
+      for (int i0 = tid; i0 < quads; i0 += kQuads * 256) {
+        if (i0 != tid) load_quads(i0);
+#pragma unroll
+        for (int a = 0; a < kQuads; ++a) {
+          const int i = i0 + 256 * a;
+          if (i < quads) {
+            const int hd = head_of(i), of_run = i - hd * run;
+            const int page = static_cast<int>((static_cast<float>(of_run) + 0.5f) * rcp_q4), q = of_run - page * q4;
+            const f32x4 rl = *reinterpret_cast<const f32x4*>(sm_row + hd * Rc + 4 * q);
+            float sum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              if (rl[e] != -INFINITY) sum += fast_exp2(quad[a][e] - rl[e]);
+            sm_quad[(hd * 32 + page) * pitch + q] = sum;
+          }
+        }
+      }
+      __syncthreads();
+    }
+  }
   {
     const int j = jbase + pg;
     float sc = 0.f;
     if (j < nblk) {
-      if (pre_ok) {
+      if (by_quads) {
+        for (int h = slot; h < p.Hkv; h += 8) {
+          const float* const sums = smf + HR + 256 + (h * 32 + pg) * (q4 | 1);
+          for (int q = 0; q < q4; ++q) sc += sums[q];
+        }
+      } else if (pre_ok) {
         if (slot < p.Hkv) {
           const float* rl = sm_row + slot * Rc;
 #pragma unroll

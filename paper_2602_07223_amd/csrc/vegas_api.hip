@@ -630,7 +630,7 @@ static int verify_impl(const vegas_desc* desc, const void* q, const void* k_cach
   fp.D = desc->head_dim;
   fp.plan = sp.plan;
   fp.slots_total = sp.slots_total;
-  const int rows_per_wg = 256 / fp.D;                  // merge workgroups: 256 threads, D per row
+  const int rows_per_wg = (pl.balanced ? 1024 : 256) / fp.D;   // merge workgroups: 256 threads, D per row, or D / 4
   fp.nA = (sp.Hkv * pl.R + rows_per_wg - 1) / rows_per_wg;
   const int nrows = (desc->collect_rows == VEGAS_COLLECT_ALL_ROWS) ? desc->num_queries
                                                                    : (desc->num_queries > 1 ? 2 : 1);
