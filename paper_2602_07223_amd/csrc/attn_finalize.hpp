@@ -422,7 +422,9 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
   // Balanced chunking: the page values of a head are one run of 32 pages x Rc floats.  The workgroup reads the runs as they lie,
   // in 16-byte pieces (quads of rows), and requests what a batch of kQuads per thread holds now; a quad's sum goes through LDS
   // to the thread that adds up its page.  (A thread that reads the rows of its page itself, 128 or 160 bytes apart from its
-  // neighbour's, touches every line of the run with every request; figures: merge_planned_rows.)
+  // neighbour's, touches every line of the run with every request; figures:
+  // merge_planned_rows.  One sequence is better off with that all the same, its 64 score workgroups wait for latency and not for
+  // requests: us per iteration, page by page / by quads, 4096 tokens 44.0 / 44.6, 32768 69.7 / 70.6, 131072 157.8 / 158.5.)
   constexpr int kQuads = 10;
   const bool by_quads = MAXS == kFinPlanned && (Rc & 3) == 0;
   const int q4 = Rc >> 2, run = 32 * q4, quads = p.Hkv * run;     // quads of a page, a head's run, the workgroup
@@ -431,17 +433,18 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
   const float* const lse_base = p.page_lse + (static_cast<int64_t>(b) * p.Hkv * p.lse_pages + jbase) * Rc;
   f32x4 quad[MAXS == kFinPlanned ? kQuads : 1];
   auto head_of = [&](int i) { return static_cast<int>((static_cast<float>(i) + 0.5f) * rcp_run); };   // i < 2^20: exact
-  auto load_quads = [&](int i0) {
+  auto load_quads = [&](int first) {         // (first: of the workgroup's batch)
 #pragma unroll
     for (int a = 0; a < kQuads; ++a) {
-      const int i = min(i0 + 256 * a, quads - 1);
+      if (first + 256 * a >= quads) continue;
+      const int i = min(first + 256 * a + tid, quads - 1);
       const int hd = head_of(i);
       quad[a] = *reinterpret_cast<const f32x4*>(lse_base + static_cast<int64_t>(hd) * p.lse_pages * Rc + 4 * min(i - hd * run, run_live - 1));
     }
   };
   load_units(0, tid);
   if constexpr (MAXS == kFinPlanned) {
-    if (by_quads) load_quads(tid);
+    if (by_quads) load_quads(0);
   }
 
   int n = p.lens[b];
@@ -497,11 +500,11 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
     if (by_quads) {
       float* const sm_quad = smf + HR + 256;                       // [Hkv * 32][pitch], where the pairs were
       const int pitch = q4 | 1;
-      for (int i0 = tid; i0 < quads; i0 += kQuads * 256) {
-        if (i0 != tid) load_quads(i0);
+      for (int first = 0; first < quads; first += kQuads * 256) {
+        if (first > 0) load_quads(first);
 #pragma unroll
         for (int a = 0; a < kQuads; ++a) {
-          const int i = i0 + 256 * a;
+          const int i = first + 256 * a + tid;
           if (i < quads) {
             const int hd = head_of(i), of_run = i - hd * run;
             const int page = static_cast<int>((static_cast<float>(of_run) + 0.5f) * rcp_q4), q = of_run - page * q4;
