@@ -1,8 +1,9 @@
 // Top-k selection over single tokens (the paper's own granularity: Sec. 3.3 last paragraph, Sec. 4).
 //
 // A sequence has up to a few hundred thousand prefix tokens, too many for one workgroup, so the
-// radix select of the page version is spread over workgroups (beyond 32768 tokens; up to there token_select_one_kernel) that own 4096-token slices and meet in
-// per-slice digit histograms between launches (plain stores, nothing to clear, no global atomics):
+// radix select of the page version is spread over workgroups that own 4096-token slices and meet in
+// per-slice digit histograms between launches (plain stores, nothing to clear, no global atomics; up to 32768 tokens one
+// workgroup does it all, token_select_one_kernel):
 //   token_select_hist x 4  pass q: every workgroup sums the slices' histograms of passes < q, derives
 //                          the key prefix they fix, counts digit q of its own slice's matching keys
 //                          in LDS and stores its 256 counts
