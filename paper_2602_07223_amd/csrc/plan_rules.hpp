@@ -102,4 +102,45 @@ inline int unplanned_pair_chunk(int rows, int max_len) {
   return max_len > 8192 ? (max_len + 1) / 2 : max_len;
 }
 
+// A batch whose chunk lengths are computed on the GPU (balanced_slot, vegas_common.hpp): the numbers that the plan works with,
+// per KV head (and row block), and what of them a launch holds.  units: of kTile tokens per wave.
+struct BatchPlan {
+  int J = 0;                   // workgroups of one launch wave: one per compute unit
+  int J2 = 0;                  // of two waves of equal chunks (= J where only one is planned for)
+  int JR = 0;                  // running at a time, which is how many shares a batch is cut into
+  int JS = 0;                  // workgroups launched and partial slots held
+  int cap_units = 0;           // longest chunk
+};
+inline BatchPlan batch_plan(int num_cu, int64_t per_head, int batch, int max_len, int unit, int cap_units, bool pair,
+                            bool two_per_cu, bool collects) {
+  BatchPlan p;
+  p.cap_units = cap_units;
+  p.J = static_cast<int>(num_cu / per_head);
+  // Slots no plan uses still cost a workgroup that works that out, so only those that can be used are launched: two waves
+  // of equal chunks are planned for where there are more sequences than workgroups, or where workgroups that park nothing
+  // run side by side.
+  p.JR = two_per_cu ? 2 * p.J : p.J;
+  const bool two_waves = batch > p.J || (two_per_cu && batch >= 8) || (!pair && !collects && 2 * batch > p.J);
+  p.J2 = two_waves ? 2 * p.J : p.J;
+  const int64_t most_units = (static_cast<int64_t>(max_len) + unit - 1) / unit;
+  const int64_t capped = (most_units + cap_units - 1) / cap_units;
+  // slots: a plan for J2 workgroups never takes more than max(J2, B) of them; a capped one B times the most of a sequence; JR
+  // shares one each and one more where a sequence ends inside a share (there are at most as many sequences as shares)
+  int64_t js = p.J2 > batch ? p.J2 : batch;
+  const int64_t shared = p.JR + (batch < p.JR ? batch : p.JR) - 1;
+  if (shared > js) js = shared;
+  if (batch * capped > js) js = batch * capped;
+  p.JS = static_cast<int>(js);
+  return p;
+}
+
+// Workgroups go round the 8 XCDs, on each round its 4 shader engines, so every 32nd starts on the same engine: of the
+// consecutive ones of a head, whose grid has `per_slot` workgroups (KV heads x row blocks) between them, so many start on as
+// many engines.
+inline int share_group(int per_slot) {
+  int group = 32;
+  for (int step = per_slot; step % 2 == 0 && group > 1; step /= 2) group /= 2;
+  return group;
+}
+
 }  // namespace vegas

@@ -63,8 +63,7 @@ struct SplitPlan {
   int R = 0, Rc = 0, NB = 0, NW = 0, chunk = 0, nsplit = 0, lse_pages = 0;   // Rc: collected rows per KV head
   bool pair = false;                 // verification of more than 32 rows per KV head: 64-row workgroups (attn_pair_kernel)
   bool balanced = false;             // chunk lengths per sequence, computed on the GPU from the lengths (ragged batches)
-  int J = 0, J2 = 0, JS = 0, JR = 0; // balanced: workgroups per KV head of a one-wave and a two-wave plan; slots held; running at a time
-  int cap_units = 0;                 // balanced: longest chunk, in units of kTile * NW tokens
+  BatchPlan bp;                      // balanced: numbers of workgroups, in units of kTile * NW tokens
   size_t off_plan = 0;               // balanced: [B] (first slot, chunk tokens)
   size_t off_part_o = 0, off_part_ml = 0, off_page_lse = 0, total = 0;
 };
@@ -186,35 +185,16 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
     // 18432 tokens reach 80 % of the peak, 512 of 9216 75 %, 4096-token chunks 69 %), or shares of the batch when the
     // lengths are too ragged for equal chunks.  The same for 64-row workgroups, which park no whole chunk (4 x 65536 tokens, 40
     // rows: 256 chunks 196 us, 512 198, 1024 208; 2 x 8192: 18.5, 26.9, 36.1).
-    pl->J = static_cast<int>(num_cu / per_head);
-    // Slots no plan uses still cost a workgroup that works that out, so only those that can be used are launched: two waves
-    // of equal chunks are planned for where there are more sequences than workgroups, or where workgroups that park nothing
-    // run side by side.
-    const bool two_per_cu = pl->pair && pair_two_per_cu(d->head_dim, collect);
-    pl->JR = two_per_cu ? 2 * pl->J : pl->J;
-    const bool two_waves = d->batch > pl->J || (two_per_cu && d->batch >= 8) || (!pl->pair && collect == 0 && 2 * d->batch > pl->J);
-    pl->J2 = two_waves ? 2 * pl->J : pl->J;
     int cap = 1 << 24;
     if (collect != 0 && !pl->pair) {
       const int prows = rows_per_head < 32 ? rows_per_head : 32;
       cap = unit;
       while (split_lds_bytes(pl->NW, prows, collect, cap + unit, d->head_dim) <= 150 * 1024 && cap < (1 << 24)) cap += unit;
     }
-    pl->cap_units = cap / unit;
+    pl->bp = batch_plan(num_cu, per_head, d->batch, max_len, unit, cap / unit, pl->pair,
+                        pl->pair && pair_two_per_cu(d->head_dim, collect), collect != 0);
     pl->chunk = collect != 0 && !pl->pair ? cap : unit;         // sizes the LDS that parks a chunk's collected values
-    int64_t most_chunks = (static_cast<int64_t>(max_len) + cap - 1) / cap;   // of one sequence
-    if (most_chunks < pl->J2) most_chunks = pl->J2;
-    // slots: a plan for J2 workgroups never takes more than max(J2, B) of them; a capped one B * most_chunks; JR shares one
-    // each and one more where a sequence ends inside a share (there are at most as many sequences as shares)
-    int64_t js = pl->J2 > d->batch ? pl->J2 : d->batch;
-    const int64_t shared = pl->JR + (d->batch < pl->JR ? d->batch : pl->JR) - 1;
-    if (shared > js) js = shared;
-    const int64_t capped = static_cast<int64_t>(d->batch) * ((static_cast<int64_t>(max_len) + static_cast<int64_t>(pl->cap_units) * unit - 1) /
-                                                            (static_cast<int64_t>(pl->cap_units) * unit));
-    if (capped > js) js = capped;
-    pl->JS = static_cast<int>(js);
-    pl->nsplit = static_cast<int>(most_chunks);                 // most chunks one sequence can get
-    slots = static_cast<size_t>(d->num_kv_heads) * pl->JS;   // (sibling row blocks share a slot)
+    slots = static_cast<size_t>(d->num_kv_heads) * pl->bp.JS;   // (sibling row blocks share a slot)
   }
   pl->lse_pages = collect == 1 ? (max_len + kPage - 1) / kPage
                                : (collect == 2 ? (pl->balanced ? (max_len + unit - 1) / unit * unit : pl->nsplit * chunk) : 0);
@@ -287,7 +267,7 @@ template <bool CAUSAL, int COLLECT, int D>
 int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t st, int page_size) {
   if constexpr (CAUSAL) {
     if (pl.pair) {
-      const unsigned slots = pl.balanced ? pl.JS : pl.nsplit, seqs = pl.balanced ? 1 : batch;
+      const unsigned slots = pl.balanced ? pl.bp.JS : pl.nsplit, seqs = pl.balanced ? 1 : batch;
       const PairLds lds = pair_lds(pl.R, pl.Rc, pl.NB, COLLECT, D);
       sp.row_blocks = pl.NB;
       sp.lds_q_off = static_cast<int32_t>(lds.off_max);
@@ -314,7 +294,7 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
     }
   }
   // (KV head, row block + NB * chunk, sequence): the kernels read their indices off the grid without a division
-  const dim3 grid = pl.balanced ? dim3(sp.Hkv, static_cast<unsigned>(pl.NB) * pl.JS, 1)
+  const dim3 grid = pl.balanced ? dim3(sp.Hkv, static_cast<unsigned>(pl.NB) * pl.bp.JS, 1)
                                 : dim3(sp.Hkv, static_cast<unsigned>(pl.NB) * pl.nsplit, batch);
   if (grid.y > 65535u) return VEGAS_ERR_UNSUPPORTED;        // more chunks per sequence than a grid dimension holds
   const int rows = pl.R < 32 ? pl.R : 32;
@@ -323,7 +303,7 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
   // shares all start at once, on some units two (no collection, 24 sequences of 1001..20011 tokens 184 -> 200 us; 48 of 300..3000
   // in equal chunks 70 -> 79).  Short ones gain from workgroups side by side (16 of 300..1200 18.4 us, alone 18.9).
   if (pl.balanced && lds < kLoneLds &&
-      static_cast<int64_t>(batch) * sp.max_tokens >= static_cast<int64_t>(16) * pl.J * sp.chunk_unit)
+      static_cast<int64_t>(batch) * sp.max_tokens >= static_cast<int64_t>(16) * pl.bp.J * sp.chunk_unit)
     lds = kLoneLds;
   sp.lds_q_off = static_cast<int32_t>(lds - split_lds_tail_bytes(pl.NW, D));
   sp.row_blocks = pl.NB;
@@ -402,14 +382,12 @@ void fill_split_params(const vegas_desc* d, const SplitPlan& pl, int G, const vo
   sp->epoch_mul = 0;
   sp->plan = pl.balanced ? reinterpret_cast<int2*>(ws + pl.off_plan) : nullptr;
   sp->batch = d->batch;
-  sp->slots_target = pl.J;
-  sp->slots_target2 = pl.J2;
-  sp->share_wgs = pl.JR;
-  // Workgroups go round the 8 XCDs, on each round its 4 shader engines: every 32nd starts on the same engine.
-  sp->share_group = 32;
-  for (int step = d->num_kv_heads * pl.NB; step % 2 == 0 && sp->share_group > 1; step /= 2) sp->share_group /= 2;
-  sp->chunk_cap_units = pl.cap_units;
-  sp->slots_total = pl.JS;
+  sp->slots_target = pl.bp.J;
+  sp->slots_target2 = pl.bp.J2;
+  sp->share_wgs = pl.bp.JR;
+  sp->share_group = share_group(d->num_kv_heads * pl.NB);
+  sp->chunk_cap_units = pl.bp.cap_units;
+  sp->slots_total = pl.bp.JS;
   sp->chunk_unit = kTile * pl.NW;
   sp->max_tokens = d->max_seq_len;
   sp->page_stride = d->kv_page_stride;

@@ -63,6 +63,18 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
   return static_cast<uint32_t>(v);
 }
 
+// What the batch planner (balanced_slot) asks of the 64 lanes that run it together; a host program can put a class of its
+// own in its place.
+struct GpuWave {
+  static __device__ __forceinline__ int lane() { return threadIdx.x & 63; }
+  static __device__ __forceinline__ uint32_t sum(uint32_t x) { return wave_sum(x); }
+  static __device__ __forceinline__ uint32_t max(uint32_t x) { return wave_max(x); }
+  static __device__ __forceinline__ uint32_t prefix_sum(uint32_t x) { return wave_prefix_sum(x); }   // inclusive
+  static __device__ __forceinline__ uint64_t ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
+  static __device__ __forceinline__ uint32_t readlane(uint32_t x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
+  static __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }          // within one ulp or so
+};
+
 // base + how many of the lanes below this one are set in mask.
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask, uint32_t base) {
   return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
@@ -355,8 +367,9 @@ struct BalancedSlot {
 // 16 sequences of 4000..16000 tokens, 20 rows 132 / 124 / 131 / 123; 8 of 1001..20011 75.4 / 81.5 / 70.6 / 70.3.
 constexpr uint32_t kShareCost = 3;
 // ceil(x / d) for 0 <= x < 2^23, 1 <= d < 2^23 (a float reciprocal and one correction step instead of an integer division)
-__device__ __forceinline__ uint32_t ceil_div_small(uint32_t x, uint32_t d) {
-  uint32_t q = static_cast<uint32_t>(static_cast<float>(x) * __builtin_amdgcn_rcpf(static_cast<float>(d)));
+template <typename Wave>
+__host__ __device__ __forceinline__ uint32_t ceil_div_small(uint32_t x, uint32_t d) {
+  uint32_t q = static_cast<uint32_t>(static_cast<float>(x) * Wave::rcp(static_cast<float>(d)));
   q = q * d > x ? q - 1u : q;                                   // (the estimate is off by one at most)
   q = (q + 1u) * d <= x ? q + 1u : q;                           // q = floor(x / d)
   return q * d < x ? q + 1u : q;
@@ -365,8 +378,9 @@ __device__ __forceinline__ uint32_t ceil_div_small(uint32_t x, uint32_t d) {
 // total their sum, longest their maximum (the condition always holds there when J >= number of sequences, and
 // nothing changes beyond it).  No plan can beat ceil(total / J), and a batch of equal lengths meets it, so the
 // search starts there and widens its steps before it bisects: one evaluation for a uniform batch.
-__device__ __forceinline__ uint32_t balanced_chunk_units(uint32_t nu, uint32_t total, uint32_t longest, uint32_t J) {
-  auto fits = [&](uint32_t c) { return wave_sum(ceil_div_small(nu, c)) <= J; };
+template <typename Wave>
+__host__ __device__ __forceinline__ uint32_t balanced_chunk_units(uint32_t nu, uint32_t total, uint32_t longest, uint32_t J) {
+  auto fits = [&](uint32_t c) { return Wave::sum(ceil_div_small<Wave>(nu, c)) <= J; };
   uint32_t lo = (total + J - 1u) / J;                           // wave-uniform from here on
   lo = lo < 1u ? 1u : lo;
   if (lo >= longest || fits(lo)) return lo < longest ? lo : longest;
@@ -401,81 +415,82 @@ __host__ __device__ __forceinline__ bool wants_shares(uint32_t priced, uint32_t 
 }
 // share_wgs: workgroups per KV head that run at a time (J of the shares); share_margin: for wants_shares; second_cost: for
 // wants_second_wave.
-__device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B, int max_tokens, int j1, int j2, int share_wgs,
-                                                      int share_group, int share_margin, int second_cost, int cap_units, int unit,
-                                                      int j, int2* plan_out) {
-  const int lane = threadIdx.x & 63;
+template <typename Wave = GpuWave>
+__host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B, int max_tokens, int j1, int j2, int share_wgs,
+                                                               int share_group, int share_margin, int second_cost, int cap_units,
+                                                               int unit, int j, int2* plan_out) {
+  const int lane = Wave::lane();
   uint32_t n = 0u;
   if (lane < B) {
     const int v = lens[lane];
     n = static_cast<uint32_t>(v < 0 ? 0 : (v > max_tokens ? max_tokens : v));
   }
   const uint32_t nu = (n + unit - 1u) / unit;                   // length in units
-  const uint32_t total = wave_sum(nu);
+  const uint32_t total = Wave::sum(nu);
   BalancedSlot r = {-1, 0, unit, 0};
   if (total == 0u) {
     if (plan_out && lane < B) plan_out[lane] = make_int2(0, unit);
     return r;
   }
-  const uint32_t longest = wave_max(nu);
-  const uint64_t live = __builtin_amdgcn_ballot_w64(nu > 0u);
-  const uint32_t J = share_wgs, lives = __popcll(live);
-  uint32_t C = balanced_chunk_units(nu, total, longest, J);
+  const uint32_t longest = Wave::max(nu);
+  const uint64_t live = Wave::ballot(nu > 0u);
+  const uint32_t J = share_wgs, lives = __builtin_popcountll(live);
+  uint32_t C = balanced_chunk_units<Wave>(nu, total, longest, J);
   const uint32_t priced = total + kShareCost * (lives - 1u), S = (priced + J - 1u) / J;
   if (S <= static_cast<uint32_t>(cap_units) && wants_shares(priced, lives, J, C, static_cast<uint32_t>(share_margin))) {
-    const uint32_t rank = __popcll(live & ((1ull << lane) - 1ull));
-    const uint32_t base = wave_prefix_sum(nu) - nu + kShareCost * rank;       // where the sequence's first token lies
+    const uint32_t rank = __builtin_popcountll(live & ((1ull << lane) - 1ull));
+    const uint32_t base = Wave::prefix_sum(nu) - nu + kShareCost * rank;       // where the sequence's first token lies
     const uint32_t q = base / S, count = nu > 0u ? (base + nu - 1u) / S - q + 1u : 0u;
     if (plan_out && lane < B) plan_out[lane] = nu > 0u ? make_int2(q + rank, -static_cast<int>(count)) : make_int2(0, unit);
     const uint32_t head = min(nu, (q + 1u) * S - base);                       // first piece (0 if empty); last one, where there
     const uint32_t tail = count > 1u ? nu - head - (count - 2u) * S : 0u;     // are several; whole shares between them
     const uint32_t mid = count > 2u ? count - 2u : 0u;
-    const uint32_t before = wave_prefix_sum(mid) - mid;
-    const uint32_t mids = __builtin_amdgcn_readlane(before + mid, 63);
+    const uint32_t before = Wave::prefix_sum(mid) - mid;
+    const uint32_t mids = Wave::readlane(before + mid, 63);
     const uint32_t at = static_cast<uint32_t>(j) < (J & -static_cast<uint32_t>(share_group)) ? j ^ (share_group - 1) : j;
     uint64_t hit;
     uint32_t piece;
     if (at < mids) {
-      hit = __builtin_amdgcn_ballot_w64(at >= before && at - before < mid);
-      piece = at - __builtin_amdgcn_readlane(before, __builtin_ctzll(hit)) + 1u;
+      hit = Wave::ballot(at >= before && at - before < mid);
+      piece = at - Wave::readlane(before, __builtin_ctzll(hit)) + 1u;
     } else {                                                    // the others, longest first
       uint32_t at_head = mids, at_tail = mids;
       for (int i = 0; i < B; ++i) {
-        const uint32_t hi = __builtin_amdgcn_readlane(head, i), ti = __builtin_amdgcn_readlane(tail, i);
+        const uint32_t hi = Wave::readlane(head, i), ti = Wave::readlane(tail, i);
         at_head += (hi > head || (hi == head && i < lane) ? 1u : 0u) + (ti > head ? 1u : 0u);
         at_tail += (hi >= tail ? 1u : 0u) + (ti > tail || (ti == tail && i < lane) ? 1u : 0u);
       }
-      const uint64_t heads = __builtin_amdgcn_ballot_w64(head > 0u && at_head == at);
-      const uint64_t tails = __builtin_amdgcn_ballot_w64(tail > 0u && at_tail == at);
+      const uint64_t heads = Wave::ballot(head > 0u && at_head == at);
+      const uint64_t tails = Wave::ballot(tail > 0u && at_tail == at);
       hit = heads | tails;
       if (hit == 0ull) return r;
-      piece = heads ? 0u : __builtin_amdgcn_readlane(count, __builtin_ctzll(hit)) - 1u;
+      piece = heads ? 0u : Wave::readlane(count, __builtin_ctzll(hit)) - 1u;
     }
     r.b = __builtin_ctzll(hit);
-    const uint32_t first = __builtin_amdgcn_readlane(head, r.b);
+    const uint32_t first = Wave::readlane(head, r.b);
     r.c0 = piece == 0u ? 0 : static_cast<int>((first + (piece - 1u) * S) * unit);
     r.chunk = static_cast<int>((piece == 0u ? first : S) * unit);
-    r.slot = __builtin_amdgcn_readlane(q + rank, r.b) + piece;
+    r.slot = Wave::readlane(q + rank, r.b) + piece;
     return r;
   }
-  if (static_cast<uint32_t>(j1) != J) C = balanced_chunk_units(nu, total, longest, static_cast<uint32_t>(j1));
+  if (static_cast<uint32_t>(j1) != J) C = balanced_chunk_units<Wave>(nu, total, longest, static_cast<uint32_t>(j1));
   if (j2 > j1 && wants_second_wave(total, static_cast<uint32_t>(j1), C, static_cast<uint32_t>(second_cost)))
-    C = balanced_chunk_units(nu, total, longest, static_cast<uint32_t>(j2));
+    C = balanced_chunk_units<Wave>(nu, total, longest, static_cast<uint32_t>(j2));
   C = min(C, static_cast<uint32_t>(cap_units));
   const uint32_t s = (nu + C - 1u) / C;                         // chunks of this sequence (0 if empty)
   const int chunk = s > 0u ? static_cast<int>((nu + s - 1u) / s * unit) : 0;   // equal chunks, at most C units
   int P = 0;                                                    // slots of the sequences with longer chunks
   for (int i = 0; i < B; ++i) {
-    const int ci = __builtin_amdgcn_readlane(chunk, i);
-    const int si = __builtin_amdgcn_readlane(static_cast<int>(s), i);
+    const int ci = Wave::readlane(chunk, i);
+    const int si = Wave::readlane(static_cast<int>(s), i);
     P += (ci > chunk || (ci == chunk && i < lane)) ? si : 0;
   }
   if (plan_out && lane < B) plan_out[lane] = make_int2(P, chunk > 0 ? chunk : unit);
-  const uint64_t hit = __builtin_amdgcn_ballot_w64(lane < B && s > 0u && j >= P && j < P + static_cast<int>(s));
+  const uint64_t hit = Wave::ballot(lane < B && s > 0u && j >= P && j < P + static_cast<int>(s));
   if (hit == 0ull) return r;
   r.b = __builtin_ctzll(hit);
-  r.chunk = __builtin_amdgcn_readlane(chunk, r.b);
-  r.c0 = (j - __builtin_amdgcn_readlane(P, r.b)) * r.chunk;
+  r.chunk = Wave::readlane(chunk, r.b);
+  r.c0 = (j - Wave::readlane(P, r.b)) * r.chunk;
   r.slot = j;
   return r;
 }
