@@ -102,6 +102,10 @@ inline int unplanned_pair_chunk(int rows, int max_len) {
   return max_len > 8192 ? (max_len + 1) / 2 : max_len;
 }
 
+// Units of streaming that beginning one more piece costs a compute unit: 0, 1, 2, 3 of them, verification with collection, us:
+// 16 sequences of 4000..16000 tokens, 20 rows 132 / 124 / 131 / 123; 8 of 1001..20011 75.4 / 81.5 / 70.6 / 70.3.
+constexpr uint32_t kShareCost = 3;
+
 // A batch whose chunk lengths are computed on the GPU (balanced_slot, vegas_common.hpp): the numbers that the plan works with,
 // per KV head (and row block), and what of them a launch holds.  units: of kTile tokens per wave.
 struct BatchPlan {
@@ -117,12 +121,16 @@ inline BatchPlan batch_plan(int num_cu, int64_t per_head, int batch, int max_len
   p.cap_units = cap_units;
   p.J = static_cast<int>(num_cu / per_head);
   // Slots no plan uses still cost a workgroup that works that out, so only those that can be used are launched: two waves
-  // of equal chunks are planned for where there are more sequences than workgroups, or where workgroups that park nothing
-  // run side by side.
+  // of equal chunks are planned for where there are more sequences than workgroups, where workgroups that park nothing
+  // run side by side, or where the mean share may be longer than a workgroup can park: shares are out of the question then, and
+  // one wave of the longest chunks would be followed by a few more of them (verification with collection, us, without / with
+  // the second plan: 16 sequences of 8192..65536 tokens, 24 rows 492 / 437; 8 of 10000..100000, 32 rows 418 / 364; 9 of 51202,
+  // 4 rows, token sums 435 / 334; head dimension 64: 20 of 40945, 24 rows 444 / 354).
   p.JR = two_per_cu ? 2 * p.J : p.J;
-  const bool two_waves = batch > p.J || (two_per_cu && batch >= 8) || (!pair && !collects && 2 * batch > p.J);
-  p.J2 = two_waves ? 2 * p.J : p.J;
   const int64_t most_units = (static_cast<int64_t>(max_len) + unit - 1) / unit;
+  const bool beyond_cap = batch >= 8 && batch * most_units + kShareCost * (batch - 1) > static_cast<int64_t>(cap_units) * p.J;
+  const bool two_waves = batch > p.J || (two_per_cu && batch >= 8) || (!pair && !collects && 2 * batch > p.J) || beyond_cap;
+  p.J2 = two_waves ? 2 * p.J : p.J;
   const int64_t capped = (most_units + cap_units - 1) / cap_units;
   // slots: a plan for J2 workgroups never takes more than max(J2, B) of them; a capped one B times the most of a sequence; JR
   // shares one each and one more where a sequence ends inside a share (there are at most as many sequences as shares)

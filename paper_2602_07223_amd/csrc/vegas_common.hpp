@@ -5,6 +5,8 @@
 
 #include <type_traits>
 
+#include "plan_rules.hpp"
+
 namespace vegas {
 
 constexpr int kPage = 16;       // tokens per KV page
@@ -356,16 +358,13 @@ __host__ __device__ __forceinline__ uint32_t requested_slot(int s, int last) {
 //     of the second pieces, will wait, and so on.  Verification with collection, 20 rows, us, two waves of equal chunks /
 //     shares without / with the reversal: 8 sequences of 16384..131072 tokens 439 / 465 / 413; 16 of 8192..65536 424 / 444 / 407;
 //     16 of 4000..16000 132 / 123 / 117; 24 of 1001..20011 205 / 197 / 194.  40 rows: 16 of 8192..65536 449 / 477 / 431.
-// No chunk is longer than cap_units * unit tokens (what a workgroup can park in LDS); a batch too long for J chunks of that
-// size simply takes more slots.
+// No chunk is longer than cap_units * unit tokens (what a workgroup can park in LDS), and a share that would be is not made; a
+// batch too long for J2 chunks of that size simply takes more slots.
 struct BalancedSlot {
   int32_t b;                    // sequence; < 0: workgroup j has nothing to do
   int32_t c0, chunk;            // its first token here, and how many follow (as far as the sequence reaches)
   int32_t slot;                 // partial slot of the KV head
 };
-// Units of streaming that beginning one more piece costs a compute unit: 0, 1, 2, 3 of them, verification with collection, us:
-// 16 sequences of 4000..16000 tokens, 20 rows 132 / 124 / 131 / 123; 8 of 1001..20011 75.4 / 81.5 / 70.6 / 70.3.
-constexpr uint32_t kShareCost = 3;
 // ceil(x / d) for 0 <= x < 2^23, 1 <= d < 2^23 (a float reciprocal and one correction step instead of an integer division)
 template <typename Wave>
 __host__ __device__ __forceinline__ uint32_t ceil_div_small(uint32_t x, uint32_t d) {

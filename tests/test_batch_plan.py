@@ -246,3 +246,20 @@ def test_every_plan_covers_every_sequence_once(tmp_path_factory):
     # the first wave is not whole
     assert {g for g, _, _ in seen} == {1, 2, 4, 8, 16, 32}
     assert {two for _, two, _ in seen} == {False, True} and {part for _, _, part in seen} == {False, True}
+
+
+# KV heads, head dimension, rows, collection, lengths: the mean of a compute unit is longer than a workgroup can park
+LONG = [(8, 128, 24, 1, spread(16, 8192, 65536)), (8, 128, 28, 1, spread(16, 8192, 65536)), (8, 128, 32, 1, spread(16, 8192, 65536)),
+        (8, 128, 20, 2, spread(16, 8192, 65536)), (8, 128, 28, 1, spread(8, 16384, 131072)), (8, 128, 32, 1, spread(8, 10000, 100000)),
+        (8, 64, 32, 1, spread(16, 8192, 65536)), (8, 64, 32, 1, spread(9, 13107, 131072)), (8, 128, 4, 2, [51202] * 9),
+        (8, 64, 24, 1, [40945] * 20), (8, 64, 12, 2, [44366] + [31056] * 18), (4, 128, 20, 1, [33248] * 41)]
+
+
+def test_batches_beyond_the_parking_lds_are_spread_evenly(tmp_path_factory):
+    """No compute unit is given more than a fifth above the mean (one wave of the longest chunks, and a few more of them
+    behind it, gave 1.25 to 1.77 of it)."""
+    calls = [(h, D, rows, c, max(lens), lens) for h, D, rows, c, lens in LONG]
+    for c, d in zip(calls, plans(program(tmp_path_factory), calls)):
+        check(c, d)
+        assert sum(-(-n // UNIT) for n in c[5]) > d["J"] * d["cap"] * 0.9 and not d["shares"], c[:4]
+        assert load(d) < 1.2, (c[:4], load(d), len(d["pieces"]))
