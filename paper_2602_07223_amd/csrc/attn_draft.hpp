@@ -38,6 +38,29 @@ __device__ __forceinline__ float quad_rows_sum(float x) {
   return half_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
+// Tokens of a call's selections, in sixteens, rounded up for each: lane `lane`'s share of them; own: the length of sequence
+// `lane`, if there is one.  (At most 2^25 a lane, far beyond what past_cache asks about.)
+__host__ __device__ __forceinline__ uint32_t lane_sixteens(int own, const int32_t* lens, int batch, int max_tokens, int lane) {
+  auto sixteens = [=](int n) { return static_cast<uint32_t>((n < 0 ? 0 : (n > max_tokens ? max_tokens : n)) + 15) >> 4; };
+  uint32_t sum = lane < batch ? sixteens(own) : 0u;
+  for (int first = 64; first < batch; first += 64) {
+    if (first + lane < batch) sum += sixteens(lens[first + lane]);
+    sum = sum < (1u << 25) ? sum : 1u << 25;
+  }
+  return sum;
+}
+
+// Are the selected K and V (sixteens: of tokens, of all sequences) more than the 256-MiB
+// last-level cache keeps until the next draft step reads the same pages?  Then they are read past it.  us, 8 draft calls of the
+// same selection in turn, through the cache / past it: 104 MB 18.8 / 22.7; 136 MB 28.4 / 33.0; 268 MB 45.5 / 49.4 (head
+// dimension 64 51.9 / 56.7); 302 MB 53.3 / 55.8; 336 MB 60.9 / 60.9, with 16-token pages 58.0 / 59.3; 369 MB 66.6 / 64.4;
+// 393 MB 74.1 / 68.1; 403 MB 76.6 / 71.4; 537 MB 106.7 / 95.0 (head dimension 64 117.7 / 106.2).  The rule takes the next reader
+// of the pages to be the same layer's next step.  Where the steps of other layers come between, nothing is found in the
+// cache at smaller sizes too, and reading past it would pay there as well (a first call on a selection, 537 MB: 179 -> 142).
+__host__ __device__ __forceinline__ bool past_cache(uint64_t sixteens, int kv_heads, int head_dim) {
+  return sixteens * 16u * static_cast<uint64_t>(kv_heads) * static_cast<uint64_t>(head_dim) * 4u >= static_cast<uint64_t>(352) << 20;
+}
+
 constexpr int kDraftWaves = 4;
 constexpr int kDraftRows = 16;     // query rows (of one KV head) a workgroup can take
 
@@ -51,12 +74,14 @@ inline size_t draft16_lds_bytes(int R, int D) {
 // Sec. 4 / App. D).  With small pages a tile spans 32 >> PS pages: their ids are loaded one tile ahead into one
 // register (lane e <-> page e of the tile), every lane fetches the id of each of its tokens with a lane permute and
 // forms a 64-bit address of its own; everything after the loads is the 16-token code.
-// STREAM: K and V are read with the non-temporal hint, K in whole 128-byte lines (half lines would fetch each of them twice
-// then).  For selections that the last-level cache cannot hold until the next draft step reads them again
-// (streamed_selection): 16 x 8192 tokens, one-token pages 106.7 -> 95.0 us (5.7 TB/s), 16-token pages 102.9 -> 92.4;
-// 32 x 3000, two-token pages 74.1 -> 68.1.  A plain read of the same addresses takes 96 us without the hint and 86 with it: what
-// bounds the kernel then is HBM.  Whole lines alone change nothing.
-template <int D, int PS = 4, bool STREAM = false>
+// CHOOSE: calls whose bound allows selections that the last-level cache cannot hold until the next draft step reads them
+// again.  Whether they are that long the lengths say (past_cache); if so, K and V are read with the non-temporal hint, K in
+// whole 128-byte lines (half lines would fetch each of them twice then): 16 x 8192 tokens, one-token pages 106.7 -> 95.0 us
+// (5.7 TB/s), 16-token pages 102.9 -> 92.4; 32 x 3000, two-token pages 74.1 -> 68.1.  A plain read of the same addresses takes 96
+// us without the hint and 86 with it: what bounds the kernel then is HBM.  Whole lines alone change nothing.
+// (The choice costs up to 1 us: 8 x 2048 tokens under a bound of 16384 43.6 -> 44.5, 16 x 200..8192 59.9 -> 60.5; taking the bound for
+// the length cost 55.5 and 66.5.)
+template <int D, int PS = 4, bool CHOOSE = false>
 __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS_SPLIT_HOT_PARAMS, const SplitParams pfull) {
   VEGAS_TL_DECL;
   VEGAS_TL(kTlEntry);
@@ -119,6 +144,8 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
       if (l16 < Rl) qreg[kk] = gload<u32x4, false>(qbase, static_cast<uint32_t>(l16 * D + 32 * kk + 8 * kg) * 2u);
     }
   }
+  int lane_len = 0;                          // length of sequence `lane` (the last one's beyond), used once the chunk is known to be live
+  if constexpr (CHOOSE) lane_len = p.lens[min(lane, p.batch - 1)];
   asm volatile("" : "+s"(p.k), "+s"(p.v), "+s"(p.page_stride), "+s"(p.token_stride), "+s"(p.head_stride),
                "+s"(p.num_pages), "+s"(p.out_direct));
   asm volatile("" : "+s"(p.max_tokens), "+s"(p.nsplit), "+s"(p.scale_log2e), "+s"(p.part_o), "+s"(p.part_ml));
@@ -145,273 +172,283 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   const int c1 = min(c0 + p.chunk_tokens, n);
   const int tile_end = (c1 + kTile - 1) / kTile;
 
-  const int64_t head_off = static_cast<int64_t>(h) * p.head_stride;
-  const uint32_t ts_bytes = static_cast<uint32_t>(p.token_stride) * 2u;
-  // K: token and byte of its row this lane fetches with load (pg, kk) before the lane exchange (see exchange_k)
-  const int k_tok = STREAM ? l16 & 7 : l16;
-  const uint32_t k_byte = static_cast<uint32_t>(kg) * 16u + (STREAM ? static_cast<uint32_t>(l16 >> 3) * 64u : 0u);
-  const uint32_t k_lane_off = static_cast<uint32_t>(k_tok) * ts_bytes + k_byte;
-  const uint32_t v_lane_off = static_cast<uint32_t>(4 * kg) * ts_bytes + static_cast<uint32_t>(l16) * (2u * NBLK);
-  auto page_base = [&](const uint16_t* cache, int ph) -> const unsigned char* {
-    return uniform_ptr(reinterpret_cast<const unsigned char*>(cache + static_cast<int64_t>(ph) * p.page_stride + head_off));
-  };
-  // Small pages: byte address of token t (0..31, a per-lane value) of the tile whose page ids are in ids_cur.
-  typedef const __attribute__((address_space(1))) unsigned char* gbytes;
-  auto token_addr = [&](const uint16_t* cache, int t) -> gbytes {
-    const int id = __shfl(ids_cur, t >> (PS & 3), 64);
-    const int tokin = t & ((1 << (PS & 3)) - 1);
-    const int64_t el = static_cast<int64_t>(id) * p.page_stride + static_cast<int64_t>(tokin) * p.token_stride + head_off;
-    return (gbytes)cache + el * 2;
-  };
-  // K load (pg, kk): token l16 of page pg, head dims 32 kk + 8 kg .. + 7
-  auto issue_k = [&](int k, u32x4 (&kr)[2][KK]) {
-    if constexpr (PS != 4) {
+  auto stream_chunk = [&](auto streamed) __attribute__((always_inline)) {
+    constexpr bool STREAM = decltype(streamed)::value;
+    const int64_t head_off = static_cast<int64_t>(h) * p.head_stride;
+    const uint32_t ts_bytes = static_cast<uint32_t>(p.token_stride) * 2u;
+    // K: token and byte of its row this lane fetches with load (pg, kk) before the lane exchange (see exchange_k)
+    const int k_tok = STREAM ? l16 & 7 : l16;
+    const uint32_t k_byte = static_cast<uint32_t>(kg) * 16u + (STREAM ? static_cast<uint32_t>(l16 >> 3) * 64u : 0u);
+    const uint32_t k_lane_off = static_cast<uint32_t>(k_tok) * ts_bytes + k_byte;
+    const uint32_t v_lane_off = static_cast<uint32_t>(4 * kg) * ts_bytes + static_cast<uint32_t>(l16) * (2u * NBLK);
+    auto page_base = [&](const uint16_t* cache, int ph) -> const unsigned char* {
+      return uniform_ptr(reinterpret_cast<const unsigned char*>(cache + static_cast<int64_t>(ph) * p.page_stride + head_off));
+    };
+    // Small pages: byte address of token t (0..31, a per-lane value) of the tile whose page ids are in ids_cur.
+    typedef const __attribute__((address_space(1))) unsigned char* gbytes;
+    auto token_addr = [&](const uint16_t* cache, int t) -> gbytes {
+      const int id = __shfl(ids_cur, t >> (PS & 3), 64);
+      const int tokin = t & ((1 << (PS & 3)) - 1);
+      const int64_t el = static_cast<int64_t>(id) * p.page_stride + static_cast<int64_t>(tokin) * p.token_stride + head_off;
+      return (gbytes)cache + el * 2;
+    };
+    // K load (pg, kk): token l16 of page pg, head dims 32 kk + 8 kg .. + 7
+    auto issue_k = [&](int k, u32x4 (&kr)[2][KK]) {
+      if constexpr (PS != 4) {
 #pragma unroll
-      for (int pg = 0; pg < 2; ++pg) {
-        if constexpr (STREAM) {
+        for (int pg = 0; pg < 2; ++pg) {
+          if constexpr (STREAM) {
 #pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            const gbytes row = token_addr(p.k, 16 * pg + 8 * e + k_tok) + k_byte;
+            for (int e = 0; e < 2; ++e) {
+              const gbytes row = token_addr(p.k, 16 * pg + 8 * e + k_tok) + k_byte;
 #pragma unroll
-            for (int kk = e; kk < KK; kk += 2) kr[pg][kk] = gload_at<u32x4, STREAM>(row + (kk >> 1) * 128);
+              for (int kk = e; kk < KK; kk += 2) kr[pg][kk] = gload_at<u32x4, STREAM>(row + (kk >> 1) * 128);
+            }
+          } else {
+            const gbytes row = token_addr(p.k, 16 * pg + l16) + kg * 16;
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) kr[pg][kk] = gload_at<u32x4, STREAM>(row + kk * 64);
           }
-        } else {
-          const gbytes row = token_addr(p.k, 16 * pg + l16) + kg * 16;
-#pragma unroll
-          for (int kk = 0; kk < KK; ++kk) kr[pg][kk] = gload_at<u32x4, STREAM>(row + kk * 64);
         }
+        return;
       }
-      return;
-    }
-    if ((k & 31) == 0 && k > 0) load_pagevec(k);
-    const unsigned char* kb0 = page_base(p.k, __builtin_amdgcn_readlane(pagevec, k & 31));
-    const unsigned char* kb1 = page_base(p.k, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31)));
-#pragma unroll
-    for (int pg = 0; pg < 2; ++pg)
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk)
-        kr[pg][kk] = gload<u32x4, STREAM>((pg ? kb1 : kb0) + (STREAM ? (kk >> 1) * 128u + (kk & 1) * 8u * ts_bytes : kk * 64u), k_lane_off);
-  };
-  // V load e: token 4 kg + e % 4 of page e / 4, head dims NBLK l16 .. + NBLK - 1
-  auto issue_v = [&](int k, VReg (&vr)[8]) {
-    if constexpr (PS != 4) {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) vr[e] = gload_at<VReg, STREAM>(token_addr(p.v, 16 * (e >> 2) + 4 * kg + (e & 3)) + l16 * (2 * NBLK));
-      return;
-    }
-    const unsigned char* vb0 = page_base(p.v, __builtin_amdgcn_readlane(pagevec, k & 31));
-    const unsigned char* vb1 = page_base(p.v, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31)));
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      vr[e] = gload<VReg, STREAM>((e < 4 ? vb0 : vb1) + static_cast<uint32_t>(e & 3) * ts_bytes, v_lane_off);
-  };
-
-  // Loads of whole 128-byte lines bring two tokens' pieces to the wrong lanes: of loads 2 q and 2 q + 1 the first holds, in
-  // lanes l16 < 8, the first half of line q of token l16 and, in the others, the second half of token l16 - 8's; the second
-  // load the same of tokens l16 + 8 and l16.  Lanes 8 apart exchange them.
-  auto exchange_k = [&](u32x4 (&kr)[2][KK]) {
-#pragma unroll
-    for (int pg = 0; pg < 2; ++pg)
-#pragma unroll
-      for (int q = 0; q < KK / 2; ++q)
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          const int a = static_cast<int>(kr[pg][2 * q][w]), b = static_cast<int>(kr[pg][2 * q + 1][w]);
-          kr[pg][2 * q][w] = static_cast<unsigned>(__builtin_amdgcn_update_dpp(a, b, 0x128, 0xf, 0xc, false));       // row_ror:8
-          kr[pg][2 * q + 1][w] = static_cast<unsigned>(__builtin_amdgcn_update_dpp(b, a, 0x128, 0xf, 0x3, false));
-        }
-  };
-
-  u32x4 kr[2][KK];
-  VReg va[8], vb[8];
-  if constexpr (PS != 4) ids_pending = into_pool(ids_entry(1));     // (requested before tile 0's loads: it is back first)
-  if (tile_first < tile_end) {
-    issue_k(0, kr);
-    issue_v(0, va);
-  }
-  VEGAS_TL(kTlLoadsIssued);
-  VEGAS_TL(kTlQueries);
-
-  // ---- running state of lane (row n, kg): the row maximum (the same in the row's four lanes), this lane's share
-  //      of the row sum, and acc[blk][r] = O[n][NBLK (4 kg + r) + blk]
-  float m_run = -INFINITY, l_run = 0.f;
-  f32x4 acc[NBLK];
-#pragma unroll
-  for (int blk = 0; blk < NBLK; ++blk) acc[blk] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  auto step = [&](int k, VReg (&vcur)[8], VReg (&vnxt)[8], auto has_next_tag) {
-    constexpr bool has_next = decltype(has_next_tag)::value;
-    const int tok0 = (tile_first + k * NW) * kTile;
-    if constexpr (STREAM) exchange_k(kr);
-    f32x4 st[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};     // st[pg][r]: token 4 kg + r of page pg, row l16
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-      for (int pg = 0; pg < 2; ++pg)
-        st[pg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[pg][kk]),
-                                                         __builtin_bit_cast(bf16x8, qreg[kk]), st[pg], 0, 0, 0);
-    if (has_next) {
-      if constexpr (PS != 4) {               // the next tile's ids are here (requested a tile ago); ask for the ones after
-        ids_cur = ids_pending;
-        ids_pending = into_pool(ids_entry(k + 2));
-      }
-      issue_k(k + 1, kr);
-      issue_v(k + 1, vnxt);
-    }
-    const bool tail = tok0 + kTile > n;      // (chunks are whole tiles: only the sequence's end cuts into one)
-    if (tail) {
+      if ((k & 31) == 0 && k > 0) load_pagevec(k);
+      const unsigned char* kb0 = page_base(p.k, __builtin_amdgcn_readlane(pagevec, k & 31));
+      const unsigned char* kb1 = page_base(p.k, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31)));
 #pragma unroll
       for (int pg = 0; pg < 2; ++pg)
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-          if (tok0 + 16 * pg + 4 * kg + r >= n) st[pg][r] = -INFINITY;
-    }
-    float tmax = fmaxf(fmaxf(fmaxf(st[0][0], st[0][1]), fmaxf(st[0][2], st[0][3])),
-                       fmaxf(fmaxf(st[1][0], st[1][1]), fmaxf(st[1][2], st[1][3])));
-    tmax = quad_rows_max(tmax) * p.scale_log2e;           // scale > 0: max commutes with scaling
-    const float m_new = fmaxf(m_run, tmax);
-    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-    const float alpha = fast_exp2(m_run - m_use);
-    float pw[8];
+        for (int kk = 0; kk < KK; ++kk)
+          kr[pg][kk] = gload<u32x4, STREAM>((pg ? kb1 : kb0) + (STREAM ? (kk >> 1) * 128u + (kk & 1) * 8u * ts_bytes : kk * 64u), k_lane_off);
+    };
+    // V load e: token 4 kg + e % 4 of page e / 4, head dims NBLK l16 .. + NBLK - 1
+    auto issue_v = [&](int k, VReg (&vr)[8]) {
+      if constexpr (PS != 4) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) pw[i] = fast_exp2(__builtin_fmaf(st[i >> 2][i & 3], p.scale_log2e, -m_use));
-    // The row sum adds the weights as the second contraction sees them, i.e. rounded to bf16: numerator and
-    // denominator of Eq. 1 then carry the same rounding errors, which cancel where one key dominates (the output
-    // is a convex combination of V rows again) and do no harm elsewhere.
-    bf16x8 pb;
-    float pr[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      pb[i] = static_cast<__bf16>(pw[i]);
-      pr[i] = static_cast<float>(pb[i]);
-    }
-    l_run = l_run * alpha + ((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]));
-    const float m_before = m_run;
-    m_run = m_new;
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f && m_before != -INFINITY) != 0) {   // (no key seen yet: sums still zero)
-#pragma unroll
-      for (int blk = 0; blk < NBLK; ++blk) acc[blk] *= alpha;
-    }
-    if (tail) {                              // slots past the end may hold anything: feed zeros
+        for (int e = 0; e < 8; ++e) vr[e] = gload_at<VReg, STREAM>(token_addr(p.v, 16 * (e >> 2) + 4 * kg + (e & 3)) + l16 * (2 * NBLK));
+        return;
+      }
+      const unsigned char* vb0 = page_base(p.v, __builtin_amdgcn_readlane(pagevec, k & 31));
+      const unsigned char* vb1 = page_base(p.v, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31)));
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        if (tok0 + 16 * (e >> 2) + 4 * kg + (e & 3) >= n) vcur[e] = VReg{};
-    }
+        vr[e] = gload<VReg, STREAM>((e < 4 ? vb0 : vb1) + static_cast<uint32_t>(e & 3) * ts_bytes, v_lane_off);
+    };
+
+    // Loads of whole 128-byte lines bring two tokens' pieces to the wrong lanes: of loads 2 q and 2 q + 1 the first holds, in
+    // lanes l16 < 8, the first half of line q of token l16 and, in the others, the second half of token l16 - 8's; the second
+    // load the same of tokens l16 + 8 and l16.  Lanes 8 apart exchange them.
+    auto exchange_k = [&](u32x4 (&kr)[2][KK]) {
 #pragma unroll
-    for (int blk = 0; blk < NBLK; ++blk) {
-      u32x4 raw;
+      for (int pg = 0; pg < 2; ++pg)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)              // head dim blk of this lane's group, tokens 2 j and 2 j + 1 of its eight
-        raw[j] = __builtin_amdgcn_perm(vcur[2 * j + 1][blk >> 1], vcur[2 * j][blk >> 1],
-                                       (blk & 1) ? 0x07060302u : 0x05040100u);
-      acc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, raw), pb, acc[blk], 0, 0, 0);
+        for (int q = 0; q < KK / 2; ++q)
+#pragma unroll
+          for (int w = 0; w < 4; ++w) {
+            const int a = static_cast<int>(kr[pg][2 * q][w]), b = static_cast<int>(kr[pg][2 * q + 1][w]);
+            kr[pg][2 * q][w] = static_cast<unsigned>(__builtin_amdgcn_update_dpp(a, b, 0x128, 0xf, 0xc, false));       // row_ror:8
+            kr[pg][2 * q + 1][w] = static_cast<unsigned>(__builtin_amdgcn_update_dpp(b, a, 0x128, 0xf, 0x3, false));
+          }
+    };
+
+    u32x4 kr[2][KK];
+    VReg va[8], vb[8];
+    if constexpr (PS != 4) ids_pending = into_pool(ids_entry(1));     // (requested before tile 0's loads: it is back first)
+    if (tile_first < tile_end) {
+      issue_k(0, kr);
+      issue_v(0, va);
     }
+    VEGAS_TL(kTlLoadsIssued);
+    VEGAS_TL(kTlQueries);
+
+    // ---- running state of lane (row n, kg): the row maximum (the same in the row's four lanes), this lane's share
+    //      of the row sum, and acc[blk][r] = O[n][NBLK (4 kg + r) + blk]
+    float m_run = -INFINITY, l_run = 0.f;
+    f32x4 acc[NBLK];
+#pragma unroll
+    for (int blk = 0; blk < NBLK; ++blk) acc[blk] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    auto step = [&](int k, VReg (&vcur)[8], VReg (&vnxt)[8], auto has_next_tag) {
+      constexpr bool has_next = decltype(has_next_tag)::value;
+      const int tok0 = (tile_first + k * NW) * kTile;
+      if constexpr (STREAM) exchange_k(kr);
+      f32x4 st[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};     // st[pg][r]: token 4 kg + r of page pg, row l16
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+        for (int pg = 0; pg < 2; ++pg)
+          st[pg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[pg][kk]),
+                                                           __builtin_bit_cast(bf16x8, qreg[kk]), st[pg], 0, 0, 0);
+      if (has_next) {
+        if constexpr (PS != 4) {               // the next tile's ids are here (requested a tile ago); ask for the ones after
+          ids_cur = ids_pending;
+          ids_pending = into_pool(ids_entry(k + 2));
+        }
+        issue_k(k + 1, kr);
+        issue_v(k + 1, vnxt);
+      }
+      const bool tail = tok0 + kTile > n;      // (chunks are whole tiles: only the sequence's end cuts into one)
+      if (tail) {
+#pragma unroll
+        for (int pg = 0; pg < 2; ++pg)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (tok0 + 16 * pg + 4 * kg + r >= n) st[pg][r] = -INFINITY;
+      }
+      float tmax = fmaxf(fmaxf(fmaxf(st[0][0], st[0][1]), fmaxf(st[0][2], st[0][3])),
+                         fmaxf(fmaxf(st[1][0], st[1][1]), fmaxf(st[1][2], st[1][3])));
+      tmax = quad_rows_max(tmax) * p.scale_log2e;           // scale > 0: max commutes with scaling
+      const float m_new = fmaxf(m_run, tmax);
+      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+      const float alpha = fast_exp2(m_run - m_use);
+      float pw[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) pw[i] = fast_exp2(__builtin_fmaf(st[i >> 2][i & 3], p.scale_log2e, -m_use));
+      // The row sum adds the weights as the second contraction sees them, i.e. rounded to bf16: numerator and
+      // denominator of Eq. 1 then carry the same rounding errors, which cancel where one key dominates (the output
+      // is a convex combination of V rows again) and do no harm elsewhere.
+      bf16x8 pb;
+      float pr[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        pb[i] = static_cast<__bf16>(pw[i]);
+        pr[i] = static_cast<float>(pb[i]);
+      }
+      l_run = l_run * alpha + ((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]));
+      const float m_before = m_run;
+      m_run = m_new;
+      if (__builtin_amdgcn_ballot_w64(alpha != 1.0f && m_before != -INFINITY) != 0) {   // (no key seen yet: sums still zero)
+#pragma unroll
+        for (int blk = 0; blk < NBLK; ++blk) acc[blk] *= alpha;
+      }
+      if (tail) {                              // slots past the end may hold anything: feed zeros
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (tok0 + 16 * (e >> 2) + 4 * kg + (e & 3) >= n) vcur[e] = VReg{};
+      }
+#pragma unroll
+      for (int blk = 0; blk < NBLK; ++blk) {
+        u32x4 raw;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)              // head dim blk of this lane's group, tokens 2 j and 2 j + 1 of its eight
+          raw[j] = __builtin_amdgcn_perm(vcur[2 * j + 1][blk >> 1], vcur[2 * j][blk >> 1],
+                                         (blk & 1) ? 0x07060302u : 0x05040100u);
+        acc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, raw), pb, acc[blk], 0, 0, 0);
+      }
 #ifdef VEGAS_TIMELINE
-    if (tl_stamps[kTlFirstTile] == 0) VEGAS_TL(kTlFirstTile);
+      if (tl_stamps[kTlFirstTile] == 0) VEGAS_TL(kTlFirstTile);
 #endif
-  };
+    };
 
-  // ---- stream the chunk's tiles (the last one peeled: prefetches are unconditional, load-counter waits exact)
-  if (tile_first < tile_end) {
-    const int ntiles = (tile_end - tile_first + NW - 1) / NW;      // this wave's tiles
-    using yes = std::integral_constant<bool, true>;
-    using no = std::integral_constant<bool, false>;
-    int k = 0;
-    while (k + 2 < ntiles) {
-      step(k, va, vb, yes{});
-      step(k + 1, vb, va, yes{});
-      k += 2;
-    }
-    if (k + 1 < ntiles) {
-      step(k, va, vb, yes{});
-      step(k + 1, vb, va, no{});
-    } else {
-      step(k, va, vb, no{});
-    }
-  }
-
-  // ---- merge the waves: row maxima meet in LDS, every wave rescales and parks its rows as [wave][row][d], all
-  //      threads add the waves' copies and write the workgroup's partial (or the finished rows)
-  VEGAS_TL(kTlStreamed);
-  if (kg == 0) sm_m[wave * kDraftRows + l16] = m_run;
-  __syncthreads();
-  VEGAS_TL(kTlMerged);
-  {
-    float mw = -INFINITY;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) mw = fmaxf(mw, sm_m[w * kDraftRows + l16]);
-    const float m_fin = (mw == -INFINITY) ? 0.f : mw;
-    const float sc = fast_exp2(m_run - m_fin);
-    const float lsum = quad_rows_sum(l_run * sc);
-    if (kg == 0) sm_l[wave * kDraftRows + l16] = lsum;
-    if (l16 < Rl) {
-      float* dst = red + (wave * Rl + l16) * kRedPitch;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int d0 = NBLK * (4 * kg + r);
-        *reinterpret_cast<f32x4*>(dst + d0) = f32x4{acc[0][r] * sc, acc[1][r] * sc, acc[2][r] * sc, acc[3][r] * sc};
-        if constexpr (D == 128)
-          *reinterpret_cast<f32x4*>(dst + d0 + 4) = f32x4{acc[4][r] * sc, acc[5][r] * sc, acc[6][r] * sc, acc[7][r] * sc};
+    // ---- stream the chunk's tiles (the last one peeled: prefetches are unconditional, load-counter waits exact)
+    if (tile_first < tile_end) {
+      const int ntiles = (tile_end - tile_first + NW - 1) / NW;      // this wave's tiles
+      using yes = std::integral_constant<bool, true>;
+      using no = std::integral_constant<bool, false>;
+      int k = 0;
+      while (k + 2 < ntiles) {
+        step(k, va, vb, yes{});
+        step(k + 1, vb, va, yes{});
+        k += 2;
+      }
+      if (k + 1 < ntiles) {
+        step(k, va, vb, yes{});
+        step(k + 1, vb, va, no{});
+      } else {
+        step(k, va, vb, no{});
       }
     }
-  }
-  __syncthreads();
-  constexpr int V4 = D / 4;
-  constexpr int kSumTrips = (kDraftRows * V4 + NW * 64 - 1) / (NW * 64);
-  f32x4 sums[kSumTrips];
-  const int sum_trips = (Rl * V4 + NW * 64 - 1) / (NW * 64);       // (few rows: the later trips have nothing to do)
+
+    // ---- merge the waves: row maxima meet in LDS, every wave rescales and parks its rows as [wave][row][d], all
+    //      threads add the waves' copies and write the workgroup's partial (or the finished rows)
+    VEGAS_TL(kTlStreamed);
+    if (kg == 0) sm_m[wave * kDraftRows + l16] = m_run;
+    __syncthreads();
+    VEGAS_TL(kTlMerged);
+    {
+      float mw = -INFINITY;
 #pragma unroll
-  for (int it = 0; it < kSumTrips; ++it) {
-    if (it < sum_trips) {
-      const int e = min(tid + it * NW * 64, Rl * V4 - 1);
-      const float* src = red + (e / V4) * kRedPitch + 4 * (e % V4);
-      f32x4 acc4 = *reinterpret_cast<const f32x4*>(src);
+      for (int w = 0; w < NW; ++w) mw = fmaxf(mw, sm_m[w * kDraftRows + l16]);
+      const float m_fin = (mw == -INFINITY) ? 0.f : mw;
+      const float sc = fast_exp2(m_run - m_fin);
+      const float lsum = quad_rows_sum(l_run * sc);
+      if (kg == 0) sm_l[wave * kDraftRows + l16] = lsum;
+      if (l16 < Rl) {
+        float* dst = red + (wave * Rl + l16) * kRedPitch;
 #pragma unroll
-      for (int w = 1; w < NW; ++w) acc4 += *reinterpret_cast<const f32x4*>(src + w * Rl * kRedPitch);
-      sums[it] = acc4;
+        for (int r = 0; r < 4; ++r) {
+          const int d0 = NBLK * (4 * kg + r);
+          *reinterpret_cast<f32x4*>(dst + d0) = f32x4{acc[0][r] * sc, acc[1][r] * sc, acc[2][r] * sc, acc[3][r] * sc};
+          if constexpr (D == 128)
+            *reinterpret_cast<f32x4*>(dst + d0 + 4) = f32x4{acc[4][r] * sc, acc[5][r] * sc, acc[6][r] * sc, acc[7][r] * sc};
+        }
+      }
     }
-  }
-  if (p.out_direct != nullptr) {
-    // The only chunk of its (sequence, KV head): divide by the softmax denominator and write the bf16 rows (Eq. 1).
-    uint16_t* const rows = out_rows();
+    __syncthreads();
+    constexpr int V4 = D / 4;
+    constexpr int kSumTrips = (kDraftRows * V4 + NW * 64 - 1) / (NW * 64);
+    f32x4 sums[kSumTrips];
+    const int sum_trips = (Rl * V4 + NW * 64 - 1) / (NW * 64);       // (few rows: the later trips have nothing to do)
+#pragma unroll
+    for (int it = 0; it < kSumTrips; ++it) {
+      if (it < sum_trips) {
+        const int e = min(tid + it * NW * 64, Rl * V4 - 1);
+        const float* src = red + (e / V4) * kRedPitch + 4 * (e % V4);
+        f32x4 acc4 = *reinterpret_cast<const f32x4*>(src);
+#pragma unroll
+        for (int w = 1; w < NW; ++w) acc4 += *reinterpret_cast<const f32x4*>(src + w * Rl * kRedPitch);
+        sums[it] = acc4;
+      }
+    }
+    if (p.out_direct != nullptr) {
+      // The only chunk of its (sequence, KV head): divide by the softmax denominator and write the bf16 rows (Eq. 1).
+      uint16_t* const rows = out_rows();
+#pragma unroll
+      for (int it = 0; it < kSumTrips; ++it) {
+        const int e = tid + it * NW * 64;
+        if (e < Rl * V4) {
+          const int row = e / V4;
+          float lw = 0.f;
+#pragma unroll
+          for (int w = 0; w < NW; ++w) lw += sm_l[w * kDraftRows + row];
+          const float inv = lw > 0.f ? 1.0f / lw : 0.f;       // (a row with no visible key: zeros)
+          u32x2 packed;
+          packed[0] = static_cast<uint32_t>(float_to_bf16_bits(sums[it][0] * inv)) |
+                      (static_cast<uint32_t>(float_to_bf16_bits(sums[it][1] * inv)) << 16);
+          packed[1] = static_cast<uint32_t>(float_to_bf16_bits(sums[it][2] * inv)) |
+                      (static_cast<uint32_t>(float_to_bf16_bits(sums[it][3] * inv)) << 16);
+          *reinterpret_cast<u32x2*>(rows + 4 * e) = packed;
+        }
+      }
+      VEGAS_TL(kTlExit);
+      VEGAS_TL_FLUSH(p.timeline, NW);
+      return;
+    }
+    float* po = p.part_o + pbase * p.R * D;
 #pragma unroll
     for (int it = 0; it < kSumTrips; ++it) {
       const int e = tid + it * NW * 64;
-      if (e < Rl * V4) {
-        const int row = e / V4;
-        float lw = 0.f;
+      if (e < Rl * V4) *reinterpret_cast<f32x4*>(po + 4 * e) = sums[it];
+    }
+    if (tid < Rl) {
+      float mw = -INFINITY, lw = 0.f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) lw += sm_l[w * kDraftRows + row];
-        const float inv = lw > 0.f ? 1.0f / lw : 0.f;       // (a row with no visible key: zeros)
-        u32x2 packed;
-        packed[0] = static_cast<uint32_t>(float_to_bf16_bits(sums[it][0] * inv)) |
-                    (static_cast<uint32_t>(float_to_bf16_bits(sums[it][1] * inv)) << 16);
-        packed[1] = static_cast<uint32_t>(float_to_bf16_bits(sums[it][2] * inv)) |
-                    (static_cast<uint32_t>(float_to_bf16_bits(sums[it][3] * inv)) << 16);
-        *reinterpret_cast<u32x2*>(rows + 4 * e) = packed;
+      for (int w = 0; w < NW; ++w) {
+        mw = fmaxf(mw, sm_m[w * kDraftRows + tid]);
+        lw += sm_l[w * kDraftRows + tid];
       }
+      p.part_ml[pbase * p.R + tid] = make_float2(mw, lw);
     }
     VEGAS_TL(kTlExit);
     VEGAS_TL_FLUSH(p.timeline, NW);
-    return;
-  }
-  float* po = p.part_o + pbase * p.R * D;
-#pragma unroll
-  for (int it = 0; it < kSumTrips; ++it) {
-    const int e = tid + it * NW * 64;
-    if (e < Rl * V4) *reinterpret_cast<f32x4*>(po + 4 * e) = sums[it];
-  }
-  if (tid < Rl) {
-    float mw = -INFINITY, lw = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      mw = fmaxf(mw, sm_m[w * kDraftRows + tid]);
-      lw += sm_l[w * kDraftRows + tid];
+  };
+  if constexpr (CHOOSE) {
+    if (past_cache(wave_sum(lane_sixteens(lane_len, p.lens, p.batch, p.max_tokens, lane)), p.Hkv, D)) {
+      stream_chunk(std::true_type{});
+      return;
     }
-    p.part_ml[pbase * p.R + tid] = make_float2(mw, lw);
   }
-  VEGAS_TL(kTlExit);
-  VEGAS_TL_FLUSH(p.timeline, NW);
+  stream_chunk(std::false_type{});
 }
 
 }  // namespace vegas

@@ -34,16 +34,6 @@ inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
   return 0;
 }
 
-// Draft calls of up to kDraftRows rows: are the selected K and V (bound: sequences x KV heads x longest selection) more than the
-// 256-MiB last-level cache keeps until the next draft step reads the same pages?  Then they are read past it.  us, 8 draft calls
-// of the same selection in turn, through the cache / past it: 104 MB 18.8 / 22.7; 136 MB 28.4 / 33.0; 268 MB 45.5 / 49.4 (head
-// dimension 64 51.9 / 56.7); 302 MB 53.3 / 55.8; 336 MB 60.9 / 60.9, with 16-token pages 58.0 / 59.3; 369 MB 66.6 / 64.4;
-// 393 MB 74.1 / 68.1; 403 MB 76.6 / 71.4; 537 MB 106.7 / 95.0 (head dimension 64 117.7 / 106.2).  (A call on a selection that
-// nothing has read before gains in any case, 537 MB 179 -> 142.)
-inline bool streamed_selection(int batch, int kv_heads, int max_len, int head_dim) {
-  return static_cast<int64_t>(batch) * kv_heads * max_len * head_dim * 4 >= (static_cast<int64_t>(352) << 20);
-}
-
 // Verification with a local mask: does one workgroup per column (sequence x KV head x row block) stream the whole band
 // (no row sees more than window + queries tokens, nor than the longest sequence has) and write the output rows, or is the context cut into chunks
 // (`chunk` tokens, of which the band touches a few) and merged?  Cutting only helps where the chunks are shorter than the

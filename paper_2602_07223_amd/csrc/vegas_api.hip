@@ -313,10 +313,11 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
     if (pl.R <= kDraftRows && sp.G == 1 && pl.NB == 1) {
       const dim3 dblock(kDraftWaves * 64);
       const size_t dlds = draft16_lds_bytes(pl.R, D);
-      const bool stream = streamed_selection(batch, sp.Hkv, sp.max_tokens, D);
+      // (the bound first: lengths that cannot get there are not looked at)
+      const bool choose = past_cache(static_cast<uint64_t>(batch) * ((static_cast<uint64_t>(sp.max_tokens) + 15) / 16), sp.Hkv, D);
       auto launch = [&](auto ps) {
         constexpr int PS = decltype(ps)::value;
-        if (stream) return launch_one(attn_draft16_kernel<D, PS, true>, grid, dblock, dlds, st, sp);
+        if (choose) return launch_one(attn_draft16_kernel<D, PS, true>, grid, dblock, dlds, st, sp);
         return launch_one(attn_draft16_kernel<D, PS, false>, grid, dblock, dlds, st, sp);
       };
       switch (page_size) {                              // (draft calls may walk a table of smaller pages)

@@ -1,7 +1,7 @@
-"""Draft calls whose bound on the selected K and V exceeds the last-level cache (plan_rules.hpp, streamed_selection): the 16-row
-kernel then loads K in whole 128-byte lines past that cache and exchanges pieces between lanes.  The bound is the call's, not
-the selection's, so short selections under a large bound reach the kernel: ends inside a page, a tile and on one, every page
-size, both head dimensions, against the oracle."""
+"""Draft calls whose bound on the selected K and V exceeds the last-level cache: the 16-row kernel that chooses by the lengths
+(attn_draft.hpp, past_cache).  Short selections under a large bound: ends inside a page, a tile and on one, every page size,
+both head dimensions, chunk lengths from the planner and of one tile per wave, against the oracle.  (Selections that are read past
+the cache: test_gpu_draft_lengths.py.)"""
 import numpy as np
 import pytest
 import torch
