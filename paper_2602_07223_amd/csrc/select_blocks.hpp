@@ -36,6 +36,16 @@ struct LastKey {
   uint32_t base, span, need;
 };
 
+constexpr uint32_t kNoDigit = 0xFFFFFFFFu;      // of a key that is not counted
+constexpr int kOften = 4;                       // digits that a crowded wave counts by itself
+// Do so many lanes have the digit of the lane beside them?  (The chance that two keys share a digit, at the price of one
+// comparison.)
+__device__ __forceinline__ bool crowded(uint32_t digit, int lanes) {
+  const uint32_t beside = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int>(kNoDigit), static_cast<int>(digit),
+                                                                            0x111, 0xf, 0xf, false));   // row_shr:1
+  return __popcll(__builtin_amdgcn_ballot_w64(digit == beside && digit != kNoDigit)) >= lanes;
+}
+
 // Radix select: where the `take` largest of the workgroup's keys end.  Keys below `full` of every thread hold positions, of
 // those from there to `live` valid(u) says which; a key without a position is 0 and its place lies behind all positions.  0 <
 // take < positions.  Followed by no barrier; the first thing it does is not ordered behind reads of `sh` either.
@@ -43,8 +53,16 @@ struct LastKey {
 // (sign, most of the exponent) costs no pass, the counts spread over the bins so that one shared histogram and plain adds
 // do, and two passes as a rule, three at most, find the end.  (With four passes over 8 fixed bits, a histogram per wave and
 // one add for the lanes that share a digit, an iteration took, us: 2048 pages 70.2 instead of 69.7, 4096 pages of each of 16
-// sequences 590.6 instead of 587.6, 8192 pages 161.0 instead of 158.0.)  What bounds it is latency, a barrier and one wave's walk through the counts per pass, and
-// with 16 and more keys a thread the instructions issued per key.
+// sequences 590.6 instead of 587.6, 8192 pages 161.0 instead of 158.0.)  What bounds it is latency, a barrier and one wave's walk
+// through the counts per pass, and with 16 and more keys a thread the instructions issued per key.
+// Scores need not spread: adds of many lanes to one bin wait for each other.  A wave whose first keys meet in few bins counts
+// the digits of up to four of them in registers and adds the rest; and where a bin holds an eighth of the keys, its own
+// smallest and largest set the next digits, instead of passes that tell nothing apart.  us per call, four passes of 8 bits (five
+// launches for tokens) / without these two / with them, 8192 pages: normally distributed 10.5 / 7.8 / 8.1, four values 16.3 /
+// 13.2 / 8.8, fifteen in sixteen 0 8.7 / 12.6 / 8.4, a twentieth -infinity beside scores within a percent 12.9 / 14.7 / 11.1, one
+// far outlier 13.5 / 22.1 / 11.5; 32768 tokens: 20.8 / 16.7 / 16.9, 20.7 / 39.0 / 20.4, 20.8 / 38.0 / 18.4, 20.8 / 42.8 / 22.8, 20.7 / 73.4 /
+// 26.9; 2048 pages, of which a thread has two, which are not looked at for this: 5.8 / 6.0 / 6.3, 8.3 / 7.5 / 6.7, 5.0 / 6.5 / 6.5, 7.7 /
+// 7.9 / 9.2, 8.0 / 9.6 / 8.4.
 template <int N, typename Valid>
 __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int full, int live, Valid valid, uint32_t take,
                                                  RegisterSelectShared& sh) {
@@ -52,40 +70,74 @@ __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int f
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   for (int i = tid; i < 3 * 2048 / 4; i += kSelectThreads) reinterpret_cast<u32x4*>(sh.hist)[i] = u32x4{0u, 0u, 0u, 0u};
-  uint32_t hi = 0u, inv_lo = 0u;                                    // (the smallest as the largest complement)
-#pragma unroll
-  for (int u = 0; u < N; ++u) {
-    if (u >= live) continue;
-    hi = max(hi, key[u]);
-    if (u < full || valid(u)) inv_lo = max(inv_lo, ~key[u]);
-  }
-  hi = wave_max(hi);
-  inv_lo = wave_max(inv_lo);
-  if (lane == 0) {
-    sh.high[wave] = hi;
-    sh.low[wave] = inv_lo;
-  }
-  __syncthreads();
-  hi = __builtin_amdgcn_readfirstlane(wave_max(sh.high[lane & (kWaves - 1)]));
   LastKey r;
-  r.base = ~__builtin_amdgcn_readfirstlane(wave_max(sh.low[lane & (kWaves - 1)]));
-  r.span = hi - r.base;
   r.need = take;
+  auto set_range = [&](uint32_t hi, uint32_t inv_lo) {              // (the smallest as the largest complement)
+    hi = wave_max(hi);
+    inv_lo = wave_max(inv_lo);
+    if (lane == 0) {
+      sh.high[wave] = hi;
+      sh.low[wave] = inv_lo;
+    }
+    __syncthreads();
+    hi = __builtin_amdgcn_readfirstlane(wave_max(sh.high[lane & (kWaves - 1)]));
+    r.base = ~__builtin_amdgcn_readfirstlane(wave_max(sh.low[lane & (kWaves - 1)]));
+    r.span = hi - r.base;
+  };
+  {
+    uint32_t hi = 0u, inv_lo = 0u;
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      if (u >= live) continue;
+      hi = max(hi, key[u]);
+      if (u < full || valid(u)) inv_lo = max(inv_lo, ~key[u]);
+    }
+    set_range(hi, inv_lo);
+  }
+  uint32_t keys = static_cast<uint32_t>(live) * kSelectThreads;     // in the range
   // (Keys without a position lie outside every range unless it starts at 0, the key of NaNs, and are the last there: a bin is
   //  then never taken whole, and of equal keys the first positions are.)
   int shift = max(32 - __builtin_clz(r.span | 1u) - 11, 0);
 #pragma unroll
   for (int pass = 0; pass < 3; ++pass) {
     if (r.span == 0u) break;                                        // all keys are equal: nothing to find
-    // (Adds of many lanes to one bin wait for each other: scores of four values 2048 pages 7.6 us, 8192 13.4, 32768 tokens 39.  One
-    //  add for all lanes that share the first lane's digit, where a wave's first keys ask for it, takes a row with one far
-    //  outlier from 22.3 us to 11.5 at 8192 pages and from 74 to 29 at 32768 tokens, and costs every other call 0.3 to 0.9.)
     uint32_t* const h = sh.hist[pass];
+    auto digit = [&](int u) { return (key[u] - r.base) >> shift; };
+    auto counted = [&](int u) { return (pass == 0 && u < full) || key[u] - r.base <= r.span; };
+    const uint32_t first = counted(0) ? digit(0) : kNoDigit;
+    // (later passes count a fraction of the keys, so that neighbours seldom are both among them)
+    if (__builtin_expect(live < 4 || !crowded(first, pass == 0 ? 8 : 1), 1)) {
 #pragma unroll
-    for (int u = 0; u < N; ++u) {
-      if (u >= live) continue;
-      const uint32_t d = key[u] - r.base;
-      if ((pass == 0 && u < full) || d <= r.span) atomicAdd(&h[d >> shift], 1u);
+      for (int u = 0; u < N; ++u) {
+        if (u >= live) continue;
+        if (counted(u)) atomicAdd(&h[digit(u)], 1u);
+      }
+    } else {
+      uint32_t often[kOften], n[kOften];
+      uint64_t left = __builtin_amdgcn_ballot_w64(first != kNoDigit);
+#pragma unroll
+      for (int c = 0; c < kOften; ++c) {
+        n[c] = 0u;
+        often[c] = left ? __builtin_amdgcn_readlane(first, __builtin_ctzll(left)) : kNoDigit - 1u;
+        left &= ~__builtin_amdgcn_ballot_w64(first == often[c]);
+      }
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        if (u >= live) continue;
+        const uint32_t d = counted(u) ? digit(u) : kNoDigit;
+        bool seldom = d != kNoDigit;
+#pragma unroll
+        for (int c = 0; c < kOften; ++c) {
+          n[c] += d == often[c] ? 1u : 0u;
+          seldom = seldom && d != often[c];
+        }
+        if (seldom) atomicAdd(&h[d], 1u);
+      }
+#pragma unroll
+      for (int c = 0; c < kOften; ++c) {
+        const uint32_t of_wave = wave_sum(n[c]);
+        if (lane == 0 && of_wave != 0u) atomicAdd(&h[often[c]], of_wave);
+      }
     }
     __syncthreads();
     if (wave == 0) {
@@ -115,8 +167,21 @@ __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int f
     r.base += __builtin_amdgcn_readfirstlane(sh.bin) << shift;
     r.need = __builtin_amdgcn_readfirstlane(sh.need);
     r.span = (1u << shift) - 1u;
-    if (shift == 0 || __builtin_amdgcn_readfirstlane(sh.count) == r.need) break;   // equal keys, or the whole bin is taken
+    const uint32_t count = __builtin_amdgcn_readfirstlane(sh.count);
+    if (shift == 0 || count == r.need) break;                       // equal keys, or the whole bin is taken
     shift = max(shift - 11, 0);
+    if (__builtin_expect(8u * count >= keys, 0)) {
+      uint32_t hi = 0u, inv_lo = 0u;
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        if (u >= live || key[u] - r.base > r.span) continue;
+        hi = max(hi, key[u]);
+        inv_lo = max(inv_lo, ~key[u]);
+      }
+      set_range(hi, inv_lo);
+      shift = max(32 - __builtin_clz(r.span | 1u) - 11, 0);
+    }
+    keys = count;
   }
   return r;
 }
