@@ -160,6 +160,7 @@ __global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_H
 // Loads are ordered so that a workgroup's dependent memory round trips are as few as possible: the
 // kernel runs for a handful of microseconds and every trip is a sizeable part of that.
 constexpr int kFinPlanned = -1;
+constexpr int kFinPlannedSmall = -2;   // the same in a call of few rows: merged a head dim per thread, pages scored row by row
 constexpr int kFinPre = 8;       // page log-sum-exps a score thread keeps in registers: 4 * kFinPre rows
 
 // Merge under balanced chunking: 1024 / D consecutive rows of the Hkv R rows per workgroup, a thread has four head dims of
@@ -231,6 +232,7 @@ __device__ __forceinline__ void merge_planned_rows(const FinalizeParams& p, cons
 template <int MAXS, int METRIC = 0>
 __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizeParams p) {
   extern __shared__ __attribute__((aligned(16))) float smf[];              // role A (general path): [256 / D][D] weights + [256 / D][4]; role B: [Hkv*R] + [8][32] + [Hkv*R][8] pairs
+  constexpr bool kPlanned = MAXS < 0;
   const int b = blockIdx.y;
   const int tid = threadIdx.x;
   const int HR = p.Hkv * p.R;
@@ -378,9 +380,9 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
   // bound by bytes at such batch sizes); otherwise every slot up to the host's bound is requested at once.
   // (Six units per batch hold the whole table of one sequence of 32 chunks and 160 rows in flight; a planned
   // sequence has few chunks, and there it pays to have more workgroups on a CU than its registers would leave room for.)
-  constexpr int kUnits = MAXS == kFinPlanned ? 2 : 6;
+  constexpr int kUnits = kPlanned ? 2 : 6;
   int ns_live = p.nsplit;
-  if constexpr (MAXS == kFinPlanned) {
+  if constexpr (kPlanned) {
     int n0 = p.lens[b];
     n0 = n0 < 0 ? 0 : (n0 > p.max_tokens ? p.max_tokens : n0);
     ns_live = column_chunks(cs, n0).ns;
@@ -389,7 +391,7 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
       return;
     }
   }
-  const int lg = MAXS != kFinPlanned ? 3 : (ns_live <= 4 ? 0 : (ns_live <= 8 ? 1 : (ns_live <= 16 ? 2 : 3)));   // log2 of the parts
+  const int lg = !kPlanned ? 3 : (ns_live <= 4 ? 0 : (ns_live <= 8 ? 1 : (ns_live <= 16 ? 2 : 3)));   // log2 of the parts
   // (Only the collected rows' pairs: two-row collection of 48 rows and 32K tokens, verification 38.0 -> 34.0 us.)
   const int Rc = p.Rc;                        // collected rows per KV head: the only ones whose page values were written
   const int parts = 1 << lg, units = (p.Hkv * Rc) << lg;
@@ -553,8 +555,15 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
                 if (rl[r + q] != -INFINITY) sc += fast_exp2(x[q] - rl[r + q]);
             }
           } else {
-            for (int r = 0; r < Rc; ++r)
-              if (rl[r] != -INFINITY) sc += fast_exp2(pl[r] - rl[r]);
+            // (Eight requests at a time: one by one a page's rows are as many round trips, 77 rows 48 us for the kernel.)
+            for (int r = 0; r < Rc; r += 8) {
+              float x[8];
+#pragma unroll
+              for (int e = 0; e < 8; ++e) x[e] = pl[min(r + e, Rc - 1)];
+#pragma unroll
+              for (int e = 0; e < 8; ++e)
+                if (r + e < Rc && rl[r + e] != -INFINITY) sc += fast_exp2(x[e] - rl[r + e]);
+            }
           }
         }
       }

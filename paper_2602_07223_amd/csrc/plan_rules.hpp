@@ -132,6 +132,16 @@ inline BatchPlan batch_plan(int num_cu, int64_t per_head, int batch, int max_len
   return p;
 }
 
+// Merge and page scores of a planned batch (attn_finalize.hpp): does one head dim per thread leave fewer than four workgroups per
+// compute unit?  Then nothing waits for a workgroup to end, and that form, which requests all of a row's chunks at once, is
+// the faster one.  us per verification, one head dim and page by page / four and by quads, by workgroups of the former, 20 rows:
+// 160 12.8 / 13.3 (token sums 13.5 / 14.4), 320 13.8 / 14.1, 480 16.3 / 16.5, 960 19.2 / 19.4, 1280 21.1 / 20.9, 1920 25.4 / 24.4;
+// 40 rows: 320 17.3 / 17.6, 960 21.9 / 21.9, 1920 25.1 / 24.3, 2560 27.8 / 25.9; head dimension 64: 160 11.7 / 12.1, 960 20.4 / 20.6,
+// 1920 35.7 / 34.7; one KV head, 80 12.1 / 13.3.
+inline bool planned_merge_is_small(int batch, int rows, int head_dim) {
+  return static_cast<int64_t>(batch) * rows * head_dim < 1024 * 256;
+}
+
 // Workgroups go round the 8 XCDs, on each round its 4 shader engines, so every 32nd starts on the same engine: of the
 // consecutive ones of a head, whose grid has `per_slot` workgroups (KV heads x row blocks) between them, so many start on as
 // many engines.

@@ -519,6 +519,7 @@ int for_each_lds_kernel(F f) {
   one(verify_finalize_kernel<16, 1>); one(verify_finalize_kernel<32, 1>);
   one(verify_finalize_kernel<64, 1>); one(verify_finalize_kernel<0, 1>);
   one(verify_finalize_kernel<kFinPlanned, 0>); one(verify_finalize_kernel<kFinPlanned, 1>);
+  one(verify_finalize_kernel<kFinPlannedSmall, 0>); one(verify_finalize_kernel<kFinPlannedSmall, 1>);
   one(select_blocks_kernel);
   return rc;
 }
@@ -609,7 +610,8 @@ static int verify_impl(const vegas_desc* desc, const void* q, const void* k_cach
   fp.D = desc->head_dim;
   fp.plan = sp.plan;
   fp.slots_total = sp.slots_total;
-  const int rows_per_wg = (pl.balanced ? 1024 : 256) / fp.D;   // merge workgroups: 256 threads, D per row, or D / 4
+  const bool small = planned_merge_is_small(desc->batch, sp.Hkv * pl.R, fp.D);
+  const int rows_per_wg = (pl.balanced && !small ? 1024 : 256) / fp.D;   // merge workgroups: 256 threads, D per row, or D / 4
   fp.nA = (sp.Hkv * pl.R + rows_per_wg - 1) / rows_per_wg;
   const int nrows = (desc->collect_rows == VEGAS_COLLECT_ALL_ROWS) ? desc->num_queries
                                                                    : (desc->num_queries > 1 ? 2 : 1);
@@ -635,13 +637,15 @@ static int verify_impl(const vegas_desc* desc, const void* q, const void* k_cach
     return VEGAS_OK;
   };
   if (logits) {
-    if (pl.balanced) rc = launch_finalize(verify_finalize_kernel<kFinPlanned, 1>);
+    if (pl.balanced && small) rc = launch_finalize(verify_finalize_kernel<kFinPlannedSmall, 1>);
+    else if (pl.balanced) rc = launch_finalize(verify_finalize_kernel<kFinPlanned, 1>);
     else if (pl.nsplit <= 16) rc = launch_finalize(verify_finalize_kernel<16, 1>);
     else if (pl.nsplit <= 32) rc = launch_finalize(verify_finalize_kernel<32, 1>);
     else if (pl.nsplit <= 64) rc = launch_finalize(verify_finalize_kernel<64, 1>);
     else rc = launch_finalize(verify_finalize_kernel<0, 1>);
   } else {
-    if (pl.balanced) rc = launch_finalize(verify_finalize_kernel<kFinPlanned>);
+    if (pl.balanced && small) rc = launch_finalize(verify_finalize_kernel<kFinPlannedSmall>);
+    else if (pl.balanced) rc = launch_finalize(verify_finalize_kernel<kFinPlanned>);
     else if (pl.nsplit <= 16) rc = launch_finalize(verify_finalize_kernel<16>);
     else if (pl.nsplit <= 32) rc = launch_finalize(verify_finalize_kernel<32>);
     else if (pl.nsplit <= 64) rc = launch_finalize(verify_finalize_kernel<64>);
