@@ -95,6 +95,20 @@ inline int unplanned_pair_chunk(int rows, int max_len) {
 // Units of streaming that beginning one more piece costs a compute unit: 0, 1, 2, 3 of them, verification with collection, us:
 // 16 sequences of 4000..16000 tokens, 20 rows 132 / 124 / 131 / 123; 8 of 1001..20011 75.4 / 81.5 / 70.6 / 70.3.
 constexpr uint32_t kShareCost = 3;
+// Units that cutting a batch into shares has to win at least (wants_shares), with 32-row and with 64-row workgroups.
+constexpr int kShareMargin = 2, kPairShareMargin = 4;
+
+// May the lengths of a batch be such that it is cut into shares (wants_shares), if none is longer than `most` units?  With C the
+// longest equal chunk of a plan for J workgroups, chunks of C - 1 take more than J, so that the sequences have at least
+// (J + 1) (C - 1) - batch (C - 2) units, and C is at most ceil(most / (ceil((J + 1) / batch) - 1)); C >= S + margin then asks for
+// C (batch - 1) >= J (margin - 1) - 4 + 5 batch (kShareCost is 3).  Fewer sequences than `batch` ask for a longer C.  (Slots for
+// shares that cannot be: 3 sequences of 900..1500 tokens, 20 rows 15.1 us instead of 13.3, 6 of them 16.5 / 14.9; with a bound of
+// 32768 they can be for all the host knows, and 14.5 and 16.2 remain.)
+inline bool shares_possible(int J, int batch, int64_t most, int margin) {
+  const int64_t per = (static_cast<int64_t>(J) + batch) / batch;                     // ceil((J + 1) / batch)
+  const int64_t C = per > 1 ? (most + per - 2) / (per - 1) : most;
+  return batch >= 2 && C * (batch - 1) >= static_cast<int64_t>(J) * (margin - 1) - 4 + 5 * static_cast<int64_t>(batch);
+}
 
 // A batch whose chunk lengths are computed on the GPU (balanced_slot, vegas_common.hpp): the numbers that the plan works with,
 // per KV head (and row block), and what of them a launch holds.  units: of kTile tokens per wave.
@@ -126,7 +140,7 @@ inline BatchPlan batch_plan(int num_cu, int64_t per_head, int batch, int max_len
   // shares one each and one more where a sequence ends inside a share (there are at most as many sequences as shares)
   int64_t js = p.J2 > batch ? p.J2 : batch;
   const int64_t shared = p.JR + (batch < p.JR ? batch : p.JR) - 1;
-  if (shared > js) js = shared;
+  if (shared > js && shares_possible(p.JR, batch, most_units, pair ? kPairShareMargin : kShareMargin)) js = shared;
   if (batch * capped > js) js = batch * capped;
   p.JS = static_cast<int>(js);
   return p;

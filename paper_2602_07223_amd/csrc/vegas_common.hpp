@@ -412,12 +412,12 @@ __host__ __device__ __forceinline__ bool wants_second_wave(uint32_t total, uint3
 __host__ __device__ __forceinline__ bool wants_shares(uint32_t priced, uint32_t lives, uint32_t J, uint32_t C, uint32_t margin) {
   return lives <= J && 10u * J * C > 11u * priced + 8u * lives && C >= (priced + J - 1u) / J + margin;
 }
-// share_wgs: workgroups per KV head that run at a time (J of the shares); share_margin: for wants_shares; second_cost: for
-// wants_second_wave.
+// share_wgs: workgroups per KV head that run at a time (J of the shares); slots: workgroups there are; share_margin: for
+// wants_shares; second_cost: for wants_second_wave.
 template <typename Wave = GpuWave>
 __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B, int max_tokens, int j1, int j2, int share_wgs,
-                                                               int share_group, int share_margin, int second_cost, int cap_units,
-                                                               int unit, int j, int2* plan_out) {
+                                                               int share_group, int slots, int share_margin, int second_cost,
+                                                               int cap_units, int unit, int j, int2* plan_out) {
   const int lane = Wave::lane();
   uint32_t n = 0u;
   if (lane < B) {
@@ -436,7 +436,8 @@ __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* le
   const uint32_t J = share_wgs, lives = __builtin_popcountll(live);
   uint32_t C = balanced_chunk_units<Wave>(nu, total, longest, J);
   const uint32_t priced = total + kShareCost * (lives - 1u), S = (priced + J - 1u) / J;
-  if (S <= static_cast<uint32_t>(cap_units) && wants_shares(priced, lives, J, C, static_cast<uint32_t>(share_margin))) {
+  if (S <= static_cast<uint32_t>(cap_units) && J + lives <= static_cast<uint32_t>(slots) + 1u &&
+      wants_shares(priced, lives, J, C, static_cast<uint32_t>(share_margin))) {
     const uint32_t rank = __builtin_popcountll(live & ((1ull << lane) - 1ull));
     const uint32_t base = Wave::prefix_sum(nu) - nu + kShareCost * rank;       // where the sequence's first token lies
     const uint32_t q = base / S, count = nu > 0u ? (base + nu - 1u) / S - q + 1u : 0u;

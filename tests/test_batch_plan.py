@@ -70,8 +70,8 @@ static char stack[64][1 << 16];
 static void body() {
   const int lane = Lanes::cur;
   const BatchPlan& p = call.bp;
-  call.out[lane] = balanced_slot<Lanes>(call.lens, call.batch, call.max_len, p.J, p.J2, p.JR, call.group, call.margin,
-                                        call.second, p.cap_units, 128, call.slot, call.plan);
+  call.out[lane] = balanced_slot<Lanes>(call.lens, call.batch, call.max_len, p.J, p.J2, p.JR, call.group, p.JS,
+                                        call.margin, call.second, p.cap_units, 128, call.slot, call.plan);
   Lanes::done[lane] = true;
   _longjmp(Lanes::back, 1);
 }
@@ -124,7 +124,7 @@ int main() {             // lines of: KV heads, head dimension, rows, collection
     call.batch = batch;
     call.max_len = max_len;
     call.second = pair ? pair_second_cost(D, collect) : 2;
-    call.margin = pair ? 4 : 2;
+    call.margin = pair ? kPairShareMargin : kShareMargin;
     call.group = share_group(heads * blocks);
     call.bp = batch_plan(256, heads * blocks, batch, max_len, 128, cap / 128, pair, two_per_cu, collect != 0);
     call.plan = plan.data();
@@ -200,6 +200,18 @@ def check(call, d):
         assert last == ns - 1, (call, b)
 
 
+def wanted(c, d):
+    """Would the lengths be cut into shares (wants_shares), had the call the slots?"""
+    nu = [-(-n // UNIT) for n in c[5]]
+    live, J = sum(1 for x in nu if x), d["JR"]
+    if not live:
+        return False
+    longest = next(x for x in range(1, max(nu) + 1) if x == max(nu) or sum(-(-u // x) for u in nu) <= J)
+    priced, margin = sum(nu) + 3 * (live - 1), 4 if c[2] + (2 if c[3] == 2 else 0) > 32 else 2
+    S = -(-priced // J)
+    return S <= d["cap"] and live <= J and 10 * J * longest > 11 * priced + 8 * live and longest >= S + margin
+
+
 def load(d, begin=3):
     """The longest a compute unit is busy over the mean, in units of 128 tokens, with `begin` of them for every piece."""
     free = [0] * d["JR"]
@@ -240,6 +252,7 @@ def test_every_plan_covers_every_sequence_once(tmp_path_factory):
     seen = set()
     for c, d in zip(calls, plans(program(tmp_path_factory), calls)):
         check(c, d)
+        assert d["shares"] == wanted(c, d), c
         if d["shares"]:
             seen.add((d["group"], d["JR"] > d["J"], d["J"] % d["group"] != 0))
     # shares were met with every length of the reversed groups, with two workgroups per compute unit, and where the last group of
@@ -263,3 +276,23 @@ def test_batches_beyond_the_parking_lds_are_spread_evenly(tmp_path_factory):
         check(c, d)
         assert sum(-(-n // UNIT) for n in c[5]) > d["J"] * d["cap"] * 0.9 and not d["shares"], c[:4]
         assert load(d) < 1.2, (c[:4], load(d), len(d["pieces"]))
+
+
+def test_no_slots_for_shares_that_cannot_be(tmp_path_factory):
+    """A workgroup that finds nothing to do waits for a compute unit all the same: where the bound on the lengths rules shares
+    out, a call has one per compute unit; where they are possible they are found, down to the shortest such bound."""
+    calls = [(8, 128, 20, 1, max(lens), lens) for lens in
+             (spread(3, 900, 1500), spread(4, 300, 3000), spread(6, 900, 1500), spread(2, 1000, 10000), spread(16, 400, 500))]
+    for c, d in zip(calls, plans(program(tmp_path_factory), calls)):
+        assert d["JS"] == d["J"] == 32, c
+    rng = random.Random(7)
+    calls = []
+    for _ in range(1200):                        # few sequences of few units, lengths of every shape
+        n, most = rng.randint(2, 12), rng.choice([3, 8, 15, 30, 60, 130])
+        lens = [rng.choice([most, rng.randint(1, most), rng.randint(1, most), 1]) * UNIT for _ in range(n)]
+        calls.append((rng.choice([8, 16, 32, 64]), 128, rng.choice([20, 40]), rng.choice([0, 1]), max(lens), lens))
+    answers = plans(program(tmp_path_factory), calls)
+    for c, d in zip(calls, answers):
+        check(c, d)
+        assert d["shares"] == wanted(c, d), c
+    assert sum(d["shares"] for d in answers) > 50
