@@ -95,7 +95,11 @@ inline int unplanned_pair_chunk(int rows, int max_len) {
 // Units of streaming that beginning one more piece costs a compute unit: 0, 1, 2, 3 of them, verification with collection, us:
 // 16 sequences of 4000..16000 tokens, 20 rows 132 / 124 / 131 / 123; 8 of 1001..20011 75.4 / 81.5 / 70.6 / 70.3.
 constexpr uint32_t kShareCost = 3;
-// Units that cutting a batch into shares has to win at least (wants_shares), with 32-row and with 64-row workgroups.
+// Units that cutting a batch into shares has to win at least (wants_shares), with 32-row and with 64-row workgroups.  Not where two
+// 64-row workgroups fit a compute unit: two waves of equal chunks all start at once there, and what one leaves idle the others
+// stream with.  Shares instead, head dimension 64, us: token sums, 48 rows, 24 sequences of 4000..40000 tokens 286 (equal chunks
+// 273), 16 190 (183), 31 of 2000..20000 191 (185); 32 rows 28 of 4000..40000 308 (299); 12 of 1000..4000 33.0 (33.0); no collection, 64
+// rows, 28 of 4000..40000 275 (270), 12 of 2000..20000 69.3 (70.1).
 constexpr int kShareMargin = 2, kPairShareMargin = 4;
 
 // May the lengths of a batch be such that it is cut into shares (wants_shares), if none is longer than `most` units?  With C the
@@ -115,7 +119,6 @@ inline bool shares_possible(int J, int batch, int64_t most, int margin) {
 struct BatchPlan {
   int J = 0;                   // workgroups of one launch wave: one per compute unit
   int J2 = 0;                  // of two waves of equal chunks (= J where only one is planned for)
-  int JR = 0;                  // running at a time, which is how many shares a batch is cut into
   int JS = 0;                  // workgroups launched and partial slots held
   int cap_units = 0;           // longest chunk
 };
@@ -130,17 +133,17 @@ inline BatchPlan batch_plan(int num_cu, int64_t per_head, int batch, int max_len
   // one wave of the longest chunks would be followed by a few more of them (verification with collection, us, without / with
   // the second plan: 16 sequences of 8192..65536 tokens, 24 rows 492 / 437; 8 of 10000..100000, 32 rows 418 / 364; 9 of 51202,
   // 4 rows, token sums 435 / 334; head dimension 64: 20 of 40945, 24 rows 444 / 354).
-  p.JR = two_per_cu ? 2 * p.J : p.J;
   const int64_t most_units = (static_cast<int64_t>(max_len) + unit - 1) / unit;
   const bool beyond_cap = batch >= 8 && batch * most_units + kShareCost * (batch - 1) > static_cast<int64_t>(cap_units) * p.J;
   const bool two_waves = batch > p.J || (two_per_cu && batch >= 8) || (!pair && !collects && 2 * batch > p.J) || beyond_cap;
   p.J2 = two_waves ? 2 * p.J : p.J;
   const int64_t capped = (most_units + cap_units - 1) / cap_units;
-  // slots: a plan for J2 workgroups never takes more than max(J2, B) of them; a capped one B times the most of a sequence; JR
+  // slots: a plan for J2 workgroups never takes more than max(J2, B) of them; a capped one B times the most of a sequence; J
   // shares one each and one more where a sequence ends inside a share (there are at most as many sequences as shares)
   int64_t js = p.J2 > batch ? p.J2 : batch;
-  const int64_t shared = p.JR + (batch < p.JR ? batch : p.JR) - 1;
-  if (shared > js && shares_possible(p.JR, batch, most_units, pair ? kPairShareMargin : kShareMargin)) js = shared;
+  const int64_t shared = p.J + (batch < p.J ? batch : p.J) - 1;
+  if (shared > js && !two_per_cu &&
+      shares_possible(p.J, batch, most_units, pair ? kPairShareMargin : kShareMargin)) js = shared;
   if (batch * capped > js) js = batch * capped;
   p.JS = static_cast<int>(js);
   return p;

@@ -385,7 +385,6 @@ void fill_split_params(const vegas_desc* d, const SplitPlan& pl, int G, const vo
   sp->batch = d->batch;
   sp->slots_target = pl.bp.J;
   sp->slots_target2 = pl.bp.J2;
-  sp->share_wgs = pl.bp.JR;
   sp->share_group = share_group(d->num_kv_heads * pl.NB);
   sp->chunk_cap_units = pl.bp.cap_units;
   sp->slots_total = pl.bp.JS;

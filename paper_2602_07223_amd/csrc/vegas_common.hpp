@@ -172,7 +172,6 @@ struct SplitParams {
   int32_t batch;            // B (balanced chunking)
   int32_t slots_target;     // workgroups per KV head (and row block) of one launch wave
   int32_t slots_target2;    // j2: of two waves (= j1 where only one plan is wanted)
-  int32_t share_wgs;        // workgroups per KV head (and row block) that run at a time
   int32_t share_group;      // so many consecutive workgroups of a head start on as many shader engines (a power of two)
   int32_t chunk_cap_units;  // longest chunk the plan may produce, in units
   int32_t slots_total;      // slots per KV head the workspace holds
@@ -412,10 +411,9 @@ __host__ __device__ __forceinline__ bool wants_second_wave(uint32_t total, uint3
 __host__ __device__ __forceinline__ bool wants_shares(uint32_t priced, uint32_t lives, uint32_t J, uint32_t C, uint32_t margin) {
   return lives <= J && 10u * J * C > 11u * priced + 8u * lives && C >= (priced + J - 1u) / J + margin;
 }
-// share_wgs: workgroups per KV head that run at a time (J of the shares); slots: workgroups there are; share_margin: for
-// wants_shares; second_cost: for wants_second_wave.
+// slots: workgroups there are; share_margin: for wants_shares, or -1 for no shares; second_cost: for wants_second_wave.
 template <typename Wave = GpuWave>
-__host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B, int max_tokens, int j1, int j2, int share_wgs,
+__host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B, int max_tokens, int j1, int j2,
                                                                int share_group, int slots, int share_margin, int second_cost,
                                                                int cap_units, int unit, int j, int2* plan_out) {
   const int lane = Wave::lane();
@@ -433,10 +431,10 @@ __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* le
   }
   const uint32_t longest = Wave::max(nu);
   const uint64_t live = Wave::ballot(nu > 0u);
-  const uint32_t J = share_wgs, lives = __builtin_popcountll(live);
+  const uint32_t J = j1, lives = __builtin_popcountll(live);
   uint32_t C = balanced_chunk_units<Wave>(nu, total, longest, J);
   const uint32_t priced = total + kShareCost * (lives - 1u), S = (priced + J - 1u) / J;
-  if (S <= static_cast<uint32_t>(cap_units) && J + lives <= static_cast<uint32_t>(slots) + 1u &&
+  if (share_margin >= 0 && S <= static_cast<uint32_t>(cap_units) && J + lives <= static_cast<uint32_t>(slots) + 1u &&
       wants_shares(priced, lives, J, C, static_cast<uint32_t>(share_margin))) {
     const uint32_t rank = __builtin_popcountll(live & ((1ull << lane) - 1ull));
     const uint32_t base = Wave::prefix_sum(nu) - nu + kShareCost * rank;       // where the sequence's first token lies
@@ -473,7 +471,6 @@ __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* le
     r.slot = Wave::readlane(q + rank, r.b) + piece;
     return r;
   }
-  if (static_cast<uint32_t>(j1) != J) C = balanced_chunk_units<Wave>(nu, total, longest, static_cast<uint32_t>(j1));
   if (j2 > j1 && wants_second_wave(total, static_cast<uint32_t>(j1), C, static_cast<uint32_t>(second_cost)))
     C = balanced_chunk_units<Wave>(nu, total, longest, static_cast<uint32_t>(j2));
   C = min(C, static_cast<uint32_t>(cap_units));

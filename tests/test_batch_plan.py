@@ -70,7 +70,7 @@ static char stack[64][1 << 16];
 static void body() {
   const int lane = Lanes::cur;
   const BatchPlan& p = call.bp;
-  call.out[lane] = balanced_slot<Lanes>(call.lens, call.batch, call.max_len, p.J, p.J2, p.JR, call.group, p.JS,
+  call.out[lane] = balanced_slot<Lanes>(call.lens, call.batch, call.max_len, p.J, p.J2, call.group, p.JS,
                                         call.margin, call.second, p.cap_units, 128, call.slot, call.plan);
   Lanes::done[lane] = true;
   _longjmp(Lanes::back, 1);
@@ -124,12 +124,12 @@ int main() {             // lines of: KV heads, head dimension, rows, collection
     call.batch = batch;
     call.max_len = max_len;
     call.second = pair ? pair_second_cost(D, collect) : 2;
-    call.margin = pair ? kPairShareMargin : kShareMargin;
+    call.margin = two_per_cu ? -1 : pair ? kPairShareMargin : kShareMargin;
     call.group = share_group(heads * blocks);
     call.bp = batch_plan(256, heads * blocks, batch, max_len, 128, cap / 128, pair, two_per_cu, collect != 0);
     call.plan = plan.data();
     const BatchPlan& p = call.bp;
-    std::printf("%d %d %d %d %d %d", p.J, p.J2, p.JR, p.JS, p.cap_units, call.group);
+    std::printf("%d %d %d %d %d", p.J, p.J2, p.JS, p.cap_units, call.group);
     for (int j = 0; j < p.JS; ++j) {
       call.slot = j;
       const BalancedSlot s = run();
@@ -170,7 +170,7 @@ def plans(exe, calls):
     for line in r.stdout.strip().split("\n"):
         head, *columns = line.split(" ; ")
         nums, *pieces = head.split(" | ")
-        d = dict(zip(("J", "J2", "JR", "JS", "cap", "group"), map(int, nums.split())))
+        d = dict(zip(("J", "J2", "JS", "cap", "group"), map(int, nums.split())))
         d["pieces"] = [tuple(map(int, p.split())) for p in pieces]
         d["columns"] = [tuple(map(int, c.split())) for c in columns]
         d["shares"] = any(c[3] < 0 for c in d["columns"])
@@ -203,24 +203,25 @@ def check(call, d):
 def wanted(c, d):
     """Would the lengths be cut into shares (wants_shares), had the call the slots?"""
     nu = [-(-n // UNIT) for n in c[5]]
-    live, J = sum(1 for x in nu if x), d["JR"]
-    if not live:
+    live, J = sum(1 for x in nu if x), d["J"]
+    tile_rows = c[2] + (2 if c[3] == 2 else 0)
+    if not live or (tile_rows > 32 and c[1] == 64 and c[3] != 1):     # (two workgroups per compute unit)
         return False
     longest = next(x for x in range(1, max(nu) + 1) if x == max(nu) or sum(-(-u // x) for u in nu) <= J)
-    priced, margin = sum(nu) + 3 * (live - 1), 4 if c[2] + (2 if c[3] == 2 else 0) > 32 else 2
+    priced, margin = sum(nu) + 3 * (live - 1), 4 if tile_rows > 32 else 2
     S = -(-priced // J)
     return S <= d["cap"] and live <= J and 10 * J * longest > 11 * priced + 8 * live and longest >= S + margin
 
 
 def load(d, begin=3):
     """The longest a compute unit is busy over the mean, in units of 128 tokens, with `begin` of them for every piece."""
-    free = [0] * d["JR"]
+    free = [0] * d["J"]
     total = 0
     for _, _, _, chunk, _ in d["pieces"]:
         t = heapq.heappop(free) + chunk // UNIT + begin
         total += chunk // UNIT
         heapq.heappush(free, t)
-    return max(free) / (total / d["JR"])
+    return max(free) / (total / d["J"])
 
 
 def spread(n, lo, hi):
@@ -254,11 +255,9 @@ def test_every_plan_covers_every_sequence_once(tmp_path_factory):
         check(c, d)
         assert d["shares"] == wanted(c, d), c
         if d["shares"]:
-            seen.add((d["group"], d["JR"] > d["J"], d["J"] % d["group"] != 0))
-    # shares were met with every length of the reversed groups, with two workgroups per compute unit, and where the last group of
-    # the first wave is not whole
-    assert {g for g, _, _ in seen} == {1, 2, 4, 8, 16, 32}
-    assert {two for _, two, _ in seen} == {False, True} and {part for _, _, part in seen} == {False, True}
+            seen.add((d["group"], d["J"] % d["group"] != 0))
+    # shares were met with every length of the reversed groups, and where the last group of the first wave is not whole
+    assert {g for g, _ in seen} == {1, 2, 4, 8, 16, 32} and {part for _, part in seen} == {False, True}
 
 
 # KV heads, head dimension, rows, collection, lengths: the mean of a compute unit is longer than a workgroup can park
