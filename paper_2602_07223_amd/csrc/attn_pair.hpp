@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
   int64_t pbase = (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + split;   // this workgroup's partial slot
   if (p.plan) {                              // balanced chunking: workgroup `split` of this head -> (sequence, tokens)
     const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2, p.share_group, p.slots_total,
-                                          pair_two_per_cu(D, COLLECT) ? -1 : kPairShareMargin, pair_second_cost(D, COLLECT),
+                                          p.share_margin, pair_second_cost(D, COLLECT),
                                           p.chunk_cap_units, p.chunk_unit, split, ((blockIdx.x | yy) == 0 && wave == 0) ? p.plan : nullptr);
     if (bs.b < 0) return;
     b = __builtin_amdgcn_readfirstlane(bs.b);

@@ -211,7 +211,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
   if constexpr (CAUSAL && PS == 4 && !LOCAL) {
     if (p.plan) {                            // balanced chunking: workgroup `split` of this head -> (sequence, tokens)
       const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2, p.share_group,
-                                            p.slots_total, kShareMargin, 2, p.chunk_cap_units, p.chunk_unit, split,
+                                            p.slots_total, p.share_margin, 2, p.chunk_cap_units, p.chunk_unit, split,
                                             ((blockIdx.x | blockIdx.y) == 0 && wave == 0) ? p.plan : nullptr);
       if (bs.b < 0) return;
       b = bs.b;

@@ -114,6 +114,18 @@ inline bool shares_possible(int J, int batch, int64_t most, int margin) {
   return batch >= 2 && C * (batch - 1) >= static_cast<int64_t>(J) * (margin - 1) - 4 + 5 * static_cast<int64_t>(batch);
 }
 
+// Does a planned batch's 32-row workgroup that parks nothing have a compute unit to itself?  Sharing one, the pieces of a plan by
+// shares all start at once, on some units two, so a batch that may be cut into shares is run as that plan assumes, from a bound of
+// 12 units per workgroup on (16 at head dimension 64); below, workgroups run side by side and there are no shares.  us, side by side /
+// alone, verification without collection, 20 rows, by bound per workgroup: 4.7 16 sequences of 300..1200 tokens 18.1 / 18.8; 11 18 of
+// 1000..2500 32.2 / 33.3; 12.7 20 of 2000..2600 44.8 / 43.8 (head dimension 64 29.4 / 31.7); 14.6 30 of 300..2000 40.9 / 39.5 (27.4 /
+// 30.5); 117 24 of 1001..20011 210 / 189; 192 12 of 8192..65536 365 / 302.  With more sequences than workgroups there are no shares,
+// and the host cannot tell a long batch from a short one under a loose bound: 48 of 300..3000 83 / 72, but 64 of 400..800 under a
+// bound of 131072 46.2 / 52.6.
+inline bool alone_on_compute_unit(int J, int batch, int max_len, int unit, int head_dim) {
+  return batch <= J && static_cast<int64_t>(batch) * max_len >= static_cast<int64_t>(head_dim == 64 ? 16 : 12) * J * unit;
+}
+
 // A batch whose chunk lengths are computed on the GPU (balanced_slot, vegas_common.hpp): the numbers that the plan works with,
 // per KV head (and row block), and what of them a launch holds.  units: of kTile tokens per wave.
 struct BatchPlan {
@@ -121,9 +133,11 @@ struct BatchPlan {
   int J2 = 0;                  // of two waves of equal chunks (= J where only one is planned for)
   int JS = 0;                  // workgroups launched and partial slots held
   int cap_units = 0;           // longest chunk
+  int share_margin = -1;       // what shares have to win (wants_shares); -1: the batch is not cut into shares
+  bool alone = false;          // a workgroup has a compute unit to itself, whatever LDS it needs
 };
 inline BatchPlan batch_plan(int num_cu, int64_t per_head, int batch, int max_len, int unit, int cap_units, bool pair,
-                            bool two_per_cu, bool collects) {
+                            bool two_per_cu, bool collects, int head_dim) {
   BatchPlan p;
   p.cap_units = cap_units;
   p.J = static_cast<int>(num_cu / per_head);
@@ -133,6 +147,8 @@ inline BatchPlan batch_plan(int num_cu, int64_t per_head, int batch, int max_len
   // one wave of the longest chunks would be followed by a few more of them (verification with collection, us, without / with
   // the second plan: 16 sequences of 8192..65536 tokens, 24 rows 492 / 437; 8 of 10000..100000, 32 rows 418 / 364; 9 of 51202,
   // 4 rows, token sums 435 / 334; head dimension 64: 20 of 40945, 24 rows 444 / 354).
+  p.alone = !pair && !collects && alone_on_compute_unit(p.J, batch, max_len, unit, head_dim);
+  if (pair ? !two_per_cu : collects || p.alone) p.share_margin = pair ? kPairShareMargin : kShareMargin;
   const int64_t most_units = (static_cast<int64_t>(max_len) + unit - 1) / unit;
   const bool beyond_cap = batch >= 8 && batch * most_units + kShareCost * (batch - 1) > static_cast<int64_t>(cap_units) * p.J;
   const bool two_waves = batch > p.J || (two_per_cu && batch >= 8) || (!pair && !collects && 2 * batch > p.J) || beyond_cap;
@@ -142,8 +158,7 @@ inline BatchPlan batch_plan(int num_cu, int64_t per_head, int batch, int max_len
   // shares one each and one more where a sequence ends inside a share (there are at most as many sequences as shares)
   int64_t js = p.J2 > batch ? p.J2 : batch;
   const int64_t shared = p.J + (batch < p.J ? batch : p.J) - 1;
-  if (shared > js && !two_per_cu &&
-      shares_possible(p.J, batch, most_units, pair ? kPairShareMargin : kShareMargin)) js = shared;
+  if (shared > js && p.share_margin >= 0 && shares_possible(p.J, batch, most_units, p.share_margin)) js = shared;
   if (batch * capped > js) js = batch * capped;
   p.JS = static_cast<int>(js);
   return p;

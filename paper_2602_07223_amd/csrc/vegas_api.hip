@@ -27,7 +27,7 @@ using namespace vegas;
 
 constexpr int kDefaultCU = 256;       // MI355X compute units: assumed where no device is visible
 constexpr size_t kAlign = 256;
-constexpr size_t kLoneLds = 81 * 1024;   // LDS of a workgroup that is to have a compute unit to itself
+constexpr size_t kLoneLds = 81 * 1024;   // LDS of a workgroup that is to have a compute unit to itself (BatchPlan::alone)
 
 // Compute units of the current device, asked once per device.  The launch plans aim at one or two workgroups per
 // compute unit, and the workspace is sized from the same plans, so sizing and launching must see the same number:
@@ -192,7 +192,7 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
       while (split_lds_bytes(pl->NW, prows, collect, cap + unit, d->head_dim) <= 150 * 1024 && cap < (1 << 24)) cap += unit;
     }
     pl->bp = batch_plan(num_cu, per_head, d->batch, max_len, unit, cap / unit, pl->pair,
-                        pl->pair && pair_two_per_cu(d->head_dim, collect), collect != 0);
+                        pl->pair && pair_two_per_cu(d->head_dim, collect), collect != 0, d->head_dim);
     pl->chunk = collect != 0 && !pl->pair ? cap : unit;         // sizes the LDS that parks a chunk's collected values
     slots = static_cast<size_t>(d->num_kv_heads) * pl->bp.JS;   // (sibling row blocks share a slot)
   }
@@ -299,12 +299,7 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
   if (grid.y > 65535u) return VEGAS_ERR_UNSUPPORTED;        // more chunks per sequence than a grid dimension holds
   const int rows = pl.R < 32 ? pl.R : 32;
   size_t lds = split_lds_bytes(pl.NW, rows, COLLECT, pl.chunk, D);
-  // A long batch's workgroups have a compute unit to themselves, as their plan assumes: sharing one, the pieces of a plan by
-  // shares all start at once, on some units two (no collection, 24 sequences of 1001..20011 tokens 184 -> 200 us; 48 of 300..3000
-  // in equal chunks 70 -> 79).  Short ones gain from workgroups side by side (16 of 300..1200 18.4 us, alone 18.9).
-  if (pl.balanced && lds < kLoneLds &&
-      static_cast<int64_t>(batch) * sp.max_tokens >= static_cast<int64_t>(16) * pl.bp.J * sp.chunk_unit)
-    lds = kLoneLds;
+  if (pl.balanced && pl.bp.alone && lds < kLoneLds) lds = kLoneLds;
   sp.lds_q_off = static_cast<int32_t>(lds - split_lds_tail_bytes(pl.NW, D));
   sp.row_blocks = pl.NB;
   if (lds > 160 * 1024) return VEGAS_ERR_UNSUPPORTED;
@@ -385,6 +380,7 @@ void fill_split_params(const vegas_desc* d, const SplitPlan& pl, int G, const vo
   sp->batch = d->batch;
   sp->slots_target = pl.bp.J;
   sp->slots_target2 = pl.bp.J2;
+  sp->share_margin = pl.bp.share_margin;
   sp->share_group = share_group(d->num_kv_heads * pl.NB);
   sp->chunk_cap_units = pl.bp.cap_units;
   sp->slots_total = pl.bp.JS;

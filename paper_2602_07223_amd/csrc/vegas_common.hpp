@@ -172,6 +172,7 @@ struct SplitParams {
   int32_t batch;            // B (balanced chunking)
   int32_t slots_target;     // workgroups per KV head (and row block) of one launch wave
   int32_t slots_target2;    // j2: of two waves (= j1 where only one plan is wanted)
+  int32_t share_margin;     // what cutting the batch into shares has to win, in units (-1: it is not cut)
   int32_t share_group;      // so many consecutive workgroups of a head start on as many shader engines (a power of two)
   int32_t chunk_cap_units;  // longest chunk the plan may produce, in units
   int32_t slots_total;      // slots per KV head the workspace holds

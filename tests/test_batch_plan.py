@@ -59,7 +59,7 @@ struct Lanes {
 
 struct Call {
   const int* lens;
-  int batch, max_len, second, margin, group, slot;
+  int batch, max_len, second, group, slot;
   BatchPlan bp;
   int2* plan;
   BalancedSlot out[64];
@@ -71,7 +71,7 @@ static void body() {
   const int lane = Lanes::cur;
   const BatchPlan& p = call.bp;
   call.out[lane] = balanced_slot<Lanes>(call.lens, call.batch, call.max_len, p.J, p.J2, call.group, p.JS,
-                                        call.margin, call.second, p.cap_units, 128, call.slot, call.plan);
+                                        p.share_margin, call.second, p.cap_units, 128, call.slot, call.plan);
   Lanes::done[lane] = true;
   _longjmp(Lanes::back, 1);
 }
@@ -124,9 +124,8 @@ int main() {             // lines of: KV heads, head dimension, rows, collection
     call.batch = batch;
     call.max_len = max_len;
     call.second = pair ? pair_second_cost(D, collect) : 2;
-    call.margin = two_per_cu ? -1 : pair ? kPairShareMargin : kShareMargin;
     call.group = share_group(heads * blocks);
-    call.bp = batch_plan(256, heads * blocks, batch, max_len, 128, cap / 128, pair, two_per_cu, collect != 0);
+    call.bp = batch_plan(256, heads * blocks, batch, max_len, 128, cap / 128, pair, two_per_cu, collect != 0, D);
     call.plan = plan.data();
     const BatchPlan& p = call.bp;
     std::printf("%d %d %d %d %d", p.J, p.J2, p.JS, p.cap_units, call.group);
@@ -207,6 +206,8 @@ def wanted(c, d):
     tile_rows = c[2] + (2 if c[3] == 2 else 0)
     if not live or (tile_rows > 32 and c[1] == 64 and c[3] != 1):     # (two workgroups per compute unit)
         return False
+    if tile_rows <= 32 and c[3] == 0 and (len(nu) > J or len(nu) * c[4] < (16 if c[1] == 64 else 12) * J * UNIT):
+        return False                                                  # (workgroups that park nothing run side by side)
     longest = next(x for x in range(1, max(nu) + 1) if x == max(nu) or sum(-(-u // x) for u in nu) <= J)
     priced, margin = sum(nu) + 3 * (live - 1), 4 if tile_rows > 32 else 2
     S = -(-priced // J)

@@ -267,3 +267,27 @@ def test_batches_are_cut_into_shares_where_that_is_faster(tmp_path):
                 ((778, 48, 32, 23, 2), 0), ((778, 48, 32, 500, 2), 0)]
     out = run_host_program(tmp_path, SHARES, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
     assert [int(x) for x in out] == [s for _, s in measured]
+
+
+ALONE = r'''
+#include <cstdio>
+#include "plan_rules.hpp"
+int main() {                       // lines of: sequences, longest, head dimension (20 rows, 8 KV heads, no collection, 256 compute units)
+  int batch, longest, D;
+  while (std::scanf("%d %d %d", &batch, &longest, &D) == 3) {
+    const vegas::BatchPlan p = vegas::batch_plan(256, 8, batch, longest, 128, 1 << 17, false, false, false, D);
+    std::printf("%d\n", p.alone && p.share_margin == vegas::kShareMargin ? 1 : p.alone || p.share_margin >= 0 ? 2 : 0);
+  }
+}
+'''
+
+
+def test_workgroups_alone_on_a_compute_unit_where_that_is_faster(tmp_path):
+    """Measured faster alone (and cut into shares), or not; never with more sequences than workgroups, whose bound says nothing
+    about their lengths."""
+    measured = [((16, 1200, 128), 0), ((18, 2500, 128), 0), ((8, 6000, 128), 0), ((20, 2600, 128), 1), ((30, 2000, 128), 1),
+                ((24, 2500, 128), 1), ((28, 2200, 128), 1), ((32, 1900, 128), 1), ((24, 20011, 128), 1), ((12, 65536, 128), 1),
+                ((20, 2600, 64), 0), ((30, 2000, 64), 0), ((32, 1900, 64), 0), ((24, 20011, 64), 1), ((12, 65536, 64), 1),
+                ((64, 800, 128), 0), ((64, 131072, 128), 0), ((33, 1 << 20, 128), 0)]
+    out = run_host_program(tmp_path, ALONE, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
+    assert [int(x) for x in out] == [s for _, s in measured]
