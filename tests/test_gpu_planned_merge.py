@@ -1,6 +1,6 @@
 """Balanced chunking's merge and page scores over every number of chunks the merge distinguishes: a batch in which one
 sequence gets 1, 4, 5, 8, 9, 16, 17, 31 or 57 chunks (the shortest chunk is 128 tokens) and the others one each, with
-and without collection, against the oracle."""
+and without collection, in calls of few rows and (57 chunks) of many, against the oracle."""
 import pytest
 import torch
 
@@ -8,15 +8,32 @@ from oracle import vegas_oracle as O
 from paper_2602_07223_amd import binding as vb
 from paper_2602_07223_amd import harness, synth
 from tests import parity_util as U
+from tests.test_batch_plan import plans, program
 
-pytestmark = pytest.mark.gpu
+
+def batch_of(chunks):
+    """KV heads and lengths: 8 heads leave 32 workgroups per head, which 57 chunks do not fit; 4 leave 64."""
+    return (8, [128 * chunks - 3, 16]) if chunks < 32 else (4, [128 * chunks - 3] + [16] * 3)
 
 
+MANY = (2, [128 * 57 - 3] + [16] * 25)       # 26 sequences x 80 rows: a merge of many rows
+
+CHUNKS = [1, 4, 5, 8, 9, 16, 17, 31, 57]
+
+
+def test_the_batches_have_so_many_chunks(tmp_path_factory):
+    calls = [(heads, 128, rows, c, max(lens), lens) for rows in (20, 40) for c in (0, 1)
+             for heads, lens in [batch_of(n) for n in CHUNKS] + [MANY]]
+    for c, d in zip(calls, plans(program(tmp_path_factory), calls)):
+        assert not d["shares"] and d["columns"][0][1] == -(-c[5][0] // 128), c
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("Hq", [32, 64], ids=["20_rows", "40_rows"])
-@pytest.mark.parametrize("chunks", [1, 4, 5, 8, 9, 16, 17, 31, 57])
+@pytest.mark.parametrize("chunks", CHUNKS + ["many_rows"])
 def test_planned_sequences_with_every_chunk_count(chunks, Hq):
-    lens = [128 * chunks - 3, 16] if chunks < 32 else [128 * chunks - 3] + [16] * 7
-    L = synth.make_random_case(seed=41000 + chunks + Hq, batch=len(lens), num_q_heads=Hq, num_kv_heads=8, num_queries=5,
+    heads, lens = MANY if chunks == "many_rows" else batch_of(chunks)
+    L = synth.make_random_case(seed=41000 + lens[0] // 128 + Hq, batch=len(lens), num_q_heads=Hq // 8 * heads, num_kv_heads=heads, num_queries=5,
                                seq_lens=lens, logit_std=2.0, value_std=1.0, outliers=2, outlier_logit=25.0)
     print(f"[case] planned merge, {chunks} chunks, Hq={Hq}", flush=True)
     dl = harness.DeviceLayer.upload(L)
@@ -34,6 +51,7 @@ def test_planned_sequences_with_every_chunk_count(chunks, Hq):
             U.check_scores(f"planned.{chunks}", path.block_scores, ref_scores)
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("collect", [vb.COLLECT_NONE, vb.COLLECT_ALL_ROWS], ids=["none", "all_rows"])
 @pytest.mark.parametrize("lens", [[4096, 0], [0, 4096, 0], [0, 0]], ids=str)
 def test_empty_members_of_a_plan_that_fills_every_slot(lens, collect):

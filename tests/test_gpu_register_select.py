@@ -1,5 +1,5 @@
 """Token selection by one workgroup per sequence (prefixes of at most 32768 tokens) against the oracle, bit for bit, at
-the edges of its rows of 1024 keys and of its digit passes."""
+lengths inside its rows of 4096 tokens and at the edges of its digit passes (whole rows: test_gpu_select_crowded.py)."""
 import numpy as np
 import pytest
 
