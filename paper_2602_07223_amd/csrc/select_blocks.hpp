@@ -164,9 +164,10 @@ __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int f
       }
     }
     __syncthreads();
-    r.base += __builtin_amdgcn_readfirstlane(sh.bin) << shift;
+    const uint32_t start = __builtin_amdgcn_readfirstlane(sh.bin) << shift;
+    r.base += start;
     r.need = __builtin_amdgcn_readfirstlane(sh.need);
-    r.span = (1u << shift) - 1u;
+    r.span = min((1u << shift) - 1u, r.span - start);               // (the last bin ends with the range: above it are taken keys)
     const uint32_t count = __builtin_amdgcn_readfirstlane(sh.count);
     if (shift == 0 || count == r.need) break;                       // equal keys, or the whole bin is taken
     shift = max(shift - 11, 0);

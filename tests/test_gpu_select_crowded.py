@@ -62,6 +62,36 @@ def test_tokens(kind, longest, G):
         assert np.array_equal(sel, ref_sel)
 
 
+def bordering(n, above):
+    """Keys (as bits of scores in [1, 2)): an eighth of them and more within one bin of 4096 from its second key to its last,
+    which `above` keys, before it by position, follow at once; the last one taken is the bin's last.  Its exact range, cut by
+    11-bit digits, ends half a digit after it."""
+    rng = np.random.default_rng(n)
+    off = 10 * 4096 + rng.integers(0, 2**23 - 10 * 4096, size=n)
+    off[::3] = 5 * 4096 + 1
+    off[1::7] = 0
+    off[-1] = 2**23 - 1
+    off[-2] = 5 * 4096 + 4095
+    off[2:2 + 3 * above:3] = 6 * 4096
+    return (np.uint32(0x3F800000) + off.astype(np.uint32)).view(np.float32), int((off >= 5 * 4096 + 4095).sum())
+
+
+@pytest.mark.parametrize("above", [0, 1, 20])
+@pytest.mark.parametrize("longest", [4096, 8192, 32768])
+def test_tokens_above_the_last_bin_of_an_exact_range(longest, above):
+    G = 5
+    x, take = bordering(longest - G, above)
+    scores = np.zeros((1, longest), dtype=np.float32)
+    scores[0, :longest - G] = x
+    table = np.arange(longest // PAGE, dtype=np.int32)[None]
+    lens = np.array([longest], dtype=np.int32)
+    for k in (take, take - 1, take + 1):
+        sel, ssl = gpu_select_tokens(scores, table, lens, G, k + G, longest, None)
+        ref_sel, ref_ssl, _ = O.select_tokens(scores, table, lens, G, k + G, longest, None)
+        assert np.array_equal(ssl, ref_ssl)
+        assert np.array_equal(sel, ref_sel)
+
+
 @pytest.mark.parametrize("pages", [100, 1025, 2049, 3072, 3073, 4097, 8192])
 @pytest.mark.parametrize("kind", KINDS)
 def test_pages(kind, pages):
