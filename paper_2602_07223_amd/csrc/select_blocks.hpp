@@ -38,12 +38,15 @@ struct LastKey {
 
 constexpr uint32_t kNoDigit = 0xFFFFFFFFu;      // of a key that is not counted
 constexpr int kOften = 4;                       // digits that a crowded wave counts by itself
-// Do so many lanes have the digit of the lane beside them?  (The chance that two keys share a digit, at the price of one
-// comparison.)
-__device__ __forceinline__ bool crowded(uint32_t digit, int lanes) {
-  const uint32_t beside = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int>(kNoDigit), static_cast<int>(digit),
-                                                                            0x111, 0xf, 0xf, false));   // row_shr:1
-  return __popcll(__builtin_amdgcn_ballot_w64(digit == beside && digit != kNoDigit)) >= lanes;
+constexpr int kRunLanes = 32;                   // so many lanes with the digit of the lane beside them: one add per run of lanes
+// The digit of the lane below, of sixteen; none for the first.
+__device__ __forceinline__ uint32_t digit_beside(uint32_t digit) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int>(kNoDigit), static_cast<int>(digit), 0x111, 0xf, 0xf,
+                                                           false));   // row_shr:1
+}
+// Lanes that have the digit of the lane beside them: the chance that two keys share a digit, at the price of one comparison.
+__device__ __forceinline__ int sharing_lanes(uint32_t digit) {
+  return __popcll(__builtin_amdgcn_ballot_w64(digit == digit_beside(digit) && digit != kNoDigit));
 }
 
 // Radix select: where the `take` largest of the workgroup's keys end.  Keys below `full` of every thread hold positions, of
@@ -56,13 +59,16 @@ __device__ __forceinline__ bool crowded(uint32_t digit, int lanes) {
 // sequences 590.6 instead of 587.6, 8192 pages 161.0 instead of 158.0.)  What bounds it is latency, a barrier and one wave's walk
 // through the counts per pass, and with 16 and more keys a thread the instructions issued per key.
 // Scores need not spread: adds of many lanes to one bin wait for each other.  A wave whose first keys meet in few bins counts
-// the digits of up to four of them in registers and adds the rest; and where a bin holds an eighth of the keys, its own
-// smallest and largest set the next digits, instead of passes that tell nothing apart.  us per call, four passes of 8 bits (five
-// launches for tokens) / without these two / with them, 8192 pages: normally distributed 10.5 / 7.8 / 8.1, four values 16.3 /
-// 13.2 / 8.8, fifteen in sixteen 0 8.7 / 12.6 / 8.4, a twentieth -infinity beside scores within a percent 12.9 / 14.7 / 11.1, one
-// far outlier 13.5 / 22.1 / 11.5; 32768 tokens: 20.8 / 16.7 / 16.9, 20.7 / 39.0 / 20.4, 20.8 / 38.0 / 18.4, 20.8 / 42.8 / 22.8, 20.7 / 73.4 /
-// 26.9; 2048 pages, of which a thread has two, which are not looked at for this: 5.8 / 6.0 / 6.3, 8.3 / 7.5 / 6.7, 5.0 / 6.5 / 6.5, 7.7 /
-// 7.9 / 9.2, 8.0 / 9.6 / 8.4.
+// the digits of up to four of them in registers and adds the rest, or, where half its lanes have the digit of the lane beside
+// them (scores that rise or fall with the position, or nearly all equal), adds once for each run of lanes; and where a bin holds
+// an eighth of the keys, its own smallest and largest set the next digits, instead of passes that tell nothing apart.
+// us per call, four passes of 8 bits (five launches for tokens) / plain adds and fixed digits / now.  8192 pages: normally
+// distributed 9.2 / 7.7 / 8.1, four values 15.6 / 13.1 / 8.8, fifteen in sixteen 0 8.6 / 12.4 / 7.7, a twentieth -infinity beside
+// scores within a percent 12.8 / 14.5 / 10.6, one far outlier there 12.9 / 14.9 / 10.6, ascending 9.9 / 12.8 / 8.3.  32768 tokens:
+// 20.8 / 17.1 / 17.3, 20.4 / 38.9 / 20.4, 20.6 / 90.0 / 19.7, 20.5 / 42.7 / 23.8, 20.6 / 44.1 / 25.7, 20.5 / 39.1 / 19.4.  2048 pages, of
+// which a thread has two, which are not looked at for this: 5.6 / 5.7 / 6.05, 8.2 / 7.4 / 6.5, 7.9 / 10.6 / 7.4, 6.9 / 7.6 / 8.9,
+// 7.8 / 7.8 / 9.1, 5.7 / 6.7 / 7.0.  (A first range that leaves masks' scores and a lone low one out, with up to four passes:
+// masked and outlier 8.6 and 18.2 at the larger two, but every other call 0.3 to 1.6 more.)
 template <int N, typename Valid>
 __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int full, int live, Valid valid, uint32_t take,
                                                  RegisterSelectShared& sh) {
@@ -106,11 +112,21 @@ __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int f
     auto counted = [&](int u) { return (pass == 0 && u < full) || key[u] - r.base <= r.span; };
     const uint32_t first = counted(0) ? digit(0) : kNoDigit;
     // (later passes count a fraction of the keys, so that neighbours seldom are both among them)
-    if (__builtin_expect(live < 4 || !crowded(first, pass == 0 ? 8 : 1), 1)) {
+    const int sharing = live < 4 ? 0 : sharing_lanes(first);
+    if (__builtin_expect(sharing < (pass == 0 ? 8 : 1), 1)) {
 #pragma unroll
       for (int u = 0; u < N; ++u) {
         if (u >= live) continue;
         if (counted(u)) atomicAdd(&h[digit(u)], 1u);
+      }
+    } else if (sharing >= kRunLanes) {
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        if (u >= live) continue;
+        const uint32_t d = counted(u) ? digit(u) : kNoDigit;
+        const uint64_t heads = __builtin_amdgcn_ballot_w64(d != digit_beside(d) || (lane & 15) == 0);
+        const uint64_t beyond = (heads >> lane) >> 1;
+        if (((heads >> lane) & 1u) && d != kNoDigit) atomicAdd(&h[d], static_cast<uint32_t>(beyond ? __builtin_ctzll(beyond) + 1 : 64 - lane));
       }
     } else {
       uint32_t often[kOften], n[kOften];

@@ -1,5 +1,5 @@
 """Selection among keys in registers (select_blocks.hpp, find_last_key) where scores do not spread over the digits: waves that
-count a few digits by themselves, bins that hold an eighth of the keys and set the range of the next pass, at the edges of
+count a few digits or runs of lanes by themselves, bins that hold an eighth of the keys and set the range of the next pass, at the edges of
 the rows of 4096 tokens (or 1024 pages) and of the launch variants, against the oracle, bit for bit."""
 import numpy as np
 import pytest
@@ -36,10 +36,12 @@ def make_scores(kind, n, rng):
         x[rng.integers(0, n, size=max(n // 5, 1))] = np.float32(1.25)
         x[n // 2], x[n // 3], x[n // 4] = np.float32(-3e38), INF, NAN
         return x
+    if kind == "ascending":
+        return np.sort(x)
     return np.repeat(x[:n // 97 + 1], 97)[:n].copy()      # runs of equal scores
 
 
-KINDS = ["four_values", "forty_values", "half_zero", "few_nonzero", "masked", "outliers", "runs"]
+KINDS = ["four_values", "forty_values", "half_zero", "few_nonzero", "masked", "outliers", "runs", "ascending"]
 
 
 # longest sequence, queries: prefixes of whole rows of 4096 tokens and one token more, both sides of every launch variant
