@@ -63,13 +63,14 @@ __device__ __forceinline__ int sharing_lanes(uint32_t digit) {
 // them (scores that rise or fall with the position, or nearly all equal), adds once for each run of lanes; and where a bin holds
 // an eighth of the keys, its own smallest and largest set the next digits, instead of passes that tell nothing apart.
 // us per call, four passes of 8 bits (five launches for tokens) / plain adds and fixed digits / now.  8192 pages: normally
-// distributed 9.2 / 7.7 / 8.1, four values 15.6 / 13.1 / 8.8, fifteen in sixteen 0 8.6 / 12.4 / 7.7, a twentieth -infinity beside
-// scores within a percent 12.8 / 14.5 / 10.6, one far outlier there 12.9 / 14.9 / 10.6, ascending 9.9 / 12.8 / 8.3.  32768 tokens:
-// 20.8 / 17.1 / 17.3, 20.4 / 38.9 / 20.4, 20.6 / 90.0 / 19.7, 20.5 / 42.7 / 23.8, 20.6 / 44.1 / 25.7, 20.5 / 39.1 / 19.4.  2048 pages, of
-// which a thread has two, which are not looked at for this: 5.6 / 5.7 / 6.05, 8.2 / 7.4 / 6.5, 7.9 / 10.6 / 7.4, 6.9 / 7.6 / 8.9,
-// 7.8 / 7.8 / 9.1, 5.7 / 6.7 / 7.0.  (A first range that leaves masks' scores and a lone low one out, with up to four passes:
-// masked and outlier 8.6 and 18.2 at the larger two, but every other call 0.3 to 1.6 more.)
-template <int N, typename Valid>
+// distributed 9.2 / 7.75 / 8.1, four values 15.7 / 13.1 / 8.9, fifteen in sixteen 0 8.6 / 12.5 / 7.8, a twentieth -infinity beside
+// scores within a percent 12.9 / 14.5 / 10.6, one far outlier there 13.0 / 15.0 / 10.6, ascending 9.9 / 12.8 / 8.3.  32768 tokens:
+// 20.8 / 17.1 / 17.0, 20.5 / 39.0 / 19.9, 20.6 / 90.3 / 19.3, 20.6 / 42.8 / 23.4, 20.6 / 44.2 / 25.3, 20.6 / 39.1 / 19.0.
+// !CROWDS: none of this, for two keys a thread: 2048 pages 5.6 / 5.8 / 5.9, 8.3 / 7.4 / 5.7, 7.9 / 10.7 / 10.7, 6.9 / 7.6 / 7.8, 7.9 /
+// 7.85 / 8.0, 5.7 / 6.7 / 6.8 (with the exact ranges 6.05, 6.5, 7.4, 8.9, 9.1, 7.0).  The passes are a loop, whose code is cold
+// in an iteration: token selection at 32768 there 0.7 less than unrolled.  (A first range that leaves masks' scores and a lone
+// low one out, with up to four passes: masked and outlier 8.6 and 18.2 at the larger two, but every other call 0.3 to 1.6 more.)
+template <bool CROWDS = true, int N, typename Valid>
 __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int full, int live, Valid valid, uint32_t take,
                                                  RegisterSelectShared& sh) {
   constexpr int kWaves = kSelectThreads / 64;
@@ -104,15 +105,15 @@ __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int f
   // (Keys without a position lie outside every range unless it starts at 0, the key of NaNs, and are the last there: a bin is
   //  then never taken whole, and of equal keys the first positions are.)
   int shift = max(32 - __builtin_clz(r.span | 1u) - 11, 0);
-#pragma unroll
+#pragma unroll 1                              // (later passes find the first one's instructions in the cache)
   for (int pass = 0; pass < 3; ++pass) {
     if (r.span == 0u) break;                                        // all keys are equal: nothing to find
     uint32_t* const h = sh.hist[pass];
     auto digit = [&](int u) { return (key[u] - r.base) >> shift; };
-    auto counted = [&](int u) { return (pass == 0 && u < full) || key[u] - r.base <= r.span; };
+    auto counted = [&](int u) { return key[u] - r.base <= r.span; };
     const uint32_t first = counted(0) ? digit(0) : kNoDigit;
     // (later passes count a fraction of the keys, so that neighbours seldom are both among them)
-    const int sharing = live < 4 ? 0 : sharing_lanes(first);
+    const int sharing = !CROWDS || live < 4 ? 0 : sharing_lanes(first);
     if (__builtin_expect(sharing < (pass == 0 ? 8 : 1), 1)) {
 #pragma unroll
       for (int u = 0; u < N; ++u) {
@@ -187,7 +188,7 @@ __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int f
     const uint32_t count = __builtin_amdgcn_readfirstlane(sh.count);
     if (shift == 0 || count == r.need) break;                       // equal keys, or the whole bin is taken
     shift = max(shift - 11, 0);
-    if (__builtin_expect(8u * count >= keys, 0)) {
+    if (CROWDS && __builtin_expect(8u * count >= keys, 0)) {
       uint32_t hi = 0u, inv_lo = 0u;
 #pragma unroll
       for (int u = 0; u < N; ++u) {
@@ -294,8 +295,15 @@ __global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const Sel
     }
 #pragma unroll
     for (int u = 0; u < kRows; ++u) key[u] = tid < f0 - u * kSelectThreads ? score_key(v[u]) : 0u;
-    const LastKey last = find_last_key(key, f0 / kSelectThreads, rows, [&](int u) { return tid < f0 - u * kSelectThreads; },
-                                       static_cast<uint32_t>(kc), reg_shared);
+    // Two rows at most: neither counting by waves nor exact ranges, which cost there what they save (find_last_key).
+    auto valid = [&](int u) { return tid < f0 - u * kSelectThreads; };
+    LastKey last;
+    if (rows <= 2) {
+      const uint32_t two[2] = {key[0], key[1]};
+      last = find_last_key<false>(two, f0 / kSelectThreads, rows, valid, static_cast<uint32_t>(kc), reg_shared);
+    } else {
+      last = find_last_key(key, f0 / kSelectThreads, rows, valid, static_cast<uint32_t>(kc), reg_shared);
+    }
     // Cell (row u, wave w) covers the 64 pages from 1024 u + 64 w on; it counts its keys above the last bin (low half) and in
     // it.  A taken page's place: keys above before it + keys in the bin before it, of these at most as many as are taken.
     const uint32_t top = last.base + last.span;
