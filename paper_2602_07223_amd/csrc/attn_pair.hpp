@@ -4,7 +4,7 @@
 // log-sum-exps for Eq. 2 / Eq. 3, or the token sums of the logit metric), but a wave serves 64 query rows from ONE read
 // of K and V.  Two row blocks leave no registers for tiles in flight (128 accumulators), so K and V never pass through
 // registers on their way in: they are loaded straight into LDS.
-//   * A workgroup = 4 waves on one (sequence, KV head, chunk); every wave takes a contiguous quarter of the chunk's
+//   * A workgroup = 4 waves (8: pair_waves) on one (sequence, KV head, chunk); every wave takes a contiguous part of the chunk's
 //     32-token tiles and owns a ring of LDS (2 tiles, or 4 at head dimension 64; pair_ring) that only it
 //     fills and reads, so the streaming loop has no barrier and no wave waits for another one.
 //   * K goes into a ring slot as soon as the first contraction has read the slot's old K, V as soon as the second one
@@ -50,8 +50,19 @@ constexpr int kPairRows = 64;               // query rows (of one KV head) of a 
 // 1000..8000, 80 rows, 8 KV heads 132.2 -> 110.6, 16 of 4000..16000, 64 rows, 4 KV heads 101.1 -> 77.8.  (Of page values
 // only two tiles could be parked beside 64 rows, and short bursts are what slows the reads.)
 constexpr bool pair_two_per_cu(int D, int collect) { return D == 64 && collect != 1; }
-// Bytes of K and V tiles per wave.
+// Bytes of K and V tiles per wave, where there are kPairWaves of them.
 constexpr int pair_ring(int D, int collect) { return pair_two_per_cu(D, collect) ? 16 * 1024 : 32 * 1024; }
+// Waves of a workgroup that parks page values at head dimension 64 and so has its compute unit to itself.  One wave per SIMD
+// leaves a tile's chain (first contraction, maximum, exponentials, second contraction: 1.3 us) nothing to run beside; two halve the
+// ring and what is parked per wave (two tiles instead of four).  `share`: tokens of the call's bound per compute unit.  One row
+// block is bound by HBM in long streams, where the deeper rings win, and by the merge of the waves in the shortest; siblings, of
+// which one reads from the L2, are bound by the chain at any size.  us a call, four waves / eight, 8 KV heads: 40 rows, one sequence
+// of 4096 15.5 / 16.5; 6000 16.7 / 16.1; 16384 23.0 / 21.5; 32768 29.6 / 27.6 (the kernel 22.8 / 19.7); 65536 41.7 / 41.9; 131072
+// 67 / 71; 16 of 8192..65536 251 / 286; 12 of 375..1500 21.6 / 20.3; 64 rows, 4 of 4000..8000 31.1 / 29.4, of 12000..24000 51.7 /
+// 52.1; 96 rows, one of 12000 32.8 / 32.7, 32768 47.0 / 38.7, 131072 122 / 101; 12 of 12500..50000 324 / 274.
+constexpr int pair_waves(int D, int collect, int row_blocks, int64_t share) {
+  return D == 64 && collect == 1 && (row_blocks > 1 || (share > 128 && share <= 2048)) ? 2 * kPairWaves : kPairWaves;
+}
 // What a second launch wave costs, in units of 128 tokens (see wants_second_wave): nothing where two workgroups fit.
 constexpr int pair_second_cost(int D, int collect) { return pair_two_per_cu(D, collect) ? 0 : 11; }
 constexpr int kPairFold = 32768;           // chunks per round of a folded grid
@@ -89,9 +100,9 @@ __device__ __forceinline__ void wait_vm() {
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // ONE: all rows fit one workgroup, which is then the only reader of its K/V lines (non-temporal loads); otherwise sibling
-// workgroups read them too and want to find them in the L2.
-template <int COLLECT, int D, bool ONE>
-__global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPLIT_HOT_PARAMS, const SplitParams pfull) {
+// workgroups read them too and want to find them in the L2.  NW: waves, kPairWaves or twice as many (pair_waves).
+template <int COLLECT, int D, bool ONE, int NW = kPairWaves>
+__global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(VEGAS_SPLIT_HOT_PARAMS, const SplitParams pfull) {
   VEGAS_TL_DECL;                             // (profiling builds: per-wave phase stamps, see vegas_common.hpp)
   VEGAS_TL(kTlEntry);
   SplitParams p = pfull;                     // (see attn_split_kernel: the preloaded arguments)
@@ -100,11 +111,10 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
   // Dynamic LDS (pair_lds): [ring of every wave][queries][collected values of every wave][row maxima][row sums]; the
   // merge buffer aliases everything before the row maxima.
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  constexpr int NW = kPairWaves;
   constexpr int NB = 2;                      // 32-row blocks of a wave
   constexpr int CH = D / 8;                  // 16-byte pieces of a K/V row
   constexpr int TPI = 64 / CH;               // token rows of one load instruction
-  constexpr int kRing = pair_ring(D, COLLECT);
+  constexpr int kRing = pair_ring(D, COLLECT) * kPairWaves / NW;
   constexpr int NP = kPage / TPI;            // load instructions per page (of K, of V)
   constexpr int NL = 2 * NP;                 // ... per tile
   constexpr int NBLK = D / 32;               // 32-wide blocks of the output's head dimension
@@ -170,7 +180,7 @@ __global__ __launch_bounds__(kPairWaves * 64, 2) void attn_pair_kernel(VEGAS_SPL
   VEGAS_TL(kTlLength);
   const int c1 = min(c0 + chunk_tokens, n);
   const int nblk = (n + kPage - 1) / kPage;
-  // A wave's tiles are a contiguous quarter of the chunk's: what it collects is contiguous too.
+  // A wave's tiles are a contiguous part of the chunk's: what it collects is contiguous too.
   const int chunk_tiles = (c1 - c0 + kTile - 1) / kTile;
   const int tile_first = c0 / kTile + chunk_tiles * wave / NW;
   const int ntiles = c0 / kTile + chunk_tiles * (wave + 1) / NW - tile_first;
@@ -572,20 +582,20 @@ struct PairLds {
   size_t bytes, off_max;
   int park_tiles;
 };
-inline PairLds pair_lds(int R, int Rc, int row_blocks, int collect, int D) {
+inline PairLds pair_lds(int R, int Rc, int row_blocks, int collect, int D, int waves = kPairWaves) {
   const size_t q = static_cast<size_t>(row_blocks == 1 ? R + (collect == 2 ? 2 : 0) : kPairRows) * row_pitch(D);
-  const size_t rows_ml = 2 * static_cast<size_t>(kPairWaves) * kPairRows * sizeof(float);
+  const size_t rows_ml = 2 * static_cast<size_t>(waves) * kPairRows * sizeof(float);
   size_t before = kPairWaves * pair_ring(D, collect) + q;
   PairLds l = {0, 0, 0};
   if (collect != 0) {
     const size_t tile = sizeof(float) * pair_park_floats(1, Rc, collect);
     const size_t room = (pair_two_per_cu(D, collect) ? 80 : 160) * 1024;
-    l.park_tiles = static_cast<int>((room - rows_ml - before) / (kPairWaves * tile));
+    l.park_tiles = static_cast<int>((room - rows_ml - before) / (waves * tile));
     if (l.park_tiles > 64) l.park_tiles = 64;
     if (tile % 16) l.park_tiles &= ~1;       // (an odd number of collected rows: tiles of 8 bytes more than a multiple of 16)
-    before += kPairWaves * tile * l.park_tiles;
+    before += waves * tile * l.park_tiles;
   }
-  const size_t red = static_cast<size_t>(kPairWaves) * (R < kPairRows ? R : kPairRows) * red_pitch(D) * sizeof(float);
+  const size_t red = static_cast<size_t>(waves) * (R < kPairRows ? R : kPairRows) * red_pitch(D) * sizeof(float);
   if (red > before) before = red;
   l.off_max = (before + 15) / 16 * 16;
   l.bytes = l.off_max + rows_ml;

@@ -62,6 +62,7 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 struct SplitPlan {
   int R = 0, Rc = 0, NB = 0, NW = 0, chunk = 0, nsplit = 0, lse_pages = 0;   // Rc: collected rows per KV head
   bool pair = false;                 // verification of more than 32 rows per KV head: 64-row workgroups (attn_pair_kernel)
+  int pair_waves = kPairWaves;       // its waves
   bool balanced = false;             // chunk lengths per sequence, computed on the GPU from the lengths (ragged batches)
   BatchPlan bp;                      // balanced: numbers of workgroups, in units of kTile * NW tokens
   size_t off_plan = 0;               // balanced: [B] (first slot, chunk tokens)
@@ -196,6 +197,7 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
     pl->chunk = collect != 0 && !pl->pair ? cap : unit;         // sizes the LDS that parks a chunk's collected values
     slots = static_cast<size_t>(d->num_kv_heads) * pl->bp.JS;   // (sibling row blocks share a slot)
   }
+  if (pl->pair) pl->pair_waves = pair_waves(d->head_dim, collect, pl->NB, static_cast<int64_t>(d->batch) * max_len * per_head / num_cu);
   pl->lse_pages = collect == 1 ? (max_len + kPage - 1) / kPage
                                : (collect == 2 ? (pl->balanced ? (max_len + unit - 1) / unit * unit : pl->nsplit * chunk) : 0);
   size_t off = 0;
@@ -268,7 +270,7 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
   if constexpr (CAUSAL) {
     if (pl.pair) {
       const unsigned slots = pl.balanced ? pl.bp.JS : pl.nsplit, seqs = pl.balanced ? 1 : batch;
-      const PairLds lds = pair_lds(pl.R, pl.Rc, pl.NB, COLLECT, D);
+      const PairLds lds = pair_lds(pl.R, pl.Rc, pl.NB, COLLECT, D, pl.pair_waves);
       sp.row_blocks = pl.NB;
       sp.lds_q_off = static_cast<int32_t>(lds.off_max);
       sp.park_tiles = lds.park_tiles;
@@ -276,7 +278,7 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
       // A wave parks a tile every 2.7 us (1.35 at head dimension 64) where HBM bounds the stream; the interval ends when
       // its LDS is three quarters full, so that the faster compute units seldom have to write before it does (16 x 36864
       // tokens, 40 rows, 15 tiles: 60 % 434 us, 75 % 430, 95 % 440, 140 % 446; without collection 395).
-      const double ticks = 0.75 * lds.park_tiles * (D == 128 ? 270 : 135);
+      const double ticks = 0.75 * lds.park_tiles * (D == 128 ? 270 : 135) * pl.pair_waves / kPairWaves;
       sp.epoch_mul = static_cast<uint32_t>(4294967296.0 / (ticks < 256 ? 256 : ticks));
       dim3 pgrid(sp.Hkv, pl.NB * slots, seqs);
       // Chunks are a dimension of the grid, and the interface's limit on them (vegas.h, kv_chunk_tokens) counts 32-row
@@ -289,8 +291,15 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
         pgrid.y = kPairFold;
         if (pgrid.z > 65535u) return VEGAS_ERR_UNSUPPORTED;
       }
-      if (pl.NB == 1) return launch_one(attn_pair_kernel<COLLECT, D, true>, pgrid, dim3(kPairWaves * 64), lds.bytes, st, sp);
-      return launch_one(attn_pair_kernel<COLLECT, D, false>, pgrid, dim3(kPairWaves * 64), lds.bytes, st, sp);
+      const dim3 block(pl.pair_waves * 64);
+      if constexpr (pair_waves(D, COLLECT, 2, 0) != kPairWaves) {
+        if (pl.pair_waves != kPairWaves) {
+          if (pl.NB == 1) return launch_one(attn_pair_kernel<COLLECT, D, true, 2 * kPairWaves>, pgrid, block, lds.bytes, st, sp);
+          return launch_one(attn_pair_kernel<COLLECT, D, false, 2 * kPairWaves>, pgrid, block, lds.bytes, st, sp);
+        }
+      }
+      if (pl.NB == 1) return launch_one(attn_pair_kernel<COLLECT, D, true>, pgrid, block, lds.bytes, st, sp);
+      return launch_one(attn_pair_kernel<COLLECT, D, false>, pgrid, block, lds.bytes, st, sp);
     }
   }
   // (KV head, row block + NB * chunk, sequence): the kernels read their indices off the grid without a division
@@ -507,6 +516,7 @@ int for_each_lds_kernel(F f) {
     one(attn_pair_kernel<1, D, true>); one(attn_pair_kernel<1, D, false>);
     one(attn_pair_kernel<2, D, true>); one(attn_pair_kernel<2, D, false>);
   };
+  one(attn_pair_kernel<1, 64, true, 2 * kPairWaves>); one(attn_pair_kernel<1, 64, false, 2 * kPairWaves>);
   per_dim(std::integral_constant<int, 128>{});
   per_dim(std::integral_constant<int, 64>{});
   one(verify_finalize_kernel<16, 0>); one(verify_finalize_kernel<32, 0>);
