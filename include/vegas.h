@@ -273,6 +273,21 @@ int vegas_draft_attention(const vegas_desc* desc, const void* q, const void* k_c
                           void* out, void* workspace, size_t workspace_bytes, void* hip_stream);
 
 /*
+ * One step of a live drafting phase (Sec. 2.3, Sec. 3.2 last sentence): vegas_append_kv_extend(cache_desc, ..., num_new = 1, ...,
+ * sel_page_size = desc->page_size, ...) followed by vegas_draft_attention(desc, ...), with the results of the two calls, bit for
+ * bit, and their arguments and refusals (nothing is launched where either would refuse).  Where the draft call is cut into chunks
+ * of 16-token pages, the append and the growth ride along in its two launches.
+ *   cache_desc             describes the cache and block_table (max_seq_len: how long a sequence may become)
+ *   desc                   the draft call's; page_size 16 or 1; batch, KV heads, head_dim, max_sel_blocks and the token and head
+ *                          strides are cache_desc's (VEGAS_ERR_SHAPE)
+ *   k_new / v_new  bf16 [B, H_kv, D]   the drafted token's rows; must not overlap the caches
+ *   workspace              vegas_workspace_bytes(desc) bytes or more
+ */
+int vegas_draft_step(const vegas_desc* cache_desc, const vegas_desc* desc, const void* q, const void* k_new, const void* v_new,
+                     const int32_t* block_table, int32_t* seq_lens, void* k_cache, void* v_cache, int32_t* sel_table,
+                     int32_t* sel_seq_lens, void* out, void* workspace, size_t workspace_bytes, void* hip_stream);
+
+/*
  * vegas_draft_attention for callers that cannot allocate device memory or carry a workspace around: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same
  * kernels and bit-identical results, but the chunk partials live in a scratch array inside the library's

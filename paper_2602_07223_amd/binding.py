@@ -40,7 +40,7 @@ STAGE_MERGE = 2
 
 EXPORTS = ("vegas_init", "vegas_workspace_bytes", "vegas_verify_attention", "vegas_select_blocks",
            "vegas_select_tokens", "vegas_append_kv", "vegas_append_kv_extend", "vegas_extend_selection", "vegas_draft_attention",
-           "vegas_draft_attention_static", "vegas_static_scratch_bytes",
+           "vegas_draft_step", "vegas_draft_attention_static", "vegas_static_scratch_bytes",
            "vegas_debug_verify_attention_stages", "vegas_debug_draft_attention_stages", "vegas_debug_stream_read",
            "vegas_debug_check_tables", "vegas_debug_set_timeline", "vegas_strerror")
 
@@ -110,6 +110,8 @@ def load_library(path: Optional[str] = None):
     lib.vegas_extend_selection.argtypes = [D, P, P, ctypes.c_int32, P, P, P]
     lib.vegas_draft_attention.restype = ctypes.c_int
     lib.vegas_draft_attention.argtypes = [D, P, P, P, P, P, P, P, ctypes.c_size_t, P]
+    lib.vegas_draft_step.restype = ctypes.c_int
+    lib.vegas_draft_step.argtypes = [D, D, P, P, P, P, P, P, P, P, P, P, P, ctypes.c_size_t, P]
     lib.vegas_draft_attention_static.restype = ctypes.c_int
     lib.vegas_draft_attention_static.argtypes = [D, P, P, P, P, P, P, P]
     lib.vegas_static_scratch_bytes.restype = ctypes.c_size_t
@@ -328,6 +330,25 @@ def vegas_draft_attention(desc: VegasDesc, q, k_cache, v_cache, sel_table, sel_s
         rc = load_library().vegas_draft_attention(*args)
     if rc != VEGAS_OK:
         raise VegasError(rc, "vegas_draft_attention")
+
+
+def vegas_draft_step(cache_desc: VegasDesc, desc: VegasDesc, q, k_new, v_new, block_table, seq_lens, k_cache, v_cache, sel_table,
+                     sel_seq_lens, out, workspace, stream=None, workspace_bytes: Optional[int] = None) -> None:
+    """vegas_append_kv_extend of one token (cache_desc) and vegas_draft_attention (desc) in one call (see include/vegas.h)."""
+    wb = workspace_bytes if workspace_bytes is not None else (_nbytes(workspace) if workspace is not None else 0)
+    if not (isinstance(q, int) and isinstance(k_cache, int)):
+        d, c = desc, cache_desc
+        rows, new = d.batch * d.num_q_heads * d.head_dim * 2, c.batch * c.num_kv_heads * c.head_dim * 2
+        extent = max(cache_extent_bytes(d), cache_extent_bytes(c))
+        _check_extents("vegas_draft_step", q=(q, rows), out=(out, rows), k_new=(k_new, new), v_new=(v_new, new),
+                       k_cache=(k_cache, extent), v_cache=(v_cache, extent), block_table=(block_table, c.batch * c.max_blocks * 4),
+                       seq_lens=(seq_lens, c.batch * 4), sel_table=(sel_table, d.batch * d.max_sel_blocks * 4),
+                       sel_seq_lens=(sel_seq_lens, d.batch * 4))
+    rc = load_library().vegas_draft_step(ctypes.byref(cache_desc), ctypes.byref(desc), _ptr(q), _ptr(k_new), _ptr(v_new),
+                                         _ptr(block_table), _ptr(seq_lens), _ptr(k_cache), _ptr(v_cache), _ptr(sel_table),
+                                         _ptr(sel_seq_lens), _ptr(out), _ptr(workspace), wb, _stream(stream))
+    if rc != VEGAS_OK:
+        raise VegasError(rc, "vegas_draft_step")
 
 
 def vegas_static_scratch_bytes() -> int:

@@ -81,14 +81,21 @@ inline size_t draft16_lds_bytes(int R, int D) {
 // us without the hint and 86 with it: what bounds the kernel then is HBM.  Whole lines alone change nothing.
 // (The choice costs up to 1 us: 8 x 2048 tokens under a bound of 16384 43.6 -> 44.5, 16 x 200..8192 59.9 -> 60.5; taking the bound for
 // the length cost 55.5 and 66.5.)
-template <int D, int PS = 4, bool CHOOSE = false>
-__global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS_SPLIT_HOT_PARAMS, const SplitParams pfull) {
+// Step: DraftStep in a draft step of a live drafting phase (16-token pages).  The new token's rows come from k_new and v_new instead of the
+// cache: the wave that has the selection's last tile puts them in place of what it read there, so no launch has to go before this
+// one, and the first workgroup of every KV head writes them into the cache for later calls.  Every workgroup works out for itself,
+// from the lengths before the step, whether the sequence has room and how long the selection is; the lengths are stored by the
+// merge, which reads copies of them.  (Figures: vegas_draft_step.)
+template <int D, int PS = 4, bool CHOOSE = false, typename... Step>
+__global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS_SPLIT_HOT_PARAMS, const SplitParams pfull, const Step... step) {
   VEGAS_TL_DECL;
   VEGAS_TL(kTlEntry);
   SplitParams p = pfull;                     // (see attn_split_kernel: the preloaded arguments)
   VEGAS_SPLIT_HOT_ASSIGN(p);
   static_assert(D == 128 || D == 64, "head dimension");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  constexpr bool APPEND = sizeof...(Step) == 1;
+  static_assert(!APPEND || (PS == 4 && !CHOOSE), "draft steps: 16-token pages through the cache");
   constexpr int NW = kDraftWaves;
   constexpr int KK = D / 32;                 // steps of the first contraction = K loads per page
   constexpr int NBLK = D / 16;               // 16-wide blocks of the output = head dims one V load covers
@@ -134,6 +141,8 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   //      rest of the argument block is pulled in one go meanwhile (see attn_split_kernel)
   int first_entry = PS == 4 ? table_entry(0) : ids_entry(0);
   int n = p.lens[b];
+  int n_seq = 0;                             // the sequence's length (APPEND: its address takes the plan's place)
+  if constexpr (APPEND) n_seq = reinterpret_cast<const int32_t*>(p.plan)[b];
   u32x4 qreg[KK];
   {
     const unsigned char* qbase = uniform_ptr(reinterpret_cast<const unsigned char*>(
@@ -160,8 +169,43 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   if constexpr (PS == 4) pagevec = into_pool(first_entry);
   else ids_cur = into_pool(first_entry);
 
+  // ---- APPEND: room and growth as append_kv_kernel and extend_selection_row decide them
+  const int covered = n;
+  bool grows = false;
+  bool appends = false;                      // this thread moves 16 bytes of the new rows into the cache
+  int new_page = 0;
+  u32x4 new_piece = {0u, 0u, 0u, 0u};
+  constexpr int kPieces = D / 8;             // 16-byte pieces of a row
+  if constexpr (APPEND) {
+    const bool room = n_seq >= 0 && n_seq < the_one(step...).cap;
+    grows = room && covered > 0 && (covered - 1) / kPage + 1 + (n_seq % kPage == 0 ? 1 : 0) <= p.table_stride;
+    appends = room && split == 0 && tid < 2 * kPieces;
+    if (appends) {
+      new_page = the_one(step...).block_table[static_cast<int64_t>(b) * the_one(step...).max_blocks + n_seq / kPage];
+      const uint16_t* const rows = tid < kPieces ? the_one(step...).k_new : the_one(step...).v_new;
+      new_piece = *reinterpret_cast<const u32x4*>(rows + (static_cast<int64_t>(b) * p.Hkv + h) * D + tid % kPieces * 8);
+    }
+  }
+  auto append_row = [&]() {
+    if constexpr (APPEND) {
+      if (appends) {
+        uint16_t* const cache = const_cast<uint16_t*>(tid < kPieces ? p.k : p.v);
+        *reinterpret_cast<u32x4*>(cache + static_cast<int64_t>(into_pool(new_page)) * p.page_stride +
+                                  static_cast<int64_t>(n_seq % kPage) * p.token_stride + static_cast<int64_t>(h) * p.head_stride +
+                                  tid % kPieces * 8) = new_piece;
+      }
+      if ((h | split | tid) == 0) {
+        const int after = covered + (grows ? 1 : 0);
+        if (grows && n_seq % kPage == 0) the_one(step...).sel_table[static_cast<int64_t>(b) * p.table_stride + (covered - 1) / kPage + 1] = new_page;
+        the_one(step...).grown[b] = make_int2(appends ? n_seq + 1 : n_seq, after);
+        the_one(step...).sel_lens[b] = after;
+      }
+    }
+  };
+  if constexpr (APPEND) n += grows ? 1 : 0;
   n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
   if (c0 >= n) {                             // nothing to do, no partial is read
+    append_row();
     if (p.out_direct != nullptr) {           // no merge kernel follows: the rows of an empty sequence are zeros
       uint16_t* rows = out_rows();
       for (int e = tid; e < Rl * D; e += NW * 64) rows[e] = 0;
@@ -251,6 +295,20 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
           }
     };
 
+    // APPEND: the new token's rows in the layout of the loads, where the chunk holds the selection's end
+    u32x4 k_row[APPEND ? KK : 1];
+    VReg v_row = {};
+    const bool has_new = APPEND && grows && c1 == n && n == covered + 1;       // (not where max_tokens ends the selection before it)
+    if constexpr (APPEND) {
+      if (has_new) {
+        const int64_t row = (static_cast<int64_t>(b) * p.Hkv + h) * D;
+        const unsigned char* const k_at = uniform_ptr(reinterpret_cast<const unsigned char*>(the_one(step...).k_new + row));
+        const unsigned char* const v_at = uniform_ptr(reinterpret_cast<const unsigned char*>(the_one(step...).v_new + row));
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) k_row[kk] = gload<u32x4, false>(k_at, static_cast<uint32_t>(64 * kk + 16 * kg));
+        v_row = gload<VReg, false>(v_at, static_cast<uint32_t>(l16) * (2u * NBLK));
+      }
+    }
     u32x4 kr[2][KK];
     VReg va[8], vb[8];
     if constexpr (PS != 4) ids_pending = into_pool(ids_entry(1));     // (requested before tile 0's loads: it is back first)
@@ -272,6 +330,19 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
       constexpr bool has_next = decltype(has_next_tag)::value;
       const int tok0 = (tile_first + k * NW) * kTile;
       if constexpr (STREAM) exchange_k(kr);
+      if constexpr (APPEND) {
+        if (has_new && tok0 + kTile >= n) {    // the tile of the selection's last token, the new one
+#pragma unroll
+          for (int pg = 0; pg < 2; ++pg) {
+            if (tok0 + 16 * pg + l16 != n - 1) continue;
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) kr[pg][kk] = k_row[kk];
+          }
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (tok0 + 16 * (e >> 2) + 4 * kg + (e & 3) == n - 1) vcur[e] = v_row;
+        }
+      }
       f32x4 st[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};     // st[pg][r]: token 4 kg + r of page pg, row l16
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk)
@@ -449,6 +520,7 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
     }
   }
   stream_chunk(std::false_type{});
+  append_row();
 }
 
 }  // namespace vegas

@@ -55,7 +55,9 @@ struct RowMerge {
 // chunking, where a sequence has few of its head's slots and how many is known once the plan has been read: they, and
 // no others, are then requested together.  Many chunks take two passes: the (max, sum) pairs, fetched by one thread
 // each, then the partial rows.
-__global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p) {
+// Lengths: GrownLengths in a draft step, otherwise nothing.
+template <typename... Lengths>
+__global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p, const Lengths... lengths) {
   __shared__ float sw[128];
   __shared__ float sred[4];
   const int r = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
@@ -75,6 +77,7 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p
   const int s_lo = first_live_chunk(n, p.G, p.window, cs.chunk);   // earlier chunks were skipped (local masking)
   const int t = r / p.g, j = r % p.g;
   uint16_t* const out = p.out + ((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * T + tid;
+  if ((r | h | tid) == 0) (lengths.store(b), ...);
   if (cc.last < 0) {                         // an empty sequence: it may own no slot, so nothing is requested
     *out = 0;
     return;
@@ -130,8 +133,8 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p
   *out = float_to_bf16_bits(o);
 }
 
-template <int MAXS>
-__global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_HOT_PARAMS, const CombineParams pfull) {   // launched with D threads
+template <int MAXS, typename... Lengths>
+__global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_HOT_PARAMS, const CombineParams pfull, const Lengths... lengths) {   // launched with D threads
   CombineParams p = pfull;                   // what the requests depend on arrives preloaded in scalar registers
   VEGAS_COMBINE_HOT_ASSIGN(p);
   const int r = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
@@ -143,6 +146,7 @@ __global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_H
   rm.issue(p.part_ml + pbase * p.R + r, p.part_o + (pbase * p.R + r) * p.D, tid, p.R, cs.last, p.D);
   n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
   const int ns = (n + cs.chunk - 1) / cs.chunk;
+  if ((r | h | tid) == 0) (lengths.store(b), ...);
   const float o = rm.finish(ns, first_live_chunk(n, p.G, p.window, cs.chunk));
   const int t = r / p.g, j = r % p.g;
   p.out[((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * p.D + tid] = float_to_bf16_bits(o);

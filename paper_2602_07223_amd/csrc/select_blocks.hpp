@@ -540,7 +540,7 @@ __device__ __forceinline__ void extend_selection_row(const ExtendParams& p, int 
   const int P = p.page_size;
   int32_t* sel = p.sel_table + static_cast<int64_t>(b) * p.max_sel_blocks;
   const int32_t* table = p.block_table + static_cast<int64_t>(b) * p.max_blocks;
-  int count = (covered + P - 1) / P;
+  int count = (covered - 1) / P + 1;
   int added = 0;
   for (int i = n_new - p.num_new; i < n_new; ++i) added += (i >= 0 && i % P == 0) ? 1 : 0;
   if (count + added > p.max_sel_blocks) return;            // row full: left as it is

@@ -142,6 +142,31 @@ __device__ __forceinline__ void store_through(unsigned char* base, uint32_t off,
   asm volatile("global_store_dword %0, %1, %2 sc0 sc1\n\ts_nop 1" :: "v"(off), "v"(v), "s"(base) : "memory");
 }
 
+// A draft step: the drafted token's K/V rows enter the cache and the selection grows by it in the draft call's own launches
+// (attn_draft16_kernel with APPEND, then the merge).
+struct DraftStep {
+  const uint16_t* k_new;      // bf16 [B, Hkv, D]
+  const uint16_t* v_new;
+  const int32_t* block_table; // [B, max_blocks]
+  int32_t* sel_table;         // [B, table_stride]: SplitParams::table
+  int2* grown;                // [B] (length of the sequence, of the selection) after the step, for the merge to store
+  int32_t* sel_lens;          // [B] what the draft call reads, for the merge
+  int32_t max_blocks, cap;    // a sequence of `cap` tokens takes no more
+};
+// Where the merge of a draft step stores the lengths (one thread per sequence; nobody else in the merge reads or writes them).
+struct GrownLengths {
+  const int2* grown;          // DraftStep::grown
+  int32_t* seq_lens;
+  int32_t* sel_seq_lens;
+  __device__ __forceinline__ void store(int b) const {
+    const int2 to = grown[b];
+    seq_lens[b] = to.x;
+    sel_seq_lens[b] = to.y;
+  }
+};
+// (Both are an argument of their own, of the kernels of a draft step only: 64 bytes more for every kernel cost an iteration 0.5 us.)
+__device__ __forceinline__ const DraftStep& the_one(const DraftStep& s) { return s; }
+
 // Arguments of the KV-streaming attention kernel (verification and draft share it).
 struct SplitParams {
   const uint16_t* q;        // verify [B, G, Hq, D]; draft [B, Hq, D] (G = 1)

@@ -183,7 +183,7 @@ class VegasPath:
         then per draft step the new token's K/V is appended, the selection grows by it (Sec. 3.2, last sentence)
         and the draft call attends over the grown selection.  The live lengths are rewound first (one small device
         copy), so every iteration starts from the same state; the appended slots are simply overwritten.
-        fused: append and growth in one launch (vegas_append_kv_extend) instead of two calls."""
+        fused: append, growth and draft as one call (vegas_draft_step) instead of three."""
         st = self.stream()
         a, o = self._addrs(dl), self._own()
         dl.seq_lens_live.copy_(dl.seq_lens)
@@ -191,15 +191,14 @@ class VegasPath:
         self.select(dl, stream=st)
         sll = dl.seq_lens_live.data_ptr()
         row = dl.k_new[0].numel() * dl.k_new.element_size()
+        k_new, v_new = dl.k_new.data_ptr(), dl.v_new.data_ptr()
         for s in range(self.G):
             if fused:
-                vb.vegas_append_kv_extend(self.desc_append, dl.k_new.data_ptr() + s * row, dl.v_new.data_ptr() + s * row,
-                                          1, a["bt"], sll, a["k"], a["v"], o["st"], o["ssl"],
-                                          self.desc_extend.page_size, stream=st)
-            else:
-                vb.vegas_append_kv(self.desc_append, dl.k_new.data_ptr() + s * row, dl.v_new.data_ptr() + s * row, 1,
-                                   a["bt"], sll, a["k"], a["v"], stream=st)
-                vb.vegas_extend_selection(self.desc_extend, a["bt"], sll, 1, o["st"], o["ssl"], stream=st)
+                vb.vegas_draft_step(self.desc_append, self.desc_draft, a["qd"][s], k_new + s * row, v_new + s * row, a["bt"], sll,
+                                    a["k"], a["v"], o["st"], o["ssl"], o["od"][s], o["ws"], stream=st, workspace_bytes=o["wsn"])
+                continue
+            vb.vegas_append_kv(self.desc_append, k_new + s * row, v_new + s * row, 1, a["bt"], sll, a["k"], a["v"], stream=st)
+            vb.vegas_extend_selection(self.desc_extend, a["bt"], sll, 1, o["st"], o["ssl"], stream=st)
             self.draft(dl, s, st)
 
     def iteration(self, dl: DeviceLayer) -> None:
