@@ -10,7 +10,8 @@
 //     matrix-core time of the 32-row tile, 8 logits and 32 (D = 128) accumulators per lane instead of 16 and 64.
 //   * K needs no LDS: lane (token i, dim group kg) loads the 16 bytes K[i][32 kk + 8 kg ..] straight into the A
 //     operand's register layout (four lanes read 64 consecutive bytes of a token row).
-//   * Q needs no LDS and no barrier: lane (row n, kg) loads Q[n][32 kk + 8 kg ..] into the B operand's layout once.
+//   * Q needs no LDS and no barrier: lane (row n, kg) loads Q[n][32 kk + 8 kg ..] into the B operand's layout once (lanes of rows
+//     past the group's heads the last row again).
 //   * The softmax weights leave the first MFMA as P[token 4 kg + r of page pg][row n] in lane (n, kg): taking the
 //     second contraction's index as k = 8 kg + e <-> (page e / 4, token 4 kg + e % 4) makes {P of page 0, P of page 1}
 //     the B operand as it stands, and V is loaded to match: lane (m, kg) reads 16 bytes (D / 16 head dims from
@@ -114,6 +115,7 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   const int b = blockIdx.z;
   const int Rl = p.R;                        // rows of this KV head: one draft token, g heads (G = 1)
 
+  int last_page = 0;                         // (set below, from arguments that are not there yet)
   // Physical page ids of the wave's next 32 tiles in one register, lane (k, half) <-> page `half` of tile
   // tile_first + k NW, requested before the length is known (see attn_split_kernel).
   const int32_t* table = p.table + static_cast<int64_t>(b) * p.table_stride;
@@ -125,10 +127,7 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
     page = page < p.table_stride ? page : p.table_stride - 1;
     return table[page];
   };
-  auto into_pool = [&](int raw) -> int {
-    const int64_t ph = raw;
-    return static_cast<int>(ph < 0 ? 0 : (ph >= p.num_pages ? p.num_pages - 1 : ph));
-  };
+  auto into_pool = [&](int raw) -> int { return min(max(raw, 0), last_page); };
   auto load_pagevec = [&](int kbase) { pagevec = into_pool(table_entry(kbase)); };
   // Small pages: ids of the TP pages of this wave's tile k, lane e (mod TP) <-> page e of the tile.
   auto ids_entry = [&](int k) -> int {
@@ -138,27 +137,43 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   };
 
   // ---- one round trip for everything the preloaded arguments can address: table entry, length, query rows; the
-  //      rest of the argument block is pulled in one go meanwhile (see attn_split_kernel)
+  //      rest of the argument block is pulled in one go meanwhile (see attn_split_kernel).  No wave has another beside it here, so
+  //      every instruction before a request or after its arrival is time: no integer division (the group size is an argument),
+  //      no masked query loads, addresses ready but for the page id.  With the merge kernel's the same, one sequence of 32768
+  //      tokens 70.4 -> 69.0 us an iteration, 131072 157.2 -> 154.2.
   int first_entry = PS == 4 ? table_entry(0) : ids_entry(0);
-  int n = p.lens[b];
+  int zero = 0;
+  asm("" : "+v"(zero));                      // (a vector load: a scalar one would wait in line behind the argument block's)
+  int n = p.lens[b + zero];
   int n_seq = 0;                             // the sequence's length (APPEND: its address takes the plan's place)
-  if constexpr (APPEND) n_seq = reinterpret_cast<const int32_t*>(p.plan)[b];
+  if constexpr (APPEND) n_seq = reinterpret_cast<const int32_t*>(p.plan)[b + zero];
   u32x4 qreg[KK];
   {
     const unsigned char* qbase = uniform_ptr(reinterpret_cast<const unsigned char*>(
         p.q + (static_cast<int64_t>(b) * p.Hq + h * p.g) * D));
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
-      qreg[kk] = u32x4{0u, 0u, 0u, 0u};      // rows past the group's heads: zeros
-      if (l16 < Rl) qreg[kk] = gload<u32x4, false>(qbase, static_cast<uint32_t>(l16 * D + 32 * kk + 8 * kg) * 2u);
+      // (rows past the group's heads: copies of the last one, which nobody reads)
+      qreg[kk] = gload<u32x4, false>(qbase, static_cast<uint32_t>(min(l16, Rl - 1) * D + 32 * kk + 8 * kg) * 2u);
     }
   }
   int lane_len = 0;                          // length of sequence `lane` (the last one's beyond), used once the chunk is known to be live
   if constexpr (CHOOSE) lane_len = p.lens[min(lane, p.batch - 1)];
-  asm volatile("" : "+s"(p.k), "+s"(p.v), "+s"(p.page_stride), "+s"(p.token_stride), "+s"(p.head_stride),
-               "+s"(p.num_pages), "+s"(p.out_direct));
-  asm volatile("" : "+s"(p.max_tokens), "+s"(p.nsplit), "+s"(p.scale_log2e), "+s"(p.part_o), "+s"(p.part_ml));
-  asm volatile("" : "+v"(first_entry));
+  asm volatile("" : "+s"(p.k), "+s"(p.v), "+s"(p.page_stride), "+s"(p.token_stride), "+s"(p.head_stride), "+s"(p.num_pages),
+               "+s"(p.out_direct), "+s"(p.max_tokens), "+s"(p.nsplit), "+s"(p.scale_log2e), "+s"(p.part_o), "+s"(p.part_ml));
+  last_page = static_cast<int>(p.num_pages < INT32_MAX ? p.num_pages - 1 : INT32_MAX);     // (an id is an int32)
+  // What the first loads' addresses take besides page ids is worked out while those are on their way.
+  const int64_t head_off = static_cast<int64_t>(h) * p.head_stride;
+  const unsigned char* k_head = reinterpret_cast<const unsigned char*>(p.k + head_off);
+  const unsigned char* v_head = reinterpret_cast<const unsigned char*>(p.v + head_off);
+  uint64_t page_bytes = static_cast<uint64_t>(p.page_stride) * 2u;
+  const uint32_t ts_bytes = static_cast<uint32_t>(p.token_stride) * 2u;
+  uint32_t k_cached_off = static_cast<uint32_t>(l16) * ts_bytes + static_cast<uint32_t>(kg) * 16u;
+  uint32_t v_lane_off = static_cast<uint32_t>(4 * kg) * ts_bytes + static_cast<uint32_t>(l16) * (2u * NBLK);
+  asm volatile("" : "+v"(k_cached_off), "+v"(v_lane_off), "+s"(k_head), "+s"(v_head), "+s"(page_bytes), "+s"(last_page));
+  asm volatile("" : "+v"(first_entry), "+v"(n));
+  n = __builtin_amdgcn_readfirstlane(n);
+  if constexpr (APPEND) n_seq = __builtin_amdgcn_readfirstlane(n_seq);
   float* red = reinterpret_cast<float*>(smem);                     // [wave][row][D] (padded rows)
   float* sm_m = red + NW * Rl * kRedPitch;                         // [wave][16] row maxima
   float* sm_l = sm_m + NW * kDraftRows;                            // [wave][16] row sums
@@ -204,7 +219,7 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   };
   if constexpr (APPEND) n += grows ? 1 : 0;
   n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
-  if (c0 >= n) {                             // nothing to do, no partial is read
+  if (__builtin_expect(c0 >= n, 0)) {        // nothing to do, no partial is read
     append_row();
     if (p.out_direct != nullptr) {           // no merge kernel follows: the rows of an empty sequence are zeros
       uint16_t* rows = out_rows();
@@ -218,15 +233,12 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
 
   auto stream_chunk = [&](auto streamed) __attribute__((always_inline)) {
     constexpr bool STREAM = decltype(streamed)::value;
-    const int64_t head_off = static_cast<int64_t>(h) * p.head_stride;
-    const uint32_t ts_bytes = static_cast<uint32_t>(p.token_stride) * 2u;
     // K: token and byte of its row this lane fetches with load (pg, kk) before the lane exchange (see exchange_k)
     const int k_tok = STREAM ? l16 & 7 : l16;
     const uint32_t k_byte = static_cast<uint32_t>(kg) * 16u + (STREAM ? static_cast<uint32_t>(l16 >> 3) * 64u : 0u);
-    const uint32_t k_lane_off = static_cast<uint32_t>(k_tok) * ts_bytes + k_byte;
-    const uint32_t v_lane_off = static_cast<uint32_t>(4 * kg) * ts_bytes + static_cast<uint32_t>(l16) * (2u * NBLK);
-    auto page_base = [&](const uint16_t* cache, int ph) -> const unsigned char* {
-      return uniform_ptr(reinterpret_cast<const unsigned char*>(cache + static_cast<int64_t>(ph) * p.page_stride + head_off));
+    const uint32_t k_lane_off = STREAM ? static_cast<uint32_t>(k_tok) * ts_bytes + k_byte : k_cached_off;
+    auto page_base = [&](const unsigned char* head, int ph) -> const unsigned char* {
+      return uniform_ptr(head + static_cast<uint64_t>(static_cast<uint32_t>(ph)) * page_bytes);
     };
     // Small pages: byte address of token t (0..31, a per-lane value) of the tile whose page ids are in ids_cur.
     typedef const __attribute__((address_space(1))) unsigned char* gbytes;
@@ -257,8 +269,8 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
         return;
       }
       if ((k & 31) == 0 && k > 0) load_pagevec(k);
-      const unsigned char* kb0 = page_base(p.k, __builtin_amdgcn_readlane(pagevec, k & 31));
-      const unsigned char* kb1 = page_base(p.k, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31)));
+      const unsigned char* kb0 = page_base(k_head, __builtin_amdgcn_readlane(pagevec, k & 31));
+      const unsigned char* kb1 = page_base(k_head, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31)));
 #pragma unroll
       for (int pg = 0; pg < 2; ++pg)
 #pragma unroll
@@ -272,8 +284,8 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
         for (int e = 0; e < 8; ++e) vr[e] = gload_at<VReg, STREAM>(token_addr(p.v, 16 * (e >> 2) + 4 * kg + (e & 3)) + l16 * (2 * NBLK));
         return;
       }
-      const unsigned char* vb0 = page_base(p.v, __builtin_amdgcn_readlane(pagevec, k & 31));
-      const unsigned char* vb1 = page_base(p.v, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31)));
+      const unsigned char* vb0 = page_base(v_head, __builtin_amdgcn_readlane(pagevec, k & 31));
+      const unsigned char* vb1 = page_base(v_head, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31)));
 #pragma unroll
       for (int e = 0; e < 8; ++e)
         vr[e] = gload<VReg, STREAM>((e < 4 ? vb0 : vb1) + static_cast<uint32_t>(e & 3) * ts_bytes, v_lane_off);

@@ -34,7 +34,11 @@ struct RowMerge {
   // Chunks before s_lo were skipped by a call with local masking and hold nothing either.
   __device__ __forceinline__ float finish(int ns, int s_lo = 0) const {
     const int lane = threadIdx.x & 63;
-    const bool live = lane >= s_lo && lane < ns;
+    return finish(lane >= s_lo && lane < ns);
+  }
+  // The same for the chunks s whose lane s says `live`.
+  __device__ __forceinline__ float finish(bool live) const {
+    const uint64_t lives = __builtin_amdgcn_ballot_w64(live);
     const float ms = live ? mine[0] : -INFINITY;
     const float m = wave_max(ms);
     const float m_use = (m == -INFINITY) ? 0.f : m;
@@ -44,7 +48,7 @@ struct RowMerge {
 #pragma unroll
     for (int s = 0; s < MAXS; ++s) {
       const float ws = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s));
-      acc += (s >= s_lo && s < ns) ? ws * x[s] : 0.f;
+      acc += ((lives >> s) & 1u) ? ws * x[s] : 0.f;
     }
     return (L > 0.f) ? acc / L : 0.f;
   }
@@ -133,23 +137,30 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p
   *out = float_to_bf16_bits(o);
 }
 
+// (Uniform chunking.  A chunk is live if the sequence reaches it, no count is needed; a row's token comes from one reciprocal, r <
+// 128: integer divisions are two dozen instructions each, in a kernel of one round trip.)
 template <int MAXS, typename... Lengths>
-__global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_HOT_PARAMS, const CombineParams pfull, const Lengths... lengths) {   // launched with D threads
-  CombineParams p = pfull;                   // what the requests depend on arrives preloaded in scalar registers
-  VEGAS_COMBINE_HOT_ASSIGN(p);
+__global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_SMALL_PARAMS, const Lengths... lengths) {   // launched with D threads
   const int r = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x;
-  const ColumnSlots cs = column_slots(p.plan, p.slots_total, b, p.Hkv, p.nsplit, p.chunk_tokens);
-  const int64_t pbase = cs.off + static_cast<int64_t>(h) * cs.stride_h;
-  int n = p.lens[b];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int R = shape & 255, D = (shape >> 8) & 255, nsplit = shape >> 16;
+  const int64_t row = (static_cast<int64_t>(b) * Hkv + h) * nsplit * R + r;
+  int zero = 0;
+  asm("" : "+v"(zero));                      // (a vector load, the first to come back: the compiler puts a scalar one last)
+  int n = lens[b + zero];
   RowMerge<MAXS> rm;
-  rm.issue(p.part_ml + pbase * p.R + r, p.part_o + (pbase * p.R + r) * p.D, tid, p.R, cs.last, p.D);
-  n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
-  const int ns = (n + cs.chunk - 1) / cs.chunk;
+  rm.issue(part_ml + row, part_o + row * D, tid, R, nsplit - 1, D);
   if ((r | h | tid) == 0) (lengths.store(b), ...);
-  const float o = rm.finish(ns, first_live_chunk(n, p.G, p.window, cs.chunk));
-  const int t = r / p.g, j = r % p.g;
-  p.out[((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * p.D + tid] = float_to_bf16_bits(o);
+  const int t = static_cast<int>((static_cast<float>(r) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(g)));
+  const int64_t at = ((static_cast<int64_t>(b) * R + t * g) * Hkv + h * g + (r - t * g)) * D;
+  uint16_t* const dst = out + at + tid;
+  n = __builtin_amdgcn_readfirstlane(n);
+  n = n < 0 ? 0 : (n > max_tokens ? max_tokens : n);
+  int s_lo = 0;
+  if (window > 0) s_lo = first_live_chunk(n, R / g, window, chunk_tokens);
+  // (a chunk that starts past 2^31 tokens is behind every end)
+  const bool live = lane >= s_lo && static_cast<uint64_t>(static_cast<uint32_t>(lane)) * static_cast<uint32_t>(chunk_tokens) < static_cast<uint32_t>(n);
+  *dst = float_to_bf16_bits(rm.finish(live));
 }
 
 // Verification epilogue in ONE launch (a kernel boundary costs ~3 us on this GPU): workgroups

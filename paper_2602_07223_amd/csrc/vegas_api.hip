@@ -443,8 +443,7 @@ int launch_combine(const vegas_desc* d, const SplitPlan& pl, const SplitParams& 
   const dim3 grid(pl.R, sp.Hkv, d->batch);
   auto any = [&] { hipLaunchKernelGGL((attn_combine_kernel<Lengths...>), grid, dim3(cp.D), 0, st, cp, lengths...); };
   auto small = [&](auto maxs) {
-    hipLaunchKernelGGL((attn_combine_small_kernel<decltype(maxs)::value, Lengths...>), grid, dim3(cp.D), 0, st, VEGAS_COMBINE_HOT_ARGS(cp), cp,
-                       lengths...);
+    hipLaunchKernelGGL((attn_combine_small_kernel<decltype(maxs)::value, Lengths...>), grid, dim3(cp.D), 0, st, VEGAS_COMBINE_SMALL_ARGS(cp), lengths...);
   };
   if (pl.balanced) any();
   else if (pl.nsplit <= 8) small(std::integral_constant<int, 8>{});

@@ -246,11 +246,11 @@ enum {
 #endif
 
 // Leading kernel arguments of the streaming kernels: the fields of SplitParams that the first memory requests (page
-// ids, sequence length, query rows) depend on -- 14 dwords, all that can be preloaded.  Leading scalar arguments are preloaded into scalar registers when a wave starts
+// ids, sequence length, query rows) depend on (heads by way of the group size, which saves a division) -- 14 dwords, all that can be preloaded.  Leading scalar arguments are preloaded into scalar registers when a wave starts
 // (the library is built with kernel-argument preloading); the copies inside SplitParams are then not read.
 #define VEGAS_SPLIT_HOT_PARAMS                                                                                     \
   const int32_t *hot_table, const int32_t *hot_lens, int2 *hot_plan, const uint16_t *hot_q, int32_t hot_table_stride, \
-      int32_t hot_chunk_tokens, int32_t hot_Hkv, int32_t hot_row_blocks, int32_t hot_G, int32_t hot_Hq
+      int32_t hot_chunk_tokens, int32_t hot_Hkv, int32_t hot_row_blocks, int32_t hot_G, int32_t hot_g
 #define VEGAS_SPLIT_HOT_ASSIGN(p)            \
   do {                                       \
     (p).table = hot_table;                   \
@@ -262,13 +262,13 @@ enum {
     (p).Hkv = hot_Hkv;                       \
     (p).row_blocks = hot_row_blocks;         \
     (p).G = hot_G;                           \
-    (p).Hq = hot_Hq;                         \
-    (p).g = hot_Hq / hot_Hkv;                \
-    (p).R = hot_G * (p).g;                   \
+    (p).Hq = hot_Hkv * hot_g;                \
+    (p).g = hot_g;                           \
+    (p).R = hot_G * hot_g;                   \
   } while (0)
 #define VEGAS_SPLIT_HOT_ARGS(sp)                                                                                   \
   (sp).table, (sp).lens, (sp).plan, (sp).q, (sp).table_stride, (sp).chunk_tokens, (sp).Hkv, (sp).row_blocks, (sp).G, \
-      (sp).Hq
+      (sp).g
 
 struct CombineParams {
   const float* part_o;
@@ -282,25 +282,14 @@ struct CombineParams {
   int32_t slots_total;      // balanced chunking: partial slots per KV head
 };
 
-// Leading (preloaded) kernel arguments of the one-round-trip merge kernel: everything its requests depend on.
-#define VEGAS_COMBINE_HOT_PARAMS                                                                                   \
-  const float *hot_part_o, const float2 *hot_part_ml, const int32_t *hot_lens, const int2 *hot_plan, int32_t hot_R, \
-      int32_t hot_Hkv, int32_t hot_nsplit, int32_t hot_chunk_tokens, int32_t hot_D, int32_t hot_slots_total
-#define VEGAS_COMBINE_HOT_ASSIGN(p)          \
-  do {                                       \
-    (p).part_o = hot_part_o;                 \
-    (p).part_ml = hot_part_ml;               \
-    (p).lens = hot_lens;                     \
-    (p).plan = hot_plan;                     \
-    (p).R = hot_R;                           \
-    (p).Hkv = hot_Hkv;                       \
-    (p).nsplit = hot_nsplit;                 \
-    (p).chunk_tokens = hot_chunk_tokens;     \
-    (p).D = hot_D;                           \
-    (p).slots_total = hot_slots_total;       \
-  } while (0)
-#define VEGAS_COMBINE_HOT_ARGS(cp) \
-  (cp).part_o, (cp).part_ml, (cp).lens, (cp).plan, (cp).R, (cp).Hkv, (cp).nsplit, (cp).chunk_tokens, (cp).D, (cp).slots_total
+// Arguments of the one-round-trip merge kernel, all of them preloaded.  shape: rows per KV head (<= 128), head dimension << 8,
+// chunks per column (<= 64) << 16.
+#define VEGAS_COMBINE_SMALL_PARAMS                                                                                  \
+  const float *part_o, const float2 *part_ml, const int32_t *lens, uint16_t *out, int32_t shape, int32_t Hkv,       \
+      int32_t chunk_tokens, int32_t max_tokens, int32_t g, int32_t window
+#define VEGAS_COMBINE_SMALL_ARGS(cp)                                                                                \
+  (cp).part_o, (cp).part_ml, (cp).lens, (cp).out, (cp).R | (cp).D << 8 | (cp).nsplit << 16, (cp).Hkv, (cp).chunk_tokens, \
+      (cp).max_tokens, (cp).g, (cp).window
 
 // The rows of one KV head (row = t * g + j for verification token t, head j of the group) whose page log-sum-exps
 // are collected: all G g rows (Eq. 2), or the g rows of the first verification token and the g rows of the bonus
