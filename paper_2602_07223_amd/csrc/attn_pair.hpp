@@ -149,16 +149,18 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(VEGAS_SPLIT_HOT_P
   const int split = ONE ? yy : yy / p.row_blocks;
   int chunk_tokens = p.chunk_tokens;
   int c0 = split * chunk_tokens;
-  int64_t pbase = (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + split;   // this workgroup's partial slot
+  int slot = split;                          // this workgroup's partial slot, of the head's or the column's
+  int n = 0;                                 // the sequence's length: a plan brings it
   if (p.plan) {                              // balanced chunking: workgroup `split` of this head -> (sequence, tokens)
     const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2, p.share_group, p.slots_total,
                                           p.share_margin, pair_second_cost(D, COLLECT),
-                                          p.chunk_cap_units, p.chunk_unit, split, ((blockIdx.x | yy) == 0 && wave == 0) ? p.plan : nullptr);
+                                          p.chunk_cap_units, kTile * kPairWaves, split, ((blockIdx.x | yy) == 0 && wave == 0) ? p.plan : nullptr);
     if (bs.b < 0) return;
     b = __builtin_amdgcn_readfirstlane(bs.b);
     c0 = __builtin_amdgcn_readfirstlane(bs.c0);
     chunk_tokens = __builtin_amdgcn_readfirstlane(bs.chunk);
-    pbase = static_cast<int64_t>(h) * p.slots_total + __builtin_amdgcn_readfirstlane(bs.slot);
+    slot = __builtin_amdgcn_readfirstlane(bs.slot);
+    n = bs.n;
   }
   const int row0 = kPairRows * rb;           // first query row (of this KV head) of this workgroup
   const int Rl = max(min(kPairRows, p.R - row0), 0);   // valid rows (none in a block that only carries the sum rows)
@@ -173,29 +175,33 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(VEGAS_SPLIT_HOT_P
   constexpr int QI = kPairRows * CH / (NW * 64);
   u32x4 qraw[QI];
   const int qrows = ONE ? p.R + (COLLECT == 2 ? 2 : 0) : kPairRows;      // rows the query tile holds
-  if constexpr (COLLECT != 2) issue_query_loads<D, QI>(qraw, p, b, h, qrows, row0, Rl, tid, NW * 64);
-  int n = p.lens[b];
-  n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
-  if (c0 >= n) return;                       // whole workgroup: nothing to do, no partial is read
-  VEGAS_TL(kTlLength);
-  const int c1 = min(c0 + chunk_tokens, n);
-  const int nblk = (n + kPage - 1) / kPage;
-  // A wave's tiles are a contiguous part of the chunk's: what it collects is contiguous too.
-  const int chunk_tiles = (c1 - c0 + kTile - 1) / kTile;
-  const int tile_first = c0 / kTile + chunk_tiles * wave / NW;
-  const int ntiles = c0 / kTile + chunk_tiles * (wave + 1) / NW - tile_first;
+  const bool all_rows_here = COLLECT != 2 || ONE;
+  if (all_rows_here) issue_query_loads<D, QI>(qraw, p, b, h, row0, Rl, tid, NW * 64);
+  int zero = 0;
+  asm("" : "+v"(zero));                      // (see attn_split_kernel)
+  if (!p.plan) n = p.lens[b + zero];
+  // A wave's tiles are a contiguous part of the chunk's: what it collects is contiguous too.  Where they begin depends on the
+  // chunk's end, which is the sequence's in its last chunk only: the page ids of the others are requested beside the length.
+  int tile_first, ntiles;
+  auto place = [&](int end) {
+    const int chunk_tiles = (end - c0 + kTile - 1) / kTile;
+    tile_first = c0 / kTile + chunk_tiles * wave / NW;
+    ntiles = c0 / kTile + chunk_tiles * (wave + 1) / NW - tile_first;
+  };
+  int first_ids[2 * NS];                     // of the ring's first tiles
   auto page_id = [&](int k, int pg) -> int {           // page pg of this wave's tile k
     const int page = min(2 * (tile_first + k) + pg, p.table_stride - 1);
     return table[page];
   };
-
-  // ---- query rows -> LDS [rows][CH pieces of 16 B], padded rows (lanes of later rows work on a copy of the last one).
-  // COLLECT == 2: the last row block's rows Rl (high part) and Rl + 1 (low part) carry the sum of the collected rows.
-  // (Before the first tile is requested: the wait for the queries would count its loads.)
-  const bool has_extra = COLLECT == 2 && (ONE || rb == p.row_blocks - 1);
-  if constexpr (COLLECT == 2) load_queries_to_lds<D>(qlds, p, b, h, qrows, row0, Rl, has_extra, tid, NW * 64);
-  else store_queries_to_lds<D, QI>(qlds, qraw, qrows, tid, NW * 64);
-
+  auto request_ids = [&]() {
+#pragma unroll
+    for (int i = 0; i < 2 * NS; ++i) first_ids[i] = page_id(i >> 1, i & 1);
+  };
+  place(c0 + chunk_tokens);
+  request_ids();
+  // (the rest of the argument block in one go, and what follows from it, while these are on their way; see attn_split_kernel)
+  asm volatile("" : "+s"(p.k), "+s"(p.v), "+s"(p.page_stride), "+s"(p.token_stride), "+s"(p.head_stride), "+s"(p.num_pages),
+               "+s"(p.max_tokens), "+s"(p.nsplit));
   // ---- which 16 bytes of a page this lane fetches with each load instruction
   const int64_t head_off = static_cast<int64_t>(h) * p.head_stride;
   const uint32_t ts_bytes = static_cast<uint32_t>(p.token_stride) * 2u;
@@ -212,6 +218,30 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(VEGAS_SPLIT_HOT_P
       voff[i] = static_cast<uint32_t>(tok) * ts_bytes + static_cast<uint32_t>(piece) * 16u;
     }
   }
+#pragma unroll
+  for (int i = 0; i < NP; ++i) asm volatile("" : "+v"(koff[i]), "+v"(voff[i]));
+  if constexpr (NS == 2) asm volatile("" : "+v"(n), "+s"(first_ids[0]), "+s"(first_ids[1]), "+s"(first_ids[2]), "+s"(first_ids[3]));
+  else asm volatile("" : "+v"(n), "+s"(first_ids[0]), "+s"(first_ids[1]), "+s"(first_ids[2]), "+s"(first_ids[3]), "+s"(first_ids[4]),
+                    "+s"(first_ids[5]), "+s"(first_ids[6]), "+s"(first_ids[7]));
+  n = __builtin_amdgcn_readfirstlane(n);
+  n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
+  if (c0 >= n) return;                       // whole workgroup: nothing to do, no partial is read
+  const int64_t pbase = p.plan ? static_cast<int64_t>(h) * p.slots_total + slot : (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + slot;
+  VEGAS_TL(kTlLength);
+  const int c1 = min(c0 + chunk_tokens, n);
+  const int nblk = (n + kPage - 1) / kPage;
+  if (c1 != c0 + chunk_tokens) {
+    place(c1);
+    request_ids();
+  }
+
+  // ---- query rows -> LDS [rows][CH pieces of 16 B], padded rows (lanes of later rows work on a copy of the last one).
+  // COLLECT == 2: the last row block's rows Rl (high part) and Rl + 1 (low part) carry the sum of the collected rows.
+  // (Before the first tile is requested: the wait for the queries would count its loads.)
+  const bool has_extra = COLLECT == 2 && (ONE || rb == p.row_blocks - 1);
+  if (all_rows_here) store_queries_to_lds<D, QI>(qlds, qraw, qrows, tid, NW * 64);
+  else load_queries_to_lds<D>(qlds, p, b, h, qrows, row0, Rl, has_extra, tid, NW * 64);
+
   typedef const __attribute__((address_space(3))) unsigned char* lptr;
   const uint32_t ring_lds = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lptr)ring)));
   auto page_base = [&](const uint16_t* cache, int ph) -> const unsigned char* {
@@ -230,7 +260,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(VEGAS_SPLIT_HOT_P
 #pragma unroll
   for (int k = 0; k < NS; ++k) {
     if (k < ntiles) {
-      const int id0 = into_pool(page_id(k, 0)), id1 = into_pool(page_id(k, 1));
+      const int id0 = into_pool(first_ids[2 * k]), id1 = into_pool(first_ids[2 * k + 1]);
       load_k(k, id0, id1);
       load_v(k, id0, id1);
     }
@@ -243,7 +273,8 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(VEGAS_SPLIT_HOT_P
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     const int r = 32 * nb + l32;
-    limit[nb] = min(n - p.G + ((r < Rl) ? (row0 + r) / p.g : 0), c1 - 1);
+    const int t = static_cast<int>((static_cast<float>(row0 + min(r, max(Rl - 1, 0))) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(p.g)));
+    limit[nb] = min(n - p.G + t, c1 - 1);    // (rows past the valid ones: the last one's)
   }
   // ---- collection: index of this lane's rows among the collected ones (COLLECT 1), columns of the sum rows (COLLECT 2)
   int ci[NB];
@@ -320,6 +351,10 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(VEGAS_SPLIT_HOT_P
     parked = 0;
   };
   __syncthreads();                           // queries in LDS
+  if constexpr (COLLECT == 2 && ONE) {
+    add_query_sums<D>(qlds, p, Rl, tid);
+    __syncthreads();
+  }
   VEGAS_TL(kTlQueries);
 
   // ---- running state: lane (row, half) keeps the running maximum m (same in both halves), its half's partial sum l,

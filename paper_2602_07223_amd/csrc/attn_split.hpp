@@ -57,6 +57,23 @@ __device__ __forceinline__ float half_sum(float x) {
 constexpr int row_pitch(int D) { return 2 * D + 16; }
 constexpr int red_pitch(int D) { return D + 4; }
 
+// Eight head dims (16-byte piece `chunk`) of the sum rows: high part to query tile row `row`, low part to the next.
+template <int D>
+__device__ __forceinline__ void store_sum_rows(unsigned char* qlds, const float (&sum)[8], int row, int chunk) {
+  constexpr int pitch = row_pitch(D);
+  u32x4 hi, lo;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint16_t h0 = float_to_bf16_bits(sum[2 * e]), h1 = float_to_bf16_bits(sum[2 * e + 1]);
+    const uint16_t l0 = float_to_bf16_bits(sum[2 * e] - bf16_bits_to_float(h0));
+    const uint16_t l1 = float_to_bf16_bits(sum[2 * e + 1] - bf16_bits_to_float(h1));
+    hi[e] = static_cast<uint32_t>(h0) | (static_cast<uint32_t>(h1) << 16);
+    lo[e] = static_cast<uint32_t>(l0) | (static_cast<uint32_t>(l1) << 16);
+  }
+  *reinterpret_cast<u32x4*>(qlds + row * pitch + chunk * 16) = hi;
+  *reinterpret_cast<u32x4*>(qlds + (row + 1) * pitch + chunk * 16) = lo;
+}
+
 // Query rows of one KV head -> LDS [rows][D / 8 chunks of 16 B] with padded rows, by all `threads` threads of the
 // workgroup.  Tile row r holds row row0 + r of the head's R = G g rows (row = t g + j) for r < valid; later rows
 // are zero.  with_sums (the logit metric, Sec. 3.2 footnote / App. B): rows `valid` and `valid + 1` carry the sum of
@@ -97,17 +114,7 @@ __device__ __forceinline__ void load_queries_to_lds(unsigned char* qlds, const S
           }
         }
       }
-      u32x4 hi, lo;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint16_t h0 = float_to_bf16_bits(sum[2 * e]), h1 = float_to_bf16_bits(sum[2 * e + 1]);
-        const uint16_t l0 = float_to_bf16_bits(sum[2 * e] - bf16_bits_to_float(h0));
-        const uint16_t l1 = float_to_bf16_bits(sum[2 * e + 1] - bf16_bits_to_float(h1));
-        hi[e] = static_cast<uint32_t>(h0) | (static_cast<uint32_t>(h1) << 16);
-        lo[e] = static_cast<uint32_t>(l0) | (static_cast<uint32_t>(l1) << 16);
-      }
-      *reinterpret_cast<u32x4*>(qlds + valid * pitch + chunk * 16) = hi;
-      *reinterpret_cast<u32x4*>(qlds + (valid + 1) * pitch + chunk * 16) = lo;
+      store_sum_rows<D>(qlds, sum, valid, chunk);
       continue;
     }
     if (with_sums && row == valid + 1) continue;                             // written together with row `valid`
@@ -117,9 +124,10 @@ __device__ __forceinline__ void load_queries_to_lds(unsigned char* qlds, const S
 
 // The same copy in two phases, for the kernels' common case (no sum rows): the loads leave as soon as the workgroup
 // knows its sequence and head -- they depend on nothing else, so they travel together with the first page-table
-// request instead of after the first K/V requests -- and reach LDS later.  QI 16-byte pieces per thread.
+// request instead of after the first K/V requests -- and reach LDS later.  QI 16-byte pieces per thread; rows past the valid
+// ones (one at least) are copies of the last, which nobody reads: a masked load costs a branch and four moves.
 template <int D, int QI>
-__device__ __forceinline__ void issue_query_loads(u32x4 (&raw)[QI], const SplitParams& p, int b, int h, int rows, int row0,
+__device__ __forceinline__ void issue_query_loads(u32x4 (&raw)[QI], const SplitParams& p, int b, int h, int row0,
                                                   int valid, int tid, int threads) {
   constexpr int CH = D / 8;
   // Row r of the KV head is token t = r / g, head j = r % g of the group.  r < 128, so the quotient comes exactly
@@ -132,12 +140,9 @@ __device__ __forceinline__ void issue_query_loads(u32x4 (&raw)[QI], const SplitP
   for (int i = 0; i < QI; ++i) {
     const int idx = tid + i * threads;
     const int row = idx / CH, chunk = idx % CH;
-    raw[i] = u32x4{0u, 0u, 0u, 0u};
-    if (idx < rows * CH && row < valid) {
-      const int r = row0 + row;
-      const int t = static_cast<int>((static_cast<float>(r) + 0.5f) * rcp_g), j = r - t * p.g;
-      raw[i] = gload<u32x4, false>(base, static_cast<uint32_t>((t * p.Hq + j) * D + chunk * 8) * 2u);
-    }
+    const int r = row0 + min(row, valid - 1);
+    const int t = static_cast<int>((static_cast<float>(r) + 0.5f) * rcp_g), j = r - t * p.g;
+    raw[i] = gload<u32x4, false>(base, static_cast<uint32_t>((t * p.Hq + j) * D + chunk * 8) * 2u);
   }
 }
 template <int D, int QI>
@@ -148,8 +153,38 @@ __device__ __forceinline__ void store_queries_to_lds(unsigned char* qlds, const 
 #pragma unroll
   for (int i = 0; i < QI; ++i) {
     const int idx = tid + i * threads;
-    if (idx < rows * CH) *reinterpret_cast<u32x4*>(qlds + (idx / CH) * pitch + (idx % CH) * 16) = raw[i];
+    if (QI * threads == rows * CH || idx < rows * CH) *reinterpret_cast<u32x4*>(qlds + (idx / CH) * pitch + (idx % CH) * 16) = raw[i];
   }
+}
+
+// The sum rows of a workgroup that holds all of its KV head's rows in LDS (rows `valid` and `valid` + 1 of the query tile), from
+// there, by its first wave: 64 / CH lanes share a 16-byte piece and take every so many-th row.  A barrier goes before, one has to
+// follow.  (Read from memory again, eight rows at a time, they were three round trips behind the first K/V requests at 20 rows: the
+// first tile was done 4 us later than without them, now 1.2.  Token drafting at 32768 tokens 87.5 -> 83.2 us an iteration.)
+template <int D>
+__device__ __forceinline__ void add_query_sums(unsigned char* qlds, const SplitParams& p, int valid, int tid) {
+  constexpr int CH = D / 8;
+  constexpr int pitch = row_pitch(D);
+  if (tid >= 64) return;
+  const int chunk = tid & (CH - 1);
+  float sum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int c = tid / CH; c < p.Rc; c += 64 / CH) {
+    const u32x4 qv = *reinterpret_cast<const u32x4*>(qlds + collected_row(c, p.collect_rows, p.G, p.g) * pitch + chunk * 16);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      sum[2 * e] += bf16_bits_to_float(static_cast<uint16_t>(qv[e] & 0xFFFFu));
+      sum[2 * e + 1] += bf16_bits_to_float(static_cast<uint16_t>(qv[e] >> 16));
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {              // over the lanes CH apart
+    if constexpr (CH == 8)
+      sum[e] += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, sum[e]), 0x128, 0xf, 0xf, true));   // row_ror:8
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(sum[e]), __float_as_uint(sum[e]), false, false);
+    sum[e] = half_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+  }
+  if (tid < CH) store_sum_rows<D>(qlds, sum, valid, chunk);
 }
 
 // NW: waves per workgroup; WPS: waves per SIMD the register budget is sized for (2 -> at most
@@ -207,17 +242,19 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
   int b = blockIdx.z;
   int chunk_tokens = p.chunk_tokens;
   int c0 = split * chunk_tokens;
-  int64_t pbase = (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + split;   // this workgroup's partial slot
+  int slot = split;                          // this workgroup's partial slot, of the head's or the column's
+  int n = 0;                                 // the sequence's length: a plan brings it
   if constexpr (CAUSAL && PS == 4 && !LOCAL) {
     if (p.plan) {                            // balanced chunking: workgroup `split` of this head -> (sequence, tokens)
       const BalancedSlot bs = balanced_slot(p.lens, p.batch, p.max_tokens, p.slots_target, p.slots_target2, p.share_group,
-                                            p.slots_total, p.share_margin, 2, p.chunk_cap_units, p.chunk_unit, split,
+                                            p.slots_total, p.share_margin, 2, p.chunk_cap_units, kTile * NW, split,
                                             ((blockIdx.x | blockIdx.y) == 0 && wave == 0) ? p.plan : nullptr);
-      if (bs.b < 0) return;
-      b = bs.b;
-      c0 = bs.c0;
-      chunk_tokens = bs.chunk;
-      pbase = static_cast<int64_t>(h) * p.slots_total + bs.slot;
+      b = __builtin_amdgcn_readfirstlane(bs.b);
+      if (b < 0) return;
+      c0 = __builtin_amdgcn_readfirstlane(bs.c0);
+      chunk_tokens = __builtin_amdgcn_readfirstlane(bs.chunk);
+      slot = __builtin_amdgcn_readfirstlane(bs.slot);
+      n = bs.n;
     }
   }
   const int row0 = rb * 32;                  // first query row (of this KV head) handled here
@@ -256,20 +293,31 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
   //      (left to itself the compiler fetches it piecemeal, each piece with a wait of its own, several of them between
   //      the table's arrival and the first K/V request).  (3) The query loads follow.  (4) Only then is the table
   //      entry waited for -- pinned here, or the compiler sinks the request below the length's early exit and turns
-  //      two parallel trips into two consecutive ones.
+  //      two parallel trips into two consecutive ones.  The length is a vector load, since a scalar one is waited for at once, and a
+  //      plan brings it along.  With one wait for all of it, divisions by reciprocals and uniform values in scalar registers the
+  //      first tile is done 0.3 us earlier (0.6 in a planned call); 4 sequences of 1000..4000 tokens, 40 rows 26.3 -> 25.7 us a
+  //      call, 16 of 300..1500, 20 rows 22.8 -> 22.4.
   int first_entry = 0;
   if constexpr (PS == 4) first_entry = table_entry(0);
   else first_entry = ids_entry(0);
-  int n = p.lens[b];
+  int zero = 0;
+  asm("" : "+v"(zero));                      // (a vector load, waited for below: a scalar one is waited for at once)
+  if (!p.plan) n = p.lens[b + zero];
   // Query loads leave now (they depend on the sequence and the head only).
   constexpr int QI = (32 * CH + NW * 64 - 1) / (NW * 64);
   u32x4 qraw[QI];
-  if constexpr (COLLECT != 2) issue_query_loads<D, QI>(qraw, p, b, h, NB * 32, row0, Rl, tid, NW * 64);
-  asm volatile("" : "+s"(p.k), "+s"(p.v), "+s"(p.page_stride), "+s"(p.token_stride), "+s"(p.head_stride),
-               "+s"(p.num_pages), "+s"(p.out_direct));
-  asm volatile("" : "+s"(p.max_tokens), "+s"(p.lds_q_off), "+s"(p.nsplit), "+s"(p.scale_log2e), "+s"(p.part_o),
+  const bool all_rows_here = COLLECT != 2 || p.row_blocks == 1;
+  if (all_rows_here) issue_query_loads<D, QI>(qraw, p, b, h, row0, Rl, tid, NW * 64);
+  asm volatile("" : "+s"(p.k), "+s"(p.v), "+s"(p.page_stride), "+s"(p.token_stride), "+s"(p.head_stride), "+s"(p.num_pages),
+               "+s"(p.out_direct), "+s"(p.max_tokens), "+s"(p.lds_q_off), "+s"(p.nsplit), "+s"(p.scale_log2e), "+s"(p.part_o),
                "+s"(p.part_ml));
-  asm volatile("" : "+v"(first_entry));
+  if (all_rows_here) {                       // (they are back with the entry; behind the first tile the wait would count its loads)
+#pragma unroll
+    for (int i = 0; i < QI; ++i) asm volatile("" : "+v"(qraw[i]));
+  }
+  asm volatile("" : "+v"(first_entry), "+v"(n));
+  n = __builtin_amdgcn_readfirstlane(n);
+  const int64_t pbase = p.plan ? static_cast<int64_t>(h) * p.slots_total + slot : (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + slot;
   // Dynamic LDS: [K staging, NW tiles + page lse | merge buffer NW x R rows][queries][row maxima][row sums][page-id ring]
   unsigned char* qlds = smem + p.lds_q_off;
   float* sm_m = reinterpret_cast<float*>(qlds + NB * 32 * kRowPitch);
@@ -284,7 +332,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
   else ids_pending = into_pool(first_entry);
 
   n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
-  if (c0 >= n) {                             // whole workgroup: nothing to do, no partial is read
+  if (__builtin_expect(c0 >= n, 0)) {        // whole workgroup: nothing to do, no partial is read
     if (p.out_direct != nullptr) {           // no merge kernel follows: the rows of an empty sequence are zeros
       for (int e = tid; e < Rl * D; e += NW * 64) {
         const int r = row0 + e / D;
@@ -391,18 +439,24 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
   }
   VEGAS_TL(kTlLoadsIssued);
 
-  // ---- query rows -> LDS [row][CH chunks of 16 B], padded rows; rows past R are zero
+  // ---- query rows -> LDS [row][CH chunks of 16 B], padded rows
   // COLLECT == 2: the last row block carries the sum of the collected query rows in rows Rl (high part) and Rl + 1 (low part)
   const bool has_extra = COLLECT == 2 && rb == p.row_blocks - 1;
-  if constexpr (COLLECT == 2) load_queries_to_lds<D>(qlds, p, b, h, NB * 32, row0, Rl, has_extra, tid, NW * 64);
-  else store_queries_to_lds<D, QI>(qlds, qraw, NB * 32, tid, NW * 64);
+  if (all_rows_here) store_queries_to_lds<D, QI>(qlds, qraw, NB * 32, tid, NW * 64);
+  else load_queries_to_lds<D>(qlds, p, b, h, NB * 32, row0, Rl, has_extra, tid, NW * 64);
   int limit[NB];                             // last visible token of this lane's row
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
-    const int t = (l32 < Rl) ? (row0 + l32) / p.g : 0;
-    limit[nb] = CAUSAL ? (n - p.G + t) : (n - 1);
+    const int t = static_cast<int>((static_cast<float>(row0 + min(l32, max(Rl - 1, 0))) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(p.g)));
+    limit[nb] = CAUSAL ? (n - p.G + t) : (n - 1);          // (rows past the valid ones: the last one's)
   }
   __syncthreads();
+  if constexpr (COLLECT == 2) {
+    if (all_rows_here) {
+      add_query_sums<D>(qlds, p, Rl, tid);
+      __syncthreads();
+    }
+  }
   VEGAS_TL(kTlQueries);
 
   // ---- running state: lane (row, half) keeps the row max m (same in both halves), its half's

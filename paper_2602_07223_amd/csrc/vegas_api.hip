@@ -402,7 +402,7 @@ void fill_split_params(const vegas_desc* d, const SplitPlan& pl, int G, const vo
   sp->share_group = share_group(d->num_kv_heads * pl.NB);
   sp->chunk_cap_units = pl.bp.cap_units;
   sp->slots_total = pl.bp.JS;
-  sp->chunk_unit = kTile * pl.NW;
+  if (pl.balanced) sp->chunk_tokens = d->batch;                    // (VEGAS_SPLIT_HOT_ASSIGN)
   sp->max_tokens = d->max_seq_len;
   sp->page_stride = d->kv_page_stride;
   sp->token_stride = d->kv_token_stride;

@@ -69,8 +69,9 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x) {
 // own in its place.
 struct GpuWave {
   static __device__ __forceinline__ int lane() { return threadIdx.x & 63; }
-  static __device__ __forceinline__ uint32_t sum(uint32_t x) { return wave_sum(x); }
-  static __device__ __forceinline__ uint32_t max(uint32_t x) { return wave_max(x); }
+  // (in a scalar register: what follows from them are the same branches for all lanes)
+  static __device__ __forceinline__ uint32_t sum(uint32_t x) { return __builtin_amdgcn_readfirstlane(wave_sum(x)); }
+  static __device__ __forceinline__ uint32_t max(uint32_t x) { return __builtin_amdgcn_readfirstlane(wave_max(x)); }
   static __device__ __forceinline__ uint32_t prefix_sum(uint32_t x) { return wave_prefix_sum(x); }   // inclusive
   static __device__ __forceinline__ uint64_t ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
   static __device__ __forceinline__ uint32_t readlane(uint32_t x, int lane) { return __builtin_amdgcn_readlane(x, lane); }
@@ -181,7 +182,8 @@ struct SplitParams {
                             // the collected rows' q . k
   int32_t table_stride;
   int32_t G, g, R, Hq, Hkv;
-  int32_t chunk_tokens, nsplit, lse_pages, max_tokens;
+  int32_t chunk_tokens;     // tokens per chunk (a planned call's are the plan's: the batch, see the leading arguments below)
+  int32_t nsplit, lse_pages, max_tokens;
   int32_t lds_q_off;        // byte offset of the query tile inside dynamic LDS
   int32_t row_blocks;       // row blocks of one KV head (32 rows; attn_pair_kernel: 64), one workgroup each
   int32_t collect_rows;     // which verification rows are collected (1: all, 2: first and last)
@@ -201,7 +203,6 @@ struct SplitParams {
   int32_t share_group;      // so many consecutive workgroups of a head start on as many shader engines (a power of two)
   int32_t chunk_cap_units;  // longest chunk the plan may produce, in units
   int32_t slots_total;      // slots per KV head the workspace holds
-  int32_t chunk_unit;       // chunk lengths are multiples of this many tokens
   int64_t page_stride, token_stride, head_stride, num_pages;
   float scale_log2e;
   unsigned long long* timeline;   // profiling builds: where the waves' phase stamps go (nullptr: nowhere)
@@ -247,7 +248,8 @@ enum {
 
 // Leading kernel arguments of the streaming kernels: the fields of SplitParams that the first memory requests (page
 // ids, sequence length, query rows) depend on (heads by way of the group size, which saves a division) -- 14 dwords, all that can be preloaded.  Leading scalar arguments are preloaded into scalar registers when a wave starts
-// (the library is built with kernel-argument preloading); the copies inside SplitParams are then not read.
+// (the library is built with kernel-argument preloading); the copies inside SplitParams are then not read.  A planned call's
+// first request is for the lengths, so it has the batch where others have the chunk length.
 #define VEGAS_SPLIT_HOT_PARAMS                                                                                     \
   const int32_t *hot_table, const int32_t *hot_lens, int2 *hot_plan, const uint16_t *hot_q, int32_t hot_table_stride, \
       int32_t hot_chunk_tokens, int32_t hot_Hkv, int32_t hot_row_blocks, int32_t hot_G, int32_t hot_g
@@ -259,6 +261,7 @@ enum {
     (p).q = hot_q;                           \
     (p).table_stride = hot_table_stride;     \
     (p).chunk_tokens = hot_chunk_tokens;     \
+    if ((p).plan) (p).batch = hot_chunk_tokens; \
     (p).Hkv = hot_Hkv;                       \
     (p).row_blocks = hot_row_blocks;         \
     (p).G = hot_G;                           \
@@ -378,13 +381,19 @@ struct BalancedSlot {
   int32_t b;                    // sequence; < 0: workgroup j has nothing to do
   int32_t c0, chunk;            // its first token here, and how many follow (as far as the sequence reaches)
   int32_t slot;                 // partial slot of the KV head
+  int32_t n;                    // the sequence's length
 };
-// ceil(x / d) for 0 <= x < 2^23, 1 <= d < 2^23 (a float reciprocal and one correction step instead of an integer division)
+// floor and ceil of x / d for 0 <= x < 2^23, 1 <= d < 2^23 (a float reciprocal and one correction step instead of an integer
+// division, which is two dozen instructions)
 template <typename Wave>
-__host__ __device__ __forceinline__ uint32_t ceil_div_small(uint32_t x, uint32_t d) {
+__host__ __device__ __forceinline__ uint32_t floor_div_small(uint32_t x, uint32_t d) {
   uint32_t q = static_cast<uint32_t>(static_cast<float>(x) * Wave::rcp(static_cast<float>(d)));
   q = q * d > x ? q - 1u : q;                                   // (the estimate is off by one at most)
-  q = (q + 1u) * d <= x ? q + 1u : q;                           // q = floor(x / d)
+  return (q + 1u) * d <= x ? q + 1u : q;
+}
+template <typename Wave>
+__host__ __device__ __forceinline__ uint32_t ceil_div_small(uint32_t x, uint32_t d) {
+  const uint32_t q = floor_div_small<Wave>(x, d);
   return q * d < x ? q + 1u : q;
 }
 // Smallest C >= 1 (in units) with sum over lanes of ceil(nu / C) <= J; nu is this lane's length in units (< 2^18),
@@ -394,7 +403,7 @@ __host__ __device__ __forceinline__ uint32_t ceil_div_small(uint32_t x, uint32_t
 template <typename Wave>
 __host__ __device__ __forceinline__ uint32_t balanced_chunk_units(uint32_t nu, uint32_t total, uint32_t longest, uint32_t J) {
   auto fits = [&](uint32_t c) { return Wave::sum(ceil_div_small<Wave>(nu, c)) <= J; };
-  uint32_t lo = (total + J - 1u) / J;                           // wave-uniform from here on
+  uint32_t lo = ceil_div_small<Wave>(total, J);                 // wave-uniform from here on
   lo = lo < 1u ? 1u : lo;
   if (lo >= longest || fits(lo)) return lo < longest ? lo : longest;
   uint32_t step = (lo + 15u) / 16u, hi = lo + step;             // lo fails; find a length that fits
@@ -426,6 +435,7 @@ __host__ __device__ __forceinline__ bool wants_second_wave(uint32_t total, uint3
 __host__ __device__ __forceinline__ bool wants_shares(uint32_t priced, uint32_t lives, uint32_t J, uint32_t C, uint32_t margin) {
   return lives <= J && 10u * J * C > 11u * priced + 8u * lives && C >= (priced + J - 1u) / J + margin;
 }
+
 // slots: workgroups there are; share_margin: for wants_shares, or -1 for no shares; second_cost: for wants_second_wave.
 template <typename Wave = GpuWave>
 __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B, int max_tokens, int j1, int j2,
@@ -437,9 +447,9 @@ __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* le
     const int v = lens[lane];
     n = static_cast<uint32_t>(v < 0 ? 0 : (v > max_tokens ? max_tokens : v));
   }
-  const uint32_t nu = (n + unit - 1u) / unit;                   // length in units
+  const uint32_t nu = (n + unit - 1u) / unit;                   // length in units (a constant in the kernels)
   const uint32_t total = Wave::sum(nu);
-  BalancedSlot r = {-1, 0, unit, 0};
+  BalancedSlot r = {-1, 0, unit, 0, 0};
   if (total == 0u) {
     if (plan_out && lane < B) plan_out[lane] = make_int2(0, unit);
     return r;
@@ -448,12 +458,12 @@ __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* le
   const uint64_t live = Wave::ballot(nu > 0u);
   const uint32_t J = j1, lives = __builtin_popcountll(live);
   uint32_t C = balanced_chunk_units<Wave>(nu, total, longest, J);
-  const uint32_t priced = total + kShareCost * (lives - 1u), S = (priced + J - 1u) / J;
+  const uint32_t priced = total + kShareCost * (lives - 1u), S = ceil_div_small<Wave>(priced, J);
   if (share_margin >= 0 && S <= static_cast<uint32_t>(cap_units) && J + lives <= static_cast<uint32_t>(slots) + 1u &&
       wants_shares(priced, lives, J, C, static_cast<uint32_t>(share_margin))) {
     const uint32_t rank = __builtin_popcountll(live & ((1ull << lane) - 1ull));
     const uint32_t base = Wave::prefix_sum(nu) - nu + kShareCost * rank;       // where the sequence's first token lies
-    const uint32_t q = base / S, count = nu > 0u ? (base + nu - 1u) / S - q + 1u : 0u;
+    const uint32_t q = floor_div_small<Wave>(base, S), count = nu > 0u ? floor_div_small<Wave>(base + nu - 1u, S) - q + 1u : 0u;
     if (plan_out && lane < B) plan_out[lane] = nu > 0u ? make_int2(q + rank, -static_cast<int>(count)) : make_int2(0, unit);
     const uint32_t head = min(nu, (q + 1u) * S - base);                       // first piece (0 if empty); last one, where there
     const uint32_t tail = count > 1u ? nu - head - (count - 2u) * S : 0u;     // are several; whole shares between them
@@ -484,13 +494,14 @@ __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* le
     r.c0 = piece == 0u ? 0 : static_cast<int>((first + (piece - 1u) * S) * unit);
     r.chunk = static_cast<int>((piece == 0u ? first : S) * unit);
     r.slot = Wave::readlane(q + rank, r.b) + piece;
+    r.n = Wave::readlane(n, r.b);
     return r;
   }
   if (j2 > j1 && wants_second_wave(total, static_cast<uint32_t>(j1), C, static_cast<uint32_t>(second_cost)))
     C = balanced_chunk_units<Wave>(nu, total, longest, static_cast<uint32_t>(j2));
   C = min(C, static_cast<uint32_t>(cap_units));
-  const uint32_t s = (nu + C - 1u) / C;                         // chunks of this sequence (0 if empty)
-  const int chunk = s > 0u ? static_cast<int>((nu + s - 1u) / s * unit) : 0;   // equal chunks, at most C units
+  const uint32_t s = ceil_div_small<Wave>(nu, C);               // chunks of this sequence (0 if empty)
+  const int chunk = s > 0u ? static_cast<int>(ceil_div_small<Wave>(nu, s) * unit) : 0;   // equal chunks, at most C units
   int P = 0;                                                    // slots of the sequences with longer chunks
   for (int i = 0; i < B; ++i) {
     const int ci = Wave::readlane(chunk, i);
@@ -504,6 +515,7 @@ __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* le
   r.chunk = Wave::readlane(chunk, r.b);
   r.c0 = (j - Wave::readlane(P, r.b)) * r.chunk;
   r.slot = j;
+  r.n = Wave::readlane(n, r.b);
   return r;
 }
 
