@@ -273,8 +273,7 @@ __global__ __launch_bounds__(NW * 64, 2) void attn_pair_kernel(VEGAS_SPLIT_HOT_P
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     const int r = 32 * nb + l32;
-    const int t = static_cast<int>((static_cast<float>(row0 + min(r, max(Rl - 1, 0))) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(p.g)));
-    limit[nb] = min(n - p.G + t, c1 - 1);    // (rows past the valid ones: the last one's)
+    limit[nb] = min(n - p.G + ((r < Rl) ? (row0 + r) / p.g : 0), c1 - 1);
   }
   // ---- collection: index of this lane's rows among the collected ones (COLLECT 1), columns of the sum rows (COLLECT 2)
   int ci[NB];

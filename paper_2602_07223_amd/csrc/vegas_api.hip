@@ -300,14 +300,13 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
         if (pgrid.z > 65535u) return VEGAS_ERR_UNSUPPORTED;
       }
       const dim3 block(pl.pair_waves * 64);
-      if constexpr (pair_waves(D, COLLECT, 2, 0) != kPairWaves) {
-        if (pl.pair_waves != kPairWaves) {
-          if (pl.NB == 1) return launch_one(attn_pair_kernel<COLLECT, D, true, 2 * kPairWaves>, pgrid, block, lds.bytes, st, sp);
-          return launch_one(attn_pair_kernel<COLLECT, D, false, 2 * kPairWaves>, pgrid, block, lds.bytes, st, sp);
-        }
+      constexpr int kSiblingWaves = pair_waves(D, COLLECT, 2, 0);
+      if constexpr (kSiblingWaves != kPairWaves) {
+        if (pl.NB == 1 && pl.pair_waves != kPairWaves)
+          return launch_one(attn_pair_kernel<COLLECT, D, true, 2 * kPairWaves>, pgrid, block, lds.bytes, st, sp);
       }
       if (pl.NB == 1) return launch_one(attn_pair_kernel<COLLECT, D, true>, pgrid, block, lds.bytes, st, sp);
-      return launch_one(attn_pair_kernel<COLLECT, D, false>, pgrid, block, lds.bytes, st, sp);
+      return launch_one(attn_pair_kernel<COLLECT, D, false, kSiblingWaves>, pgrid, block, lds.bytes, st, sp);
     }
   }
   // (KV head, row block + NB * chunk, sequence): the kernels read their indices off the grid without a division
@@ -517,10 +516,10 @@ int for_each_lds_kernel(F f) {
     one(attn_draft16_kernel<D, 4, false>); one(attn_draft16_kernel<D, 4, true>);
     one(attn_draft16_kernel<D, 4, false, DraftStep>);
     one(attn_pair_kernel<0, D, true>); one(attn_pair_kernel<0, D, false>);
-    one(attn_pair_kernel<1, D, true>); one(attn_pair_kernel<1, D, false>);
+    one(attn_pair_kernel<1, D, true>); one(attn_pair_kernel<1, D, false, pair_waves(D, 1, 2, 0)>);
     one(attn_pair_kernel<2, D, true>); one(attn_pair_kernel<2, D, false>);
   };
-  one(attn_pair_kernel<1, 64, true, 2 * kPairWaves>); one(attn_pair_kernel<1, 64, false, 2 * kPairWaves>);
+  one(attn_pair_kernel<1, 64, true, 2 * kPairWaves>);
   per_dim(std::integral_constant<int, 128>{});
   per_dim(std::integral_constant<int, 64>{});
   one(verify_finalize_kernel<16, 0>); one(verify_finalize_kernel<32, 0>);
