@@ -65,6 +65,9 @@ __host__ __device__ __forceinline__ bool past_cache(uint64_t sixteens, int kv_he
 constexpr int kDraftWaves = 4;
 constexpr int kDraftRows = 16;     // query rows (of one KV head) a workgroup can take
 
+constexpr int kDraftRing = 32 * 1024;          // bytes of a wave's ring
+// Dynamic LDS of attn_draft16_kernel with rings; the merge's rows alias them.
+constexpr size_t draft_ring_lds_bytes() { return kDraftWaves * kDraftRing + 2 * kDraftWaves * kDraftRows * sizeof(float); }
 // Dynamic LDS of attn_draft16_kernel for R (<= 16) rows: the waves' rows for the merge, their row maxima and sums.
 inline size_t draft16_lds_bytes(int R, int D) {
   return static_cast<size_t>(kDraftWaves) * R * red_pitch(D) * sizeof(float) +
@@ -87,7 +90,10 @@ inline size_t draft16_lds_bytes(int R, int D) {
 // one, and the first workgroup of every KV head writes them into the cache for later calls.  Every workgroup works out for itself,
 // from the lengths before the step, whether the sequence has room and how long the selection is; the lengths are stored by the
 // merge, which reads copies of them.  (Figures: vegas_draft_step.)
-template <int D, int PS = 4, bool CHOOSE = false, typename... Step>
+// RING: K and V land in LDS, in a ring of two tiles per wave, instead of in registers: both are on their way from the start, where the
+// registers hold one and the next is asked for when the first contraction has used its K.  One workgroup to a compute unit, so what
+// bounds it is how much that unit has under way; the rule and its figures: ring_draft.
+template <int D, int PS = 4, bool CHOOSE = false, bool RING = false, typename... Step>
 __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS_SPLIT_HOT_PARAMS, const SplitParams pfull, const Step... step) {
   VEGAS_TL_DECL;
   VEGAS_TL(kTlEntry);
@@ -96,7 +102,8 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   static_assert(D == 128 || D == 64, "head dimension");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr bool APPEND = sizeof...(Step) == 1;
-  static_assert(!APPEND || (PS == 4 && !CHOOSE), "draft steps: 16-token pages through the cache");
+  static_assert(!APPEND || (PS == 4 && !CHOOSE && !RING), "draft steps: 16-token pages through the cache");
+  static_assert(!RING || (PS == 4 && !CHOOSE && D == 128), "rings: 16-token pages through the cache, head dimension 128");
   constexpr int NW = kDraftWaves;
   constexpr int KK = D / 32;                 // steps of the first contraction = K loads per page
   constexpr int NBLK = D / 16;               // 16-wide blocks of the output = head dims one V load covers
@@ -175,7 +182,7 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   n = __builtin_amdgcn_readfirstlane(n);
   if constexpr (APPEND) n_seq = __builtin_amdgcn_readfirstlane(n_seq);
   float* red = reinterpret_cast<float*>(smem);                     // [wave][row][D] (padded rows)
-  float* sm_m = red + NW * Rl * kRedPitch;                         // [wave][16] row maxima
+  float* sm_m = RING ? reinterpret_cast<float*>(smem + NW * kDraftRing) : red + NW * Rl * kRedPitch;   // [wave][16] row maxima
   float* sm_l = sm_m + NW * kDraftRows;                            // [wave][16] row sums
   const int64_t pbase = (static_cast<int64_t>(b) * p.Hkv + h) * p.nsplit + split;   // this workgroup's partial slot
   // (when the workgroup finishes the rows itself: G = 1, so the group's rows are consecutive)
@@ -321,10 +328,58 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
         v_row = gload<VReg, false>(v_at, static_cast<uint32_t>(l16) * (2u * NBLK));
       }
     }
+    // RING: 16-byte piece c of K row t sits at c ^ (t mod 16), V rows stay whole: reads without bank conflicts (attn_pair.hpp).
+    constexpr int TPI = 64 / (D / 8);          // token rows of one load instruction
+    constexpr int NP = kPage / TPI;            // load instructions per page (of K, of V)
+    constexpr int NL = 2 * NP;                 // ... per tile
+    constexpr int kRow = 2 * D, kHalfSlot = kTile * kRow;
+    constexpr int NS = kDraftRing / (2 * kHalfSlot);
+    unsigned char* const ring = smem + wave * kDraftRing;
+    uint32_t ring_lds = 0, koff[NP] = {}, voff[NP] = {};
+    if constexpr (RING) {
+      typedef const __attribute__((address_space(3))) unsigned char* lptr;
+      ring_lds = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lptr)ring)));
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        const int row = TPI * i + lane / (D / 8), piece = lane % (D / 8);     // where the 16 bytes land
+        koff[i] = static_cast<uint32_t>(row) * ts_bytes + static_cast<uint32_t>(piece ^ row) * 16u;
+        voff[i] = static_cast<uint32_t>(row) * ts_bytes + static_cast<uint32_t>(piece) * 16u;
+      }
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qreg[kk]));      // (waited for before loads that the compiler does not count)
+    }
+    auto ring_k = [&](int k) {
+      if ((k & 31) == 0 && k > 0) load_pagevec(k);
+      const uint32_t at = ring_lds + static_cast<uint32_t>((k & (NS - 1)) * 2 * kHalfSlot);
+      load_to_lds<NP, false>(at, page_base(k_head, __builtin_amdgcn_readlane(pagevec, k & 31)), koff);
+      load_to_lds<NP, false>(at + kHalfSlot / 2, page_base(k_head, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31))), koff);
+    };
+    auto ring_v = [&](int k) {
+      const uint32_t at = ring_lds + static_cast<uint32_t>((k & (NS - 1)) * 2 * kHalfSlot + kHalfSlot);
+      load_to_lds<NP, false>(at, page_base(v_head, __builtin_amdgcn_readlane(pagevec, k & 31)), voff);
+      load_to_lds<NP, false>(at + kHalfSlot / 2, page_base(v_head, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31))), voff);
+    };
+    const uint32_t k_first = static_cast<uint32_t>(l16 * kRow + ((kg ^ l16) * 16));
+    static_assert(!RING || NS == 2, "ring_wait counts the requests of two tiles");
+    // Of the ring's last tiles, for K (V is younger) or V: what is under way when it has to be there.
+    auto ring_wait = [&](bool last, auto is_k) {
+      constexpr int OWN = decltype(is_k)::value ? 1 : 0;
+      if (last) wait_vm<OWN * NL>();
+      else wait_vm<(2 + OWN) * NL>();
+    };
+    const int ntiles = tile_first < tile_end ? (tile_end - tile_first + NW - 1) / NW : 0;      // this wave's tiles
     u32x4 kr[2][KK];
     VReg va[8], vb[8];
     if constexpr (PS != 4) ids_pending = into_pool(ids_entry(1));     // (requested before tile 0's loads: it is back first)
-    if (tile_first < tile_end) {
+    if constexpr (RING) {
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        if (k < ntiles) {
+          ring_k(k);
+          ring_v(k);
+        }
+      }
+    } else if (tile_first < tile_end) {
       issue_k(0, kr);
       issue_v(0, va);
     }
@@ -342,6 +397,17 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
       constexpr bool has_next = decltype(has_next_tag)::value;
       const int tok0 = (tile_first + k * NW) * kTile;
       if constexpr (STREAM) exchange_k(kr);
+      const unsigned char* const kt = ring + (k & (NS - 1)) * (2 * kHalfSlot);
+      const unsigned char* const vt = kt + kHalfSlot;
+      if constexpr (RING) {
+        if constexpr (has_next) wait_vm<(2 * NS - 1) * NL>();
+        else ring_wait(k + 1 == ntiles, std::true_type{});
+#pragma unroll
+        for (int pg = 0; pg < 2; ++pg)
+#pragma unroll
+          for (int kk = 0; kk < KK; ++kk)
+            kr[pg][kk] = *reinterpret_cast<const u32x4*>(kt + pg * (kPage * kRow) + (k_first ^ static_cast<uint32_t>(64 * kk)));
+      }
       if constexpr (APPEND) {
         if (has_new && tok0 + kTile >= n) {    // the tile of the selection's last token, the new one
 #pragma unroll
@@ -367,8 +433,13 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
           ids_cur = ids_pending;
           ids_pending = into_pool(ids_entry(k + 2));
         }
-        issue_k(k + 1, kr);
-        issue_v(k + 1, vnxt);
+        if constexpr (RING) {
+          wait_lds();
+          ring_k(k + NS);
+        } else {
+          issue_k(k + 1, kr);
+          issue_v(k + 1, vnxt);
+        }
       }
       const bool tail = tok0 + kTile > n;      // (chunks are whole tiles: only the sequence's end cuts into one)
       if (tail) {
@@ -404,6 +475,14 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
 #pragma unroll
         for (int blk = 0; blk < NBLK; ++blk) acc[blk] *= alpha;
       }
+      if constexpr (RING) {
+        if constexpr (has_next) wait_vm<(2 * NS - 1) * NL>();
+        else ring_wait(k + 1 == ntiles, std::false_type{});
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          vcur[e] = *reinterpret_cast<const VReg*>(vt + (16 * (e >> 2) + 4 * kg + (e & 3)) * kRow + l16 * (2 * NBLK));
+        }
+      }
       if (tail) {                              // slots past the end may hold anything: feed zeros
 #pragma unroll
         for (int e = 0; e < 8; ++e)
@@ -418,27 +497,35 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
                                          (blk & 1) ? 0x07060302u : 0x05040100u);
         acc[blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, raw), pb, acc[blk], 0, 0, 0);
       }
+      if constexpr (RING && has_next) {
+        wait_lds();
+        ring_v(k + NS);
+      }
 #ifdef VEGAS_TIMELINE
       if (tl_stamps[kTlFirstTile] == 0) VEGAS_TL(kTlFirstTile);
 #endif
     };
 
     // ---- stream the chunk's tiles (the last one peeled: prefetches are unconditional, load-counter waits exact)
-    if (tile_first < tile_end) {
-      const int ntiles = (tile_end - tile_first + NW - 1) / NW;      // this wave's tiles
+    if (ntiles > 0) {
       using yes = std::integral_constant<bool, true>;
       using no = std::integral_constant<bool, false>;
       int k = 0;
-      while (k + 2 < ntiles) {
-        step(k, va, vb, yes{});
-        step(k + 1, vb, va, yes{});
-        k += 2;
-      }
-      if (k + 1 < ntiles) {
-        step(k, va, vb, yes{});
-        step(k + 1, vb, va, no{});
+      if constexpr (RING) {
+        for (; k + NS < ntiles; ++k) step(k, va, va, yes{});
+        for (; k < ntiles; ++k) step(k, va, va, no{});
       } else {
-        step(k, va, vb, no{});
+        while (k + 2 < ntiles) {
+          step(k, va, vb, yes{});
+          step(k + 1, vb, va, yes{});
+          k += 2;
+        }
+        if (k + 1 < ntiles) {
+          step(k, va, vb, yes{});
+          step(k + 1, vb, va, no{});
+        } else {
+          step(k, va, vb, no{});
+        }
       }
     }
 

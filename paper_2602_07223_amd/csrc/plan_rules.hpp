@@ -34,6 +34,13 @@ inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
   return 0;
 }
 
+// A draft call in which one workgroup streams each column's selection (head dimension 128, 16-token pages): through rings in LDS, which
+// leave a compute unit room for no other workgroup, or through registers, a tile ahead?  us a call (captured), registers / rings, by
+// columns and tokens: 8 128 4.1 / 4.1, 160 4.5 / 4.2, 272 6.0 / 5.3, 448 7.2 / 5.9; 96 800 13.1 / 9.6; 128 300 6.7 / 6.0, 1056 16.4 /
+// 14.3; 160 2000 30.1 / 28.8; 192 300 7.4 / 6.7, 1040 19.4 / 19.0, 3000 54.5 / 51.6; 256 300 8.3 / 8.4, 1040 23.3 / 23.0, 3000 67.1 /
+// 67.3.  (Head dimension 64: 8 400 5.0 / 5.2; 128 2000 14.4 / 15.2; 192 1040 11.2 / 12.7.  Calls cut into chunks: within 1 %.)
+inline bool ring_draft(int64_t columns, int num_cu, int tokens) { return columns < num_cu && tokens > 128; }
+
 // Verification with a local mask: does one workgroup per column (sequence x KV head x row block) stream the whole band
 // (no row sees more than window + queries tokens, nor than the longest sequence has) and write the output rows, or is the context cut into chunks
 // (`chunk` tokens, of which the band touches a few) and merged?  Cutting only helps where the chunks are shorter than the

@@ -325,7 +325,11 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
       const dim3 dblock(kDraftWaves * 64);
       const size_t dlds = draft16_lds_bytes(pl.R, D);
       const bool choose = draft_chooses(batch, sp.max_tokens, sp.Hkv, D);
-      if (step != nullptr) return launch_one(attn_draft16_kernel<D, 4, false, DraftStep>, grid, dblock, dlds, st, sp, *step);
+      if (step != nullptr) return launch_one(attn_draft16_kernel<D, 4, false, false, DraftStep>, grid, dblock, dlds, st, sp, *step);
+      if constexpr (D == 128) {
+        if (page_size == kPage && !choose && pl.nsplit == 1 && ring_draft(static_cast<int64_t>(batch) * sp.Hkv, device_cu_count(), pl.chunk))
+          return launch_one(attn_draft16_kernel<D, 4, false, true>, grid, dblock, draft_ring_lds_bytes(), st, sp);
+      }
       auto launch = [&](auto ps) {
         constexpr int PS = decltype(ps)::value;
         if (choose) return launch_one(attn_draft16_kernel<D, PS, true>, grid, dblock, dlds, st, sp);
@@ -514,12 +518,13 @@ int for_each_lds_kernel(F f) {
     one(attn_draft16_kernel<D, 2, false>); one(attn_draft16_kernel<D, 2, true>);
     one(attn_draft16_kernel<D, 3, false>); one(attn_draft16_kernel<D, 3, true>);
     one(attn_draft16_kernel<D, 4, false>); one(attn_draft16_kernel<D, 4, true>);
-    one(attn_draft16_kernel<D, 4, false, DraftStep>);
+    one(attn_draft16_kernel<D, 4, false, false, DraftStep>);
     one(attn_pair_kernel<0, D, true>); one(attn_pair_kernel<0, D, false>);
     one(attn_pair_kernel<1, D, true>); one(attn_pair_kernel<1, D, false, pair_waves(D, 1, 2, 0)>);
     one(attn_pair_kernel<2, D, true>); one(attn_pair_kernel<2, D, false>);
   };
   one(attn_pair_kernel<1, 64, true, 2 * kPairWaves>);
+  one(attn_draft16_kernel<128, 4, false, true>);
   per_dim(std::integral_constant<int, 128>{});
   per_dim(std::integral_constant<int, 64>{});
   one(verify_finalize_kernel<16, 0>); one(verify_finalize_kernel<32, 0>);
