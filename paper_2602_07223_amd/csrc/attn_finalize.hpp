@@ -177,6 +177,7 @@ __global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_S
 constexpr int kFinPlanned = -1;
 constexpr int kFinPlannedSmall = -2;   // the same in a call of few rows: merged a head dim per thread, pages scored row by row
 constexpr int kFinPre = 8;       // page log-sum-exps a score thread keeps in registers: 4 * kFinPre rows
+constexpr int kFinUnits = 6, kFinWideUnits = 10;   // (row, part of its chunks) pairs a score thread has in flight (finalize_is_wide)
 
 // Merge under balanced chunking: 1024 / D consecutive rows of the Hkv R rows per workgroup, a thread has four head dims of
 // one, and asks for the slots of its sequence (few as a rule, and known by now: the plan had to be read first) four or eight at a
@@ -244,7 +245,7 @@ __device__ __forceinline__ void merge_planned_rows(const FinalizeParams& p, cons
 // METRIC 1 (the paper's logit metric, token granularity) replaces the page-score role by workgroups
 // [nA, nA + nC) that add the H_kv per-head token sums of 1024 tokens each: score[b][i] = tok_norm *
 // sum_h partial[b][h][i] for prefix tokens i < n_b - G (Sec. 3.3, last paragraph), 0 elsewhere.
-template <int MAXS, int METRIC = 0>
+template <int MAXS, int METRIC = 0, int UNITS = kFinUnits>
 __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizeParams p) {
   extern __shared__ __attribute__((aligned(16))) float smf[];              // role A (general path): [256 / D][D] weights + [256 / D][4]; role B: [Hkv*R] + [8][32] + [Hkv*R][8] pairs
   constexpr bool kPlanned = MAXS < 0;
@@ -393,9 +394,9 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
   // ns_live: chunk slots worth loading.  With balanced chunking the slots of a head are shared by all sequences and
   // one sequence owns few of them, so its count is worked out first (one more round trip, in a kernel that is
   // bound by bytes at such batch sizes); otherwise every slot up to the host's bound is requested at once.
-  // (Six units per batch hold the whole table of one sequence of 32 chunks and 160 rows in flight; a planned
+  // (Six units per batch hold the whole table of one sequence of 32 chunks and 192 rows in flight, ten that of 320; a planned
   // sequence has few chunks, and there it pays to have more workgroups on a CU than its registers would leave room for.)
-  constexpr int kUnits = kPlanned ? 2 : 6;
+  constexpr int kUnits = kPlanned ? 2 : UNITS;
   int ns_live = p.nsplit;
   if constexpr (kPlanned) {
     int n0 = p.lens[b];

@@ -181,6 +181,13 @@ inline bool planned_merge_is_small(int batch, int rows, int head_dim) {
   return static_cast<int64_t>(batch) * rows * head_dim < 1024 * 256;
 }
 
+// Merge and page scores of one sequence (or of chunks that the host cuts): does a score workgroup keep the (max, sum) pairs of ten
+// units per thread in flight instead of six?  Six hold 192 rows; more are a second round trip, unless ten hold them; beyond 320 rows it
+// is two or more with either, and at 193 to 208 half of what ten ask for is nothing.  us per verification, six / ten, one sequence, by collected rows: 196 32.9 / 33.5
+// (32768 tokens), 224 13.4 / 13.1, 256 18.8 / 18.2 and (32768) 37.6 / 36.9, 308 21.7 / 21.3, 320 16.1 / 15.8 and (32768) 39.0 / 38.5, at
+// head dimension 64 27.8 / 27.1; 512 20.5 / 20.9, 768 21.1 / 22.2.
+inline bool finalize_is_wide(int rows) { return rows > 208 && rows <= 320; }
+
 // Workgroups go round the 8 XCDs, on each round its 4 shader engines, so every 32nd starts on the same engine: of the
 // consecutive ones of a head, whose grid has `per_slot` workgroups (KV heads x row blocks) between them, so many start on as
 // many engines.
