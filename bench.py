@@ -216,7 +216,7 @@ TIMELINE_EVENTS = ["wave entry", "length known", "first tile's loads issued", "q
                    "first tile done", "last tile done", "merge barrier passed", "partial stored (exit)"]
 
 
-def timeline_table(buf, label: str) -> dict:
+def timeline_table(buf, label: str, waves: int = 4) -> dict:
     """Per-phase summary of one launch's stamps ([records][8] uint64 at 100 MHz; records never written stay zero):
     event times relative to the first wave's entry, and per-wave phase durations, in microseconds."""
     import numpy as np
@@ -227,9 +227,9 @@ def timeline_table(buf, label: str) -> dict:
         return {"kernel": label, "waves": 0}
     t0 = rec[:, 0].min()
     rel = (rec - t0) / 100.0
-    # Workgroup ids are dealt round-robin to the 8 XCDs (record index = 4 * workgroup id + wave): when each XCD's
+    # Workgroup ids are dealt round-robin to the 8 XCDs (record index = waves * workgroup id + wave): when each XCD's
     # waves are done streaming, which is what a static partition of the work has to live with.
-    xcd = ((np.nonzero(live)[0] // 4) % 8)
+    xcd = ((np.nonzero(live)[0] // waves) % 8)
     by_xcd = [float(rel[xcd == x, 5].mean()) if np.any(xcd == x) else None for x in range(8)]
 
     def summary(col):
@@ -260,7 +260,8 @@ def run_timeline(args, torch, vb, harness, synth) -> int:
     path.verify(copies[6 % len(copies)], stages=vb.STAGE_STREAM)
     torch.cuda.synchronize()
     vb.vegas_debug_set_timeline(None)
-    out["kernels"].append(timeline_table(buf, "KV-streaming kernel of vegas_verify_attention"))
+    eight = spec.head_dim == 64 and spec.batch == 1 and spec.num_q_heads // spec.num_kv_heads * G > 32   # (pair_waves, attn_pair.hpp)
+    out["kernels"].append(timeline_table(buf, "KV-streaming kernel of vegas_verify_attention", 8 if eight else 4))
     path.iteration(copies[7 % len(copies)])                                # the selection a draft call walks
     path.draft(copies[7 % len(copies)], 0)
     torch.cuda.synchronize()
