@@ -34,6 +34,21 @@ inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
   return 0;
 }
 
+// Chunk length of a draft call of `columns` that workgroups of a whole unit (128 tokens, a tile per wave) would leave much of the chip idle: 64 or
+// 96 tokens, with a wave or two of every workgroup idle, while there are at most three workgroups for four compute units and 24
+// partials to merge.  Fewer waves then share a compute unit's way to memory.  us a call (captured), 128 / 96 / 64 tokens, head
+// dimension 128: 8 columns, 500 tokens 6.29 / 5.94 / 5.82, 1056 6.25 / 6.01 / 5.85, 1600 6.32 / 6.12 / 6.16, 2080 6.44 / 6.21 / 6.75,
+// 2560 6.47 / 6.62 / 7.10; 16, 800 6.29 / 6.06 / 5.87, 1056 6.36 / 6.09 / 6.23, 1600 6.61 / 6.96 / 7.01; 32, 500 6.30 / 6.05 / 5.81,
+// 800 6.55 / 6.62 / 6.68; 1, 2080 6.26 / 6.02 / 6.12; head dimension 64: 8, 1056 5.46 / 5.31 / 5.24, 2080 5.56 / 5.53 / 5.97.  An iteration of
+// 32768 tokens with 2048 selected 68.5 / 67.6 / 68.0, of a live one 72.0 / 71.2 / 74.2. .
+inline int draft_chunk_tokens(int64_t columns, int num_cu, int tokens, int unit) {
+  for (int chunk = unit / 2; chunk < unit; chunk += unit / 4) {
+    const int chunks = (tokens + chunk - 1) / chunk;
+    if (chunks <= 24 && 4 * columns * chunks <= 3 * static_cast<int64_t>(num_cu)) return chunk;
+  }
+  return unit;
+}
+
 // A draft call in which one workgroup streams each column's selection (head dimension 128, 16-token pages): through rings in LDS, which
 // leave a compute unit room for no other workgroup, or through registers, a tile ahead?  us a call (captured), registers / rings, by
 // columns and tokens: 8 128 4.1 / 4.1, 160 4.5 / 4.2, 272 6.0 / 5.3, 448 7.2 / 5.9; 96 800 13.1 / 9.6; 128 300 6.7 / 6.0, 1056 16.4 /

@@ -101,7 +101,7 @@ int check_paged16(const vegas_desc* d) {
 // max_len bounds the lengths the call may see; small problems get small workgroups.
 // collect: 0 nothing, 1 page log-sum-exps [pages x rows], 2 token sums [padded tokens] per (sequence, KV head)
 int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect, int wg_per_cu, SplitPlan* pl,
-               bool may_pair = false, bool may_finish = false) {
+               bool may_pair = false, bool may_finish = false, bool fine = false) {
   pl->R = rows_per_head;
   const int num_cu = device_cu_count();
   const int64_t heads = static_cast<int64_t>(d->batch) * d->num_kv_heads;
@@ -175,6 +175,8 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   const bool banded = !may_finish && d->window > 0 && d->kv_chunk_tokens == 0 &&
                       lone_workgroup_band(d->window, d->num_queries, max_len, chunk);
   const bool finish = banded || (own_chunks && rows_per_head <= kDraftRows && max_len <= lone_workgroup_tokens(heads, num_cu, d->head_dim));
+  if (fine && own_chunks && !finish && rows_per_head <= kDraftRows && chunk == unit)
+    chunk = draft_chunk_tokens(heads, num_cu, max_len, unit);
   // (A call that one workgroup per column finishes uses no partials; its workspace is sized for the chunked plan all
   //  the same, so that these rules move neither the sizes callers allocate nor what the built-in scratch takes.)
   size_t slots = static_cast<size_t>(heads) * ((max_len + chunk - 1) / chunk);   // chunk partials the workspace holds
@@ -227,8 +229,12 @@ int plan_verify(const vegas_desc* d, SplitPlan* pl) {
 // What a draft step keeps for its merge behind a draft call's partials: per sequence the grown lengths and the one it attends over.
 size_t step_bytes(const vegas_desc* d) { return align_up(static_cast<size_t>(d->batch) * (sizeof(int2) + sizeof(int32_t))); }
 
-int plan_draft(const vegas_desc* d, SplitPlan* pl) {
+// have: bytes of workspace there are.  (Chunks shorter than a unit need more slots: a workspace sized without them, for another
+// descriptor, keeps the units.)
+int plan_draft(const vegas_desc* d, SplitPlan* pl, size_t have = ~size_t(0)) {
   const int g = d->num_q_heads / d->num_kv_heads;
+  const int rc = plan_split(d, g, d->max_seq_len, 0, 2, pl, false, true, true);
+  if (rc != VEGAS_OK || pl->total <= have) return rc;
   return plan_split(d, g, d->max_seq_len, 0, 2, pl, false, true);
 }
 
@@ -873,7 +879,7 @@ static int check_draft(const vegas_desc* desc, const void* q, const void* k_cach
   if (desc->max_sel_blocks <= 0) return VEGAS_ERR_SHAPE;
   if (static_cast<int64_t>(desc->max_seq_len) > static_cast<int64_t>(desc->max_sel_blocks) * desc->page_size)
     return VEGAS_ERR_SHAPE;
-  rc = plan_draft(desc, pl);
+  rc = plan_draft(desc, pl, workspace_bytes);
   if (rc != VEGAS_OK) return rc;
   if (!aligned16(q) || !aligned16(k_cache) || !aligned16(v_cache) || !aligned16(out) || !aligned16(sel_table))
     return VEGAS_ERR_ALIGN;
@@ -966,7 +972,7 @@ int vegas_draft_attention_static(const vegas_desc* desc, const void* q, const vo
   const int rc = check_common(desc);
   if (rc != VEGAS_OK) return rc;
   SplitPlan pl;
-  if (int prc = plan_draft(desc, &pl)) return prc;
+  if (int prc = plan_draft(desc, &pl, kStaticScratchBytes)) return prc;
   if (pl.total > kStaticScratchBytes) return VEGAS_ERR_WORKSPACE;      // the call needs more than the built-in scratch
   void* ptr = nullptr;
   if (int src = static_scratch_address(&ptr)) return src;
