@@ -279,6 +279,11 @@ bool draft_chooses(int batch, int max_tokens, int kv_heads, int head_dim) {
   return past_cache(static_cast<uint64_t>(batch) * ((static_cast<uint64_t>(max_tokens) + 15) / 16), kv_heads, head_dim);
 }
 
+// More workgroups per (KV head, sequence) than a grid dimension holds?  (32-row blocks; 64-row ones: launch_split_d)
+bool exceeds_grid(const SplitPlan& pl) {
+  return static_cast<int64_t>(pl.NB) * (pl.balanced ? pl.bp.JS : pl.nsplit) > 65535;
+}
+
 template <bool CAUSAL, int COLLECT, int D>
 int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t st, int page_size, const DraftStep* step) {
   if constexpr (CAUSAL) {
@@ -318,7 +323,7 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
   // (KV head, row block + NB * chunk, sequence): the kernels read their indices off the grid without a division
   const dim3 grid = pl.balanced ? dim3(sp.Hkv, static_cast<unsigned>(pl.NB) * pl.bp.JS, 1)
                                 : dim3(sp.Hkv, static_cast<unsigned>(pl.NB) * pl.nsplit, batch);
-  if (grid.y > 65535u) return VEGAS_ERR_UNSUPPORTED;        // more chunks per sequence than a grid dimension holds
+  if (exceeds_grid(pl)) return VEGAS_ERR_UNSUPPORTED;
   const int rows = pl.R < 32 ? pl.R : 32;
   size_t lds = split_lds_bytes(pl.NW, rows, COLLECT, pl.chunk, D);
   if (pl.balanced && pl.bp.alone && lds < kLoneLds) lds = kLoneLds;
@@ -922,6 +927,7 @@ int vegas_draft_step(const vegas_desc* cache_desc, const vegas_desc* desc, const
   if (c.batch != d.batch || c.num_kv_heads != d.num_kv_heads || c.head_dim != d.head_dim || c.max_sel_blocks != d.max_sel_blocks ||
       c.kv_token_stride != d.kv_token_stride || c.kv_head_stride != d.kv_head_stride)
     return VEGAS_ERR_SHAPE;
+  if (exceeds_grid(pl)) return VEGAS_ERR_UNSUPPORTED;              // (before the append: the draft call would refuse after it)
   // Where a second launch merges chunks of 16-token pages it stores the lengths too, and the append needs no launch of its own: an
   // iteration of one sequence of 32749 tokens, 2048 selected, five steps, 86.9 -> 76.5 us.  A call that one workgroup per column
   // finishes has no second launch, and nothing in it could tell when the last of the columns has read the old lengths.

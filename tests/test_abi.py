@@ -172,6 +172,21 @@ def test_select_and_draft_reject_bad_arguments():
     assert e.value.status == vb.VEGAS_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("page", [16, 1])
+def test_draft_step_refuses_too_many_chunks_before_it_appends(page):
+    """65537 chunks of 32 tokens are more than a grid dimension holds: vegas_draft_attention refuses the descriptor, so the step does,
+    with nothing launched before (without a GPU a launch would report VEGAS_ERR_LAUNCH)."""
+    tokens = 65537 * 32
+    cache = good_desc(max_blocks=tokens // 16, max_sel_blocks=tokens // page, max_seq_len=tokens)
+    draft = good_desc(max_blocks=tokens // 16, max_sel_blocks=tokens // page, max_seq_len=tokens, page_size=page, kv_chunk_tokens=32)
+    with pytest.raises(vb.VegasError) as e:
+        vb.vegas_draft_attention(draft, A, A, A, A, A, A, A, workspace_bytes=1 << 40)
+    assert e.value.status == vb.VEGAS_ERR_UNSUPPORTED
+    with pytest.raises(vb.VegasError) as e:
+        vb.vegas_draft_step(cache, draft, A, A, A, A, A, A, A, A, A, A, A, workspace_bytes=1 << 40)
+    assert e.value.status == vb.VEGAS_ERR_UNSUPPORTED
+
+
 def test_static_scratch_refuses_what_does_not_fit():
     """A descriptor whose chunk partials exceed the built-in array is refused on the host, before any launch."""
     desc = vb.make_desc(batch=4096, num_q_heads=64, num_kv_heads=8, num_queries=1, max_blocks=64, max_sel_blocks=64,
