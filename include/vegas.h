@@ -282,6 +282,11 @@ int vegas_draft_attention(const vegas_desc* desc, const void* q, const void* k_c
  *                          strides are cache_desc's (VEGAS_ERR_SHAPE)
  *   k_new / v_new  bf16 [B, H_kv, D]   the drafted token's rows; must not overlap the caches
  *   workspace              vegas_workspace_bytes(desc) bytes or more
+ * Precondition, vegas_extend_selection's: the selection of every sequence that takes its token ends with the sequence's last
+ * page, listed once and filled as far as the sequence fills it (sel_seq_lens[b] and seq_lens[b] leave the same rest modulo 16;
+ * every selection of this library is so), or its row of sel_table is full.  Here it decides the output: what the grown
+ * selection's last slot holds is taken from k_new and v_new, not from the cache.  `out` is unspecified for a sequence whose
+ * selection ends elsewhere; lengths, cache and selection are still those of the two calls.
  */
 int vegas_draft_step(const vegas_desc* cache_desc, const vegas_desc* desc, const void* q, const void* k_new, const void* v_new,
                      const int32_t* block_table, int32_t* seq_lens, void* k_cache, void* v_cache, int32_t* sel_table,
