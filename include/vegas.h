@@ -267,6 +267,9 @@ int vegas_append_kv_extend(const vegas_desc* desc, const void* k_new, const void
  * kv_page_stride = page_size * kv_token_stride for a contiguous pool and num_pages counted in such
  * pages; only the last listed page of a sequence may be partial.  The other two calls return
  * VEGAS_ERR_UNSUPPORTED for page sizes other than 16.
+ * The bits of `out` are the same for every workspace of vegas_workspace_bytes(desc) bytes or more.  In a smaller one (sized
+ * for another descriptor, say) a call that the library would cut into chunks of less than 128 tokens is cut into chunks of
+ * 128, if their partials fit, and the last bits may differ; a call whose partials do not fit is VEGAS_ERR_WORKSPACE.
  */
 int vegas_draft_attention(const vegas_desc* desc, const void* q, const void* k_cache, const void* v_cache,
                           const int32_t* sel_table, const int32_t* sel_seq_lens,
@@ -295,9 +298,9 @@ int vegas_draft_step(const vegas_desc* cache_desc, const vegas_desc* desc, const
 /*
  * vegas_draft_attention for callers that cannot allocate device memory or carry a workspace around: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same
- * kernels and bit-identical results, but the chunk partials live in a scratch array inside the library's
- * device image (vegas_static_scratch_bytes() bytes per device, held until the process ends) instead of a
- * caller's workspace.  The call allocates nothing.
+ * kernels and results bit-identical to those in a workspace of vegas_workspace_bytes(desc) bytes or more, but
+ * the chunk partials live in a scratch array inside the library's device image (vegas_static_scratch_bytes()
+ * bytes per device, held until the process ends) instead of a caller's workspace.  The call allocates nothing.
  *   - Returns VEGAS_ERR_WORKSPACE, before anything is launched, when the descriptor needs more scratch
  *     than that (compare vegas_workspace_bytes(desc), for a draft-only descriptor, with the limit).
  *   - All calls on one device share the one array: calls that may overlap in time (different streams

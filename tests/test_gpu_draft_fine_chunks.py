@@ -1,5 +1,6 @@
 """Draft calls in chunks of 64 and 96 tokens (draft_chunk_tokens: a wave or two of every workgroup without a tile), at the ends of the range
-and one token past them, for every page size, against the oracle; and in a workspace that holds the chunks of 128 tokens only."""
+and one token past them, for every page size, against the oracle; and in a workspace that holds the chunks of 128 tokens only.
+Of the bits: any workspace of the size asked for and the built-in scratch give the same."""
 import pytest
 import torch
 
@@ -35,9 +36,16 @@ def test_fine_chunks(call):
     ref, _ = O.verify_attention(L.q_draft[:1].transpose(1, 0, 2, 3), L.k_cache, L.v_cache, L.block_table, L.seq_lens, L.softmax_scale, 0)
     slots = heads * batch * -(-tokens // 128)                        # of chunks of 128 tokens
     coarse = -(-slots * group * D * 4 // 256) * 256 + -(-slots * group * 8 // 256) * 256
-    for size in (vb.vegas_workspace_bytes(desc), coarse):
+    asked = vb.vegas_workspace_bytes(desc)
+    outs = {}
+    for size in (asked, asked + 4096, coarse):
         ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda:0")   # NaN partials where nothing was written
-        out = torch.full((batch, heads * group, D), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+        out = outs[size] = torch.full((batch, heads * group, D), float("nan"), dtype=torch.bfloat16, device="cuda:0")
         vb.vegas_draft_attention(desc, dl.q_draft[0], dl.k_cache, dl.v_cache, table, dl.seq_lens, out, ws)
         torch.cuda.synchronize()
         U.check_out(f"fine_chunks.{call}.{size}", out[:, None], ref, U.vmax_visible(L))
+    static = torch.full_like(out, float("nan"))
+    vb.vegas_draft_attention_static(desc, dl.q_draft[0], dl.k_cache, dl.v_cache, table, dl.seq_lens, static)
+    torch.cuda.synchronize()
+    for name, other in (("static", static), ("larger", outs[asked + 4096])):
+        assert torch.equal(other.view(torch.int16), outs[asked].view(torch.int16)), name
