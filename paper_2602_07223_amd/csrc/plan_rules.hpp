@@ -196,11 +196,14 @@ inline bool planned_merge_is_small(int batch, int rows, int head_dim) {
   return static_cast<int64_t>(batch) * rows * head_dim < 1024 * 256;
 }
 
-// Merge and page scores of one sequence (or of chunks that the host cuts): does a score workgroup keep the (max, sum) pairs of ten
-// units per thread in flight instead of six?  Six hold 192 rows; more are a second round trip, unless ten hold them; beyond 320 rows it
-// is two or more with either, and at 193 to 208 half of what ten ask for is nothing.  us per verification, six / ten, one sequence, by collected rows: 196 32.9 / 33.5
-// (32768 tokens), 224 13.4 / 13.1, 256 18.8 / 18.2 and (32768) 37.6 / 36.9, 308 21.7 / 21.3, 320 16.1 / 15.8 and (32768) 39.0 / 38.5, at
-// head dimension 64 27.8 / 27.1; 512 20.5 / 20.9, 768 21.1 / 22.2.
+// Merge and page scores of chunks that the host cuts (one sequence, more than 64, or a caller's chunk length): does a score workgroup
+// keep the (max, sum) pairs of ten units per thread in flight instead of six?  Six hold 192 rows; more are a second round trip, unless
+// ten hold them; beyond 320 rows it is two or more with either, and at 193 to 208 half of what ten ask for is nothing.  us per
+// verification, six / ten, one sequence, by collected rows: 196 32.9 / 33.5 (32768 tokens), 224 13.4 / 13.1, 256 18.8 / 18.2 and (32768)
+// 37.6 / 36.9, 308 21.7 / 21.3, 320 16.1 / 15.8 and (32768) 39.0 / 38.5, at head dimension 64 27.8 / 27.1; 512 20.5 / 20.9, 768 21.1 / 22.2.
+// Several sequences, the merge alone: 65 of 500..2000, 256 rows 27.6 / 27.2, 320 rows 32.6 / 31.9; 65 of 4000..9000, 256 35.3 / 34.6; 96 of
+// 500..3000, 320, head dimension 64 29.9 / 29.3; 128 of 300..1500, 224 40.7 / 40.1; 200 of 300..1000, 256 58.5 / 57.6; in chunks of the caller's
+// 4 of 2000..8000 (512), 256 8.8 / 8.4; 16 of 2000..8000 (1024), 320 16.1 / 15.4; 2 of 8000..16000 (256), 320, head dimension 64 12.6 / 11.6.
 inline bool finalize_is_wide(int rows) { return rows > 208 && rows <= 320; }
 
 // Workgroups go round the 8 XCDs, on each round its 4 shader engines, so every 32nd starts on the same engine: of the

@@ -1,5 +1,6 @@
-"""Page scores of one sequence whose score workgroups keep ten units of (max, sum) pairs per thread in flight (finalize_is_wide: 209 to
-320 collected rows), at both ends of that range and beyond them, for up to 16, 32, 64 and more chunks, against the oracle."""
+"""Page scores of calls whose score workgroups keep ten units of (max, sum) pairs per thread in flight (finalize_is_wide: 209 to
+320 collected rows, chunks that the host cuts), at both ends of that range and beyond them, for up to 16, 32, 64 and more chunks, for
+one sequence, more than a plan takes (64) and several in chunks of the caller's, against the oracle."""
 import pytest
 import torch
 
@@ -32,3 +33,26 @@ def test_page_scores(shape, D):
         torch.cuda.synchronize()
         U.check_out(f"wide_finalize.{shape}.{tokens}", path.out_verify, ref_out, U.vmax_visible(L))
         U.check_scores(f"wide_finalize.{shape}.{tokens}", path.block_scores, ref_scores)
+
+
+# sequences and their lengths (ragged, an empty one and one shorter than the queries among them), chunk of the caller's
+BATCHES = [([(37 * b * b) % 400 for b in range(65)], 0), ([3, 0, 1500, 2000, 129], 128), ([2049, 700, 4100], 64)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("lens,chunk", BATCHES, ids=["65_sequences", "chunks_of_128", "chunks_of_64"])
+def test_page_scores_of_batches(lens, chunk, D):
+    for heads, group, queries in ((8, 4, 8), (8, 8, 5), (5, 7, 6)):
+        print(f"[case] wide finalize, {heads * group * queries} rows, D={D}, {len(lens)} sequences in chunks of {chunk}", flush=True)
+        L = synth.make_random_case(seed=62000 + heads * group + len(lens) + D, batch=len(lens), num_q_heads=heads * group, num_kv_heads=heads,
+                                   num_queries=queries, seq_lens=lens, head_dim=D, logit_std=2.0, value_std=1.0, outliers=2, outlier_logit=25.0)
+        ref_out, ref_scores = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens, L.softmax_scale)
+        path = harness.VegasPath.for_layer(L, budget_tokens=256, verify_chunk=chunk)
+        path.workspace.fill_(0xFF)               # NaN partials where nothing was written
+        path.out_verify.fill_(float("nan"))
+        path.block_scores.fill_(float("nan"))
+        path.verify(harness.DeviceLayer.upload(L))
+        torch.cuda.synchronize()
+        U.check_out(f"wide_finalize.batch.{len(lens)}.{chunk}", path.out_verify, ref_out, U.vmax_visible(L))
+        U.check_scores(f"wide_finalize.batch.{len(lens)}.{chunk}", path.block_scores, ref_scores)
