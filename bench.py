@@ -260,8 +260,7 @@ def run_timeline(args, torch, vb, harness, synth) -> int:
     path.verify(copies[6 % len(copies)], stages=vb.STAGE_STREAM)
     torch.cuda.synchronize()
     vb.vegas_debug_set_timeline(None)
-    eight = spec.head_dim == 64 and spec.batch == 1 and spec.num_q_heads // spec.num_kv_heads * G > 32   # (pair_waves, attn_pair.hpp)
-    out["kernels"].append(timeline_table(buf, "KV-streaming kernel of vegas_verify_attention", 8 if eight else 4))
+    out["kernels"].append(timeline_table(buf, "KV-streaming kernel of vegas_verify_attention", vb.vegas_debug_verify_waves(path.desc_verify)))
     path.iteration(copies[7 % len(copies)])                                # the selection a draft call walks
     path.draft(copies[7 % len(copies)], 0)
     torch.cuda.synchronize()

@@ -366,6 +366,10 @@ int vegas_debug_check_tables(const vegas_desc* desc, int32_t which, const int32_
  */
 int vegas_debug_set_timeline(void* buffer, size_t bytes);
 
+/* Waves per workgroup of the KV-streaming kernel that vegas_verify_attention launches for this descriptor (to read the stamps by
+ * workgroup; a draft call's have 4), or a negative vegas_status.  Pure host function. */
+int vegas_debug_verify_waves(const vegas_desc* desc);
+
 /*
  * Measurement yardstick, not part of the method: one kernel that does nothing but read two device buffers of
  * bytes_each bytes (a multiple of 16; 16-byte aligned) front to back, coalesced, with `workgroups` workgroups of

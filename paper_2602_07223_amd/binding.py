@@ -42,7 +42,7 @@ EXPORTS = ("vegas_init", "vegas_workspace_bytes", "vegas_verify_attention", "veg
            "vegas_select_tokens", "vegas_append_kv", "vegas_append_kv_extend", "vegas_extend_selection", "vegas_draft_attention",
            "vegas_draft_step", "vegas_draft_attention_static", "vegas_static_scratch_bytes",
            "vegas_debug_verify_attention_stages", "vegas_debug_draft_attention_stages", "vegas_debug_stream_read",
-           "vegas_debug_check_tables", "vegas_debug_set_timeline", "vegas_strerror")
+           "vegas_debug_check_tables", "vegas_debug_set_timeline", "vegas_debug_verify_waves", "vegas_strerror")
 
 
 class VegasDesc(ctypes.Structure):
@@ -126,6 +126,8 @@ def load_library(path: Optional[str] = None):
     lib.vegas_debug_check_tables.argtypes = [D, ctypes.c_int32, P, P, P, P]
     lib.vegas_debug_set_timeline.restype = ctypes.c_int
     lib.vegas_debug_set_timeline.argtypes = [P, ctypes.c_size_t]
+    lib.vegas_debug_verify_waves.restype = ctypes.c_int
+    lib.vegas_debug_verify_waves.argtypes = [D]
     lib.vegas_strerror.restype = ctypes.c_char_p
     lib.vegas_strerror.argtypes = [ctypes.c_int]
     _lib = lib
@@ -387,6 +389,14 @@ def vegas_debug_set_timeline(buffer, nbytes: Optional[int] = None) -> None:
     rc = load_library().vegas_debug_set_timeline(_ptr(buffer), nb)
     if rc != VEGAS_OK:
         raise VegasError(rc, "vegas_debug_set_timeline")
+
+
+def vegas_debug_verify_waves(desc: VegasDesc) -> int:
+    """Waves per workgroup of the KV-streaming kernel of vegas_verify_attention for this descriptor."""
+    rc = int(load_library().vegas_debug_verify_waves(ctypes.byref(desc)))
+    if rc < 0:
+        raise VegasError(rc, "vegas_debug_verify_waves")
+    return rc
 
 
 def vegas_debug_stream_read(a, b, bytes_each: int, workgroups: int, non_temporal: bool, sink, stream=None) -> None:

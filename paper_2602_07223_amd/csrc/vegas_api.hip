@@ -1055,6 +1055,15 @@ int vegas_debug_set_timeline(void* buffer, size_t bytes) {
 #endif
 }
 
+int vegas_debug_verify_waves(const vegas_desc* desc) {
+  int rc = check_common(desc);
+  if (rc == VEGAS_OK) rc = check_paged16(desc);
+  SplitPlan pl;
+  if (rc == VEGAS_OK) rc = plan_verify(desc, &pl);
+  if (rc != VEGAS_OK) return rc;
+  return pl.pair ? pl.pair_waves : pl.NW;
+}
+
 const char* vegas_strerror(int status) {
   switch (status) {
     case VEGAS_OK: return "ok";

@@ -197,6 +197,25 @@ def test_static_scratch_refuses_what_does_not_fit():
     assert e.value.status == vb.VEGAS_ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("over,waves", [
+    (dict(), 4), (dict(head_dim=64, num_q_heads=64), 8),
+    (dict(head_dim=64, num_q_heads=64, max_seq_len=131072, max_blocks=8192), 4),          # more than 2048 tokens a compute unit
+    (dict(head_dim=64, num_q_heads=64, max_seq_len=2048), 4),                             # 64 a unit
+    (dict(head_dim=64, num_q_heads=64, batch=12, max_seq_len=1500), 8), (dict(head_dim=64, num_q_heads=64, batch=16, max_seq_len=32768), 4),
+    (dict(head_dim=64, num_q_heads=64, num_queries=12, max_seq_len=131072, max_blocks=8192), 8),      # siblings
+    (dict(head_dim=64, num_q_heads=64, collect_rows=vb.COLLECT_NONE), 4), (dict(num_q_heads=64), 4),
+])
+def test_waves_of_the_streaming_kernel_come_from_the_plan(over, waves):
+    """What bench.py --timeline divides the record number by (256 compute units where no device is visible, as on the card)."""
+    assert vb.vegas_debug_verify_waves(good_desc(**over)) == waves
+
+
+def test_waves_of_a_refused_descriptor():
+    with pytest.raises(vb.VegasError) as e:
+        vb.vegas_debug_verify_waves(good_desc(num_queries=33))
+    assert e.value.status == vb.VEGAS_ERR_UNSUPPORTED           # 132 rows per KV head
+
+
 def test_product_path_does_not_touch_the_oracle():
     pkg = os.path.join(ROOT, "paper_2602_07223_amd")
     for dirpath, _, files in os.walk(pkg):
