@@ -218,7 +218,8 @@ TIMELINE_EVENTS = ["wave entry", "length known", "first tile's loads issued", "q
 
 def timeline_table(buf, label: str, waves: int = 4) -> dict:
     """Per-phase summary of one launch's stamps ([records][8] uint64 at 100 MHz; records never written stay zero):
-    event times relative to the first wave's entry, and per-wave phase durations, in microseconds."""
+    event times relative to the first wave's entry, and per-wave phase durations, in microseconds.  An event that a wave
+    never reached is zero in its record (a wave without a tile has no first one): it counts in no summary."""
     import numpy as np
     raw = buf.cpu().numpy().view(np.uint64).reshape(-1, 8)
     live = raw[:, 0] > 0
@@ -226,14 +227,17 @@ def timeline_table(buf, label: str, waves: int = 4) -> dict:
     if rec.shape[0] == 0:
         return {"kernel": label, "waves": 0}
     t0 = rec[:, 0].min()
-    rel = (rec - t0) / 100.0
+    rel = np.where(rec > 0, (rec - t0) / 100.0, np.nan)
     # Workgroup ids are dealt round-robin to the 8 XCDs (record index = waves * workgroup id + wave): when each XCD's
     # waves are done streaming, which is what a static partition of the work has to live with.
     xcd = ((np.nonzero(live)[0] // waves) % 8)
-    by_xcd = [float(rel[xcd == x, 5].mean()) if np.any(xcd == x) else None for x in range(8)]
+    streamed = np.isfinite(rel[:, 4])
+    by_xcd = [float(rel[(xcd == x) & streamed, 5].mean()) if np.any((xcd == x) & streamed) else None for x in range(8)]
 
     def summary(col):
-        c = np.sort(col)
+        c = np.sort(col[np.isfinite(col)])
+        if c.size == 0:
+            return {"min": None, "p50": None, "p90": None, "max": None}
         return {"min": float(c[0]), "p50": float(c[len(c) // 2]), "p90": float(c[int(0.9 * (len(c) - 1))]), "max": float(c[-1])}
     events = {name: summary(rel[:, i]) for i, name in enumerate(TIMELINE_EVENTS)}
     phases = {f"{TIMELINE_EVENTS[i]} -> {TIMELINE_EVENTS[i + 1]}": summary(rel[:, i + 1] - rel[:, i]) for i in range(7)}
@@ -274,9 +278,11 @@ def run_timeline(args, torch, vb, harness, synth) -> int:
     for k in out["kernels"]:
         print(f"== {k['kernel']}: {k['waves']} waves", file=sys.stderr)
         for name, v in k.get("events_after_first_entry", {}).items():
-            print(f"   at   {name:40s} min {v['min']:6.2f}  p50 {v['p50']:6.2f}  p90 {v['p90']:6.2f}  max {v['max']:6.2f}", file=sys.stderr)
+            if v["min"] is not None:
+                print(f"   at   {name:40s} min {v['min']:6.2f}  p50 {v['p50']:6.2f}  p90 {v['p90']:6.2f}  max {v['max']:6.2f}", file=sys.stderr)
         for name, v in k.get("phase_durations_per_wave", {}).items():
-            print(f"   took {name:80s} p50 {v['p50']:6.2f}  p90 {v['p90']:6.2f}  max {v['max']:6.2f}", file=sys.stderr)
+            if v["min"] is not None:
+                print(f"   took {name:80s} p50 {v['p50']:6.2f}  p90 {v['p90']:6.2f}  max {v['max']:6.2f}", file=sys.stderr)
         if k.get("last_tile_done_mean_by_xcd"):
             print("   last tile done, mean over the waves of XCD 0..7 (workgroup id mod 8): " +
                   "  ".join("   -  " if v is None else f"{v:6.2f}" for v in k["last_tile_done_mean_by_xcd"]), file=sys.stderr)
