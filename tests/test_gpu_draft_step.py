@@ -14,11 +14,12 @@ DEV = "cuda:0"
 
 # name, query heads, KV heads, head dim, lengths, selected pages (None: all), entries of a selection row, chunk, bound of the call
 CASES = [
-    ("merged", 32, 8, 128, [2045], 100, 104, 0, None),                    # crosses into a new page, 13 chunks
-    ("page_starts_a_chunk", 32, 8, 128, [4096], 128, 132, 0, None),       # the selection ends with a whole chunk
-    ("row_fills_up", 32, 8, 128, [3198, 3200], 128, 129, 0, None),        # one new page fits, the second does not
+    ("merged", 32, 8, 128, [2045], 100, 104, 0, None),                    # crosses into a new page, 18 chunks of 96 tokens
+    ("page_starts_a_chunk", 32, 8, 128, [4096], 128, 132, 128, None),     # the selection ends with a whole chunk of 128 tokens
+    ("page_starts_a_fine_chunk", 32, 8, 128, [4096], 126, 132, 0, None),  # ... of 96: the next has one tile and three idle waves
+    ("row_fills_up", 32, 8, 128, [3198, 3200], 128, 128, 0, None),        # no new page fits: at the third step, at the first
     ("no_room", 32, 8, 128, [3215, 3216, 1000], 128, 140, 0, None),       # at the end of the table: refused
-    ("bound_ends_it", 32, 8, 128, [3000], 128, 140, 0, 2046),             # the draft call's own bound lies before the new token
+    ("bound_ends_it", 32, 8, 128, [3000], 128, 140, 0, 2042),             # 2040 tokens, then the draft call's own bound lies before the new one
     ("empty_and_short", 16, 4, 64, [0, 5, 3100], None, 256, 0, None),
     ("many_chunks", 8, 8, 128, [3333], None, 220, 32, None),              # more than 64 chunks: the general merge
     ("one_tile_chunks", 28, 4, 64, [700, 31, 16], None, 50, 32, None),
@@ -29,11 +30,11 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("P", [16, 1])
-@pytest.mark.parametrize("name,Hq,Hkv,D,lens,pages,row,chunk,bound", CASES, ids=[c[0] for c in CASES])
-def test_one_call_is_the_two_calls(name, Hq, Hkv, D, lens, pages, row, chunk, bound, P):
-    if P == 1 and name in ("past_the_cache", "row_fills_up"):
-        pytest.skip("16-token pages")
+CALLS = [(P, *c) for P in (16, 1) for c in CASES if P == 16 or c[0] not in ("past_the_cache", "row_fills_up")]   # (those: 16-token pages)
+
+
+@pytest.mark.parametrize("P,name,Hq,Hkv,D,lens,pages,row,chunk,bound", CALLS, ids=[f"{c[1]}-{c[0]}" for c in CALLS])
+def test_one_call_is_the_two_calls(P, name, Hq, Hkv, D, lens, pages, row, chunk, bound):
     B, steps, max_blocks = len(lens), 4, 201 if name == "no_room" else 300
     gen = torch.Generator(device=DEV).manual_seed(71000 + sum(lens) + D + Hq)
     rng = np.random.default_rng(71000 + sum(lens))
@@ -72,7 +73,9 @@ def test_one_call_is_the_two_calls(name, Hq, Hkv, D, lens, pages, row, chunk, bo
                     ws=torch.full((vb.vegas_workspace_bytes(draft),), 0xFF, dtype=torch.uint8, device=DEV))
 
     one, two = state(), state()
+    kept = set()                                                          # sequences that took a token and did not select it
     for step in range(steps):
+        before = {x: one[x].clone() for x in ("n", "ssl")}
         q, kn, vn = (torch.randn((B, h, D), generator=gen, device=DEV).to(torch.bfloat16) for h in (Hq, Hkv, Hkv))
         vb.vegas_draft_step(cache, draft, q, kn, vn, one["table"], one["n"], one["k"], one["v"], one["sel"], one["ssl"], one["out"], one["ws"])
         vb.vegas_append_kv_extend(cache, kn, vn, 1, two["table"], two["n"], two["k"], two["v"], two["sel"], two["ssl"], P)
@@ -86,8 +89,12 @@ def test_one_call_is_the_two_calls(name, Hq, Hkv, D, lens, pages, row, chunk, bo
                 a, b_ = a.view(torch.int16), b_.view(torch.int16)
             assert torch.equal(a, b_), f"{name} P={P} step {step}: {name_}"
         assert bool(torch.isfinite(one["out"].float()).all()), f"{name} P={P} step {step}"
+        kept |= set(torch.nonzero((one["n"] > before["n"]) & (one["ssl"] == before["ssl"]) & (before["ssl"] > 0)).flatten().tolist())
     grown = one["n"].cpu().numpy()
     assert [int(x) for x in grown] == [min(n + steps, max_blocks * PAGE) for n in lens]
+    assert kept == ({0, 1} if name == "row_fills_up" else set())          # (the named edge is the one that was met)
+    if name == "bound_ends_it":
+        assert int(one["ssl"].max()) > draft.max_seq_len
 
 
 def test_refused_steps_launch_nothing():
