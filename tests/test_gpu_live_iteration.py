@@ -20,7 +20,22 @@ def bits_of(t: torch.Tensor) -> np.ndarray:
     return t.detach().contiguous().view(torch.int16).cpu().numpy().view(np.uint16)
 
 
-def run_live(L, budget, name, token_granular=False, fused=True):
+def live_with_extend(path, dl, P):
+    """VegasPath.live_iteration with append and growth in one launch, vegas_append_kv_extend, before every draft call."""
+    dl.seq_lens_live.copy_(dl.seq_lens)
+    path.verify(dl)
+    path.select(dl)
+    for s in range(path.G):
+        vb.vegas_append_kv_extend(path.desc_append, dl.k_new[s], dl.v_new[s], 1, dl.block_table, dl.seq_lens_live, dl.k_cache, dl.v_cache,
+                                  path.sel_table, path.sel_seq_lens, P, stream=path.stream())
+        path.draft(dl, s)
+
+
+# The forms of a live step: vegas_draft_step; vegas_append_kv_extend and the draft call; append, growth and draft call by themselves.
+FORMS = ("one_call", "two_calls", "three_calls")
+
+
+def run_live(L, budget, name, token_granular=False, form="one_call"):
     G = L.spec.num_queries
     L = synth.with_growth(L, G)
     dl = harness.DeviceLayer.upload(L)
@@ -31,7 +46,10 @@ def run_live(L, budget, name, token_granular=False, fused=True):
     print(f"[case] live {name}: lens={list(map(int, L.seq_lens[:8]))} budget={budget} P={P}", flush=True)
     # the GPU runs the whole iteration as one stream of calls; the stages are then replayed one by one for comparison
     k0, v0 = dl.k_cache.clone(), dl.v_cache.clone()
-    path.live_iteration(dl, fused=fused)      # fused: vegas_append_kv_extend, one launch per step instead of two
+    if form == "two_calls":
+        live_with_extend(path, dl, P)
+    else:
+        path.live_iteration(dl, fused=form == "one_call")
     torch.cuda.synchronize()
     # nothing the draft calls were given lay outside what their descriptor lets them see (they would clamp silently)
     err = torch.zeros(1, dtype=torch.int32, device=path.device)
@@ -100,12 +118,12 @@ LIVE = [
 ]
 
 
-@pytest.mark.parametrize("fused", [True, False], ids=["one_launch", "two_calls"])
+@pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("name,B,Hq,Hkv,G,lens,budget", LIVE, ids=[c[0] for c in LIVE])
-def test_live_iteration_pages(name, B, Hq, Hkv, G, lens, budget, fused):
+def test_live_iteration_pages(name, B, Hq, Hkv, G, lens, budget, form):
     L = synth.make_random_case(seed=600 + len(name), batch=B, num_q_heads=Hq, num_kv_heads=Hkv, num_queries=G,
                                seq_lens=lens, logit_std=1.5, value_std=1.0, outliers=2, outlier_logit=20.0)
-    run_live(L, budget, name, fused=fused)
+    run_live(L, budget, name, form=form)
 
 
 LIVE_TOKENS = LIVE[:4] + [
@@ -115,12 +133,13 @@ LIVE_TOKENS = LIVE[:4] + [
 ]
 
 
+@pytest.mark.parametrize("form", FORMS)
 @pytest.mark.parametrize("name,B,Hq,Hkv,G,lens,budget", LIVE_TOKENS, ids=[c[0] for c in LIVE_TOKENS])
-def test_live_iteration_tokens(name, B, Hq, Hkv, G, lens, budget):
+def test_live_iteration_tokens(name, B, Hq, Hkv, G, lens, budget, form):
     """The paper's own granularity: token selection from averaged logits, one-token pages, growing by one entry a step."""
     L = synth.make_random_case(seed=650 + len(name), batch=B, num_q_heads=Hq, num_kv_heads=Hkv, num_queries=G,
                                seq_lens=lens, logit_std=1.5, value_std=1.0, outliers=2, outlier_logit=20.0)
-    run_live(L, min(budget, 200), name + ".tokens", token_granular=True)
+    run_live(L, min(budget, 200), name + ".tokens", token_granular=True, form=form)
 
 
 def test_live_iteration_ctx32k_full_size():
