@@ -40,7 +40,7 @@ inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
 // dimension 128: 8 columns, 500 tokens 6.29 / 5.94 / 5.82, 1056 6.25 / 6.01 / 5.85, 1600 6.32 / 6.12 / 6.16, 2080 6.44 / 6.21 / 6.75,
 // 2560 6.47 / 6.62 / 7.10; 16, 800 6.29 / 6.06 / 5.87, 1056 6.36 / 6.09 / 6.23, 1600 6.61 / 6.96 / 7.01; 32, 500 6.30 / 6.05 / 5.81,
 // 800 6.55 / 6.62 / 6.68; 1, 2080 6.26 / 6.02 / 6.12; head dimension 64: 8, 1056 5.46 / 5.31 / 5.24, 2080 5.56 / 5.53 / 5.97.  An iteration of
-// 32768 tokens with 2048 selected 68.5 / 67.6 / 68.0, of a live one 72.0 / 71.2 / 74.2. .
+// 32768 tokens with 2048 selected 68.5 / 67.6 / 68.0, of a live one 72.0 / 71.2 / 74.2.
 inline int draft_chunk_tokens(int64_t columns, int num_cu, int tokens, int unit) {
   for (int chunk = unit / 2; chunk < unit; chunk += unit / 4) {
     const int chunks = (tokens + chunk - 1) / chunk;
