@@ -379,7 +379,12 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
           ring_v(k);
         }
       }
-    } else if (tile_first < tile_end) {
+    } else if (PS == 4 && D == 128 ? tile_first < tile_end : ntiles > 0) {
+      // (The stream below is under ntiles > 0.  Under the same condition the compiler sees that a wave that streams has these loads under
+      //  way; under another it waits for all of a wave's loads in every second tile.  us a call, other condition / same, captured: one-token
+      //  pages, 96 columns x 692 tokens 10.99 / 9.95, 128 x 840 13.0 / 12.2; 8-token ones, 8 x 393 7.14 / 6.70; 16-token ones at head dimension 64,
+      //  128 x 1474 11.59 / 11.34, 192 x 5828 74.2 / 73.5.  At head dimension 128 16-token pages have the same waits either way and a better
+      //  order of instructions under the other: 64 x 1246 12.36 / 12.68, 32 x 2427 12.42 / 12.78.)
       issue_k(0, kr);
       issue_v(0, va);
     }

@@ -53,3 +53,19 @@ def test_m0_belongs_to_the_loads_into_lds(report):
     assert loads >= 12 * 16 and not foreign, (loads, foreign[:4])
     planted = report[1].replace("s_nop 0\n\tglobal_load_lds", "v_readlane_b32 s0, v1, m0\n\ts_nop 0\n\tglobal_load_lds", 1)
     assert foreign_m0_lines(planted)[1]
+
+
+def drained_waits(asm: str):
+    """Waits for all of a wave's loads, per draft kernel of pages of 1, 2, 4 or 8 tokens that does not choose by length (template
+    arguments head dimension, log2 of the page size)."""
+    out = {}
+    for D, page, body in re.findall(r"^_ZN5vegas19attn_draft16_kernelILi(\d+)ELi([0-3])ELb0ELb0EJEEE\w*:(.*?)^\.Lfunc_end", asm, flags=re.M | re.S):
+        out[int(D), int(page)] = len(re.findall(r"s_waitcnt vmcnt\(0\)", body))
+    return out
+
+
+def test_small_page_draft_kernels_keep_their_prefetch(report):
+    """The streaming loops request a tile ahead and wait for the tile at hand only.  Five or six waits for everything are at the
+    kernel's ends and in the last tiles; one or two more are in the loop, where they cost a call of several tiles per wave 6 to 10 %."""
+    waits = drained_waits(report[1])
+    assert len(waits) == 8 and max(waits.values()) <= 6, waits
