@@ -41,10 +41,15 @@ inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
 // 2560 6.47 / 6.62 / 7.10; 16, 800 6.29 / 6.06 / 5.87, 1056 6.36 / 6.09 / 6.23, 1600 6.61 / 6.96 / 7.01; 32, 500 6.30 / 6.05 / 5.81,
 // 800 6.55 / 6.62 / 6.68; 1, 2080 6.26 / 6.02 / 6.12; head dimension 64: 8, 1056 5.46 / 5.31 / 5.24, 2080 5.56 / 5.53 / 5.97.  An iteration of
 // 32768 tokens with 2048 selected 68.5 / 67.6 / 68.0, of a live one 72.0 / 71.2 / 74.2.
-inline int draft_chunk_tokens(int64_t columns, int num_cu, int tokens, int unit) {
+// row_dims: a column's rows x head dimension.  Partials of more than 1.25 MB in all cost the merge what shorter chunks gain, and up to 3 %
+// more on some cards: 16 rows of head dimension 128, 128 / 96 / 64 tokens, 8 columns, 1250 6.81 / 6.71 / 6.85 (1.25 MB of the last), 1400 6.85 / 6.72 /
+// 6.92, 1900 7.06 / 7.03 / 7.35 (1.25 MB of 96), 2300 7.25 / 7.27 / 8.54; 12 columns, 1250 7.00 / 6.99 / 7.08, 1536 7.00 / 7.09 / 8.34; elsewhere, 128
+// and what was chosen without the bound, 8 columns, 1536 6.83 / 7.07, 2300 7.26 / 7.47; 12, 1536 7.17 / 7.30.  (Groups of up to 12, and head dimension
+// 64, stay below it.)
+inline int draft_chunk_tokens(int64_t columns, int num_cu, int tokens, int unit, int row_dims) {
   for (int chunk = unit / 2; chunk < unit; chunk += unit / 4) {
     const int chunks = (tokens + chunk - 1) / chunk;
-    if (chunks <= 24 && 4 * columns * chunks <= 3 * static_cast<int64_t>(num_cu)) return chunk;
+    if (chunks <= 24 && 4 * columns * chunks <= 3 * static_cast<int64_t>(num_cu) && columns * chunks * row_dims <= 320 * 1024) return chunk;
   }
   return unit;
 }

@@ -176,7 +176,7 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
                       lone_workgroup_band(d->window, d->num_queries, max_len, chunk);
   const bool finish = banded || (own_chunks && rows_per_head <= kDraftRows && max_len <= lone_workgroup_tokens(heads, num_cu, d->head_dim));
   if (fine && own_chunks && !finish && rows_per_head <= kDraftRows && chunk == unit)
-    chunk = draft_chunk_tokens(heads, num_cu, max_len, unit);
+    chunk = draft_chunk_tokens(heads, num_cu, max_len, unit, rows_per_head * d->head_dim);
   // (A call that one workgroup per column finishes uses no partials; its workspace is sized for the chunked plan all
   //  the same, so that these rules move neither the sizes callers allocate nor what the built-in scratch takes.)
   size_t slots = static_cast<size_t>(heads) * ((max_len + chunk - 1) / chunk);   // chunk partials the workspace holds

@@ -12,6 +12,7 @@ from tests import parity_util as U
 # sequences, KV heads, query heads per KV head, selected tokens (bound), head dim, page size
 CALLS = [
     (1, 8, 4, 465, 128, 16), (1, 8, 4, 1536, 128, 16), (1, 8, 8, 1537, 128, 16), (1, 8, 4, 2304, 128, 16), (1, 8, 4, 2305, 128, 16),
+    (1, 8, 16, 1280, 128, 16), (1, 8, 16, 1281, 128, 16), (1, 8, 16, 1920, 128, 16), (1, 8, 16, 1921, 128, 16),   # the bound on the partials
     (2, 16, 2, 481, 128, 16), (1, 4, 7, 1000, 64, 16), (3, 2, 16, 1700, 64, 16), (1, 8, 4, 2048, 128, 1), (1, 8, 4, 1003, 64, 4),
 ]
 
