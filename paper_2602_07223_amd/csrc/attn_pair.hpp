@@ -55,13 +55,17 @@ constexpr int pair_ring(int D, int collect) { return pair_two_per_cu(D, collect)
 // Waves of a workgroup that parks page values at head dimension 64 and so has its compute unit to itself.  One wave per SIMD
 // leaves a tile's chain (first contraction, maximum, exponentials, second contraction: 1.3 us) nothing to run beside; two halve the
 // ring and what is parked per wave (two tiles instead of four).  `share`: tokens of the call's bound per compute unit.  One row
-// block is bound by HBM in long streams, where the deeper rings win, and by the merge of the waves in the shortest; siblings, of
-// which one reads from the L2, are bound by the chain at any size.  us a call, four waves / eight, 8 KV heads: 40 rows, one sequence
-// of 4096 15.5 / 16.5; 6000 16.7 / 16.1; 16384 23.0 / 21.5; 32768 29.6 / 27.6 (the kernel 22.8 / 19.7); 65536 41.7 / 41.9; 131072
-// 67 / 71; 16 of 8192..65536 251 / 286; 12 of 375..1500 21.6 / 20.3; 64 rows, 4 of 4000..8000 31.1 / 29.4, of 12000..24000 51.7 /
-// 52.1; 96 rows, one of 12000 32.8 / 32.7, 32768 47.0 / 38.7, 131072 122 / 101; 12 of 12500..50000 324 / 274.
-constexpr int pair_waves(int D, int collect, int row_blocks, int64_t share) {
-  return D == 64 && collect == 1 && (row_blocks > 1 || (share > 128 && share <= 2048)) ? 2 * kPairWaves : kPairWaves;
+// block is bound by HBM in long streams, where the deeper rings win; siblings, of which one reads from the L2, are bound by the chain.
+// A workgroup of 128 tokens or fewer has a tile for each of four waves, and merging eight costs 1.1 us; batches reach that with a
+// higher bound, being ragged.  us a call, four waves / eight, 8 KV heads: 40 rows, one sequence of 4096 15.5 / 16.5; 6000 16.7 / 16.1;
+// 16384 23.0 / 21.5; 32768 29.6 / 27.6 (the kernel 22.8 / 19.7); 65536 41.7 / 41.9; 131072 67 / 71; 16 of 8192..65536 251 / 286; 12 of
+// 375..1500 21.6 / 20.3; 64 rows, 4 of 4000..8000 31.1 / 29.4, of 12000..24000 51.7 / 52.1; 96 rows, one of 12000 32.8 / 32.7, 32768
+// 47.0 / 38.7, 131072 122 / 101; 12 of 12500..50000 324 / 274; 112 rows, one of 1959 (share 122) +9 %, of 2268 (141) -3 %; 24 x 124, 96 rows
+// 24.1 / 26.7.  Of 4200 batches drawn, four / eight by share: up to 128 0.923, 128..160 0.975, 160..200 0.996, 200..256 1.006, 256..512 1.024,
+// 512..2048 1.09.
+constexpr int pair_waves(int D, int collect, int row_blocks, int batch, int max_len, int64_t share) {
+  return D == 64 && collect == 1 && max_len > 128 && share > (batch > 1 ? 200 : 128) && (row_blocks > 1 || share <= 2048) ? 2 * kPairWaves
+                                                                                                                        : kPairWaves;
 }
 // What a second launch wave costs, in units of 128 tokens (see wants_second_wave): nothing where two workgroups fit.
 constexpr int pair_second_cost(int D, int collect) { return pair_two_per_cu(D, collect) ? 0 : 11; }

@@ -199,7 +199,7 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
     pl->chunk = collect != 0 && !pl->pair ? cap : unit;         // sizes the LDS that parks a chunk's collected values
     slots = static_cast<size_t>(d->num_kv_heads) * pl->bp.JS;   // (sibling row blocks share a slot)
   }
-  if (pl->pair) pl->pair_waves = pair_waves(d->head_dim, collect, pl->NB, static_cast<int64_t>(d->batch) * max_len * per_head / num_cu);
+  if (pl->pair) pl->pair_waves = pair_waves(d->head_dim, collect, pl->NB, d->batch, max_len, static_cast<int64_t>(d->batch) * max_len * per_head / num_cu);
   pl->lse_pages = collect == 1 ? (max_len + kPage - 1) / kPage
                                : (collect == 2 ? (pl->balanced ? (max_len + unit - 1) / unit * unit : pl->nsplit * chunk) : 0);
   size_t off = 0;
@@ -311,13 +311,14 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
         if (pgrid.z > 65535u) return VEGAS_ERR_UNSUPPORTED;
       }
       const dim3 block(pl.pair_waves * 64);
-      constexpr int kSiblingWaves = pair_waves(D, COLLECT, 2, 0);
-      if constexpr (kSiblingWaves != kPairWaves) {
-        if (pl.NB == 1 && pl.pair_waves != kPairWaves)
-          return launch_one(attn_pair_kernel<COLLECT, D, true, 2 * kPairWaves>, pgrid, block, lds.bytes, st, sp);
+      if constexpr (D == 64 && COLLECT == 1) {
+        if (pl.pair_waves != kPairWaves) {
+          if (pl.NB == 1) return launch_one(attn_pair_kernel<COLLECT, D, true, 2 * kPairWaves>, pgrid, block, lds.bytes, st, sp);
+          return launch_one(attn_pair_kernel<COLLECT, D, false, 2 * kPairWaves>, pgrid, block, lds.bytes, st, sp);
+        }
       }
       if (pl.NB == 1) return launch_one(attn_pair_kernel<COLLECT, D, true>, pgrid, block, lds.bytes, st, sp);
-      return launch_one(attn_pair_kernel<COLLECT, D, false, kSiblingWaves>, pgrid, block, lds.bytes, st, sp);
+      return launch_one(attn_pair_kernel<COLLECT, D, false>, pgrid, block, lds.bytes, st, sp);
     }
   }
   // (KV head, row block + NB * chunk, sequence): the kernels read their indices off the grid without a division
@@ -531,10 +532,10 @@ int for_each_lds_kernel(F f) {
     one(attn_draft16_kernel<D, 4, false>); one(attn_draft16_kernel<D, 4, true>);
     one(attn_draft16_kernel<D, 4, false, false, DraftStep>);
     one(attn_pair_kernel<0, D, true>); one(attn_pair_kernel<0, D, false>);
-    one(attn_pair_kernel<1, D, true>); one(attn_pair_kernel<1, D, false, pair_waves(D, 1, 2, 0)>);
+    one(attn_pair_kernel<1, D, true>); one(attn_pair_kernel<1, D, false>);
     one(attn_pair_kernel<2, D, true>); one(attn_pair_kernel<2, D, false>);
   };
-  one(attn_pair_kernel<1, 64, true, 2 * kPairWaves>);
+  one(attn_pair_kernel<1, 64, true, 2 * kPairWaves>); one(attn_pair_kernel<1, 64, false, 2 * kPairWaves>);
   one(attn_draft16_kernel<128, 4, false, true>);
   per_dim(std::integral_constant<int, 128>{});
   per_dim(std::integral_constant<int, 64>{});

@@ -203,6 +203,10 @@ def test_static_scratch_refuses_what_does_not_fit():
     (dict(head_dim=64, num_q_heads=64, max_seq_len=2048), 4),                             # 64 a unit
     (dict(head_dim=64, num_q_heads=64, batch=12, max_seq_len=1500), 8), (dict(head_dim=64, num_q_heads=64, batch=16, max_seq_len=32768), 4),
     (dict(head_dim=64, num_q_heads=64, num_queries=12, max_seq_len=131072, max_blocks=8192), 8),      # siblings
+    (dict(head_dim=64, num_q_heads=64, num_queries=14, max_seq_len=2080, collect_rows=vb.COLLECT_FIRST_LAST), 8),
+    (dict(head_dim=64, num_q_heads=64, num_queries=14, max_seq_len=2048, collect_rows=vb.COLLECT_FIRST_LAST), 4),
+    (dict(head_dim=64, num_q_heads=64, num_queries=12, batch=24, max_seq_len=128), 4), (dict(head_dim=64, num_q_heads=64, num_queries=12, batch=24, max_seq_len=144), 8),
+    (dict(head_dim=64, num_q_heads=64, batch=8, max_seq_len=816), 8), (dict(head_dim=64, num_q_heads=64, batch=8, max_seq_len=800), 4),
     (dict(head_dim=64, num_q_heads=64, collect_rows=vb.COLLECT_NONE), 4), (dict(num_q_heads=64), 4),
 ])
 def test_waves_of_the_streaming_kernel_come_from_the_plan(over, waves):

@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("Hq,Hkv,G", [(88, 8, 3), (64, 8, 5), (64, 8, 8), (104, 8, 5), (64, 8, 12)],
                          ids=["33_rows", "40_rows", "64_rows", "65_rows", "96_rows"])
 @pytest.mark.parametrize("lens,chunk", [([4127], 0), ([4128], 0), ([4128], 32), ([4129], 288), ([8192], 0), ([9000], 9024),
-                                        ([4133, 0, 517], 0), ([700, 1300, 33, 2048, 1, 900, 1029, 500], 0)], ids=str)
+                                        ([4133, 0, 517], 0), ([700, 1300, 33, 2048, 1, 900, 1029, 500], 0),
+                                        ([1100], 0), ([2065], 0), ([128, 37, 5, 120], 0)], ids=str)
 def test_eight_waves(lens, chunk, Hq, Hkv, G):
     L = synth.make_random_case(seed=6700 + sum(lens) + Hq + G, batch=len(lens), num_q_heads=Hq, num_kv_heads=Hkv, num_queries=G,
                                seq_lens=lens, head_dim=64, logit_std=2.0, value_std=1.0, outliers=2,
