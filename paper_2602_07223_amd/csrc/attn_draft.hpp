@@ -232,6 +232,10 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
       uint16_t* rows = out_rows();
       for (int e = tid; e < Rl * D; e += NW * 64) rows[e] = 0;
     }
+    // (The stores are waited for here.  The compiler lets this way out run into the stream below and counts stores and loads in one
+    //  counter without an order between the two kinds: as long as a store may be under way it waits for everything where it wants the
+    //  oldest load, the next tile's page ids.)
+    __builtin_amdgcn_s_waitcnt(0x0f70);      // vmcnt(0)
     return;
   }
   VEGAS_TL(kTlLength);
@@ -370,7 +374,10 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
     const int ntiles = tile_first < tile_end ? (tile_end - tile_first + NW - 1) / NW : 0;      // this wave's tiles
     u32x4 kr[2][KK];
     VReg va[8], vb[8];
-    if constexpr (PS != 4) ids_pending = into_pool(ids_entry(1));     // (requested before tile 0's loads: it is back first)
+    // (Brought into the pool when they are used: a wave of one tile never waits for them.  With that and the wait above, us a call in
+    //  one-token pages, captured, before / after: 8 columns x 64 tokens 3.71 / 3.39, x 2048 6.37 / 6.06; 24 x 600 6.28 / 5.96; 2-token ones, 64 x
+    //  120 4.32 / 4.03; head dimension 64, 8 x 2048 5.58 / 5.38; calls of many tiles per wave the same, 128 x 2000 23.7 / 23.55.)
+    if constexpr (PS != 4) ids_pending = ids_entry(1);                // (requested before tile 0's loads: it is back first)
     if constexpr (RING) {
 #pragma unroll
       for (int k = 0; k < NS; ++k) {
@@ -435,8 +442,8 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
                                                            __builtin_bit_cast(bf16x8, qreg[kk]), st[pg], 0, 0, 0);
       if (has_next) {
         if constexpr (PS != 4) {               // the next tile's ids are here (requested a tile ago); ask for the ones after
-          ids_cur = ids_pending;
-          ids_pending = into_pool(ids_entry(k + 2));
+          ids_cur = into_pool(ids_pending);
+          ids_pending = ids_entry(k + 2);
         }
         if constexpr (RING) {
           wait_lds();

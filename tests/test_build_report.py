@@ -69,3 +69,19 @@ def test_small_page_draft_kernels_keep_their_prefetch(report):
     kernel's ends and in the last tiles; one or two more are in the loop, where they cost a call of several tiles per wave 6 to 10 %."""
     waits = drained_waits(report[1])
     assert len(waits) == 8 and max(waits.values()) <= 6, waits
+
+
+def waits_before_the_stream(asm: str):
+    """Loads left under way by the waits before the first contraction, per kernel of drained_waits."""
+    out = {}
+    for D, page, body in re.findall(r"^_ZN5vegas19attn_draft16_kernelILi(\d+)ELi([0-3])ELb0ELb0EJEEE\w*:(.*?)^\.Lfunc_end", asm, flags=re.M | re.S):
+        out[int(D), int(page)] = [int(n) for n in re.findall(r"s_waitcnt vmcnt\((\d+)\)", body[:body.index("v_mfma")])]
+    return out
+
+
+def test_small_page_draft_kernels_start_without_draining(report):
+    """Before a wave's first contraction only what it uses is waited for: the length and the page ids, then its keys' first load.  A
+    wait for everything (the next tile's page ids brought into the pool at once, stores of an empty sequence's rows that may be under
+    way as far as the compiler knows) cost a call of one tile per wave 0.2 to 0.3 us."""
+    waits = waits_before_the_stream(report[1])
+    assert len(waits) == 8 and all(0 not in w for w in waits.values()), waits
