@@ -21,8 +21,8 @@ Beyond the default run:
                        CPU baseline and the counter-derived traffic belong to the default workload only
   --extras             adds per-iteration percentiles, the warm-cache figure (one cache copy) and the
                        iteration replayed from captured HIP graphs to the same JSON line
-  --live               the drafting phase as it runs live: every draft step first appends the drafted token's K/V rows
-                       (vegas_append_kv) and grows the selection by them (vegas_extend_selection)
+  --live               the drafting phase as it runs live: every draft step appends the drafted token's K/V rows, grows
+                       the selection by them and drafts, as one call (vegas_draft_step)
   --all-layers         a multi-layer workload (stack32) with every layer's cache resident: a step is one pass over all
                        layers
   --timeline           per-wave phase times of the two KV-streaming kernels (profiling build of the library)
@@ -50,8 +50,8 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 # runs, each scaled by what the same counter reads for a plain 64 MiB copy (factors 1.9990 and 1.0); the figures are
 # the `traffic_bytes_per_launch[...]` lines of the two summaries (tests/test_profiles_match_bench.py compares them).
 VERIFY_TRAFFIC_BYTES = {
-    "ctx32k": 138574632,       # (131447 KiB fetched + 3880 KiB written), profiles/ctx32k_hbm_traffic_pmc.md
-    "ragged16": 2434575050,    # (2312055 KiB fetched + 65460 KiB written), profiles/ragged16_hbm_traffic_pmc.md
+    "ctx32k": 138531840,       # (131405 KiB fetched + 3880 KiB written), profiles/ctx32k_hbm_traffic_pmc.md
+    "ragged16": 2415472762,    # (2306406 KiB fetched + 52454 KiB written), profiles/ragged16_hbm_traffic_pmc.md
 }
 DEFAULT_WORKLOAD = "ctx32k"
 ROTATE_BYTES = 1.2e9           # rotate cache copies up to about this much K+V in total
