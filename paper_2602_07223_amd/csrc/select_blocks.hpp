@@ -29,11 +29,12 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 struct RegisterSelectShared {
   uint32_t hist[3][2048];                       // digit counts of the up to three passes
   uint32_t low[kSelectThreads / 64], high[kSelectThreads / 64];
-  uint32_t bin, need, count;
+  uint32_t bin, need, count, crowded, listed;
 };
-// Taken are the keys above base + span and the first `need`, by position, of those in [base, base + span].
+// Taken are the keys above base + span and the first `need`, by position, of those in [base, base + span]; whole: these are all.
 struct LastKey {
   uint32_t base, span, need;
+  bool whole;
 };
 
 constexpr uint32_t kNoDigit = 0xFFFFFFFFu;      // of a key that is not counted
@@ -47,6 +48,33 @@ __device__ __forceinline__ uint32_t digit_beside(uint32_t digit) {
 // Lanes that have the digit of the lane beside them: the chance that two keys share a digit, at the price of one comparison.
 __device__ __forceinline__ int sharing_lanes(uint32_t digit) {
   return __popcll(__builtin_amdgcn_ballot_w64(digit == digit_beside(digit) && digit != kNoDigit));
+}
+
+// One full wave: from the top, the bin of the 2048 in `h` that holds key number `need` (0 < need <= keys counted), how many of its
+// keys are wanted and how many it has.
+__device__ __forceinline__ void walk_to_last_bin(const uint32_t* h, uint32_t need, RegisterSelectShared& sh) {
+  const int lane = threadIdx.x & 63;
+  // lane l owns the 32 bins from 32 (63 - l) on, read in an order that spreads the lanes over the banks; then lanes
+  // 0..31 the bins of the lane that holds the wanted key, both from the top bin down
+  const u32x4* g4 = reinterpret_cast<const u32x4*>(h) + 8 * (63 - lane);
+  u32x4 s4 = {0u, 0u, 0u, 0u};
+#pragma unroll
+  for (int i = 0; i < 8; ++i) s4 += g4[(i + lane) & 7];
+  const uint32_t mine = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+  const uint32_t above = wave_prefix_sum(mine) - mine;
+  const uint64_t who = __builtin_amdgcn_ballot_w64(above < need && need <= above + mine);   // one lane: 0 < need <= all
+  const int src = who ? __builtin_ctzll(who) : 0;
+  const int top = 32 * (63 - src) + 31;
+  const uint32_t left = need - __builtin_amdgcn_readlane(above, src);
+  const uint32_t c = lane < 32 ? h[top - lane] : 0u;
+  const uint32_t over = wave_prefix_sum(c) - c;
+  const uint64_t in = __builtin_amdgcn_ballot_w64(over < left && left <= over + c);
+  const int at = in ? __builtin_ctzll(in) : 0;
+  if (lane == at) {
+    sh.bin = static_cast<uint32_t>(top - at);
+    sh.need = left - over;
+    sh.count = c;
+  }
 }
 
 // Radix select: where the `take` largest of the workgroup's keys end.  Keys below `full` of every thread hold positions, of
@@ -70,15 +98,17 @@ __device__ __forceinline__ int sharing_lanes(uint32_t digit) {
 // 7.85 / 8.0, 5.7 / 6.7 / 6.8 (with the exact ranges 6.05, 6.5, 7.4, 8.9, 9.1, 7.0).  The passes are a loop, whose code is cold
 // in an iteration: token selection at 32768 there 0.7 less than unrolled.  (A first range that leaves masks' scores and a lone
 // low one out, with up to four passes: masked and outlier 8.6 and 18.2 at the larger two, but every other call 0.3 to 1.6 more.)
+// given: a range that holds all keys taken and the last of them, [base, base + span], instead of the workgroup's smallest and largest key.
 template <bool CROWDS = true, int N, typename Valid>
 __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int full, int live, Valid valid, uint32_t take,
-                                                 RegisterSelectShared& sh) {
+                                                 RegisterSelectShared& sh, const LastKey* given = nullptr) {
   constexpr int kWaves = kSelectThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   for (int i = tid; i < 3 * 2048 / 4; i += kSelectThreads) reinterpret_cast<u32x4*>(sh.hist)[i] = u32x4{0u, 0u, 0u, 0u};
   LastKey r;
   r.need = take;
+  r.whole = false;
   auto set_range = [&](uint32_t hi, uint32_t inv_lo) {              // (the smallest as the largest complement)
     hi = wave_max(hi);
     inv_lo = wave_max(inv_lo);
@@ -91,7 +121,11 @@ __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int f
     r.base = ~__builtin_amdgcn_readfirstlane(wave_max(sh.low[lane & (kWaves - 1)]));
     r.span = hi - r.base;
   };
-  {
+  if (given != nullptr) {
+    r.base = given->base;
+    r.span = given->span;
+    __syncthreads();
+  } else {
     uint32_t hi = 0u, inv_lo = 0u;
 #pragma unroll
     for (int u = 0; u < N; ++u) {
@@ -157,36 +191,15 @@ __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int f
       }
     }
     __syncthreads();
-    if (wave == 0) {
-      // lane l owns the 32 bins from 32 (63 - l) on, read in an order that spreads the lanes over the banks; then lanes
-      // 0..31 the bins of the lane that holds the wanted key, both from the top bin down
-      const u32x4* g4 = reinterpret_cast<const u32x4*>(h) + 8 * (63 - lane);
-      u32x4 s4 = {0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int i = 0; i < 8; ++i) s4 += g4[(i + lane) & 7];
-      const uint32_t mine = (s4[0] + s4[1]) + (s4[2] + s4[3]);
-      const uint32_t above = wave_prefix_sum(mine) - mine;
-      const uint64_t who = __builtin_amdgcn_ballot_w64(above < r.need && r.need <= above + mine);   // one lane: 0 < need <= all
-      const int src = who ? __builtin_ctzll(who) : 0;
-      const int top = 32 * (63 - src) + 31;
-      const uint32_t left = r.need - __builtin_amdgcn_readlane(above, src);
-      const uint32_t c = lane < 32 ? h[top - lane] : 0u;
-      const uint32_t over = wave_prefix_sum(c) - c;
-      const uint64_t in = __builtin_amdgcn_ballot_w64(over < left && left <= over + c);
-      const int at = in ? __builtin_ctzll(in) : 0;
-      if (lane == at) {
-        sh.bin = static_cast<uint32_t>(top - at);
-        sh.need = left - over;
-        sh.count = c;
-      }
-    }
+    if (wave == 0) walk_to_last_bin(h, r.need, sh);
     __syncthreads();
     const uint32_t start = __builtin_amdgcn_readfirstlane(sh.bin) << shift;
     r.base += start;
     r.need = __builtin_amdgcn_readfirstlane(sh.need);
     r.span = min((1u << shift) - 1u, r.span - start);               // (the last bin ends with the range: above it are taken keys)
     const uint32_t count = __builtin_amdgcn_readfirstlane(sh.count);
-    if (shift == 0 || count == r.need) break;                       // equal keys, or the whole bin is taken
+    r.whole = count == r.need;
+    if (shift == 0 || r.whole) break;                       // equal keys, or the whole bin is taken
     shift = max(shift - 11, 0);
     if (CROWDS && __builtin_expect(8u * count >= keys, 0)) {
       uint32_t hi = 0u, inv_lo = 0u;
@@ -211,7 +224,8 @@ struct CellWalk {
   static constexpr int kWaves = kSelectThreads / 64;
   static constexpr int kPerLane = ROWS * kWaves > 64 ? ROWS * kWaves / 64 : 1;
   static_assert(kWaves % kPerLane == 0, "a wave's cells sit at one place of their lanes");
-  static __device__ __forceinline__ uint32_t before(const uint32_t* cells, int rows, int wave, int lane) {
+  // total: the sum of all cells
+  static __device__ __forceinline__ uint32_t before(const uint32_t* cells, int rows, int wave, int lane, uint32_t* total = nullptr) {
     uint32_t part = 0u, all = 0u;
 #pragma unroll
     for (int c = 0; c < kPerLane; ++c) {
@@ -220,7 +234,9 @@ struct CellWalk {
       if (c < (wave & (kPerLane - 1))) part += v;
       all += v;
     }
-    return wave_prefix_sum(all) - all + part;
+    const uint32_t incl = wave_prefix_sum(all);
+    if (total != nullptr) *total = __builtin_amdgcn_readlane(incl, 63);
+    return incl - all + part;
   }
   static __device__ __forceinline__ int lane_of(int u, int wave) { return (kWaves * u + wave) / kPerLane; }
 };

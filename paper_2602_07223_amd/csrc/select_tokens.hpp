@@ -277,26 +277,270 @@ __global__ __launch_bounds__(kTokThreads) void token_select_write(const TokenSel
   }
 }
 
-// One workgroup per sequence, for prefixes of at most 4096 ROWS tokens, in one launch instead of five: a thread holds the keys
-// of tokens 4096 g + 4 tid .. + 3 in registers, find_last_key finds where the selection ends, and the taken tokens' places come
-// from one prefix sum over a wave per four keys.  The sequence's page ids wait in LDS.
-// Bound by the instructions issued on one compute unit (with one key per lane and row, places by ballots, twice as many: 32768
-// tokens 22.5 us).  us, captured, five launches / one, normally distributed
-// scores: 1 sequence of 4096 tokens 19.2 / 5.1, 8192 19.9 / 6.6, 16384 20.5 / 9.9, 32768 21.0 / 16.7; 16 of 4096 19.9 / 5.4, of
-// 32768 22.4 / 18.5.
+// ---- up to 32768 tokens: one workgroup per sequence, thread tid has tokens 4096 g + 4 tid + e (row g, e = 0..3) in registers; token
+// (g, e) is bit 4 g + e of a thread's set of tokens.
+constexpr int kRowTokens = 4 * kTokThreads;
+constexpr int kBinTies = 256;          // tokens of one bin that are ranked among each other
+
+// Tokens of all threads before each of this thread's rows, and of all rows (the result); n[g] of row g (4 at most) are this thread's.
+// One barrier inside.
+template <int ROWS>
+__device__ __forceinline__ uint32_t counts_before(const uint32_t (&n)[ROWS], uint32_t (&before)[ROWS], int rows, uint32_t* cells) {
+  constexpr int kWaves = kTokThreads / 64, kPacks = (ROWS + 2) / 3;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  uint32_t lower[kPacks], own = 0u;                // (a wave's row has 256 tokens: three counts of ten bits in one sum)
+#pragma unroll
+  for (int q = 0; q < kPacks; ++q) {
+    uint32_t pack = n[3 * q];
+    if (3 * q + 1 < ROWS) pack |= n[3 * q + 1 < ROWS ? 3 * q + 1 : 0] << 10;
+    if (3 * q + 2 < ROWS) pack |= n[3 * q + 2 < ROWS ? 3 * q + 2 : 0] << 20;
+    const uint32_t incl = wave_prefix_sum(pack);
+    lower[q] = incl - pack;
+    const uint32_t of_wave = __builtin_amdgcn_readlane(incl, 63);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (lane == 3 * q + i) own = (of_wave >> (10 * i)) & 1023u;
+  }
+  if (lane < rows) cells[lane * kWaves + wave] = own;
+  __syncthreads();
+  uint32_t total;
+  const uint32_t cell = CellWalk<ROWS>::before(cells, rows, wave, lane, &total);
+#pragma unroll
+  for (int g = 0; g < ROWS; ++g)
+    before[g] = ((lower[g / 3] >> (10 * (g % 3))) & 1023u) + __builtin_amdgcn_readlane(cell, CellWalk<ROWS>::lane_of(g, wave));
+  return total;
+}
+
+// The same of a set of tokens.
+template <int ROWS>
+__device__ __forceinline__ uint32_t row_counts(uint32_t set, uint32_t (&before)[ROWS], int rows, uint32_t* cells) {
+  uint32_t n[ROWS];
+#pragma unroll
+  for (int g = 0; g < ROWS; ++g) n[g] = __popc((set >> (4 * g)) & 15u);
+  return counts_before<ROWS>(n, before, rows, cells);
+}
+
+__device__ __forceinline__ float max3(float a, float b, float c) {      // (fmaxf quiets what it is given first: an instruction a key)
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+// set = 16 set + (bit e: y[e] >= bound), of floats or unsigned keys.  (Two instructions a bit; left to the compiler, a select, a shift
+// and an or as well.)
+#define VEGAS_SHIFT_IN_GE(TYPE, SUFFIX)                                                                                                \
+  __device__ __forceinline__ void shift_in_ge(uint32_t& set, TYPE y0, TYPE y1, TYPE y2, TYPE y3, TYPE bound) {                        \
+    uint64_t c0, c1, c2, c3;                                                                                                           \
+    asm("v_cmp_le_" SUFFIX "_e64 %4, %9, %8\n\tv_cmp_le_" SUFFIX "_e64 %3, %9, %7\n\t"                                                 \
+        "v_cmp_le_" SUFFIX "_e64 %2, %9, %6\n\tv_cmp_le_" SUFFIX "_e64 %1, %9, %5\n\t"                                                 \
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %4\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\t"                                           \
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %1"                                               \
+        : "+v"(set), "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3)                                                                      \
+        : "v"(y0), "v"(y1), "v"(y2), "v"(y3), "v"(bound)                                                                            \
+        : "vcc");                                                                                                                      \
+  }
+VEGAS_SHIFT_IN_GE(float, "f32")
+VEGAS_SHIFT_IN_GE(uint32_t, "u32")
+#undef VEGAS_SHIFT_IN_GE
+
+// Largest key of the workgroup, and a lower bound of the `take`-th largest: the smallest of the largest keys of groups of tokens that are
+// disjoint and at least `take` in number, so that masked and far low scores do not count.  False where there are no such groups.
+template <int ROWS>
+__device__ __forceinline__ bool key_bounds(const float (&x)[4 * ROWS], int rows, int p_len, uint32_t take, RegisterSelectShared& sh,
+                                           LastKey& range) {
+  constexpr int kWaves = kTokThreads / 64;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (4u * take > static_cast<uint32_t>(p_len)) return false;
+  float m[ROWS], top = -INFINITY;
+#pragma unroll
+  for (int g = 0; g < ROWS; ++g) {
+    m[g] = -INFINITY;
+    if (g >= rows) continue;
+    const float three = max3(x[4 * g], x[4 * g + 1], x[4 * g + 2]);
+    m[g] = max3(three, x[4 * g + 3], x[4 * g + 3]);
+    top = max3(top, m[g], m[g]);
+  }
+  uint32_t hi = score_key(top), inv_lo = 0u;
+  // groups of N rows of a thread have 4 N tokens or fewer, so there are p_len / (4 N) of them or more
+  auto group_bound = [&](auto rows_per) {
+    constexpr int N = decltype(rows_per)::value;
+#pragma unroll
+    for (int g = 0; g < ROWS; g += N) {
+      float of_group = m[g];
+#pragma unroll
+      for (int i = 1; i < N; ++i) of_group = max3(of_group, m[g + i], m[g + i]);
+      if (kRowTokens * g + 4 * tid < p_len) inv_lo = max(inv_lo, ~score_key(of_group));
+    }
+  };
+  if (ROWS >= 4 && 16u * take <= static_cast<uint32_t>(p_len)) group_bound(std::integral_constant<int, ROWS >= 4 ? 4 : 1>{});
+  else if (ROWS >= 2 && 8u * take <= static_cast<uint32_t>(p_len)) group_bound(std::integral_constant<int, ROWS >= 2 ? 2 : 1>{});
+  else group_bound(std::integral_constant<int, 1>{});
+  hi = wave_max(hi);
+  inv_lo = wave_max(inv_lo);
+  if (lane == 0) {
+    sh.high[wave] = hi;
+    sh.low[wave] = inv_lo;
+  }
+  __syncthreads();
+  hi = __builtin_amdgcn_readfirstlane(wave_max(sh.high[lane & (kWaves - 1)]));
+  range.base = ~__builtin_amdgcn_readfirstlane(wave_max(sh.low[lane & (kWaves - 1)]));
+  range.span = hi - range.base;
+  const bool ok = range.base > score_key(-INFINITY) && hi >= range.base && hi < score_key(INFINITY);
+  if (!ok) __syncthreads();                        // (find_last_key writes its own bounds there)
+  return ok;
+}
+
+// The set of this thread's tokens among the `take` largest scores, found among the scores themselves: 2048 bins of equal width over the
+// range, one pass that counts, one that takes what lies above the last bin, and the few tokens of that bin ranked among each other.  False
+// where the scores do not spread over such bins.  A bin is a monotone function of the score (one multiply-add to a number whose low bits
+// are the bin), whatever it rounds, so the set is right if it has `take` tokens, and false is the result if it has not.
+// before: tokens taken before this thread's of a row.
+template <int ROWS>
+__device__ __forceinline__ bool take_by_bins(const float (&x)[4 * ROWS], int rows, uint32_t take, const LastKey& range,
+                                             RegisterSelectShared& sh, uint32_t* cells, uint32_t& taken, uint32_t (&before)[ROWS]) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint32_t* const hist = sh.hist[0];
+  uint32_t* const ranked = sh.hist[1];             // [thread] its tokens of the last bin that are kept
+  uint64_t* const ties = reinterpret_cast<uint64_t*>(sh.hist[2]);
+  static_assert(sizeof(sh.hist[1]) >= kTokThreads * 4 && sizeof(sh.hist[2]) >= kBinTies * 8, "sets and ties alias digit counts");
+  auto score_of = [](uint32_t key) { return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key); };
+  const float lo = score_of(range.base), hi = score_of(range.base + range.span);
+  constexpr float kOne = 2097152.f;                // 2^21: numbers from there to its double have their quarters in bits 0 and 1
+  const float scale = 2040.f / (hi - lo);
+  const float shift = kOne + 3.f - lo * scale;
+  if (!(scale > 0.f && fabsf(lo) * scale < kOne && fabsf(hi) * scale < kOne)) return false;      // (too near, too far from 0)
+  auto place = [&](float v) { return __builtin_fmaf(v, scale, shift); };                        // 2^21 + bin
+  constexpr uint32_t kBinBytes = 2047u * 4u;
+  reinterpret_cast<u32x4*>(hist)[tid] = u32x4{0u, 0u, 0u, 0u};     // (both)
+  if (tid == 0) sh.crowded = sh.listed = 0u;
+  __syncthreads();
+  const float first = place(x[0]);
+  if (sharing_lanes(first >= kOne + 1.f ? __float_as_uint(first) & kBinBytes : kNoDigit) < 3) {
+    uint32_t one = 1u;
+    asm("" : "+v"(one));
+#pragma unroll
+    for (int u = 0; u < 4 * ROWS; ++u) {
+      if ((u >> 2) >= rows) continue;
+      const float y = place(x[u]);
+      if (y >= kOne + 1.f) atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(hist) + (__float_as_uint(y) & kBinBytes)), one);
+    }
+  } else if (lane == 0) {
+    sh.crowded = 1u;
+  }
+  __syncthreads();
+  if (sh.crowded != 0u) return false;
+  if (wave == 0) walk_to_last_bin(hist, take, sh);
+  __syncthreads();
+  const uint32_t bin = __builtin_amdgcn_readfirstlane(sh.bin), need = __builtin_amdgcn_readfirstlane(sh.need);
+  const uint32_t count = __builtin_amdgcn_readfirstlane(sh.count);
+  const bool whole = need == count;                // the last bin is kept whole
+  if (!whole && count > kBinTies) return false;
+  const float in = kOne + static_cast<float>(bin), above = whole ? in : in + 1.f;
+  uint32_t set = 0u;
+#pragma unroll
+  for (int g = ROWS - 1; g >= 0; --g) {
+    if (g >= rows) continue;
+    float y[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = place(x[4 * g + e]);
+    uint32_t at_least = 0u;
+    shift_in_ge(set, y[0], y[1], y[2], y[3], above);
+    shift_in_ge(at_least, y[0], y[1], y[2], y[3], in);
+    const uint32_t tie = at_least ^ (set & 15u);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(tie != 0u) != 0, 0)) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if ((tie >> e) & 1u) {                     // larger score, then lower position: larger entry
+          const uint32_t at = atomicAdd(&sh.listed, 1u);
+          if (at < kBinTies) ties[at] = (static_cast<uint64_t>(score_key(x[4 * g + e])) << 32) | ~static_cast<uint32_t>(kRowTokens * g + 4 * tid + e);
+        }
+      }
+    }
+  }
+  if (!whole) {
+    __syncthreads();
+    if (tid < static_cast<int>(count)) {
+      const uint64_t own = ties[tid];
+      uint32_t before = 0u;
+#pragma unroll 4
+      for (uint32_t c = 0; c < count; ++c) before += ties[c] > own ? 1u : 0u;
+      const uint32_t j = ~static_cast<uint32_t>(own);
+      if (before < need) atomicOr(&ranked[(j >> 2) & (kTokThreads - 1)], 1u << ((4 * (j / kRowTokens) + (j & 3)) & 31u));
+    }
+    __syncthreads();
+    set |= ranked[tid];
+  }
+  taken = set;
+  return row_counts<ROWS>(set, before, rows, cells) == take;
+}
+
+// The same by find_last_key, for scores of any kind: within the range, if there is one, and if that does not yield `take` tokens (the
+// range is that of floating-point comparisons, which some NaNs upset) among all keys.
+template <int ROWS>
+__device__ __forceinline__ uint32_t take_by_digits(const uint32_t (&key)[4 * ROWS], int rows, int p_len, uint32_t take, bool ranged,
+                                                   const LastKey& range, RegisterSelectShared& sh, uint32_t (*cells)[ROWS * (kTokThreads / 64)],
+                                                   uint32_t (&before)[ROWS]) {
+  const int tid = threadIdx.x;
+  auto valid = [&](int u) { return kRowTokens * (u >> 2) + 4 * tid + (u & 3) < p_len; };
+  uint32_t set;
+#pragma unroll 1
+  for (;; ranged = false) {
+    const LastKey last = find_last_key(key, p_len / kRowTokens * 4, 4 * rows, valid, take, sh, ranged ? &range : nullptr);
+    // (a last bin that ends with the largest key there is has nothing above it)
+    const uint32_t above = last.base + last.span + 1u;
+    uint32_t in = 0u;
+    set = 0u;
+#pragma unroll
+    for (int g = ROWS - 1; g >= 0; --g) {
+      if (g >= rows) continue;
+      shift_in_ge(in, key[4 * g], key[4 * g + 1], key[4 * g + 2], key[4 * g + 3], last.base);
+      if (above != 0u) shift_in_ge(set, key[4 * g], key[4 * g + 1], key[4 * g + 2], key[4 * g + 3], above);
+    }
+    in &= ~set;
+    if (last.whole) {
+      set |= in;
+    } else {
+      row_counts<ROWS>(in, before, rows, cells[0]);
+#pragma unroll
+      for (int g = 0; g < ROWS; ++g) {
+        // of the row's tokens in the last bin as many as are still wanted, the lower ones first
+        const uint32_t left = last.need > before[g] ? last.need - before[g] : 0u;
+        uint32_t row = (in >> (4 * g)) & 15u;
+#pragma unroll
+        for (int drop = 3; drop >= 0; --drop)
+          if (__popc(row) > static_cast<int>(left)) row &= ~(1u << drop);
+        set |= row << (4 * g);
+      }
+    }
+    if (row_counts<ROWS>(set, before, rows, cells[1]) == take || !ranged) break;
+  }
+  return set;
+}
+
+// One workgroup per sequence, for prefixes of at most 4096 ROWS tokens, in one launch instead of five: a thread holds the scores
+// of tokens 4096 g + 4 tid .. + 3 in registers; which are taken is a bit each, and their places come from prefix sums over a wave that
+// count three rows at once.  The sequence's page ids wait in LDS.
+// Bound by the instructions issued on one compute unit, 0.2 us for each one that every key of 32768 takes.  Digits of the keys
+// (find_last_key) take some forty a key, most of them to make keys and to count and place one by one; bins over the scores take half.
+// us, captured, five launches / by digits / now, normally distributed scores: 1 sequence of 4096 tokens 19.2 / 5.1 / 4.4, 8192 19.9 / 6.7 /
+// 5.1, 16384 20.5 / 11.6 / 7.0, 32768 21.0 / 16.8 / 10.5; 16 of 32768 22.4 / 18.6 / 11.3; a twentieth -infinity 32768 20.6 / 25.6 / 10.2, a far
+// low one 20.6 / 23.4 / 10.6, rising with the position 20.6 / 19.0 / 10.6, half 0 19.7 / 10.5.  Where bins do not tell the scores apart, by
+// digits / now: four values 19.8 / 22.5, one at 3e38 23.4 / 25.0, fifteen in sixteen 0 19.2 / 20.5, all equal 10.9 / 11.9, exp of five times
+// a normal one 15.7 / 14.9; over a quarter of the tokens taken, which has digits alone, 16.8 / 15.6.  In an iteration of 32768 tokens, whose
+// instructions are cold, 80.3 -> 71.1.
 template <int ROWS>
 __global__ __launch_bounds__(kTokThreads) void token_select_one_kernel(const TokenSelectParams p) {
   static_assert(kTokThreads == kSelectThreads, "find_last_key");
   constexpr int kWaves = kTokThreads / 64;
-  constexpr int kRowTokens = 4 * kTokThreads;
   constexpr int kPageTrips = (ROWS * kRowTokens / kPage + kTokThreads - 1) / kTokThreads;
   __shared__ __align__(16) RegisterSelectShared reg_shared;
-  __shared__ uint32_t cells[ROWS * kWaves];
+  __shared__ uint32_t cells[2][ROWS * kWaves];
   __shared__ int32_t pages[kPageTrips * kTokThreads];
   typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));     // (scores may start at any float)
   const int b = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = threadIdx.x;
   const int32_t* table = p.block_table + static_cast<int64_t>(b) * p.max_blocks;
   const float* scores = p.scores + static_cast<int64_t>(b) * p.max_blocks * kPage;
   int32_t* sel = p.sel_table + static_cast<int64_t>(b) * p.max_sel;
@@ -316,50 +560,43 @@ __global__ __launch_bounds__(kTokThreads) void token_select_one_kernel(const Tok
   auto slot_of = [&](int j) -> int32_t { return pages[j >> 4] * kPage + (j & 15); };
   if (t.need_search) {
     const int rows = (t.p_len + kRowTokens - 1) / kRowTokens;        // at most ROWS: the host's bound on the lengths says so
-    uint32_t key[4 * ROWS];
-    auto valid = [&](int u) { return kRowTokens * (u >> 2) + 4 * tid + (u & 3) < t.p_len; };
-#pragma unroll
-    for (int u = 0; u < 4 * ROWS; ++u) {
-      key[u] = score_key(sc[u >> 2][u & 3]);
-      if (kRowTokens * ((u >> 2) + 1) > t.p_len && !valid(u)) key[u] = 0u;
-    }
-    const LastKey last = find_last_key(key, t.p_len / kRowTokens * 4, 4 * rows, valid, static_cast<uint32_t>(t.kc), reg_shared);
-    // Counts of keys above the last bin (low half) and in it, of the lower lanes of this wave and of each (row, wave).
-    const uint32_t top = last.base + last.span;
-    uint32_t below[ROWS], total = 0u;
+    const uint32_t take = static_cast<uint32_t>(t.kc);
+    float x[4 * ROWS];
 #pragma unroll
     for (int g = 0; g < ROWS; ++g) {
-      below[g] = 0u;
-      if (g >= rows) continue;
-      uint32_t gt = 0u, ge = 0u;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        gt += key[4 * g + e] > top ? 1u : 0u;
-        ge += key[4 * g + e] >= last.base ? 1u : 0u;
+      for (int e = 0; e < 4; ++e) x[4 * g + e] = sc[g][e];
+      if (kRowTokens * (g + 1) > t.p_len) {
+        asm volatile("");                          // (a branch; as selects, three instructions for every key of every row)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (kRowTokens * g + 4 * tid + e >= t.p_len) x[4 * g + e] = -INFINITY;
       }
-      const uint32_t mine = gt | ((ge - gt) << 16);
-      const uint32_t incl = wave_prefix_sum(mine);
-      below[g] = incl - mine;
-      const uint32_t of_wave = __builtin_amdgcn_readlane(incl, 63);
-      if (lane == g) total = of_wave;
     }
-    if (lane < rows) cells[lane * kWaves + wave] = total;
-    __syncthreads();
-    const uint32_t before = CellWalk<ROWS>::before(cells, rows, wave, lane);
+    LastKey range;
+    uint32_t taken, before[ROWS];
+    const bool ranged = key_bounds<ROWS>(x, rows, t.p_len, take, reg_shared, range);
+    if (!(ranged && take_by_bins<ROWS>(x, rows, take, range, reg_shared, cells[1], taken, before))) {
+      uint32_t key[4 * ROWS];
+#pragma unroll
+      for (int u = 0; u < 4 * ROWS; ++u) {
+        key[u] = score_key(x[u]);
+        if (kRowTokens * ((u >> 2) + 1) > t.p_len && kRowTokens * (u >> 2) + 4 * tid + (u & 3) >= t.p_len) key[u] = 0u;
+      }
+      taken = take_by_digits<ROWS>(key, rows, t.p_len, take, ranged, range, reg_shared, cells, before);
+    }
+    unsigned char* const out = uniform_ptr_mut(reinterpret_cast<unsigned char*>(sel));
 #pragma unroll
     for (int g = 0; g < ROWS; ++g) {
       if (g >= rows) continue;
-      const uint32_t run = below[g] + __builtin_amdgcn_readlane(before, CellWalk<ROWS>::lane_of(g, wave));
-      uint32_t above = run & 0xFFFFu, in = run >> 16;
-      const int j0 = kRowTokens * g + 4 * tid;
-      const int32_t slot0 = slot_of(j0);
+      const int32_t slot0 = slot_of(kRowTokens * g + 4 * tid);
+      uint32_t at = before[g] * 4u;                // (take <= max_sel)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const bool gt = key[4 * g + e] > top, ge = key[4 * g + e] >= last.base;
-        const uint32_t rank = above + min(in, last.need);
-        if (ge && (gt || in < last.need) && rank < static_cast<uint32_t>(p.max_sel)) sel[rank] = slot0 + e;
-        above += gt ? 1u : 0u;
-        in += ge && !gt ? 1u : 0u;
+        if ((taken >> (4 * g + e)) & 1u) {
+          *reinterpret_cast<int32_t*>(out + at) = slot0 + e;
+          at += 4u;
+        }
       }
     }
   } else if (t.take_all) {
