@@ -422,25 +422,38 @@ __host__ __device__ __forceinline__ uint32_t ceil_div_small(uint32_t x, uint32_t
   const uint32_t q = floor_div_small<Wave>(x, d);
   return q * d < x ? q + 1u : q;
 }
+// Are chunks of c units, of sequences of nu units (this lane's), at most J?
+template <typename Wave>
+__host__ __device__ __forceinline__ bool chunks_fit(uint32_t nu, uint32_t c, uint32_t J) {
+  return Wave::sum(ceil_div_small<Wave>(nu, c)) <= J;
+}
 // Smallest C >= 1 (in units) with sum over lanes of ceil(nu / C) <= J; nu is this lane's length in units (< 2^18),
 // total their sum, longest their maximum (the condition always holds there when J >= number of sequences, and
 // nothing changes beyond it).  No plan can beat ceil(total / J), and a batch of equal lengths meets it, so the
-// search starts there and widens its steps before it bisects: one evaluation for a uniform batch.
+// search starts there (balanced_lower_bound) and, where that fails, widens its steps before it bisects; it ends at `most` units at the latest,
+// which fit or are no less than the longest.
 template <typename Wave>
-__host__ __device__ __forceinline__ uint32_t balanced_chunk_units(uint32_t nu, uint32_t total, uint32_t longest, uint32_t J) {
-  auto fits = [&](uint32_t c) { return Wave::sum(ceil_div_small<Wave>(nu, c)) <= J; };
-  uint32_t lo = ceil_div_small<Wave>(total, J);                 // wave-uniform from here on
-  lo = lo < 1u ? 1u : lo;
-  if (lo >= longest || fits(lo)) return lo < longest ? lo : longest;
+__host__ __device__ __forceinline__ uint32_t balanced_lower_bound(uint32_t total, uint32_t J) {
+  const uint32_t lo = ceil_div_small<Wave>(total, J);           // wave-uniform from here on
+  return lo < 1u ? 1u : lo;
+}
+template <typename Wave>
+__host__ __device__ __forceinline__ uint32_t balanced_search(uint32_t nu, uint32_t lo, uint32_t most, uint32_t J) {
   uint32_t step = (lo + 15u) / 16u, hi = lo + step;             // lo fails; find a length that fits
-  while (hi < longest && !fits(hi)) { lo = hi; step *= 2u; hi = lo + step; }
-  hi = hi < longest ? hi : longest;
+  while (hi < most && !chunks_fit<Wave>(nu, hi, J)) { lo = hi; step *= 2u; hi = lo + step; }
+  hi = hi < most ? hi : most;
   ++lo;                                                         // invariant: everything below lo fails, hi fits (or is the end)
   while (lo < hi) {
     const uint32_t mid = (lo + hi) >> 1;
-    if (fits(mid)) hi = mid; else lo = mid + 1u;
+    if (chunks_fit<Wave>(nu, mid, J)) hi = mid; else lo = mid + 1u;
   }
   return lo;
+}
+template <typename Wave>
+__host__ __device__ __forceinline__ uint32_t balanced_chunk_units(uint32_t nu, uint32_t total, uint32_t longest, uint32_t J) {
+  const uint32_t lo = balanced_lower_bound<Wave>(total, J);
+  if (lo >= longest || chunks_fit<Wave>(nu, lo, J)) return lo < longest ? lo : longest;
+  return balanced_search<Wave>(nu, lo, longest, J);
 }
 // Would chunks of C units, the longest of a plan for j1 workgroups, leave more than a tenth of them idle after giving up
 // second_cost units, what the alternative costs?  total / j1 is the lower bound of any plan.  second_cost is high where its workgroups cannot start beside the first's (64-row workgroups fill a
@@ -460,6 +473,15 @@ __host__ __device__ __forceinline__ bool wants_second_wave(uint32_t total, uint3
 // begin and to end (7 of 15501, 48 rows and token sums, 31 / 27.3: 215.9 / 218.9 for the iteration).
 __host__ __device__ __forceinline__ bool wants_shares(uint32_t priced, uint32_t lives, uint32_t J, uint32_t C, uint32_t margin) {
   return lives <= J && 10u * J * C > 11u * priced + 8u * lives && C >= (priced + J - 1u) / J + margin;
+}
+
+// The smallest C for which it is, given no more sequences than workgroups: C is at least that if one unit less does not fit, so a batch that
+// is cut into shares needs two trial lengths and no search, which takes eight as a rule, each a division and a sum over the wave.  (11
+// priced + 8 lives is below 2^27 and the quotient below 2^18: the division holds.)
+template <typename Wave>
+__host__ __device__ __forceinline__ uint32_t least_shared_chunk(uint32_t priced, uint32_t lives, uint32_t J, uint32_t S, uint32_t margin) {
+  const uint32_t more = floor_div_small<Wave>(11u * priced + 8u * lives, 10u * J) + 1u;
+  return more > S + margin ? more : S + margin;
 }
 
 // slots: workgroups there are; share_margin: for wants_shares, or -1 for no shares; second_cost: for wants_second_wave.
@@ -483,10 +505,23 @@ __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* le
   const uint32_t longest = Wave::max(nu);
   const uint64_t live = Wave::ballot(nu > 0u);
   const uint32_t J = j1, lives = __builtin_popcountll(live);
-  uint32_t C = balanced_chunk_units<Wave>(nu, total, longest, J);
   const uint32_t priced = total + kShareCost * (lives - 1u), S = ceil_div_small<Wave>(priced, J);
-  if (share_margin >= 0 && S <= static_cast<uint32_t>(cap_units) && J + lives <= static_cast<uint32_t>(slots) + 1u &&
-      wants_shares(priced, lives, J, C, static_cast<uint32_t>(share_margin))) {
+  const uint32_t bound = balanced_lower_bound<Wave>(total, J);
+  const bool equal = bound >= longest || chunks_fit<Wave>(nu, bound, J);       // (the longest chunk is the bound: no shares)
+  bool shares = false;
+  uint32_t C = bound < longest ? bound : longest;
+  if (!equal) {
+    uint32_t most = longest;
+    if (share_margin >= 0 && S <= static_cast<uint32_t>(cap_units) && J + lives <= static_cast<uint32_t>(slots) + 1u && lives <= J) {
+      const uint32_t below = least_shared_chunk<Wave>(priced, lives, J, S, static_cast<uint32_t>(share_margin)) - 1u;
+      if (below < longest) {
+        shares = !chunks_fit<Wave>(nu, below, J);
+        most = below;
+      }
+    }
+    if (!shares) C = balanced_search<Wave>(nu, bound, most, J);
+  }
+  if (shares) {
     const uint32_t rank = __builtin_popcountll(live & ((1ull << lane) - 1ull));
     const uint32_t base = Wave::prefix_sum(nu) - nu + kShareCost * rank;       // where the sequence's first token lies
     const uint32_t q = floor_div_small<Wave>(base, S), count = nu > 0u ? floor_div_small<Wave>(base + nu - 1u, S) - q + 1u : 0u;
@@ -504,10 +539,13 @@ __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* le
       piece = at - Wave::readlane(before, __builtin_ctzll(hit)) + 1u;
     } else {                                                    // the others, longest first
       uint32_t at_head = mids, at_tail = mids;
-      for (int i = 0; i < B; ++i) {
-        const uint32_t hi = Wave::readlane(head, i), ti = Wave::readlane(tail, i);
-        at_head += (hi > head || (hi == head && i < lane) ? 1u : 0u) + (ti > head ? 1u : 0u);
-        at_tail += (hi >= tail ? 1u : 0u) + (ti > tail || (ti == tail && i < lane) ? 1u : 0u);
+      for (int i0 = 0; i0 < B; i0 += 4) {                       // (lanes past the batch have nothing)
+#pragma unroll
+        for (int i = i0; i < i0 + 4; ++i) {
+          const uint32_t hi = Wave::readlane(head, i), ti = Wave::readlane(tail, i);
+          at_head += (hi + (i < lane ? 1u : 0u) > head ? 1u : 0u) + (ti > head ? 1u : 0u);
+          at_tail += (hi >= tail ? 1u : 0u) + (ti + (i < lane ? 1u : 0u) > tail ? 1u : 0u);
+        }
       }
       const uint64_t heads = Wave::ballot(head > 0u && at_head == at);
       const uint64_t tails = Wave::ballot(tail > 0u && at_tail == at);
@@ -529,10 +567,13 @@ __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* le
   const uint32_t s = ceil_div_small<Wave>(nu, C);               // chunks of this sequence (0 if empty)
   const int chunk = s > 0u ? static_cast<int>(ceil_div_small<Wave>(nu, s) * unit) : 0;   // equal chunks, at most C units
   int P = 0;                                                    // slots of the sequences with longer chunks
-  for (int i = 0; i < B; ++i) {
-    const int ci = Wave::readlane(chunk, i);
-    const int si = Wave::readlane(static_cast<int>(s), i);
-    P += (ci > chunk || (ci == chunk && i < lane)) ? si : 0;
+  for (int i0 = 0; i0 < B; i0 += 4) {                           // (lanes past the batch have none)
+#pragma unroll
+    for (int i = i0; i < i0 + 4; ++i) {
+      const int ci = Wave::readlane(chunk, i);
+      const int si = Wave::readlane(static_cast<int>(s), i);
+      P += ci + (i < lane ? 1 : 0) > chunk ? si : 0;
+    }
   }
   if (plan_out && lane < B) plan_out[lane] = make_int2(P, chunk > 0 ? chunk : unit);
   const uint64_t hit = Wave::ballot(lane < B && s > 0u && j >= P && j < P + static_cast<int>(s));
