@@ -242,6 +242,152 @@ __device__ __forceinline__ void merge_planned_rows(const FinalizeParams& p, cons
   *reinterpret_cast<u32x2*>(p.out + ((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * p.D + d) = packed;
 }
 
+// Page criticality of 32 pages for at most MAXS (<= 64) chunks that the host cut, all of a head's slots its own: the global log-sum-exp of
+// every collected row from its chunks' (max, sum) pairs, then the sums over rows and heads.
+// Wave w takes the chunks MAXS / 4 w .., lane and round the row: a pair's address is a uniform base per chunk and a 32-bit offset per row, one
+// division (by a reciprocal) per round, and whether a chunk counts is uniform.  Four waves with a compute unit to themselves have nothing
+// that hides an instruction: of 10600 cycles at 160 rows and 32 chunks 2500 went into the addresses of 24 pairs a thread (a unit of four
+// chunks of one row each, with two integer divisions), 2900 into merging them in two stages.  us for merge and scores, captured, units of
+// four chunks / this: 20 rows of 8 heads 4096 tokens 5.4 / 4.3, 32768 5.5 / 4.3; 28 rows, 131072 7.7 / 5.6; 32 rows, 50000 9.9 / 5.8; 40 rows,
+// head dimension 64, 32768 7.8 / 5.5; 48 rows, 8192 10.8 / 5.8, two of twelve tokens', 32768 6.0 / 3.8; 56 rows, 131072 11.9 / 7.8; 96 rows, head
+// dimension 64, 20000 14.8 / 8.0; one head, 700 4.1 / 3.1.
+template <int MAXS, int ROUNDS>
+__device__ __forceinline__ void score_pages(const FinalizeParams& p, float* smf, int b) {
+  static_assert(MAXS > 0, "a bound on the chunks");
+  constexpr int NC = MAXS / 4;                // chunks of a wave
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int Rc = p.Rc, rows = p.Hkv * Rc;     // the collected rows
+  const int jbase = (static_cast<int>(blockIdx.x) - p.nA) * 32, pg = tid & 31, slot = tid >> 5;
+  float2* const sm_pair = reinterpret_cast<float2*>(smf);          // [wave][rows] (max, sum) of a row over a wave's chunks
+  float* const sm_row = smf + ((8 * rows + 3) & ~3);               // [rows] global log-sum-exp; -inf for rows that do not count
+  float* const sm_sum = smf + ((8 * rows + 3) & ~3) + ((rows + 3) & ~3);     // [8][32]
+  int zero = 0;
+  asm("" : "+v"(zero));                       // (a vector load, the first to come back: a scalar one is waited for at once)
+  int n = p.lens[b + zero];
+  const unsigned char* const ml = reinterpret_cast<const unsigned char*>(p.part_ml + static_cast<int64_t>(b) * p.Hkv * p.nsplit * p.R);
+  const uint32_t chunk_bytes = static_cast<uint32_t>(p.R) * 8u;
+  const float rcp_rc = __builtin_amdgcn_rcpf(static_cast<float>(Rc));
+  const bool all = p.collect_rows == 1 || p.G <= 2;
+  f32x2 v[ROUNDS][NC];
+  auto load_pairs = [&](int first) {
+#pragma unroll
+    for (int a = 0; a < ROUNDS; ++a) {
+      const int i = min(first + 64 * a + lane, rows - 1);
+      const int h = static_cast<int>((static_cast<float>(i) + 0.5f) * rcp_rc), c = i - h * Rc;
+      const int r = all || c < p.g ? c : c + (p.G - 2) * p.g;      // (collected_row)
+      const uint32_t off = static_cast<uint32_t>(h * p.nsplit) * chunk_bytes + static_cast<uint32_t>(r) * 8u;
+#pragma unroll
+      for (int q = 0; q < NC; ++q)
+        v[a][q] = gload<f32x2, false>(uniform_ptr(ml + static_cast<uint32_t>(min(wave * NC + q, p.nsplit - 1)) * chunk_bytes), off);
+    }
+  };
+  load_pairs(0);
+  // The thread's page values, where they are few, are requested behind the pairs: they are needed last.
+  const bool pre_ok = (Rc & 3) == 0 && Rc <= 4 * kFinPre && p.Hkv <= 8;
+  f32x4 pre[kFinPre];
+  if (pre_ok && slot < p.Hkv) {
+    const float* pl = p.page_lse + ((static_cast<int64_t>(b) * p.Hkv + slot) * p.lse_pages + min(jbase + pg, p.lse_pages - 1)) * Rc;
+#pragma unroll
+    for (int q = 0; q < kFinPre; ++q)
+      if (4 * q < Rc) pre[q] = *reinterpret_cast<const f32x4*>(pl + 4 * q);
+  }
+  float* const out_row = p.block_scores + static_cast<int64_t>(b) * p.max_blocks;
+  n = __builtin_amdgcn_readfirstlane(n);
+  n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
+  const int nblk = (n + kPage - 1) / kPage;
+  if (jbase >= nblk) {                        // whole workgroup past the sequence
+    if (tid < 32 && jbase + tid < p.max_blocks) out_row[jbase + tid] = 0.f;
+    return;
+  }
+  // chunks of this wave that the sequence reaches
+  int mine = 0;
+#pragma unroll
+  for (int q = 0; q < NC; ++q) mine += static_cast<int64_t>(wave * NC + q) * p.chunk_tokens < n ? 1 : 0;
+  auto merge = [&](const f32x2 (&x)[NC], auto whole) {
+    float m = -INFINITY, L = 0.f;
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+      if (decltype(whole)::value || q < mine) m = fmaxf(m, x[q][0]);
+    const float mu = (m == -INFINITY) ? 0.f : m;
+#pragma unroll
+    for (int q = 0; q < NC; ++q)
+      if (decltype(whole)::value || q < mine) L += x[q][1] * fast_exp2(x[q][0] - mu);
+    return make_float2(m, L);
+  };
+  for (int first = 0; first < rows; first += 64 * ROUNDS) {
+    if (first > 0) load_pairs(first);
+#pragma unroll
+    for (int a = 0; a < ROUNDS; ++a) {
+      const int i = first + 64 * a + lane;
+      if (first + 64 * a >= rows) continue;
+      const float2 pair = mine == NC ? merge(v[a], std::true_type{}) : merge(v[a], std::false_type{});
+      if (i < rows) sm_pair[wave * rows + i] = pair;
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < rows; i += 256) {
+    float2 w[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) w[q] = sm_pair[q * rows + i];
+    const float m = fmaxf(fmaxf(w[0].x, w[1].x), fmaxf(w[2].x, w[3].x));
+    const float mu = (m == -INFINITY) ? 0.f : m;
+    float L = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) L += w[q].y * fast_exp2(w[q].x - mu);
+    sm_row[i] = (L > 0.f) ? mu + fast_log2(L) : -INFINITY;
+  }
+  __syncthreads();
+  const int j = jbase + pg;
+  float sc = 0.f;
+  auto add = [&](float x, float rl) { sc += rl != -INFINITY ? fast_exp2(x - rl) : 0.f; };
+  if (j < nblk) {
+    if (pre_ok) {
+      if (slot < p.Hkv) {
+#pragma unroll
+        for (int q = 0; q < kFinPre; ++q) {
+          if (4 * q < Rc) {
+            const f32x4 rl = *reinterpret_cast<const f32x4*>(sm_row + slot * Rc + 4 * q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) add(pre[q][e], rl[e]);
+          }
+        }
+      }
+    } else {
+      for (int h = slot; h < p.Hkv; h += 8) {
+        const float* pl = p.page_lse + ((static_cast<int64_t>(b) * p.Hkv + h) * p.lse_pages + j) * Rc;
+        const float* rl = sm_row + h * Rc;
+        if ((Rc & 3) == 0) {
+          for (int r = 0; r < Rc; r += 4) {
+            const f32x4 x = *reinterpret_cast<const f32x4*>(pl + r);
+            const f32x4 of = *reinterpret_cast<const f32x4*>(rl + r);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) add(x[e], of[e]);
+          }
+        } else {
+          // (Eight requests at a time: one by one a page's rows are as many round trips, 77 rows 48 us for the kernel.)
+          for (int r = 0; r < Rc; r += 8) {
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = pl[min(r + e, Rc - 1)];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+              if (r + e < Rc) add(x[e], rl[r + e]);
+          }
+        }
+      }
+    }
+  }
+  sm_sum[slot * 32 + pg] = sc;
+  __syncthreads();
+  if (slot == 0 && j < p.max_blocks) {
+    float tot = 0.f;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) tot += sm_sum[q * 32 + pg];
+    out_row[j] = (j < nblk) ? tot * p.inv_norm : 0.f;
+  }
+}
+
 // METRIC 1 (the paper's logit metric, token granularity) replaces the page-score role by workgroups
 // [nA, nA + nC) that add the H_kv per-head token sums of 1024 tokens each: score[b][i] = tok_norm *
 // sum_h partial[b][h][i] for prefix tokens i < n_b - G (Sec. 3.3, last paragraph), 0 elsewhere.
@@ -379,6 +525,10 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
   }
 
   // ---- role B: 32 pages; thread = (page, head slot)
+  if constexpr (MAXS > 0) {
+    score_pages<MAXS, UNITS / 2>(p, smf, b);
+    return;
+  }
   const int pg = tid & 31, slot = tid >> 5;
   const int jbase = (blockIdx.x - p.nA) * 32;
   float* out_row = p.block_scores + static_cast<int64_t>(b) * p.max_blocks;
