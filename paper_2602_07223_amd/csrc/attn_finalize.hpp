@@ -184,7 +184,7 @@ constexpr int kFinUnits = 6, kFinWideUnits = 10;   // (row, part of its chunks) 
 // time, (max, sum) pairs and partial rows together.  A batch has thousands of rows, so it is not one row's round trip that
 // counts but how many workgroups have to follow one another.  (With the page values below, by the profiler: 16 sequences of 8K..64K
 // tokens, 40 rows 20.4 -> 17.3 us, 24 of 1K..20K, 32 rows 13.7 -> 10.0; 4 of 64K, 20 rows 7.9 -> 7.9.)
-__device__ __forceinline__ void merge_planned_rows(const FinalizeParams& p, const ColumnSlots& cs, int b, int HR) {
+__device__ __forceinline__ void merge_planned_rows(const FinalizeParams& p, const ColumnSlots& cs, int b, int n, int HR) {
   const int per_row = p.D >> 2;                                   // threads
   const int rr = static_cast<int>(blockIdx.x) * (256 / per_row) + static_cast<int>(threadIdx.x) / per_row;
   const int d = 4 * (static_cast<int>(threadIdx.x) & (per_row - 1));
@@ -194,8 +194,6 @@ __device__ __forceinline__ void merge_planned_rows(const FinalizeParams& p, cons
   const int64_t row = (cs.off + static_cast<int64_t>(h) * cs.stride_h) * p.R + r;   // of the first slot; R rows between slots
   const float2* const ml = p.part_ml + row;
   const float* const po = p.part_o + row * p.D + d;
-  int n = p.lens[b];
-  n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
   const ColumnChunks cc = column_chunks(cs, n);
   float m = -INFINITY, L = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -242,7 +240,45 @@ __device__ __forceinline__ void merge_planned_rows(const FinalizeParams& p, cons
   *reinterpret_cast<u32x2*>(p.out + ((static_cast<int64_t>(b) * p.G + t) * p.Hq + h * p.g + j) * p.D + d) = packed;
 }
 
-// Page criticality of 32 pages for at most MAXS (<= 64) chunks that the host cut, all of a head's slots its own: the global log-sum-exp of
+// Role B's page sums of rows that no thread has in registers: page j, heads slot, slot + 8, ...
+__device__ __forceinline__ float page_by_rows(const FinalizeParams& p, const float* sm_row, int b, int slot, int j) {
+  const int Rc = p.Rc;
+  float sc = 0.f;
+  auto add = [&](float x, float rl) { sc += rl != -INFINITY ? fast_exp2(x - rl) : 0.f; };
+  for (int h = slot; h < p.Hkv; h += 8) {
+    const float* pl = p.page_lse + ((static_cast<int64_t>(b) * p.Hkv + h) * p.lse_pages + j) * Rc;
+    const float* rl = sm_row + h * Rc;
+    if ((Rc & 3) == 0) {
+      for (int r = 0; r < Rc; r += 4) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(pl + r);
+        const f32x4 of = *reinterpret_cast<const f32x4*>(rl + r);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) add(x[e], of[e]);
+      }
+    } else {
+      // (Eight requests at a time: one by one a page's rows are as many round trips, 77 rows 48 us for the kernel.)
+      for (int r = 0; r < Rc; r += 8) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = pl[min(r + e, Rc - 1)];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (r + e < Rc) add(x[e], rl[r + e]);
+      }
+    }
+  }
+  return sc;
+}
+// The score of page j (lanes of the first 32 threads): the sums of the eight head slots.
+__device__ __forceinline__ void store_page_scores(const FinalizeParams& p, const float* sm_sum, float* out_row, int j, int nblk) {
+  if (threadIdx.x >= 32 || j >= p.max_blocks) return;
+  float tot = 0.f;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) tot += sm_sum[q * 32 + threadIdx.x];
+  out_row[j] = (j < nblk) ? tot * p.inv_norm : 0.f;
+}
+
+// Page criticality of 32 pages for at most MAXS (<= 64) chunks (MANY: any number, MAXS at a time) that the host cut, all of a head's slots its own: the global log-sum-exp of
 // every collected row from its chunks' (max, sum) pairs, then the sums over rows and heads.
 // Wave w takes the chunks MAXS / 4 w .., lane and round the row: a pair's address is a uniform base per chunk and a 32-bit offset per row, one
 // division (by a reciprocal) per round, and whether a chunk counts is uniform.  Four waves with a compute unit to themselves have nothing
@@ -251,7 +287,7 @@ __device__ __forceinline__ void merge_planned_rows(const FinalizeParams& p, cons
 // four chunks / this: 20 rows of 8 heads 4096 tokens 5.4 / 4.3, 32768 5.5 / 4.3; 28 rows, 131072 7.7 / 5.6; 32 rows, 50000 9.9 / 5.8; 40 rows,
 // head dimension 64, 32768 7.8 / 5.5; 48 rows, 8192 10.8 / 5.8, two of twelve tokens', 32768 6.0 / 3.8; 56 rows, 131072 11.9 / 7.8; 96 rows, head
 // dimension 64, 20000 14.8 / 8.0; one head, 700 4.1 / 3.1.
-template <int MAXS, int ROUNDS>
+template <int MAXS, int ROUNDS, bool MANY>
 __device__ __forceinline__ void score_pages(const FinalizeParams& p, float* smf, int b) {
   static_assert(MAXS > 0, "a bound on the chunks");
   constexpr int NC = MAXS / 4;                // chunks of a wave
@@ -270,19 +306,19 @@ __device__ __forceinline__ void score_pages(const FinalizeParams& p, float* smf,
   const float rcp_rc = __builtin_amdgcn_rcpf(static_cast<float>(Rc));
   const bool all = p.collect_rows == 1 || p.G <= 2;
   f32x2 v[ROUNDS][NC];
-  auto load_pairs = [&](int first) {
+  auto load_pairs = [&](int base, int first) {
 #pragma unroll
     for (int a = 0; a < ROUNDS; ++a) {
       const int i = min(first + 64 * a + lane, rows - 1);
       const int h = static_cast<int>((static_cast<float>(i) + 0.5f) * rcp_rc), c = i - h * Rc;
       const int r = all || c < p.g ? c : c + (p.G - 2) * p.g;      // (collected_row)
-      const uint32_t off = static_cast<uint32_t>(h * p.nsplit) * chunk_bytes + static_cast<uint32_t>(r) * 8u;
+      const uint32_t off = static_cast<uint32_t>(h) * static_cast<uint32_t>(p.nsplit) * chunk_bytes + static_cast<uint32_t>(r) * 8u;
 #pragma unroll
       for (int q = 0; q < NC; ++q)
-        v[a][q] = gload<f32x2, false>(uniform_ptr(ml + static_cast<uint32_t>(min(wave * NC + q, p.nsplit - 1)) * chunk_bytes), off);
+        v[a][q] = gload<f32x2, false>(uniform_ptr(ml + static_cast<uint64_t>(min(base + wave * NC + q, p.nsplit - 1)) * chunk_bytes), off);
     }
   };
-  load_pairs(0);
+  load_pairs(0, 0);
   // The thread's page values, where they are few, are requested behind the pairs: they are needed last.
   const bool pre_ok = (Rc & 3) == 0 && Rc <= 4 * kFinPre && p.Hkv <= 8;
   f32x4 pre[kFinPre];
@@ -300,29 +336,33 @@ __device__ __forceinline__ void score_pages(const FinalizeParams& p, float* smf,
     if (tid < 32 && jbase + tid < p.max_blocks) out_row[jbase + tid] = 0.f;
     return;
   }
-  // chunks of this wave that the sequence reaches
-  int mine = 0;
+  for (int base = 0; base == 0 || (MANY && static_cast<int64_t>(base) * p.chunk_tokens < n); base += MAXS) {
+    int mine = 0;                             // chunks of this wave that the sequence reaches
 #pragma unroll
-  for (int q = 0; q < NC; ++q) mine += static_cast<int64_t>(wave * NC + q) * p.chunk_tokens < n ? 1 : 0;
-  auto merge = [&](const f32x2 (&x)[NC], auto whole) {
-    float m = -INFINITY, L = 0.f;
+    for (int q = 0; q < NC; ++q) mine += static_cast<int64_t>(base + wave * NC + q) * p.chunk_tokens < n ? 1 : 0;
+    auto merge = [&](const f32x2 (&x)[NC], float2 before, auto whole) {
+      float m = before.x, L = 0.f;
 #pragma unroll
-    for (int q = 0; q < NC; ++q)
-      if (decltype(whole)::value || q < mine) m = fmaxf(m, x[q][0]);
-    const float mu = (m == -INFINITY) ? 0.f : m;
+      for (int q = 0; q < NC; ++q)
+        if (decltype(whole)::value || q < mine) m = fmaxf(m, x[q][0]);
+      const float mu = (m == -INFINITY) ? 0.f : m;
+      if constexpr (MANY) L = before.y * fast_exp2(before.x - mu);
 #pragma unroll
-    for (int q = 0; q < NC; ++q)
-      if (decltype(whole)::value || q < mine) L += x[q][1] * fast_exp2(x[q][0] - mu);
-    return make_float2(m, L);
-  };
-  for (int first = 0; first < rows; first += 64 * ROUNDS) {
-    if (first > 0) load_pairs(first);
+      for (int q = 0; q < NC; ++q)
+        if (decltype(whole)::value || q < mine) L += x[q][1] * fast_exp2(x[q][0] - mu);
+      return make_float2(m, L);
+    };
+    for (int first = 0; first < rows; first += 64 * ROUNDS) {
+      if ((MANY && base > 0) || first > 0) load_pairs(base, first);
 #pragma unroll
-    for (int a = 0; a < ROUNDS; ++a) {
-      const int i = first + 64 * a + lane;
-      if (first + 64 * a >= rows) continue;
-      const float2 pair = mine == NC ? merge(v[a], std::true_type{}) : merge(v[a], std::false_type{});
-      if (i < rows) sm_pair[wave * rows + i] = pair;
+      for (int a = 0; a < ROUNDS; ++a) {
+        const int i = first + 64 * a + lane;
+        if (first + 64 * a >= rows) continue;
+        float2 pair = make_float2(-INFINITY, 0.f);
+        if (MANY && base > 0) pair = sm_pair[wave * rows + min(i, rows - 1)];
+        pair = mine == NC ? merge(v[a], pair, std::true_type{}) : merge(v[a], pair, std::false_type{});
+        if (i < rows) sm_pair[wave * rows + i] = pair;
+      }
     }
   }
   __syncthreads();
@@ -354,38 +394,150 @@ __device__ __forceinline__ void score_pages(const FinalizeParams& p, float* smf,
         }
       }
     } else {
-      for (int h = slot; h < p.Hkv; h += 8) {
-        const float* pl = p.page_lse + ((static_cast<int64_t>(b) * p.Hkv + h) * p.lse_pages + j) * Rc;
-        const float* rl = sm_row + h * Rc;
-        if ((Rc & 3) == 0) {
-          for (int r = 0; r < Rc; r += 4) {
-            const f32x4 x = *reinterpret_cast<const f32x4*>(pl + r);
-            const f32x4 of = *reinterpret_cast<const f32x4*>(rl + r);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) add(x[e], of[e]);
-          }
-        } else {
-          // (Eight requests at a time: one by one a page's rows are as many round trips, 77 rows 48 us for the kernel.)
-          for (int r = 0; r < Rc; r += 8) {
-            float x[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = pl[min(r + e, Rc - 1)];
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (r + e < Rc) add(x[e], rl[r + e]);
-          }
-        }
-      }
+      sc = page_by_rows(p, sm_row, b, slot, j);
     }
   }
   sm_sum[slot * 32 + pg] = sc;
   __syncthreads();
-  if (slot == 0 && j < p.max_blocks) {
-    float tot = 0.f;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) tot += sm_sum[q * 32 + pg];
-    out_row[j] = (j < nblk) ? tot * p.inv_norm : 0.f;
+  store_page_scores(p, sm_sum, out_row, j, nblk);
+}
+
+// The same under balanced chunking, for sequence b of n tokens with the slots cs: the sequence has few chunks as a rule, so a thread has a
+// row, and asks for four or eight of its pairs at a time, with one division by a reciprocal for their address.  us for merge and scores,
+// captured, units of four chunks of a row behind integer divisions, length read after the plan / this: 24 sequences of 1001..20011, 32 rows
+// 9.1 / 7.8; 16 of 8192..65536, 40 rows 15.0 / 14.5; 4 of 65536, 20 rows 6.0 / 5.2; 2 of 900..1500 5.5 / 4.5; 32 of 300..1500 5.9 / 5.3.
+// SMALL: page values are read page by page, a thread those of its page and head, as in score_pages; otherwise as they lie: a wave has every
+// fourth head, whose 32 pages are one run of quads of rows, and a quad's sum goes through LDS to the thread that adds up its page.
+// (A thread that reads the rows of its page itself, 128 or 160 bytes apart from its neighbour's, touches every line of the run with every request;
+// figures: merge_planned_rows.  One sequence, and calls of few rows, are better off with that all the same, their score workgroups wait
+// for latency and not for requests: us per iteration, page by page / by quads, 4096 tokens 44.0 / 44.6, 32768 69.7 / 70.6, 131072 157.8 /
+// 158.5.)
+template <bool SMALL>
+__device__ __forceinline__ void score_pages_planned(const FinalizeParams& p, const ColumnSlots& cs, float* smf, int b, int n) {
+  constexpr int kRuns = 5;                    // requests per head in flight, of two heads
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int Rc = p.Rc, rows = p.Hkv * Rc;
+  const int jbase = (static_cast<int>(blockIdx.x) - p.nA) * 32, pg = tid & 31, slot = tid >> 5, j = jbase + pg;
+  float* const out_row = p.block_scores + static_cast<int64_t>(b) * p.max_blocks;
+  const int nblk = (n + kPage - 1) / kPage;
+  if (jbase >= nblk) {                        // whole workgroup past the sequence
+    if (tid < 32 && j < p.max_blocks) out_row[j] = 0.f;
+    return;
   }
+  const ColumnChunks cc = column_chunks(cs, n);
+  float* const sm_row = smf;                                       // [rows] global log-sum-exp; -inf for rows that do not count
+  float* const sm_sum = smf + ((rows + 3) & ~3);                   // [8][32]
+  float* const sm_quad = sm_sum + 256;                             // [Hkv * 32][pitch]
+  const float rcp_rc = __builtin_amdgcn_rcpf(static_cast<float>(Rc));
+  const bool all = p.collect_rows == 1 || p.G <= 2;
+  const float2* const ml = p.part_ml + cs.off * p.R;
+  auto row_pairs = [&](int i) {               // the first of row i's pairs
+    const int h = static_cast<int>((static_cast<float>(i) + 0.5f) * rcp_rc), c = i - h * Rc;
+    const int r = all || c < p.g ? c : c + (p.G - 2) * p.g;        // (collected_row)
+    return ml + static_cast<int64_t>(h) * cs.stride_h * p.R + r;
+  };
+  float m = -INFINITY, L = 0.f;
+  auto add_pairs = [&](const float2* at, int s0, auto tag) {
+    constexpr int N = decltype(tag)::value;
+    float2 v[N];
+#pragma unroll
+    for (int s = 0; s < N; ++s) v[s] = at[static_cast<int64_t>(requested_slot(s0 + s, cc.last)) * p.R];
+    __builtin_amdgcn_sched_barrier(0);       // every request leaves before the first use
+    const float old = m;
+#pragma unroll
+    for (int s = 0; s < N; ++s)
+      if (s0 + s < cc.ns) m = fmaxf(m, v[s].x);
+    const float mu = (m == -INFINITY) ? 0.f : m;
+    L *= fast_exp2(old - mu);
+#pragma unroll
+    for (int s = 0; s < N; ++s)
+      if (s0 + s < cc.ns) L += v[s].y * fast_exp2(v[s].x - mu);
+  };
+  auto row_lse = [&](int i) {
+    const float2* const at = row_pairs(min(i, rows - 1));
+    m = -INFINITY;
+    L = 0.f;
+    if (cc.ns <= 4) add_pairs(at, 0, std::integral_constant<int, 4>{});
+    else for (int s0 = 0; s0 < cc.ns; s0 += 8) add_pairs(at, s0, std::integral_constant<int, 8>{});
+    if (i < rows) sm_row[i] = (L > 0.f) ? (m == -INFINITY ? 0.f : m) + fast_log2(L) : -INFINITY;
+  };
+  // page values requested before the rows' pairs are back
+  const int q4 = Rc >> 2, run = 32 * q4;                           // quads of a page, of a head's run
+  const int run_live = min(32, p.lse_pages - jbase) * q4;          // quads of a run that exist
+  const bool pre_ok = SMALL && (Rc & 3) == 0 && Rc <= 4 * kFinPre && p.Hkv <= 8;
+  const bool by_quads = !SMALL && (Rc & 3) == 0;
+  f32x4 pre[SMALL ? kFinPre : 2 * kRuns];
+  const float* const lse_base = p.page_lse + (static_cast<int64_t>(b) * p.Hkv * p.lse_pages + jbase) * Rc;
+  auto load_quads = [&](int h, int first) {
+#pragma unroll
+    for (int a = 0; a < 2 * kRuns; ++a) {
+      const int hd = h + 4 * (a / kRuns), i = first + 64 * (a % kRuns) + lane;
+      if (hd >= p.Hkv || first + 64 * (a % kRuns) >= run) continue;
+      pre[SMALL ? 0 : a] = *reinterpret_cast<const f32x4*>(lse_base + static_cast<int64_t>(hd) * p.lse_pages * Rc + 4 * min(i, run_live - 1));
+    }
+  };
+  if (pre_ok && slot < p.Hkv) {
+    const float* pl = p.page_lse + ((static_cast<int64_t>(b) * p.Hkv + slot) * p.lse_pages + min(j, p.lse_pages - 1)) * Rc;
+#pragma unroll
+    for (int q = 0; q < kFinPre; ++q)
+      if (4 * q < Rc) pre[SMALL ? q : 0] = *reinterpret_cast<const f32x4*>(pl + 4 * q);
+  }
+  if (by_quads) load_quads(wave, 0);
+  for (int first = 0; first < rows; first += 256) row_lse(first + tid);
+  __syncthreads();
+  auto add = [&](float& sum, float x, float rl) { sum += rl != -INFINITY ? fast_exp2(x - rl) : 0.f; };
+  float sc = 0.f;
+  if (by_quads) {
+    const float rcp_q4 = __builtin_amdgcn_rcpf(static_cast<float>(q4));
+    const int pitch = q4 | 1;
+    for (int h = wave; h < p.Hkv; h += 8) {
+      for (int first = 0; first < run; first += 64 * kRuns) {
+        if (h != wave || first > 0) load_quads(h, first);
+#pragma unroll
+        for (int t = 0; t < kRuns; ++t) {
+          const int i = first + 64 * t + lane;
+          if (first + 64 * t >= run) continue;
+          const int page = static_cast<int>((static_cast<float>(i) + 0.5f) * rcp_q4), q = i - page * q4;
+#pragma unroll
+          for (int two = 0; two < 2; ++two) {
+            const int hd = h + 4 * two;
+            if (hd >= p.Hkv || i >= run) continue;
+            const f32x4 x = pre[SMALL ? 0 : two * kRuns + t], rl = *reinterpret_cast<const f32x4*>(sm_row + hd * Rc + 4 * q);
+            float sum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) add(sum, x[e], rl[e]);
+            sm_quad[(hd * 32 + page) * pitch + q] = sum;
+          }
+        }
+      }
+    }
+    __syncthreads();
+    if (j < nblk) {
+      for (int h = slot; h < p.Hkv; h += 8) {
+        const float* const sums = sm_quad + (h * 32 + pg) * pitch;
+        for (int q = 0; q < q4; ++q) sc += sums[q];
+      }
+    }
+  } else if (j < nblk) {
+    if (pre_ok) {
+      if (slot < p.Hkv) {
+#pragma unroll
+        for (int q = 0; q < kFinPre; ++q) {
+          if (4 * q < Rc) {
+            const f32x4 rl = *reinterpret_cast<const f32x4*>(sm_row + slot * Rc + 4 * q);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) add(sc, pre[SMALL ? q : 0][e], rl[e]);
+          }
+        }
+      }
+    } else {
+      sc = page_by_rows(p, sm_row, b, slot, j);
+    }
+  }
+  sm_sum[slot * 32 + pg] = sc;
+  __syncthreads();
+  store_page_scores(p, sm_sum, out_row, j, nblk);
 }
 
 // METRIC 1 (the paper's logit metric, token granularity) replaces the page-score role by workgroups
@@ -398,11 +550,25 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
   const int b = blockIdx.y;
   const int tid = threadIdx.x;
   const int HR = p.Hkv * p.R;
-  const ColumnSlots cs = column_slots(p.plan, p.slots_total, b, p.Hkv, p.nsplit, p.chunk_tokens);
+  ColumnSlots cs;
+  int plan_n = 0;                             // kPlanned: the sequence's length
+  if constexpr (kPlanned) {                   // (its entry of the plan and its length in one round trip: two after each other were 0.7 us)
+    int zero = 0;
+    asm("" : "+v"(zero));
+    int2 e = p.plan[b + zero];
+    plan_n = p.lens[b + zero];
+    asm volatile("" : "+v"(e.x), "+v"(e.y), "+v"(plan_n));
+    e = make_int2(__builtin_amdgcn_readfirstlane(e.x), __builtin_amdgcn_readfirstlane(e.y));
+    plan_n = __builtin_amdgcn_readfirstlane(plan_n);
+    plan_n = plan_n < 0 ? 0 : (plan_n > p.max_tokens ? p.max_tokens : plan_n);
+    cs = planned_slots(e, p.slots_total);
+  } else {
+    cs = column_slots(nullptr, p.slots_total, b, p.Hkv, p.nsplit, p.chunk_tokens);
+  }
 
   if (static_cast<int>(blockIdx.x) < p.nA) {
     if constexpr (MAXS == kFinPlanned) {
-      merge_planned_rows(p, cs, b, HR);
+      merge_planned_rows(p, cs, b, plan_n, HR);
       return;
     }
     // ---- role A: 256 / D consecutive rows of the Hkv*R rows, D threads (= head dims) each
@@ -422,8 +588,11 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
       n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
       o = rm.finish((n + cs.chunk - 1) / cs.chunk);
     } else {
-      int n = p.lens[b];
-      n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
+      int n = plan_n;
+      if constexpr (!kPlanned) {
+        n = p.lens[b];
+        n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
+      }
       const ColumnChunks cc = column_chunks(cs, n);
       const int ns = cc.ns;
       auto store = [&](uint16_t bits) {
@@ -526,222 +695,11 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
 
   // ---- role B: 32 pages; thread = (page, head slot)
   if constexpr (MAXS > 0) {
-    score_pages<MAXS, UNITS / 2>(p, smf, b);
-    return;
-  }
-  const int pg = tid & 31, slot = tid >> 5;
-  const int jbase = (blockIdx.x - p.nA) * 32;
-  float* out_row = p.block_scores + static_cast<int64_t>(b) * p.max_blocks;
-  float* sm_row = smf;                        // [HR] global row lse; -inf for rows that do not count
-  float* sm_sum = smf + HR;                   // [8][32]
-  float2* sm_pair = reinterpret_cast<float2*>(smf + HR + 256);   // [HR][parts] (max, sum) of a row over one part of the chunks
-
-  // Each (row, part of the chunks) pair is one unit of work: a thread requests the (max, sum) pairs of
-  // kUnits units (four chunks each) at once and merges them afterwards, so the table costs about one
-  // memory round trip per batch instead of one per chunk.  Slots of chunks past the sequence's end are
-  // loaded too (the workspace holds nsplit of them) and dropped at the merge.  Eight parts, or as few as cover a
-  // smaller number of chunks four at a time (units without chunks would only add rounds).
-  // ns_live: chunk slots worth loading.  With balanced chunking the slots of a head are shared by all sequences and
-  // one sequence owns few of them, so its count is worked out first (one more round trip, in a kernel that is
-  // bound by bytes at such batch sizes); otherwise every slot up to the host's bound is requested at once.
-  // (Six units per batch hold the whole table of one sequence of 32 chunks and 192 rows in flight, ten that of 320; a planned
-  // sequence has few chunks, and there it pays to have more workgroups on a CU than its registers would leave room for.)
-  constexpr int kUnits = kPlanned ? 2 : UNITS;
-  int ns_live = p.nsplit;
-  if constexpr (kPlanned) {
-    int n0 = p.lens[b];
-    n0 = n0 < 0 ? 0 : (n0 > p.max_tokens ? p.max_tokens : n0);
-    ns_live = column_chunks(cs, n0).ns;
-    if (jbase * kPage >= n0) {                                     // whole workgroup past the sequence
-      if (tid < 32 && jbase + tid < p.max_blocks) out_row[jbase + tid] = 0.f;
-      return;
-    }
-  }
-  const int lg = !kPlanned ? 3 : (ns_live <= 4 ? 0 : (ns_live <= 8 ? 1 : (ns_live <= 16 ? 2 : 3)));   // log2 of the parts
-  // (Only the collected rows' pairs: two-row collection of 48 rows and 32K tokens, verification 38.0 -> 34.0 us.)
-  const int Rc = p.Rc;                        // collected rows per KV head: the only ones whose page values were written
-  const int parts = 1 << lg, units = (p.Hkv * Rc) << lg;
-  float2 v[kUnits][4];
-  auto load_units = [&](int s0, int u0) {
-#pragma unroll
-    for (int a = 0; a < kUnits; ++a) {
-      const int u = u0 + 256 * a;
-      const int i = u < units ? (u >> lg) : 0, sg = u & (parts - 1);
-      const int h = i / Rc, r = collected_row(i % Rc, p.collect_rows, p.G, p.g);
-      const float2* ml = p.part_ml + (cs.off + static_cast<int64_t>(h) * cs.stride_h) * p.R + r;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int sidx = s0 + sg + (q << lg);
-        v[a][q] = sidx < ns_live ? ml[static_cast<int64_t>(min(sidx, cs.last)) * p.R] : make_float2(-INFINITY, 0.f);
-      }
-    }
-  };
-  // The first batch, and (with few rows) this thread's page log-sum-exps, are
-  // requested before the sequence length is needed.
-  const bool pre_ok = MAXS != kFinPlanned && (Rc & 3) == 0 && Rc <= 4 * kFinPre && p.Hkv <= 8;
-  f32x4 pre[kFinPre];
-  const int jpre = min(jbase + pg, p.lse_pages - 1);
-  if (pre_ok && slot < p.Hkv) {
-    const float* pl = p.page_lse + ((static_cast<int64_t>(b) * p.Hkv + slot) * p.lse_pages + jpre) * Rc;
-#pragma unroll
-    for (int q = 0; q < kFinPre; ++q)
-      if (4 * q < Rc) pre[q] = *reinterpret_cast<const f32x4*>(pl + 4 * q);
-  }
-  // Balanced chunking: the page values of a head are one run of 32 pages x Rc floats.  The workgroup reads the runs as they lie,
-  // in 16-byte pieces (quads of rows), and requests what a batch of kQuads per thread holds now; a quad's sum goes through LDS
-  // to the thread that adds up its page.  (A thread that reads the rows of its page itself, 128 or 160 bytes apart from its
-  // neighbour's, touches every line of the run with every request; figures:
-  // merge_planned_rows.  One sequence is better off with that all the same, its 64 score workgroups wait for latency and not for
-  // requests: us per iteration, page by page / by quads, 4096 tokens 44.0 / 44.6, 32768 69.7 / 70.6, 131072 157.8 / 158.5.)
-  constexpr int kQuads = 10;
-  const bool by_quads = MAXS == kFinPlanned && (Rc & 3) == 0;
-  const int q4 = Rc >> 2, run = 32 * q4, quads = p.Hkv * run;     // quads of a page, a head's run, the workgroup
-  const int run_live = min(32, p.lse_pages - jbase) * q4;         // quads of a run that exist
-  const float rcp_run = __builtin_amdgcn_rcpf(static_cast<float>(run)), rcp_q4 = __builtin_amdgcn_rcpf(static_cast<float>(q4));
-  const float* const lse_base = p.page_lse + (static_cast<int64_t>(b) * p.Hkv * p.lse_pages + jbase) * Rc;
-  f32x4 quad[MAXS == kFinPlanned ? kQuads : 1];
-  auto head_of = [&](int i) { return static_cast<int>((static_cast<float>(i) + 0.5f) * rcp_run); };   // i < 2^20: exact
-  auto load_quads = [&](int first) {         // (first: of the workgroup's batch)
-#pragma unroll
-    for (int a = 0; a < kQuads; ++a) {
-      if (first + 256 * a >= quads) continue;
-      const int i = min(first + 256 * a + tid, quads - 1);
-      const int hd = head_of(i);
-      quad[a] = *reinterpret_cast<const f32x4*>(lse_base + static_cast<int64_t>(hd) * p.lse_pages * Rc + 4 * min(i - hd * run, run_live - 1));
-    }
-  };
-  load_units(0, tid);
-  if constexpr (MAXS == kFinPlanned) {
-    if (by_quads) load_quads(0);
-  }
-
-  int n = p.lens[b];
-  n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
-  const int ns = column_chunks(cs, n).ns;
-  const int nblk = (n + kPage - 1) / kPage;
-  if (jbase >= nblk) {                                             // whole workgroup past the sequence
-    if (tid < 32 && jbase + tid < p.max_blocks) out_row[jbase + tid] = 0.f;
-    return;
-  }
-  bool loaded = true;
-  for (int s0 = 0; s0 < ns; s0 += 4 << lg) {
-    for (int u0 = tid; u0 < units; u0 += kUnits * 256) {
-      if (!loaded) load_units(s0, u0);
-      loaded = false;
-#pragma unroll
-      for (int a = 0; a < kUnits; ++a) {
-        const int u = u0 + 256 * a;
-        if (u < units) {
-          const int sg = u & (parts - 1);
-          float2 cur = (s0 == 0) ? make_float2(-INFINITY, 0.f) : sm_pair[u];
-          float m = cur.x;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            if (s0 + sg + (q << lg) >= ns) v[a][q] = make_float2(-INFINITY, 0.f);
-            m = fmaxf(m, v[a][q].x);
-          }
-          const float mu = (m == -INFINITY) ? 0.f : m;
-          float L = cur.y * fast_exp2(cur.x - mu);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) L += v[a][q].y * fast_exp2(v[a][q].x - mu);
-          sm_pair[u] = make_float2(m, L);
-        }
-      }
-    }
-  }
-  __syncthreads();
-  for (int i = tid; i < p.Hkv * Rc; i += 256) {           // sm_row: [Hkv][Rc], the collected rows only
-    float m = -INFINITY;
-#pragma unroll
-    for (int q = 0; q < parts; ++q) m = fmaxf(m, sm_pair[(i << lg) + q].x);
-    const float m_use = (m == -INFINITY) ? 0.f : m;
-    float L = 0.f;
-#pragma unroll
-    for (int q = 0; q < parts; ++q) {
-      const float2 pr = sm_pair[(i << lg) + q];
-      L += fast_exp2(pr.x - m_use) * pr.y;
-    }
-    sm_row[i] = (L > 0.f) ? m_use + fast_log2(L) : -INFINITY;
-  }
-  __syncthreads();
-  if constexpr (MAXS == kFinPlanned) {
-    if (by_quads) {
-      float* const sm_quad = smf + HR + 256;                       // [Hkv * 32][pitch], where the pairs were
-      const int pitch = q4 | 1;
-      for (int first = 0; first < quads; first += kQuads * 256) {
-        if (first > 0) load_quads(first);
-#pragma unroll
-        for (int a = 0; a < kQuads; ++a) {
-          const int i = first + 256 * a + tid;
-          if (i < quads) {
-            const int hd = head_of(i), of_run = i - hd * run;
-            const int page = static_cast<int>((static_cast<float>(of_run) + 0.5f) * rcp_q4), q = of_run - page * q4;
-            const f32x4 rl = *reinterpret_cast<const f32x4*>(sm_row + hd * Rc + 4 * q);
-            float sum = 0.f;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (rl[e] != -INFINITY) sum += fast_exp2(quad[a][e] - rl[e]);
-            sm_quad[(hd * 32 + page) * pitch + q] = sum;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  }
-  {
-    const int j = jbase + pg;
-    float sc = 0.f;
-    if (j < nblk) {
-      if (by_quads) {
-        for (int h = slot; h < p.Hkv; h += 8) {
-          const float* const sums = smf + HR + 256 + (h * 32 + pg) * (q4 | 1);
-          for (int q = 0; q < q4; ++q) sc += sums[q];
-        }
-      } else if (pre_ok) {
-        if (slot < p.Hkv) {
-          const float* rl = sm_row + slot * Rc;
-#pragma unroll
-          for (int q = 0; q < kFinPre; ++q) {
-            if (4 * q < Rc) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (rl[4 * q + e] != -INFINITY) sc += fast_exp2(pre[q][e] - rl[4 * q + e]);
-            }
-          }
-        }
-      } else {
-        for (int h = slot; h < p.Hkv; h += 8) {
-          const float* pl = p.page_lse + ((static_cast<int64_t>(b) * p.Hkv + h) * p.lse_pages + j) * Rc;
-          const float* rl = sm_row + h * Rc;
-          if ((Rc & 3) == 0) {
-            for (int r = 0; r < Rc; r += 4) {
-              const f32x4 x = *reinterpret_cast<const f32x4*>(pl + r);
-#pragma unroll
-              for (int q = 0; q < 4; ++q)
-                if (rl[r + q] != -INFINITY) sc += fast_exp2(x[q] - rl[r + q]);
-            }
-          } else {
-            // (Eight requests at a time: one by one a page's rows are as many round trips, 77 rows 48 us for the kernel.)
-            for (int r = 0; r < Rc; r += 8) {
-              float x[8];
-#pragma unroll
-              for (int e = 0; e < 8; ++e) x[e] = pl[min(r + e, Rc - 1)];
-#pragma unroll
-              for (int e = 0; e < 8; ++e)
-                if (r + e < Rc && rl[r + e] != -INFINITY) sc += fast_exp2(x[e] - rl[r + e]);
-            }
-          }
-        }
-      }
-    }
-    sm_sum[slot * 32 + pg] = sc;
-    __syncthreads();
-    if (slot == 0 && j < p.max_blocks) {
-      float tot = 0.f;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) tot += sm_sum[q * 32 + pg];
-      out_row[j] = (j < nblk) ? tot * p.inv_norm : 0.f;
-    }
+    score_pages<MAXS, UNITS / 2, false>(p, smf, b);
+  } else if constexpr (kPlanned) {
+    score_pages_planned<MAXS == kFinPlannedSmall>(p, cs, smf, b, plan_n);
+  } else {
+    score_pages<32, UNITS / 2, true>(p, smf, b);
   }
 }
 

@@ -347,23 +347,24 @@ struct ColumnSlots {
   int32_t stride_h, chunk, last;
   int32_t count;               // chunks the column has, where they are not equal (0: they follow from `chunk`)
 };
+__host__ __device__ __forceinline__ ColumnSlots planned_slots(int2 e, int slots_total) {      // e: the plan's entry
+  ColumnSlots c;
+  c.off = e.x;
+  c.stride_h = slots_total;
+  c.chunk = e.y > 0 ? e.y : 1;
+  c.last = slots_total - 1 - e.x;
+  c.count = e.y < 0 ? -e.y : 0;
+  return c;
+}
 __host__ __device__ __forceinline__ ColumnSlots column_slots(const int2* plan, int slots_total, int b, int Hkv, int nsplit,
                                                     int chunk_tokens) {
+  if (plan) return planned_slots(plan[b], slots_total);
   ColumnSlots c;
-  if (plan) {
-    const int2 e = plan[b];
-    c.off = e.x;
-    c.stride_h = slots_total;
-    c.chunk = e.y > 0 ? e.y : 1;
-    c.last = slots_total - 1 - e.x;
-    c.count = e.y < 0 ? -e.y : 0;
-  } else {
-    c.off = static_cast<int64_t>(b) * Hkv * nsplit;
-    c.stride_h = nsplit;
-    c.chunk = chunk_tokens;
-    c.last = nsplit - 1;
-    c.count = 0;
-  }
+  c.off = static_cast<int64_t>(b) * Hkv * nsplit;
+  c.stride_h = nsplit;
+  c.chunk = chunk_tokens;
+  c.last = nsplit - 1;
+  c.count = 0;
   return c;
 }
 // Chunks of n tokens in such a column, and the largest slot that a merge which knows n requests: its last chunk's; none
