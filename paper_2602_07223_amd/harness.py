@@ -120,12 +120,14 @@ class VegasPath:
                    softmax_scale=L.softmax_scale, head_dim=s.head_dim, **kw)
 
     def stream(self) -> int:
-        return int(torch.cuda.current_stream(self.device).cuda_stream)
+        # (the raw handle, without a Stream object around it: 0.2 us instead of 2)
+        index = self.device.index
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device() if index is None else index)
 
     # The calls below pass raw device addresses (cached per DeviceLayer) so that the host cost of one
     # call stays at a few microseconds: at batch 1 the kernels are that short.
     def _addrs(self, dl: DeviceLayer):
-        a = getattr(dl, "_addrs", None)
+        a = dl.__dict__.get("_addrs")
         if a is None:
             # checked once per layer, since the calls below hand over addresses: both descriptors' cache extents
             for desc in (self.desc_verify, self.desc_draft):
@@ -146,7 +148,7 @@ class VegasPath:
         return a
 
     def _own(self):
-        o = getattr(self, "_own_addrs", None)
+        o = self.__dict__.get("_own_addrs")
         if o is None:
             step_bytes = self.out_draft[0].numel() * self.out_draft.element_size()
             o = dict(ws=self.workspace.data_ptr(), wsn=self.workspace.numel(), ov=self.out_verify.data_ptr(),
@@ -157,9 +159,8 @@ class VegasPath:
 
     def verify(self, dl: DeviceLayer, stream=None, stages: int = 0) -> None:
         a, o = self._addrs(dl), self._own()
-        vb.vegas_verify_attention(self.desc_verify, a["qv"], a["k"], a["v"], a["bt"], a["sl"], o["ov"], o["bs"],
-                                  o["ws"], stream=self.stream() if stream is None else stream,
-                                  workspace_bytes=o["wsn"], stages=stages)
+        vb.vegas_verify_attention(self.desc_verify, a["qv"], a["k"], a["v"], a["bt"], a["sl"], o["ov"], o["bs"], o["ws"],
+                                  self.stream() if stream is None else stream, o["wsn"], stages)
 
     def select(self, dl: DeviceLayer, block_scores: Optional[torch.Tensor] = None, budgets=None, stream=None) -> None:
         a, o = self._addrs(dl), self._own()
@@ -174,9 +175,8 @@ class VegasPath:
 
     def draft(self, dl: DeviceLayer, step: int, stream=None, stages: int = 0) -> None:
         a, o = self._addrs(dl), self._own()
-        vb.vegas_draft_attention(self.desc_draft, a["qd"][step], a["k"], a["v"], o["st"], o["ssl"], o["od"][step],
-                                 o["ws"], stream=self.stream() if stream is None else stream,
-                                 workspace_bytes=o["wsn"], stages=stages)
+        vb.vegas_draft_attention(self.desc_draft, a["qd"][step], a["k"], a["v"], o["st"], o["ssl"], o["od"][step], o["ws"],
+                                 self.stream() if stream is None else stream, o["wsn"], stages)
 
     def live_iteration(self, dl: DeviceLayer, fused: bool = True) -> None:
         """One decoding iteration with a live drafting phase (Sec. 2.3): verify and select at the layer's lengths,
