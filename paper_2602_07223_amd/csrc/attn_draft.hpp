@@ -66,6 +66,7 @@ constexpr int kDraftWaves = 4;
 constexpr int kDraftRows = 16;     // query rows (of one KV head) a workgroup can take
 
 constexpr int kDraftRing = 32 * 1024;          // bytes of a wave's ring
+static_assert(kDraftRing >= kDraftRows * red_pitch(128) * 4, "a wave's rows fit its ring");
 // Dynamic LDS of attn_draft16_kernel with rings; the merge's rows alias them.
 constexpr size_t draft_ring_lds_bytes() { return kDraftWaves * kDraftRing + 2 * kDraftWaves * kDraftRows * sizeof(float); }
 // Dynamic LDS of attn_draft16_kernel for R (<= 16) rows: the waves' rows for the merge, their row maxima and sums.
@@ -541,44 +542,61 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
       }
     }
 
-    // ---- merge the waves: row maxima meet in LDS, every wave rescales and parks its rows as [wave][row][d], all
-    //      threads add the waves' copies and write the workgroup's partial (or the finished rows)
+    // ---- merge the waves: every wave parks its rows as [wave][row][d], with their maxima and sums, and after the one barrier all threads
+    //      scale and add the waves' copies and write the workgroup's partial (or the finished rows).  (Scaled by the common maximum before
+    //      they are parked they need a barrier more.  us for the launch, captured, before / so: 8 columns of 2048 tokens 4.01 / 3.89, of 4096
+    //      4.41 / 4.24, 256 tokens through rings 4.35 / 4.27.)
+    // RING: a wave's copy lies in its own ring, which it is done with; another wave may still be streaming through its own.
     VEGAS_TL(kTlStreamed);
-    if (kg == 0) sm_m[wave * kDraftRows + l16] = m_run;
-    __syncthreads();
-    VEGAS_TL(kTlMerged);
+    const int copy_floats = RING ? kDraftRing / 4 : Rl * kRedPitch;
     {
-      float mw = -INFINITY;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) mw = fmaxf(mw, sm_m[w * kDraftRows + l16]);
-      const float m_fin = (mw == -INFINITY) ? 0.f : mw;
-      const float sc = fast_exp2(m_run - m_fin);
-      const float lsum = quad_rows_sum(l_run * sc);
-      if (kg == 0) sm_l[wave * kDraftRows + l16] = lsum;
+      const float lsum = quad_rows_sum(l_run);
+      if (kg == 0) {
+        sm_m[wave * kDraftRows + l16] = m_run;
+        sm_l[wave * kDraftRows + l16] = lsum;
+      }
       if (l16 < Rl) {
-        float* dst = red + (wave * Rl + l16) * kRedPitch;
+        float* dst = red + wave * copy_floats + l16 * kRedPitch;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int d0 = NBLK * (4 * kg + r);
-          *reinterpret_cast<f32x4*>(dst + d0) = f32x4{acc[0][r] * sc, acc[1][r] * sc, acc[2][r] * sc, acc[3][r] * sc};
-          if constexpr (D == 128)
-            *reinterpret_cast<f32x4*>(dst + d0 + 4) = f32x4{acc[4][r] * sc, acc[5][r] * sc, acc[6][r] * sc, acc[7][r] * sc};
+          *reinterpret_cast<f32x4*>(dst + d0) = f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
+          if constexpr (D == 128) *reinterpret_cast<f32x4*>(dst + d0 + 4) = f32x4{acc[4][r], acc[5][r], acc[6][r], acc[7][r]};
         }
       }
     }
     __syncthreads();
+    VEGAS_TL(kTlMerged);
     constexpr int V4 = D / 4;
     constexpr int kSumTrips = (kDraftRows * V4 + NW * 64 - 1) / (NW * 64);
     f32x4 sums[kSumTrips];
     const int sum_trips = (Rl * V4 + NW * 64 - 1) / (NW * 64);       // (few rows: the later trips have nothing to do)
+    // Scales of the waves' copies of a row to their common maximum.
+    auto wave_scales = [&](int row, float (&sc)[NW]) {
+      float mw[NW];
+#pragma unroll
+      for (int w = 0; w < NW; ++w) mw[w] = sm_m[w * kDraftRows + row];
+      float top = mw[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) top = fmaxf(top, mw[w]);
+      const float m_fin = (top == -INFINITY) ? 0.f : top;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) sc[w] = fast_exp2(mw[w] - m_fin);
+      return top;
+    };
 #pragma unroll
     for (int it = 0; it < kSumTrips; ++it) {
       if (it < sum_trips) {
         const int e = min(tid + it * NW * 64, Rl * V4 - 1);
         const float* src = red + (e / V4) * kRedPitch + 4 * (e % V4);
-        f32x4 acc4 = *reinterpret_cast<const f32x4*>(src);
+        f32x4 part[NW];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) acc4 += *reinterpret_cast<const f32x4*>(src + w * Rl * kRedPitch);
+        for (int w = 0; w < NW; ++w) part[w] = *reinterpret_cast<const f32x4*>(src + w * copy_floats);
+        float sc[NW];
+        wave_scales(e / V4, sc);
+        f32x4 acc4 = part[0] * sc[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) acc4 += part[w] * sc[w];
         sums[it] = acc4;
       }
     }
@@ -590,9 +608,10 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
         const int e = tid + it * NW * 64;
         if (e < Rl * V4) {
           const int row = e / V4;
-          float lw = 0.f;
+          float lw = 0.f, sc[NW];
+          wave_scales(row, sc);
 #pragma unroll
-          for (int w = 0; w < NW; ++w) lw += sm_l[w * kDraftRows + row];
+          for (int w = 0; w < NW; ++w) lw += sm_l[w * kDraftRows + row] * sc[w];
           const float inv = lw > 0.f ? 1.0f / lw : 0.f;       // (a row with no visible key: zeros)
           u32x2 packed;
           packed[0] = static_cast<uint32_t>(float_to_bf16_bits(sums[it][0] * inv)) |
@@ -613,12 +632,10 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
       if (e < Rl * V4) *reinterpret_cast<f32x4*>(po + 4 * e) = sums[it];
     }
     if (tid < Rl) {
-      float mw = -INFINITY, lw = 0.f;
+      float lw = 0.f, sc[NW];
+      const float mw = wave_scales(tid, sc);
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        mw = fmaxf(mw, sm_m[w * kDraftRows + tid]);
-        lw += sm_l[w * kDraftRows + tid];
-      }
+      for (int w = 0; w < NW; ++w) lw += sm_l[w * kDraftRows + tid] * sc[w];
       p.part_ml[pbase * p.R + tid] = make_float2(mw, lw);
     }
     VEGAS_TL(kTlExit);
