@@ -94,7 +94,9 @@ inline size_t draft16_lds_bytes(int R, int D) {
 // RING: K and V land in LDS, in a ring of two tiles per wave, instead of in registers: both are on their way from the start, where the
 // registers hold one and the next is asked for when the first contraction has used its K.  One workgroup to a compute unit, so what
 // bounds it is how much that unit has under way; the rule and its figures: ring_draft.
-template <int D, int PS = 4, bool CHOOSE = false, bool RING = false, typename... Step>
+// DV: head dims of V that the workgroup reads and of the output rows that it writes: D, or a part of it in calls that one workgroup per
+// column could finish (grid (KV head, part, sequence); draft_value_parts).
+template <int D, int PS = 4, bool CHOOSE = false, bool RING = false, int DV = D, typename... Step>
 __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS_SPLIT_HOT_PARAMS, const SplitParams pfull, const Step... step) {
   VEGAS_TL_DECL;
   VEGAS_TL(kTlEntry);
@@ -104,12 +106,14 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr bool APPEND = sizeof...(Step) == 1;
   static_assert(!APPEND || (PS == 4 && !CHOOSE && !RING), "draft steps: 16-token pages through the cache");
+  static_assert(DV == D || (!APPEND && !CHOOSE && (DV == 32 || (DV == 64 && D == 128))), "parts of V: 32 or 64 head dims, calls without a merge");
   static_assert(!RING || (PS == 4 && !CHOOSE && D == 128), "rings: 16-token pages through the cache, head dimension 128");
   constexpr int NW = kDraftWaves;
   constexpr int KK = D / 32;                 // steps of the first contraction = K loads per page
-  constexpr int NBLK = D / 16;               // 16-wide blocks of the output = head dims one V load covers
-  constexpr int kRedPitch = red_pitch(D);
-  using VReg = typename std::conditional<D == 128, u32x4, u32x2>::type;      // NBLK head dims of one token
+  constexpr int NBLK = DV / 16;              // 16-wide blocks of the output = head dims one V load covers
+  constexpr int kRedPitch = red_pitch(DV);
+  typedef unsigned int u32x1 __attribute__((ext_vector_type(1)));
+  using VReg = typename std::conditional<NBLK == 8, u32x4, typename std::conditional<NBLK == 4, u32x2, u32x1>::type>::type;   // NBLK head dims of one token
   constexpr int TP = 32 >> (PS < 4 ? PS : 0);   // pages per tile on the small-page path
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -119,7 +123,8 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   const int l16 = lane & 15;                 // token of a page (K), query row (Q, S^T, O^T), head-dim group (V)
   const int kg = lane >> 4;                  // which 8 of a contraction step's 32 indices
   const int h = blockIdx.x;                  // grid (KV head, chunk, sequence)
-  const int split = blockIdx.y;
+  const int split = DV == D ? blockIdx.y : 0;
+  const int part = DV == D ? 0 : blockIdx.y;  // which DV head dims of V
   const int b = blockIdx.z;
   const int Rl = p.R;                        // rows of this KV head: one draft token, g heads (G = 1)
 
@@ -173,7 +178,7 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   // What the first loads' addresses take besides page ids is worked out while those are on their way.
   const int64_t head_off = static_cast<int64_t>(h) * p.head_stride;
   const unsigned char* k_head = reinterpret_cast<const unsigned char*>(p.k + head_off);
-  const unsigned char* v_head = reinterpret_cast<const unsigned char*>(p.v + head_off);
+  const unsigned char* v_head = reinterpret_cast<const unsigned char*>(p.v + head_off + part * DV);
   uint64_t page_bytes = static_cast<uint64_t>(p.page_stride) * 2u;
   const uint32_t ts_bytes = static_cast<uint32_t>(p.token_stride) * 2u;
   uint32_t k_cached_off = static_cast<uint32_t>(l16) * ts_bytes + static_cast<uint32_t>(kg) * 16u;
@@ -231,7 +236,11 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
     append_row();
     if (p.out_direct != nullptr) {           // no merge kernel follows: the rows of an empty sequence are zeros
       uint16_t* rows = out_rows();
-      for (int e = tid; e < Rl * D; e += NW * 64) rows[e] = 0;
+      if constexpr (DV == D) {
+        for (int e = tid; e < Rl * D; e += NW * 64) rows[e] = 0;
+      } else {
+        for (int e = tid; e < Rl * DV; e += NW * 64) rows[e / DV * D + part * DV + e % DV] = 0;
+      }
     }
     // (The stores are waited for here.  The compiler lets this way out run into the stream below and counts stores and loads in one
     //  counter without an order between the two kinds: as long as a store may be under way it waits for everything where it wants the
@@ -293,7 +302,7 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
     auto issue_v = [&](int k, VReg (&vr)[8]) {
       if constexpr (PS != 4) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) vr[e] = gload_at<VReg, STREAM>(token_addr(p.v, 16 * (e >> 2) + 4 * kg + (e & 3)) + l16 * (2 * NBLK));
+        for (int e = 0; e < 8; ++e) vr[e] = gload_at<VReg, STREAM>(token_addr(p.v, 16 * (e >> 2) + 4 * kg + (e & 3)) + (part * 2 * DV + l16 * (2 * NBLK)));
         return;
       }
       const unsigned char* vb0 = page_base(v_head, __builtin_amdgcn_readlane(pagevec, k & 31));
@@ -337,10 +346,12 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
     constexpr int TPI = 64 / (D / 8);          // token rows of one load instruction
     constexpr int NP = kPage / TPI;            // load instructions per page (of K, of V)
     constexpr int NL = 2 * NP;                 // ... per tile
-    constexpr int kRow = 2 * D, kHalfSlot = kTile * kRow;
-    constexpr int NS = kDraftRing / (2 * kHalfSlot);
+    constexpr int VPI = 64 / (DV / 8), NPV = kPage / VPI, NLV = 2 * NPV;       // the same of V
+    constexpr int kRow = 2 * D, kVRow = 2 * DV, kHalfSlot = kTile * kRow, kSlot = kTile * (kRow + kVRow);
+    constexpr int NS = 2;                      // tiles the ring holds
+    static_assert(!RING || NS * kSlot <= kDraftRing, "the ring's tiles");
     unsigned char* const ring = smem + wave * kDraftRing;
-    uint32_t ring_lds = 0, koff[NP] = {}, voff[NP] = {};
+    uint32_t ring_lds = 0, koff[NP] = {}, voff[NPV] = {};
     if constexpr (RING) {
       typedef const __attribute__((address_space(3))) unsigned char* lptr;
       ring_lds = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lptr)ring)));
@@ -348,29 +359,34 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
       for (int i = 0; i < NP; ++i) {
         const int row = TPI * i + lane / (D / 8), piece = lane % (D / 8);     // where the 16 bytes land
         koff[i] = static_cast<uint32_t>(row) * ts_bytes + static_cast<uint32_t>(piece ^ row) * 16u;
-        voff[i] = static_cast<uint32_t>(row) * ts_bytes + static_cast<uint32_t>(piece) * 16u;
       }
+#pragma unroll
+      for (int i = 0; i < NPV; ++i)
+        voff[i] = static_cast<uint32_t>(VPI * i + lane / (DV / 8)) * ts_bytes + static_cast<uint32_t>(lane % (DV / 8)) * 16u;
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+v"(qreg[kk]));      // (waited for before loads that the compiler does not count)
     }
     auto ring_k = [&](int k) {
       if ((k & 31) == 0 && k > 0) load_pagevec(k);
-      const uint32_t at = ring_lds + static_cast<uint32_t>((k & (NS - 1)) * 2 * kHalfSlot);
+      const uint32_t at = ring_lds + static_cast<uint32_t>((k & (NS - 1)) * kSlot);
       load_to_lds<NP, false>(at, page_base(k_head, __builtin_amdgcn_readlane(pagevec, k & 31)), koff);
       load_to_lds<NP, false>(at + kHalfSlot / 2, page_base(k_head, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31))), koff);
     };
     auto ring_v = [&](int k) {
-      const uint32_t at = ring_lds + static_cast<uint32_t>((k & (NS - 1)) * 2 * kHalfSlot + kHalfSlot);
-      load_to_lds<NP, false>(at, page_base(v_head, __builtin_amdgcn_readlane(pagevec, k & 31)), voff);
-      load_to_lds<NP, false>(at + kHalfSlot / 2, page_base(v_head, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31))), voff);
+      const uint32_t at = ring_lds + static_cast<uint32_t>((k & (NS - 1)) * kSlot + kHalfSlot);
+      load_to_lds<NPV, false>(at, page_base(v_head, __builtin_amdgcn_readlane(pagevec, k & 31)), voff);
+      load_to_lds<NPV, false>(at + kPage * kVRow, page_base(v_head, __builtin_amdgcn_readlane(pagevec, 32 + (k & 31))), voff);
     };
     const uint32_t k_first = static_cast<uint32_t>(l16 * kRow + ((kg ^ l16) * 16));
-    static_assert(!RING || NS == 2, "ring_wait counts the requests of two tiles");
-    // Of the ring's last tiles, for K (V is younger) or V: what is under way when it has to be there.
-    auto ring_wait = [&](bool last, auto is_k) {
-      constexpr int OWN = decltype(is_k)::value ? 1 : 0;
-      if (last) wait_vm<OWN * NL>();
-      else wait_vm<(2 + OWN) * NL>();
+    // For tile k's K or V: what has been requested after it.  With a tile to follow behind the ring's, the other tile's K and V and
+    // either its own V or the K that has just been asked for; in the ring's last tiles what is left of that.
+    auto wait_k = [&](bool last) {
+      if (last) wait_vm<NLV>();
+      else wait_vm<NLV + NL + NLV>();
+    };
+    auto wait_v = [&](bool last) {
+      if (last) wait_vm<0>();
+      else wait_vm<NL + NLV>();
     };
     const int ntiles = tile_first < tile_end ? (tile_end - tile_first + NW - 1) / NW : 0;      // this wave's tiles
     u32x4 kr[2][KK];
@@ -410,11 +426,10 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
       constexpr bool has_next = decltype(has_next_tag)::value;
       const int tok0 = (tile_first + k * NW) * kTile;
       if constexpr (STREAM) exchange_k(kr);
-      const unsigned char* const kt = ring + (k & (NS - 1)) * (2 * kHalfSlot);
+      const unsigned char* const kt = ring + (k & (NS - 1)) * kSlot;
       const unsigned char* const vt = kt + kHalfSlot;
       if constexpr (RING) {
-        if constexpr (has_next) wait_vm<(2 * NS - 1) * NL>();
-        else ring_wait(k + 1 == ntiles, std::true_type{});
+        wait_k(!has_next && k + 1 == ntiles);
 #pragma unroll
         for (int pg = 0; pg < 2; ++pg)
 #pragma unroll
@@ -489,11 +504,11 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
         for (int blk = 0; blk < NBLK; ++blk) acc[blk] *= alpha;
       }
       if constexpr (RING) {
-        if constexpr (has_next) wait_vm<(2 * NS - 1) * NL>();
-        else ring_wait(k + 1 == ntiles, std::false_type{});
+        if constexpr (has_next) wait_vm<NL + NLV + NL>();
+        else wait_v(k + 1 == ntiles);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-          vcur[e] = *reinterpret_cast<const VReg*>(vt + (16 * (e >> 2) + 4 * kg + (e & 3)) * kRow + l16 * (2 * NBLK));
+          vcur[e] = *reinterpret_cast<const VReg*>(vt + (16 * (e >> 2) + 4 * kg + (e & 3)) * kVRow + l16 * (2 * NBLK));
         }
       }
       if (tail) {                              // slots past the end may hold anything: feed zeros
@@ -560,14 +575,15 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int d0 = NBLK * (4 * kg + r);
-          *reinterpret_cast<f32x4*>(dst + d0) = f32x4{acc[0][r], acc[1][r], acc[2][r], acc[3][r]};
-          if constexpr (D == 128) *reinterpret_cast<f32x4*>(dst + d0 + 4) = f32x4{acc[4][r], acc[5][r], acc[6][r], acc[7][r]};
+          if constexpr (NBLK == 2) *reinterpret_cast<f32x2*>(dst + d0) = f32x2{acc[0][r], acc[1][r]};
+          else *reinterpret_cast<f32x4*>(dst + d0) = f32x4{acc[0][r], acc[1][r], acc[2 % NBLK][r], acc[3 % NBLK][r]};
+          if constexpr (NBLK == 8) *reinterpret_cast<f32x4*>(dst + d0 + 4) = f32x4{acc[4 % NBLK][r], acc[5 % NBLK][r], acc[6 % NBLK][r], acc[7 % NBLK][r]};
         }
       }
     }
     __syncthreads();
     VEGAS_TL(kTlMerged);
-    constexpr int V4 = D / 4;
+    constexpr int V4 = DV / 4;
     constexpr int kSumTrips = (kDraftRows * V4 + NW * 64 - 1) / (NW * 64);
     f32x4 sums[kSumTrips];
     const int sum_trips = (Rl * V4 + NW * 64 - 1) / (NW * 64);       // (few rows: the later trips have nothing to do)
@@ -618,7 +634,7 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
                       (static_cast<uint32_t>(float_to_bf16_bits(sums[it][1] * inv)) << 16);
           packed[1] = static_cast<uint32_t>(float_to_bf16_bits(sums[it][2] * inv)) |
                       (static_cast<uint32_t>(float_to_bf16_bits(sums[it][3] * inv)) << 16);
-          *reinterpret_cast<u32x2*>(rows + 4 * e) = packed;
+          *reinterpret_cast<u32x2*>(rows + (DV == D ? 4 * e : row * D + part * DV + 4 * (e % V4))) = packed;
         }
       }
       VEGAS_TL(kTlExit);

@@ -25,7 +25,15 @@ namespace vegas {
 //      320    3200 +0.4/-10/+5.4, 4128 +7.2/+21/+14                 3200 -2.6/-3.2/+0.9, 4128 +11/-1.6/+5.4
 // The lines lie where a call gains with equal and with spread lengths (0.8 us lost at most) and a lone long selection takes no
 // more than half as long again (192 columns, 3200 tokens, head dimension 128: 24 -> 32 us, in an iteration of 319).
-inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
+// rings: head dimension 128 and 16-token pages, where K and V go through rings and V is read in parts (ring_draft, draft_value_parts).  us a
+// call, chunks / one workgroup per part, equal / spread / one: 64 columns, 608 tokens 7.7 / 5.8, 7.5 / 5.6, 6.5 / 5.6; 72, 608 7.9 / 6.2, 7.8 / 5.9,
+// 6.6 / 5.8; 96, 928 11.7 / 9.5, 10.8 / 7.9, 9.9 / 7.7; 1056 12.7 / 10.8, 10.7 / 8.5, 9.9 / 8.3.  Both go on to win there (64 columns, 928 8.1 / 7.8;
+// 96, 1312 16.3 / 12.8), and with fewer up to 600 to 800 tokens, but not by the launch that a live draft step then takes for its append.
+inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim, bool rings = false) {
+  if (rings) {
+    if (32 * columns >= 8 * static_cast<int64_t>(num_cu) && 32 * columns < 12 * static_cast<int64_t>(num_cu)) return 640;
+    if (32 * columns >= 12 * static_cast<int64_t>(num_cu) && 32 * columns < 16 * static_cast<int64_t>(num_cu)) return 1056;
+  }
   struct Line { int per32, tokens128, tokens64; };        // from that many 32nds of the compute units on
   constexpr Line lines[] = {{24, 3200, 3200}, {18, 2176, 3200}, {17, 1312, 3200}, {16, 1312, 2176},
                             {12, 800, 928}, {9, 544, 928}, {0, 448, 672}};
@@ -60,6 +68,17 @@ inline int draft_chunk_tokens(int64_t columns, int num_cu, int tokens, int unit,
 // 14.3; 160 2000 30.1 / 28.8; 192 300 7.4 / 6.7, 1040 19.4 / 19.0, 3000 54.5 / 51.6; 256 300 8.3 / 8.4, 1040 23.3 / 23.0, 3000 67.1 /
 // 67.3.  (Head dimension 64: 8 400 5.0 / 5.2; 128 2000 14.4 / 15.2; 192 1040 11.2 / 12.7.  Calls cut into chunks: within 1 %.)
 inline bool ring_draft(int64_t columns, int num_cu, int tokens) { return columns < num_cu && tokens > 128; }
+
+// Parts of V, of 32 or 64 head dims, that a draft call of one workgroup per column is split into while there are compute units for them: a
+// workgroup reads all of the column's K, its part of V, and writes its part of the output rows.  Such a call is bound by how fast one
+// compute unit can read (about 50 GB/s), and no part has anything to merge.  us a call, captured, one / two / four workgroups, head dimension
+// 128, 16-token pages: 8 columns, 128 tokens 3.96 / 3.70 / 3.46, 256 4.31 / 3.80 / 3.59, 448 5.71 / 5.03 / 4.71; 64 columns, 256 4.47 / 3.97 / 3.89,
+// 448 5.91 / 5.24 / 5.08; 128 columns, 256 4.75 / 4.29 (four do not fit the chip: 6.51), 1300 15.8 / 15.3; one-token pages, 8 columns, 256 4.99 / - /
+// 4.34, 448 6.74 / - / 5.85; head dimension 64, two parts, 8 columns, 256 3.93 / 3.46, 640 5.83 / 4.87, 128 columns, 1300 10.5 / 9.5.
+inline int draft_value_parts(int64_t columns, int num_cu, int head_dim) {
+  if (head_dim == 128 && 4 * columns <= num_cu) return 4;
+  return 2 * columns <= num_cu ? 2 : 1;
+}
 
 // Verification with a local mask: does one workgroup per column (sequence x KV head x row block) stream the whole band
 // (no row sees more than window + queries tokens, nor than the longest sequence has) and write the output rows, or is the context cut into chunks

@@ -174,7 +174,7 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   // head dimension 64, window 128: 11.7 us with a merge, 8.1 without).
   const bool banded = !may_finish && d->window > 0 && d->kv_chunk_tokens == 0 &&
                       lone_workgroup_band(d->window, d->num_queries, max_len, chunk);
-  const bool finish = banded || (own_chunks && rows_per_head <= kDraftRows && max_len <= lone_workgroup_tokens(heads, num_cu, d->head_dim));
+  const bool finish = banded || (own_chunks && rows_per_head <= kDraftRows && max_len <= lone_workgroup_tokens(heads, num_cu, d->head_dim, d->head_dim == 128 && d->page_size == kPage));
   if (fine && own_chunks && !finish && rows_per_head <= kDraftRows && chunk == unit)
     chunk = draft_chunk_tokens(heads, num_cu, max_len, unit, rows_per_head * d->head_dim);
   // (A call that one workgroup per column finishes uses no partials; its workspace is sized for the chunked plan all
@@ -337,22 +337,37 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
       const dim3 dblock(kDraftWaves * 64);
       const size_t dlds = draft16_lds_bytes(pl.R, D);
       const bool choose = draft_chooses(batch, sp.max_tokens, sp.Hkv, D);
-      if (step != nullptr) return launch_one(attn_draft16_kernel<D, 4, false, false, DraftStep>, grid, dblock, dlds, st, sp, *step);
+      if (step != nullptr) return launch_one(attn_draft16_kernel<D, 4, false, false, D, DraftStep>, grid, dblock, dlds, st, sp, *step);
+      const int64_t columns = static_cast<int64_t>(batch) * sp.Hkv;
+      const bool lone = sp.out_direct != nullptr && !choose;       // one workgroup per column, or one per part of its V
+      const int parts = lone ? draft_value_parts(columns, device_cu_count(), D) : 1;
+      auto launch = [&](auto ps, auto ring, auto value_dims) {
+        constexpr int PS = decltype(ps)::value, DV = decltype(value_dims)::value;
+        constexpr bool RING = decltype(ring)::value;
+        const dim3 pgrid = DV == D ? grid : dim3(sp.Hkv, D / DV, batch);
+        return launch_one(attn_draft16_kernel<D, PS, false, RING, DV>, pgrid, dblock, RING ? draft_ring_lds_bytes() : dlds, st, sp);
+      };
+      auto by_parts = [&](auto ps, auto ring) {
+        if (parts == D / 32) return launch(ps, ring, std::integral_constant<int, 32>{});
+        if constexpr (D == 128) {
+          if (parts == 2) return launch(ps, ring, std::integral_constant<int, 64>{});
+        }
+        return launch(ps, ring, std::integral_constant<int, D>{});
+      };
       if constexpr (D == 128) {
-        if (page_size == kPage && !choose && pl.nsplit == 1 && ring_draft(static_cast<int64_t>(batch) * sp.Hkv, device_cu_count(), pl.chunk))
-          return launch_one(attn_draft16_kernel<D, 4, false, true>, grid, dblock, draft_ring_lds_bytes(), st, sp);
+        if (page_size == kPage && lone && ring_draft(columns, device_cu_count(), pl.chunk))
+          return by_parts(std::integral_constant<int, 4>{}, std::true_type{});
       }
-      auto launch = [&](auto ps) {
-        constexpr int PS = decltype(ps)::value;
-        if (choose) return launch_one(attn_draft16_kernel<D, PS, true>, grid, dblock, dlds, st, sp);
-        return launch_one(attn_draft16_kernel<D, PS, false>, grid, dblock, dlds, st, sp);
+      auto by_page = [&](auto ps) {
+        if (choose) return launch_one(attn_draft16_kernel<D, decltype(ps)::value, true>, grid, dblock, dlds, st, sp);
+        return by_parts(ps, std::false_type{});
       };
       switch (page_size) {                              // (draft calls may walk a table of smaller pages)
-        case 1: return launch(std::integral_constant<int, 0>{});
-        case 2: return launch(std::integral_constant<int, 1>{});
-        case 4: return launch(std::integral_constant<int, 2>{});
-        case 8: return launch(std::integral_constant<int, 3>{});
-        default: return launch(std::integral_constant<int, 4>{});
+        case 1: return by_page(std::integral_constant<int, 0>{});
+        case 2: return by_page(std::integral_constant<int, 1>{});
+        case 4: return by_page(std::integral_constant<int, 2>{});
+        case 8: return by_page(std::integral_constant<int, 3>{});
+        default: return by_page(std::integral_constant<int, 4>{});
       }
     }
     switch (page_size) {                                // larger groups: the 32-row kernel, any page size
@@ -525,18 +540,21 @@ int for_each_lds_kernel(F f) {
     one(attn_split_kernel<4, 2, true, 1, false, 4, false, D>);
     one(attn_split_kernel<4, 2, true, 2, false, 4, false, D>);
     one(attn_split_kernel<4, 2, true, 2, true, 4, false, D>);
-    one(attn_draft16_kernel<D, 0, false>); one(attn_draft16_kernel<D, 0, true>);
-    one(attn_draft16_kernel<D, 1, false>); one(attn_draft16_kernel<D, 1, true>);
-    one(attn_draft16_kernel<D, 2, false>); one(attn_draft16_kernel<D, 2, true>);
-    one(attn_draft16_kernel<D, 3, false>); one(attn_draft16_kernel<D, 3, true>);
-    one(attn_draft16_kernel<D, 4, false>); one(attn_draft16_kernel<D, 4, true>);
-    one(attn_draft16_kernel<D, 4, false, false, DraftStep>);
+    auto draft16 = [&](auto ps) {
+      constexpr int PS = decltype(ps)::value;
+      one(attn_draft16_kernel<D, PS, false>); one(attn_draft16_kernel<D, PS, true>);
+      one(attn_draft16_kernel<D, PS, false, false, 32>);
+      if constexpr (D == 128) one(attn_draft16_kernel<D, PS, false, false, 64>);
+    };
+    draft16(std::integral_constant<int, 0>{}); draft16(std::integral_constant<int, 1>{}); draft16(std::integral_constant<int, 2>{});
+    draft16(std::integral_constant<int, 3>{}); draft16(std::integral_constant<int, 4>{});
+    one(attn_draft16_kernel<D, 4, false, false, D, DraftStep>);
     one(attn_pair_kernel<0, D, true>); one(attn_pair_kernel<0, D, false>);
     one(attn_pair_kernel<1, D, true>); one(attn_pair_kernel<1, D, false>);
     one(attn_pair_kernel<2, D, true>); one(attn_pair_kernel<2, D, false>);
   };
   one(attn_pair_kernel<1, 64, true, 2 * kPairWaves>); one(attn_pair_kernel<1, 64, false, 2 * kPairWaves>);
-  one(attn_draft16_kernel<128, 4, false, true>);
+  one(attn_draft16_kernel<128, 4, false, true>); one(attn_draft16_kernel<128, 4, false, true, 64>); one(attn_draft16_kernel<128, 4, false, true, 32>);
   per_dim(std::integral_constant<int, 128>{});
   per_dim(std::integral_constant<int, 64>{});
   one(verify_finalize_kernel<16, 0>); one(verify_finalize_kernel<32, 0>);
