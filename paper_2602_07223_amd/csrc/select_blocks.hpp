@@ -15,7 +15,8 @@ namespace vegas {
 
 constexpr int kSelectThreads = 1024;
 constexpr int kSelectKeyCap = 16384;   // keys kept in LDS (64 KB); longer prefixes re-read the scores
-constexpr int kSelectRegRows = 8;      // prefixes of up to 8 x 1024 pages keep their keys in registers instead
+constexpr int kSelectRegRows = 8;      // prefixes of up to 8 pages a thread keep their keys in registers instead
+constexpr int kSelectFewThreads = 512; // threads for prefixes that these can hold in registers (select_blocks_kernel)
 
 // Order-preserving key of a score (larger float <=> larger unsigned); -0 is folded onto +0 and every NaN onto
 // key 0, below -infinity: a NaN score ranks last, NaNs among themselves by index like any other tie.
@@ -94,18 +95,18 @@ __device__ __forceinline__ void walk_to_last_bin(const uint32_t* h, uint32_t nee
 // distributed 9.2 / 7.75 / 8.1, four values 15.7 / 13.1 / 8.9, fifteen in sixteen 0 8.6 / 12.5 / 7.8, a twentieth -infinity beside
 // scores within a percent 12.9 / 14.5 / 10.6, one far outlier there 13.0 / 15.0 / 10.6, ascending 9.9 / 12.8 / 8.3.  32768 tokens:
 // 20.8 / 17.1 / 17.0, 20.5 / 39.0 / 19.9, 20.6 / 90.3 / 19.3, 20.6 / 42.8 / 23.4, 20.6 / 44.2 / 25.3, 20.6 / 39.1 / 19.0.
-// !CROWDS: none of this, for two keys a thread: 2048 pages 5.6 / 5.8 / 5.9, 8.3 / 7.4 / 5.7, 7.9 / 10.7 / 10.7, 6.9 / 7.6 / 7.8, 7.9 /
+// !CROWDS: none of this, up to 2048 pages: 2048 pages 5.6 / 5.8 / 5.9, 8.3 / 7.4 / 5.7, 7.9 / 10.7 / 10.7, 6.9 / 7.6 / 7.8, 7.9 /
 // 7.85 / 8.0, 5.7 / 6.7 / 6.8 (with the exact ranges 6.05, 6.5, 7.4, 8.9, 9.1, 7.0).  The passes are a loop, whose code is cold
 // in an iteration: token selection at 32768 there 0.7 less than unrolled.  (A first range that leaves masks' scores and a lone
 // low one out, with up to four passes: masked and outlier 8.6 and 18.2 at the larger two, but every other call 0.3 to 1.6 more.)
 // given: a range that holds all keys taken and the last of them, [base, base + span], instead of the workgroup's smallest and largest key.
-template <bool CROWDS = true, int N, typename Valid>
+template <bool CROWDS = true, int THREADS = kSelectThreads, int N, typename Valid>
 __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int full, int live, Valid valid, uint32_t take,
                                                  RegisterSelectShared& sh, const LastKey* given = nullptr) {
-  constexpr int kWaves = kSelectThreads / 64;
+  constexpr int kWaves = THREADS / 64;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int i = tid; i < 3 * 2048 / 4; i += kSelectThreads) reinterpret_cast<u32x4*>(sh.hist)[i] = u32x4{0u, 0u, 0u, 0u};
+  for (int i = tid; i < 3 * 2048 / 4; i += THREADS) reinterpret_cast<u32x4*>(sh.hist)[i] = u32x4{0u, 0u, 0u, 0u};
   LastKey r;
   r.need = take;
   r.whole = false;
@@ -135,7 +136,7 @@ __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int f
     }
     set_range(hi, inv_lo);
   }
-  uint32_t keys = static_cast<uint32_t>(live) * kSelectThreads;     // in the range
+  uint32_t keys = static_cast<uint32_t>(live) * THREADS;     // in the range
   // (Keys without a position lie outside every range unless it starts at 0, the key of NaNs, and are the last there: a bin is
   //  then never taken whole, and of equal keys the first positions are.)
   int shift = max(32 - __builtin_clz(r.span | 1u) - 11, 0);
@@ -217,11 +218,11 @@ __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int f
   return r;
 }
 
-// ROWS x 16 cells in LDS, row-major, one per (row, wave), each with two 16-bit counts: lane kCellLanes u + wave / kCellsPerLane of
+// ROWS x waves cells in LDS, row-major, one per (row, wave), each with two 16-bit counts: lane kCellLanes u + wave / kCellsPerLane of
 // the result holds the sum of the cells before cell (u, this wave).  `rows` of them are in use.
-template <int ROWS>
+template <int ROWS, int THREADS = kSelectThreads>
 struct CellWalk {
-  static constexpr int kWaves = kSelectThreads / 64;
+  static constexpr int kWaves = THREADS / 64;
   static constexpr int kPerLane = ROWS * kWaves > 64 ? ROWS * kWaves / 64 : 1;
   static_assert(kWaves % kPerLane == 0, "a wave's cells sit at one place of their lanes");
   // total: the sum of all cells
@@ -241,14 +242,23 @@ struct CellWalk {
   static __device__ __forceinline__ int lane_of(int u, int wave) { return (kWaves * u + wave) / kPerLane; }
 };
 
-__global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const SelectParams p) {
+// One workgroup a sequence; prefixes of up to 8 THREADS pages keep their keys in registers.  What bounds it there is latency: two
+// dependent requests, then per digit a barrier, one wave's walk through 2048 counts and another barrier, and ahead of them the
+// instructions of every wave; with four waves on each SIMD of the one CU these run in turn.  kSelectFewThreads (max_seq_len of up to
+// 4096 pages; no general path, no LDS for keys): half the waves to start, to meet at each barrier and to walk for, more keys a thread.
+// us per captured call, 1024 threads / 512: 256 pages 5.4 / 4.6 (equal scores 4.0 / 3.4), 1024 pages 5.6 / 4.8, 2048 pages 5.8 / 5.3
+// (a twentieth -infinity 7.7 / 7.4), 24 x 1250 pages 6.1 / 5.4, 16 x 4096 pages 6.9 / 6.6; an iteration at 4096 tokens 38.5 -> 36.9,
+// at 32768 65.5 -> 65.1.  With 256: 4.5, 5.1, 5.9, 5.8.  Past 4096 pages the keys of 512 would leave the registers.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void select_blocks_kernel(const SelectParams p) {
   extern __shared__ uint32_t skeys[];                 // [min(prefix pages, key_cap)]
   __shared__ __align__(16) RegisterSelectShared reg_shared;
+  constexpr bool kGeneral = THREADS == kSelectThreads;  // prefixes of any length
   uint32_t (*hist)[256] = reinterpret_cast<uint32_t (*)[256]>(reg_shared.hist);   // general path: one digit histogram per wave
-  static_assert(sizeof(reg_shared.hist) >= (kSelectThreads / 64) * 256 * sizeof(uint32_t), "a histogram per wave");
+  static_assert(sizeof(reg_shared.hist) >= (THREADS / 64) * 256 * sizeof(uint32_t), "a histogram per wave");
   __shared__ uint32_t sh_prefix, sh_need, sh_count;
-  __shared__ uint32_t wave_take[kSelectThreads / 64], wave_eq[kSelectThreads / 64];
-  __shared__ uint32_t cells[kSelectRegRows * (kSelectThreads / 64)];
+  __shared__ uint32_t wave_take[THREADS / 64], wave_eq[THREADS / 64];
+  __shared__ uint32_t cells[kSelectRegRows * (THREADS / 64)];
 
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
@@ -257,22 +267,22 @@ __global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const Sel
   const int32_t* table = p.block_table + static_cast<int64_t>(b) * p.max_blocks;
   const float* scores = p.block_scores + static_cast<int64_t>(b) * p.max_blocks;
 
-  // With at most 8192 pages per row the scores are requested before the sequence length is known (one memory
+  // With at most 8 THREADS pages per row the scores are requested before the sequence length is known (one memory
   // round trip less, and all requests in flight together): every index below max_blocks is a valid address, what
   // lies past the prefix is dropped.
   constexpr int kPre = 8;
-  const bool prefetched = p.max_blocks <= kPre * kSelectThreads;
+  const bool prefetched = !kGeneral || p.max_blocks <= kPre * THREADS;   // (!kGeneral: the prefix fits, whatever the table's width)
   float pre[kPre];
   if (prefetched) {
 #pragma unroll
-    for (int i = 0; i < kPre; ++i) pre[i] = scores[min(tid + i * kSelectThreads, p.max_blocks - 1)];
+    for (int i = 0; i < kPre; ++i) pre[i] = scores[min(tid + i * THREADS, p.max_blocks - 1)];
   }
 
   int n = p.seq_lens[b];
   n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
   const int nblk = (n + kPage - 1) / kPage;
   if (nblk == 0) {
-    for (int i = tid; i < p.max_sel_blocks; i += kSelectThreads) sel[i] = -1;
+    for (int i = tid; i < p.max_sel_blocks; i += THREADS) sel[i] = -1;
     if (tid == 0) p.sel_seq_lens[b] = 0;
     return;
   }
@@ -289,13 +299,13 @@ __global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const Sel
 
   // ---- the whole prefix is taken: its pages in order, nothing to search
   if (kc > 0 && take_all) {
-    for (int j = tid; j < f0; j += kSelectThreads) sel[j] = table[j];
+    for (int j = tid; j < f0; j += THREADS) sel[j] = table[j];
   }
 
-  // ---- up to 8192 prefix pages: a thread keeps the keys of pages tid, tid + 1024, ... and their table entries in registers
+  // ---- up to 8 THREADS prefix pages: a thread keeps the keys of pages tid, tid + THREADS, ... and their table entries in registers
   auto register_path = [&]() {
     constexpr int kRows = kSelectRegRows;
-    const int rows = (f0 + kSelectThreads - 1) / kSelectThreads;          // 1 .. kRows, uniform
+    const int rows = (f0 + THREADS - 1) / THREADS;          // 1 .. kRows, uniform
     uint32_t key[kRows];
     int32_t page[kRows];
     // (rows past the prefix are skipped by uniform branches: loops stay fully unrolled, arrays in registers)
@@ -305,22 +315,25 @@ __global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const Sel
       v[u] = 0.f;
       page[u] = 0;
       if (u < rows) {
-        v[u] = (prefetched && u < kPre) ? pre[u < kPre ? u : 0] : scores[min(u * kSelectThreads + tid, f0 - 1)];
-        page[u] = table[min(u * kSelectThreads + tid, f0 - 1)];           // coalesced, used if the page is taken
+        v[u] = (prefetched && u < kPre) ? pre[u < kPre ? u : 0] : scores[min(u * THREADS + tid, f0 - 1)];
+        page[u] = table[min(u * THREADS + tid, f0 - 1)];           // coalesced, used if the page is taken
       }
     }
 #pragma unroll
-    for (int u = 0; u < kRows; ++u) key[u] = tid < f0 - u * kSelectThreads ? score_key(v[u]) : 0u;
-    // Two rows at most: neither counting by waves nor exact ranges, which cost there what they save (find_last_key).
-    auto valid = [&](int u) { return tid < f0 - u * kSelectThreads; };
+    for (int u = 0; u < kRows; ++u) key[u] = tid < f0 - u * THREADS ? score_key(v[u]) : 0u;
+    // 2048 pages at most: neither counting by waves nor exact ranges, which cost there what they save (find_last_key).
+    auto valid = [&](int u) { return tid < f0 - u * THREADS; };
     LastKey last;
-    if (rows <= 2) {
-      const uint32_t two[2] = {key[0], key[1]};
-      last = find_last_key<false>(two, f0 / kSelectThreads, rows, valid, static_cast<uint32_t>(kc), reg_shared);
+    constexpr int kFewRows = 2048 / THREADS;
+    if (rows <= kFewRows) {
+      uint32_t few[kFewRows];
+#pragma unroll
+      for (int u = 0; u < kFewRows; ++u) few[u] = key[u];
+      last = find_last_key<false, THREADS>(few, f0 / THREADS, rows, valid, static_cast<uint32_t>(kc), reg_shared);
     } else {
-      last = find_last_key(key, f0 / kSelectThreads, rows, valid, static_cast<uint32_t>(kc), reg_shared);
+      last = find_last_key<true, THREADS>(key, f0 / THREADS, rows, valid, static_cast<uint32_t>(kc), reg_shared);
     }
-    // Cell (row u, wave w) covers the 64 pages from 1024 u + 64 w on; it counts its keys above the last bin (low half) and in
+    // Cell (row u, wave w) covers the 64 pages from THREADS u + 64 w on; it counts its keys above the last bin (low half) and in
     // it.  A taken page's place: keys above before it + keys in the bin before it, of these at most as many as are taken.
     const uint32_t top = last.base + last.span;
     uint32_t packed = 0u;
@@ -331,15 +344,15 @@ __global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const Sel
       const uint32_t eq = __popcll(__builtin_amdgcn_ballot_w64(key[u] - last.base <= last.span));
       if (lane == u) packed = gt | (eq << 16);
     }
-    if (lane < rows) cells[lane * (kSelectThreads / 64) + wave] = packed;
+    if (lane < rows) cells[lane * (THREADS / 64) + wave] = packed;
     __syncthreads();
-    const uint32_t before = CellWalk<kRows>::before(cells, rows, wave, lane);
+    const uint32_t before = CellWalk<kRows, THREADS>::before(cells, rows, wave, lane);
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
       if (u >= rows) continue;
       const bool gt = key[u] > top, eq = key[u] - last.base <= last.span;
       const uint64_t bgt = __builtin_amdgcn_ballot_w64(gt), beq = __builtin_amdgcn_ballot_w64(eq);
-      const uint32_t w = __builtin_amdgcn_readlane(before, CellWalk<kRows>::lane_of(u, wave));
+      const uint32_t w = __builtin_amdgcn_readlane(before, CellWalk<kRows, THREADS>::lane_of(u, wave));
       const uint32_t e = lanes_below(beq, w >> 16);
       const uint32_t rank = lanes_below(bgt, w & 0xFFFFu) + min(e, last.need);
       if ((gt || (eq && e < last.need)) && rank < static_cast<uint32_t>(p.max_sel_blocks)) sel[rank] = page[u];
@@ -347,17 +360,17 @@ __global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const Sel
   };
 
   // ---- longer prefixes: keys go to LDS once (up to key_cap of them; beyond that they are recomputed from the scores)
-  const bool in_regs = f0 <= kSelectRegRows * kSelectThreads;
+  const bool in_regs = !kGeneral || f0 <= kSelectRegRows * THREADS;
   const bool in_lds = f0 <= p.key_cap;
-  if (need_search && !in_regs && in_lds) {
+  if (kGeneral && need_search && !in_regs && in_lds) {
     // groups of kPre independent requests (clamped, so that none sits behind a branch)
-    for (int base = tid; base < f0; base += kPre * kSelectThreads) {
+    for (int base = tid; base < f0; base += kPre * THREADS) {
       float v[kPre];
 #pragma unroll
-      for (int i = 0; i < kPre; ++i) v[i] = scores[min(base + i * kSelectThreads, f0 - 1)];
+      for (int i = 0; i < kPre; ++i) v[i] = scores[min(base + i * THREADS, f0 - 1)];
 #pragma unroll
       for (int i = 0; i < kPre; ++i)
-        if (base + i * kSelectThreads < f0) skeys[base + i * kSelectThreads] = score_key(v[i]);
+        if (base + i * THREADS < f0) skeys[base + i * THREADS] = score_key(v[i]);
     }
     __syncthreads();
   }
@@ -394,7 +407,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const Sel
           bool act[kR];
 #pragma unroll
           for (int u = 0; u < kR; ++u) {
-            const int j = base + u * kSelectThreads + tid;
+            const int j = base + u * THREADS + tid;
             const uint32_t key = key_at(min(j, f0 - 1));
             act[u] = j < f0 && (key & mask) == prefix;
             d[u] = (key >> shift) & 255u;
@@ -419,23 +432,23 @@ __global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const Sel
           }
         };
         for (int base = 0; base < f0;) {
-          const int rows = (f0 - base + kSelectThreads - 1) / kSelectThreads;
+          const int rows = (f0 - base + THREADS - 1) / THREADS;
           if (rows >= 4) {
             count_rows(base, std::integral_constant<int, 4>{});
-            base += 4 * kSelectThreads;
+            base += 4 * THREADS;
           } else if (rows >= 2) {
             count_rows(base, std::integral_constant<int, 2>{});
-            base += 2 * kSelectThreads;
+            base += 2 * THREADS;
           } else {
             count_rows(base, std::integral_constant<int, 1>{});
-            base += kSelectThreads;
+            base += THREADS;
           }
         }
         __syncthreads();
         if (wave == 0) {
           // lane l owns bins 4l .. 4l+3; count from the top bin downwards
           uint32_t c[4] = {0u, 0u, 0u, 0u};
-          for (int w = 0; w < kSelectThreads / 64; ++w) {
+          for (int w = 0; w < THREADS / 64; ++w) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) c[i] += hist[w][4 * lane + i];
           }
@@ -473,7 +486,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const Sel
     //      coalesced.  Ballots count the keys above T and the ties; a 16-entry prefix over the wave totals turns
     //      the counts into global tie ranks and output positions.
     {
-      constexpr int kWaves = kSelectThreads / 64;
+      constexpr int kWaves = THREADS / 64;
       const int span = ((f0 + kWaves - 1) / kWaves + 63) / 64 * 64;
       const int w0 = min(wave * span, f0), w1 = min(w0 + span, f0);
       const uint64_t lt = (1ull << lane) - 1ull;
@@ -538,13 +551,15 @@ __global__ __launch_bounds__(kSelectThreads) void select_blocks_kernel(const Sel
   };
   if (need_search) {
     if (in_regs) register_path();
-    else if (in_lds) search_and_compact(std::true_type{});
-    else search_and_compact(std::false_type{});
+    if constexpr (kGeneral) {
+      if (!in_regs && in_lds) search_and_compact(std::true_type{});
+      if (!in_regs && !in_lds) search_and_compact(std::false_type{});
+    }
   }
 
   // ---- forced tail pages, padding, covered length
-  for (int i = tid; i < nF; i += kSelectThreads) sel[kc + i] = table[nblk - nF + i];
-  for (int i = k + tid; i < p.max_sel_blocks; i += kSelectThreads) sel[i] = -1;
+  for (int i = tid; i < nF; i += THREADS) sel[kc + i] = table[nblk - nF + i];
+  for (int i = k + tid; i < p.max_sel_blocks; i += THREADS) sel[i] = -1;
   if (tid == 0) p.sel_seq_lens[b] = kPage * (k - 1) + (n - kPage * (nblk - 1));
 }
 

@@ -565,7 +565,7 @@ int for_each_lds_kernel(F f) {
   one(verify_finalize_kernel<64, 1>); one(verify_finalize_kernel<0, 1>);
   one(verify_finalize_kernel<kFinPlanned, 0>); one(verify_finalize_kernel<kFinPlanned, 1>);
   one(verify_finalize_kernel<kFinPlannedSmall, 0>); one(verify_finalize_kernel<kFinPlannedSmall, 1>);
-  one(select_blocks_kernel);
+  one(select_blocks_kernel<kSelectThreads>);
   return rc;
 }
 
@@ -746,9 +746,13 @@ int vegas_select_blocks(const vegas_desc* desc, const float* block_scores, const
   const int64_t max_pages = (static_cast<int64_t>(desc->max_seq_len) + kPage - 1) / kPage;
   sp.key_cap = static_cast<int32_t>(max_pages < kSelectKeyCap ? max_pages : kSelectKeyCap);
   const size_t shm = static_cast<size_t>(sp.key_cap) * sizeof(uint32_t);
-  if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(select_blocks_kernel), shm)) return rc;
-  hipLaunchKernelGGL(select_blocks_kernel, dim3(desc->batch), dim3(kSelectThreads), shm,
-                     static_cast<hipStream_t>(hip_stream), sp);
+  const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  if (max_pages <= kSelectRegRows * kSelectFewThreads) {
+    hipLaunchKernelGGL(select_blocks_kernel<kSelectFewThreads>, dim3(desc->batch), dim3(kSelectFewThreads), 0, stream, sp);
+  } else {
+    if (int rc = ensure_dynamic_lds(reinterpret_cast<const void*>(select_blocks_kernel<kSelectThreads>), shm)) return rc;
+    hipLaunchKernelGGL(select_blocks_kernel<kSelectThreads>, dim3(desc->batch), dim3(kSelectThreads), shm, stream, sp);
+  }
   return hipGetLastError() == hipSuccess ? VEGAS_OK : VEGAS_ERR_LAUNCH;
 }
 
