@@ -534,7 +534,6 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int tok = tok0 + 8 * (i >> 2) + 4 * half + (i & 3);
-          // (the local variant may step on a tile past its chunk, see below: nothing there is visible)
           if (tok > limit[nb] || (LOCAL && (tok <= limit[nb] - p.window || tok >= c1))) st[nb][i] = -INFINITY;
         }
       }
@@ -626,20 +625,9 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
     using yes = std::integral_constant<bool, true>;
     using no = std::integral_constant<bool, false>;
     int k = k_first;
-    if constexpr (LOCAL) {
-      // (Local masking may leave this wave without a tile.)  This variant always steps two tiles at a time, the last
-      // one possibly past the chunk's end, where every token is masked out: one loop shape less keeps it inside its
-      // register budget.
-      if (k < ntiles) {
-        const int stop = k + ((ntiles - k + 1) & ~1);
-        for (; k + 2 < stop; k += 2) {
-          step(k, va, vb, yes{});
-          step(k + 1, vb, va, yes{});
-        }
-        step(k, va, vb, yes{});
-        step(k + 1, vb, va, no{});
-      }
-    } else {
+    // (Local masking may leave a wave without a tile, and few have many: no step past the last one.  Steps by two whatever their number:
+    //  window 16, 64, 128 in 32 sequences x 8 heads, 20 rows, head dimension 128 7.2, 8.3, 9.0 us a call instead of 5.6, 6.3, 8.0.)
+    if (!LOCAL || k < ntiles) {
       while (k + 2 < ntiles) {
         step(k, va, vb, yes{});
         step(k + 1, vb, va, yes{});

@@ -90,10 +90,28 @@ inline int draft_value_parts(int64_t columns, int num_cu, int head_dim) {
 // head dimension 64:  128: 389 9.1 / 7.5, 517 9.1 / 9.5;  1024: 1029 13.2 / 12.6;  1792: 1029 15.1 / 12.7, 2053 17.7 / 18.6.
 // (Where in its chunk a band of less than a chunk falls decides whether it is one part or two, which is worth up to half
 // of the streaming time: the figures are for one place at batch 1, for a batch of many beyond.)
-inline bool lone_workgroup_band(int window, int queries, int max_len, int chunk) {
+// These are workgroups of four waves that always took a second tile; with kBandWaves of them where eight_wave_band says so, and
+// chunks of 128 (8 to 16 workgroups): head dimension 64, 20 rows: 424 7.2 / 6.0, 564 7.6 / 6.5 and 8.4 / 6.9, 704 7.3 / 7.1, 1004 7.6 / 8.0;
+// 4 rows: 564 7.1 / 6.3, 1001 7.2 / 7.8; 128, 20 rows: 424 9.0 / 8.4, 564 9.3 / 9.2, 704 9.0 / 10.4; 4 rows: 420 8.1 / 7.9, 480 7.8 / 8.1.
+// alone: the longest band that is not cut for being longer than a chunk (lone_band_tokens).
+inline bool lone_workgroup_band(int window, int queries, int max_len, int chunk, int alone = 416) {
   int64_t seen = static_cast<int64_t>(window) + queries;
   if (seen > max_len) seen = max_len;
-  return seen <= 416 || seen <= chunk;
+  return seen <= alone || seen <= chunk;
+}
+constexpr int lone_band_tokens(int head_dim) { return head_dim == 64 ? 640 : 448; }
+
+
+// Waves of such a workgroup: a wave's second tile is a round trip behind its first, and a band of 128 tokens has five or six.  Eight
+// instead of four where the band can have more than four tiles (98 tokens; fewer lose the 0.2 to 0.3 us by which eight waves' rows are
+// merged later), every workgroup has a compute unit to itself (384 and more are a second round, 8.2 -> 9.8), and what a row block's
+// workgroups read in all is not itself the time (seen: tokens of the band).  us a call, captured, four waves / eight, window 64, 128, 256,
+// 400, 1000; head dimension 64, 16 sequences x 8 heads, 40 rows (256 workgroups): 4.8 / 5.1, 6.0 / 5.5, 6.8 / 6.6, 8.0 / 6.8, 11.9 / 10.9; one
+// sequence, 20 rows 4.4 / 4.6, 5.6 / 5.0, 6.4 / 5.9, 7.1 / 6.2; 32 of them 4.7 / 5.1, 5.9 / 5.4, 7.1 / 6.9, 8.1 / 7.8, 15.0 / 15.4; 128, 40 rows,
+// 16 sequences 6.2 / 6.4, 7.9 / 7.0, 9.4 / 8.7, 10.7 / 10.1, 17.0 / 17.6; 20 rows, 32 sequences 6.3 / 6.6, 8.0 / 7.6, 10.4 / 10.9, 12.9 / 13.2.
+constexpr int kBandWaves = 8;
+inline bool eight_wave_band(int64_t columns, int row_blocks, int num_cu, int64_t seen, int head_dim) {
+  return columns * row_blocks <= num_cu && seen > 97 && columns * seen * head_dim * 4 <= (int64_t{18} << 20) * row_blocks;
 }
 
 // Verification of more than 64 rows per KV head (with the two sum rows of the logit metric, and there of just above 32 as

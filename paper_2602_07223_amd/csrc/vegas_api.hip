@@ -106,7 +106,7 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   const int num_cu = device_cu_count();
   const int64_t heads = static_cast<int64_t>(d->batch) * d->num_kv_heads;
   if (rows_per_head > 128) return VEGAS_ERR_UNSUPPORTED;
-  pl->NW = 4;                                        // measured: 4-wave groups match or beat 8-wave groups everywhere
+  pl->NW = 4;                                        // measured: 4-wave groups match or beat 8-wave groups everywhere but in short bands (below)
   // Row blocks: 32 rows each, sibling workgroups that share an XCD's L2; verification of more than 32 rows (with the two
   // sum rows of the logit metric, which take a block's spare rows) has blocks of 64 served from one read of K/V, small
   // calls excepted (unless they bring a chunk length, whose collected values siblings might not park).  The sum rows may
@@ -171,9 +171,9 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
                  per_head <= num_cu;
   // Smaller groups have a rule of their own, and so has verification with a local mask: no row sees more than
   // window + G - 1 tokens, and a workgroup begins where the first of them is (16 sequences of 8192..65536 tokens, 40 rows,
-  // head dimension 64, window 128: 11.7 us with a merge, 8.1 without).
+  // head dimension 64, window 128: 11.7 us with a merge, 5.5 without).
   const bool banded = !may_finish && d->window > 0 && d->kv_chunk_tokens == 0 &&
-                      lone_workgroup_band(d->window, d->num_queries, max_len, chunk);
+                      lone_workgroup_band(d->window, d->num_queries, max_len, chunk, lone_band_tokens(d->head_dim));
   const bool finish = banded || (own_chunks && rows_per_head <= kDraftRows && max_len <= lone_workgroup_tokens(heads, num_cu, d->head_dim, d->head_dim == 128 && d->page_size == kPage));
   if (fine && own_chunks && !finish && rows_per_head <= kDraftRows && chunk == unit)
     chunk = draft_chunk_tokens(heads, num_cu, max_len, unit, rows_per_head * d->head_dim);
@@ -181,6 +181,8 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   //  the same, so that these rules move neither the sizes callers allocate nor what the built-in scratch takes.)
   size_t slots = static_cast<size_t>(heads) * ((max_len + chunk - 1) / chunk);   // chunk partials the workspace holds
   if (finish) chunk = whole;
+  if (banded && eight_wave_band(heads, pl->NB, num_cu, std::min<int64_t>(static_cast<int64_t>(d->window) + d->num_queries - 1, max_len), d->head_dim))
+    pl->NW = kBandWaves;
   pl->chunk = chunk;
   pl->nsplit = (max_len + chunk - 1) / chunk;
   if (pl->balanced) {
@@ -380,6 +382,10 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
   }
   if constexpr (CAUSAL && COLLECT == 0) {           // banded layer: local masking on top of the causal mask
     if (sp.window > 0) {
+      if (pl.NW == kBandWaves) {
+        if (pl.NB == 1) return launch_one(attn_split_kernel<kBandWaves, 2, true, 0, true, 4, true, D>, grid, dim3(kBandWaves * 64), lds, st, sp);
+        return launch_one(attn_split_kernel<kBandWaves, 2, true, 0, false, 4, true, D>, grid, dim3(kBandWaves * 64), lds, st, sp);
+      }
       if (pl.NB == 1) return launch_one(attn_split_kernel<4, 2, true, 0, true, 4, true, D>, grid, dim3(256), lds, st, sp);
       return launch_one(attn_split_kernel<4, 2, true, 0, false, 4, true, D>, grid, dim3(256), lds, st, sp);
     }
@@ -534,6 +540,7 @@ int for_each_lds_kernel(F f) {
     one(attn_split_kernel<4, 2, false, 0, false, 4, false, D>);
     one(attn_split_kernel<4, 2, true, 0, true, 4, true, D>);         // verification of a banded layer
     one(attn_split_kernel<4, 2, true, 0, false, 4, true, D>);
+    one(attn_split_kernel<kBandWaves, 2, true, 0, true, 4, true, D>); one(attn_split_kernel<kBandWaves, 2, true, 0, false, 4, true, D>);
     one(attn_split_kernel<4, 2, true, 0, true, 4, false, D>);        // verification: no collection / page weights / logits
     one(attn_split_kernel<4, 2, true, 1, true, 4, false, D>);
     one(attn_split_kernel<4, 2, true, 0, false, 4, false, D>);       // ... as sibling row blocks
