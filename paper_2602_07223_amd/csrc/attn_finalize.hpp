@@ -31,32 +31,38 @@ struct RowMerge {
     __builtin_amdgcn_sched_barrier(0);     // every request leaves before the first use
   }
   // Output element: sum_s 2^(m_s - m) x_s / sum_s 2^(m_s - m) l_s over the first ns chunks; 0 if no key was visible.
-  // Chunks before s_lo were skipped by a call with local masking and hold nothing either.  last: as in issue.
-  __device__ __forceinline__ float finish(int ns, int last, int s_lo = 0) const {
+  // Chunks before s_lo were skipped by a call with local masking and hold nothing either.
+  __device__ __forceinline__ float finish(int ns, int s_lo = 0) const {
     const int lane = threadIdx.x & 63;
-    return finish(lane >= s_lo && lane < ns, s_lo == 0 && ns > last);
+    return finish(lane >= s_lo && lane < ns);
   }
-  // The same for the chunks s whose lane s says `live`; whole: all slots that were requested are.
-  __device__ __forceinline__ float finish(bool live, bool whole) const {
+  // The same for the chunks s whose lane s says `live`.
+  __device__ __forceinline__ float finish(bool live) const {
     const uint64_t lives = __builtin_amdgcn_ballot_w64(live);
     const float ms = live ? mine[0] : -INFINITY;
     const float m = wave_max(ms);
     const float m_use = (m == -INFINITY) ? 0.f : m;
     const float w = fast_exp2(ms - m_use);              // 0 for lanes at or past ns
     const float L = wave_sum(live ? w * mine[1] : 0.f);
-    // Four sums, whose steps do not wait for each other.  Where the row's last slot is live, and with it (s_lo aside, see `whole`) every
-    // one that was requested, no element has to be looked at: the weights of lanes behind it are 0.  (One sum with a test per element: the
-    // merge alone, captured, 22 chunks 2.31 / 2.18 us, 33 2.71 / 2.62.)
+    // Four sums, whose steps do not wait for each other, and four slots at a time: elements are looked at only where some of four are live
+    // and some not, so that a slot that is not (unwritten, or the row's last one once more) never meets a weight: 0 times an infinity is
+    // no 0.  (One sum with a test per element: the merge alone, captured, 22 chunks 2.31 / 2.18 us, 33 2.71 / 2.62, with one
+    // test for all slots.  With that / by fours, us per iteration: 32768 tokens 65.4 / 65.4, live 69.4 / 70.1, 4 x 65536 259.0 / 257.9, 131072
+    // 150.5 / 147.7.)
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    auto add_up = [&](auto all) {
 #pragma unroll
-      for (int s = 0; s < MAXS; ++s) {
-        const float ws = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s));
-        acc[s & 3] = __builtin_fmaf(ws, decltype(all)::value || ((lives >> s) & 1u) ? x[s] : 0.f, acc[s & 3]);
-      }
-    };
-    if (whole) add_up(std::true_type{});
-    else add_up(std::false_type{});
+    for (int s0 = 0; s0 < MAXS; s0 += 4) {
+      const uint32_t four = static_cast<uint32_t>(lives >> s0) & 15u;
+      auto add_up = [&](auto all) {
+#pragma unroll
+        for (int s = s0; s < s0 + 4; ++s) {
+          const float ws = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s));
+          acc[s & 3] = __builtin_fmaf(ws, decltype(all)::value || ((four >> (s - s0)) & 1u) ? x[s] : 0.f, acc[s & 3]);
+        }
+      };
+      if (four == 15u) add_up(std::true_type{});
+      else if (four != 0u) add_up(std::false_type{});
+    }
     return (L > 0.f) ? ((acc[0] + acc[1]) + (acc[2] + acc[3])) / L : 0.f;
   }
 };
@@ -97,7 +103,7 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p
     auto merge = [&](auto maxs) {
       RowMerge<decltype(maxs)::value> rm;
       rm.issue(ml, po - tid, tid, p.R, cc.last, T);
-      return rm.finish(ns, cc.last, s_lo);
+      return rm.finish(ns, s_lo);
     };
     float o;
     if (ns <= 4) o = merge(std::integral_constant<int, 4>{});
@@ -167,8 +173,7 @@ __global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_S
   if (window > 0) s_lo = first_live_chunk(n, R / g, window, chunk_tokens);
   // (a chunk that starts past 2^31 tokens is behind every end)
   const bool live = lane >= s_lo && static_cast<uint64_t>(static_cast<uint32_t>(lane)) * static_cast<uint32_t>(chunk_tokens) < static_cast<uint32_t>(n);
-  const bool whole = s_lo == 0 && static_cast<uint64_t>(static_cast<uint32_t>(nsplit - 1)) * static_cast<uint32_t>(chunk_tokens) < static_cast<uint32_t>(n);
-  *dst = float_to_bf16_bits(rm.finish(live, whole));
+  *dst = float_to_bf16_bits(rm.finish(live));
 }
 
 // Verification epilogue in ONE launch (a kernel boundary costs ~3 us on this GPU): workgroups
@@ -594,7 +599,7 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
       RowMerge<MAXS> rm;
       rm.issue(ml, p.part_o + (pbase * p.R + r) * T, t128, p.R, cs.last, T);
       n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
-      o = rm.finish((n + cs.chunk - 1) / cs.chunk, cs.last);
+      o = rm.finish((n + cs.chunk - 1) / cs.chunk);
     } else {
       int n = plan_n;
       if constexpr (!kPlanned) {
@@ -621,7 +626,7 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
         auto merge = [&](auto maxs) {
           RowMerge<decltype(maxs)::value> rm;
           rm.issue(ml, po, t128, p.R, cc.last, T);
-          return rm.finish(ns, cc.last);
+          return rm.finish(ns);
         };
         if (ns <= 4) o = merge(std::integral_constant<int, 4>{});
         else if (ns <= 8) o = merge(std::integral_constant<int, 8>{});
