@@ -96,12 +96,10 @@ inline size_t draft16_lds_bytes(int R, int D) {
 // bounds it is how much that unit has under way; the rule and its figures: ring_draft.
 // DV: head dims of V that the workgroup reads and of the output rows that it writes: D, or a part of it in calls that one workgroup per
 // column could finish (grid (KV head, part, sequence); draft_value_parts).
-template <int D, int PS = 4, bool CHOOSE = false, bool RING = false, int DV = D, typename... Step>
-__global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS_SPLIT_HOT_PARAMS, const SplitParams pfull, const Step... step) {
+template <int D, int PS, bool CHOOSE, bool RING, int DV, typename... Step>
+__device__ __forceinline__ void draft16(SplitParams& p, const Step&... step) {
   VEGAS_TL_DECL;
   VEGAS_TL(kTlEntry);
-  SplitParams p = pfull;                     // (see attn_split_kernel: the preloaded arguments)
-  VEGAS_SPLIT_HOT_ASSIGN(p);
   static_assert(D == 128 || D == 64, "head dimension");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr bool APPEND = sizeof...(Step) == 1;
@@ -665,6 +663,21 @@ __global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS
   }
   stream_chunk(std::false_type{});
   append_row();
+}
+
+template <int D, int PS = 4, bool CHOOSE = false, bool RING = false, typename... Step>
+__global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_kernel(VEGAS_SPLIT_HOT_PARAMS, const SplitParams pfull, const Step... step) {
+  SplitParams p = pfull;                     // (see attn_split_kernel: the preloaded arguments)
+  VEGAS_SPLIT_HOT_ASSIGN(p);
+  draft16<D, PS, CHOOSE, RING, D>(p, step...);
+}
+
+// A workgroup for every DV head dims of V (draft_value_parts).
+template <int D, int DV, int PS, bool RING>
+__global__ __launch_bounds__(kDraftWaves * 64, 2) void attn_draft16_parts_kernel(VEGAS_SPLIT_HOT_PARAMS, const SplitParams pfull) {
+  SplitParams p = pfull;
+  VEGAS_SPLIT_HOT_ASSIGN(p);
+  draft16<D, PS, false, RING, DV>(p);
 }
 
 }  // namespace vegas

@@ -339,15 +339,16 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
       const dim3 dblock(kDraftWaves * 64);
       const size_t dlds = draft16_lds_bytes(pl.R, D);
       const bool choose = draft_chooses(batch, sp.max_tokens, sp.Hkv, D);
-      if (step != nullptr) return launch_one(attn_draft16_kernel<D, 4, false, false, D, DraftStep>, grid, dblock, dlds, st, sp, *step);
+      if (step != nullptr) return launch_one(attn_draft16_kernel<D, 4, false, false, DraftStep>, grid, dblock, dlds, st, sp, *step);
       const int64_t columns = static_cast<int64_t>(batch) * sp.Hkv;
       const bool lone = sp.out_direct != nullptr && !choose;       // one workgroup per column, or one per part of its V
       const int parts = lone ? draft_value_parts(columns, device_cu_count(), D) : 1;
       auto launch = [&](auto ps, auto ring, auto value_dims) {
         constexpr int PS = decltype(ps)::value, DV = decltype(value_dims)::value;
         constexpr bool RING = decltype(ring)::value;
-        const dim3 pgrid = DV == D ? grid : dim3(sp.Hkv, D / DV, batch);
-        return launch_one(attn_draft16_kernel<D, PS, false, RING, DV>, pgrid, dblock, RING ? draft_ring_lds_bytes() : dlds, st, sp);
+        const size_t bytes = RING ? draft_ring_lds_bytes() : dlds;
+        if constexpr (DV == D) return launch_one(attn_draft16_kernel<D, PS, false, RING>, grid, dblock, bytes, st, sp);
+        else return launch_one(attn_draft16_parts_kernel<D, DV, PS, RING>, dim3(sp.Hkv, D / DV, batch), dblock, bytes, st, sp);
       };
       auto by_parts = [&](auto ps, auto ring) {
         if (parts == D / 32) return launch(ps, ring, std::integral_constant<int, 32>{});
@@ -550,18 +551,18 @@ int for_each_lds_kernel(F f) {
     auto draft16 = [&](auto ps) {
       constexpr int PS = decltype(ps)::value;
       one(attn_draft16_kernel<D, PS, false>); one(attn_draft16_kernel<D, PS, true>);
-      one(attn_draft16_kernel<D, PS, false, false, 32>);
-      if constexpr (D == 128) one(attn_draft16_kernel<D, PS, false, false, 64>);
+      one(attn_draft16_parts_kernel<D, 32, PS, false>);
+      if constexpr (D == 128) one(attn_draft16_parts_kernel<D, 64, PS, false>);
     };
     draft16(std::integral_constant<int, 0>{}); draft16(std::integral_constant<int, 1>{}); draft16(std::integral_constant<int, 2>{});
     draft16(std::integral_constant<int, 3>{}); draft16(std::integral_constant<int, 4>{});
-    one(attn_draft16_kernel<D, 4, false, false, D, DraftStep>);
+    one(attn_draft16_kernel<D, 4, false, false, DraftStep>);
     one(attn_pair_kernel<0, D, true>); one(attn_pair_kernel<0, D, false>);
     one(attn_pair_kernel<1, D, true>); one(attn_pair_kernel<1, D, false>);
     one(attn_pair_kernel<2, D, true>); one(attn_pair_kernel<2, D, false>);
   };
   one(attn_pair_kernel<1, 64, true, 2 * kPairWaves>); one(attn_pair_kernel<1, 64, false, 2 * kPairWaves>);
-  one(attn_draft16_kernel<128, 4, false, true>); one(attn_draft16_kernel<128, 4, false, true, 64>); one(attn_draft16_kernel<128, 4, false, true, 32>);
+  one(attn_draft16_kernel<128, 4, false, true>); one(attn_draft16_parts_kernel<128, 64, 4, true>); one(attn_draft16_parts_kernel<128, 32, 4, true>);
   per_dim(std::integral_constant<int, 128>{});
   per_dim(std::integral_constant<int, 64>{});
   one(verify_finalize_kernel<16, 0>); one(verify_finalize_kernel<32, 0>);

@@ -85,3 +85,14 @@ def test_small_page_draft_kernels_start_without_draining(report):
     way as far as the compiler knows) cost a call of one tile per wave 0.2 to 0.3 us."""
     waits = waits_before_the_stream(report[1])
     assert len(waits) == 8 and all(0 not in w for w in waits.values()), waits
+
+
+def test_m0_belongs_to_the_loads_into_lds_of_draft_parts(report):
+    """As above for the workgroups of a part of V each, whose K and V go through rings: 8 loads of K and 2 or 4 of V a tile."""
+    rings = [b for b in re.findall(r"^_ZN5vegas25attn_draft16_parts_kernel\w*:(.*?)^\.Lfunc_end", report[1], flags=re.M | re.S) if "global_load_lds" in b]
+    assert len(rings) == 2
+    for body in rings:
+        body = re.sub(r"[ \t]*;.*", "", body)
+        own = re.compile(r"s_mov_b32 m0, s\d+\s+s_nop 0\s+global_load_lds_dwordx4 v\d+, s\[\d+:\d+\]")
+        foreign = [line.strip() for line in own.sub("", body).splitlines() if re.search(r"\bm0\b|global_load_lds", line)]
+        assert len(own.findall(body)) >= 16 and not foreign, foreign[:4]
