@@ -13,7 +13,7 @@ namespace vegas {
 // sequence were never written; their slots are loaded all the same (the workspace holds nsplit of them)
 // and then discarded.  Addresses are a scalar base plus a 32-bit offset: the kernel is so short that
 // 64-bit address arithmetic per load would show in its run time.
-template <int MAXS>
+template <int MAXS, int SURE = MAXS < 8 ? 0 : MAXS / 2>
 struct RowMerge {
   f32x2 mine;        // (max, sum) of chunk `lane`
   float x[MAXS];     // this thread's head dim of every chunk's partial row
@@ -44,25 +44,38 @@ struct RowMerge {
     const float m_use = (m == -INFINITY) ? 0.f : m;
     const float w = fast_exp2(ms - m_use);              // 0 for lanes at or past ns
     const float L = wave_sum(live ? w * mine[1] : 0.f);
-    // Four sums, whose steps do not wait for each other, and four slots at a time: elements are looked at only where some of four are live
-    // and some not, so that a slot that is not (unwritten, or the row's last one once more) never meets a weight: 0 times an infinity is
-    // no 0.  (One sum with a test per element: the merge alone, captured, 22 chunks 2.31 / 2.18 us, 33 2.71 / 2.62, with one
-    // test for all slots.  With that / by fours, us per iteration: 32768 tokens 65.4 / 65.4, live 69.4 / 70.1, 4 x 65536 259.0 / 257.9, 131072
-    // 150.5 / 147.7.)
+    // Four sums, whose steps do not wait for each other.  Elements are looked at only where a slot may not be live, so that one that is not
+    // (unwritten, or the row's last one once more) never meets a weight: 0 times an infinity is no 0.  SURE: slots that are live if
+    // all requested ones are, by the rule that chose MAXS; behind them four at a time, those that hold nothing left out.  us per iteration,
+    // no slot looked at where all requested ones are live / all by fours / so: 32768 tokens 65.4 / 65.4 / 65.2, live 69.4 / 70.1 / 69.5,
+    // 131072 (33 chunks) 150.5 / 147.4 / 147.0.  (One sum with a test per element, the merge alone, captured: 22 chunks 2.31 against 2.18 us, 33
+    // 2.71 against 2.62.)
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    auto add_up = [&](auto first, auto end, auto all) {
 #pragma unroll
-    for (int s0 = 0; s0 < MAXS; s0 += 4) {
-      const uint32_t four = static_cast<uint32_t>(lives >> s0) & 15u;
-      auto add_up = [&](auto all) {
-#pragma unroll
-        for (int s = s0; s < s0 + 4; ++s) {
-          const float ws = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s));
-          acc[s & 3] = __builtin_fmaf(ws, decltype(all)::value || ((four >> (s - s0)) & 1u) ? x[s] : 0.f, acc[s & 3]);
-        }
-      };
-      if (four == 15u) add_up(std::true_type{});
-      else if (four != 0u) add_up(std::false_type{});
-    }
+      for (int s = decltype(first)::value; s < decltype(end)::value; ++s) {
+        const float ws = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), s));
+        acc[s & 3] = __builtin_fmaf(ws, decltype(all)::value || ((lives >> s) & 1u) ? x[s] : 0.f, acc[s & 3]);
+      }
+    };
+    using none = std::integral_constant<int, 0>;
+    using sure = std::integral_constant<int, SURE>;
+    if ((~lives & ((1ull << SURE) - 1ull)) == 0u) add_up(none{}, sure{}, std::true_type{});
+    else add_up(none{}, sure{}, std::false_type{});
+    auto rest = [&](auto at) {
+      constexpr int s0 = SURE + 4 * decltype(at)::value;
+      if constexpr (s0 < MAXS)
+        if ((static_cast<uint32_t>(lives >> s0) & 15u) != 0u) add_up(std::integral_constant<int, s0>{}, std::integral_constant<int, s0 + 4>{}, std::false_type{});
+    };
+    static_assert(MAXS - SURE <= 32 && (MAXS - SURE) % 4 == 0, "eight groups of four");
+    rest(std::integral_constant<int, 0>{});
+    rest(std::integral_constant<int, 1>{});
+    rest(std::integral_constant<int, 2>{});
+    rest(std::integral_constant<int, 3>{});
+    rest(std::integral_constant<int, 4>{});
+    rest(std::integral_constant<int, 5>{});
+    rest(std::integral_constant<int, 6>{});
+    rest(std::integral_constant<int, 7>{});
     return (L > 0.f) ? ((acc[0] + acc[1]) + (acc[2] + acc[3])) / L : 0.f;
   }
 };
@@ -161,7 +174,7 @@ __global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_S
   int zero = 0;
   asm("" : "+v"(zero));                      // (a vector load, the first to come back: the compiler puts a scalar one last)
   int n = lens[b + zero];
-  RowMerge<MAXS> rm;
+  RowMerge<MAXS, MAXS <= 8 ? 0 : MAXS <= 24 ? MAXS - 4 : MAXS <= 48 ? MAXS - 8 : 48> rm;       // (launch_combine: the step below MAXS)
   rm.issue(part_ml + row, part_o + row * D, tid, R, nsplit - 1, D);
   if ((r | h | tid) == 0) (lengths.store(b), ...);
   const int t = static_cast<int>((static_cast<float>(r) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(g)));
