@@ -25,15 +25,10 @@ namespace vegas {
 //      320    3200 +0.4/-10/+5.4, 4128 +7.2/+21/+14                 3200 -2.6/-3.2/+0.9, 4128 +11/-1.6/+5.4
 // The lines lie where a call gains with equal and with spread lengths (0.8 us lost at most) and a lone long selection takes no
 // more than half as long again (192 columns, 3200 tokens, head dimension 128: 24 -> 32 us, in an iteration of 319).
-// rings: head dimension 128 and 16-token pages, where K and V go through rings and V is read in parts (ring_draft, draft_value_parts).  us a
-// call, chunks / one workgroup per part, equal / spread / one: 64 columns, 608 tokens 7.7 / 5.8, 7.5 / 5.6, 6.5 / 5.6; 72, 608 7.9 / 6.2, 7.8 / 5.9,
-// 6.6 / 5.8; 96, 928 11.7 / 9.5, 10.8 / 7.9, 9.9 / 7.7; 1056 12.7 / 10.8, 10.7 / 8.5, 9.9 / 8.3.  Both go on to win there (64 columns, 928 8.1 / 7.8;
-// 96, 1312 16.3 / 12.8), and with fewer up to 600 to 800 tokens, but not by the launch that a live draft step then takes for its append.
-inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim, bool rings = false) {
-  if (rings) {
-    if (32 * columns >= 8 * static_cast<int64_t>(num_cu) && 32 * columns < 12 * static_cast<int64_t>(num_cu)) return 640;
-    if (32 * columns >= 12 * static_cast<int64_t>(num_cu) && 32 * columns < 16 * static_cast<int64_t>(num_cu)) return 1056;
-  }
+// (With V in parts, draft_value_parts, 64 columns go on to win up to 928 tokens and 96 up to 1312: 64 x 608 7.7 -> 5.8 us a call, 96 x 928 11.7 -> 9.5.  But a live
+// step of one workgroup per column has a launch of its own for its append: live iterations, with these lines at 640 from a
+// quarter and 1056 from 3/8 / as they are: 64 x 600 109.4 / 104.7, 96 x 900 153.5 / 148.0, 120 x 800 176.4 / 169.1.)
+inline int lone_workgroup_tokens(int64_t columns, int num_cu, int head_dim) {
   struct Line { int per32, tokens128, tokens64; };        // from that many 32nds of the compute units on
   constexpr Line lines[] = {{24, 3200, 3200}, {18, 2176, 3200}, {17, 1312, 3200}, {16, 1312, 2176},
                             {12, 800, 928}, {9, 544, 928}, {0, 448, 672}};

@@ -174,7 +174,7 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   // head dimension 64, window 128: 11.7 us with a merge, 5.5 without).
   const bool banded = !may_finish && d->window > 0 && d->kv_chunk_tokens == 0 &&
                       lone_workgroup_band(d->window, d->num_queries, max_len, chunk, lone_band_tokens(d->head_dim));
-  const bool finish = banded || (own_chunks && rows_per_head <= kDraftRows && max_len <= lone_workgroup_tokens(heads, num_cu, d->head_dim, d->head_dim == 128 && d->page_size == kPage));
+  const bool finish = banded || (own_chunks && rows_per_head <= kDraftRows && max_len <= lone_workgroup_tokens(heads, num_cu, d->head_dim));
   if (fine && own_chunks && !finish && rows_per_head <= kDraftRows && chunk == unit)
     chunk = draft_chunk_tokens(heads, num_cu, max_len, unit, rows_per_head * d->head_dim);
   // (A call that one workgroup per column finishes uses no partials; its workspace is sized for the chunked plan all
