@@ -100,13 +100,26 @@ constexpr int lone_band_tokens(int head_dim) { return head_dim == 64 ? 640 : 448
 // Waves of such a workgroup: a wave's second tile is a round trip behind its first, and a band of 128 tokens has five or six.  Eight
 // instead of four where the band can have more than four tiles (98 tokens; fewer lose the 0.2 to 0.3 us by which eight waves' rows are
 // merged later), every workgroup has a compute unit to itself (384 and more are a second round, 8.2 -> 9.8), and what a row block's
-// workgroups read in all is not itself the time (seen: tokens of the band).  us a call, captured, four waves / eight, window 64, 128, 256,
-// 400, 1000; head dimension 64, 16 sequences x 8 heads, 40 rows (256 workgroups): 4.8 / 5.1, 6.0 / 5.5, 6.8 / 6.6, 8.0 / 6.8, 11.9 / 10.9; one
-// sequence, 20 rows 4.4 / 4.6, 5.6 / 5.0, 6.4 / 5.9, 7.1 / 6.2; 32 of them 4.7 / 5.1, 5.9 / 5.4, 7.1 / 6.9, 8.1 / 7.8, 15.0 / 15.4; 128, 40 rows,
-// 16 sequences 6.2 / 6.4, 7.9 / 7.0, 9.4 / 8.7, 10.7 / 10.1, 17.0 / 17.6; 20 rows, 32 sequences 6.3 / 6.6, 8.0 / 7.6, 10.4 / 10.9, 12.9 / 13.2.
+// workgroups read in all is not itself the time (seen: tokens of the band).  us a call, captured, four waves / eight, window 128, 256,
+// 384, 512, 1000 (both end at a wave's last tile): head dimension 64, 16 sequences x 8 heads, 40 rows (256 workgroups) 6.1 / 5.5, 6.9 / 6.7, 7.7 / 6.7,
+// 8.5 / 7.9, 11.0 / 10.0; one sequence, 20 rows 5.8 / 5.4, 6.6 / 6.4, 7.3 / 6.4, 8.1 / 7.6, 10.2 / 9.2; 128, 8 sequences, 40 rows 7.6 / 7.1, 9.0 / 8.8,
+// 10.1 / 8.9, 11.1 / 10.7, 14.4 / 14.1.
+// A lone row block has K and V to itself, and one compute unit's way to memory is soon what counts.  Up to eleven tiles eight waves then gain
+// with five or six (160 tokens), or where there are many rows to merge at head dimension 64: 8 heads, window 150, 200, 320, 20 rows, 64 5.6 / 5.3,
+// 5.6 / 5.5, 6.4 / 6.3, but 16 rows 200 5.2 / 5.5; 128, 20 rows 7.0 / 6.7, 7.0 / 7.1, 8.2 / 8.3, and 16 sequences of 4 rows 256 7.0 / 7.4.  From
+// twelve on a wave of four has a third or fourth round trip (head dimension 128, 20 rows, 384, four sequences 9.9 / 9.0, eight 10.4 / 10.2;
+// 64, 4 rows, 440, eight 7.0 / 6.4), until the call reads enough for bandwidth to be what is left: 128, 20 rows, two of 630 (5.2 MB) 11.9 /
+// 11.1, four of 440 10.2 / 10.4, of 512 11.4 / 11.8, 12 rows, one of 1000 13.7 / 14.5; 8 rows, two of 630 11.1 / 12.0; 64, 40 rows of 8 heads, one of
+// 1000 10.2 / 8.7, 20 rows, two 10.0 / 10.0, three 10.8 / 11.2.
 constexpr int kBandWaves = 8;
-inline bool eight_wave_band(int64_t columns, int row_blocks, int num_cu, int64_t seen, int head_dim) {
-  return columns * row_blocks <= num_cu && seen > 97 && columns * seen * head_dim * 4 <= (int64_t{18} << 20) * row_blocks;
+inline bool eight_wave_band(int64_t columns, int row_blocks, int num_cu, int64_t seen, int head_dim, int rows) {
+  const int64_t bytes = columns * seen * head_dim * 4;
+  if (columns * row_blocks > num_cu || seen <= 97 || bytes > (int64_t{18} << 20) * row_blocks) return false;
+  if (row_blocks > 1) return true;
+  const bool half_lines = head_dim == 64, few = !half_lines && rows < 12;
+  if (seen <= 352) return seen <= 160 || (half_lines && rows > 16);
+  if (seen > 640) return half_lines && bytes <= (int64_t{5} << 19);
+  return half_lines || (!few && seen <= 420) || bytes <= (int64_t{5} << (few ? 19 : 20));
 }
 
 // Verification of more than 64 rows per KV head (with the two sum rows of the logit metric, and there of just above 32 as

@@ -181,7 +181,8 @@ int plan_split(const vegas_desc* d, int rows_per_head, int max_len, int collect,
   //  the same, so that these rules move neither the sizes callers allocate nor what the built-in scratch takes.)
   size_t slots = static_cast<size_t>(heads) * ((max_len + chunk - 1) / chunk);   // chunk partials the workspace holds
   if (finish) chunk = whole;
-  if (banded && eight_wave_band(heads, pl->NB, num_cu, std::min<int64_t>(static_cast<int64_t>(d->window) + d->num_queries - 1, max_len), d->head_dim))
+  if (banded && eight_wave_band(heads, pl->NB, num_cu, std::min<int64_t>(static_cast<int64_t>(d->window) + d->num_queries - 1, max_len), d->head_dim,
+                                rows_per_head))
     pl->NW = kBandWaves;
   pl->chunk = chunk;
   pl->nsplit = (max_len + chunk - 1) / chunk;

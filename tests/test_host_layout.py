@@ -291,3 +291,27 @@ def test_workgroups_alone_on_a_compute_unit_where_that_is_faster(tmp_path):
                 ((64, 800, 128), 0), ((64, 131072, 128), 0), ((33, 1 << 20, 128), 0)]
     out = run_host_program(tmp_path, ALONE, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
     assert [int(x) for x in out] == [s for _, s in measured]
+
+
+BAND_WAVES = r'''
+#include <cstdio>
+#include "plan_rules.hpp"
+int main() {                       // lines of: columns, row blocks, tokens of the band, head dimension, rows (256 compute units)
+  int columns, blocks, seen, D, rows;
+  while (std::scanf("%d %d %d %d %d", &columns, &blocks, &seen, &D, &rows) == 5)
+    std::printf("%d\n", vegas::eight_wave_band(columns, blocks, 256, seen, D, rows) ? 1 : 0);
+}
+'''
+
+
+def test_eight_waves_take_a_band_where_that_is_faster(tmp_path):
+    """(columns, row blocks, tokens of the band, head dimension, rows): eight waves measured faster than four, or not; with one row block of
+    head dimension 128 or of few rows they are slower than four from seven to eleven tiles, and where the call reads much."""
+    measured = [((8, 1, 97, 128, 20), 0), ((8, 1, 98, 128, 20), 1), ((8, 1, 132, 128, 20), 1), ((128, 1, 128, 64, 8), 1), ((8, 1, 204, 128, 20), 0),
+                ((8, 1, 260, 128, 20), 0), ((8, 1, 324, 128, 20), 0), ((8, 1, 388, 128, 20), 1), ((32, 1, 388, 128, 20), 1), ((32, 1, 444, 128, 20), 0),
+                ((16, 1, 634, 128, 20), 1), ((16, 1, 1004, 128, 20), 0), ((32, 1, 516, 128, 20), 0), ((16, 1, 630, 128, 8), 0), ((64, 1, 256, 128, 4), 0),
+                ((8, 1, 204, 64, 20), 1), ((8, 1, 324, 64, 20), 1), ((8, 1, 201, 64, 16), 0), ((32, 1, 440, 64, 4), 1), ((8, 1, 1004, 64, 20), 1),
+                ((24, 1, 1004, 64, 20), 0), ((8, 2, 204, 128, 40), 1), ((64, 2, 1004, 128, 40), 1), ((128, 2, 132, 64, 40), 1), ((129, 2, 132, 64, 40), 0),
+                ((256, 1, 132, 64, 20), 1), ((264, 1, 132, 64, 20), 0)]
+    out = run_host_program(tmp_path, BAND_WAVES, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
+    assert [int(x) for x in out] == [w for _, w in measured]
