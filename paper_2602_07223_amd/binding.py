@@ -136,9 +136,9 @@ def load_library(path: Optional[str] = None):
 
 
 # A kernel launch takes the host three microseconds, and small calls are over on the GPU in five, so Python's share counts: addresses
-# and streams that are plain integers already are not passed through _ptr and _stream, and a contiguous tensor's own size answers whether it is
-# large enough.  Host us, before / with that and the raw stream handle (harness): an iteration of 4096 tokens 42.6 / 33.8 (GPU 38),
-# of 32768 56 / 43, a verification of one launch 6.8 / 4.5 (7.3 -> 6.4 a call), a draft call on tensors 15.1 / 11.4.
+# and streams that are plain integers already are not passed through _ptr and _stream.  Host us, before / with that and the raw stream
+# handle (harness): an iteration of 4096 tokens 42.6 / 33.8 (GPU 38), of 32768 56 / 43, a verification of one launch 6.8 / 4.5 (7.3 ->
+# 6.4 a call).
 def _ptr(x) -> Optional[int]:
     if x is None:
         return None
@@ -153,7 +153,8 @@ def _nbytes(x) -> int:
 
 def _avail_bytes(x) -> int:
     """Bytes from a tensor's first element to the end of its storage (what a kernel may address through it)."""
-    return int(x.untyped_storage().nbytes()) - int(x.storage_offset()) * int(x.element_size())
+    have, first = x.untyped_storage().nbytes(), x.storage_offset()
+    return have - first * x.element_size() if first else have
 
 
 def cache_extent_bytes(desc: "VegasDesc") -> int:
@@ -169,10 +170,9 @@ def _fits(where: str, name: str, x, nbytes: int) -> Optional[int]:
     passed, refuse any that is smaller than what the descriptor lets the kernels touch.  Returns the address."""
     if x is None or isinstance(x, int):
         return x
-    if not (x.is_contiguous() and x.nbytes >= nbytes):  # (its own elements are enough, whatever its storage holds besides)
-        have = _avail_bytes(x)
-        if have < nbytes:
-            raise ValueError(f"{where}: {name} spans {have} bytes, the descriptor needs {nbytes}")
+    have = _avail_bytes(x)                          # (the storage's: it may have been resized under a tensor that still has its shape)
+    if have < nbytes:
+        raise ValueError(f"{where}: {name} spans {have} bytes, the descriptor needs {nbytes}")
     return x.data_ptr()
 
 

@@ -273,6 +273,23 @@ def test_binding_refuses_tensors_smaller_than_the_descriptor():
     assert vb._avail_bytes(view[1:]) < vb.cache_extent_bytes(dv)
 
 
+@pytest.mark.parametrize("left", [0, 256])
+def test_binding_refuses_tensors_whose_storage_was_resized(left):
+    """A tensor keeps its shape when its storage is released or shrunk (resize_, as parameter sharding does): what it spans is
+    the storage's, not the shape's."""
+    import torch
+    d = good_desc(batch=2, max_blocks=8, max_sel_blocks=4, max_seq_len=100, num_pages=10)
+    q = torch.zeros((2, 32, 128), dtype=torch.bfloat16)
+    cache, gone = (torch.zeros((10, 16, 8, 128), dtype=torch.bfloat16) for _ in range(2))
+    sel, lens = torch.zeros((2, 4), dtype=torch.int32), torch.zeros((2,), dtype=torch.int32)
+    gone.untyped_storage().resize_(left)
+    assert gone.is_contiguous() and gone.nbytes >= vb.cache_extent_bytes(d)
+    with pytest.raises(ValueError, match="k_cache spans %d bytes" % left):
+        vb.vegas_draft_attention(d, q, gone, cache, sel, lens, torch.zeros_like(q), None)
+    with pytest.raises(ValueError, match="v_cache spans %d bytes" % left):
+        vb.vegas_draft_attention(d, q, cache, gone, sel, lens, torch.zeros_like(q), None)
+
+
 def test_bench_refuses_more_than_one_gpu():
     """This build runs on one GPU; bench.py says so and exits before touching a device."""
     import subprocess
