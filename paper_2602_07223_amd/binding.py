@@ -226,29 +226,31 @@ def vegas_verify_attention(desc: VegasDesc, q, k_cache, v_cache, block_table, se
                            workspace, stream=None, workspace_bytes: Optional[int] = None, stages: int = 0) -> None:
     """stages != 0: vegas_debug_verify_attention_stages (a profiling aid: only those kernels of the call)."""
     wb = workspace_bytes if workspace_bytes is not None else (_nbytes(workspace) if workspace is not None else 0)
+    q_at, k_cache_at, v_cache_at, block_table_at, seq_lens_at = q, k_cache, v_cache, block_table, seq_lens
+    out_at, block_scores_at, workspace_at, stream_at = out, block_scores, workspace, stream
     if not (isinstance(q, int) and isinstance(k_cache, int)):      # raw addresses: the caller has checked (harness)
         d = desc
         rows = d.batch * d.num_queries * d.num_q_heads * d.head_dim * 2
         extent = cache_extent_bytes(d)
         per_page = 16 if d.score_metric == METRIC_TOKEN_LOGITS else 1
-        q = _fits("vegas_verify_attention", "q", q, rows)
-        out = _fits("vegas_verify_attention", "out", out, rows)
-        k_cache = _fits("vegas_verify_attention", "k_cache", k_cache, extent)
-        v_cache = _fits("vegas_verify_attention", "v_cache", v_cache, extent)
-        block_table = _fits("vegas_verify_attention", "block_table", block_table, d.batch * d.max_blocks * 4)
-        seq_lens = _fits("vegas_verify_attention", "seq_lens", seq_lens, d.batch * 4)
+        q_at = _fits("vegas_verify_attention", "q", q, rows)
+        out_at = _fits("vegas_verify_attention", "out", out, rows)
+        k_cache_at = _fits("vegas_verify_attention", "k_cache", k_cache, extent)
+        v_cache_at = _fits("vegas_verify_attention", "v_cache", v_cache, extent)
+        block_table_at = _fits("vegas_verify_attention", "block_table", block_table, d.batch * d.max_blocks * 4)
+        seq_lens_at = _fits("vegas_verify_attention", "seq_lens", seq_lens, d.batch * 4)
         if d.collect_rows != COLLECT_NONE:
-            block_scores = _fits("vegas_verify_attention", "block_scores", block_scores, d.batch * d.max_blocks * per_page * 4)
-    if type(q) is not int: q = _ptr(q)
-    if type(k_cache) is not int: k_cache = _ptr(k_cache)
-    if type(v_cache) is not int: v_cache = _ptr(v_cache)
-    if type(block_table) is not int: block_table = _ptr(block_table)
-    if type(seq_lens) is not int: seq_lens = _ptr(seq_lens)
-    if type(out) is not int: out = _ptr(out)
-    if type(block_scores) is not int: block_scores = _ptr(block_scores)
-    if type(workspace) is not int: workspace = _ptr(workspace)
-    if type(stream) is not int: stream = _stream(stream)
-    args = (_byref(desc), q, k_cache, v_cache, block_table, seq_lens, out, block_scores, workspace, wb, stream)
+            block_scores_at = _fits("vegas_verify_attention", "block_scores", block_scores, d.batch * d.max_blocks * per_page * 4)
+    if type(q_at) is not int: q_at = _ptr(q_at)
+    if type(k_cache_at) is not int: k_cache_at = _ptr(k_cache_at)
+    if type(v_cache_at) is not int: v_cache_at = _ptr(v_cache_at)
+    if type(block_table_at) is not int: block_table_at = _ptr(block_table_at)
+    if type(seq_lens_at) is not int: seq_lens_at = _ptr(seq_lens_at)
+    if type(out_at) is not int: out_at = _ptr(out_at)
+    if type(block_scores_at) is not int: block_scores_at = _ptr(block_scores_at)
+    if type(workspace_at) is not int: workspace_at = _ptr(workspace_at)
+    if type(stream_at) is not int: stream_at = _stream(stream_at)
+    args = (_byref(desc), q_at, k_cache_at, v_cache_at, block_table_at, seq_lens_at, out_at, block_scores_at, workspace_at, wb, stream_at)
     if stages:
         rc = (_lib or load_library()).vegas_debug_verify_attention_stages(*args, int(stages))
     else:
@@ -260,24 +262,26 @@ def vegas_verify_attention(desc: VegasDesc, q, k_cache, v_cache, block_table, se
 def vegas_select_blocks(desc: VegasDesc, block_scores, block_table, seq_lens, budget_tokens: int, sel_table,
                         sel_seq_lens, budgets=None, workspace=None, stream=None) -> None:
     wb = _nbytes(workspace) if workspace is not None and not isinstance(workspace, int) else 0
+    block_scores_at, block_table_at, seq_lens_at, budgets_at = block_scores, block_table, seq_lens, budgets
+    sel_table_at, sel_seq_lens_at, workspace_at, stream_at = sel_table, sel_seq_lens, workspace, stream
     if not (isinstance(block_scores, int) and isinstance(sel_table, int)):
         d = desc
-        block_scores = _fits("vegas_select_blocks", "block_scores", block_scores, d.batch * d.max_blocks * 4)
-        block_table = _fits("vegas_select_blocks", "block_table", block_table, d.batch * d.max_blocks * 4)
-        seq_lens = _fits("vegas_select_blocks", "seq_lens", seq_lens, d.batch * 4)
-        budgets = _fits("vegas_select_blocks", "budgets", budgets, d.batch * 4)
-        sel_table = _fits("vegas_select_blocks", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
-        sel_seq_lens = _fits("vegas_select_blocks", "sel_seq_lens", sel_seq_lens, d.batch * 4)
-    if type(block_scores) is not int: block_scores = _ptr(block_scores)
-    if type(block_table) is not int: block_table = _ptr(block_table)
-    if type(seq_lens) is not int: seq_lens = _ptr(seq_lens)
-    if type(budgets) is not int: budgets = _ptr(budgets)
-    if type(sel_table) is not int: sel_table = _ptr(sel_table)
-    if type(sel_seq_lens) is not int: sel_seq_lens = _ptr(sel_seq_lens)
-    if type(workspace) is not int: workspace = _ptr(workspace)
-    if type(stream) is not int: stream = _stream(stream)
-    rc = (_lib or load_library()).vegas_select_blocks(_byref(desc), block_scores, block_table, seq_lens, int(budget_tokens), budgets, sel_table,
-        sel_seq_lens, workspace, wb, stream)
+        block_scores_at = _fits("vegas_select_blocks", "block_scores", block_scores, d.batch * d.max_blocks * 4)
+        block_table_at = _fits("vegas_select_blocks", "block_table", block_table, d.batch * d.max_blocks * 4)
+        seq_lens_at = _fits("vegas_select_blocks", "seq_lens", seq_lens, d.batch * 4)
+        budgets_at = _fits("vegas_select_blocks", "budgets", budgets, d.batch * 4)
+        sel_table_at = _fits("vegas_select_blocks", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
+        sel_seq_lens_at = _fits("vegas_select_blocks", "sel_seq_lens", sel_seq_lens, d.batch * 4)
+    if type(block_scores_at) is not int: block_scores_at = _ptr(block_scores_at)
+    if type(block_table_at) is not int: block_table_at = _ptr(block_table_at)
+    if type(seq_lens_at) is not int: seq_lens_at = _ptr(seq_lens_at)
+    if type(budgets_at) is not int: budgets_at = _ptr(budgets_at)
+    if type(sel_table_at) is not int: sel_table_at = _ptr(sel_table_at)
+    if type(sel_seq_lens_at) is not int: sel_seq_lens_at = _ptr(sel_seq_lens_at)
+    if type(workspace_at) is not int: workspace_at = _ptr(workspace_at)
+    if type(stream_at) is not int: stream_at = _stream(stream_at)
+    rc = (_lib or load_library()).vegas_select_blocks(_byref(desc), block_scores_at, block_table_at, seq_lens_at, int(budget_tokens), budgets_at, sel_table_at,
+        sel_seq_lens_at, workspace_at, wb, stream_at)
     if rc != VEGAS_OK:
         raise VegasError(rc, "vegas_select_blocks")
 
@@ -285,95 +289,102 @@ def vegas_select_blocks(desc: VegasDesc, block_scores, block_table, seq_lens, bu
 def vegas_select_tokens(desc: VegasDesc, token_scores, block_table, seq_lens, budget_tokens: int, sel_table,
                         sel_seq_lens, workspace, budgets=None, stream=None, workspace_bytes: Optional[int] = None) -> None:
     wb = workspace_bytes if workspace_bytes is not None else (_nbytes(workspace) if workspace is not None else 0)
+    token_scores_at, block_table_at, seq_lens_at, budgets_at = token_scores, block_table, seq_lens, budgets
+    sel_table_at, sel_seq_lens_at, workspace_at, stream_at = sel_table, sel_seq_lens, workspace, stream
     if not (isinstance(token_scores, int) and isinstance(sel_table, int)):
         d = desc
-        token_scores = _fits("vegas_select_tokens", "token_scores", token_scores, d.batch * d.max_blocks * 16 * 4)
-        block_table = _fits("vegas_select_tokens", "block_table", block_table, d.batch * d.max_blocks * 4)
-        seq_lens = _fits("vegas_select_tokens", "seq_lens", seq_lens, d.batch * 4)
-        budgets = _fits("vegas_select_tokens", "budgets", budgets, d.batch * 4)
-        sel_table = _fits("vegas_select_tokens", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
-        sel_seq_lens = _fits("vegas_select_tokens", "sel_seq_lens", sel_seq_lens, d.batch * 4)
-    if type(token_scores) is not int: token_scores = _ptr(token_scores)
-    if type(block_table) is not int: block_table = _ptr(block_table)
-    if type(seq_lens) is not int: seq_lens = _ptr(seq_lens)
-    if type(budgets) is not int: budgets = _ptr(budgets)
-    if type(sel_table) is not int: sel_table = _ptr(sel_table)
-    if type(sel_seq_lens) is not int: sel_seq_lens = _ptr(sel_seq_lens)
-    if type(workspace) is not int: workspace = _ptr(workspace)
-    if type(stream) is not int: stream = _stream(stream)
-    rc = (_lib or load_library()).vegas_select_tokens(_byref(desc), token_scores, block_table, seq_lens, int(budget_tokens), budgets, sel_table,
-        sel_seq_lens, workspace, wb, stream)
+        token_scores_at = _fits("vegas_select_tokens", "token_scores", token_scores, d.batch * d.max_blocks * 16 * 4)
+        block_table_at = _fits("vegas_select_tokens", "block_table", block_table, d.batch * d.max_blocks * 4)
+        seq_lens_at = _fits("vegas_select_tokens", "seq_lens", seq_lens, d.batch * 4)
+        budgets_at = _fits("vegas_select_tokens", "budgets", budgets, d.batch * 4)
+        sel_table_at = _fits("vegas_select_tokens", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
+        sel_seq_lens_at = _fits("vegas_select_tokens", "sel_seq_lens", sel_seq_lens, d.batch * 4)
+    if type(token_scores_at) is not int: token_scores_at = _ptr(token_scores_at)
+    if type(block_table_at) is not int: block_table_at = _ptr(block_table_at)
+    if type(seq_lens_at) is not int: seq_lens_at = _ptr(seq_lens_at)
+    if type(budgets_at) is not int: budgets_at = _ptr(budgets_at)
+    if type(sel_table_at) is not int: sel_table_at = _ptr(sel_table_at)
+    if type(sel_seq_lens_at) is not int: sel_seq_lens_at = _ptr(sel_seq_lens_at)
+    if type(workspace_at) is not int: workspace_at = _ptr(workspace_at)
+    if type(stream_at) is not int: stream_at = _stream(stream_at)
+    rc = (_lib or load_library()).vegas_select_tokens(_byref(desc), token_scores_at, block_table_at, seq_lens_at, int(budget_tokens), budgets_at, sel_table_at,
+        sel_seq_lens_at, workspace_at, wb, stream_at)
     if rc != VEGAS_OK:
         raise VegasError(rc, "vegas_select_tokens")
 
 
 def vegas_append_kv(desc: VegasDesc, k_new, v_new, num_new: int, block_table, seq_lens, k_cache, v_cache,
                     stream=None) -> None:
+    k_new_at, v_new_at, block_table_at, seq_lens_at = k_new, v_new, block_table, seq_lens
+    k_cache_at, v_cache_at, stream_at = k_cache, v_cache, stream
     if not (isinstance(k_new, int) and isinstance(k_cache, int)):
         d = desc
         rows = d.batch * int(num_new) * d.num_kv_heads * d.head_dim * 2
         extent = cache_extent_bytes(d)
-        k_new = _fits("vegas_append_kv", "k_new", k_new, rows)
-        v_new = _fits("vegas_append_kv", "v_new", v_new, rows)
-        k_cache = _fits("vegas_append_kv", "k_cache", k_cache, extent)
-        v_cache = _fits("vegas_append_kv", "v_cache", v_cache, extent)
-        block_table = _fits("vegas_append_kv", "block_table", block_table, d.batch * d.max_blocks * 4)
-        seq_lens = _fits("vegas_append_kv", "seq_lens", seq_lens, d.batch * 4)
-    if type(k_new) is not int: k_new = _ptr(k_new)
-    if type(v_new) is not int: v_new = _ptr(v_new)
-    if type(block_table) is not int: block_table = _ptr(block_table)
-    if type(seq_lens) is not int: seq_lens = _ptr(seq_lens)
-    if type(k_cache) is not int: k_cache = _ptr(k_cache)
-    if type(v_cache) is not int: v_cache = _ptr(v_cache)
-    if type(stream) is not int: stream = _stream(stream)
-    rc = (_lib or load_library()).vegas_append_kv(_byref(desc), k_new, v_new, int(num_new), block_table, seq_lens, k_cache, v_cache, stream)
+        k_new_at = _fits("vegas_append_kv", "k_new", k_new, rows)
+        v_new_at = _fits("vegas_append_kv", "v_new", v_new, rows)
+        k_cache_at = _fits("vegas_append_kv", "k_cache", k_cache, extent)
+        v_cache_at = _fits("vegas_append_kv", "v_cache", v_cache, extent)
+        block_table_at = _fits("vegas_append_kv", "block_table", block_table, d.batch * d.max_blocks * 4)
+        seq_lens_at = _fits("vegas_append_kv", "seq_lens", seq_lens, d.batch * 4)
+    if type(k_new_at) is not int: k_new_at = _ptr(k_new_at)
+    if type(v_new_at) is not int: v_new_at = _ptr(v_new_at)
+    if type(block_table_at) is not int: block_table_at = _ptr(block_table_at)
+    if type(seq_lens_at) is not int: seq_lens_at = _ptr(seq_lens_at)
+    if type(k_cache_at) is not int: k_cache_at = _ptr(k_cache_at)
+    if type(v_cache_at) is not int: v_cache_at = _ptr(v_cache_at)
+    if type(stream_at) is not int: stream_at = _stream(stream_at)
+    rc = (_lib or load_library()).vegas_append_kv(_byref(desc), k_new_at, v_new_at, int(num_new), block_table_at, seq_lens_at, k_cache_at, v_cache_at, stream_at)
     if rc != VEGAS_OK:
         raise VegasError(rc, "vegas_append_kv")
 
 
 def vegas_append_kv_extend(desc: VegasDesc, k_new, v_new, num_new: int, block_table, seq_lens, k_cache, v_cache,
                            sel_table, sel_seq_lens, sel_page_size: int, stream=None) -> None:
+    k_new_at, v_new_at, block_table_at, seq_lens_at, k_cache_at = k_new, v_new, block_table, seq_lens, k_cache
+    v_cache_at, sel_table_at, sel_seq_lens_at, stream_at = v_cache, sel_table, sel_seq_lens, stream
     if not (isinstance(k_new, int) and isinstance(k_cache, int)):
         d = desc
         rows = d.batch * int(num_new) * d.num_kv_heads * d.head_dim * 2
         extent = cache_extent_bytes(d)
-        k_new = _fits("vegas_append_kv_extend", "k_new", k_new, rows)
-        v_new = _fits("vegas_append_kv_extend", "v_new", v_new, rows)
-        k_cache = _fits("vegas_append_kv_extend", "k_cache", k_cache, extent)
-        v_cache = _fits("vegas_append_kv_extend", "v_cache", v_cache, extent)
-        block_table = _fits("vegas_append_kv_extend", "block_table", block_table, d.batch * d.max_blocks * 4)
-        seq_lens = _fits("vegas_append_kv_extend", "seq_lens", seq_lens, d.batch * 4)
-        sel_table = _fits("vegas_append_kv_extend", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
-        sel_seq_lens = _fits("vegas_append_kv_extend", "sel_seq_lens", sel_seq_lens, d.batch * 4)
-    if type(k_new) is not int: k_new = _ptr(k_new)
-    if type(v_new) is not int: v_new = _ptr(v_new)
-    if type(block_table) is not int: block_table = _ptr(block_table)
-    if type(seq_lens) is not int: seq_lens = _ptr(seq_lens)
-    if type(k_cache) is not int: k_cache = _ptr(k_cache)
-    if type(v_cache) is not int: v_cache = _ptr(v_cache)
-    if type(sel_table) is not int: sel_table = _ptr(sel_table)
-    if type(sel_seq_lens) is not int: sel_seq_lens = _ptr(sel_seq_lens)
-    if type(stream) is not int: stream = _stream(stream)
+        k_new_at = _fits("vegas_append_kv_extend", "k_new", k_new, rows)
+        v_new_at = _fits("vegas_append_kv_extend", "v_new", v_new, rows)
+        k_cache_at = _fits("vegas_append_kv_extend", "k_cache", k_cache, extent)
+        v_cache_at = _fits("vegas_append_kv_extend", "v_cache", v_cache, extent)
+        block_table_at = _fits("vegas_append_kv_extend", "block_table", block_table, d.batch * d.max_blocks * 4)
+        seq_lens_at = _fits("vegas_append_kv_extend", "seq_lens", seq_lens, d.batch * 4)
+        sel_table_at = _fits("vegas_append_kv_extend", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
+        sel_seq_lens_at = _fits("vegas_append_kv_extend", "sel_seq_lens", sel_seq_lens, d.batch * 4)
+    if type(k_new_at) is not int: k_new_at = _ptr(k_new_at)
+    if type(v_new_at) is not int: v_new_at = _ptr(v_new_at)
+    if type(block_table_at) is not int: block_table_at = _ptr(block_table_at)
+    if type(seq_lens_at) is not int: seq_lens_at = _ptr(seq_lens_at)
+    if type(k_cache_at) is not int: k_cache_at = _ptr(k_cache_at)
+    if type(v_cache_at) is not int: v_cache_at = _ptr(v_cache_at)
+    if type(sel_table_at) is not int: sel_table_at = _ptr(sel_table_at)
+    if type(sel_seq_lens_at) is not int: sel_seq_lens_at = _ptr(sel_seq_lens_at)
+    if type(stream_at) is not int: stream_at = _stream(stream_at)
     rc = (_lib or load_library()).vegas_append_kv_extend(
-        _byref(desc), k_new, v_new, int(num_new), block_table, seq_lens, k_cache, v_cache, sel_table, sel_seq_lens, int(sel_page_size), stream)
+        _byref(desc), k_new_at, v_new_at, int(num_new), block_table_at, seq_lens_at, k_cache_at, v_cache_at, sel_table_at, sel_seq_lens_at, int(sel_page_size), stream_at)
     if rc != VEGAS_OK:
         raise VegasError(rc, "vegas_append_kv_extend")
 
 
 def vegas_extend_selection(desc: VegasDesc, block_table, seq_lens, num_new: int, sel_table, sel_seq_lens,
                            stream=None) -> None:
+    block_table_at, seq_lens_at, sel_table_at, sel_seq_lens_at, stream_at = block_table, seq_lens, sel_table, sel_seq_lens, stream
     if not (isinstance(block_table, int) and isinstance(sel_table, int)):
         d = desc
-        block_table = _fits("vegas_extend_selection", "block_table", block_table, d.batch * d.max_blocks * 4)
-        seq_lens = _fits("vegas_extend_selection", "seq_lens", seq_lens, d.batch * 4)
-        sel_table = _fits("vegas_extend_selection", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
-        sel_seq_lens = _fits("vegas_extend_selection", "sel_seq_lens", sel_seq_lens, d.batch * 4)
-    if type(block_table) is not int: block_table = _ptr(block_table)
-    if type(seq_lens) is not int: seq_lens = _ptr(seq_lens)
-    if type(sel_table) is not int: sel_table = _ptr(sel_table)
-    if type(sel_seq_lens) is not int: sel_seq_lens = _ptr(sel_seq_lens)
-    if type(stream) is not int: stream = _stream(stream)
-    rc = (_lib or load_library()).vegas_extend_selection(_byref(desc), block_table, seq_lens, int(num_new), sel_table, sel_seq_lens, stream)
+        block_table_at = _fits("vegas_extend_selection", "block_table", block_table, d.batch * d.max_blocks * 4)
+        seq_lens_at = _fits("vegas_extend_selection", "seq_lens", seq_lens, d.batch * 4)
+        sel_table_at = _fits("vegas_extend_selection", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
+        sel_seq_lens_at = _fits("vegas_extend_selection", "sel_seq_lens", sel_seq_lens, d.batch * 4)
+    if type(block_table_at) is not int: block_table_at = _ptr(block_table_at)
+    if type(seq_lens_at) is not int: seq_lens_at = _ptr(seq_lens_at)
+    if type(sel_table_at) is not int: sel_table_at = _ptr(sel_table_at)
+    if type(sel_seq_lens_at) is not int: sel_seq_lens_at = _ptr(sel_seq_lens_at)
+    if type(stream_at) is not int: stream_at = _stream(stream_at)
+    rc = (_lib or load_library()).vegas_extend_selection(_byref(desc), block_table_at, seq_lens_at, int(num_new), sel_table_at, sel_seq_lens_at, stream_at)
     if rc != VEGAS_OK:
         raise VegasError(rc, "vegas_extend_selection")
 
@@ -382,25 +393,27 @@ def vegas_draft_attention(desc: VegasDesc, q, k_cache, v_cache, sel_table, sel_s
                           stream=None, workspace_bytes: Optional[int] = None, stages: int = 0) -> None:
     """stages != 0: vegas_debug_draft_attention_stages (a profiling aid: only those kernels of the call)."""
     wb = workspace_bytes if workspace_bytes is not None else (_nbytes(workspace) if workspace is not None else 0)
+    q_at, k_cache_at, v_cache_at, sel_table_at = q, k_cache, v_cache, sel_table
+    sel_seq_lens_at, out_at, workspace_at, stream_at = sel_seq_lens, out, workspace, stream
     if not (isinstance(q, int) and isinstance(k_cache, int)):
         d = desc
         rows = d.batch * d.num_q_heads * d.head_dim * 2
         extent = cache_extent_bytes(d)
-        q = _fits("vegas_draft_attention", "q", q, rows)
-        out = _fits("vegas_draft_attention", "out", out, rows)
-        k_cache = _fits("vegas_draft_attention", "k_cache", k_cache, extent)
-        v_cache = _fits("vegas_draft_attention", "v_cache", v_cache, extent)
-        sel_table = _fits("vegas_draft_attention", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
-        sel_seq_lens = _fits("vegas_draft_attention", "sel_seq_lens", sel_seq_lens, d.batch * 4)
-    if type(q) is not int: q = _ptr(q)
-    if type(k_cache) is not int: k_cache = _ptr(k_cache)
-    if type(v_cache) is not int: v_cache = _ptr(v_cache)
-    if type(sel_table) is not int: sel_table = _ptr(sel_table)
-    if type(sel_seq_lens) is not int: sel_seq_lens = _ptr(sel_seq_lens)
-    if type(out) is not int: out = _ptr(out)
-    if type(workspace) is not int: workspace = _ptr(workspace)
-    if type(stream) is not int: stream = _stream(stream)
-    args = (_byref(desc), q, k_cache, v_cache, sel_table, sel_seq_lens, out, workspace, wb, stream)
+        q_at = _fits("vegas_draft_attention", "q", q, rows)
+        out_at = _fits("vegas_draft_attention", "out", out, rows)
+        k_cache_at = _fits("vegas_draft_attention", "k_cache", k_cache, extent)
+        v_cache_at = _fits("vegas_draft_attention", "v_cache", v_cache, extent)
+        sel_table_at = _fits("vegas_draft_attention", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
+        sel_seq_lens_at = _fits("vegas_draft_attention", "sel_seq_lens", sel_seq_lens, d.batch * 4)
+    if type(q_at) is not int: q_at = _ptr(q_at)
+    if type(k_cache_at) is not int: k_cache_at = _ptr(k_cache_at)
+    if type(v_cache_at) is not int: v_cache_at = _ptr(v_cache_at)
+    if type(sel_table_at) is not int: sel_table_at = _ptr(sel_table_at)
+    if type(sel_seq_lens_at) is not int: sel_seq_lens_at = _ptr(sel_seq_lens_at)
+    if type(out_at) is not int: out_at = _ptr(out_at)
+    if type(workspace_at) is not int: workspace_at = _ptr(workspace_at)
+    if type(stream_at) is not int: stream_at = _stream(stream_at)
+    args = (_byref(desc), q_at, k_cache_at, v_cache_at, sel_table_at, sel_seq_lens_at, out_at, workspace_at, wb, stream_at)
     if stages:
         rc = (_lib or load_library()).vegas_debug_draft_attention_stages(*args, int(stages))
     else:
@@ -413,35 +426,37 @@ def vegas_draft_step(cache_desc: VegasDesc, desc: VegasDesc, q, k_new, v_new, bl
                      sel_seq_lens, out, workspace, stream=None, workspace_bytes: Optional[int] = None) -> None:
     """vegas_append_kv_extend of one token (cache_desc) and vegas_draft_attention (desc) in one call (see include/vegas.h)."""
     wb = workspace_bytes if workspace_bytes is not None else (_nbytes(workspace) if workspace is not None else 0)
+    q_at, k_new_at, v_new_at, block_table_at, seq_lens_at, k_cache_at = q, k_new, v_new, block_table, seq_lens, k_cache
+    v_cache_at, sel_table_at, sel_seq_lens_at, out_at, workspace_at, stream_at = v_cache, sel_table, sel_seq_lens, out, workspace, stream
     if not (isinstance(q, int) and isinstance(k_cache, int)):
         d, c = desc, cache_desc
         rows, new = d.batch * d.num_q_heads * d.head_dim * 2, c.batch * c.num_kv_heads * c.head_dim * 2
         extent = max(cache_extent_bytes(d), cache_extent_bytes(c))
-        q = _fits("vegas_draft_step", "q", q, rows)
-        out = _fits("vegas_draft_step", "out", out, rows)
-        k_new = _fits("vegas_draft_step", "k_new", k_new, new)
-        v_new = _fits("vegas_draft_step", "v_new", v_new, new)
-        k_cache = _fits("vegas_draft_step", "k_cache", k_cache, extent)
-        v_cache = _fits("vegas_draft_step", "v_cache", v_cache, extent)
-        block_table = _fits("vegas_draft_step", "block_table", block_table, c.batch * c.max_blocks * 4)
-        seq_lens = _fits("vegas_draft_step", "seq_lens", seq_lens, c.batch * 4)
-        sel_table = _fits("vegas_draft_step", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
-        sel_seq_lens = _fits("vegas_draft_step", "sel_seq_lens", sel_seq_lens, d.batch * 4)
-    if type(q) is not int: q = _ptr(q)
-    if type(k_new) is not int: k_new = _ptr(k_new)
-    if type(v_new) is not int: v_new = _ptr(v_new)
-    if type(block_table) is not int: block_table = _ptr(block_table)
-    if type(seq_lens) is not int: seq_lens = _ptr(seq_lens)
-    if type(k_cache) is not int: k_cache = _ptr(k_cache)
-    if type(v_cache) is not int: v_cache = _ptr(v_cache)
-    if type(sel_table) is not int: sel_table = _ptr(sel_table)
-    if type(sel_seq_lens) is not int: sel_seq_lens = _ptr(sel_seq_lens)
-    if type(out) is not int: out = _ptr(out)
-    if type(workspace) is not int: workspace = _ptr(workspace)
-    if type(stream) is not int: stream = _stream(stream)
+        q_at = _fits("vegas_draft_step", "q", q, rows)
+        out_at = _fits("vegas_draft_step", "out", out, rows)
+        k_new_at = _fits("vegas_draft_step", "k_new", k_new, new)
+        v_new_at = _fits("vegas_draft_step", "v_new", v_new, new)
+        k_cache_at = _fits("vegas_draft_step", "k_cache", k_cache, extent)
+        v_cache_at = _fits("vegas_draft_step", "v_cache", v_cache, extent)
+        block_table_at = _fits("vegas_draft_step", "block_table", block_table, c.batch * c.max_blocks * 4)
+        seq_lens_at = _fits("vegas_draft_step", "seq_lens", seq_lens, c.batch * 4)
+        sel_table_at = _fits("vegas_draft_step", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
+        sel_seq_lens_at = _fits("vegas_draft_step", "sel_seq_lens", sel_seq_lens, d.batch * 4)
+    if type(q_at) is not int: q_at = _ptr(q_at)
+    if type(k_new_at) is not int: k_new_at = _ptr(k_new_at)
+    if type(v_new_at) is not int: v_new_at = _ptr(v_new_at)
+    if type(block_table_at) is not int: block_table_at = _ptr(block_table_at)
+    if type(seq_lens_at) is not int: seq_lens_at = _ptr(seq_lens_at)
+    if type(k_cache_at) is not int: k_cache_at = _ptr(k_cache_at)
+    if type(v_cache_at) is not int: v_cache_at = _ptr(v_cache_at)
+    if type(sel_table_at) is not int: sel_table_at = _ptr(sel_table_at)
+    if type(sel_seq_lens_at) is not int: sel_seq_lens_at = _ptr(sel_seq_lens_at)
+    if type(out_at) is not int: out_at = _ptr(out_at)
+    if type(workspace_at) is not int: workspace_at = _ptr(workspace_at)
+    if type(stream_at) is not int: stream_at = _stream(stream_at)
     rc = (_lib or load_library()).vegas_draft_step(
-        _byref(cache_desc), _byref(desc), q, k_new, v_new, block_table, seq_lens, k_cache, v_cache, sel_table, sel_seq_lens,
-        out, workspace, wb, stream)
+        _byref(cache_desc), _byref(desc), q_at, k_new_at, v_new_at, block_table_at, seq_lens_at, k_cache_at, v_cache_at, sel_table_at, sel_seq_lens_at,
+        out_at, workspace_at, wb, stream_at)
     if rc != VEGAS_OK:
         raise VegasError(rc, "vegas_draft_step")
 
@@ -452,31 +467,33 @@ def vegas_static_scratch_bytes() -> int:
 
 def vegas_draft_attention_static(desc: VegasDesc, q, k_cache, v_cache, sel_table, sel_seq_lens, out, stream=None) -> None:
     """vegas_draft_attention without a workspace argument: the library's built-in scratch array is used."""
+    q_at, out_at, k_cache_at, v_cache_at, sel_table_at, sel_seq_lens_at = q, out, k_cache, v_cache, sel_table, sel_seq_lens
     if not (isinstance(q, int) and isinstance(k_cache, int)):
         d = desc
         rows = d.batch * d.num_q_heads * d.head_dim * 2
         extent = cache_extent_bytes(d)
-        q = _fits("vegas_draft_attention_static", "q", q, rows)
-        out = _fits("vegas_draft_attention_static", "out", out, rows)
-        k_cache = _fits("vegas_draft_attention_static", "k_cache", k_cache, extent)
-        v_cache = _fits("vegas_draft_attention_static", "v_cache", v_cache, extent)
-        sel_table = _fits("vegas_draft_attention_static", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
-        sel_seq_lens = _fits("vegas_draft_attention_static", "sel_seq_lens", sel_seq_lens, d.batch * 4)
-    rc = load_library().vegas_draft_attention_static(ctypes.byref(desc), _ptr(q), _ptr(k_cache), _ptr(v_cache),
-                                                     _ptr(sel_table), _ptr(sel_seq_lens), _ptr(out), _stream(stream))
+        q_at = _fits("vegas_draft_attention_static", "q", q, rows)
+        out_at = _fits("vegas_draft_attention_static", "out", out, rows)
+        k_cache_at = _fits("vegas_draft_attention_static", "k_cache", k_cache, extent)
+        v_cache_at = _fits("vegas_draft_attention_static", "v_cache", v_cache, extent)
+        sel_table_at = _fits("vegas_draft_attention_static", "sel_table", sel_table, d.batch * d.max_sel_blocks * 4)
+        sel_seq_lens_at = _fits("vegas_draft_attention_static", "sel_seq_lens", sel_seq_lens, d.batch * 4)
+    rc = load_library().vegas_draft_attention_static(ctypes.byref(desc), _ptr(q_at), _ptr(k_cache_at), _ptr(v_cache_at),
+                                                     _ptr(sel_table_at), _ptr(sel_seq_lens_at), _ptr(out_at), _stream(stream))
     if rc != VEGAS_OK:
         raise VegasError(rc, "vegas_draft_attention_static")
 
 
 def vegas_debug_check_tables(desc: VegasDesc, which: int, table, lens, error_word, stream=None) -> None:
     """ORs VEGAS_CHECK_* bits for out-of-range lengths and page ids into the device word (see include/vegas.h)."""
+    table_at, lens_at, error_word_at = table, lens, error_word
     if not isinstance(table, int):
         stride = desc.max_blocks if which == TABLE_BLOCKS else desc.max_sel_blocks
-        table = _fits("vegas_debug_check_tables", "table", table, desc.batch * stride * 4)
-        lens = _fits("vegas_debug_check_tables", "lens", lens, desc.batch * 4)
-        error_word = _fits("vegas_debug_check_tables", "error_word", error_word, 4)
-    rc = load_library().vegas_debug_check_tables(ctypes.byref(desc), int(which), _ptr(table), _ptr(lens),
-                                                 _ptr(error_word), _stream(stream))
+        table_at = _fits("vegas_debug_check_tables", "table", table, desc.batch * stride * 4)
+        lens_at = _fits("vegas_debug_check_tables", "lens", lens, desc.batch * 4)
+        error_word_at = _fits("vegas_debug_check_tables", "error_word", error_word, 4)
+    rc = load_library().vegas_debug_check_tables(ctypes.byref(desc), int(which), _ptr(table_at), _ptr(lens_at),
+                                                 _ptr(error_word_at), _stream(stream))
     if rc != VEGAS_OK:
         raise VegasError(rc, "vegas_debug_check_tables")
 
@@ -499,12 +516,13 @@ def vegas_debug_verify_waves(desc: VegasDesc) -> int:
 
 def vegas_debug_stream_read(a, b, bytes_each: int, workgroups: int, non_temporal: bool, sink, stream=None) -> None:
     """The plain streaming read the benchmark uses as its yardstick (see include/vegas.h)."""
+    a_at, b_at, sink_at = a, b, sink
     if not isinstance(a, int):
-        a = _fits("vegas_debug_stream_read", "a", a, bytes_each)
-        b = _fits("vegas_debug_stream_read", "b", b, bytes_each)
-        sink = _fits("vegas_debug_stream_read", "sink", sink, workgroups * 256 * 4)
-    rc = load_library().vegas_debug_stream_read(_ptr(a), _ptr(b), int(bytes_each), int(workgroups), int(bool(non_temporal)),
-                                                _ptr(sink), _stream(stream))
+        a_at = _fits("vegas_debug_stream_read", "a", a, bytes_each)
+        b_at = _fits("vegas_debug_stream_read", "b", b, bytes_each)
+        sink_at = _fits("vegas_debug_stream_read", "sink", sink, workgroups * 256 * 4)
+    rc = load_library().vegas_debug_stream_read(_ptr(a_at), _ptr(b_at), int(bytes_each), int(workgroups), int(bool(non_temporal)),
+                                                _ptr(sink_at), _stream(stream))
     if rc != VEGAS_OK:
         raise VegasError(rc, "vegas_debug_stream_read")
 

@@ -290,6 +290,39 @@ def test_binding_refuses_tensors_whose_storage_was_resized(left):
         vb.vegas_draft_attention(d, q, cache, gone, sel, lens, torch.zeros_like(q), None)
 
 
+@pytest.mark.parametrize("name", ["vegas_verify_attention", "vegas_select_blocks", "vegas_select_tokens", "vegas_append_kv", "vegas_append_kv_extend",
+                                  "vegas_extend_selection", "vegas_draft_attention", "vegas_draft_attention_static", "vegas_draft_step",
+                                  "vegas_debug_check_tables", "vegas_debug_stream_read"])
+def test_binding_holds_its_tensors_until_the_call_returns(name, monkeypatch):
+    """The wrapper's own reference may be the last one (a temporary passed directly, where the caller's frame gives its arguments away): it
+    lasts until the library has enqueued its kernels, or the allocator could hand the memory to another thread's launch first."""
+    import inspect
+    import sys
+
+    import torch
+    d = good_desc(batch=1, max_blocks=1, max_sel_blocks=16, max_seq_len=16, num_pages=1, num_queries=1)
+    plain = dict(desc=d, cache_desc=d, num_new=1, budget_tokens=8, sel_page_size=16, which=vb.TABLE_BLOCKS, bytes_each=16, workgroups=1, non_temporal=0)
+    fn = getattr(vb, name)
+    args, tensors = {}, {}
+    for k, par in inspect.signature(fn).parameters.items():
+        if k in plain:
+            args[k] = plain[k]
+        elif k not in ("stream", "workspace_bytes", "stages"):
+            args[k] = tensors[k] = torch.zeros(1 << 16, dtype=torch.float32)
+    seen = []
+
+    class Library:
+        def __getattr__(self, _):
+            def call(*a):
+                held = [id(v) for v in sys._getframe(1).f_locals.values()]
+                seen.append([k for k, t in tensors.items() if id(t) not in held])
+                return vb.VEGAS_OK
+            return call
+    monkeypatch.setattr(vb, "_lib", Library())
+    fn(**args)
+    assert seen == [[]], seen
+
+
 def test_bench_refuses_more_than_one_gpu():
     """This build runs on one GPU; bench.py says so and exits before touching a device."""
     import subprocess
