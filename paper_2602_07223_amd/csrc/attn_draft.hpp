@@ -95,7 +95,7 @@ inline size_t draft16_lds_bytes(int R, int D) {
 // registers hold one and the next is asked for when the first contraction has used its K.  One workgroup to a compute unit, so what
 // bounds it is how much that unit has under way; the rule and its figures: ring_draft.
 // DV: head dims of V that the workgroup reads and of the output rows that it writes: D, or a part of it in calls that one workgroup per
-// column could finish (grid (KV head, part, sequence); draft_value_parts).
+// column could finish (draft_value_parts, part_grid_width).
 template <int D, int PS, bool CHOOSE, bool RING, int DV, typename... Step>
 __device__ __forceinline__ void draft16(SplitParams& p, const Step&... step) {
   VEGAS_TL_DECL;
@@ -120,10 +120,17 @@ __device__ __forceinline__ void draft16(SplitParams& p, const Step&... step) {
   const int l32 = lane & 31;
   const int l16 = lane & 15;                 // token of a page (K), query row (Q, S^T, O^T), head-dim group (V)
   const int kg = lane >> 4;                  // which 8 of a contraction step's 32 indices
-  const int h = blockIdx.x;                  // grid (KV head, chunk, sequence)
+  int h = blockIdx.x, b = blockIdx.z;        // grid (KV head, chunk, sequence), or part_grid_width's
   const int split = DV == D ? blockIdx.y : 0;
   const int part = DV == D ? 0 : blockIdx.y;  // which DV head dims of V
-  const int b = blockIdx.z;
+  if constexpr (DV != D) {
+    if (p.Hkv % kXcds != 0) {
+      const uint32_t column = static_cast<uint32_t>(h + kXcds * b);
+      if (column >= round_columns(p.row_blocks)) return;
+      b = static_cast<int>(round_sequence(p.row_blocks, column));
+      h = static_cast<int>(column) - b * p.Hkv;
+    }
+  }
   const int Rl = p.R;                        // rows of this KV head: one draft token, g heads (G = 1)
 
   int last_page = 0;                         // (set below, from arguments that are not there yet)

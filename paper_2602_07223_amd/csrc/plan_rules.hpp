@@ -4,6 +4,8 @@
 
 namespace vegas {
 
+constexpr int kXcds = 8;
+
 // Draft calls of up to kDraftRows rows per KV head (attn_draft16_kernel): the longest selection that one workgroup per
 // column (sequence x KV head) streams by itself, writing the output rows; a longer one is cut into chunks that a second
 // launch merges.  A single workgroup takes 0.3 us per 32 tokens at head dimension 128 (0.18 at 64) behind 3.4 us and no
@@ -74,6 +76,18 @@ inline int draft_value_parts(int64_t columns, int num_cu, int head_dim) {
   if (head_dim == 128 && 4 * columns <= num_cu) return 4;
   return 2 * columns <= num_cu ? 2 : 1;
 }
+// Their grid is (width, part, columns / width), workgroup x, y, z for column x + width z: workgroups go round the 8 XCDs in the order of the
+// grid, and with a width of whole rounds a column's parts meet on one XCD, whose L2 fetches its K once.  A sequence's KV heads are such a width
+// where they are a multiple of eight, other numbers of heads go by rounds of columns.  us a call, captured, one workgroup per column /
+// parts with the heads for a width, on several XCDs / by rounds, head dimension 128, 16-token pages: 1 head, 128 sequences, 448 tokens 6.5 / 7.6 /
+// 5.8, 1300 15.1 / 19.9 / 15.0; 2 heads, 64, 640 7.7 / 10.0 / 7.3; 4 heads, 32, 640 7.6 / 8.1 / 6.7; 7 heads, 18, 448 6.5 / 7.9 / 5.9; 5 heads, 3, 128 4.2 /
+// 3.7 / 3.7; head dimension 64, 2 heads, 64, 1300 10.6 / 13.1 / 9.0.
+inline int part_grid_width(int kv_heads) { return kv_heads % kXcds == 0 ? kv_heads : kXcds; }
+// What a workgroup needs to find its sequence without a division: the number of columns (below 2048) and, above it, 2^16 / kv_heads rounded up; a
+// column's sequence then is exact (the product is too large by at most column * kv_heads < 2^16).
+inline int32_t column_rounds(int columns, int kv_heads) { return (65535 / kv_heads + 1) << 11 | columns; }
+constexpr uint32_t round_columns(int32_t rounds) { return static_cast<uint32_t>(rounds) & 2047u; }
+constexpr uint32_t round_sequence(int32_t rounds, uint32_t column) { return column * (static_cast<uint32_t>(rounds) >> 11) >> 16; }
 
 // Verification with a local mask: does one workgroup per column (sequence x KV head x row block) stream the whole band
 // (no row sees more than window + queries tokens, nor than the longest sequence has) and write the output rows, or is the context cut into chunks

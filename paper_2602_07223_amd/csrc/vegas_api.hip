@@ -349,7 +349,13 @@ int launch_split_d(const SplitPlan& pl, SplitParams sp, int batch, hipStream_t s
         constexpr bool RING = decltype(ring)::value;
         const size_t bytes = RING ? draft_ring_lds_bytes() : dlds;
         if constexpr (DV == D) return launch_one(attn_draft16_kernel<D, PS, false, RING>, grid, dblock, bytes, st, sp);
-        else return launch_one(attn_draft16_parts_kernel<D, DV, PS, RING>, dim3(sp.Hkv, D / DV, batch), dblock, bytes, st, sp);
+        else {
+          SplitParams cut = sp;
+          cut.row_blocks = column_rounds(static_cast<int>(columns), sp.Hkv);      // (a preloaded argument that no draft call needs)
+          const unsigned width = part_grid_width(sp.Hkv);
+          return launch_one(attn_draft16_parts_kernel<D, DV, PS, RING>, dim3(width, D / DV, static_cast<unsigned>((columns + width - 1) / width)), dblock,
+                            bytes, st, cut);
+        }
       };
       auto by_parts = [&](auto ps, auto ring) {
         if (parts == D / 32) return launch(ps, ring, std::integral_constant<int, 32>{});

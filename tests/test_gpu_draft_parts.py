@@ -57,3 +57,11 @@ def test_parts(B, Hq, Hkv, P, D):
         vmax = float(V.float().abs().max())
         for out in outs:
             U.check_out(f"draft_parts.{B}.{P}.{D}.{bound}", out, ref, vmax)
+
+
+@pytest.mark.parametrize("D,P", [(128, 16), (128, 1), (64, 16), (64, 4)])
+@pytest.mark.parametrize("B,Hq,Hkv", [(1, 4, 1), (65, 2, 1), (5, 21, 3), (3, 35, 7), (18, 7, 7), (11, 10, 10), (5, 24, 24)])
+def test_parts_by_rounds_of_columns(B, Hq, Hkv, P, D):
+    """Numbers of KV heads that are not whole rounds of the XCDs (part_grid_width): the last round of columns is full or not, a sequence's heads lie
+    in one or in two."""
+    test_parts(B, Hq, Hkv, P, D)

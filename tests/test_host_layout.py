@@ -315,3 +315,41 @@ def test_eight_waves_take_a_band_where_that_is_faster(tmp_path):
                 ((256, 1, 132, 64, 20), 1), ((264, 1, 132, 64, 20), 0)]
     out = run_host_program(tmp_path, BAND_WAVES, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
     assert [int(x) for x in out] == [w for _, w in measured]
+
+
+PARTS = r'''
+#include <cstdio>
+#include "plan_rules.hpp"
+int main() {                       // lines of: columns, head dimension, KV heads
+  int columns, D, heads;
+  while (std::scanf("%d %d %d", &columns, &D, &heads) == 3) {
+    const int32_t rounds = vegas::column_rounds(columns, heads);
+    int right = vegas::round_columns(rounds) == static_cast<uint32_t>(columns);
+    for (int c = 0; c < columns; ++c) right &= vegas::round_sequence(rounds, c) == static_cast<uint32_t>(c / heads);
+    std::printf("%d %d %d\n", vegas::draft_value_parts(columns, 256, D), vegas::part_grid_width(heads), right);
+  }
+}
+'''
+
+
+def test_parts_of_a_column_meet_on_one_xcd(tmp_path):
+    """Draft calls split by parts of V: how many (four, two or one workgroup per column while there are compute units for them), and the grid
+    (width, part, columns / width): every column once, by a rule that needs no division where the width is the number of heads, and all parts of a
+    column on one of the 8 XCDs, round which workgroups go in the order of the grid; and a column's sequence without a division."""
+    edges = [((1, 128, 8), 4), ((64, 128, 8), 4), ((65, 128, 8), 2), ((128, 128, 8), 2), ((129, 128, 8), 1), ((64, 64, 8), 2), ((128, 64, 8), 2),
+             ((129, 64, 8), 1), ((1, 64, 8), 2)]
+    shapes = [(batch * heads, 128, heads) for heads in range(1, 34) for batch in (1, 2, 3, 5, 16, 31) if batch * heads <= 128]
+    out = [tuple(map(int, line.split()))
+           for line in run_host_program(tmp_path, PARTS, "\n".join(" ".join(map(str, a)) for a in [e for e, _ in edges] + shapes)).strip().split("\n")]
+    assert [parts for parts, _, _ in out[:len(edges)]] == [p for _, p in edges]
+    assert all(right for _, _, right in out)
+    for (columns, _, heads), (parts, width, _) in zip(shapes, out[len(edges):], strict=True):
+        assert width == heads or heads % 8, (heads, width)
+        place = {}
+        for z in range(-(-columns // width)):
+            for y in range(parts):
+                for x in range(width):
+                    if x + width * z < columns:
+                        place.setdefault(x + width * z, []).append((x + width * (y + parts * z)) % 8)
+        assert sorted(place) == list(range(columns)), (columns, heads)
+        assert all(len(p) == parts and len(set(p)) == 1 for p in place.values()), (columns, heads, width)
