@@ -30,7 +30,7 @@ __device__ __forceinline__ uint32_t score_key(float s) {
 struct RegisterSelectShared {
   uint32_t hist[3][2048];                       // digit counts of the up to three passes
   uint32_t low[kSelectThreads / 64], high[kSelectThreads / 64];
-  uint32_t bin, need, count, crowded, listed;
+  uint32_t bin, need, count;
 };
 // Taken are the keys above base + span and the first `need`, by position, of those in [base, base + span]; whole: these are all.
 struct LastKey {
@@ -41,10 +41,11 @@ struct LastKey {
 constexpr uint32_t kNoDigit = 0xFFFFFFFFu;      // of a key that is not counted
 constexpr int kOften = 4;                       // digits that a crowded wave counts by itself
 constexpr int kRunLanes = 32;                   // so many lanes with the digit of the lane beside them: one add per run of lanes
-// The digit of the lane below, of sixteen; none for the first.
+// The digit of the lane `BELOW` below, of sixteen; none for the first ones.
+template <int BELOW = 1>
 __device__ __forceinline__ uint32_t digit_beside(uint32_t digit) {
-  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int>(kNoDigit), static_cast<int>(digit), 0x111, 0xf, 0xf,
-                                                           false));   // row_shr:1
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int>(kNoDigit), static_cast<int>(digit), 0x110 + BELOW, 0xf, 0xf,
+                                                           false));   // row_shr
 }
 // Lanes that have the digit of the lane beside them: the chance that two keys share a digit, at the price of one comparison.
 __device__ __forceinline__ int sharing_lanes(uint32_t digit) {
@@ -100,13 +101,15 @@ __device__ __forceinline__ void walk_to_last_bin(const uint32_t* h, uint32_t nee
 // in an iteration: token selection at 32768 there 0.7 less than unrolled.  (A first range that leaves masks' scores and a lone
 // low one out, with up to four passes: masked and outlier 8.6 and 18.2 at the larger two, but every other call 0.3 to 1.6 more.)
 // given: a range that holds all keys taken and the last of them, [base, base + span], instead of the workgroup's smallest and largest key.
-template <bool CROWDS = true, int THREADS = kSelectThreads, int N, typename Valid>
+// CLEARED: the counts are zero already, with a range (no other call has one) since before a barrier.
+template <bool CROWDS = true, int THREADS = kSelectThreads, bool CLEARED = false, int N, typename Valid>
 __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int full, int live, Valid valid, uint32_t take,
                                                  RegisterSelectShared& sh, const LastKey* given = nullptr) {
   constexpr int kWaves = THREADS / 64;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int i = tid; i < 3 * 2048 / 4; i += THREADS) reinterpret_cast<u32x4*>(sh.hist)[i] = u32x4{0u, 0u, 0u, 0u};
+  if constexpr (!CLEARED)
+    for (int i = tid; i < 3 * 2048 / 4; i += THREADS) reinterpret_cast<u32x4*>(sh.hist)[i] = u32x4{0u, 0u, 0u, 0u};
   LastKey r;
   r.need = take;
   r.whole = false;
@@ -122,10 +125,9 @@ __device__ __forceinline__ LastKey find_last_key(const uint32_t (&key)[N], int f
     r.base = ~__builtin_amdgcn_readfirstlane(wave_max(sh.low[lane & (kWaves - 1)]));
     r.span = hi - r.base;
   };
-  if (given != nullptr) {
+  if (CLEARED && given != nullptr) {
     r.base = given->base;
     r.span = given->span;
-    __syncthreads();
   } else {
     uint32_t hi = 0u, inv_lo = 0u;
 #pragma unroll

@@ -40,9 +40,8 @@ struct TokenPlan {
   bool need_search, take_all;
 };
 
-__device__ __forceinline__ TokenPlan token_plan(const TokenSelectParams& p, int b) {
+__device__ __forceinline__ TokenPlan token_plan(const TokenSelectParams& p, int b, int n) {       // n: seq_lens[b]
   TokenPlan t;
-  int n = p.seq_lens[b];
   t.n = n < 0 ? 0 : (n > p.max_tokens ? p.max_tokens : n);
   t.p_len = max(t.n - p.G, 0);
   t.tail = t.n - t.p_len;
@@ -121,7 +120,7 @@ __global__ __launch_bounds__(kTokThreads) void token_select_hist(const TokenSele
   __shared__ uint32_t sh_prefix;
   const int b = blockIdx.y, s = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const TokenPlan t = token_plan(p, b);
+  const TokenPlan t = token_plan(p, b, p.seq_lens[b]);
   const int base = s * kTokSlice;
   if (!t.need_search || base >= t.p_len) return;
   const int nslices = (t.p_len + kTokSlice - 1) / kTokSlice;
@@ -178,7 +177,7 @@ __global__ __launch_bounds__(kTokThreads) void token_select_write(const TokenSel
   __shared__ uint32_t wave_take[kTokThreads / 64], wave_eq[kTokThreads / 64];
   const int b = blockIdx.y, s = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const TokenPlan t = token_plan(p, b);
+  const TokenPlan t = token_plan(p, b, p.seq_lens[b]);
   int32_t* sel = p.sel_table + static_cast<int64_t>(b) * p.max_sel;
   const int32_t* table = p.block_table + static_cast<int64_t>(b) * p.max_blocks;
   const float* scores = p.scores + static_cast<int64_t>(b) * p.max_blocks * kPage;
@@ -280,7 +279,15 @@ __global__ __launch_bounds__(kTokThreads) void token_select_write(const TokenSel
 // ---- up to 32768 tokens: one workgroup per sequence, thread tid has tokens 4096 g + 4 tid + e (row g, e = 0..3) in registers; token
 // (g, e) is bit 4 g + e of a thread's set of tokens.
 constexpr int kRowTokens = 4 * kTokThreads;
-constexpr int kBinTies = 256;          // tokens of one bin that are ranked among each other
+constexpr int kBinTies = 512;          // tokens of one bin that are ranked among each other at most
+constexpr int kCrowd = 12;             // so many of 64 scores in one bin: bins do not tell them apart (take_by_bins)
+constexpr int kFewValues = 2;          // so many of 64 scores equal to one of two sampled beside them: there are few values
+
+struct TokenSelectShared : RegisterSelectShared {
+  alignas(16) uint32_t bins[2048];     // counts of take_by_bins (hist: of find_last_key)
+  uint32_t top[kTokThreads / 64], bound[kTokThreads / 64];      // of each wave: largest key, complement of the bound (key_bounds)
+  uint32_t crowded, listed;
+};
 
 // Tokens of all threads before each of this thread's rows, and of all rows (the result); n[g] of row g (4 at most) are this thread's.
 // One barrier inside.
@@ -321,6 +328,48 @@ __device__ __forceinline__ uint32_t row_counts(uint32_t set, uint32_t (&before)[
   return counts_before<ROWS>(n, before, rows, cells);
 }
 
+// Places of the tokens above a last bin and of the first `need`, by position, of those in it, of two disjoint sets: `set` is made theirs
+// and `before` counts them.  One barrier inside; the result is their number.
+template <int ROWS>
+__device__ __forceinline__ uint32_t keep_first(uint32_t& set, uint32_t in, uint32_t need, uint32_t (&before)[ROWS], int rows, uint32_t* cells) {
+  constexpr int kWaves = kTokThreads / 64, kPacks = (2 * ROWS + 2) / 3;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  uint32_t n[3 * kPacks], lower[kPacks], of_wave[kPacks];
+#pragma unroll
+  for (int i = 0; i < 3 * kPacks; ++i) n[i] = i < ROWS ? __popc((set >> (4 * i)) & 15u) : i < 2 * ROWS ? __popc((in >> (4 * (i - ROWS))) & 15u) : 0u;
+#pragma unroll
+  for (int q = 0; q < kPacks; ++q) {
+    const uint32_t pack = n[3 * q] | (n[3 * q + 1] << 10) | (n[3 * q + 2] << 20);
+    const uint32_t incl = wave_prefix_sum(pack);
+    lower[q] = incl - pack;
+    of_wave[q] = __builtin_amdgcn_readlane(incl, 63);
+  }
+  auto field = [](const uint32_t (&packs)[kPacks], int i) { return (packs[i / 3] >> (10 * (i % 3))) & 1023u; };
+  uint32_t own = 0u;                             // (a cell's two counts are 32768 at most in sum)
+#pragma unroll
+  for (int g = 0; g < ROWS; ++g)
+    if (lane == g) own = field(of_wave, g) | (field(of_wave, ROWS + g) << 16);
+  if (lane < rows) cells[lane * kWaves + wave] = own;
+  __syncthreads();
+  uint32_t total;
+  const uint32_t cell = CellWalk<ROWS>::before(cells, rows, wave, lane, &total);
+#pragma unroll
+  for (int g = 0; g < ROWS; ++g) {
+    const uint32_t c = __builtin_amdgcn_readlane(cell, CellWalk<ROWS>::lane_of(g, wave));
+    const uint32_t in_before = field(lower, ROWS + g) + (c >> 16);
+    before[g] = field(lower, g) + (c & 0xFFFFu) + min(in_before, need);
+    // of the row's tokens in the last bin as many as are still wanted, the lower ones first
+    const uint32_t left = need > in_before ? need - in_before : 0u;
+    uint32_t row = (in >> (4 * g)) & 15u;
+#pragma unroll
+    for (int drop = 3; drop >= 0; --drop)
+      if (__popc(row) > static_cast<int>(left)) row &= ~(1u << drop);
+    set |= row << (4 * g);
+  }
+  return (total & 0xFFFFu) + min(total >> 16, need);
+}
+
 __device__ __forceinline__ float max3(float a, float b, float c) {      // (fmaxf quiets what it is given first: an instruction a key)
   float r;
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
@@ -343,15 +392,33 @@ VEGAS_SHIFT_IN_GE(float, "f32")
 VEGAS_SHIFT_IN_GE(uint32_t, "u32")
 #undef VEGAS_SHIFT_IN_GE
 
+__device__ __forceinline__ float key_score(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key); }
+
+// Scores by 2048 bins of equal width: a bin is a monotone function of the score, one multiply-add to a number whose low bits are the bin.
+struct ScoreBins {
+  static constexpr float kOne = 2097152.f;       // 2^21: numbers from there to its double have their quarters in bits 0 and 1
+  static constexpr uint32_t kBytes = 2047u * 4u;
+  float scale, shift;
+  bool ok;                                       // false: the range is too near a point, or too far from 0 for its width
+  __device__ __forceinline__ ScoreBins(float lo, float hi) {
+    scale = 2040.f * __builtin_amdgcn_rcpf(hi - lo);
+    shift = kOne + 3.f - lo * scale;
+    ok = scale > 0.f && fabsf(lo) * scale < kOne && fabsf(hi) * scale < kOne;
+  }
+  __device__ __forceinline__ float place(float v) const { return __builtin_fmaf(v, scale, shift); }      // 2^21 + bin
+  static __device__ __forceinline__ bool inside(float y) { return y >= kOne + 1.f; }
+  static __device__ __forceinline__ uint32_t offset(float y) { return __float_as_uint(y) & kBytes; }
+};
+
 // Largest key of the workgroup, and a lower bound of the `take`-th largest: the smallest of the largest keys of groups of tokens that are
-// disjoint and at least `take` in number, so that masked and far low scores do not count.  False where there are no such groups.
+// disjoint and at least `take` (a quarter of all, or fewer) in number, so that masked and far low scores do not count.  False where it is no number.
+// One barrier inside.
 template <int ROWS>
-__device__ __forceinline__ bool key_bounds(const float (&x)[4 * ROWS], int rows, int p_len, uint32_t take, RegisterSelectShared& sh,
+__device__ __forceinline__ bool key_bounds(const float (&x)[4 * ROWS], int rows, int p_len, uint32_t take, TokenSelectShared& sh,
                                            LastKey& range) {
   constexpr int kWaves = kTokThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (4u * take > static_cast<uint32_t>(p_len)) return false;
   float m[ROWS], top = -INFINITY;
 #pragma unroll
   for (int g = 0; g < ROWS; ++g) {
@@ -379,72 +446,65 @@ __device__ __forceinline__ bool key_bounds(const float (&x)[4 * ROWS], int rows,
   hi = wave_max(hi);
   inv_lo = wave_max(inv_lo);
   if (lane == 0) {
-    sh.high[wave] = hi;
-    sh.low[wave] = inv_lo;
+    sh.top[wave] = hi;
+    sh.bound[wave] = inv_lo;
   }
   __syncthreads();
-  hi = __builtin_amdgcn_readfirstlane(wave_max(sh.high[lane & (kWaves - 1)]));
-  range.base = ~__builtin_amdgcn_readfirstlane(wave_max(sh.low[lane & (kWaves - 1)]));
+  hi = __builtin_amdgcn_readfirstlane(wave_max(sh.top[lane & (kWaves - 1)]));
+  range.base = ~__builtin_amdgcn_readfirstlane(wave_max(sh.bound[lane & (kWaves - 1)]));
   range.span = hi - range.base;
-  const bool ok = range.base > score_key(-INFINITY) && hi >= range.base && hi < score_key(INFINITY);
-  if (!ok) __syncthreads();                        // (find_last_key writes its own bounds there)
-  return ok;
+  return range.base > score_key(-INFINITY) && hi >= range.base && hi < score_key(INFINITY);
 }
 
-// The set of this thread's tokens among the `take` largest scores, found among the scores themselves: 2048 bins of equal width over the
-// range, one pass that counts, one that takes what lies above the last bin, and the few tokens of that bin ranked among each other.  False
-// where the scores do not spread over such bins.  A bin is a monotone function of the score (one multiply-add to a number whose low bits
-// are the bin), whatever it rounds, so the set is right if it has `take` tokens, and false is the result if it has not.
-// before: tokens taken before this thread's of a row.
+// The set of this thread's tokens among the `take` largest scores, found among the scores themselves: 2048 bins over the range, one pass
+// that counts, one that takes what lies above the last bin, and the few tokens of that bin ranked among each other.  False where that bin
+// has too many, or where a wave finds twelve of 64 scores in one bin before anything is counted: a far one leaves the others no bins.
+// (Largest number found, 16 sequences of 2048 to 32768: normal 3, its exponential 5, rising or falling 7; exp of five times a normal one 59, one at
+// 3e38 63.)  Whatever a bin rounds, the set is right if it has `take` tokens, and false is the result if it has not.
+// before: tokens taken before this thread's of a row.  used: whether `hist` was written.
 template <int ROWS>
-__device__ __forceinline__ bool take_by_bins(const float (&x)[4 * ROWS], int rows, uint32_t take, const LastKey& range,
-                                             RegisterSelectShared& sh, uint32_t* cells, uint32_t& taken, uint32_t (&before)[ROWS]) {
+__device__ __forceinline__ bool take_by_bins(const float (&x)[4 * ROWS], int rows, uint32_t take, const LastKey& range, TokenSelectShared& sh,
+                                             uint32_t* cells, uint32_t& taken, uint32_t (&before)[ROWS], bool& used) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  uint32_t* const hist = sh.hist[0];
   uint32_t* const ranked = sh.hist[1];             // [thread] its tokens of the last bin that are kept
   uint64_t* const ties = reinterpret_cast<uint64_t*>(sh.hist[2]);
   static_assert(sizeof(sh.hist[1]) >= kTokThreads * 4 && sizeof(sh.hist[2]) >= kBinTies * 8, "sets and ties alias digit counts");
-  auto score_of = [](uint32_t key) { return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key); };
-  const float lo = score_of(range.base), hi = score_of(range.base + range.span);
-  constexpr float kOne = 2097152.f;                // 2^21: numbers from there to its double have their quarters in bits 0 and 1
-  const float scale = 2040.f / (hi - lo);
-  const float shift = kOne + 3.f - lo * scale;
-  if (!(scale > 0.f && fabsf(lo) * scale < kOne && fabsf(hi) * scale < kOne)) return false;      // (too near, too far from 0)
-  auto place = [&](float v) { return __builtin_fmaf(v, scale, shift); };                        // 2^21 + bin
-  constexpr uint32_t kBinBytes = 2047u * 4u;
-  reinterpret_cast<u32x4*>(hist)[tid] = u32x4{0u, 0u, 0u, 0u};     // (both)
-  if (tid == 0) sh.crowded = sh.listed = 0u;
-  __syncthreads();
-  const float first = place(x[0]);
-  if (sharing_lanes(first >= kOne + 1.f ? __float_as_uint(first) & kBinBytes : kNoDigit) < 3) {
+  const ScoreBins bins(key_score(range.base), key_score(range.base + range.span));
+  if (!bins.ok) return false;
+  const float first = bins.place(x[0]);
+  const uint32_t digit = ScoreBins::inside(first) ? ScoreBins::offset(first) : kNoDigit;
+  const uint64_t in_range = __builtin_amdgcn_ballot_w64(digit != kNoDigit);
+  const uint32_t probe = in_range ? __builtin_amdgcn_readlane(digit, __builtin_ctzll(in_range)) : kNoDigit - 1u;
+  if (__popcll(__builtin_amdgcn_ballot_w64(digit == probe)) < kCrowd) {
     uint32_t one = 1u;
     asm("" : "+v"(one));
 #pragma unroll
     for (int u = 0; u < 4 * ROWS; ++u) {
       if ((u >> 2) >= rows) continue;
-      const float y = place(x[u]);
-      if (y >= kOne + 1.f) atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(hist) + (__float_as_uint(y) & kBinBytes)), one);
+      const float y = bins.place(x[u]);
+      if (ScoreBins::inside(y)) atomicAdd(reinterpret_cast<uint32_t*>(reinterpret_cast<unsigned char*>(sh.bins) + ScoreBins::offset(y)), one);
     }
   } else if (lane == 0) {
     sh.crowded = 1u;
   }
   __syncthreads();
   if (sh.crowded != 0u) return false;
-  if (wave == 0) walk_to_last_bin(hist, take, sh);
+  if (wave == 0) walk_to_last_bin(sh.bins, take, sh);
   __syncthreads();
   const uint32_t bin = __builtin_amdgcn_readfirstlane(sh.bin), need = __builtin_amdgcn_readfirstlane(sh.need);
   const uint32_t count = __builtin_amdgcn_readfirstlane(sh.count);
   const bool whole = need == count;                // the last bin is kept whole
-  if (!whole && count > kBinTies) return false;
-  const float in = kOne + static_cast<float>(bin), above = whole ? in : in + 1.f;
+  if (!whole && count > min(kBinTies, 128 * ROWS)) return false;       // (ranking 270 costs what digits take up to 4096 tokens)
+  used = true;
+  const float in = ScoreBins::kOne + static_cast<float>(bin), above = whole ? in : in + 1.f;
   uint32_t set = 0u;
 #pragma unroll
   for (int g = ROWS - 1; g >= 0; --g) {
     if (g >= rows) continue;
     float y[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) y[e] = place(x[4 * g + e]);
+    for (int e = 0; e < 4; ++e) y[e] = bins.place(x[4 * g + e]);
     uint32_t at_least = 0u;
     shift_in_ge(set, y[0], y[1], y[2], y[3], above);
     shift_in_ge(at_least, y[0], y[1], y[2], y[3], in);
@@ -476,18 +536,29 @@ __device__ __forceinline__ bool take_by_bins(const float (&x)[4 * ROWS], int row
   return row_counts<ROWS>(set, before, rows, cells) == take;
 }
 
-// The same by find_last_key, for scores of any kind: within the range, if there is one, and if that does not yield `take` tokens (the
-// range is that of floating-point comparisons, which some NaNs upset) among all keys.
-template <int ROWS>
-__device__ __forceinline__ uint32_t take_by_digits(const uint32_t (&key)[4 * ROWS], int rows, int p_len, uint32_t take, bool ranged,
-                                                   const LastKey& range, RegisterSelectShared& sh, uint32_t (*cells)[ROWS * (kTokThreads / 64)],
-                                                   uint32_t (&before)[ROWS]) {
+// The same by find_last_key, for scores of any kind.
+// RANGED: within the range, and if that does not yield `take` tokens (it is that of floating-point comparisons, which some NaNs upset) among
+// all keys.  used: the counts are not zero.
+template <int ROWS, bool RANGED>
+__device__ __forceinline__ uint32_t take_by_digits(const float (&x)[4 * ROWS], int rows, int p_len, uint32_t take, bool used, const LastKey& range,
+                                                   TokenSelectShared& sh, uint32_t* cells, uint32_t (&before)[ROWS]) {
   const int tid = threadIdx.x;
+  uint32_t key[4 * ROWS];
+#pragma unroll
+  for (int u = 0; u < 4 * ROWS; ++u) {
+    key[u] = score_key(x[u]);
+    if (kRowTokens * ((u >> 2) + 1) > p_len && kRowTokens * (u >> 2) + 4 * tid + (u & 3) >= p_len) key[u] = 0u;
+  }
   auto valid = [&](int u) { return kRowTokens * (u >> 2) + 4 * tid + (u & 3) < p_len; };
   uint32_t set;
+  bool ranged = RANGED && !used;
 #pragma unroll 1
-  for (;; ranged = false) {
-    const LastKey last = find_last_key(key, p_len / kRowTokens * 4, 4 * rows, valid, take, sh, ranged ? &range : nullptr);
+  do {
+    // (A barrier is behind the last use of the counts, and one ahead of the next: in find_last_key where it has no range.)
+    if (RANGED && used)
+      for (int i = tid; i < 3 * 2048 / 4; i += kTokThreads) reinterpret_cast<u32x4*>(sh.hist)[i] = u32x4{0u, 0u, 0u, 0u};
+    const LastKey last = find_last_key<true, kTokThreads, true>(key, p_len / kRowTokens * 4, 4 * rows, valid, take, sh,
+                                                                RANGED && ranged ? &range : nullptr);
     // (a last bin that ends with the largest key there is has nothing above it)
     const uint32_t above = last.base + last.span + 1u;
     uint32_t in = 0u;
@@ -499,23 +570,17 @@ __device__ __forceinline__ uint32_t take_by_digits(const uint32_t (&key)[4 * ROW
       if (above != 0u) shift_in_ge(set, key[4 * g], key[4 * g + 1], key[4 * g + 2], key[4 * g + 3], above);
     }
     in &= ~set;
+    uint32_t found;
     if (last.whole) {
       set |= in;
+      found = row_counts<ROWS>(set, before, rows, cells);
     } else {
-      row_counts<ROWS>(in, before, rows, cells[0]);
-#pragma unroll
-      for (int g = 0; g < ROWS; ++g) {
-        // of the row's tokens in the last bin as many as are still wanted, the lower ones first
-        const uint32_t left = last.need > before[g] ? last.need - before[g] : 0u;
-        uint32_t row = (in >> (4 * g)) & 15u;
-#pragma unroll
-        for (int drop = 3; drop >= 0; --drop)
-          if (__popc(row) > static_cast<int>(left)) row &= ~(1u << drop);
-        set |= row << (4 * g);
-      }
+      found = keep_first<ROWS>(set, in, last.need, before, rows, cells);
     }
-    if (row_counts<ROWS>(set, before, rows, cells[1]) == take || !ranged) break;
-  }
+    if (!RANGED || !ranged || found == take) break;
+    ranged = false;
+    used = true;
+  } while (RANGED);
   return set;
 }
 
@@ -524,19 +589,21 @@ __device__ __forceinline__ uint32_t take_by_digits(const uint32_t (&key)[4 * ROW
 // count three rows at once.  The sequence's page ids wait in LDS.
 // Bound by the instructions issued on one compute unit, 0.2 us for each one that every key of 32768 takes.  Digits of the keys
 // (find_last_key) take some forty a key, most of them to make keys and to count and place one by one; bins over the scores take half.
-// us, captured, five launches / by digits / now, normally distributed scores: 1 sequence of 4096 tokens 19.2 / 5.1 / 4.4, 8192 19.9 / 6.7 /
-// 5.1, 16384 20.5 / 11.6 / 7.0, 32768 21.0 / 16.8 / 10.5; 16 of 32768 22.4 / 18.6 / 11.3; a twentieth -infinity 32768 20.6 / 25.6 / 10.2, a far
-// low one 20.6 / 23.4 / 10.6, rising with the position 20.6 / 19.0 / 10.6, half 0 19.7 / 10.5.  Where bins do not tell the scores apart, by
-// digits / now: four values 19.8 / 22.5, one at 3e38 23.4 / 25.0, fifteen in sixteen 0 19.2 / 20.5, all equal 10.9 / 11.9, exp of five times
-// a normal one 15.7 / 14.9; over a quarter of the tokens taken, which has digits alone, 16.8 / 15.6.  In an iteration of 32768 tokens, whose
-// instructions are cold, 80.3 -> 71.1.
+// us, captured, five launches / by digits alone, as they were / now, normally distributed scores: 1 sequence of 4096 tokens 19.2 / 5.3 / 4.5,
+// 8192 19.9 / 6.8 / 5.0, 16384 20.5 / 10.4 / 6.4, 32768 21.0 / 17.0 / 9.8; 16 of 32768 22.4 / 19.0 / 10.7; a twentieth -infinity 32768 20.6 / 18.9 /
+// 10.1, a far low one 20.6 / 16.9 / 9.8, rising with the position 20.6 / 17.2 / 11.3, half 0 19.8 / 10.2.  Where bins do not tell the scores
+// apart, digits as they were / now, 4096, 8192, 32768: four values 6.2 / 6.5, 7.9 / 8.0, 19.9 / 19.8; fifteen in sixteen 0 4.8 / 5.1, 6.5 / 6.4, 19.3 /
+// 19.2; all equal 3.5 / 3.8, 4.5 / 4.6, 11.1 / 11.0 (seen in the sample: its request and test are the difference); one at 3e38 5.2 / 5.7,
+// 6.8 / 7.0, 16.9 / 14.0; exp of five times a normal one 5.2 / 5.9, 6.5 / 6.2, 15.7 / 14.3 (seen behind the bounds); over a quarter of the tokens
+// taken, which has digits alone, 5.3 / 5.4, 6.8 / 6.7, 17.0 / 15.7.  What every wave does for one of its scores costs 7 ns: an instruction of
+// 16 waves is 16 cycles of a SIMD.  In an iteration of 32768 tokens, whose instructions are cold, 80.3 -> 71.1.
 template <int ROWS>
 __global__ __launch_bounds__(kTokThreads) void token_select_one_kernel(const TokenSelectParams p) {
   static_assert(kTokThreads == kSelectThreads, "find_last_key");
   constexpr int kWaves = kTokThreads / 64;
   constexpr int kPageTrips = (ROWS * kRowTokens / kPage + kTokThreads - 1) / kTokThreads;
-  __shared__ __align__(16) RegisterSelectShared reg_shared;
-  __shared__ uint32_t cells[2][ROWS * kWaves];
+  __shared__ __align__(16) TokenSelectShared shared;
+  __shared__ uint32_t cells[ROWS * kWaves];
   __shared__ int32_t pages[kPageTrips * kTokThreads];
   typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));     // (scores may start at any float)
   const int b = blockIdx.x;
@@ -553,10 +620,18 @@ __global__ __launch_bounds__(kTokThreads) void token_select_one_kernel(const Tok
   int32_t page[kPageTrips];
 #pragma unroll
   for (int i = 0; i < kPageTrips; ++i) page[i] = table[min(i * kTokThreads + tid, p.max_blocks - 1)];
-  const TokenPlan t = token_plan(p, b);
+  // 64 scores, the same in every wave (eight in a row from eight places: 64 places are as many lines for each of 16 waves, 0.3 us)
+  const int lane = tid & 63, sampled = (lane >> 3) * (p.max_tokens >> 3) + (lane & 7);
+  const float sample = gload<float, false>(uniform_ptr(reinterpret_cast<const unsigned char*>(scores)), static_cast<uint32_t>(min(sampled, cap - 1)) * 4u);
+  const int n = p.seq_lens[b];
+  // (counts start at zero; these, and the pages, are ordered by the search's first barrier)
+  static_assert(kTokThreads * 4 == 2 * 2048, "a thread clears four counts of two arrays each");
+  reinterpret_cast<u32x4*>(shared.hist[0])[tid] = u32x4{0u, 0u, 0u, 0u};
+  reinterpret_cast<u32x4*>(tid < kTokThreads / 2 ? shared.hist[2] : shared.bins)[tid & (kTokThreads / 2 - 1)] = u32x4{0u, 0u, 0u, 0u};
+  if (tid == 0) shared.crowded = shared.listed = 0u;
+  const TokenPlan t = token_plan(p, b, n);
 #pragma unroll
   for (int i = 0; i < kPageTrips; ++i) pages[i * kTokThreads + tid] = page[i];
-  __syncthreads();
   auto slot_of = [&](int j) -> int32_t { return pages[j >> 4] * kPage + (j & 15); };
   if (t.need_search) {
     const int rows = (t.p_len + kRowTokens - 1) / kRowTokens;        // at most ROWS: the host's bound on the lengths says so
@@ -573,18 +648,26 @@ __global__ __launch_bounds__(kTokThreads) void token_select_one_kernel(const Tok
           if (kRowTokens * g + 4 * tid + e >= t.p_len) x[4 * g + e] = -INFINITY;
       }
     }
+    // Few values, which bins do not tell apart (and to find that out with them costs half of what digits take): every wave sees it in the same
+    // sample, so that nothing waits.  Not where a quarter of the sample is above all that occurs twice and groups of 16 tokens are asked for
+    // a bound, which then is above it too (half of the scores 0: 18.5 us by digits, 10.0).
+    auto few_values = [&]() {
+      const uint32_t bits = __float_as_uint(sample);
+      const uint64_t counts = __builtin_amdgcn_ballot_w64(sampled < t.p_len) & __builtin_amdgcn_ballot_w64(sample > -INFINITY);
+      const uint64_t twice = counts & (__builtin_amdgcn_ballot_w64(sample == __uint_as_float(digit_beside<1>(bits))) |
+                                       __builtin_amdgcn_ballot_w64(sample == __uint_as_float(digit_beside<2>(bits))));
+      if (__popcll(twice) < kFewValues) return false;
+      if (ROWS < 4 || 16u * take > static_cast<uint32_t>(t.p_len)) return true;
+      const float most = key_score(wave_max((twice >> lane) & 1u ? score_key(sample) : 0u));
+      return 4 * __popcll(__builtin_amdgcn_ballot_w64(sample > most) & counts) < __popcll(counts);
+    };
     LastKey range;
     uint32_t taken, before[ROWS];
-    const bool ranged = key_bounds<ROWS>(x, rows, t.p_len, take, reg_shared, range);
-    if (!(ranged && take_by_bins<ROWS>(x, rows, take, range, reg_shared, cells[1], taken, before))) {
-      uint32_t key[4 * ROWS];
-#pragma unroll
-      for (int u = 0; u < 4 * ROWS; ++u) {
-        key[u] = score_key(x[u]);
-        if (kRowTokens * ((u >> 2) + 1) > t.p_len && kRowTokens * (u >> 2) + 4 * tid + (u & 3) >= t.p_len) key[u] = 0u;
-      }
-      taken = take_by_digits<ROWS>(key, rows, t.p_len, take, ranged, range, reg_shared, cells, before);
-    }
+    bool used = false;
+    if (4u * take > static_cast<uint32_t>(t.p_len) || few_values() || !key_bounds<ROWS>(x, rows, t.p_len, take, shared, range))
+      taken = take_by_digits<ROWS, false>(x, rows, t.p_len, take, false, range, shared, cells, before);
+    else if (!take_by_bins<ROWS>(x, rows, take, range, shared, cells, taken, before, used))
+      taken = take_by_digits<ROWS, true>(x, rows, t.p_len, take, used, range, shared, cells, before);
     unsigned char* const out = uniform_ptr_mut(reinterpret_cast<unsigned char*>(sel));
 #pragma unroll
     for (int g = 0; g < ROWS; ++g) {
@@ -600,6 +683,7 @@ __global__ __launch_bounds__(kTokThreads) void token_select_one_kernel(const Tok
       }
     }
   } else if (t.take_all) {
+    __syncthreads();
     for (int j = tid; j < min(t.p_len, p.max_sel); j += kTokThreads) sel[j] = slot_of(j);
   }
   // ---- the kept tail, the padding and the length

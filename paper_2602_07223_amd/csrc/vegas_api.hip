@@ -808,7 +808,7 @@ int vegas_select_tokens(const vegas_desc* desc, const float* token_scores, const
   tp.max_tokens = desc->max_seq_len;
   tp.slices = token_slices(desc);
   tp.budget_ratio = desc->budget_ratio;
-  // Up to 32768 tokens one workgroup per sequence (10.5 us there, five launches 21; beyond, 22.8 us at 65536, where a thread would have to
+  // Up to 32768 tokens one workgroup per sequence (9.8 us there, five launches 21; beyond, 22.8 us at 65536, where a thread would have to
   // hold 64 scores), built for the fewest rows of 4096 that the bound on the lengths allows: a row that is not there costs its tests and
   // requests.
   auto launch_one_wg = [&](auto rows) {

@@ -55,3 +55,44 @@ def test_token_bins(kind, longest, G):
             ref_sel, ref_ssl, _ = O.select_tokens(scores, table, lens, G, 1, longest + 2, budgets)
             assert np.array_equal(ssl, ref_ssl)
             assert np.array_equal(sel, ref_sel)
+
+
+def crowded_scores(kind, n, rng):
+    x = rng.standard_normal(n).astype(np.float32)
+    if kind == "four_values":
+        return rng.integers(0, 4, n).astype(np.float32)
+    if kind == "hundred_values":           # bins hold them, the last one more than are ranked
+        return rng.integers(0, 100, n).astype(np.float32)
+    if kind == "mostly_zero":
+        return np.where(rng.random(n) < 1 / 16, np.abs(x), 0).astype(np.float32)
+    if kind == "half_zero":                # what occurs twice lies below the selection's end
+        return np.where(rng.random(n) < 0.5, np.abs(x), 0).astype(np.float32)
+    if kind == "one_far":
+        x[n // 3] = 3e38
+        return x
+    if kind == "exponentials":
+        return np.exp(5 * x).astype(np.float32)
+    if kind == "masked_but_few":           # equal scores in the sample that are no scores
+        x[rng.random(n) < 0.8] = -np.inf
+        return x
+    return x
+
+
+@pytest.mark.parametrize("longest,G", [(20, 1), (64, 1), (1023, 5), (4096, 1), (8192, 5), (9000, 1), (32768, 5)])
+@pytest.mark.parametrize("kind", ["four_values", "hundred_values", "mostly_zero", "half_zero", "one_far", "exponentials", "masked_but_few"])
+def test_scores_that_bins_do_not_tell_apart(kind, longest, G):
+    """The ways past the bins: few values seen in the sample, many scores of a wave in one bin, too many in the last one; and the tokens of a last
+    bin that is not taken whole, kept by position, for shares on both sides of what bins are tried for."""
+    rng = np.random.default_rng(longest * 11 + len(kind))
+    lens = np.array([longest, max(longest - 4095, G + 1), max(longest // 3, G + 1)], dtype=np.int32)
+    B, mb = len(lens), (longest + PAGE - 1) // PAGE
+    scores = np.stack([crowded_scores(kind, mb * PAGE, rng) for _ in range(B)])
+    table = np.stack([rng.permutation(mb + 5)[:mb] for _ in range(B)]).astype(np.int32)
+    for share in (64, 16, 4, 2):
+        for extra in (0, 1):
+            budgets = np.maximum((lens - G) // share + G + extra, 1).astype(np.int32)
+            print(f"[case] token selection {kind} longest={longest} G={G} share={share} extra={extra}", flush=True)
+            sel, ssl = gpu_select_tokens(scores, table, lens, G, 1, longest + 2, budgets)
+            ref_sel, ref_ssl, _ = O.select_tokens(scores, table, lens, G, 1, longest + 2, budgets)
+            assert np.array_equal(ssl, ref_ssl)
+            assert np.array_equal(sel, ref_sel)
