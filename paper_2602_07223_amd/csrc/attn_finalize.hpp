@@ -441,6 +441,7 @@ __device__ __forceinline__ void score_pages(const FinalizeParams& p, float* smf,
 template <bool SMALL>
 __device__ __forceinline__ void score_pages_planned(const FinalizeParams& p, const ColumnSlots& cs, float* smf, int b, int n) {
   constexpr int kRuns = 5;                    // requests per head in flight, of two heads
+  constexpr int kFewHeads = 3;                // where a head's run is one or two requests: heads in flight
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int Rc = p.Rc, rows = p.Hkv * Rc;
@@ -509,7 +510,11 @@ __device__ __forceinline__ void score_pages_planned(const FinalizeParams& p, con
     for (int q = 0; q < kFinPre; ++q)
       if (4 * q < Rc) pre[SMALL ? q : 0] = *reinterpret_cast<const f32x4*>(pl + 4 * q);
   }
-  if (by_quads) load_quads(wave, 0);
+  // (At most two requests a head, up to 16 rows: three heads at a time, behind the rows.  Two, the first of them ahead, are as many round trips again where
+  //  there are many heads: 64 heads x 12 rows, head dimension 128, 32 sequences of 1000 19.8 / 18.3, 3 of 30000 13.3 / 12.0; x 8 rows, 16 of 3000
+  //  11.1 / 10.6.  More at a time are registers that cost two workgroups on a compute unit.)
+  const bool few = run <= 128;
+  if (by_quads && !few) load_quads(wave, 0);
   for (int first = 0; first < rows; first += 256) row_lse(first + tid);
   __syncthreads();
   auto add = [&](float& sum, float x, float rl) { sum += rl != -INFINITY ? fast_exp2(x - rl) : 0.f; };
@@ -517,7 +522,35 @@ __device__ __forceinline__ void score_pages_planned(const FinalizeParams& p, con
   if (by_quads) {
     const float rcp_q4 = __builtin_amdgcn_rcpf(static_cast<float>(q4));
     const int pitch = q4 | 1;
-    for (int h = wave; h < p.Hkv; h += 8) {
+    if (few) {
+      const int i0 = min(lane, run_live - 1), i1 = min(64 + lane, run_live - 1);
+      const int page0 = static_cast<int>((static_cast<float>(lane) + 0.5f) * rcp_q4), page1 = static_cast<int>((static_cast<float>(64 + lane) + 0.5f) * rcp_q4);
+      const int q0 = lane - page0 * q4, q1 = 64 + lane - page1 * q4;
+      for (int h = wave; h < p.Hkv; h += 4 * kFewHeads) {
+        f32x4 x[kFewHeads][2];
+#pragma unroll
+        for (int k = 0; k < kFewHeads; ++k) {
+          const float* const head = lse_base + static_cast<int64_t>(min(h + 4 * k, p.Hkv - 1)) * p.lse_pages * Rc;
+          x[k][0] = *reinterpret_cast<const f32x4*>(head + 4 * i0);
+          x[k][1] = *reinterpret_cast<const f32x4*>(head + 4 * i1);
+        }
+#pragma unroll
+        for (int k = 0; k < kFewHeads; ++k) {
+          const int hd = h + 4 * k;
+          if (hd >= p.Hkv) break;
+          float s0 = 0.f, s1 = 0.f;
+          const f32x4 r0 = *reinterpret_cast<const f32x4*>(sm_row + hd * Rc + 4 * q0), r1 = *reinterpret_cast<const f32x4*>(sm_row + hd * Rc + 4 * q1);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            add(s0, x[k][0][e], r0[e]);
+            add(s1, x[k][1][e], r1[e]);
+          }
+          if (lane < run) sm_quad[(hd * 32 + page0) * pitch + q0] = s0;
+          if (64 + lane < run) sm_quad[(hd * 32 + page1) * pitch + q1] = s1;
+        }
+      }
+    }
+    for (int h = wave; !few && h < p.Hkv; h += 8) {
       for (int first = 0; first < run; first += 64 * kRuns) {
         if (h != wave || first > 0) load_quads(h, first);
 #pragma unroll

@@ -35,3 +35,25 @@ def test_planned_scores_by_row_count(Hkv, group, queries, D):
         torch.cuda.synchronize()
         U.check_out(f"planned_scores.{collect}", path.out_verify, ref_out, U.vmax_visible(L))
         U.check_scores(f"planned_scores.{collect}", path.block_scores, ref_scores)
+
+
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("Hkv,group", [(64, 1), (40, 2), (29, 3), (16, 4), (17, 5)])
+def test_planned_scores_of_short_runs(Hkv, group, D):
+    """Large enough for pages scored by quads, with 4, 8, 12, 16 and 20 rows a head: runs of half a request to two of them, and just above, in groups of
+    heads that the last one fills or not."""
+    lens = [33 * 16 + 1, 5, 0, 32 * 16, 603, 31 * 16 - 2] * 4
+    assert len(lens) * Hkv * group * 4 * D >= 1024 * 256
+    L = synth.make_random_case(seed=53000 + Hkv + D, batch=len(lens), num_q_heads=Hkv * group, num_kv_heads=Hkv, num_queries=4, seq_lens=lens,
+                               head_dim=D, logit_std=2.0, value_std=1.0)
+    print(f"[case] planned scores, {Hkv} heads, {4 * group} rows, D={D}", flush=True)
+    dl = harness.DeviceLayer.upload(L)
+    ref_out, ref_scores = O.verify_attention(L.q_verify, L.k_cache, L.v_cache, L.block_table, L.seq_lens, L.softmax_scale, vb.COLLECT_ALL_ROWS)
+    path = harness.VegasPath.for_layer(L, budget_tokens=256, collect_rows=vb.COLLECT_ALL_ROWS)
+    path.workspace.fill_(0xFF)                   # NaN where nothing was written
+    path.out_verify.fill_(float("nan"))
+    path.block_scores.fill_(float("nan"))
+    path.verify(dl)
+    torch.cuda.synchronize()
+    U.check_out(f"planned_runs.{Hkv}", path.out_verify, ref_out, U.vmax_visible(L))
+    U.check_scores(f"planned_runs.{Hkv}", path.block_scores, ref_scores)
