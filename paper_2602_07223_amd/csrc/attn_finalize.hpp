@@ -203,7 +203,7 @@ __global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_S
 constexpr int kFinPlanned = -1;
 constexpr int kFinPlannedSmall = -2;   // the same in a call of few rows: merged a head dim per thread, pages scored row by row
 constexpr int kFinPre = 8;       // page log-sum-exps a score thread keeps in registers: 4 * kFinPre rows
-constexpr int kFinUnits = 6, kFinWideUnits = 10;   // (row, part of its chunks) pairs a score thread has in flight (finalize_is_wide)
+constexpr int kFinRounds = 3, kFinWideRounds = 5;   // rounds of 64 rows whose pairs a wave of a score workgroup has in flight (finalize_is_wide)
 
 // Merge under balanced chunking: 1024 / D consecutive rows of the Hkv R rows per workgroup, a thread has four head dims of
 // one, and asks for the slots of its sequence (few as a rule, and known by now: the plan had to be read first) four or eight at a
@@ -602,7 +602,7 @@ __device__ __forceinline__ void score_pages_planned(const FinalizeParams& p, con
 // METRIC 1 (the paper's logit metric, token granularity) replaces the page-score role by workgroups
 // [nA, nA + nC) that add the H_kv per-head token sums of 1024 tokens each: score[b][i] = tok_norm *
 // sum_h partial[b][h][i] for prefix tokens i < n_b - G (Sec. 3.3, last paragraph), 0 elsewhere.
-template <int MAXS, int METRIC = 0, int UNITS = kFinUnits>
+template <int MAXS, int METRIC = 0, int ROUNDS = kFinRounds>
 __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizeParams p) {
   extern __shared__ __attribute__((aligned(16))) float smf[];              // role A (general path): [256 / D][D] weights + [256 / D][4]; role B: [Hkv*R] + [8][32] + [Hkv*R][8] pairs
   constexpr bool kPlanned = MAXS < 0;
@@ -754,11 +754,11 @@ __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizePara
 
   // ---- role B: 32 pages; thread = (page, head slot)
   if constexpr (MAXS > 0) {
-    score_pages<MAXS, UNITS / 2, false>(p, smf, b);
+    score_pages<MAXS, ROUNDS, false>(p, smf, b);
   } else if constexpr (kPlanned) {
     score_pages_planned<MAXS == kFinPlannedSmall>(p, cs, smf, b, plan_n);
   } else {
-    score_pages<32, UNITS / 2, true>(p, smf, b);
+    score_pages<32, ROUNDS, true>(p, smf, b);
   }
 }
 

@@ -260,15 +260,16 @@ inline bool planned_merge_is_small(int batch, int rows, int head_dim) {
   return static_cast<int64_t>(batch) * rows * head_dim < 1024 * 256;
 }
 
-// Merge and page scores of chunks that the host cuts (one sequence, more than 64, or a caller's chunk length): does a score workgroup
-// keep the (max, sum) pairs of ten units per thread in flight instead of six?  Six hold 192 rows; more are a second round trip, unless
-// ten hold them; beyond 320 rows it is two or more with either, and at 193 to 208 half of what ten ask for is nothing.  us per
-// verification, six / ten, one sequence, by collected rows: 196 32.9 / 33.5 (32768 tokens), 224 13.4 / 13.1, 256 18.8 / 18.2 and (32768)
-// 37.6 / 36.9, 308 21.7 / 21.3, 320 16.1 / 15.8 and (32768) 39.0 / 38.5, at head dimension 64 27.8 / 27.1; 512 20.5 / 20.9, 768 21.1 / 22.2.
-// Several sequences, the merge alone: 65 of 500..2000, 256 rows 27.6 / 27.2, 320 rows 32.6 / 31.9; 65 of 4000..9000, 256 35.3 / 34.6; 96 of
-// 500..3000, 320, head dimension 64 29.9 / 29.3; 128 of 300..1500, 224 40.7 / 40.1; 200 of 300..1000, 256 58.5 / 57.6; in chunks of the caller's
-// 4 of 2000..8000 (512), 256 8.8 / 8.4; 16 of 2000..8000 (1024), 320 16.1 / 15.4; 2 of 8000..16000 (256), 320, head dimension 64 12.6 / 11.6.
-inline bool finalize_is_wide(int rows) { return rows > 208 && rows <= 320; }
+// Merge and page scores of chunks that the host cuts (one sequence, more than 64, or a caller's chunk length): does a wave of a score
+// workgroup have the (max, sum) pairs of five rounds of 64 rows in flight instead of three?  Three hold 192 rows; more are a second
+// round trip, unless five hold them.  They are registers, which the merge workgroups of the same launch have as well: where a batch fills
+// the chip that costs more.  us for merge and scores, captured, three / five, head dimension 128, 32 chunks or fewer: one sequence, 192 rows 4.3 / 4.7
+// (4096 tokens), 196 7.2 / 7.1, 208 5.0 / 4.9, 256 5.4 / 5.2, 320 5.5 / 5.3, 384 5.6 / 6.5, 512 7.1 / 7.5; two, 256 5.0 / 4.8; four, 208 4.6 / 4.5, 320
+// 5.5 / 5.4, in chunks of 512 5.4 / 5.1; eight, 224 5.4 / 5.1, 256 5.8 / 6.0, 320 6.3 / 6.6; 16, 256 7.5 / 7.7; 32 10.8 / 11.3; 65, 196 19.5 / 20.4, 320
+// 22.1 / 23.4; 128, 256 31.3 / 33.5; but in 17 to 32 chunks, a round trip of twice as many requests, 65, 256 49.5 / 47.7, 320 62.5 / 61.0, 280 at head
+// dimension 64 34.3 / 33.2.  96 chunks, one, 256 10.1 / 10.1, 320 10.5 / 10.6; 33 to 64 have three in any case (five are more registers than
+// there are): 224 rows, 48 7.3, 64 7.2.
+inline bool finalize_is_wide(int rows, int batch, int chunks) { return rows > 192 && rows <= 320 && chunks <= 32 && (batch <= 4 || chunks > 16); }
 
 // Workgroups go round the 8 XCDs, on each round its 4 shader engines, so every 32nd starts on the same engine: of the
 // consecutive ones of a head, whose grid has `per_slot` workgroups (KV heads x row blocks) between them, so many start on as

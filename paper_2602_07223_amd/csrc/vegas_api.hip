@@ -574,8 +574,7 @@ int for_each_lds_kernel(F f) {
   per_dim(std::integral_constant<int, 64>{});
   one(verify_finalize_kernel<16, 0>); one(verify_finalize_kernel<32, 0>);
   one(verify_finalize_kernel<64, 0>); one(verify_finalize_kernel<0, 0>);
-  one(verify_finalize_kernel<16, 0, kFinWideUnits>); one(verify_finalize_kernel<32, 0, kFinWideUnits>);
-  one(verify_finalize_kernel<0, 0, kFinWideUnits>);
+  one(verify_finalize_kernel<16, 0, kFinWideRounds>); one(verify_finalize_kernel<32, 0, kFinWideRounds>);
   one(verify_finalize_kernel<16, 1>); one(verify_finalize_kernel<32, 1>);
   one(verify_finalize_kernel<64, 1>); one(verify_finalize_kernel<0, 1>);
   one(verify_finalize_kernel<kFinPlanned, 0>); one(verify_finalize_kernel<kFinPlanned, 1>);
@@ -709,11 +708,9 @@ static int verify_impl(const vegas_desc* desc, const void* q, const void* k_cach
   } else {
     if (pl.balanced && small) rc = launch_finalize(verify_finalize_kernel<kFinPlannedSmall>);
     else if (pl.balanced) rc = launch_finalize(verify_finalize_kernel<kFinPlanned>);
-    else if (finalize_is_wide(sp.Hkv * pl.Rc)) {
-      if (pl.nsplit <= 16) rc = launch_finalize(verify_finalize_kernel<16, 0, kFinWideUnits>);
-      else if (pl.nsplit <= 32) rc = launch_finalize(verify_finalize_kernel<32, 0, kFinWideUnits>);
-      else if (pl.nsplit <= 64) rc = launch_finalize(verify_finalize_kernel<64>);       // (ten units of 16 chunks are more registers than there are)
-      else rc = launch_finalize(verify_finalize_kernel<0, 0, kFinWideUnits>);
+    else if (finalize_is_wide(sp.Hkv * pl.Rc, desc->batch, pl.nsplit)) {
+      if (pl.nsplit <= 16) rc = launch_finalize(verify_finalize_kernel<16, 0, kFinWideRounds>);
+      else rc = launch_finalize(verify_finalize_kernel<32, 0, kFinWideRounds>);
     } else if (pl.nsplit <= 16) rc = launch_finalize(verify_finalize_kernel<16>);
     else if (pl.nsplit <= 32) rc = launch_finalize(verify_finalize_kernel<32>);
     else if (pl.nsplit <= 64) rc = launch_finalize(verify_finalize_kernel<64>);

@@ -1,5 +1,5 @@
-"""Page scores of calls whose score workgroups keep ten units of (max, sum) pairs per thread in flight (finalize_is_wide: 209 to
-320 collected rows, chunks that the host cuts), at both ends of that range and beyond them, for up to 16, 32, 64 and more chunks, for
+"""Page scores around what finalize_is_wide decides (five rounds of (max, sum) pairs in flight instead of three: up to 320 collected
+rows in up to 32 chunks that the host cuts, four sequences or more than 16 chunks), below and beyond that many rows, for up to 16, 32, 64 and more chunks, for
 one sequence, more than a plan takes (64) and several in chunks of the caller's, against the oracle."""
 import pytest
 import torch

@@ -353,3 +353,21 @@ def test_parts_of_a_column_meet_on_one_xcd(tmp_path):
                         place.setdefault(x + width * z, []).append((x + width * (y + parts * z)) % 8)
         assert sorted(place) == list(range(columns)), (columns, heads)
         assert all(len(p) == parts and len(set(p)) == 1 for p in place.values()), (columns, heads, width)
+
+
+WIDE = r'''
+#include <cstdio>
+#include "plan_rules.hpp"
+int main() {                       // lines of: collected rows, sequences, chunks
+  int rows, batch, chunks;
+  while (std::scanf("%d %d %d", &rows, &batch, &chunks) == 3) std::printf("%d\n", vegas::finalize_is_wide(rows, batch, chunks) ? 1 : 0);
+}
+'''
+
+
+def test_score_workgroups_are_wide_where_that_is_faster(tmp_path):
+    """(collected rows, sequences, chunks): five rounds of pairs in flight measured faster than three, or not."""
+    measured = [((192, 1, 32), 0), ((196, 1, 32), 1), ((208, 1, 12), 1), ((320, 1, 16), 1), ((384, 1, 32), 0), ((256, 1, 96), 0), ((224, 1, 48), 0),
+                ((256, 2, 16), 1), ((320, 4, 16), 1), ((256, 8, 4), 0), ((320, 8, 4), 0), ((256, 16, 16), 0), ((256, 65, 2), 0), ((256, 65, 32), 1), ((280, 65, 17), 1), ((320, 128, 8), 0)]
+    out = run_host_program(tmp_path, WIDE, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
+    assert [int(x) for x in out] == [w for _, w in measured]
