@@ -181,14 +181,14 @@ inline int unplanned_pair_chunk(int rows, int max_len) {
 // Units of streaming that beginning one more piece costs a compute unit: 0, 1, 2, 3 of them, verification with collection, us:
 // 16 sequences of 4000..16000 tokens, 20 rows 132 / 124 / 131 / 123; 8 of 1001..20011 75.4 / 81.5 / 70.6 / 70.3.
 constexpr uint32_t kShareCost = 3;
-// Units that cutting a batch into shares has to win at least (wants_shares), with 32-row and with 64-row workgroups.  Not where two
+// Units that cutting a batch into shares has to win at least (least_shared_chunk), with 32-row and with 64-row workgroups.  Not where two
 // 64-row workgroups fit a compute unit: two waves of equal chunks all start at once there, and what one leaves idle the others
 // stream with.  Shares instead, head dimension 64, us: token sums, 48 rows, 24 sequences of 4000..40000 tokens 286 (equal chunks
 // 273), 16 190 (183), 31 of 2000..20000 191 (185); 32 rows 28 of 4000..40000 308 (299); 12 of 1000..4000 33.0 (33.0); no collection, 64
 // rows, 28 of 4000..40000 275 (270), 12 of 2000..20000 69.3 (70.1).
 constexpr int kShareMargin = 2, kPairShareMargin = 4;
 
-// May the lengths of a batch be such that it is cut into shares (wants_shares), if none is longer than `most` units?  With C the
+// May the lengths of a batch be such that it is cut into shares (least_shared_chunk), if none is longer than `most` units?  With C the
 // longest equal chunk of a plan for J workgroups, chunks of C - 1 take more than J, so that the sequences have at least
 // (J + 1) (C - 1) - batch (C - 2) units, and C is at most ceil(most / (ceil((J + 1) / batch) - 1)); C >= S + margin then asks for
 // C (batch - 1) >= J (margin - 1) - 4 + 5 batch (kShareCost is 3).  Fewer sequences than `batch` ask for a longer C.  (Slots for
@@ -219,7 +219,7 @@ struct BatchPlan {
   int J2 = 0;                  // of two waves of equal chunks (= J where only one is planned for)
   int JS = 0;                  // workgroups launched and partial slots held
   int cap_units = 0;           // longest chunk
-  int share_margin = -1;       // what shares have to win (wants_shares); -1: the batch is not cut into shares
+  int share_margin = -1;       // what shares have to win (least_shared_chunk); -1: the batch is not cut into shares
   bool alone = false;          // a workgroup has a compute unit to itself, whatever LDS it needs
 };
 inline BatchPlan batch_plan(int num_cu, int64_t per_head, int batch, int max_len, int unit, int cap_units, bool pair,

@@ -391,7 +391,7 @@ __host__ __device__ __forceinline__ uint32_t requested_slot(int s, int last) {
 //     with C the smallest chunk length for which sum_b ceil(n_b / C) <= J, sequence b is cut into s_b = ceil(n_b / C) equal
 //     chunks (multiples of `unit` tokens).  J is j1 (one launch wave) or j2 (two waves of half-size chunks, handed out longest
 //     first; wants_second_wave).  Partial slot j = workgroup j, laid out by descending chunk length.
-//   * Shares.  Where the longest equal chunk is well above the mean (wants_shares), the sequences are laid end to end and cut
+//   * Shares.  Where the longest equal chunk is well above the mean (least_shared_chunk), the sequences are laid end to end and cut
 //     every S units, S = 1/J of the whole, whatever sequence that falls into.  A share that holds an end of a sequence is as
 //     many pieces, each a workgroup of its own: whole shares start first, then the others by descending length, so that the
 //     pieces of one share meet on a compute unit again (the shortest first piece ends first and is followed by the longest
@@ -410,8 +410,9 @@ struct BalancedSlot {
   int32_t slot;                 // partial slot of the KV head
   int32_t n;                    // the sequence's length
 };
-// floor and ceil of x / d for 0 <= x < 2^23, 1 <= d < 2^23 (a float reciprocal and one correction step instead of an integer
-// division, which is two dozen instructions)
+// floor and ceil of x / d (a float reciprocal and one correction step either way instead of an integer division, which is two dozen
+// instructions).  The estimate is off by one at most where x and d are below 2^23, or where the quotient is below 2^20 whatever rounds (x, d and the
+// reciprocal are off by 2^-23 or less of themselves, the product by four times that of the quotient); (q + 1) d has to fit 32 bits.
 template <typename Wave>
 __host__ __device__ __forceinline__ uint32_t floor_div_small(uint32_t x, uint32_t d) {
   uint32_t q = static_cast<uint32_t>(static_cast<float>(x) * Wave::rcp(static_cast<float>(d)));
@@ -464,28 +465,25 @@ __host__ __device__ __forceinline__ uint32_t balanced_chunk_units(uint32_t nu, u
 __host__ __device__ __forceinline__ bool wants_second_wave(uint32_t total, uint32_t j1, uint32_t C, uint32_t second_cost) {
   return C > second_cost && 10u * total < 9u * j1 * (C - second_cost);
 }
-// Is a batch cut into shares?  priced: units of all sequences plus kShareCost for every one but the first, lives: sequences, J
-// workgroups, C: longest equal chunk.  us, equal chunks / shares, verification with collection, by C / (priced / J): 20 rows:
+// Is a batch cut into shares?  If it has no more sequences than workgroups and its longest equal chunk has this many units or more: more than
+// a tenth above the mean share, with something for every sequence, and `margin` units above it.  priced: units of all sequences plus kShareCost
+// for every one but the first, lives: sequences, J workgroups, S = priced / J rounded up.  The longest equal chunk has that many if one unit less
+// does not fit, so a batch that is cut into shares needs two trial lengths and no search, which takes eight as a rule, each a division and a sum
+// over the wave.
+// us, equal chunks / shares, verification with collection, by C / (priced / J), C the longest equal chunk: 20 rows:
 // 8 of 1001..20011 tokens, 25 / 22.4: 71.4 / 68.5; 16 of 4000..16000, 54 / 41: 131 / 117; 32 of 300..1500, 12 / 10.5: 38.5 /
 // 39.3; without collection 34.2 / 39.4; 4 of 4096..32768, 21 / 19.6: 63.5 / 71.5.  40 rows: 12 of 2000..20000, 41 / 34.3: 120.7 /
 // 114.6; 24 of 5000, 40 / 32.2: 107 / 110, at head dimension 64 78.6 / 74.2; 35 rows, 4 heads (J = 64): 48 of 300..3000,
-// 17 / 12.2: 64.8 / 59.8; 32 of 2000..8000, 27 / 21.5: 95.6 / 91.2.  margin: units that have to be won at least, 2 (2 of
+// 17 / 12.2: 64.8 / 59.8; 32 of 2000..8000, 27 / 21.5: 95.6 / 91.2.  margin: 2 (2 of
 // 3000..30000, 40 rows, head dimension 64, 4 / 3.6, no collection: 21 / 24.8), 4 with 64-row workgroups, which take longer to
 // begin and to end (7 of 15501, 48 rows and token sums, 31 / 27.3: 215.9 / 218.9 for the iteration).
-__host__ __device__ __forceinline__ bool wants_shares(uint32_t priced, uint32_t lives, uint32_t J, uint32_t C, uint32_t margin) {
-  return lives <= J && 10u * J * C > 11u * priced + 8u * lives && C >= (priced + J - 1u) / J + margin;
-}
-
-// The smallest C for which it is, given no more sequences than workgroups: C is at least that if one unit less does not fit, so a batch that
-// is cut into shares needs two trial lengths and no search, which takes eight as a rule, each a division and a sum over the wave.  (11
-// priced + 8 lives is below 2^27 and the quotient below 2^18: the division holds.)
 template <typename Wave>
 __host__ __device__ __forceinline__ uint32_t least_shared_chunk(uint32_t priced, uint32_t lives, uint32_t J, uint32_t S, uint32_t margin) {
-  const uint32_t more = floor_div_small<Wave>(11u * priced + 8u * lives, 10u * J) + 1u;
+  const uint32_t more = floor_div_small<Wave>(11u * priced + 8u * lives, 10u * J) + 1u;      // (its least: 10 J C > 11 priced + 8 lives)
   return more > S + margin ? more : S + margin;
 }
 
-// slots: workgroups there are; share_margin: for wants_shares, or -1 for no shares; second_cost: for wants_second_wave.
+// slots: workgroups there are; share_margin: for least_shared_chunk, or -1 for no shares; second_cost: for wants_second_wave.
 template <typename Wave = GpuWave>
 __host__ __device__ __forceinline__ BalancedSlot balanced_slot(const int32_t* lens, int B, int max_tokens, int j1, int j2,
                                                                int share_group, int slots, int share_margin, int second_cost,

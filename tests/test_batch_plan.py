@@ -200,7 +200,7 @@ def check(call, d):
 
 
 def wanted(c, d):
-    """Would the lengths be cut into shares (wants_shares), had the call the slots?"""
+    """Would the lengths be cut into shares (by the definition that least_shared_chunk turns round), had the call the slots?"""
     nu = [-(-n // UNIT) for n in c[5]]
     live, J = sum(1 for x in nu if x), d["J"]
     tile_rows = c[2] + (2 if c[3] == 2 else 0)

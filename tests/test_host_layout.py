@@ -250,23 +250,32 @@ def test_wide_rows_as_siblings_where_that_is_faster(tmp_path):
 SHARES = r'''
 #include <cstdio>
 #include "vegas_common.hpp"
-int main() {                       // lines of: units of all sequences with what further pieces cost, sequences, workgroups, longest equal chunk, margin
-  unsigned priced, lives, J, C, margin;
-  while (std::scanf("%u %u %u %u %u", &priced, &lives, &J, &C, &margin) == 5)
-    std::printf("%d\n", vegas::wants_shares(priced, lives, J, C, margin) ? 1 : 0);
+struct Host { static float rcp(float x) { return 1.f / x; } };
+int main() {                       // lines of: units of all sequences with what further pieces cost, sequences, workgroups, margin
+  unsigned priced, lives, J, margin;
+  while (std::scanf("%u %u %u %u", &priced, &lives, &J, &margin) == 4)
+    std::printf("%u\n", vegas::least_shared_chunk<Host>(priced, lives, J, (priced + J - 1u) / J, margin));
 }
 '''
 
 
 def test_batches_are_cut_into_shares_where_that_is_faster(tmp_path):
     """(units of all sequences + 3 for every one but the first, sequences, workgroups, longest equal chunk, margin: 2, or 4 of
-    64-row workgroups): shares measured faster, or not; never with more sequences than workgroups."""
+    64-row workgroups): shares measured faster, or not; and the shortest such chunk by its definition, for batches up to the longest there are."""
     measured = [((718, 8, 32, 25, 2), 1), ((1312, 16, 32, 54, 2), 1), ((1099, 12, 32, 41, 4), 1), ((2110, 24, 32, 105, 4), 1),
                 ((781, 48, 64, 17, 4), 1), ((1375, 32, 64, 27, 4), 1), ((336, 32, 32, 12, 2), 0), ((627, 4, 32, 21, 2), 0),
                 ((145, 16, 32, 4, 2), 0), ((105, 8, 32, 3, 2), 0), ((230, 2, 64, 4, 4), 0), ((872, 7, 32, 31, 4), 0),
                 ((778, 48, 32, 23, 2), 0), ((778, 48, 32, 500, 2), 0)]
-    out = run_host_program(tmp_path, SHARES, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
-    assert [int(x) for x in out] == [s for _, s in measured]
+    rng = np.random.default_rng(5)
+    drawn = [(int(np.exp(rng.uniform(0, np.log((1 << 23) + 189)))), int(rng.integers(1, 65)), int(rng.integers(1, 257)), int(rng.choice([2, 4]))) for _ in range(4000)]
+    drawn += [((1 << 23) + 189, 64, J, 2) for J in range(1, 257)] + [(10 * J * c // 11 + k, 1, J, 2) for J in (1, 7, 32, 256) for c in (11, 1000, 30000) for k in (-1, 0, 1)]
+    out = [int(x) for x in run_host_program(tmp_path, SHARES, "\n".join(" ".join(map(str, c)) for c in [m[:3] + m[4:] for m, _ in measured] + drawn)).split()]
+    for ((_, lives, J, C, _), shares), least in zip(measured, out):
+        assert (lives <= J and C >= least) == shares, (C, least)
+    for (priced, lives, J, margin), least in zip(drawn, out[len(measured):], strict=True):
+        def holds(C):
+            return 10 * J * C > 11 * priced + 8 * lives and C >= -(-priced // J) + margin
+        assert holds(least) and not holds(least - 1), (priced, lives, J, margin, least)
 
 
 ALONE = r'''
