@@ -526,7 +526,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
     }
 
     const bool tail = (tok0 + kTile > n) || (CAUSAL && (tok0 + kTile - 1 > n - p.G)) ||
-                      (LOCAL && (tok0 < n - p.window || tok0 + kTile > c1));   // tiles the largest lower bound cuts into
+                      (LOCAL && tok0 < n - p.window);      // tiles the largest lower bound cuts into
     bf16x8 pb[NB][2];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
@@ -534,7 +534,7 @@ __global__ __launch_bounds__(NW * 64, WPS) void attn_split_kernel(VEGAS_SPLIT_HO
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int tok = tok0 + 8 * (i >> 2) + 4 * half + (i & 3);
-          if (tok > limit[nb] || (LOCAL && (tok <= limit[nb] - p.window || tok >= c1))) st[nb][i] = -INFINITY;
+          if (tok > limit[nb] || (LOCAL && tok <= limit[nb] - p.window)) st[nb][i] = -INFINITY;
         }
       }
       float tmax = st[nb][0];
