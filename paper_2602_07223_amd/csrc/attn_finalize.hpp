@@ -163,6 +163,14 @@ __global__ __launch_bounds__(128) void attn_combine_kernel(const CombineParams p
   *out = float_to_bf16_bits(o);
 }
 
+// Numbers of chunks that the kernel below is built for.  A call takes the first that is not below its own, so it has more slots than the step before.
+constexpr int kSmallMerges[] = {8, 12, 16, 20, 24, 32, 40, 48, 64};
+constexpr int small_merge_below(int maxs) {
+  int below = 0;
+  for (int step : kSmallMerges) below = step < maxs ? step : below;
+  return below;
+}
+
 // (Uniform chunking.  A chunk is live if the sequence reaches it, no count is needed; a row's token comes from one reciprocal, r <
 // 128: integer divisions are two dozen instructions each, in a kernel of one round trip.)
 template <int MAXS, typename... Lengths>
@@ -174,7 +182,7 @@ __global__ __launch_bounds__(128) void attn_combine_small_kernel(VEGAS_COMBINE_S
   int zero = 0;
   asm("" : "+v"(zero));                      // (a vector load, the first to come back: the compiler puts a scalar one last)
   int n = lens[b + zero];
-  RowMerge<MAXS, MAXS <= 8 ? 0 : MAXS <= 24 ? MAXS - 4 : MAXS <= 48 ? MAXS - 8 : 48> rm;       // (launch_combine: the step below MAXS)
+  RowMerge<MAXS, small_merge_below(MAXS)> rm;
   rm.issue(part_ml + row, part_o + row * D, tid, R, nsplit - 1, D);
   if ((r | h | tid) == 0) (lengths.store(b), ...);
   const int t = static_cast<int>((static_cast<float>(r) + 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(g)));

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <iterator>
 #include <map>
 #include <mutex>
 #include <set>
@@ -489,17 +490,14 @@ int launch_combine(const vegas_desc* d, const SplitPlan& pl, const SplitParams& 
   auto small = [&](auto maxs) {
     hipLaunchKernelGGL((attn_combine_small_kernel<decltype(maxs)::value, Lengths...>), grid, dim3(cp.D), 0, st, VEGAS_COMBINE_SMALL_ARGS(cp), lengths...);
   };
+  auto by_steps = [&](auto self, auto at) {
+    constexpr size_t I = decltype(at)::value;
+    if constexpr (I == std::size(kSmallMerges)) any();
+    else if (pl.nsplit <= kSmallMerges[I]) small(std::integral_constant<int, kSmallMerges[I]>{});
+    else self(self, std::integral_constant<size_t, I + 1>{});
+  };
   if (pl.balanced) any();
-  else if (pl.nsplit <= 8) small(std::integral_constant<int, 8>{});
-  else if (pl.nsplit <= 12) small(std::integral_constant<int, 12>{});
-  else if (pl.nsplit <= 16) small(std::integral_constant<int, 16>{});
-  else if (pl.nsplit <= 20) small(std::integral_constant<int, 20>{});
-  else if (pl.nsplit <= 24) small(std::integral_constant<int, 24>{});
-  else if (pl.nsplit <= 32) small(std::integral_constant<int, 32>{});
-  else if (pl.nsplit <= 40) small(std::integral_constant<int, 40>{});
-  else if (pl.nsplit <= 48) small(std::integral_constant<int, 48>{});
-  else if (pl.nsplit <= 64) small(std::integral_constant<int, 64>{});
-  else any();
+  else by_steps(by_steps, std::integral_constant<size_t, 0>{});
   return hipGetLastError() == hipSuccess ? VEGAS_OK : VEGAS_ERR_LAUNCH;
 }
 

@@ -380,3 +380,18 @@ def test_score_workgroups_are_wide_where_that_is_faster(tmp_path):
                 ((256, 2, 16), 1), ((320, 4, 16), 1), ((256, 8, 4), 0), ((320, 8, 4), 0), ((256, 16, 16), 0), ((256, 65, 2), 0), ((256, 65, 32), 1), ((280, 65, 17), 1), ((320, 128, 8), 0)]
     out = run_host_program(tmp_path, WIDE, "\n".join(" ".join(map(str, m)) for m, _ in measured)).split()
     assert [int(x) for x in out] == [w for _, w in measured]
+
+
+STEPS = r'''
+#include <cstdio>
+#include "attn_finalize.hpp"
+int main() {
+  for (int step : vegas::kSmallMerges) std::printf("%d %d\n", step, vegas::small_merge_below(step));
+}
+'''
+
+
+def test_merges_by_number_of_chunks_share_one_ladder(tmp_path):
+    """What a merge kernel takes for sure is the step below the one it is built for, of the steps that the launch goes through."""
+    steps = [tuple(map(int, line.split())) for line in run_host_program(tmp_path, STEPS).strip().split("\n")]
+    assert [b for _, b in steps] == [0] + [s for s, _ in steps[:-1]] and steps[-1][0] == 64
