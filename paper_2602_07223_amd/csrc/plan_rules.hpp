@@ -103,13 +103,12 @@ constexpr uint32_t round_sequence(int32_t rounds, uint32_t column) { return colu
 // chunks of 128 (8 to 16 workgroups): head dimension 64, 20 rows: 424 7.2 / 6.0, 564 7.6 / 6.5 and 8.4 / 6.9, 704 7.3 / 7.1, 1004 7.6 / 8.0;
 // 4 rows: 564 7.1 / 6.3, 1001 7.2 / 7.8; 128, 20 rows: 424 9.0 / 8.4, 564 9.3 / 9.2, 704 9.0 / 10.4; 4 rows: 420 8.1 / 7.9, 480 7.8 / 8.1.
 // alone: the longest band that is not cut for being longer than a chunk (lone_band_tokens).
-inline bool lone_workgroup_band(int window, int queries, int max_len, int chunk, int alone = 416) {
+inline bool lone_workgroup_band(int window, int queries, int max_len, int chunk, int alone) {
   int64_t seen = static_cast<int64_t>(window) + queries;
   if (seen > max_len) seen = max_len;
   return seen <= alone || seen <= chunk;
 }
 constexpr int lone_band_tokens(int head_dim) { return head_dim == 64 ? 640 : 448; }
-
 
 // Waves of such a workgroup: a wave's second tile is a round trip behind its first, and a band of 128 tokens has five or six.  Eight
 // instead of four where the band can have more than four tiles (98 tokens; fewer lose the 0.2 to 0.3 us by which eight waves' rows are

@@ -14,10 +14,14 @@ pytestmark = pytest.mark.gpu
 LENGTHS = {1: [1031], 2: [9000, 16400], 4: [0, 1, 130, 8301], 33: [7 * i + 1 for i in range(33)]}
 
 
+ROWS = [(32, 8, 5), (16, 2, 5), (8, 8, 1)]
+BANDS = [(1, 93), (1, 94), (1, 444), (1, 636), (2, 129), (2, 256), (2, 444), (2, 643), (4, 93), (4, 94), (4, 225),
+         (4, 500), (4, 8300), (33, 20), (33, 120), (33, 250)]
+
+
 @pytest.mark.parametrize("D", [128, 64])
-@pytest.mark.parametrize("Hq,Hkv,G", [(32, 8, 5), (16, 2, 5), (8, 8, 1)], ids=["20_rows", "40_rows", "1_row"])
-@pytest.mark.parametrize("batch,window", [(1, 93), (1, 94), (1, 444), (1, 636), (2, 129), (2, 256), (2, 444), (2, 643), (4, 93), (4, 94), (4, 225),
-                                          (4, 500), (4, 8300), (33, 20), (33, 120), (33, 250)])
+@pytest.mark.parametrize("Hq,Hkv,G", ROWS, ids=["20_rows", "40_rows", "1_row"])
+@pytest.mark.parametrize("batch,window", BANDS)
 def test_band_by_four_and_by_eight_waves(batch, window, Hq, Hkv, G, D):
     lens = LENGTHS[batch]
     L = synth.make_random_case(seed=8100 + window + Hq + D, batch=batch, num_q_heads=Hq, num_kv_heads=Hkv, num_queries=G, seq_lens=lens,
@@ -25,7 +29,6 @@ def test_band_by_four_and_by_eight_waves(batch, window, Hq, Hkv, G, D):
     print(f"[case] band batch={batch} W={window} Hq={Hq} Hkv={Hkv} G={G} D={D}", flush=True)
     dl = harness.DeviceLayer.upload(L)
     path = harness.VegasPath.for_layer(L, budget_tokens=64, collect_rows=vb.COLLECT_NONE, window=window)
-    assert vb.vegas_debug_verify_waves(path.desc_verify) in (4, 8)
     path.workspace.fill_(0xFF)                    # NaN partials where nothing was written
     path.out_verify.fill_(float("nan"))
     path.verify(dl)
@@ -41,3 +44,15 @@ def test_waves_of_a_band(over, waves):
     args = dict(batch=1, num_q_heads=32, num_kv_heads=8, num_queries=5, max_blocks=512, max_sel_blocks=8, max_seq_len=8192, num_pages=4096,
                 softmax_scale=0.1, collect_rows=vb.COLLECT_NONE)
     assert vb.vegas_debug_verify_waves(vb.make_desc(**{**args, **over})) == waves
+
+
+@pytest.mark.parametrize("Hq,Hkv,G", ROWS, ids=["20_rows", "40_rows", "1_row"])
+@pytest.mark.parametrize("D", [128, 64])
+def test_bands_above_are_taken_by_four_and_by_eight_waves(D, Hq, Hkv, G):
+    seen = {}
+    for batch, window in BANDS:
+        longest = max(LENGTHS[batch])
+        desc = vb.make_desc(batch=batch, num_q_heads=Hq, num_kv_heads=Hkv, num_queries=G, max_blocks=-(-longest // 16), max_sel_blocks=8,
+                            max_seq_len=longest, num_pages=4096, softmax_scale=0.1, collect_rows=vb.COLLECT_NONE, head_dim=D, window=window)
+        seen.setdefault(vb.vegas_debug_verify_waves(desc), []).append((batch, window))
+    assert sorted(seen) == [4, 8] and min(map(len, seen.values())) >= 3, seen

@@ -130,7 +130,7 @@ int main() {                       // lines of: columns, head dimension, window,
   int columns, D, window, longest, chunk;
   while (std::scanf("%d %d %d %d %d", &columns, &D, &window, &longest, &chunk) == 5)
     std::printf("%d %d\n", vegas::lone_workgroup_tokens(columns, 256, D),
-                vegas::lone_workgroup_band(window, 5, longest, chunk) ? 1 : 0);
+                vegas::lone_workgroup_band(window, 5, longest, chunk, vegas::lone_band_tokens(D)) ? 1 : 0);
 }
 '''
 
@@ -145,11 +145,13 @@ def test_rules_for_calls_without_a_merge(tmp_path):
                 (136, 64, 3104, True), (136, 128, 2080, False), (144, 128, 2080, True), (144, 64, 3104, True), (192, 128, 3200, True), (192, 128, 6176, False),
                 (256, 64, 3200, True), (256, 64, 6176, False), (320, 128, 4128, False), (512, 64, 2080, True)]
     every = [(c, D) for D in (128, 64) for c in (1, 8, 24, 71, 72, 95, 96, 127, 128, 135, 136, 143, 144, 191, 192, 256, 1000)]
-    bands = [(384, 4096, 128, True), (512, 4096, 128, False), (512, 4096, 256, False), (1024, 32768, 1024, False),
-             (1024, 14591, 1792, True), (2048, 14591, 1792, False), (4096, 15699, 15744, True),
-             (3223, 400, 128, True), (3223, 637, 128, False), ((1 << 31) - 1, 400, 128, True)]   # a window beyond the context
+    bands = [(128, 384, 4096, 128, True), (128, 512, 4096, 128, False), (128, 512, 4096, 256, False), (128, 1024, 32768, 1024, False),
+             (128, 1024, 14591, 1792, True), (128, 2048, 14591, 1792, False), (128, 4096, 15699, 15744, True), (128, 3223, 400, 128, True),
+             (128, 3223, 637, 128, False), (128, (1 << 31) - 1, 400, 128, True),   # a window beyond the context
+             (128, 443, 4096, 128, True), (128, 444, 4096, 128, False), (64, 444, 4096, 128, True), (64, 635, 4096, 128, True),
+             (64, 636, 4096, 128, False), (64, 636, 4096, 768, True)]              # both sides of the line, which is the head dimension's
     ask = ([(c, D, 1, 1, 1) for c, D, _, _ in measured] + [(c, D, 1, 1, 1) for c, D in every] +
-           [(8, 128, w, n, c) for w, n, c, _ in bands])
+           [(8, D, w, n, c) for D, w, n, c, _ in bands])
     out = [tuple(map(int, line.split()))
            for line in run_host_program(tmp_path, RULES, "\n".join(" ".join(map(str, a)) for a in ask)).strip().split("\n")]
     assert len(out) == len(ask)
@@ -159,8 +161,8 @@ def test_rules_for_calls_without_a_merge(tmp_path):
     for D in (128, 64):
         per = [limits[(c, D)] for c, d in every if d == D]
         assert per == sorted(per) and per[-1] == 3200
-    for (window, longest, chunk, alone), (_, got) in zip(bands, out[-len(bands):]):
-        assert bool(got) == alone, (window, longest, chunk)
+    for (D, window, longest, chunk, alone), (_, got) in zip(bands, out[-len(bands):]):
+        assert bool(got) == alone, (D, window, longest, chunk)
 
 
 @pytest.mark.parametrize("rows,n,chunks", [(40, 8192, 1), (40, 8193, 2), (64, 16384, 2), (80, 4096, 1), (80, 65536, 16), (128, 16384, 4),
