@@ -16,7 +16,7 @@ LENGTHS = {1: [1031], 2: [9000, 16400], 4: [0, 1, 130, 8301], 33: [7 * i + 1 for
 
 ROWS = [(32, 8, 5), (16, 2, 5), (8, 8, 1)]
 BANDS = [(1, 93), (1, 94), (1, 444), (1, 636), (2, 129), (2, 256), (2, 444), (2, 643), (4, 93), (4, 94), (4, 225),
-         (4, 500), (4, 8300), (33, 20), (33, 120), (33, 250)]
+         (4, 500), (4, 8300), (33, 20), (33, 120), (33, 250), (1, 137), (4, 130)]
 
 
 @pytest.mark.parametrize("D", [128, 64])
