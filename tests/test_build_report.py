@@ -27,8 +27,10 @@ def test_no_kernel_spills_registers(usage):
 
 
 def test_streaming_kernels_fit_two_waves_per_simd(usage):
-    streaming = {k: v for k, v in usage.items() if "attn_split_kernel" in k or "attn_pair_kernel" in k or "attn_draft16_kernel" in k}
+    streaming = {k: v for k, v in usage.items() if "attn_split_kernel" in k or "attn_pair_kernel" in k or "attn_draft16" in k}
     assert len(streaming) >= 32                      # every instantiation the launch code can pick is in the report
+    # (workgroups of a part of V: three splits of five page sizes, and two of them through rings)
+    assert len([k for k in streaming if "attn_draft16_parts_kernel" in k]) == 3 * 5 + 2, sorted(streaming)
     for name, v in streaming.items():
         assert v["vgprs"] + v.get("agprs", 0) <= 256, (name, v)
         assert v["occupancy"] >= 2, (name, v)
@@ -55,28 +57,32 @@ def test_m0_belongs_to_the_loads_into_lds(report):
     assert foreign_m0_lines(planted)[1]
 
 
+WHOLE = r"^_ZN5vegas19attn_draft16_kernelILi(\d+)E()Li([0-3])ELb0ELb0EJEEE\w*:(.*?)^\.Lfunc_end"
+PARTS = r"^_ZN5vegas25attn_draft16_parts_kernelILi(\d+)ELi(\d+)ELi([0-3])ELb0EEE\w*:(.*?)^\.Lfunc_end"
+
+
+def small_page_kernels(asm: str):
+    """Code of the draft kernels of pages of 1, 2, 4 or 8 tokens that do not choose by length, by head dimension, head dims of V (those of
+    workgroups of a part of V) and log2 of the page size."""
+    return {(int(D), int(DV or D), int(page)): body
+            for form in (WHOLE, PARTS) for D, DV, page, body in re.findall(form, asm, flags=re.M | re.S)}
+
+
 def drained_waits(asm: str):
-    """Waits for all of a wave's loads, per draft kernel of pages of 1, 2, 4 or 8 tokens that does not choose by length (template
-    arguments head dimension, log2 of the page size)."""
-    out = {}
-    for D, page, body in re.findall(r"^_ZN5vegas19attn_draft16_kernelILi(\d+)ELi([0-3])ELb0ELb0EJEEE\w*:(.*?)^\.Lfunc_end", asm, flags=re.M | re.S):
-        out[int(D), int(page)] = len(re.findall(r"s_waitcnt vmcnt\(0\)", body))
-    return out
+    """Waits for all of a wave's loads, per kernel of small_page_kernels."""
+    return {k: len(re.findall(r"s_waitcnt vmcnt\(0\)", body)) for k, body in small_page_kernels(asm).items()}
 
 
 def test_small_page_draft_kernels_keep_their_prefetch(report):
     """The streaming loops request a tile ahead and wait for the tile at hand only.  Five or six waits for everything are at the
-    kernel's ends and in the last tiles; one or two more are in the loop, where they cost a call of several tiles per wave 6 to 10 %."""
+    kernel's ends and in the last tiles (a part of V: six); one or two more are in the loop, where they cost a call of several tiles per wave 6 to 10 %."""
     waits = drained_waits(report[1])
-    assert len(waits) == 8 and max(waits.values()) <= 6, waits
+    assert len(waits) == 8 + 12 and max(waits.values()) <= 6, waits
 
 
 def waits_before_the_stream(asm: str):
-    """Loads left under way by the waits before the first contraction, per kernel of drained_waits."""
-    out = {}
-    for D, page, body in re.findall(r"^_ZN5vegas19attn_draft16_kernelILi(\d+)ELi([0-3])ELb0ELb0EJEEE\w*:(.*?)^\.Lfunc_end", asm, flags=re.M | re.S):
-        out[int(D), int(page)] = [int(n) for n in re.findall(r"s_waitcnt vmcnt\((\d+)\)", body[:body.index("v_mfma")])]
-    return out
+    """Loads left under way by the waits before the first contraction, per kernel of small_page_kernels."""
+    return {k: [int(n) for n in re.findall(r"s_waitcnt vmcnt\((\d+)\)", body[:body.index("v_mfma")])] for k, body in small_page_kernels(asm).items()}
 
 
 def test_small_page_draft_kernels_start_without_draining(report):
@@ -84,7 +90,7 @@ def test_small_page_draft_kernels_start_without_draining(report):
     wait for everything (the next tile's page ids brought into the pool at once, stores of an empty sequence's rows that may be under
     way as far as the compiler knows) cost a call of one tile per wave 0.2 to 0.3 us."""
     waits = waits_before_the_stream(report[1])
-    assert len(waits) == 8 and all(0 not in w for w in waits.values()), waits
+    assert len(waits) == 8 + 12 and all(0 not in w for w in waits.values()), waits
 
 
 def test_m0_belongs_to_the_loads_into_lds_of_draft_parts(report):
