@@ -416,7 +416,8 @@ __device__ __forceinline__ void draft16(SplitParams& p, const Step&... step) {
       //  order of instructions under the other: 64 x 1246 12.36 / 12.68, 32 x 2427 12.42 / 12.78.)
       issue_k(0, kr);
       // (A part of V is few loads, which the compiler moves between K's halves; the stream's waits for K's second half, which have to hold for
-      //  this order too, then waited for the V of every tile: us without / with this, two parts, 128 columns, 120 tokens: one-token pages 4.03 / 3.86, 8-token ones 4.09 / 3.88.)
+      //  this order too, then waited for the V of every tile: us without / with this, two parts, 128 columns, 120 tokens: one-token pages
+      //  4.03 / 3.86, 8-token ones 4.09 / 3.88.)
       if constexpr (D == 128 && DV < D) __builtin_amdgcn_sched_barrier(0);
       issue_v(0, va);
     }

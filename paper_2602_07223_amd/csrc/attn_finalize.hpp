@@ -612,7 +612,9 @@ __device__ __forceinline__ void score_pages_planned(const FinalizeParams& p, con
 // sum_h partial[b][h][i] for prefix tokens i < n_b - G (Sec. 3.3, last paragraph), 0 elsewhere.
 template <int MAXS, int METRIC = 0, int ROUNDS = kFinRounds>
 __global__ __launch_bounds__(256) void verify_finalize_kernel(const FinalizeParams p) {
-  extern __shared__ __attribute__((aligned(16))) float smf[];              // role A (general path): [256 / D][D] weights + [256 / D][4]; role B: [Hkv*R] + [8][32] + [Hkv*R][8] pairs
+  // Merging, general path: [256 / D][D] weights + [256 / D][4].  Page scores, of rows = Hkv * Rc: score_pages 8 x rows + rows + [8][32] floats,
+  // score_pages_planned rows + [8][32] + [Hkv * 32][pitch], pitch at most 3/8 Rc (Rc of 8): 12 x rows.
+  extern __shared__ __attribute__((aligned(16))) float smf[];
   constexpr bool kPlanned = MAXS < 0;
   const int b = blockIdx.y;
   const int tid = threadIdx.x;

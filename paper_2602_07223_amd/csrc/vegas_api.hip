@@ -680,7 +680,9 @@ static int verify_impl(const vegas_desc* desc, const void* q, const void* k_cach
   // (max, sum) pairs; giving a workgroup more pages to amortise that was measured slower.
   const size_t hr = static_cast<size_t>(sp.Hkv) * pl.R;
   int nB = (desc->max_blocks + 31) / 32;
-  size_t shm = (hr + 256 + 16 * hr) * sizeof(float);   // role B needs the most; role A fits inside
+  // An upper bound of what the roles lay out (at most 13 x rows + 262 floats of collected rows, up to hr; verify_finalize_kernel), by which a
+  // call of more than 2394 rows is refused.
+  size_t shm = (hr + 256 + 16 * hr) * sizeof(float);
   fp.nC = 0;
   fp.tok_norm = 0.f;
   if (logits) {                                        // token sums instead of page scores: 1024 tokens per workgroup
