@@ -594,9 +594,10 @@ __device__ __forceinline__ uint32_t take_by_digits(const float (&x)[4 * ROWS], i
 // 10.1, a far low one 20.6 / 16.9 / 9.8, rising with the position 20.6 / 17.2 / 11.3, half 0 19.8 / 10.2.  Where bins do not tell the scores
 // apart, digits as they were / now, 4096, 8192, 32768: four values 6.2 / 6.5, 7.9 / 8.0, 19.9 / 19.8; fifteen in sixteen 0 4.8 / 5.1, 6.5 / 6.4, 19.3 /
 // 19.2; all equal 3.5 / 3.8, 4.5 / 4.6, 11.1 / 11.0 (seen in the sample: its request and test are the difference); one at 3e38 5.2 / 5.7,
-// 6.8 / 7.0, 16.9 / 14.0; exp of five times a normal one 5.2 / 5.9, 6.5 / 6.2, 15.7 / 14.3 (seen behind the bounds); over a quarter of the tokens
-// taken, which has digits alone, 5.3 / 5.4, 6.8 / 6.7, 17.0 / 15.7.  What every wave does for one of its scores costs 7 ns: an instruction of
-// 16 waves is 16 cycles of a SIMD.  In an iteration of 32768 tokens, whose instructions are cold, 80.3 -> 71.1.
+// 6.8 / 7.0, 16.9 / 14.0; exp of a normal one 4.3 / 4.8, 6.4 / 5.5, 15.8 / 11.2, of five times one 5.2 / 5.9, 6.5 / 6.2, 15.7 / 14.3 (seen
+// behind the bounds); over a quarter of the tokens taken, which has digits alone, 5.3 / 5.4, 6.8 / 6.7, 17.0 / 15.7.  What every wave does for
+// one of its scores costs 7 ns: an instruction of 16 waves is 16 cycles of a SIMD.  In an iteration of 32768 tokens, whose instructions are
+// cold, 80.3 -> 71.1.
 template <int ROWS>
 __global__ __launch_bounds__(kTokThreads) void token_select_one_kernel(const TokenSelectParams p) {
   static_assert(kTokThreads == kSelectThreads, "find_last_key");
